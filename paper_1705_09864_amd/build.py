@@ -1,4 +1,5 @@
-"""Build libbmx.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Build libbmx.so (hand-written HIP for gfx950) in-tree with hipcc, and the native module of the
+Python binding with the host compiler."""
 import os
 import subprocess
 import sys
@@ -9,6 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbmx.so")
 SOURCES = ["bmx_api.hip", "pack.hip", "gemm.hip", "gemm_mfma.hip", "gemm_fp4.hip", "conv.hip", "conv_mfma.hip", "fc_small.hip", "probe.hip"]
+HOST_BINDING = os.path.join(HERE, "_bmx_host.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed-fp32 VALU forms are kept out of generated code on the test machines
@@ -83,6 +85,22 @@ def check_codegen():
                                                     int(m.group(1)) * int(m.group(2))))
 
 
+def build_host_binding():
+    """Compile the native module of the Python calls (host code against PyTorch's C++ API; the
+    library's entry points are found at import, in the libbmx.so that binding.py has loaded)."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-isystem", os.path.join(t, "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "host_binding.cpp"), "-o", HOST_BINDING,
+           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10", "-Wl,-z,now"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for host_binding.cpp:\n%s" % r.stdout)
+
+
 def build(force=True, verbose=False):
     """Compile every translation unit, verify the hand-placed scalar loads in the generated
     code, and link the shared library.  Returns its path."""
@@ -113,6 +131,8 @@ def build(force=True, verbose=False):
     # instead of the first call)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-z,defs"] + objs + ["-o", LIB]
     subprocess.check_call(cmd)
+    if force or _stale(HOST_BINDING, [os.path.join(CSRC, "host_binding.cpp")] + headers):
+        build_host_binding()
     return LIB
 
 

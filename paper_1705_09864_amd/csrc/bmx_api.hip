@@ -4,8 +4,6 @@
 #include "../../include/bmx.h"
 #include "bmx_internal.h"
 
-#include <cstdarg>
-#include <cstdio>
 #include <mutex>
 
 // Scratch memory of bmx_binary_fc_static, the entry point for callers that cannot allocate: one
@@ -69,13 +67,7 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
 }  // namespace
 
 namespace bmx {
-static thread_local char last_kernel_name[160] = "";
-void note_kernel(const char* fmt, ...) {
-  va_list ap;
-  va_start(ap, fmt);
-  vsnprintf(last_kernel_name, sizeof(last_kernel_name), fmt, ap);
-  va_end(ap);
-}
+thread_local KernelNote last_kernel_note = {};
 extern int conv_filters_per_wave, conv_path;
 extern int gemm_tune_rows, gemm_tune_ksplit, gemm_tune_order;
 }
@@ -109,7 +101,12 @@ int bmx_tune_set(int key, int value) {
 
 int bmx_version(void) { return 200; }
 
-const char* bmx_last_kernel(void) { return bmx::last_kernel_name; }
+const char* bmx_last_kernel(void) {
+  static thread_local char name[160];
+  if (!bmx::last_kernel_note.print) return "";
+  bmx::last_kernel_note.print(name, sizeof(name), bmx::last_kernel_note);
+  return name;
+}
 
 int bmx_probe_valu(int workgroups, int iters, unsigned long long* out3, int* wall_clock_khz, void* stream) {
   if (workgroups <= 0 || iters <= 0 || workgroups > (1 << 20) || iters > (1 << 24)) return BMX_ERR_SHAPE;

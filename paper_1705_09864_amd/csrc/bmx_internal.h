@@ -5,6 +5,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstdio>
+#include <new>
+#include <tuple>
+#include <type_traits>
+
 namespace bmx {
 
 __host__ __device__ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -22,8 +27,26 @@ __device__ static inline uint32_t fast_div(uint32_t n, FastDiv f) {
 __host__ __device__ static inline int64_t words_for(int64_t k) { return (k + 63) / 64; }
 
 // Name (with template arguments and launch shape) of the kernel the calling thread launched
-// last: what bmx_last_kernel() reports, so that measurements label themselves.
-void note_kernel(const char* fmt, ...) __attribute__((format(printf, 1, 2)));
+// last: what bmx_last_kernel() reports, so that measurements label themselves.  A launch only
+// puts the format and its arguments by (numbers and string literals); the text is made when it is
+// asked for (formatting it took 0.4 us of a launch's 2.7 us of host time).
+struct KernelNote {
+  int (*print)(char* to, size_t size, const KernelNote& note);
+  const char* fmt;
+  alignas(8) unsigned char args[96];
+};
+extern thread_local KernelNote last_kernel_note;
+template <class... Args>
+static inline void note_kernel(const char* fmt, Args... args) {
+  using Tuple = std::tuple<Args...>;
+  static_assert(sizeof(Tuple) <= sizeof(KernelNote::args) && std::is_trivially_destructible<Tuple>::value, "");
+  new (last_kernel_note.args) Tuple(args...);
+  last_kernel_note.fmt = fmt;
+  last_kernel_note.print = [](char* to, size_t size, const KernelNote& note) {
+    return std::apply([&](Args... a) { return snprintf(to, size, note.fmt, a...); },
+                      *reinterpret_cast<const Tuple*>(note.args));
+  };
+}
 
 // Packed rows that feed the scalar side of the GEMM kernel are zero padded to whole
 // 32-dword chunks, so that every chunk of a row can be fetched with two 64-byte scalar loads.

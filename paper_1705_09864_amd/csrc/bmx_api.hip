@@ -61,6 +61,8 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
   q.wrowsum_off = q.rowsum_off + round256((size_t)M * 4);
   q.tmp_off = q.wrowsum_off + (bits_w == 1 ? 0 : round256((size_t)N * 4));
   q.total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
+  size_t tiles = 0;  // the int8 form's operands, where it is taken
+  if (bmx::quant_i8_takes(M, N, K, bits_a, bits_w, &tiles) && round256(tiles) > q.total) q.total = round256(tiles);
   return q;
 }
 
@@ -514,6 +516,9 @@ int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int6
   if (!workspace || workspace_bytes < q.total) return BMX_ERR_WORKSPACE;
   if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
   hipStream_t s = (hipStream_t)stream;
+  hipError_t i8 = hipSuccess;  // more bits than the FP4 form holds: bytes on the matrix cores
+  if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, s, &i8))
+    return hip_status(i8);
   char* ws = (char*)workspace;
   uint64_t* planes = (uint64_t*)(ws + q.planes_off);
   uint64_t* wb = (uint64_t*)(ws + q.wb_off);

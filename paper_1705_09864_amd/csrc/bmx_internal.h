@@ -179,6 +179,12 @@ hipError_t launch_plane_gemm(const uint32_t* planes_rows, int64_t lda_dw, int bi
                              const int32_t* rowsum, const uint64_t* Wb, int64_t ldb_w, int M, int N,
                              int K, int32_t* S, float* out_f32, int64_t ldo, hipStream_t s);
 
+// gemm_i8.hip: the whole k-bit product (quantise + tile, multiply) with both operands as bytes;
+// false when the problem stays with the bit-plane kernels.  quant_i8_takes: its domain and workspace.
+bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes);
+bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
+                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, hipStream_t s, hipError_t* err);
+
 // The same convolution on the GEMM kernel (filters = A rows streamed through SGPRs, im2col
 // rows gathered per chunk): for K that does not fit the stationary kernel or grids with too
 // few pixel groups for it.

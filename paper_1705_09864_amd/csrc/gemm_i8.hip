@@ -1,0 +1,397 @@
+// k-bit products on the int8 matrix cores (Sec. 2.1, Eq. 1; arbitrary bit widths after DoReFa-Net):
+// S[m][n] = sum_k q[m][k] * v[n][k] with q the level of the activation and v the weight's odd
+// integer (sign for one bit, 2 q_w - L_w above).
+//
+// Taken where an operand has more bits than the FP4 form of gemm_fp4.hip folds into a nibble (more
+// than two for the activations, more than one for the weights).  Walked plane by plane with AND +
+// popcount, such a product costs bits_a * bits_w passes over K on the vector ALU (4 x 4 bits, 500 x
+// 1000 x 2304: 67 us, and a 16 MB array of per-plane results to add up afterwards, 5 us).  As bytes
+// it is one pass on the matrix cores, whatever the bits.
+//
+// Eight-bit levels do not fit a signed byte: q - 128 and q_w - 128 do, and the sums of the operands'
+// rows, counted from the words a lane loads anyway (v_dot4), put the difference right:
+//   S = scale * (sum a' v' + ca * sum_k v') + rs * (sum_k a' + ca * K),  a' = q - ca,
+//   v' = v, scale = 1, rs = 0  (up to 7 weight bits)  or  v' = q_w - 128, scale = 2, rs = 1  (8 bits),
+// in 32-bit wrap-around arithmetic (the result itself fits, the launcher's caller has checked).
+//
+// Layout.  A dot product does not care about the order of k, and both operands are written by
+// quant_tiles_kernel for this kernel alone, so they are stored the way the MFMA wants them: tile
+// (row block of 32, k step of 32) is 1 KiB, lane l of a wave taking bytes [16 l, 16 l + 16): row
+// l % 32, half l / 32 of the step.  Every operand load is one contiguous KiB, no LDS, no
+// transposition.  K is zero padded to whole blocks of 256, rows to whole blocks of 32.
+#include "bmx_internal.h"
+
+namespace bmx {
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+// ---- quantise + tile.  A workgroup turns 32 rows x 256 k of one operand into eight tiles: a wave
+// reads its rows, 1 KiB of each (all loads in flight), a lane quantises its four values into one
+// dword, and the tiles leave through LDS as whole KiB.  Bound by the fp32
+// operand's way in.
+constexpr int kTileRow = 132;  // dwords per half tile in LDS: 128 + 4, so that a row's 16 half tiles start on different banks
+
+struct QuantOperand {
+  const float* x;
+  int64_t ld;
+  int rows;
+  int sign;  // 1-bit weights: the sign; else the byte is mul * q + add - 128 of the level q
+  // q = round(L * clamp((x + c0) * c1)): c0, c1 = 0, 1 for activations, 1, 0.5 for weights in [-1, 1]
+  float c0, c1, L;
+  float mul, add;
+  uint4* tiles;
+};
+
+struct QuantTilesParams {
+  QuantOperand op[2];
+  int K, kblocks;      // blocks of 256
+  FastDiv div_kblocks;
+  int blocks0;         // workgroups of operand 0
+  int vec;             // rows of both operands start 16-byte aligned
+};
+
+constexpr int kTileWaves = 8, kTileRows = 32 / kTileWaves;  // rows of the block per wave
+
+__global__ void __launch_bounds__(64 * kTileWaves)
+quant_tiles_kernel(const QuantTilesParams p) {
+#pragma clang fp contract(off)  // (the rest of the rounded product L * u, not of the exact one, decides a tie)
+  __shared__ uint32_t t[16 * kTileRow];
+  // (all arguments named at the top: fetched in one batch, one trip to memory instead of one per group)
+  asm volatile("" ::"s"(p.blocks0), "s"(p.div_kblocks.mul), "s"(p.op[0].x), "s"(p.op[0].ld), "s"(p.op[0].L), "s"(p.op[0].tiles),
+               "s"(p.op[1].x), "s"(p.op[1].ld), "s"(p.op[1].L), "s"(p.op[1].tiles), "s"(p.K), "s"(p.vec));
+  const bool second = (int)blockIdx.x >= p.blocks0;
+  QuantOperand o = p.op[0];
+  if (second) o = p.op[1];
+  const int b = (int)blockIdx.x - (second ? p.blocks0 : 0);
+  const int rb = (int)fast_div((uint32_t)b, p.div_kblocks), kb = b - rb * p.kblocks;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int k0 = kb * 256 + 4 * lane;
+  float v[kTileRows][4];
+  // (rows past the matrix repeat its last: their results are never stored)
+  const int row0 = rb * 32 + wave * kTileRows;
+  const float* const x = o.x + k0;
+  const int64_t ld = o.ld;
+  const int last = o.rows - 1;
+  if (p.vec && kb * 256 + 256 <= p.K) {  // workgroup-uniform
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j) {
+      const float4 f = *(const float4*)(x + (int64_t)min(row0 + j, last) * ld);
+      v[j][0] = f.x, v[j][1] = f.y, v[j][2] = f.z, v[j][3] = f.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)  // (elements past the row read its last and are masked below)
+        v[j][e] = o.x[(int64_t)min(row0 + j, last) * ld + min(k0 + e, p.K - 1)];
+  }
+  const int left = p.K - k0;  // valid elements of this lane's four
+  const uint32_t mask = left >= 4 ? 0xffffffffu : (left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+  uint32_t* const dst = &t[(lane >> 2) * kTileRow + wave * (4 * kTileRows) + (lane & 3)];
+  if (o.sign) {
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j) {
+      uint32_t d = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d |= (v[j][e] >= 0.0f ? 1u : 255u) << (8 * e);
+      dst[4 * j] = d & mask;
+    }
+  } else {
+    // Rounding half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32: with 0.5 itself the
+    // one value 0.5 - 2^-25 would round up.  The byte is made in fp32 (whole numbers up to 255) with
+    // 128 added, so that it is never negative, and the 128 goes again as the flip of its top bit.
+    const float c0 = o.c0, c1 = o.c1, L = o.L, mul = o.mul, add = o.add;
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j) {
+      uint32_t d = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float u = fminf(fmaxf((v[j][e] + c0) * c1, 0.0f), 1.0f) * L;
+        d = __builtin_amdgcn_cvt_pk_u8_f32(truncf(u + 0x1.fffffep-2f) * mul + add, e, d);
+      }
+      dst[4 * j] = (d ^ 0x80808080u) & mask;
+    }
+  }
+  __syncthreads();
+  // half tile 2 s + h of the block is t[(2 s + h) * kTileRow ...]: row r at dword 4 r
+  uint4* out = o.tiles + (int64_t)b * 512;
+#pragma unroll
+  for (int i = 0; i < 8 / kTileWaves; ++i) {
+    const int c = threadIdx.x + 64 * kTileWaves * i;  // 16-byte piece: half tile c / 32, row c % 32
+    out[c] = *(const uint4*)&t[(c >> 5) * kTileRow + (c & 31) * 4];
+  }
+}
+
+// ---- the product.  TM x TN blocks of 32 x 32 per wave, K split over the S waves of a workgroup
+// (partial tiles added through LDS once) where there are too few tiles to fill the chip.  What
+// bounds it at the sizes of a layer is latency: operand loads of two groups of k steps are in flight
+// while one is multiplied.  Beyond that the L1 path (64 B per clock and CU against 1 KiB per 32-clock
+// MFMA and SIMD) holds it at half the matrix rate.
+struct I8Params {
+  const uint4 *A, *B;  // tiles of the activations and of the weights
+  int M, N, nk;        // nk: k steps of 32
+  int mblocks, nblocks;
+  int tiles_m, tiles, tiles_per_xcd;
+  int S;
+  int ca, scale, rs, Kreal;
+  float denom;
+  int32_t* C_i32;
+  float* C_f32;
+  int64_t ldc;
+};
+
+constexpr int kAhead = 4;  // k steps per group of loads
+
+template <int TM, int TN>
+struct Group {
+  v4i a[kAhead][TM], b[kAhead][TN];
+};
+
+template <int TM, int TN, bool SUMS>
+__global__ void __launch_bounds__(512)
+gemm_i8_kernel(const I8Params p) {
+  extern __shared__ int red[];
+  constexpr int kGroups = TM * TN * 4;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  // workgroup b sits on XCD b % 8: every XCD gets a contiguous run of tiles, rows of C fastest
+  const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
+  if (lin >= p.tiles) return;  // (the whole workgroup)
+  const int tile_n = lin / p.tiles_m, tile_m = lin - tile_n * p.tiles_m;
+  const int S = p.S;
+  const int k_lo = (int)((int64_t)wave * p.nk / S), k_hi = (int)((int64_t)(wave + 1) * p.nk / S);
+
+  const uint4 *arow[TM], *brow[TN];  // (blocks past the matrix repeat its last one)
+#pragma unroll
+  for (int i = 0; i < TM; ++i) arow[i] = p.A + (int64_t)min(tile_m * TM + i, p.mblocks - 1) * p.nk * 64 + lane;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) brow[j] = p.B + (int64_t)min(tile_n * TN + j, p.nblocks - 1) * p.nk * 64 + lane;
+
+  v16i acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+  int sa[TM] = {}, sb[TN] = {};
+
+  auto load = [&](Group<TM, TN>& g, int k) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) {
+      const int kk = min(k + d, k_hi - 1) * 64;  // (a group's steps past the range repeat its last)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) g.a[d][i] = *(const v4i*)(arow[i] + kk);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) g.b[d][j] = *(const v4i*)(brow[j] + kk);
+    }
+  };
+  auto multiply = [&](const Group<TM, TN>& g, int k) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) {
+      if (k + d >= k_hi) break;  // wave-uniform
+      if (SUMS) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sa[i] = __builtin_amdgcn_sdot4(g.a[d][i][e], 0x01010101, sa[i], false);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sb[j] = __builtin_amdgcn_sdot4(g.b[d][j][e], 0x01010101, sb[j], false);
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.a[d][i], g.b[d][j], acc[i][j], 0, 0, 0);
+    }
+  };
+  if (k_lo < k_hi) {
+    Group<TM, TN> g0, g1;
+    load(g0, k_lo);
+    for (int k = k_lo; k < k_hi; k += 2 * kAhead) {
+      if (k + kAhead < k_hi) load(g1, k + kAhead);
+      multiply(g0, k);
+      if (k + 2 * kAhead < k_hi) load(g0, k + 2 * kAhead);
+      multiply(g1, k + kAhead);
+    }
+  }
+  if (SUMS) {  // a lane summed its half of every k step
+#pragma unroll
+    for (int i = 0; i < TM; ++i) sa[i] += __shfl_xor(sa[i], 32);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sb[j] += __shfl_xor(sb[j], 32);
+  }
+
+  // Register v of lane (r, h) in block (i, j) is C[32 i + 8 (v / 4) + 4 h + v % 4][32 j + r];
+  // group g = (i * TN + j) * 4 + v / 4: four rows of one column.
+  auto finish = [&](int g, const int (&d)[4], const int (&ra)[4], int cb) {
+    const int blk = g >> 2, i = blk / TN, j = blk % TN;
+    const int n = (tile_n * TN + j) * 32 + r;
+    if (n >= p.N) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = (tile_m * TM + i) * 32 + 8 * (g & 3) + 4 * h + e;
+      if (m >= p.M) continue;
+      int sv = d[e];
+      if (SUMS)
+        sv = (int)((uint32_t)p.scale * ((uint32_t)d[e] + (uint32_t)p.ca * (uint32_t)cb) +
+                   (uint32_t)p.rs * ((uint32_t)ra[e] + (uint32_t)p.ca * (uint32_t)p.Kreal));
+      const int64_t idx = (int64_t)m * p.ldc + n;
+      if (p.C_i32) __builtin_nontemporal_store(sv, p.C_i32 + idx);
+      if (p.C_f32) __builtin_nontemporal_store((float)sv / p.denom, p.C_f32 + idx);
+    }
+  };
+  if (S == 1) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      const int i = (g >> 2) / TN, j = (g >> 2) % TN, q = g & 3;
+      int d[4], ra[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        d[e] = acc[i][j][4 * q + e];
+        ra[e] = SUMS ? __shfl(sa[i], 8 * q + 4 * h + e) : 0;
+      }
+      finish(g, d, ra, sb[j]);
+    }
+    return;
+  }
+  v4i* part = (v4i*)red;                       // [S][kGroups][64]
+  int* sums = red + S * kGroups * 64 * 4;      // [S][32 (TM + TN)]
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v4i d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = acc[i][j][4 * q + e];
+        part[(wave * kGroups + (i * TN + j) * 4 + q) * 64 + lane] = d;
+      }
+  if (SUMS && h == 0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) sums[wave * 32 * (TM + TN) + 32 * i + r] = sa[i];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sums[wave * 32 * (TM + TN) + 32 * (TM + j) + r] = sb[j];
+  }
+  __syncthreads();
+  for (int g = wave; g < kGroups; g += S) {
+    v4i t[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) t[s] = part[(min(s, S - 1) * kGroups + g) * 64 + lane];
+    int d[4] = {}, ra[4] = {}, cb = 0;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] += s < S ? t[s][e] : 0;
+    if (SUMS) {
+      const int i = (g >> 2) / TN, j = (g >> 2) % TN;
+      for (int s = 0; s < S; ++s) {
+        const int* w = sums + s * 32 * (TM + TN);
+        cb += w[32 * (TM + j) + r];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ra[e] += w[32 * i + 8 * (g & 3) + 4 * h + e];
+      }
+    }
+    finish(g, d, ra, cb);
+  }
+}
+
+template <int TM, int TN, bool SUMS>
+hipError_t launch_i8(const I8Params& p, hipStream_t s) {
+  auto kern = gemm_i8_kernel<TM, TN, SUMS>;
+  const size_t lds = p.S > 1 ? (size_t)p.S * (TM * TN * 4 * 1024 + 128 * (TM + TN)) : 0;
+  if (lds > 64 * 1024) {  // more than the default limit of dynamic LDS: raised once per device
+    static bool raised[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!raised[dev]) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (e != hipSuccess) return e;
+      raised[dev] = true;
+    }
+  }
+  note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
+  return hipGetLastError();
+}
+
+int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * ceil_div(K, 256) * 256; }
+
+}  // namespace
+
+// Workspace of the two tiled operands, and whether the problem is taken: an operand of more bits than
+// the FP4 form holds, and a result that fills a quarter of a 32 x 32 block (below that the padding of
+// the tiles is most of what is moved, and the plane kernels' workspace is smaller).
+bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes) {
+  if (bits_a <= 2 && bits_w == 1) return false;
+  if (M * N < 256) return false;
+  const int64_t a = tile_bytes(M, K), b = tile_bytes(N, K);
+  *bytes = (size_t)(a + b);
+  const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32);
+  return a < ((int64_t)1 << 40) && b < ((int64_t)1 << 40) && tiles < ((int64_t)1 << 30) &&
+         ceil_div(M, 32) * ceil_div(K, 256) + ceil_div(N, 32) * ceil_div(K, 256) < ((int64_t)1 << 30);
+}
+
+bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
+                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, hipStream_t s, hipError_t* err) {
+  size_t need;
+  if (gemm_engine == 1 || !quant_i8_takes(M, N, K, bits_a, bits_w, &need)) return false;
+  QuantTilesParams q;
+  q.K = K;
+  q.kblocks = (int)ceil_div(K, 256);
+  q.div_kblocks = make_fast_div((uint32_t)q.kblocks);
+  const int mblocks = (int)ceil_div(M, 32), nblocks = (int)ceil_div(N, 32);
+  const int La = (1 << bits_a) - 1, Lw = (1 << bits_w) - 1;
+  q.op[0] = {a, lda, M, 0, 0.0f, 1.0f, (float)La, 1.0f, bits_a == 8 ? 0.0f : 128.0f, (uint4*)workspace};
+  q.op[1] = {w, ldw, N, bits_w == 1 ? 1 : 0, 1.0f, 0.5f, (float)Lw, bits_w == 8 ? 1.0f : 2.0f, bits_w == 8 ? 0.0f : 128.0f - (float)Lw,
+             (uint4*)((char*)workspace + tile_bytes(M, K))};
+  q.blocks0 = mblocks * q.kblocks;
+  q.vec = !(lda & 3) && !(ldw & 3) && !((uintptr_t)a & 15) && !((uintptr_t)w & 15);
+  hipLaunchKernelGGL(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
+  *err = hipGetLastError();
+  if (*err != hipSuccess) return true;
+
+  I8Params p;
+  p.A = q.op[0].tiles;
+  p.B = q.op[1].tiles;
+  p.M = M;
+  p.N = N;
+  p.nk = q.kblocks * 8;
+  p.mblocks = mblocks;
+  p.nblocks = nblocks;
+  p.ca = bits_a == 8 ? 128 : 0;
+  p.scale = bits_w == 8 ? 2 : 1;
+  p.rs = bits_w == 8 ? 1 : 0;
+  p.Kreal = K;
+  p.denom = (float)(La * Lw);
+  p.C_i32 = S_out;
+  p.C_f32 = out_f32;
+  p.ldc = ldo;
+  // The most of C per wave that still gives every CU a workgroup (the waves that split K share one):
+  // 64 x 64, 32 x 64, 32 x 32.  500 x 1000 x 2304: 128 tiles of 64 x 64 9.2 us, 256 of 32 x 64 7.1 us.
+  int TM = 1, TN = 1;
+  if (ceil_div(M, 64) * ceil_div(N, 64) >= 256) TM = TN = 2;
+  else if (ceil_div(M, 32) * ceil_div(N, 64) >= 192) TN = 2;
+  p.tiles_m = (int)ceil_div(M, 32 * TM);
+  p.tiles = (int)(p.tiles_m * ceil_div(N, 32 * TN));
+  p.tiles_per_xcd = (int)ceil_div(p.tiles, 8);
+  // K split: up to two waves per SIMD, each with at least one group of k steps
+  int S = (int)(2048 / p.tiles);
+  S = S > 8 ? 8 : S;
+  if (S > p.nk / kAhead) S = p.nk / kAhead;
+  p.S = S < 1 ? 1 : S;
+  const bool sums = bits_a == 8 || bits_w == 8;
+  if (TM == 2) *err = sums ? launch_i8<2, 2, true>(p, s) : launch_i8<2, 2, false>(p, s);
+  else if (TN == 2) *err = sums ? launch_i8<1, 2, true>(p, s) : launch_i8<1, 2, false>(p, s);
+  else *err = sums ? launch_i8<1, 1, true>(p, s) : launch_i8<1, 1, false>(p, s);
+  return true;
+}
+
+}  // namespace bmx

@@ -409,6 +409,26 @@ def test_quant_gemm_kbit_weights(ba, bw, engine):
     assert_f32_close(of.cpu().numpy(), r64, atol=1e-9)
 
 
+@pytest.mark.parametrize("M,N,K", [(16, 16, 1), (32, 32, 256), (33, 65, 257), (31, 300, 2305), (512, 520, 770), (700, 2100, 100)])
+@pytest.mark.parametrize("ba,bw", [(3, 1), (8, 1), (1, 2), (4, 4), (7, 7), (8, 3), (2, 8), (8, 8)])
+def test_quant_gemm_bytes(M, N, K, ba, bw):
+    """The int8 form: edges of its 32-row blocks and 256-wide k blocks, both tile sizes, with and
+    without a K split, operands whose rows do not start 16-byte aligned, one output or both."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a = rng.uniform(-0.1, 1.1, (M, K + 1)).astype(np.float32)
+    w = rng.uniform(-1.1, 1.1, (N, K + 3)).astype(np.float32)
+    da, dw = dev(a)[:, :K], dev(w)[:, 3:] if bw > 1 else dev(w)[:, :K]
+    a, w = a[:, :K].copy(), w[:, 3:].copy() if bw > 1 else w[:, :K].copy()
+    rS, _, r32 = oracle.quant_gemm(a, w, ba, bw)
+    S, of = B.quant_gemm(da, dw, ba, bits_w=bw)
+    assert "gemm_i8_kernel" in B.last_kernel()
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    assert_f32_close(of.cpu().numpy(), r32)
+    S2, none = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw, want_float=False)
+    assert none is None
+    np.testing.assert_array_equal(S2.cpu().numpy(), rS)
+
+
 def test_config5_quant_gemm():
     c = synth.config5(small=True)
     S, of = B.quant_gemm(dev(c["a"]), dev(c["w"]), 2)

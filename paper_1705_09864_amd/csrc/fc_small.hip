@@ -1,65 +1,239 @@
-// Binary fully connected layer for problems of a few microseconds of work or less, in one launch.
+// Binary fully connected layer in one launch, for problems of a few microseconds of work or less.
 // Paper: Sec. 2 (QFullyConnected: binarise the input, xnor GEMM against the packed weights,
 // optional scale), Sec. 2.2.1 / 2.2.2 (Eq. 2): out[m][n] = K - 2 * popcount(x_bits[m] xor W[n]).
 //
-// A layer this small (64 x 512 -> 256: 13 ns of arithmetic) is two launches on the general path,
-// pack then GEMM, each a launch plus a chain of trips to memory, about 3.5 us apiece.  Here a
-// workgroup takes one batch row: its waves turn the row's fp32 values into sign bits in LDS (one
-// coalesced load and one ballot per 64 values), and thread t then produces output features
-// t, t + 256, ... with xor + popcount of the row's words against the feature's packed weights,
-// whose first words it requested before the row was packed.  The weights are read once per
-// batch row (from L2 after the first), which is why the launcher takes only small layers.
+// The general path is two launches, pack then GEMM, each a launch on the host (2.7 us) and on the
+// GPU a chain of trips to memory of about 4 us however little there is to do.  Here a workgroup
+// takes RM batch rows and a run of output features: it requests its first weight words, turns its
+// rows' fp32 values into sign bits in LDS (one coalesced load and one ballot per 64 values), and
+// then counts xor + popcount over lanes: L lanes share a feature, lane l taking words l, l + L, ...
+// of its row (whole runs of the weights per load, any alignment), the next words in flight while one
+// set is counted, and the lanes' counts are added by DPP and half-wave swaps.
+//
+// Every workgroup packs its rows for itself, so a row of x is read once per run of features, and
+// that is what decides where this form ends: the L1 path of a CU takes in 64 bytes per clock.  The
+// launcher weighs the bytes a CU has to move against the second launch.
 #include "bmx_internal.h"
+
+#include <algorithm>
 
 namespace bmx {
 
 namespace {
 
-constexpr int kAhead = 8;  // weight words a thread requests ahead of the pack
+// (sixteen waves, so that a row's runs are requested at once: 8 x 9216 -> 4096 6.0 us a call, with eight
+// waves 7.2, with eight that request a run ahead 7.5)
+constexpr int kWaves = 16;
 
-__global__ void __launch_bounds__(256)
-fc_small_kernel(const float* __restrict__ x, int64_t ldx, const uint64_t* __restrict__ Wp, int64_t ldw_w,
-                const float* __restrict__ alpha, int K, int Kw, int N, int32_t* __restrict__ out_i32,
-                float* __restrict__ out_f32, int64_t ldo) {
-  extern __shared__ uint64_t row[];  // the batch row's Kw words of sign bits
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = blockIdx.x;
-  // this thread's first output feature: its first weight words, requested first of all
-  const int n_first = min((int)threadIdx.x, N - 1);
-  uint64_t wfirst[kAhead];
+struct FcSmallParams {
+  const float* x;
+  int64_t ldx;
+  const uint64_t* W;
+  int64_t ldw;
+  const float* alpha;
+  int M, N, K, Kw, Kpad;  // Kpad: words of an LDS row, a multiple of W * L
+  int cols;               // output features per workgroup
+  int32_t* out_i32;
+  float* out_f32;
+  int64_t ldo;
+};
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+
+// Sums over the wave, two values at a time: after the swap one register holds the two halves of a,
+// the other those of b, so the sum is a's in the lower lanes and b's in the upper.
+__device__ __forceinline__ int swap_add32(int a, int b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return (int)r[0] + (int)r[1];
+}
+__device__ __forceinline__ int swap_add16(int a, int b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  return (int)r[0] + (int)r[1];
+}
+
+// L lanes per feature, U features per lane group and step, W words per lane and step.
+template <int RM, int L, int U, int W>
+__global__ void __launch_bounds__(64 * kWaves)
+fc_small_kernel(const FcSmallParams p) {
+  extern __shared__ uint64_t bits[];  // [RM][Kpad] sign bits
+  asm volatile("" ::"s"(p.x), "s"(p.ldx), "s"(p.W), "s"(p.ldw), "s"(p.alpha), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kw),
+               "s"(p.Kpad), "s"(p.cols), "s"(p.out_i32), "s"(p.out_f32), "s"(p.ldo));
+  constexpr int NV = RM * U;         // counts per lane group
+  constexpr int kGroupsPerWave = 64 / L;
+  constexpr int kPass = kGroupsPerWave * U;  // features per wave and pass
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.y * RM, n0 = blockIdx.x * p.cols;
+  const int l = lane & (L - 1), grp = lane / L;
+  const int nchunks = p.Kpad / (W * L);
+  const int n_end = min(n0 + p.cols, p.N);
+  // passes of this wave: features n0 + (wave + 8 i) * kPass ...
+  const int npass = (n_end - n0 > wave * kPass) ? (n_end - n0 - wave * kPass + kWaves * kPass - 1) / (kWaves * kPass) : 0;
+  // which of the group's counts this lane stores: value v = m * U + u
+  int v_mine;
+  bool stores;
+  if constexpr (L == 64) {
+    const int q = lane >> 4, i = lane & 15;
+    v_mine = 4 * i + 2 * (q & 1) + (q >> 1);
+    stores = v_mine < NV;
+  } else {
+    v_mine = l;
+    stores = l < NV;
+  }
+  const int u_mine = v_mine % U;
+
+  uint64_t w[U][W], nxt[U][W];
+  float al = 1.0f, al_nxt = 1.0f;
+  auto request = [&](int it) {
+    const int pass = it / nchunks, chunk = it - pass * nchunks;
+    const int nb = n0 + (wave + kWaves * pass) * kPass + grp * U;
 #pragma unroll
-  for (int w = 0; w < kAhead; ++w) wfirst[w] = Wp[(int64_t)n_first * ldw_w + min(w, Kw - 1)];
-  // sign bits of the row: wave v takes words v, v + 4, ..., four at a time so that their loads
-  // are in flight together; values past K count as negative (bit 0, like the packed weights' tail)
-  const float* xr = x + (int64_t)m * ldx;
-  for (int w0 = wave; w0 < Kw; w0 += 16) {
-    float v[4];
+    for (int u = 0; u < U; ++u) {
+      const uint64_t* row = p.W + (int64_t)min(nb + u, p.N - 1) * p.ldw;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 64 * (w0 + 4 * i) + lane;
-      v[i] = k < K ? xr[k] : -1.0f;
+      for (int j = 0; j < W; ++j) nxt[u][j] = row[min((chunk * W + j) * L + l, p.Kw - 1)];
     }
+    if (p.alpha) al_nxt = p.alpha[min(nb + u_mine, p.N - 1)];
+  };
+  const int total = npass * nchunks;
+  if (total > 0) request(0);
+
+  // ---- sign bits of the rows; values past K count as negative (bit 0, like the weights' tail).  A
+  // row is read as a buffer of K floats: what lies beyond reads as zero (and is masked), so a run of
+  // 16 words that ends past the row needs no addresses of its own.
+  const int cpr = (p.Kpad + 15) >> 4;  // runs per row
+  int m = 0, c = wave;
+  while (c >= cpr) c -= cpr, ++m;
+  while (m < RM) {
+    const float* xr = p.x + (int64_t)min(m0 + m, p.M - 1) * p.ldx;
+    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc((void*)xr, 0, 4 * p.K, 0x00020000);
+    const uint32_t off = (uint32_t)c * 4096u + 4u * (uint32_t)lane;
+    uint32_t v[16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint64_t bits = __ballot(v[i] >= 0.0f);
-      if (lane == 0 && w0 + 4 * i < Kw) row[w0 + 4 * i] = bits;
+    for (int j = 0; j < 16; ++j) v[j] = __builtin_amdgcn_raw_buffer_load_b32(row, off + 256u * j, 0, 0);
+    const int left = p.K - c * 1024;
+    uint32_t lo = 0, hi = 0;  // lane j: word j of the run
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      uint64_t b = __ballot(__uint_as_float(v[j]) >= 0.0f);
+      if (left < 64 * j + 64) b &= left > 64 * j ? (1ull << (left - 64 * j)) - 1 : 0ull;  // (scalar)
+      asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)b), "i"(j));
+      asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(b >> 32)), "i"(j));
     }
+    if (lane < 16 && 16 * c + lane < p.Kpad) bits[m * p.Kpad + 16 * c + lane] = (uint64_t)hi << 32 | lo;
+    c += kWaves;
+    while (c >= cpr) c -= cpr, ++m;
   }
   __syncthreads();
-  for (int n = threadIdx.x; n < N; n += 256) {
-    const uint64_t* wr = Wp + (int64_t)n * ldw_w;
-    int pc = 0;
-    if (n == (int)threadIdx.x) {
+
+  int pc[NV];
+  int pass = 0, chunk = 0;
+  for (int it = 0; it < total; ++it) {
 #pragma unroll
-      for (int w = 0; w < kAhead; ++w)
-        if (w < Kw) pc += __popcll(row[w] ^ wfirst[w]);
-      for (int w = kAhead; w < Kw; ++w) pc += __popcll(row[w] ^ wr[w]);
-    } else {
-      for (int w = 0; w < Kw; ++w) pc += __popcll(row[w] ^ wr[w]);
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < W; ++j) w[u][j] = nxt[u][j];
+    al = al_nxt;
+    if (it + 1 < total) request(it + 1);
+    if (chunk == 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) pc[i] = 0;
     }
-    const int dot = K - 2 * pc;
-    if (out_i32) out_i32[(int64_t)m * ldo + n] = dot;
-    else out_f32[(int64_t)m * ldo + n] = (alpha ? alpha[n] : 1.0f) * (float)dot;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const int wi = (chunk * W + j) * L + l;
+      if (wi >= p.Kw) {  // (the rows' bits are zero there too)
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u][j] = 0;
+      }
+#pragma unroll
+      for (int m = 0; m < RM; ++m) {
+        const uint64_t xb = bits[m * p.Kpad + wi];
+#pragma unroll
+        for (int u = 0; u < U; ++u) pc[m * U + u] += __popcll(xb ^ w[u][j]);
+      }
+    }
+    if (++chunk < nchunks) continue;
+    chunk = 0;
+    // ---- the pass's features are counted: add the lanes up, one count per storing lane
+    int mine = 0;
+    if constexpr (L == 64) {
+      constexpr int N4 = (NV + 3) / 4;
+#pragma unroll
+      for (int i = 0; i < N4; ++i) {
+        int a[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] = 4 * i + k < NV ? pc[4 * i + k] : 0;
+        int s = swap_add16(swap_add32(a[0], a[1]), swap_add32(a[2], a[3]));
+        s = dpp_add<0x121>(dpp_add<0x122>(dpp_add<0x124>(dpp_add<0x128>(s))));  // row_ror 8, 4, 2, 1
+        if ((lane & 15) == i) mine = s;
+      }
+    } else if constexpr (L == 16) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int s = dpp_add<0x121>(dpp_add<0x122>(dpp_add<0x124>(dpp_add<0x128>(pc[i]))));
+        if (l == i) mine = s;
+      }
+    }
+    const int nb = n0 + (wave + kWaves * pass) * kPass + grp * U;
+    ++pass;
+    auto store = [&](int v, int count) {
+      const int m = m0 + v / U, n = nb + v % U;
+      if (m >= p.M || n >= n_end) return;
+      const int dot = p.K - 2 * count;
+      if (p.out_i32) p.out_i32[(int64_t)m * p.ldo + n] = dot;
+      else p.out_f32[(int64_t)m * p.ldo + n] = al * (float)dot;
+    };
+    if constexpr (L == 4) {  // U = 1: lane l of a group stores rows l, l + 4
+      static_assert(L != 4 || U == 1, "");
+#pragma unroll
+      for (int i = 0; i < NV; i += 4) {
+        int t = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (i + k >= NV) break;
+          const int s = dpp_add<0x4e>(dpp_add<0xb1>(pc[i + k]));  // quad_perm [1,0,3,2], [2,3,0,1]
+          if (l == k) t = s;
+        }
+        if (i + l < NV) store(i + l, t);
+      }
+    } else if (stores) {
+      store(v_mine, mine);
+    }
+  }
+}
+
+// Lanes per feature and words per lane and step by the length of a row: the least padding.
+struct Lanes {
+  int L, W;
+};
+Lanes lanes_for(int64_t Kw) {
+  if (Kw <= 16) return {4, Kw <= 8 ? 2 : 4};
+  if (Kw <= 64) return {16, (int)ceil_div(Kw, 16)};
+  if (Kw <= 128) return {64, 2};
+  const int64_t n = ceil_div(Kw, 64);
+  return {64, ceil_div(n, 3) * 3 < ceil_div(n, 4) * 4 ? 3 : 4};
+}
+
+template <int RM>
+void launch_rm(const FcSmallParams& p, Lanes l, dim3 grid, hipStream_t s) {
+  const size_t lds = (size_t)RM * p.Kpad * 8;
+  note_kernel("fc_small_kernel<%d,%d,%d> grid %u x %u x %d, %d features", RM, l.L, l.W, grid.x, grid.y, 64 * kWaves, p.cols);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), lds, s, p); };
+  if (l.L == 64) {
+    if (l.W == 2) go(fc_small_kernel<RM, 64, 2, 2>);
+    else if (l.W == 3) go(fc_small_kernel<RM, 64, 2, 3>);
+    else go(fc_small_kernel<RM, 64, 2, 4>);
+  } else if (l.L == 16) {
+    if (l.W == 2) go(fc_small_kernel<RM, 16, 2, 2>);
+    else if (l.W == 3) go(fc_small_kernel<RM, 16, 2, 3>);
+    else go(fc_small_kernel<RM, 16, 2, 4>);
+  } else {
+    if (l.W == 2) go(fc_small_kernel<RM, 4, 1, 2>);
+    else go(fc_small_kernel<RM, 4, 1, 4>);
   }
 }
 
@@ -67,17 +241,55 @@ fc_small_kernel(const float* __restrict__ x, int64_t ldx, const uint64_t* __rest
 
 int fc_small = 0;  // 1 = never (measurements and tests of the general path on small layers)
 
-// Takes layers whose whole weight matrix is at most 64 words per thread of a workgroup and whose
-// rows fit 8 KB of LDS; false otherwise.
+// Takes the layer where what the busiest CU has to move in this form costs less than a second
+// launch; false otherwise (nothing launched then).
 bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
                      int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo,
                      hipStream_t s, hipError_t* err) {
-  const int64_t Kw = words_for(in_features);
   // (a GEMM engine pinned through the tuning hook is what the caller wants to run)
-  if (fc_small == 1 || gemm_engine != 0 || Kw > 1024 || (int64_t)out_features * Kw > 256 * 64 || batch > 4096) return false;
-  note_kernel("fc_small_kernel grid %d x 256", batch);
-  hipLaunchKernelGGL(fc_small_kernel, dim3((unsigned)batch), dim3(256), (size_t)Kw * 8, s, x, ldx, Wp, ldw_w, alpha,
-                     in_features, (int)Kw, out_features, out_i32, out_f32, ldo);
+  if (fc_small == 1 || gemm_engine != 0) return false;
+  const int64_t Kw = words_for(in_features);
+  if (Kw > 4096 || batch > 65535) return false;
+  const Lanes lanes = lanes_for(Kw);
+  const int64_t Kpad = ceil_div(Kw, lanes.W * lanes.L) * lanes.W * lanes.L;
+  // Rows and features per workgroup: the pair that leaves the busiest CU the least to move (fp32 rows
+  // and packed weights of its workgroups, and a fixed share per workgroup for its latencies).
+  int64_t best = INT64_MAX, rm = 1, cols = 16;
+  for (int64_t r = 1; r <= 8; r *= 2) {
+    if (r > 1 && (r / 2 >= batch || r * Kpad * 8 > 48 * 1024)) break;
+    for (int64_t c = 16; c <= 512; c *= 2) {
+      if (c > 16 && c / 2 >= out_features) break;
+      const int64_t wgs = ceil_div(batch, r) * ceil_div(out_features, c);
+      const int64_t cost = ceil_div(wgs, 256) * (r * in_features * 4 + c * Kw * 8 + 4 * r * c * Kpad + (16 << 10));
+      if (cost < best) best = cost, rm = r, cols = c;
+    }
+  }
+  // Level with two launches at about 384 KB (608 x 771 -> 1487, 348 KB: 7.6 against 11.4 us; 12 x 8385
+  // -> 3257, 405 KB: 8.8 against 9.2 us; 490 x 3356 -> 829, 738 KB: 14.3 against 12.8 us).  A few
+  // workgroups have the memory system to themselves, and the general path's one or two tiles take a
+  // chain as long (2 x 65536 -> 16: 7.0 against 16.2 us).
+  const int64_t wgs = ceil_div(batch, rm) * ceil_div(out_features, cols);
+  if (best > (wgs <= 32 ? 768 << 10 : 384 << 10)) return false;
+  FcSmallParams p;
+  p.x = x;
+  p.ldx = ldx;
+  p.W = Wp;
+  p.ldw = ldw_w;
+  p.alpha = alpha;
+  p.M = batch;
+  p.N = out_features;
+  p.K = in_features;
+  p.Kw = (int)Kw;
+  p.Kpad = (int)Kpad;
+  p.cols = (int)cols;
+  p.out_i32 = out_i32;
+  p.out_f32 = out_f32;
+  p.ldo = ldo;
+  const dim3 grid((unsigned)ceil_div(out_features, cols), (unsigned)ceil_div(batch, rm));
+  if (rm == 1) launch_rm<1>(p, lanes, grid, s);
+  else if (rm == 2) launch_rm<2>(p, lanes, grid, s);
+  else if (rm == 4) launch_rm<4>(p, lanes, grid, s);
+  else launch_rm<8>(p, lanes, grid, s);
   *err = hipGetLastError();
   return true;
 }

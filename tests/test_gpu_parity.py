@@ -243,6 +243,22 @@ def test_fc_small_layers_one_launch(batch, fin, fout):
         assert "fc_small_kernel" not in B.last_kernel()
 
 
+@pytest.mark.parametrize("batch,fin,fout", [(1, 512, 1), (3, 513, 17), (5, 1024, 33), (6, 1025, 40), (9, 2049, 31), (4, 3073, 65),
+                                            (7, 4097, 50), (2, 8193, 130), (8, 12289, 20), (3, 20481, 9), (33, 2048, 600)])
+def test_fc_small_row_lengths(batch, fin, fout):
+    """Every split of a row over lanes (4, 16 or 64 of them, two to four words each), at the row
+    lengths where it changes, with rows and features that do not fill their workgroup."""
+    rng = np.random.default_rng(fin)
+    x = rng.standard_normal((batch, fin)).astype(np.float32)
+    w = rng.uniform(-1, 1, (fout, fin)).astype(np.float32)
+    alpha = rng.standard_normal(fout).astype(np.float32)
+    ri, rf = oracle.binary_fc(x, w, alpha)
+    Wp = B.binarize_pack(dev(w), 1)
+    np.testing.assert_array_equal(B.binary_fc(dev(x), Wp, integer_out=True).cpu().numpy(), ri)
+    assert "fc_small_kernel" in B.last_kernel()
+    np.testing.assert_array_equal(B.binary_fc(dev(x), Wp, alpha=dev(alpha)).cpu().numpy(), rf)
+
+
 @pytest.mark.parametrize("batch,fin,fout", [(1, 1, 1), (5, 27, 3), (3, 180, 70), (66, 1000, 130)])
 def test_fc_ragged(batch, fin, fout):
     rng = np.random.default_rng(batch + fin + fout)

@@ -69,6 +69,10 @@ struct MfmaParams {
   int64_t ldc;       // elements per row (C_bits: 64-bit words per row)
 };
 
+// Sixteen bytes of a row whose start is only a multiple of 8 (rows of an odd number of words, as
+// binarize_pack leaves them for such K): one global load all the same.
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(8)));
+
 // A macro step covers up to 16 words (1024 bits) of every row: half h of the wave takes
 // words h * half .. h * half + half - 1 of it (half = 8 except in a shorter last step), in
 // pieces of two words; piece step q is words h * half + 2q, + 1.  One piece step of all rows
@@ -90,7 +94,8 @@ __device__ __forceinline__ void load_rows_coalesced(const uint64_t* mat, int64_t
     const int row = min(row0 + 8 * t + (lane >> 3), nrows - 1);  // rows past the matrix repeat its last
     const uint64_t* src = mat + ((int64_t)row * planes + pl) * ld + mac * 16 + 2 * pp;
     if (whole) {
-      r[t] = *(const uint4*)src;
+      const v4u_any v = *(const v4u_any*)src;
+      r[t] = make_uint4(v[0], v[1], v[2], v[3]);
     } else {
       const int w = mac * 16 + 2 * pp;
       const uint64_t lo = w < Kw ? src[0] : 0;
@@ -566,8 +571,6 @@ bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, 
   if (launch_gemm_fp4(A, lda_w, 1, nullptr, B, ldb_w, M, N, K, alpha_n, C_i32, C_f32, C_bits, thr_n, ldc, as_count,
                       s, err))
     return true;
-  // 16-byte row pieces are loaded as one vector: rows must start 16-byte aligned
-  if ((lda_w & 1) || (ldb_w & 1) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15)) return false;
   MfmaParams p;
   p.A = A;
   p.B = B;
@@ -613,7 +616,6 @@ bool launch_plane_gemm_mfma(const uint64_t* planes_rows, int64_t lda_w, int bits
   if (launch_gemm_fp4(planes_rows, lda_w, bits, rowsum, Wb, ldb_w, M, N, K, nullptr, S_out, out_f32, nullptr, nullptr,
                       ldo, false, s, err))
     return true;
-  if ((lda_w & 1) || (ldb_w & 1) || ((uintptr_t)planes_rows & 15) || ((uintptr_t)Wb & 15)) return false;
   MfmaParams p;
   p.A = planes_rows;
   p.B = Wb;

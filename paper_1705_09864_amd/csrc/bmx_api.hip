@@ -42,21 +42,24 @@ int conv_check(int N, int C, int H, int W, int O, int KH, int KW, int stride, in
   return BMX_OK;
 }
 
+// Rows of an even number of words start 16-byte aligned, which the matrix-core kernels load fastest.
+inline int64_t even_words(int64_t words) { return (words + 1) / 2 * 2; }
+
 // 64-bit row length (even: 16-byte rows) that rows of 32-bit words are widened to
-inline int64_t w32_row_words(int64_t K) { return (bmx::words_for(K) + 1) / 2 * 2; }
+inline int64_t w32_row_words(int64_t K) { return even_words(bmx::words_for(K)); }
 
 struct QuantWs {
   size_t planes_off, wb_off, rowsum_off, wrowsum_off, tmp_off, total;
 };
 
-// bits_w = 1: sign-packed weights [N][Kw].  bits_w > 1: weight planes [N * bits_w][padded K]
+// bits_w = 1: sign-packed weights [N][even Kw].  bits_w > 1: weight planes [N * bits_w][padded K]
 // like the activations', their (unused) row sums, and the int32 results per weight plane.
 QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
   const int64_t Kw = bmx::words_for(K);
   QuantWs q;
   q.planes_off = 0;
   q.wb_off = round256((size_t)bits_a * M * bmx::padded_words(K) * 8);
-  q.rowsum_off = q.wb_off + round256(bits_w == 1 ? (size_t)N * Kw * 8
+  q.rowsum_off = q.wb_off + round256(bits_w == 1 ? (size_t)N * even_words(Kw) * 8
                                                    : (size_t)bits_w * N * bmx::padded_words(K) * 8);
   q.wrowsum_off = q.rowsum_off + round256((size_t)M * 4);
   q.tmp_off = q.wrowsum_off + (bits_w == 1 ? 0 : round256((size_t)N * 4));
@@ -543,9 +546,9 @@ int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int6
     return hip_status(bmx::launch_quant_combine(tmp, M, N, bits_w, denom, out_i32_scaled, out_f32, ldo, s));
   }
   // one launch quantises + plane-packs the activations and sign-packs the weights
-  hipError_t e = bmx::launch_quant_pack(a, M, K, lda, bits_a, planes, ldp, rowsum, w, N, ldw, wb, Kw, s);
+  hipError_t e = bmx::launch_quant_pack(a, M, K, lda, bits_a, planes, ldp, rowsum, w, N, ldw, wb, even_words(Kw), s);
   if (e != hipSuccess) return BMX_ERR_HIP;
-  return hip_status(bmx::launch_plane_gemm((const uint32_t*)planes, ldp * 2, bits_a, rowsum, wb, Kw,
+  return hip_status(bmx::launch_plane_gemm((const uint32_t*)planes, ldp * 2, bits_a, rowsum, wb, even_words(Kw),
                                            M, N, K, out_i32_scaled, out_f32, ldo, s));
 }
 

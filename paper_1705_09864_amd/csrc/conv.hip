@@ -85,7 +85,7 @@ __device__ __forceinline__ void touch_args(const ConvParams& p) {
   if constexpr (KW <= 9) touch_offsets<KW>(p);  // longer tables would not stay in SGPRs anyway
 }
 
-template <int KW, int OUT>
+template <int KW, int OUT, bool NT>
 __global__ void __launch_bounds__(256)
 conv_stationary_kernel(const ConvParams p) {
   constexpr int SEG = SegShape<KW>::kSeg;
@@ -136,6 +136,11 @@ conv_stationary_kernel(const ConvParams p) {
                 ((int64_t)img0 * p.O + o0) * p.HoWo * 4;
   const int64_t ostride = (int64_t)p.HoWo * 4;
 
+  auto store = [&](uint32_t off, auto v, char* base) {
+    if constexpr (NT) asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(v), "s"(base) : "memory");
+    else asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(v), "s"(base) : "memory");
+  };
+
   ScalarSeg<SEG> buf[2];
   int pc = 0;
   const_u32_ptr src = stream;
@@ -160,17 +165,18 @@ conv_stationary_kernel(const ConvParams p) {
           int dot;  // K - 2 * popcount in one VALU op (both operands are below 2^23)
           asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(dot) : "v"(pc), "s"(p.Kreal));
           // scalar base + 32-bit lane offset: the store needs no vector address arithmetic
-          // (non-temporal: the output is written once and never read here; measured 6.5
-          // against 7.8 us on the 16 x 64 x 56 x 56 layer)
+          // (NT, non-temporal: the output is written once and never read here; measured 6.5
+          // against 7.8 us on the 16 x 64 x 56 x 56 layer.  Only where a wave's 64 pixels are whole 128-byte
+          // lines: 107 x 192 planes of 23 x 25 took 19.3 us with it, planes of 24 x 24 9.6 us)
           if (OUT == kOutF32Alpha) {
             const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lane), row));
             const float v = a * (float)dot;
-            asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(ooff), "v"(v), "s"(obase) : "memory");
+            store(ooff, v, obase);
           } else if (OUT == kOutF32) {
             const float v = (float)dot;
-            asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(ooff), "v"(v), "s"(obase) : "memory");
+            store(ooff, v, obase);
           } else {
-            asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(ooff), "v"(dot), "s"(obase) : "memory");
+            store(ooff, dot, obase);
           }
         }
         obase += ostride;
@@ -214,12 +220,11 @@ void launch_stationary(const ConvParams& p, int64_t groups, int cblocks, hipStre
   dim3 grid((unsigned)ceil_div(groups, 4), (unsigned)cblocks);
   note_kernel("conv_stationary_kernel<%d,%s> grid %u x %u x 256, %d filters per wave", KW,
               p.out_f32 ? (p.alpha ? "f32*alpha" : "f32") : "i32", grid.x, grid.y, p.cn);
-  if (p.out_f32 && p.alpha)
-    hipLaunchKernelGGL((conv_stationary_kernel<KW, kOutF32Alpha>), grid, dim3(256), 0, s, p);
-  else if (p.out_f32)
-    hipLaunchKernelGGL((conv_stationary_kernel<KW, kOutF32>), grid, dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((conv_stationary_kernel<KW, kOutI32>), grid, dim3(256), 0, s, p);
+  const bool nt = p.HoWo % 64 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 127) == 0;
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
+  if (p.out_f32 && p.alpha) nt ? go(conv_stationary_kernel<KW, kOutF32Alpha, true>) : go(conv_stationary_kernel<KW, kOutF32Alpha, false>);
+  else if (p.out_f32) nt ? go(conv_stationary_kernel<KW, kOutF32, true>) : go(conv_stationary_kernel<KW, kOutF32, false>);
+  else nt ? go(conv_stationary_kernel<KW, kOutI32, true>) : go(conv_stationary_kernel<KW, kOutI32, false>);
 }
 
 }  // namespace
@@ -272,14 +277,16 @@ hipError_t launch_binary_conv2d(const uint64_t* Xp, int N, int C, int H, int W, 
   // 16 x 128 x 28 x 28 -> 128; at 36 words 15.6 against 16.8 us for the GEMM-shaped matrix-core
   // kernel (64 x 256 x 14 x 14 -> 256) and 8.2 against 8.6 us at stride 2.
   // The GEMM kernel with 64 x 64 per wave and LDS-staged operands in its convolution form (6
-  // forces it): the choice beyond the 50 words the short-K kernel reaches, given an even number
-  // of channel words.  Measured per call against the 32 x 32 per wave matrix-core kernel, inputs
-  // from HBM: 200 x 256 x 12 x 12, 5 x 5, 64 filters 16.0 against 19.3 us, 512 channels 25.2
-  // against 30.8 us, 7 x 7 over 256 channels 20.5 against 26.3 us.  Within the short-K kernel's
-  // reach it wins only where that kernel cannot fill the chip (64 x 256 x 14 x 14 at stride 2: 6.5
-  // against 7.1 us) and loses where the output is large (stride 1: 12.8 against 11.2 us: its
-  // tiles store all at once at the end, the short-K kernel block by block), so it is not chosen there.
-  if (conv_path == 6 || (conv_path == 0 && kwords > 50 && (Cw & 1) == 0)) {
+  // forces it): the choice for every K that neither the short-K kernel nor the stationary kernel
+  // holds, from 64 tiles on; below, the 32 x 32 per wave kernel has four times the waves (kernel alone:
+  // 7 x 7 over 391 channels of 26 x 13 x 13, 140 tiles, 14.2 against 24.8 us; 3 x 3 over 320 channels of
+  // 105 x 28 x 27 25.2 against 33.4; 3 x 332 x 26 x 28, 5 x 5, 50 tiles, 8.0 against 7.0).
+  // Within the short-K kernel's reach it wins only where that kernel cannot fill the chip (64 x 256 x 14 x
+  // 14 at stride 2: 6.5 against 7.1 us) and loses where the output is large (stride 1: 12.8 against
+  // 11.2 us: its tiles store all at once at the end, the short-K kernel block by block), so it is not
+  // chosen there.
+  const int64_t tiles64 = ceil_div(O, 64) * ceil_div(P, 64);
+  if (conv_path == 6 || (conv_path == 0 && !stationary_ok && !conv_weight_short_k(kwords) && tiles64 >= 64)) {
     hipError_t err = hipSuccess;
     if (launch_conv_fp4(Xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, s, &err)) return err;
   }

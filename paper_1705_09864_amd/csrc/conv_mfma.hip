@@ -56,6 +56,7 @@ struct WsParams {
   int nblocks, nchunks;  // blocks of 32 pixels in all; waves they are dealt out to (evenly)
   int blk_q, blk_r;      // nblocks / nchunks and nblocks % nchunks
   int x4;                // 1: K-words 2 q, 2 q + 1 are 16 consecutive, 16-byte aligned bytes of the image; 2: 4 q .. 4 q + 3 are 32
+  int nt;                // fp32 and int32 result stores bypass the caches
   FastDiv div_howo, div_wo;
   int off[kMaxWsWords];  // word offset of K-word j relative to the pixel base
 };
@@ -202,10 +203,10 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
   // Fields at most 64 bytes apart, named in one statement here, bring all lines in with the
   // first group; the groups that follow hit the scalar cache.
   static_assert(offsetof(WsParams, Nimg) <= 64 && offsetof(WsParams, blk_q) - offsetof(WsParams, Nimg) <= 64 &&
-                    offsetof(WsParams, off) + 7 * 4 - offsetof(WsParams, blk_q) <= 64 &&
-                    sizeof(WsParams) - (offsetof(WsParams, off) + 39 * 4) <= 64 && kMaxWsWords > 39,
+                    offsetof(WsParams, off) + 5 * 4 - offsetof(WsParams, blk_q) <= 64 &&
+                    sizeof(WsParams) - (offsetof(WsParams, off) + 37 * 4) <= 64 && kMaxWsWords > 37,
                 "a named field in every 64 bytes");
-  asm volatile("" ::"s"(p.Xp), "s"(p.Nimg), "s"(p.blk_q), "s"(p.off[7]), "s"(p.off[23]), "s"(p.off[39]));
+  asm volatile("" ::"s"(p.Xp), "s"(p.Nimg), "s"(p.blk_q), "s"(p.off[5]), "s"(p.off[21]), "s"(p.off[37]));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -453,7 +454,7 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
         const uint32_t pitch = (uint32_t)p.HoWo * 4u;
         const uint32_t lane_off = cur.obase * 4u + (uint32_t)(m0 + 32 * i + 4 * h) * pitch;
         const bool inside = b * 32 + 32 <= p.P && m0 + 32 * TM <= p.O;
-        auto put = [&](auto inside_tag, auto int_tag) {
+        auto put = [&](auto inside_tag, auto int_tag, auto nt_tag) {
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int mi = 8 * (v / 4) + (v % 4);
@@ -468,21 +469,34 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
               // store even from a uniform base and a 32-bit offset)
               if constexpr (decltype(int_tag)::value) {
                 const int iv = (int)t;
-                asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(iv), "s"((const char*)p.out_i32 + row_bytes) : "memory");
+                if constexpr (decltype(nt_tag)::value)
+                  asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(iv), "s"((const char*)p.out_i32 + row_bytes) : "memory");
+                else
+                  asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(iv), "s"((const char*)p.out_i32 + row_bytes) : "memory");
               } else {
                 const float fv = al[v] * t;
-                asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(fv), "s"((const char*)p.out_f32 + row_bytes) : "memory");
+                if constexpr (decltype(nt_tag)::value)
+                  asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(fv), "s"((const char*)p.out_f32 + row_bytes) : "memory");
+                else
+                  asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(fv), "s"((const char*)p.out_f32 + row_bytes) : "memory");
               }
             }
           }
         };
-        if (p.out_i32) {
-          if (inside) put(std::true_type{}, std::true_type{});
-          else put(std::false_type{}, std::true_type{});
-        } else {
-          if (inside) put(std::true_type{}, std::false_type{});
-          else put(std::false_type{}, std::false_type{});
-        }
+        // (non-temporal where a block's 32 pixels of a plane are one whole 128-byte line, 8.9 against
+        // 10.3 us a call on 16 x 64 x 56 x 56; where they are parts of two lines such parts of a large result
+        // reach memory one by one: 57 x 64 x 54 x 54 26.1 us with the hint, 18.4 through L2)
+        auto put_nt = [&](auto nt_tag) {
+          if (p.out_i32) {
+            if (inside) put(std::true_type{}, std::true_type{}, nt_tag);
+            else put(std::false_type{}, std::true_type{}, nt_tag);
+          } else {
+            if (inside) put(std::true_type{}, std::false_type{}, nt_tag);
+            else put(std::false_type{}, std::false_type{}, nt_tag);
+          }
+        };
+        if (p.nt) put_nt(std::true_type{});
+        else put_nt(std::false_type{});
       }
     }
     if constexpr (ONE) break;
@@ -570,6 +584,9 @@ bool launch_conv_mfma_ws(const uint64_t* Xp, int Nimg, int C, int H, int W, cons
   p.out_i32 = out_i32;
   p.out_f32 = out_f32;
   p.out_bits = (uint32_t*)out_bits;
+  // (whole lines, or results the memory-side cache takes in as they come: 64 x 256 x 14 x 14, 12.8 MB,
+  // 13.5 us a call with the hint and 14.1 without; from about 30 MB on parts of lines lose)
+  p.nt = (Ho * Wo % 32 == 0 && (((uintptr_t)out_i32 | (uintptr_t)out_f32) & 127) == 0) || (int64_t)Nimg * O * Ho * Wo * 4 <= (20 << 20);
   p.thr = thr;
   p.Nimg = Nimg;
   p.Ho = Ho;

@@ -71,6 +71,7 @@ struct Fp4Params {
   float* C_f32;
   uint32_t* C_bits;  // packed sign bits, addressed in 32-bit halves of the output words
   int ldc;           // elements per row (C_bits: 64-bit words per row); M * ldc < 2^31
+  int nt;            // result stores bypass the caches: every 32-column run is one whole 128-byte line
   // Convolution form (Sec. 3.1: M = filters, N = batch * output pixels, K = kh * kw * C): A is the
   // packed filter matrix, B the halo-padded packed image.  Column n is output pixel n (flat over
   // the images); its K words are KH runs of KW * Cw consecutive words, one run per kernel row
@@ -79,6 +80,7 @@ struct Fp4Params {
   // row m here, and the result goes to NCHW: element (image * M + m) * HoWo + pixel.
   int HoWo, Wo, Hp, Wpp, Cw, stride;
   uint32_t run_pieces, row_bytes, npieces;  // pieces per run; bytes from run to run; pieces per pixel
+                                            // (through registers: words per run, per pixel)
   FastDiv div_howo, div_wo, div_run;
 };
 
@@ -164,6 +166,44 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
     }
 }
 
+// The same segment through registers, for rows that start 8-byte aligned only (an odd number of words
+// per row) and for images whose 16-byte pieces are not contiguous (an odd number of channel words):
+// the load unit writes LDS from 16-byte aligned addresses, an ordinary 16-byte load needs 4.  The words
+// go to the same places of the staging area when the wave gets to the segment.
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(8)));
+
+template <int NA, int NB, bool CONV>
+__device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB][2], const uint32_t (&voff)[NB][2],
+                                              int piece0, int piece1, int seg) {
+  const bool tail = 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
+#pragma unroll
+  for (int b = NB - 1; b >= 0; --b)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int pc = t ? piece1 : piece0;
+      const char* base = b < NA ? (const char*)p.A : (const char*)p.B;
+      if (!(CONV && b >= NA) && !tail) {
+        const v4u_any v = *(const v4u_any*)(base + (uint32_t)seg * 64u + voff[b][t]);
+        nx[b][t] = make_uint4(v[0], v[1], v[2], v[3]);
+      } else {  // word by word; words past the row repeat its last (the reader zeroes them)
+        uint64_t w[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const uint32_t k = (uint32_t)min(8 * seg + 2 * pc + e, p.Kw - 1);
+          uint32_t off;
+          if (CONV && b >= NA) {
+            const uint32_t run = fast_div(k, p.div_run);
+            off = voff[b][t] + run * p.row_bytes + (k - run * p.run_pieces) * 8u;
+          } else {
+            off = voff[b][t] - 16u * pc + k * 8u;
+          }
+          w[e] = *(const uint64_t*)(base + off);
+        }
+        nx[b][t] = make_uint4((uint32_t)w[0], (uint32_t)(w[0] >> 32), (uint32_t)w[1], (uint32_t)(w[1] >> 32));
+      }
+    }
+}
+
 #ifdef BMX_FP4_STAMPS
 // Profiling builds only: per-wave shader-clock stamps at the phase boundaries of the kernel.
 }  // namespace
@@ -184,10 +224,11 @@ constexpr int kOutF32 = 0, kOutI32 = 1, kOutBits = 2;
 // popcounts from the words themselves), else the plane form (row sums given); OUT: what the
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
 // HALF: the partial tiles of a split cross LDS as fp16 pairs (exact while a wave's sums stay
-// at or below 2048, which the launcher checks); CONV: the convolution form (see Fp4Params).
+// at or below 2048, which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
+// segments travel through registers (see fetch_segment).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV>
+template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
 __global__ void __launch_bounds__(512)
 gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #ifdef BMX_FP4_STAMPS
@@ -292,7 +333,11 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   const int rowsum_lane = XNOR ? 0 : p.rowsum[min(m0 + lane, p.M - 1)];
   const float alpha_lane = (CONV && p.alpha) ? p.alpha[min(m0 + lane, p.M - 1)] : 1.0f;
 
-  if (seg_lo < seg_hi) issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
+  uint4 nx[NB][2];  // REG: the next segment's words
+  if (seg_lo < seg_hi) {
+    if constexpr (REG) fetch_segment<NA, NB, CONV>(p, nx, voff, piece[0], piece[1], seg_lo);
+    else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
+  }
   FP4_STAMP(1);
   FP4_REALTIME(4);
 
@@ -312,6 +357,12 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   for (int seg = seg_lo; seg < seg_hi; ++seg) {
     // the segment's words into registers (the compiler waits for the loads in flight: it tracks
     // LDS writes of the load unit)
+    if constexpr (REG) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) stage[b * 128 + t * 64 + lane] = nx[b][t];
+    }
     uint4 w[NB][2];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -337,11 +388,15 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     // because the compiler waits for every pending load of the load unit before an LDS read it
     // knows of, both measured no faster with operands that really come from HBM: 9.5 and 9.9
     // against 9.5 us on the first fully connected layer.)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    // (Through registers a segment is written by the wave itself, behind its reads.)
+    if (!REG) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #ifdef BMX_FP4_STAMPS
     if (seg == seg_lo) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); FP4_STAMP(2); }
 #endif
-    if (seg + 1 < seg_hi) issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1);
+    if (seg + 1 < seg_hi) {
+      if constexpr (REG) fetch_segment<NA, NB, CONV>(p, nx, voff, piece[0], piece[1], seg + 1);
+      else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1);
+    }
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int kg = 2 * seg + g;
@@ -412,8 +467,17 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   // tot: the full-K sum of the MFMA results; ra, cb: pc(A row), pc(B column) over the full K
   // (plane form: ra = the row sum of the quantised activations).
   // inside: the tile lies wholly inside C (wave-uniform), so no element needs its bounds tested
-  auto finish = [&](auto inside_tag, int i, int j, int v, float tot, int ra, int cb, float al, float th) {
+  // nt: past the caches, which is worth 2 to 15 % where a run of 32 results is one whole 128-byte line.
+  // Where it is parts of two, each part would be a memory access of its own: 2017 x 6017 of C took
+  // 27 us with such stores and 12.3 us through L2, which joins them; 6016 columns 11.9 us either way.
+  auto finish = [&](auto inside_tag, auto nt_tag, int i, int j, int v, float tot, int ra, int cb, float al, float th) {
     constexpr bool INSIDE = decltype(inside_tag)::value;
+    auto put = [&](auto value, auto* to) {
+      // (written out: as a builtin the compiler merges it with the ordinary store of the other branch,
+      // and the hint is gone)
+      if constexpr (decltype(nt_tag)::value) asm volatile("global_store_dword %0, %1, off nt" ::"v"(to), "v"(value) : "memory");
+      else *to = value;
+    };
     const int mi = 32 * i + 8 * (v >> 2) + 4 * h + (v & 3);
     const int m = m0 + mi, n = n0 + 32 * j + r;
     const uint32_t idx = CONV ? (pix_img[j] * (uint32_t)p.M + (uint32_t)m) * (uint32_t)p.HoWo + pix_rem[j]
@@ -421,8 +485,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     if (!XNOR) {
       if (INSIDE || (m < p.M && n < p.N && live)) {
         const int sv = 2 * (int)tot - ra;
-        if (p.C_i32) __builtin_nontemporal_store(sv, p.C_i32 + idx);
-        if (p.C_f32) __builtin_nontemporal_store((float)sv / p.levels, p.C_f32 + idx);
+        if (p.C_i32) put(sv, p.C_i32 + idx);
+        if (p.C_f32) put((float)sv / p.levels, p.C_f32 + idx);
       }
       return;
     }
@@ -434,8 +498,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
       if (r == 0 && m < p.M && live)
         p.C_bits[(uint32_t)(m * (2 * p.ldc) + (n >> 5))] = h ? (uint32_t)(mask >> 32) : (uint32_t)mask;
     } else if (INSIDE || (m < p.M && n < p.N && live)) {
-      if (OUT == kOutI32) __builtin_nontemporal_store(p.as_count ? ((int)dot + p.Kreal) >> 1 : (int)dot, p.C_i32 + idx);
-      else __builtin_nontemporal_store(al * dot, p.C_f32 + idx);
+      if (OUT == kOutI32) put(p.as_count ? ((int)dot + p.Kreal) >> 1 : (int)dot, p.C_i32 + idx);
+      else put(al * dot, p.C_f32 + idx);
     }
   };
   // popcounts: a lane counted its half of K for row / column r; the other half sits 32 lanes away
@@ -459,17 +523,21 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
         ra[i][v] = XNOR ? __shfl(pa[i], mi & 31) : __shfl(rowsum_l, mi);
         alm[i][v] = CONV ? __shfl(alpha_l, mi) : 1.0f;
       }
-    auto store_tile = [&](auto inside_tag) {
+    auto store_tile = [&](auto inside_tag, auto nt_tag) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            finish(inside_tag, i, j, v, acc[i][j][v], ra[i][v], pb[j], CONV ? alm[i][v] : (j ? aln1 : aln0), j ? thn1 : thn0);
+            finish(inside_tag, nt_tag, i, j, v, acc[i][j][v], ra[i][v], pb[j], CONV ? alm[i][v] : (j ? aln1 : aln0), j ? thn1 : thn0);
     };
-    if (m0 + 32 * TM <= p.M && n0 + 32 * TN <= p.N) store_tile(std::true_type{});
-    else store_tile(std::false_type{});
+    if (m0 + 32 * TM <= p.M && n0 + 32 * TN <= p.N) {
+      if (p.nt) store_tile(std::true_type{}, std::true_type{});
+      else store_tile(std::true_type{}, std::false_type{});
+    } else {
+      store_tile(std::false_type{}, std::false_type{});
+    }
     return;
   }
 
@@ -539,10 +607,14 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #pragma unroll
         for (int e = 0; e < 4; ++e) alm[e] = __shfl(alpha_l, row0 + e);
       }
-      finish(std::false_type{}, i, j, 4 * q, tot.x, ra[0], cb, alm[0], th);
-      finish(std::false_type{}, i, j, 4 * q + 1, tot.y, ra[1], cb, alm[1], th);
-      finish(std::false_type{}, i, j, 4 * q + 2, tot.z, ra[2], cb, alm[2], th);
-      finish(std::false_type{}, i, j, 4 * q + 3, tot.w, ra[3], cb, alm[3], th);
+      auto put4 = [&](auto nt_tag) {
+        finish(std::false_type{}, nt_tag, i, j, 4 * q, tot.x, ra[0], cb, alm[0], th);
+        finish(std::false_type{}, nt_tag, i, j, 4 * q + 1, tot.y, ra[1], cb, alm[1], th);
+        finish(std::false_type{}, nt_tag, i, j, 4 * q + 2, tot.z, ra[2], cb, alm[2], th);
+        finish(std::false_type{}, nt_tag, i, j, 4 * q + 3, tot.w, ra[3], cb, alm[3], th);
+      };
+      if (OUT != kOutBits && p.nt) put4(std::true_type{});
+      else put4(std::false_type{});
     };
     if constexpr (FULL && HALF) {
       // Eight waves, fp16 partials (the fully connected layers): a wave has exactly kGroups / 8
@@ -624,14 +696,14 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 int gemm_fp4_half = 0;  // 2 = keep fp32 partials (tests of both forms)
 namespace {
 
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV>
+template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   constexpr int NB = TM * PL + TN, kStage = NB * 128, kGroups = TM * TN * 4, kCnt = (TM + TN) * 8;
   constexpr int part = HALF ? kGroups * 32 : kGroups * 64;
   constexpr int slot = (!SPLIT || kStage > part + kCnt) ? kStage : part + kCnt;
   const int waves = SPLIT ? S : tiles_per_wg;
   const size_t lds = (size_t)waves * slot * 16;
-  auto kern = gemm_fp4_kernel<TM, TN, PL, XNOR, OUT, SPLIT, HALF, CONV>;
+  auto kern = gemm_fp4_kernel<TM, TN, PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
   if (lds > 64 * 1024) {  // more than the default limit of dynamic LDS: raised once per device
     static bool raised[64] = {};
     int dev = 0;
@@ -644,7 +716,7 @@ hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t bloc
     }
   }
   note_kernel("gemm_fp4_kernel<%d,%d,%d,%s,%s%s> grid %lld x %d, K split %d%s, fp4", TM, TN, PL, XNOR ? "xnor" : "planes",
-              !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? ",conv" : "",
+              !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? (REG ? ",conv,reg" : ",conv") : (REG ? ",reg" : ""),
               (long long)blocks, 64 * waves, SPLIT ? S : 1, HALF ? " (fp16 partials)" : "");
 #ifdef BMX_FP4_STAMPS
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S, fp4_stamps);
@@ -668,17 +740,17 @@ void set_tile_order(Fp4Params& p) {
   p.div_last = make_fast_div((uint32_t)p.last_rows);
 }
 
-template <int PL, bool XNOR, int OUT, bool CONV = false>
+template <int PL, bool XNOR, int OUT, bool CONV = false, bool REG = false>
 hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   if (S > 1) {
     // a wave's partial sums are at most (its bits of K) x (2^PL - 1): whole numbers up to 2048
     // are exact in fp16
     const int64_t most = (int64_t)(p.g_base + (p.g_rem ? 1 : 0)) * 256 * ((1 << PL) - 1);
     if (most <= 2048 && gemm_fp4_half != 2)
-      return launch_tile<2, 2, PL, XNOR, OUT, true, true, CONV>(p, S, tiles_per_wg, blocks, s);
-    return launch_tile<2, 2, PL, XNOR, OUT, true, false, CONV>(p, S, tiles_per_wg, blocks, s);
+      return launch_tile<2, 2, PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+    return launch_tile<2, 2, PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
   }
-  return launch_tile<2, 2, PL, XNOR, OUT, false, false, CONV>(p, S, tiles_per_wg, blocks, s);
+  return launch_tile<2, 2, PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
 }
 
 }  // namespace
@@ -686,7 +758,18 @@ hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blo
 int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests of every split
 int gemm_fp4_tall = 0;   // 0 = automatic; 1 = never 128 x 64 of C per wave; 2 = wherever the form exists
 
-// Takes the problem when both operands have 16-byte aligned rows, sums stay exact in fp32, the
+// Waves that share a tile's K: eight while every CU gets at most one tile, four up to four_up_to tiles
+// (two workgroups of four waves are resident on a CU), one beyond, and one where K is shorter than
+// `least` words: a wave's share is then less than the reduction costs.  Powers of two, so that the
+// SIMDs of a CU stay level: 390 x 3329 x 5632 (371 tiles) takes 10.4 us over four waves, 15.1 over five,
+// 12.2 over three; a 5 x 5 convolution over 384 channels of 42 x 38 x 37 (474 tiles) 14.0 over four, 17.1 over
+// three, 20 undivided; 1272 x 2474 x 2046 (780 tiles) 10.3 undivided, 12.7 over two.
+static int choose_k_split(int64_t tiles, int kwords, int least, int four_up_to) {
+  if (kwords < least || tiles > four_up_to) return 1;
+  return tiles <= 256 ? 8 : 4;
+}
+
+// Takes the problem when sums stay exact in fp32, the
 // operands can be addressed with 32-bit byte offsets, and there are enough 64 x 64 tiles for
 // the tile shape to pay; false otherwise (the caller then uses the 32 x 32 kernel).
 bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t* rowsum, const uint64_t* B,
@@ -695,7 +778,10 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
                      hipError_t* err) {
   if (gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
   if (planes < 1 || planes > 2) return false;
-  if ((lda_w & 1) || (ldb_w & 1) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15)) return false;
+  // rows that do not start 16-byte aligned travel through registers (xnor products only: a k-bit
+  // product's operands are the library's own rows)
+  const bool reg = (lda_w & 1) || (ldb_w & 1) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
+  if (reg && rowsum) return false;
   if ((int64_t)K * ((1 << planes) - 1) >= ((int64_t)1 << 24)) return false;
   if ((int64_t)M * planes * lda_w * 8 >= ((int64_t)1 << 32) || (int64_t)N * ldb_w * 8 >= ((int64_t)1 << 32))
     return false;
@@ -703,7 +789,12 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
   if (((int64_t)M + 64) * ldc * (C_bits ? 2 : 1) >= ((int64_t)1 << 31)) return false;
   const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  if (gemm_engine != 5 && tiles < 64) return false;
+  const int Kwords = (int)words_for(K);
+  // Below 64 tiles, and below 300 while K is short, the 32 x 32 per wave kernel: four times the waves,
+  // and there is not enough K to give these tiles to several waves each (xnor products, us a call:
+  // 331 x 1790 x 553 6.1 against 7.8, 2075 x 464 x 1408 6.6 against 7.7; 358 x 3179 x 1152, 300 tiles,
+  // 8.4 against 7.9; 217 x 1566 x 4352 8.0 against 6.2).
+  if (gemm_engine != 5 && (tiles < 64 || (tiles < 300 && Kwords < 48 && !rowsum))) return false;
   if (tiles >= ((int64_t)1 << 28)) return false;
   Fp4Params p;
   p.A = A;
@@ -712,7 +803,7 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
   p.ldb_bytes = (uint32_t)(ldb_w * 8);
   p.M = M;
   p.N = N;
-  p.Kw = (int)words_for(K);
+  p.Kw = Kwords;
   p.Kreal = K;
   const int ngroups = (int)ceil_div(p.Kw, 4);
   p.tiles_m = tiles_m;
@@ -727,16 +818,12 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
   p.C_f32 = C_f32;
   p.C_bits = (uint32_t*)C_bits;
   p.ldc = (int)ldc;
+  p.nt = ldc % 32 == 0 && (((uintptr_t)C_i32 | (uintptr_t)C_f32) & 127) == 0;
   p.HoWo = p.Wo = p.Hp = p.Wpp = p.Cw = p.stride = 1;
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
-  // K split: about two waves per SIMD (2048 in all), at most eight per tile, and every wave
-  // keeps at least one 64-byte segment
-  int S = gemm_fp4_split;
-  if (S <= 0) {
-    S = (int)(2048 / tiles);
-    S = S > 8 ? 8 : S;
-  }
+  // (every wave of a split keeps at least one 64-byte segment)
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, 48, 512);
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;
@@ -750,21 +837,25 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
   // the two come out level except where a SIMD works through many tiles (half as many tile
   // starts and ends per MFMA): 8192^3 214 against 222 us, 4096^3 38.6 against 34.1 us.  Taken
   // from four rounds of tiles on.
-  if (planes == 1 && rowsum == nullptr && !C_bits && S == 1 && gemm_fp4_tall != 1 &&
+  if (planes == 1 && rowsum == nullptr && !C_bits && !reg && S == 1 && gemm_fp4_tall != 1 &&
       (gemm_fp4_tall == 2 || ceil_div(M, 128) * (int64_t)tiles_n >= 8192) &&
       ((int64_t)M + 128) * ldc < ((int64_t)1 << 31)) {
     p.tiles_m = (int)ceil_div(M, 128);
     set_tile_order(p);
     p.tiles_per_xcd = (int)ceil_div(ceil_div((int64_t)p.tiles_m * tiles_n, tiles_per_wg), 8);
     const int64_t tall_blocks = 8 * (int64_t)p.tiles_per_xcd;
-    if (C_i32) *err = launch_tile<4, 2, 1, true, kOutI32, false, false, false>(p, 1, tiles_per_wg, tall_blocks, s);
-    else *err = launch_tile<4, 2, 1, true, kOutF32, false, false, false>(p, 1, tiles_per_wg, tall_blocks, s);
+    if (C_i32) *err = launch_tile<4, 2, 1, true, kOutI32, false, false, false, false>(p, 1, tiles_per_wg, tall_blocks, s);
+    else *err = launch_tile<4, 2, 1, true, kOutF32, false, false, false, false>(p, 1, tiles_per_wg, tall_blocks, s);
     return true;
   }
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (planes == 1 && rowsum == nullptr) {
+  if (reg) {
+    if (C_bits) *err = launch_split<1, true, kOutBits, false, true>(p, S, tiles_per_wg, blocks, s);
+    else if (C_i32) *err = launch_split<1, true, kOutI32, false, true>(p, S, tiles_per_wg, blocks, s);
+    else *err = launch_split<1, true, kOutF32, false, true>(p, S, tiles_per_wg, blocks, s);
+  } else if (planes == 1 && rowsum == nullptr) {
     if (C_bits) *err = launch_split<1, true, kOutBits>(p, S, tiles_per_wg, blocks, s);
     else if (C_i32) *err = launch_split<1, true, kOutI32>(p, S, tiles_per_wg, blocks, s);
     else *err = launch_split<1, true, kOutF32>(p, S, tiles_per_wg, blocks, s);
@@ -777,8 +868,7 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
 }
 
 // The convolution on the same kernel (Xp, Wp as for launch_binary_conv2d).  Takes the problem when
-// every 16-byte piece of an im2col row is 16 consecutive bytes of the packed image (an even number
-// of channel words), rows are 16-byte aligned, and image and output fit 32-bit offsets.
+// the filter rows are 16-byte aligned, and image and output fit 32-bit offsets.
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
                      int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s,
                      hipError_t* err) {
@@ -790,7 +880,8 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t ld_words = conv_weight_row_words(kwords);
   const int64_t P = (int64_t)Nimg * Ho * Wo;
   const int Hp = H + 2 * pad, Wpp = W + 2 * pad;
-  if ((Cw & 1) || (ld_words & 1) || ((uintptr_t)Wp & 15) || ((uintptr_t)Xp & 15)) return false;
+  if ((ld_words & 1) || ((uintptr_t)Wp & 15)) return false;
+  const bool reg = (Cw & 1) || ((uintptr_t)Xp & 15);  // a piece is not 16 contiguous, aligned bytes: word by word
   if ((int64_t)kwords * 64 >= ((int64_t)1 << 24)) return false;
   if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= ((int64_t)1 << 32) || (int64_t)O * ld_words * 8 >= ((int64_t)1 << 32))
     return false;
@@ -820,21 +911,21 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   p.C_f32 = out_f32;
   p.C_bits = nullptr;
   p.ldc = 0;
+  p.nt = Ho * Wo % 32 == 0 && (((uintptr_t)out_i32 | (uintptr_t)out_f32) & 127) == 0;
   p.HoWo = Ho * Wo;
   p.Wo = Wo;
   p.Hp = Hp;
   p.Wpp = Wpp;
   p.Cw = Cw;
   p.stride = stride;
-  p.run_pieces = (uint32_t)(KW * Cw / 2);
+  p.run_pieces = (uint32_t)(reg ? KW * Cw : KW * Cw / 2);
   p.row_bytes = (uint32_t)((int64_t)Wpp * Cw * 8);
-  p.npieces = (uint32_t)(kwords / 2);
+  p.npieces = (uint32_t)(reg ? kwords : kwords / 2);
   p.div_howo = make_fast_div((uint32_t)(Ho * Wo));
   p.div_wo = make_fast_div((uint32_t)Wo);
   p.div_run = make_fast_div(p.run_pieces);
-  // K split: about two waves per SIMD; a wave may carry a single group of 256 bits
-  int S = gemm_fp4_split;
-  if (S <= 0) S = (int)ceil_div(2048, tiles);
+  // (a wave may carry a single group of 256 bits)
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, kwords, 0, kwords >= 75 ? 1100 : 512);
   S = S > 8 ? 8 : S;
   if (S > ngroups) S = ngroups;
   if (S < 1) S = 1;
@@ -844,7 +935,9 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
+  if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, true>(p, S, tiles_per_wg, blocks, s);
+  else if (reg) *err = launch_split<1, true, kOutF32, true, true>(p, S, tiles_per_wg, blocks, s);
+  else if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
   else *err = launch_split<1, true, kOutF32, true>(p, S, tiles_per_wg, blocks, s);
   return true;
 }

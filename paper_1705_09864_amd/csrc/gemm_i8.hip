@@ -243,8 +243,8 @@ gemm_i8_kernel(const I8Params p) {
         sv = (int)((uint32_t)p.scale * ((uint32_t)d[e] + (uint32_t)p.ca * (uint32_t)cb) +
                    (uint32_t)p.rs * ((uint32_t)ra[e] + (uint32_t)p.ca * (uint32_t)p.Kreal));
       const int64_t idx = (int64_t)m * p.ldc + n;
-      if (p.C_i32) __builtin_nontemporal_store(sv, p.C_i32 + idx);
-      if (p.C_f32) __builtin_nontemporal_store((float)sv / p.denom, p.C_f32 + idx);
+      if (p.C_i32) p.C_i32[idx] = sv;
+      if (p.C_f32) p.C_f32[idx] = (float)sv / p.denom;
     }
   };
   if (S == 1) {

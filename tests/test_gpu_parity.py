@@ -1159,3 +1159,45 @@ def test_conv_fp4_lds_staged_kernel(split):
             np.testing.assert_array_equal(got_i, ri)
             assert_f32_close(run_conv(x, w, s, p, alpha=alpha), rf)
             np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))
+
+
+@pytest.mark.parametrize("M,N,K,off", [(512, 1024, 4096 - 64, 0), (700, 1900, 1, 0), (650, 2000, 129, 0), (520, 600, 64 * 49 - 3, 0),
+                                       (1100, 1700, 64 * 7, 0), (640, 1300, 4096, 1), (333, 4001, 64 * 61, 1)])
+def test_gemm_fp4_rows_through_registers(M, N, K, off):
+    """Operand rows of an odd number of words, or an even number behind a base that is only 8-byte
+    aligned, on the 64 x 64 per wave kernel: with and without a K split, K tails inside a segment,
+    output rows that are whole 128-byte lines and that are not; int32, fp32 and packed bits."""
+    rng = np.random.default_rng(M + N + K)
+    a, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    alpha, thr = rng.standard_normal(N).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+
+    def rows(m):
+        words = (K + 63) // 64
+        flat = torch.full((m.shape[0] * words + off,), -1, dtype=torch.int64, device="cuda")
+        return B.binarize_pack(dev(m), 1, out=flat[off:].view(m.shape[0], words))
+
+    A, W = rows(a), rows(w)
+    ri, rf = oracle.binary_fc(a, w, alpha)
+    with tuned(k7=5):
+        np.testing.assert_array_equal(B.xnor_gemm(A, W, K).cpu().numpy(), ri)
+        assert "reg" in B.last_kernel()
+        np.testing.assert_array_equal(B.binary_fc_packed(A, K, W, alpha=dev(alpha)).cpu().numpy(), rf)
+        bits = B.binary_fc_packed(A, K, W, alpha=dev(alpha), mode="bits", thr=dev(thr))
+    ref = np.where(rf >= thr[None, :], np.float32(1), np.float32(-1))
+    np.testing.assert_array_equal(bits.cpu().numpy(), B.binarize_pack(dev(ref), 1).cpu().numpy())
+    np.testing.assert_array_equal(B.xnor_gemm(A, W, K, count=True).cpu().numpy(), (ri + K) // 2)
+
+
+@pytest.mark.parametrize("N,C,H,W,O,k,s,p", [(6, 300, 20, 21, 80, 3, 1, 1), (30, 150, 17, 18, 130, 5, 2, 2), (12, 140, 24, 25, 70, 7, 1, 0),
+                                             (40, 190, 20, 20, 64, 1, 1, 0), (3, 420, 40, 41, 200, 3, 1, 0)])
+def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
+    """The 64 x 64 per wave convolution where the image has an odd number of channel words (its
+    16-byte pieces straddle taps and kernel rows), at sizes the dispatch sends there."""
+    rng = np.random.default_rng(N + C + H + O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha = rng.standard_normal(O).astype(np.float32)
+    Wp = B.pack_conv_weights(dev(w))
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
+    assert "conv,reg" in B.last_kernel()
+    np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)

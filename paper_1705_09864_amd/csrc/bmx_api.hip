@@ -3,6 +3,7 @@
 // ran and no output byte was written.  The contract of each call is in include/bmx.h.
 #include "../../include/bmx.h"
 #include "bmx_internal.h"
+#include "lazy_calls.h"
 
 #include <mutex>
 
@@ -307,14 +308,16 @@ int fc_check(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, con
   return BMX_OK;
 }
 
-// Pack the activations into chunk-padded rows at xp (the scalar side of the GEMM kernel reads
-// whole chunks), then the GEMM with the epilogue.
+// In one launch where the layer is small enough, else pack the activations into chunk-padded rows at
+// xp (the scalar side of the GEMM kernel reads whole chunks), then the GEMM with the epilogue.  xp null:
+// BMX_ERR_WORKSPACE, with nothing launched, where it is needed.
 int fc_launch(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
               int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, uint64_t* xp,
               hipStream_t s) {
   hipError_t small = hipSuccess;  // a layer of a few microseconds or less: one launch, no workspace
   if (bmx::launch_fc_small(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo, s, &small))
     return hip_status(small);
+  if (!xp) return BMX_ERR_WORKSPACE;
   const int64_t ldp = bmx::padded_words(in_features);
   hipError_t e = bmx::launch_pack_rows_padded(x, batch, in_features, ldx, xp, ldp, s);
   if (e != hipSuccess) return BMX_ERR_HIP;
@@ -324,19 +327,35 @@ int fc_launch(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, co
 }
 }  // namespace
 
+static int binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
+                     int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, void* workspace,
+                     size_t workspace_bytes, void* stream, bool lazy) {
+  const int rc = fc_check(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo);
+  if (rc != BMX_OK) return rc;
+  if (batch == 0 || out_features == 0) return BMX_OK;
+  if (!lazy || workspace) {
+    const int64_t dims[3] = {batch, in_features, out_features};
+    const size_t need = bmx_workspace_bytes(BMX_OP_BINARY_FC, dims, 3);
+    if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
+    if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  }
+  return fc_launch(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo,
+                   (uint64_t*)workspace, (hipStream_t)stream);
+}
+
 int bmx_binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w,
                   const float* alpha, int batch, int in_features, int out_features,
                   int32_t* out_i32, float* out_f32, int64_t ldo, void* workspace,
                   size_t workspace_bytes, void* stream) {
-  const int rc = fc_check(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo);
-  if (rc != BMX_OK) return rc;
-  if (batch == 0 || out_features == 0) return BMX_OK;
-  const int64_t dims[3] = {batch, in_features, out_features};
-  const size_t need = bmx_workspace_bytes(BMX_OP_BINARY_FC, dims, 3);
-  if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
-  if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
-  return fc_launch(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo,
-                   (uint64_t*)workspace, (hipStream_t)stream);
+  return binary_fc(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo, workspace,
+                   workspace_bytes, stream, false);
+}
+
+int bmx_lazy_binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
+                       int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, void* workspace,
+                       size_t workspace_bytes, void* stream) {
+  return binary_fc(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo, workspace,
+                   workspace_bytes, stream, true);
 }
 
 int bmx_binary_fc_static(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w,
@@ -499,9 +518,9 @@ int bmx_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t
                                   out_f32, stream);
 }
 
-int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,
-                   int bits_w, int M, int N, int K, int32_t* out_i32_scaled, float* out_f32,
-                   int64_t ldo, void* workspace, size_t workspace_bytes, void* stream) {
+static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,
+                      int bits_w, int M, int N, int K, int32_t* out_i32_scaled, float* out_f32,
+                      int64_t ldo, void* workspace, size_t workspace_bytes, void* stream, bool lazy) {
   if (M < 0 || N < 0) return BMX_ERR_SHAPE;
   if (K <= 0 || K >= kMaxK) return BMX_ERR_SHAPE;
   if (bits_a < 1 || bits_a > 8 || bits_w < 1 || bits_w > 8) return BMX_ERR_UNSUPPORTED;
@@ -516,12 +535,18 @@ int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int6
       misaligned(out_f32, 4))
     return BMX_ERR_ALIGN;
   const QuantWs q = quant_ws(M, N, K, bits_a, bits_w);
-  if (!workspace || workspace_bytes < q.total) return BMX_ERR_WORKSPACE;
-  if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  if (!lazy || workspace) {
+    if (!workspace || workspace_bytes < q.total) return BMX_ERR_WORKSPACE;
+    if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  }
   hipStream_t s = (hipStream_t)stream;
-  hipError_t i8 = hipSuccess;  // more bits than the FP4 form holds: bytes on the matrix cores
-  if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, s, &i8))
-    return hip_status(i8);
+  hipError_t direct = hipSuccess;
+  if (bmx::launch_quant_small(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, s, &direct))
+    return hip_status(direct);
+  if (!workspace) return BMX_ERR_WORKSPACE;
+  // more bits than the FP4 form holds: bytes on the matrix cores
+  if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, s, &direct))
+    return hip_status(direct);
   char* ws = (char*)workspace;
   uint64_t* planes = (uint64_t*)(ws + q.planes_off);
   uint64_t* wb = (uint64_t*)(ws + q.wb_off);
@@ -550,6 +575,20 @@ int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int6
   if (e != hipSuccess) return BMX_ERR_HIP;
   return hip_status(bmx::launch_plane_gemm((const uint32_t*)planes, ldp * 2, bits_a, rowsum, wb, even_words(Kw),
                                            M, N, K, out_i32_scaled, out_f32, ldo, s));
+}
+
+int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,
+                   int bits_w, int M, int N, int K, int32_t* out_i32_scaled, float* out_f32,
+                   int64_t ldo, void* workspace, size_t workspace_bytes, void* stream) {
+  return quant_gemm(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, workspace_bytes,
+                    stream, false);
+}
+
+int bmx_lazy_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
+                        int K, int32_t* out_i32_scaled, float* out_f32, int64_t ldo, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+  return quant_gemm(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, workspace_bytes,
+                    stream, true);
 }
 
 int bmx_alpha_mean_abs(const float* w, int64_t rows, int64_t cols, int64_t ldw, float* alpha,

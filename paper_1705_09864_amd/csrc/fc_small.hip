@@ -218,6 +218,8 @@ Lanes lanes_for(int64_t Kw) {
   return {64, ceil_div(n, 3) * 3 < ceil_div(n, 4) * 4 ? 3 : 4};
 }
 
+inline int64_t shift_up(int64_t n, int log) { return (n + ((int64_t)1 << log) - 1) >> log; }
+
 template <int RM>
 void launch_rm(const FcSmallParams& p, Lanes l, dim3 grid, hipStream_t s) {
   const size_t lds = (size_t)RM * p.Kpad * 8;
@@ -254,21 +256,23 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   const int64_t Kpad = ceil_div(Kw, lanes.W * lanes.L) * lanes.W * lanes.L;
   // Rows and features per workgroup: the pair that leaves the busiest CU the least to move (fp32 rows
   // and packed weights of its workgroups, and a fixed share per workgroup for its latencies).
-  int64_t best = INT64_MAX, rm = 1, cols = 16;
-  for (int64_t r = 1; r <= 8; r *= 2) {
-    if (r > 1 && (r / 2 >= batch || r * Kpad * 8 > 48 * 1024)) break;
-    for (int64_t c = 16; c <= 512; c *= 2) {
-      if (c > 16 && c / 2 >= out_features) break;
-      const int64_t wgs = ceil_div(batch, r) * ceil_div(out_features, c);
-      const int64_t cost = ceil_div(wgs, 256) * (r * in_features * 4 + c * Kw * 8 + 4 * r * c * Kpad + (16 << 10));
-      if (cost < best) best = cost, rm = r, cols = c;
+  int64_t best = INT64_MAX;
+  int rm_log = 0, cols_log = 4;
+  for (int r = 0; r <= 3; ++r) {
+    if (r > 0 && (((int64_t)1 << r) / 2 >= batch || (Kpad * 8 << r) > 48 * 1024)) break;
+    for (int c = 4; c <= 9; ++c) {
+      if (c > 4 && (1 << c) / 2 >= out_features) break;
+      const int64_t wgs = shift_up(batch, r) * shift_up(out_features, c);
+      const int64_t cost = shift_up(wgs, 8) * (((int64_t)in_features * 4 << r) + (Kw * 8 << c) + (4 * Kpad << (r + c)) + (16 << 10));
+      if (cost < best) best = cost, rm_log = r, cols_log = c;
     }
   }
   // Level with two launches at about 384 KB (608 x 771 -> 1487, 348 KB: 7.6 against 11.4 us; 12 x 8385
   // -> 3257, 405 KB: 8.8 against 9.2 us; 490 x 3356 -> 829, 738 KB: 14.3 against 12.8 us).  A few
   // workgroups have the memory system to themselves, and the general path's one or two tiles take a
   // chain as long (2 x 65536 -> 16: 7.0 against 16.2 us).
-  const int64_t wgs = ceil_div(batch, rm) * ceil_div(out_features, cols);
+  const int rm = 1 << rm_log, cols = 1 << cols_log;
+  const int64_t wgs = shift_up(batch, rm_log) * shift_up(out_features, cols_log);
   if (best > (wgs <= 32 ? 768 << 10 : 384 << 10)) return false;
   FcSmallParams p;
   p.x = x;
@@ -281,7 +285,7 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   p.K = in_features;
   p.Kw = (int)Kw;
   p.Kpad = (int)Kpad;
-  p.cols = (int)cols;
+  p.cols = cols;
   p.out_i32 = out_i32;
   p.out_f32 = out_f32;
   p.ldo = ldo;

@@ -3,7 +3,7 @@
 // integer (sign for one bit, 2 q_w - L_w above).
 //
 // Taken where an operand has more bits than the FP4 form of gemm_fp4.hip folds into a nibble (more
-// than two for the activations, more than one for the weights).  Walked plane by plane with AND +
+// than two for the activations, more than one for the weights), and for small products of any.  Walked plane by plane with AND +
 // popcount, such a product costs bits_a * bits_w passes over K on the vector ALU (4 x 4 bits, 500 x
 // 1000 x 2304: 67 us, and a 16 MB array of per-plane results to add up afterwards, 5 us).  As bytes
 // it is one pass on the matrix cores, whatever the bits.
@@ -20,6 +20,8 @@
 // l % 32, half l / 32 of the step.  Every operand load is one contiguous KiB, no LDS, no
 // transposition.  K is zero padded to whole blocks of 256, rows to whole blocks of 32.
 #include "bmx_internal.h"
+
+#include <algorithm>
 
 namespace bmx {
 
@@ -45,23 +47,46 @@ struct QuantOperand {
   uint4* tiles;
 };
 
+// Four values of an operand as four bytes, the first lowest.
+__device__ __forceinline__ uint32_t quant_bytes(const QuantOperand& o, float x, float y, float z, float w) {
+#pragma clang fp contract(off)  // (the rest of the rounded product L * u, not of the exact one, decides a tie)
+  const float v[4] = {x, y, z, w};
+  uint32_t d = 0;
+  // Rounding half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32: with 0.5 itself the
+  // one value 0.5 - 2^-25 would round up.  The byte is made in fp32 (whole numbers up to 255) with
+  // 128 added, so that it is never negative, and the 128 goes again as the flip of its top bit.
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float u = fminf(fmaxf((v[e] + o.c0) * o.c1, 0.0f), 1.0f) * o.L;
+    d = __builtin_amdgcn_cvt_pk_u8_f32(truncf(u + 0x1.fffffep-2f) * o.mul + o.add, e, d);
+  }
+  return d ^ 0x80808080u;
+}
+__device__ __forceinline__ uint32_t sign_bytes(float x, float y, float z, float w) {
+  return (x >= 0.0f ? 1u : 255u) | (y >= 0.0f ? 1u : 255u) << 8 | (z >= 0.0f ? 1u : 255u) << 16 | (w >= 0.0f ? 1u : 255u) << 24;
+}
+// Bytes of a dword that lie inside a row with `left` elements to go.
+__device__ __forceinline__ uint32_t byte_mask(int left) {
+  return left >= 4 ? 0xffffffffu : (left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+}
+// Four floats at any 4-byte aligned address in one load.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 struct QuantTilesParams {
   QuantOperand op[2];
   int K, kblocks;      // blocks of 256
   FastDiv div_kblocks;
   int blocks0;         // workgroups of operand 0
-  int vec;             // rows of both operands start 16-byte aligned
 };
 
 constexpr int kTileWaves = 8, kTileRows = 32 / kTileWaves;  // rows of the block per wave
 
 __global__ void __launch_bounds__(64 * kTileWaves)
 quant_tiles_kernel(const QuantTilesParams p) {
-#pragma clang fp contract(off)  // (the rest of the rounded product L * u, not of the exact one, decides a tie)
   __shared__ uint32_t t[16 * kTileRow];
   // (all arguments named at the top: fetched in one batch, one trip to memory instead of one per group)
   asm volatile("" ::"s"(p.blocks0), "s"(p.div_kblocks.mul), "s"(p.op[0].x), "s"(p.op[0].ld), "s"(p.op[0].L), "s"(p.op[0].tiles),
-               "s"(p.op[1].x), "s"(p.op[1].ld), "s"(p.op[1].L), "s"(p.op[1].tiles), "s"(p.K), "s"(p.vec));
+               "s"(p.op[1].x), "s"(p.op[1].ld), "s"(p.op[1].L), "s"(p.op[1].tiles), "s"(p.K));
   const bool second = (int)blockIdx.x >= p.blocks0;
   QuantOperand o = p.op[0];
   if (second) o = p.op[1];
@@ -75,11 +100,11 @@ quant_tiles_kernel(const QuantTilesParams p) {
   const float* const x = o.x + k0;
   const int64_t ld = o.ld;
   const int last = o.rows - 1;
-  if (p.vec && kb * 256 + 256 <= p.K) {  // workgroup-uniform
+  if (kb * 256 + 256 <= p.K) {  // workgroup-uniform
 #pragma unroll
     for (int j = 0; j < kTileRows; ++j) {
-      const float4 f = *(const float4*)(x + (int64_t)min(row0 + j, last) * ld);
-      v[j][0] = f.x, v[j][1] = f.y, v[j][2] = f.z, v[j][3] = f.w;
+      const v4f_any f = *(const v4f_any*)(x + (int64_t)min(row0 + j, last) * ld);
+      v[j][0] = f[0], v[j][1] = f[1], v[j][2] = f[2], v[j][3] = f[3];
     }
   } else {
 #pragma unroll
@@ -88,32 +113,14 @@ quant_tiles_kernel(const QuantTilesParams p) {
       for (int e = 0; e < 4; ++e)  // (elements past the row read its last and are masked below)
         v[j][e] = o.x[(int64_t)min(row0 + j, last) * ld + min(k0 + e, p.K - 1)];
   }
-  const int left = p.K - k0;  // valid elements of this lane's four
-  const uint32_t mask = left >= 4 ? 0xffffffffu : (left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+  const uint32_t mask = byte_mask(p.K - k0);
   uint32_t* const dst = &t[(lane >> 2) * kTileRow + wave * (4 * kTileRows) + (lane & 3)];
   if (o.sign) {
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j) {
-      uint32_t d = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) d |= (v[j][e] >= 0.0f ? 1u : 255u) << (8 * e);
-      dst[4 * j] = d & mask;
-    }
+    for (int j = 0; j < kTileRows; ++j) dst[4 * j] = sign_bytes(v[j][0], v[j][1], v[j][2], v[j][3]) & mask;
   } else {
-    // Rounding half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32: with 0.5 itself the
-    // one value 0.5 - 2^-25 would round up.  The byte is made in fp32 (whole numbers up to 255) with
-    // 128 added, so that it is never negative, and the 128 goes again as the flip of its top bit.
-    const float c0 = o.c0, c1 = o.c1, L = o.L, mul = o.mul, add = o.add;
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j) {
-      uint32_t d = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float u = fminf(fmaxf((v[j][e] + c0) * c1, 0.0f), 1.0f) * L;
-        d = __builtin_amdgcn_cvt_pk_u8_f32(truncf(u + 0x1.fffffep-2f) * mul + add, e, d);
-      }
-      dst[4 * j] = (d ^ 0x80808080u) & mask;
-    }
+    for (int j = 0; j < kTileRows; ++j) dst[4 * j] = quant_bytes(o, v[j][0], v[j][1], v[j][2], v[j][3]) & mask;
   }
   __syncthreads();
   // half tile 2 s + h of the block is t[(2 s + h) * kTileRow ...]: row r at dword 4 r
@@ -150,14 +157,101 @@ struct Group {
   v4i a[kAhead][TM], b[kAhead][TN];
 };
 
+// The tile's end: operand sums of the two half-waves, the partial tiles of the S waves of a workgroup
+// through LDS (S > 1, at most MAXS), the 8-bit correction, stores.
+template <int TM, int TN, bool SUMS, int MAXS>
+__device__ __forceinline__ void finish_tile(const I8Params& p, const v16i (&acc)[TM][TN], int (&sa)[TM], int (&sb)[TN],
+                                            int* red, int lane, int wave, int tile_m, int tile_n) {
+  constexpr int kGroups = TM * TN * 4;
+  const int r = lane & 31, h = lane >> 5, S = p.S;
+  if (SUMS) {  // a lane summed its half of every k step
+#pragma unroll
+    for (int i = 0; i < TM; ++i) sa[i] += __shfl_xor(sa[i], 32);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sb[j] += __shfl_xor(sb[j], 32);
+  }
+
+  // Register v of lane (r, h) in block (i, j) is C[32 i + 8 (v / 4) + 4 h + v % 4][32 j + r];
+  // group g = (i * TN + j) * 4 + v / 4: four rows of one column.
+  auto finish = [&](int g, const int (&d)[4], const int (&ra)[4], int cb) {
+    const int blk = g >> 2, i = blk / TN, j = blk % TN;
+    const int n = (tile_n * TN + j) * 32 + r;
+    if (n >= p.N) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = (tile_m * TM + i) * 32 + 8 * (g & 3) + 4 * h + e;
+      if (m >= p.M) continue;
+      int sv = d[e];
+      if (SUMS)
+        sv = (int)((uint32_t)p.scale * ((uint32_t)d[e] + (uint32_t)p.ca * (uint32_t)cb) +
+                   (uint32_t)p.rs * ((uint32_t)ra[e] + (uint32_t)p.ca * (uint32_t)p.Kreal));
+      const int64_t idx = (int64_t)m * p.ldc + n;
+      if (p.C_i32) p.C_i32[idx] = sv;
+      if (p.C_f32) p.C_f32[idx] = (float)sv / p.denom;
+    }
+  };
+  if (S == 1) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      const int i = (g >> 2) / TN, j = (g >> 2) % TN, q = g & 3;
+      int d[4], ra[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        d[e] = acc[i][j][4 * q + e];
+        ra[e] = SUMS ? __shfl(sa[i], 8 * q + 4 * h + e) : 0;
+      }
+      finish(g, d, ra, sb[j]);
+    }
+    return;
+  }
+  v4i* part = (v4i*)red;                       // [S][kGroups][64]
+  int* sums = red + S * kGroups * 64 * 4;      // [S][32 (TM + TN)]
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v4i d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = acc[i][j][4 * q + e];
+        part[(wave * kGroups + (i * TN + j) * 4 + q) * 64 + lane] = d;
+      }
+  if (SUMS && h == 0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) sums[wave * 32 * (TM + TN) + 32 * i + r] = sa[i];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) sums[wave * 32 * (TM + TN) + 32 * (TM + j) + r] = sb[j];
+  }
+  __syncthreads();
+  for (int g = wave; g < kGroups; g += S) {
+    v4i t[MAXS];
+#pragma unroll
+    for (int s = 0; s < MAXS; ++s) t[s] = part[(min(s, S - 1) * kGroups + g) * 64 + lane];
+    int d[4] = {}, ra[4] = {}, cb = 0;
+#pragma unroll
+    for (int s = 0; s < MAXS; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] += s < S ? t[s][e] : 0;
+    if (SUMS) {
+      const int i = (g >> 2) / TN, j = (g >> 2) % TN;
+      for (int s = 0; s < S; ++s) {
+        const int* w = sums + s * 32 * (TM + TN);
+        cb += w[32 * (TM + j) + r];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ra[e] += w[32 * i + 8 * (g & 3) + 4 * h + e];
+      }
+    }
+    finish(g, d, ra, cb);
+  }
+}
+
 template <int TM, int TN, bool SUMS>
 __global__ void __launch_bounds__(512)
 gemm_i8_kernel(const I8Params p) {
   extern __shared__ int red[];
-  constexpr int kGroups = TM * TN * 4;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = lane & 31, h = lane >> 5;
   // workgroup b sits on XCD b % 8: every XCD gets a contiguous run of tiles, rows of C fastest
   const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
   if (lin >= p.tiles) return;  // (the whole workgroup)
@@ -221,86 +315,86 @@ gemm_i8_kernel(const I8Params p) {
       multiply(g1, k + kAhead);
     }
   }
-  if (SUMS) {  // a lane summed its half of every k step
-#pragma unroll
-    for (int i = 0; i < TM; ++i) sa[i] += __shfl_xor(sa[i], 32);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) sb[j] += __shfl_xor(sb[j], 32);
-  }
+  finish_tile<TM, TN, SUMS, 8>(p, acc, sa, sb, red, lane, wave, tile_m, tile_n);
+}
 
-  // Register v of lane (r, h) in block (i, j) is C[32 i + 8 (v / 4) + 4 h + v % 4][32 j + r];
-  // group g = (i * TN + j) * 4 + v / 4: four rows of one column.
-  auto finish = [&](int g, const int (&d)[4], const int (&ra)[4], int cb) {
-    const int blk = g >> 2, i = blk / TN, j = blk % TN;
-    const int n = (tile_n * TN + j) * 32 + r;
-    if (n >= p.N) return;
+// ---- the whole product in one launch, for problems small enough that a second launch costs more
+// than quantising a row once per tile of results.  A wave takes its 16 values per lane straight from the
+// fp32 rows (lane (r, h): k = 16 h .. 16 h + 15 of a step of 32, row r: a 64-byte run, the half-waves'
+// two make whole lines), quantises them in registers and multiplies; up to 16 waves split a tile's K.
+struct QuantSmallParams {
+  I8Params g;
+  QuantOperand a, w;
+};
+
+__device__ __forceinline__ void load_values(const float* row, int k0, int K, v4f_any (&v)[4]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = (tile_m * TM + i) * 32 + 8 * (g & 3) + 4 * h + e;
-      if (m >= p.M) continue;
-      int sv = d[e];
-      if (SUMS)
-        sv = (int)((uint32_t)p.scale * ((uint32_t)d[e] + (uint32_t)p.ca * (uint32_t)cb) +
-                   (uint32_t)p.rs * ((uint32_t)ra[e] + (uint32_t)p.ca * (uint32_t)p.Kreal));
-      const int64_t idx = (int64_t)m * p.ldc + n;
-      if (p.C_i32) p.C_i32[idx] = sv;
-      if (p.C_f32) p.C_f32[idx] = (float)sv / p.denom;
+  for (int q = 0; q < 4; ++q) {
+    if (k0 + 4 * q + 4 <= K) {
+      v[q] = *(const v4f_any*)(row + k0 + 4 * q);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = row[min(k0 + 4 * q + e, K - 1)];
     }
-  };
-  if (S == 1) {
+  }
+}
+__device__ __forceinline__ v4i make_bytes(const QuantOperand& o, const v4f_any (&v)[4], int left) {
+  v4i b;
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-      const int i = (g >> 2) / TN, j = (g >> 2) % TN, q = g & 3;
-      int d[4], ra[4];
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t d = o.sign ? sign_bytes(v[q][0], v[q][1], v[q][2], v[q][3]) : quant_bytes(o, v[q][0], v[q][1], v[q][2], v[q][3]);
+    b[q] = (int)(d & byte_mask(left - 4 * q));
+  }
+  return b;
+}
+
+template <bool SUMS, bool SIGN>
+__global__ void __launch_bounds__(1024)
+quant_small_kernel(const QuantSmallParams p) {
+  extern __shared__ int red[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  const int tile_n = (int)blockIdx.x / p.g.tiles_m, tile_m = (int)blockIdx.x - tile_n * p.g.tiles_m;
+  const int k_lo = wave * p.g.nk / p.g.S, k_hi = (wave + 1) * p.g.nk / p.g.S, K = p.g.Kreal;
+  // (rows past a matrix repeat its last; their results are never stored)
+  const float* arow = p.a.x + (int64_t)min(tile_m * 32 + r, p.g.M - 1) * p.a.ld;
+  const float* wrow = p.w.x + (int64_t)min(tile_n * 32 + r, p.g.N - 1) * p.w.ld;
+  v16i acc[1][1];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[0][0][e] = 0;
+  int sa[1] = {}, sb[1] = {};
+  QuantOperand oa = p.a, ow = p.w;
+  oa.sign = 0;
+  ow.sign = SIGN ? 1 : 0;
+  v4f_any va[2][4], vw[2][4];
+  auto load = [&](int i, int k) {
+    load_values(arow, 32 * k + 16 * h, K, va[i]);
+    load_values(wrow, 32 * k + 16 * h, K, vw[i]);
+  };
+  auto multiply = [&](int i, int k) {
+    const int left = K - (32 * k + 16 * h);
+    const v4i a = make_bytes(oa, va[i], left), b = make_bytes(ow, vw[i], left);
+    if (SUMS) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        d[e] = acc[i][j][4 * q + e];
-        ra[e] = SUMS ? __shfl(sa[i], 8 * q + 4 * h + e) : 0;
-      }
-      finish(g, d, ra, sb[j]);
-    }
-    return;
-  }
-  v4i* part = (v4i*)red;                       // [S][kGroups][64]
-  int* sums = red + S * kGroups * 64 * 4;      // [S][32 (TM + TN)]
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v4i d;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) d[e] = acc[i][j][4 * q + e];
-        part[(wave * kGroups + (i * TN + j) * 4 + q) * 64 + lane] = d;
-      }
-  if (SUMS && h == 0) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) sums[wave * 32 * (TM + TN) + 32 * i + r] = sa[i];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) sums[wave * 32 * (TM + TN) + 32 * (TM + j) + r] = sb[j];
-  }
-  __syncthreads();
-  for (int g = wave; g < kGroups; g += S) {
-    v4i t[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) t[s] = part[(min(s, S - 1) * kGroups + g) * 64 + lane];
-    int d[4] = {}, ra[4] = {}, cb = 0;
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) d[e] += s < S ? t[s][e] : 0;
-    if (SUMS) {
-      const int i = (g >> 2) / TN, j = (g >> 2) % TN;
-      for (int s = 0; s < S; ++s) {
-        const int* w = sums + s * 32 * (TM + TN);
-        cb += w[32 * (TM + j) + r];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ra[e] += w[32 * i + 8 * (g & 3) + 4 * h + e];
+        sa[0] = __builtin_amdgcn_sdot4(a[e], 0x01010101, sa[0], false);
+        sb[0] = __builtin_amdgcn_sdot4(b[e], 0x01010101, sb[0], false);
       }
     }
-    finish(g, d, ra, cb);
+    acc[0][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[0][0], 0, 0, 0);
+  };
+  if (k_lo < k_hi) {
+    load(0, k_lo);
+    for (int k = k_lo; k < k_hi; k += 2) {
+      load(1, min(k + 1, k_hi - 1));
+      multiply(0, k);
+      if (k + 1 >= k_hi) break;
+      load(0, min(k + 2, k_hi - 1));
+      multiply(1, k + 1);
+    }
   }
+  finish_tile<1, 1, SUMS, 16>(p.g, acc, sa, sb, red, lane, wave, tile_m, tile_n);
 }
 
 template <int TM, int TN, bool SUMS>
@@ -327,10 +421,12 @@ int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * c
 }  // namespace
 
 // Workspace of the two tiled operands, and whether the problem is taken: an operand of more bits than
-// the FP4 form holds, and a result that fills a quarter of a 32 x 32 block (below that the padding of
+// the FP4 form holds, or a product so small that reading bytes costs nothing and the plane pack and its
+// GEMM are the slower pair (2 x 1 bits, us a call: 64 x 907 x 256 11.2 -> 7.0, 475 x 1088 x 832 12.6 -> 8.5,
+// 360 x 1408 x 1600 14.5 -> 14.1; 1024 x 1024 x 4096 15.2 against 19.0); and a result that fills a quarter of a 32 x 32 block (below that the padding of
 // the tiles is most of what is moved, and the plane kernels' workspace is smaller).
 bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes) {
-  if (bits_a <= 2 && bits_w == 1) return false;
+  if (bits_a <= 2 && bits_w == 1 && M * N * K >= 1000000000) return false;
   if (M * N < 256) return false;
   const int64_t a = tile_bytes(M, K), b = tile_bytes(N, K);
   *bytes = (size_t)(a + b);
@@ -339,41 +435,87 @@ bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, siz
          ceil_div(M, 32) * ceil_div(K, 256) + ceil_div(N, 32) * ceil_div(K, 256) < ((int64_t)1 << 30);
 }
 
-bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
-                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, hipStream_t s, hipError_t* err) {
-  size_t need;
-  if (gemm_engine == 1 || !quant_i8_takes(M, N, K, bits_a, bits_w, &need)) return false;
-  QuantTilesParams q;
-  q.K = K;
-  q.kblocks = (int)ceil_div(K, 256);
-  q.div_kblocks = make_fast_div((uint32_t)q.kblocks);
-  const int mblocks = (int)ceil_div(M, 32), nblocks = (int)ceil_div(N, 32);
-  const int La = (1 << bits_a) - 1, Lw = (1 << bits_w) - 1;
-  q.op[0] = {a, lda, M, 0, 0.0f, 1.0f, (float)La, 1.0f, bits_a == 8 ? 0.0f : 128.0f, (uint4*)workspace};
-  q.op[1] = {w, ldw, N, bits_w == 1 ? 1 : 0, 1.0f, 0.5f, (float)Lw, bits_w == 8 ? 1.0f : 2.0f, bits_w == 8 ? 0.0f : 128.0f - (float)Lw,
-             (uint4*)((char*)workspace + tile_bytes(M, K))};
-  q.blocks0 = mblocks * q.kblocks;
-  q.vec = !(lda & 3) && !(ldw & 3) && !((uintptr_t)a & 15) && !((uintptr_t)w & 15);
-  hipLaunchKernelGGL(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
-  *err = hipGetLastError();
-  if (*err != hipSuccess) return true;
+namespace {
 
-  I8Params p;
-  p.A = q.op[0].tiles;
-  p.B = q.op[1].tiles;
+void fill_operands(QuantOperand (&op)[2], const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w,
+                   int M, int N) {
+  const int La = (1 << bits_a) - 1, Lw = (1 << bits_w) - 1;
+  op[0] = {a, lda, M, 0, 0.0f, 1.0f, (float)La, 1.0f, bits_a == 8 ? 0.0f : 128.0f, nullptr};
+  op[1] = {w, ldw, N, bits_w == 1 ? 1 : 0, 1.0f, 0.5f, (float)Lw, bits_w == 8 ? 1.0f : 2.0f,
+           bits_w == 8 ? 0.0f : 128.0f - (float)Lw, nullptr};
+}
+
+void fill_product(I8Params& p, int bits_a, int bits_w, int M, int N, int K, int32_t* S_out, float* out_f32, int64_t ldo) {
+  p.A = p.B = nullptr;
   p.M = M;
   p.N = N;
-  p.nk = q.kblocks * 8;
-  p.mblocks = mblocks;
-  p.nblocks = nblocks;
+  p.mblocks = (int)ceil_div(M, 32);
+  p.nblocks = (int)ceil_div(N, 32);
   p.ca = bits_a == 8 ? 128 : 0;
   p.scale = bits_w == 8 ? 2 : 1;
   p.rs = bits_w == 8 ? 1 : 0;
   p.Kreal = K;
-  p.denom = (float)(La * Lw);
+  p.denom = (float)(((1 << bits_a) - 1) * ((1 << bits_w) - 1));
   p.C_i32 = S_out;
   p.C_f32 = out_f32;
   p.ldc = ldo;
+}
+
+}  // namespace
+
+// The one-launch form, for any pair of bit widths; false when the problem is too large for it.
+bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
+                        int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
+  if (gemm_engine != 0) return false;
+  const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32), nk = ceil_div(K, 32);
+  // (level with two launches at about 12 steps of K per CU, where gathering 64 runs per load, one L1 line each,
+  // takes the time: 202 x 192 x 437 7.65 us both ways, 1000 x 402 x 1152 27 against 10.4, 64 x 907 x 256 7.0
+  // against 7.8, 134 x 328 x 64 5.3)
+  if (ceil_div(tiles, 256) * nk > 10) return false;
+  QuantSmallParams p;
+  QuantOperand op[2];
+  fill_operands(op, a, lda, bits_a, w, ldw, bits_w, M, N);
+  p.a = op[0];
+  p.w = op[1];
+  fill_product(p.g, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
+  p.g.nk = (int)nk;
+  p.g.tiles_m = p.g.mblocks;
+  p.g.tiles = (int)tiles;
+  p.g.tiles_per_xcd = 0;
+  // waves per tile: a step or two of K each while the chip has room for them
+  const bool sums = bits_a == 8 || bits_w == 8;
+  const int64_t S = std::min<int64_t>(sums ? 15 : 16, std::max<int64_t>(1, 4096 / tiles));  // (15: 64 KB of LDS)
+  p.g.S = (int)std::min(S, nk);
+  const size_t lds = p.g.S > 1 ? (size_t)p.g.S * (4096 + (sums ? 256 : 0)) : 0;
+  note_kernel("quant_small_kernel%s grid %lld x %d", sums ? "<sums>" : "", (long long)tiles, 64 * p.g.S);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
+  if (bits_w == 1) sums ? go(quant_small_kernel<true, true>) : go(quant_small_kernel<false, true>);
+  else sums ? go(quant_small_kernel<true, false>) : go(quant_small_kernel<false, false>);
+  *err = hipGetLastError();
+  return true;
+}
+
+bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
+                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, hipStream_t s, hipError_t* err) {
+  size_t need;
+  if (gemm_engine == 1 || !quant_i8_takes(M, N, K, bits_a, bits_w, &need)) return false;
+  if (gemm_engine != 0 && bits_a <= 2 && bits_w == 1) return false;  // (an engine of the plane form is pinned)
+  QuantTilesParams q;
+  fill_operands(q.op, a, lda, bits_a, w, ldw, bits_w, M, N);
+  q.op[0].tiles = (uint4*)workspace;
+  q.op[1].tiles = (uint4*)((char*)workspace + tile_bytes(M, K));
+  q.K = K;
+  q.kblocks = (int)ceil_div(K, 256);
+  q.div_kblocks = make_fast_div((uint32_t)q.kblocks);
+  I8Params p;
+  fill_product(p, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
+  q.blocks0 = p.mblocks * q.kblocks;
+  hipLaunchKernelGGL(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + p.nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
+  *err = hipGetLastError();
+  if (*err != hipSuccess) return true;
+  p.A = q.op[0].tiles;
+  p.B = q.op[1].tiles;
+  p.nk = q.kblocks * 8;
   // The most of C per wave that still gives every CU a workgroup (the waves that split K share one):
   // 64 x 64, 32 x 64, 32 x 32.  500 x 1000 x 2304: 128 tiles of 64 x 64 9.2 us, 256 of 32 x 64 7.1 us.
   int TM = 1, TN = 1;

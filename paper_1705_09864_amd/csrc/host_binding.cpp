@@ -22,6 +22,7 @@
 #include <string>
 
 #include "../../include/bmx.h"
+#include "lazy_calls.h"
 
 namespace {
 
@@ -137,17 +138,22 @@ struct Workspace {
   void* p = nullptr;
   size_t bytes = 0;
   bool mine = false;
+  Workspace() = default;
   Workspace(PyObject* o, int op, std::initializer_list<int64_t> dims, T like, hipStream_t s) {
-    if (o != Py_None) {
-      if (!THPVariable_Check(o) || !THPVariable_Unpack(o).is_cuda() || !THPVariable_Unpack(o).is_contiguous()) {
-        PyErr_SetString(PyExc_ValueError, "workspace must be a contiguous GPU tensor");
-        throw python_error();
-      }
-      const at::Tensor& t = THPVariable_Unpack(o);
-      p = t.data_ptr();
-      bytes = t.nbytes();
-      return;
+    if (!given(o)) allocate(op, dims, like, s);
+  }
+  bool given(PyObject* o) {
+    if (o == Py_None) return false;
+    if (!THPVariable_Check(o) || !THPVariable_Unpack(o).is_cuda() || !THPVariable_Unpack(o).is_contiguous()) {
+      PyErr_SetString(PyExc_ValueError, "workspace must be a contiguous GPU tensor");
+      throw python_error();
     }
+    const at::Tensor& t = THPVariable_Unpack(o);
+    bytes = t.nbytes();
+    p = bytes ? t.data_ptr() : (void*)16;  // (an empty one is a workspace that is too small, not none)
+    return true;
+  }
+  void allocate(int op, std::initializer_list<int64_t> dims, T like, hipStream_t s) {
     bytes = bmx_workspace_bytes(op, dims.begin(), (int)dims.size());
     if (bytes == 0) return;  // nothing needed, or sizes that the call itself will refuse
     const c10::OptionalDeviceGuard guard(like->device());
@@ -159,6 +165,16 @@ struct Workspace {
   }
   Workspace(const Workspace&) = delete;
 };
+
+// A call whose workspace is allocated only if it asks for one.
+template <class Call>
+int lazily(Workspace& ws, PyObject* given, int op, std::initializer_list<int64_t> dims, T like, hipStream_t s, Call call) {
+  if (ws.given(given)) return call();
+  const int status = call();
+  if (status != BMX_ERR_WORKSPACE) return status;
+  ws.allocate(op, dims, like, s);
+  return call();
+}
 
 using Args = PyObject* const*;
 #define FUNCTION(name, count)                                                    \
@@ -237,10 +253,14 @@ FUNCTION(binary_fc, 7) {  // x, Wp, alpha, integer_out, out, workspace, stream
   const bool i32 = truth(a[3]);
   Out out(a[4], i32 ? kI32 : kF32, {batch, fout}, x, "binary_fc out");
   const hipStream_t s = stream_of(a[6]);
-  Workspace ws(a[5], BMX_OP_BINARY_FC, {batch, fin, fout}, x, s);
-  check_status(bmx_binary_fc(ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha), as_int(batch), as_int(fin),
-                             as_int(fout), i32 ? ptr<int32_t>(out.t) : nullptr, i32 ? nullptr : ptr<float>(out.t),
-                             ld(out.t), ws.p, ws.bytes, s),
+  Workspace ws;
+  check_status(lazily(ws, a[5], BMX_OP_BINARY_FC, {batch, fin, fout}, x, s,
+                      [&] {
+                        return bmx_lazy_binary_fc(ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha),
+                                                  as_int(batch), as_int(fin), as_int(fout),
+                                                  i32 ? ptr<int32_t>(out.t) : nullptr, i32 ? nullptr : ptr<float>(out.t),
+                                                  ld(out.t), ws.p, ws.bytes, s);
+                      }),
                "bmx_binary_fc");
   return out.result();
 }
@@ -375,9 +395,13 @@ FUNCTION(quant_gemm, 10) {
     throw python_error();
   }
   const hipStream_t s = stream_of(a[9]);
-  Workspace ws(a[8], BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, x, s);
-  check_status(bmx_quant_gemm(ptr<float>(x), ld(x), bits_a, ptr<float>(w), ld(w), bits_w, as_int(M), as_int(N), as_int(K),
-                              S ? ptr<int32_t>(S->t) : nullptr, F ? ptr<float>(F->t) : nullptr, ldo, ws.p, ws.bytes, s),
+  Workspace ws;
+  check_status(lazily(ws, a[8], BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, x, s,
+                      [&] {
+                        return bmx_lazy_quant_gemm(ptr<float>(x), ld(x), bits_a, ptr<float>(w), ld(w), bits_w, as_int(M),
+                                                   as_int(N), as_int(K), S ? ptr<int32_t>(S->t) : nullptr,
+                                                   F ? ptr<float>(F->t) : nullptr, ldo, ws.p, ws.bytes, s);
+                      }),
                "bmx_quant_gemm");
   PyObject* r = PyTuple_New(2);
   if (!r) throw python_error();

@@ -436,13 +436,34 @@ def test_quant_gemm_bytes(M, N, K, ba, bw):
     da, dw = dev(a)[:, :K], dev(w)[:, 3:] if bw > 1 else dev(w)[:, :K]
     a, w = a[:, :K].copy(), w[:, 3:].copy() if bw > 1 else w[:, :K].copy()
     rS, _, r32 = oracle.quant_gemm(a, w, ba, bw)
-    S, of = B.quant_gemm(da, dw, ba, bits_w=bw)
-    assert "gemm_i8_kernel" in B.last_kernel()
+    with tuned(k7=3):
+        S, of = B.quant_gemm(da, dw, ba, bits_w=bw)
+        assert "gemm_i8_kernel" in B.last_kernel()
     np.testing.assert_array_equal(S.cpu().numpy(), rS)
     assert_f32_close(of.cpu().numpy(), r32)
     S2, none = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw, want_float=False)
     assert none is None
     np.testing.assert_array_equal(S2.cpu().numpy(), rS)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 16, 31), (33, 70, 257), (64, 32, 320), (300, 200, 65), (600, 700, 40)])
+@pytest.mark.parametrize("ba,bw", [(1, 1), (2, 1), (3, 1), (8, 1), (1, 2), (4, 4), (8, 7), (7, 8), (8, 8)])
+def test_quant_gemm_one_launch(M, N, K, ba, bw):
+    """The one-launch form, every pair of bit widths: K tails inside a lane's sixteen values and inside
+    a step, one and many waves per tile, rows and columns that do not fill a tile, operand rows further
+    apart than their length and not 16-byte aligned, a caller's workspace or none."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a = rng.uniform(-0.1, 1.1, (M, K + 1)).astype(np.float32)
+    w = rng.uniform(-1.1, 1.1, (N, K + 3)).astype(np.float32)
+    rS, _, r32 = oracle.quant_gemm(a[:, :K].copy(), w[:, :K].copy(), ba, bw)
+    S, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, :K], ba, bits_w=bw)
+    assert ("quant_small_kernel" in B.last_kernel()) == (K <= 320)
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    assert_f32_close(of.cpu().numpy(), r32)
+    ws = torch.empty(B.workspace_bytes(B.OP_QUANT_GEMM, (M, N, K, ba, bw)), dtype=torch.uint8, device="cuda")
+    none, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, :K], ba, bits_w=bw, want_int=False, workspace=ws)
+    assert none is None
+    assert_f32_close(of.cpu().numpy(), r32)
 
 
 def test_config5_quant_gemm():

@@ -84,7 +84,7 @@ extern "C" {
 int bmx_tune_set(int key, int value) {
   if (key == 0) {  // everything back to the automatic choice
     bmx::conv_filters_per_wave = bmx::gemm_tune_rows = bmx::gemm_tune_ksplit = bmx::gemm_tune_order = 0;
-    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = 0;
+    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = 0;
     return BMX_OK;
   }
   if (key == 1) bmx::conv_filters_per_wave = value;
@@ -101,6 +101,7 @@ int bmx_tune_set(int key, int value) {
   else if (key == 13) bmx::gemm_fp4_tall = value;
   else if (key == 14) bmx::conv_ws_x4 = value;
   else if (key == 15) bmx::fc_small = value;
+  else if (key == 16) bmx::conv_one = value;
   else return BMX_ERR_UNSUPPORTED;
   return BMX_OK;
 }
@@ -494,9 +495,9 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
   return hip_status(bmx::launch_pack_nchw_thr(tmp, N, O, g.Ho, g.Wo, out_pad, thr, out_xp, s));
 }
 
-int bmx_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O,
-                      int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
-                      float* out_f32, void* workspace, size_t workspace_bytes, void* stream) {
+static int binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O,
+                         int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
+                         float* out_f32, void* workspace, size_t workspace_bytes, void* stream, bool lazy) {
   ConvGeom g;
   const int rc = conv_check(N, C, H, W, O, KH, KW, stride, pad, &g);
   if (rc != BMX_OK) return rc;
@@ -507,15 +508,35 @@ int bmx_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t
   if (misaligned(x, 4) || misaligned(Wp, 8) || misaligned(alpha, 4) || misaligned(out_i32, 4) ||
       misaligned(out_f32, 4))
     return BMX_ERR_ALIGN;
-  const int64_t dims[9] = {N, C, H, W, O, KH, KW, stride, pad};
-  const size_t need = bmx_workspace_bytes(BMX_OP_BINARY_CONV2D, dims, 9);
-  if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
-  if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  if (!lazy || workspace) {
+    const int64_t dims[9] = {N, C, H, W, O, KH, KW, stride, pad};
+    const size_t need = bmx_workspace_bytes(BMX_OP_BINARY_CONV2D, dims, 9);
+    if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
+    if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  }
+  hipError_t one = hipSuccess;
+  if (bmx::launch_conv_one(x, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, (hipStream_t)stream, &one))
+    return hip_status(one);
+  if (!workspace) return BMX_ERR_WORKSPACE;
   uint64_t* xp = (uint64_t*)workspace;
   int st = bmx_pack_nchw(x, N, C, H, W, pad, xp, stream);
   if (st != BMX_OK) return st;
   return bmx_binary_conv2d_packed(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32,
                                   out_f32, stream);
+}
+
+int bmx_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O,
+                      int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
+                      float* out_f32, void* workspace, size_t workspace_bytes, void* stream) {
+  return binary_conv2d(x, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, workspace, workspace_bytes,
+                       stream, false);
+}
+
+int bmx_lazy_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
+                           int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, void* workspace,
+                           size_t workspace_bytes, void* stream) {
+  return binary_conv2d(x, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, workspace, workspace_bytes,
+                       stream, true);
 }
 
 static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,

@@ -172,6 +172,11 @@ bool launch_conv_mfma_ws(const uint64_t* Xp, int Nimg, int C, int H, int W, cons
                          int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
                          float* out_f32, uint64_t* out_bits, const float* thr, int out_pad, hipStream_t s,
                          hipError_t* err);
+// conv_one.hip: the whole convolution of an fp32 image (channel pack, products, scale) in one launch, for
+// problems too small to be worth two; false when the problem is not small enough (nothing launched then).
+bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
+                     int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s, hipError_t* err);
+extern int conv_one;
 extern int gemm_engine, gemm_mfma_ksplit, gemm_mfma_tile, conv_filters_per_wave, conv_path, conv_ws_x4;
 // S = 2*sum_p 2^p pc(plane_p & wb) - rowsum; out_f32 = float(S) / float(2^bits - 1).
 // planes_rows as written by launch_quant_pack (lda_dw dwords per row, chunk padded).

@@ -326,10 +326,14 @@ FUNCTION(binary_conv2d, 12) {  // x, Wp, O, KH, KW, stride, pad, alpha, integer_
   Out out(a[9], i32 ? kI32 : kF32, {N, std::max(O, 0), conv_out(H, KH, stride, pad), conv_out(Wd, KW, stride, pad)}, x,
           "binary_conv2d out", true);
   const hipStream_t s = stream_of(a[11]);
-  Workspace ws(a[10], BMX_OP_BINARY_CONV2D, {N, C, H, Wd, O, KH, KW, stride, pad}, x, s);
-  check_status(bmx_binary_conv2d(ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd), ptr<uint64_t>(W), O, KH, KW,
-                                 stride, pad, ptr<float>(alpha), i32 ? ptr<int32_t>(out.t) : nullptr,
-                                 i32 ? nullptr : ptr<float>(out.t), ws.p, ws.bytes, s),
+  Workspace ws;
+  check_status(lazily(ws, a[10], BMX_OP_BINARY_CONV2D, {N, C, H, Wd, O, KH, KW, stride, pad}, x, s,
+                      [&] {
+                        return bmx_lazy_binary_conv2d(ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd),
+                                                      ptr<uint64_t>(W), O, KH, KW, stride, pad, ptr<float>(alpha),
+                                                      i32 ? ptr<int32_t>(out.t) : nullptr,
+                                                      i32 ? nullptr : ptr<float>(out.t), ws.p, ws.bytes, s);
+                      }),
                "bmx_binary_conv2d");
   return out.result();
 }

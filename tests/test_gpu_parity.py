@@ -1219,6 +1219,26 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
     alpha = rng.standard_normal(O).astype(np.float32)
     Wp = B.pack_conv_weights(dev(w))
     ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
-    np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
-    assert "conv,reg" in B.last_kernel()
-    np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
+    with tuned(k16=1):
+        np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
+        assert "conv,reg" in B.last_kernel()
+        np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
+
+
+@pytest.mark.parametrize("parts,N,C,H,W,O,k,s,p", [
+    (1, 1, 1, 1, 1, 1, 1, 1, 0), (1, 3, 17, 9, 11, 33, 1, 2, 0), (1, 12, 390, 24, 26, 83, 1, 1, 0), (2, 2, 64, 10, 9, 32, 3, 1, 1),
+    (2, 5, 42, 29, 28, 31, 3, 2, 2), (4, 7, 130, 29, 27, 70, 3, 2, 1), (4, 1, 33, 7, 6, 65, 5, 1, 4), (8, 2, 211, 8, 20, 19, 3, 1, 0),
+    (8, 1, 256, 5, 5, 40, 5, 2, 2), (8, 3, 65, 13, 13, 29, 7, 1, 6), (1, 2, 16, 40, 170, 20, 3, 1, 1), (1, 40, 31, 12, 12, 200, 3, 1, 1)])
+def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
+    """The one-launch convolution: K split over 1 to 8 waves, patches that end inside a step of four
+    words, channels that end inside sixteen or inside a word, a filter tile and a pixel block that are
+    not full, the last band shorter than the others, bands that lie in the padding alone, strides."""
+    rng = np.random.default_rng(N + C + H + O + k)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    x[rng.random(x.shape) < 0.05] = 0.0
+    alpha = rng.standard_normal(O).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    np.testing.assert_array_equal(run_conv(x, w, s, p, integer_out=True), ri)
+    assert "conv_one_kernel" in B.last_kernel() and "%d parts of K" % parts in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(run_conv(x, w, s, p, alpha=alpha), rf)
+    np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))

@@ -84,7 +84,7 @@ extern "C" {
 int bmx_tune_set(int key, int value) {
   if (key == 0) {  // everything back to the automatic choice
     bmx::conv_filters_per_wave = bmx::gemm_tune_rows = bmx::gemm_tune_ksplit = bmx::gemm_tune_order = 0;
-    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = 0;
+    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = 0;
     return BMX_OK;
   }
   if (key == 1) bmx::conv_filters_per_wave = value;
@@ -102,6 +102,7 @@ int bmx_tune_set(int key, int value) {
   else if (key == 14) bmx::conv_ws_x4 = value;
   else if (key == 15) bmx::fc_small = value;
   else if (key == 16) bmx::conv_one = value;
+  else if (key == 17) bmx::gemm_small = value;
   else return BMX_ERR_UNSUPPORTED;
   return BMX_OK;
 }
@@ -253,9 +254,9 @@ int bmx_widen_words32(const uint32_t* in, int64_t rows, int64_t K, int64_t ld_dw
   return hip_status(bmx::launch_widen_words32(in, rows, K, ld_dwords, out, out_ld_words, (hipStream_t)stream));
 }
 
-int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int32_t* C,
-                      int64_t ldc, int M, int N, int K, void* workspace, size_t workspace_bytes,
-                      void* stream) {
+static int xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int32_t* C,
+                         int64_t ldc, int M, int N, int K, void* workspace, size_t workspace_bytes,
+                         void* stream, bool lazy) {
   if (M < 0 || N < 0) return BMX_ERR_SHAPE;
   if (K <= 0 || K >= kMaxK) return BMX_ERR_SHAPE;
   if (M == 0 || N == 0) return BMX_OK;
@@ -264,7 +265,8 @@ int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int6
   if (lda_dw < Kd || ldb_dw < Kd || ldc < N) return BMX_ERR_LD;
   if (misaligned(A, 4) || misaligned(B, 4) || misaligned(C, 4)) return BMX_ERR_ALIGN;
   // An operand whose rows are whole, 8-byte aligned 64-bit words already IS the 64-bit layout
-  // (same bytes); any other (odd dword count or stride, 4-byte aligned base) is widened first.
+  // (same bytes).  Any other (odd dword count or stride, 4-byte aligned base) is read as it is by the
+  // kernels that take such rows, or else widened first.
   auto direct = [&](const uint32_t* X, int64_t ld) { return !misaligned(X, 8) && (ld & 1) == 0 && (Kd & 1) == 0; };
   const bool da = direct(A, lda_dw), db = direct(B, ldb_dw);
   const int64_t ldw = w32_row_words(K);
@@ -273,8 +275,12 @@ int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int6
   int64_t lda_w = lda_dw / 2, ldb_w = ldb_dw / 2;
   hipStream_t s = (hipStream_t)stream;
   if (!da || !db) {
-    if (!workspace || workspace_bytes < a_bytes + b_bytes) return BMX_ERR_WORKSPACE;
+    // (the documented requirement holds whether or not this call goes on to use it)
+    if (!(lazy && !workspace) && (!workspace || workspace_bytes < a_bytes + b_bytes)) return BMX_ERR_WORKSPACE;
     if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+    hipError_t e = hipSuccess;
+    if (bmx::launch_xnor_gemm_dwords(A, lda_dw, B, ldb_dw, M, N, K, C, ldc, s, &e)) return e == hipSuccess ? BMX_OK : BMX_ERR_HIP;
+    if (!workspace) return BMX_ERR_WORKSPACE;
   }
   if (!da) {
     uint64_t* wa = (uint64_t*)workspace;
@@ -289,6 +295,17 @@ int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int6
     ldb_w = ldw;
   }
   return xnor_gemm_checked(A64, lda_w, B64, ldb_w, C, ldc, M, N, K, stream, false);
+}
+
+int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int32_t* C,
+                      int64_t ldc, int M, int N, int K, void* workspace, size_t workspace_bytes,
+                      void* stream) {
+  return xnor_gemm_w32(A, lda_dw, B, ldb_dw, C, ldc, M, N, K, workspace, workspace_bytes, stream, false);
+}
+int bmx_lazy_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int32_t* C,
+                           int64_t ldc, int M, int N, int K, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+  return xnor_gemm_w32(A, lda_dw, B, ldb_dw, C, ldc, M, N, K, workspace, workspace_bytes, stream, true);
 }
 
 namespace {

@@ -141,8 +141,17 @@ bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, 
 // the load unit, K split over the waves of a workgroup (FP4 only; planes = 1 with rowsum null is
 // the xnor form, otherwise the plane form with 1 or 2 planes).  Returns false when it does not
 // take the problem.
-bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t* rowsum, const uint64_t* B,
-                     int64_t ldb_w, int M, int N, int K, const float* alpha_n, int32_t* C_i32, float* C_f32,
+// gemm_small.hip: xnor products of few tiles; rows of `dwords` dwords that may start on any dword.
+bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t ldb_bytes, int M, int N, int K, int dwords,
+                       const float* alpha, int32_t* C_i32, float* C_f32, uint64_t* C_bits, const float* thr, int64_t ldc,
+                       bool as_count, hipStream_t s, hipError_t* err);
+extern int gemm_small;
+// gemm_mfma.hip: an xnor product of rows that may start on any dword, where a kernel reads them as they are.
+bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int M, int N, int K,
+                             int32_t* C, int64_t ldc, hipStream_t s, hipError_t* err);
+bool gemm_fp4_pays(int M, int N, int K);  // whether an xnor product has tiles (of 64 x 64) enough for launch_gemm_fp4
+bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t* rowsum, const void* B,
+                     int64_t ldb_bytes, int M, int N, int K, int dwords, const float* alpha_n, int32_t* C_i32, float* C_f32,
                      uint64_t* C_bits, const float* thr_n, int64_t ldc, bool as_count, hipStream_t s,
                      hipError_t* err);
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,

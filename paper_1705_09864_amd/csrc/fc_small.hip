@@ -267,13 +267,13 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
       if (cost < best) best = cost, rm_log = r, cols_log = c;
     }
   }
-  // Level with two launches at about 384 KB (608 x 771 -> 1487, 348 KB: 7.6 against 11.4 us; 12 x 8385
-  // -> 3257, 405 KB: 8.8 against 9.2 us; 490 x 3356 -> 829, 738 KB: 14.3 against 12.8 us).  A few
-  // workgroups have the memory system to themselves, and the general path's one or two tiles take a
-  // chain as long (2 x 65536 -> 16: 7.0 against 16.2 us).
+  // Level with two launches at about 320 KB (8 x 9216 -> 4096, 256 KB: 6.0 against 7.4 us; 767 x 3740 -> 124,
+  // 261 KB: 6.0 / 7.8; 719 x 832 -> 739, 7.3 / 7.3 to 8.6; 287 x 1598 -> 1213, 371 KB: 8.4 / 7.5).  A few workgroups have the memory system
+  // to themselves, and the general path's one or two tiles take a chain as long (2 x 65536 -> 16: 7.0
+  // against 13.3 us).
   const int rm = 1 << rm_log, cols = 1 << cols_log;
   const int64_t wgs = shift_up(batch, rm_log) * shift_up(out_features, cols_log);
-  if (best > (wgs <= 32 ? 768 << 10 : 384 << 10)) return false;
+  if (best > (wgs <= 32 ? 768 << 10 : 320 << 10)) return false;
   FcSmallParams p;
   p.x = x;
   p.ldx = ldx;

@@ -53,9 +53,9 @@ typedef __fp16 half2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
 struct Fp4Params {
-  const uint64_t* A;  // [M * PL][lda] words (plane pl of row m is row m * PL + pl), tail bits zero
-  const uint64_t* B;  // [N][ldb] words
-  uint32_t lda_bytes, ldb_bytes;  // row strides, multiples of 16
+  const void* A;  // [M * PL][lda] words (plane pl of row m is row m * PL + pl), tail bits zero
+  const void* B;  // [N][ldb] words
+  uint32_t lda_bytes, ldb_bytes;  // row strides, multiples of 16 (REG: of 4)
   int M, N, Kw, Kreal;            // Kw data words per row
   int g_base, g_rem;  // groups of four words (256 bits = the K of four MFMAs) per wave: g_base, the first g_rem waves one more
   int tiles_m, tiles_n, tiles_per_xcd;
@@ -82,6 +82,7 @@ struct Fp4Params {
   uint32_t run_pieces, row_bytes, npieces;  // pieces per run; bytes from run to run; pieces per pixel
                                             // (through registers: words per run, per pixel)
   FastDiv div_howo, div_wo, div_run;
+  int Kd;  // REG 2: data dwords per row (2 Kw, or one less)
 };
 
 // One nibble plane of four words of bits as the four operand dwords of one MFMA.
@@ -166,16 +167,16 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
     }
 }
 
-// The same segment through registers, for rows that start 8-byte aligned only (an odd number of words
-// per row) and for images whose 16-byte pieces are not contiguous (an odd number of channel words):
+// The same segment through registers, for rows that start 8-byte or 4-byte aligned only (an odd number
+// of words or dwords per row) and for images whose 16-byte pieces are not contiguous (an odd number of channel words):
 // the load unit writes LDS from 16-byte aligned addresses, an ordinary 16-byte load needs 4.  The words
 // go to the same places of the staging area when the wave gets to the segment.
-typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(8)));
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int NA, int NB, bool CONV>
+template <int NA, int NB, bool CONV, bool DWORDS>
 __device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB][2], const uint32_t (&voff)[NB][2],
                                               int piece0, int piece1, int seg) {
-  const bool tail = 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
+  const bool tail = DWORDS ? 16 * seg + 16 > p.Kd : 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
 #pragma unroll
   for (int b = NB - 1; b >= 0; --b)
 #pragma unroll
@@ -185,6 +186,15 @@ __device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB
       if (!(CONV && b >= NA) && !tail) {
         const v4u_any v = *(const v4u_any*)(base + (uint32_t)seg * 64u + voff[b][t]);
         nx[b][t] = make_uint4(v[0], v[1], v[2], v[3]);
+      } else if constexpr (DWORDS) {  // dword by dword; those past the row are zero
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 16 * seg + 4 * pc + e;
+          w[e] = *(const uint32_t*)(base + (voff[b][t] - 16u * pc + (uint32_t)min(k, p.Kd - 1) * 4u));
+          if (k >= p.Kd) w[e] = 0u;
+        }
+        nx[b][t] = make_uint4(w[0], w[1], w[2], w[3]);
       } else {  // word by word; words past the row repeat its last (the reader zeroes them)
         uint64_t w[2];
 #pragma unroll
@@ -225,10 +235,10 @@ constexpr int kOutF32 = 0, kOutI32 = 1, kOutBits = 2;
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
 // HALF: the partial tiles of a split cross LDS as fp16 pairs (exact while a wave's sums stay
 // at or below 2048, which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
-// segments travel through registers (see fetch_segment).
+// segments travel through registers (see fetch_segment; 2: rows that start on any dword).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
+template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
 __global__ void __launch_bounds__(512)
 gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #ifdef BMX_FP4_STAMPS
@@ -335,7 +345,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 
   uint4 nx[NB][2];  // REG: the next segment's words
   if (seg_lo < seg_hi) {
-    if constexpr (REG) fetch_segment<NA, NB, CONV>(p, nx, voff, piece[0], piece[1], seg_lo);
+    if constexpr (REG) fetch_segment<NA, NB, CONV, REG == 2>(p, nx, voff, piece[0], piece[1], seg_lo);
     else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
   }
   FP4_STAMP(1);
@@ -394,7 +404,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     if (seg == seg_lo) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); FP4_STAMP(2); }
 #endif
     if (seg + 1 < seg_hi) {
-      if constexpr (REG) fetch_segment<NA, NB, CONV>(p, nx, voff, piece[0], piece[1], seg + 1);
+      if constexpr (REG) fetch_segment<NA, NB, CONV, REG == 2>(p, nx, voff, piece[0], piece[1], seg + 1);
       else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1);
     }
 #pragma unroll
@@ -696,7 +706,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 int gemm_fp4_half = 0;  // 2 = keep fp32 partials (tests of both forms)
 namespace {
 
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
+template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   constexpr int NB = TM * PL + TN, kStage = NB * 128, kGroups = TM * TN * 4, kCnt = (TM + TN) * 8;
   constexpr int part = HALF ? kGroups * 32 : kGroups * 64;
@@ -740,7 +750,7 @@ void set_tile_order(Fp4Params& p) {
   p.div_last = make_fast_div((uint32_t)p.last_rows);
 }
 
-template <int PL, bool XNOR, int OUT, bool CONV = false, bool REG = false>
+template <int PL, bool XNOR, int OUT, bool CONV = false, int REG = 0>
 hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   if (S > 1) {
     // a wave's partial sums are at most (its bits of K) x (2^PL - 1): whole numbers up to 2048
@@ -769,38 +779,44 @@ static int choose_k_split(int64_t tiles, int kwords, int least, int four_up_to) 
   return tiles <= 256 ? 8 : 4;
 }
 
-// Takes the problem when sums stay exact in fp32, the
+// Below 64 tiles, and below 300 while K is short, kernels of 32 x 32 tiles: four times the waves, and
+// there is not enough K to give these tiles to several waves each.
+bool gemm_fp4_pays(int M, int N, int K) {
+  const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
+  return tiles >= (words_for(K) < 48 ? 300 : 64);
+}
+
+// Takes the problem (rows of `dwords` data dwords) when sums stay exact in fp32, the
 // operands can be addressed with 32-bit byte offsets, and there are enough 64 x 64 tiles for
 // the tile shape to pay; false otherwise (the caller then uses the 32 x 32 kernel).
-bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t* rowsum, const uint64_t* B,
-                     int64_t ldb_w, int M, int N, int K, const float* alpha_n, int32_t* C_i32, float* C_f32,
+bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t* rowsum, const void* B,
+                     int64_t ldb_bytes, int M, int N, int K, int dwords, const float* alpha_n, int32_t* C_i32, float* C_f32,
                      uint64_t* C_bits, const float* thr_n, int64_t ldc, bool as_count, hipStream_t s,
                      hipError_t* err) {
   if (gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
   if (planes < 1 || planes > 2) return false;
   // rows that do not start 16-byte aligned travel through registers (xnor products only: a k-bit
   // product's operands are the library's own rows)
-  const bool reg = (lda_w & 1) || (ldb_w & 1) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
-  if (reg && rowsum) return false;
+  const bool reg = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15) || (dwords & 1);
+  // (rows of 32-bit words where that shows: their own form, int32 results only)
+  const bool odd_dwords = (lda_bytes & 7) || (ldb_bytes & 7) || ((uintptr_t)A & 7) || ((uintptr_t)B & 7) || (dwords & 1);
+  if (reg && (rowsum || (odd_dwords && (!C_i32 || planes != 1)))) return false;
   if ((int64_t)K * ((1 << planes) - 1) >= ((int64_t)1 << 24)) return false;
-  if ((int64_t)M * planes * lda_w * 8 >= ((int64_t)1 << 32) || (int64_t)N * ldb_w * 8 >= ((int64_t)1 << 32))
+  if ((int64_t)M * planes * lda_bytes >= ((int64_t)1 << 32) || (int64_t)N * ldb_bytes >= ((int64_t)1 << 32))
     return false;
   // (outputs are addressed with 32-bit element indices, rows rounded up to whole tiles)
   if (((int64_t)M + 64) * ldc * (C_bits ? 2 : 1) >= ((int64_t)1 << 31)) return false;
   const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   const int Kwords = (int)words_for(K);
-  // Below 64 tiles, and below 300 while K is short, the 32 x 32 per wave kernel: four times the waves,
-  // and there is not enough K to give these tiles to several waves each (xnor products, us a call:
-  // 331 x 1790 x 553 6.1 against 7.8, 2075 x 464 x 1408 6.6 against 7.7; 358 x 3179 x 1152, 300 tiles,
-  // 8.4 against 7.9; 217 x 1566 x 4352 8.0 against 6.2).
-  if (gemm_engine != 5 && (tiles < 64 || (tiles < 300 && Kwords < 48 && !rowsum))) return false;
+  if (gemm_engine != 5 && (tiles < 64 || (!rowsum && !gemm_fp4_pays(M, N, K)))) return false;
   if (tiles >= ((int64_t)1 << 28)) return false;
   Fp4Params p;
   p.A = A;
   p.B = B;
-  p.lda_bytes = (uint32_t)(lda_w * 8);
-  p.ldb_bytes = (uint32_t)(ldb_w * 8);
+  p.lda_bytes = (uint32_t)lda_bytes;
+  p.ldb_bytes = (uint32_t)ldb_bytes;
+  p.Kd = dwords;
   p.M = M;
   p.N = N;
   p.Kw = Kwords;
@@ -852,9 +868,10 @@ bool launch_gemm_fp4(const uint64_t* A, int64_t lda_w, int planes, const int32_t
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
   if (reg) {
-    if (C_bits) *err = launch_split<1, true, kOutBits, false, true>(p, S, tiles_per_wg, blocks, s);
-    else if (C_i32) *err = launch_split<1, true, kOutI32, false, true>(p, S, tiles_per_wg, blocks, s);
-    else *err = launch_split<1, true, kOutF32, false, true>(p, S, tiles_per_wg, blocks, s);
+    if (odd_dwords) *err = launch_split<1, true, kOutI32, false, 2>(p, S, tiles_per_wg, blocks, s);
+    else if (C_bits) *err = launch_split<1, true, kOutBits, false, 1>(p, S, tiles_per_wg, blocks, s);
+    else if (C_i32) *err = launch_split<1, true, kOutI32, false, 1>(p, S, tiles_per_wg, blocks, s);
+    else *err = launch_split<1, true, kOutF32, false, 1>(p, S, tiles_per_wg, blocks, s);
   } else if (planes == 1 && rowsum == nullptr) {
     if (C_bits) *err = launch_split<1, true, kOutBits>(p, S, tiles_per_wg, blocks, s);
     else if (C_i32) *err = launch_split<1, true, kOutI32>(p, S, tiles_per_wg, blocks, s);
@@ -894,6 +911,7 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   p.B = Xp;
   p.lda_bytes = (uint32_t)(ld_words * 8);
   p.ldb_bytes = 0;
+  p.Kd = 2 * kwords;
   p.M = O;
   p.N = (int)P;
   p.Kw = kwords;
@@ -935,8 +953,8 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, true>(p, S, tiles_per_wg, blocks, s);
-  else if (reg) *err = launch_split<1, true, kOutF32, true, true>(p, S, tiles_per_wg, blocks, s);
+  if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, 1>(p, S, tiles_per_wg, blocks, s);
+  else if (reg) *err = launch_split<1, true, kOutF32, true, 1>(p, S, tiles_per_wg, blocks, s);
   else if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
   else *err = launch_split<1, true, kOutF32, true>(p, S, tiles_per_wg, blocks, s);
   return true;

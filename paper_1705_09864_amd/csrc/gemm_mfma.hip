@@ -563,12 +563,26 @@ int choose_split(int64_t tiles, int nsteps) {
 
 }  // namespace
 
+bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int M, int N, int K,
+                             int32_t* C, int64_t ldc, hipStream_t s, hipError_t* err) {
+  const int dwords = (int)ceil_div(K, 32);
+  return launch_gemm_small(A, lda_dw * 4, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, nullptr, nullptr, ldc, false, s,
+                           err) ||
+         // (its loads pass registers here, which costs a large product more than widening the operands:
+         // 3000 x 3000 x 2500 26.9 us a call as it is, 24.9 with the two passes; 2000 x 2000 x 1500 11.0 / 13.3)
+         ((double)M * N * K < 1.2e10 && launch_gemm_fp4(A, lda_dw * 4, 1, nullptr, B, ldb_dw * 4, M, N, K, dwords, nullptr, C,
+                                                        nullptr, nullptr, nullptr, ldc, false, s, err));
+}
+
 bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, int64_t ldb_w, int M,
                            int N, int K, const float* alpha_n, int32_t* C_i32, float* C_f32,
                            uint64_t* C_bits, const float* thr_n, int64_t ldc, hipStream_t s, hipError_t* err,
                            bool as_count) {
   if (gemm_engine == 1) return false;
-  if (launch_gemm_fp4(A, lda_w, 1, nullptr, B, ldb_w, M, N, K, alpha_n, C_i32, C_f32, C_bits, thr_n, ldc, as_count,
+  if (launch_gemm_small(A, lda_w * 8, B, ldb_w * 8, M, N, K, 2 * (int)words_for(K), alpha_n, C_i32, C_f32, C_bits, thr_n, ldc,
+                        as_count, s, err))
+    return true;
+  if (launch_gemm_fp4(A, lda_w * 8, 1, nullptr, B, ldb_w * 8, M, N, K, 2 * (int)words_for(K), alpha_n, C_i32, C_f32, C_bits, thr_n, ldc, as_count,
                       s, err))
     return true;
   MfmaParams p;
@@ -613,7 +627,7 @@ bool launch_plane_gemm_mfma(const uint64_t* planes_rows, int64_t lda_w, int bits
                             const uint64_t* Wb, int64_t ldb_w, int M, int N, int K, int32_t* S_out,
                             float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
   if (gemm_engine == 1 || bits > 2) return false;
-  if (launch_gemm_fp4(planes_rows, lda_w, bits, rowsum, Wb, ldb_w, M, N, K, nullptr, S_out, out_f32, nullptr, nullptr,
+  if (launch_gemm_fp4(planes_rows, lda_w * 8, bits, rowsum, Wb, ldb_w * 8, M, N, K, 2 * (int)words_for(K), nullptr, S_out, out_f32, nullptr, nullptr,
                       ldo, false, s, err))
     return true;
   MfmaParams p;

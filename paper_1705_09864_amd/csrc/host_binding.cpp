@@ -239,9 +239,12 @@ FUNCTION(xnor_gemm_w32, 6) {  // A32, B32, K, out, workspace, stream
   const int K = small(a[2]);
   Out out(a[3], kI32, {M, N}, A, "xnor_gemm_w32 out");
   const hipStream_t s = stream_of(a[5]);
-  Workspace ws(a[4], BMX_OP_XNOR_GEMM_W32, {M, N, K}, A, s);
-  check_status(bmx_xnor_gemm_w32(ptr<uint32_t>(A), ld(A), ptr<uint32_t>(B), ld(B), ptr<int32_t>(out.t), ld(out.t),
-                                 as_int(M), as_int(N), K, ws.p, ws.bytes, s),
+  Workspace ws;
+  check_status(lazily(ws, a[4], BMX_OP_XNOR_GEMM_W32, {M, N, K}, A, s,
+                      [&] {
+                        return bmx_lazy_xnor_gemm_w32(ptr<uint32_t>(A), ld(A), ptr<uint32_t>(B), ld(B), ptr<int32_t>(out.t),
+                                                      ld(out.t), as_int(M), as_int(N), K, ws.p, ws.bytes, s);
+                      }),
                "bmx_xnor_gemm_w32");
   return out.result();
 }

@@ -1209,6 +1209,42 @@ def test_gemm_fp4_rows_through_registers(M, N, K, off):
     np.testing.assert_array_equal(B.xnor_gemm(A, W, K, count=True).cpu().numpy(), (ri + K) // 2)
 
 
+@pytest.mark.parametrize("word", [32, 64])
+@pytest.mark.parametrize("M,N,K,off", [(1, 1, 1, 0), (33, 31, 33, 1), (5, 70, 65, 0), (40, 33, 97, 1), (32, 64, 128, 0), (31, 65, 256, 1),
+                                       (70, 130, 257, 0), (64, 100, 1000, 1), (100, 90, 2017, 1), (3, 40, 4096, 0), (2, 33, 16385, 1),
+                                       (1100, 2000, 4000, 1), (400, 700, 8161, 0)])
+def test_gemm_small_and_rows_on_any_dword(M, N, K, off, word):
+    """The kernel for small products (1 to 16 waves per tile, rows shorter than a 16-byte piece, pieces
+    past the row's end) and the 64 x 64 per wave kernel beyond its range, on rows of 64-bit and of 32-bit
+    words, odd numbers of them, behind a base that is aligned to one word only."""
+    rng = np.random.default_rng(M + N + K)
+    a, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    words = -(-K // word)
+
+    def rows(m):
+        flat = torch.full((m.shape[0] * words + off,), -1, dtype=torch.int64 if word == 64 else torch.int32, device="cuda")
+        full = B.binarize_pack(dev(m), 1)
+        flat[off:].view(m.shape[0], words).copy_(full.view(flat.dtype)[:, :words])
+        return flat[off:].view(m.shape[0], words)
+
+    A, W = rows(a), rows(w)
+    alpha, thr = rng.standard_normal(N).astype(np.float32), rng.standard_normal(N).astype(np.float32)
+    ri, rf = oracle.binary_fc(a, w, alpha)
+    large = M >= 1000 or K == 8161
+    if word == 32:
+        np.testing.assert_array_equal(B.xnor_gemm_w32(A, W, K).cpu().numpy(), ri)
+        assert ("gemm_small_kernel" in B.last_kernel()) != large
+        assert not large or words % 2 == 0 or "reg" in B.last_kernel()
+        return
+    np.testing.assert_array_equal(B.xnor_gemm(A, W, K).cpu().numpy(), ri)
+    assert ("gemm_small_kernel" in B.last_kernel()) != large
+    np.testing.assert_array_equal(B.xnor_gemm(A, W, K, count=True).cpu().numpy(), (ri + K) // 2)
+    np.testing.assert_array_equal(B.binary_fc_packed(A, K, W, alpha=dev(alpha)).cpu().numpy(), rf)
+    bits = B.binary_fc_packed(A, K, W, alpha=dev(alpha), mode="bits", thr=dev(thr))
+    ref = np.where(rf >= thr[None, :], np.float32(1), np.float32(-1))
+    np.testing.assert_array_equal(bits.cpu().numpy(), B.binarize_pack(dev(ref), 1).cpu().numpy())
+
+
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p", [(6, 300, 20, 21, 80, 3, 1, 1), (30, 150, 17, 18, 130, 5, 2, 2), (12, 140, 24, 25, 70, 7, 1, 0),
                                              (40, 190, 20, 20, 64, 1, 1, 0), (3, 420, 40, 41, 200, 3, 1, 0)])
 def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):

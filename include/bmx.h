@@ -290,6 +290,8 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *          counts that are multiples of four; 3: never in the form that holds one block per wave
  *   key 15 = 1: bmx_binary_fc never takes its one-launch form for very small layers
  *   key 16 = 1: bmx_binary_conv2d never takes its one-launch form
+ *   key 18 = 1: convolutions of packed images never take the kernel for small problems (nor while
+ *          one of keys 1, 5, 7 and 14 pins another)
  *   key 17 = 1: xnor products never take the kernel for small problems (nor while any of keys 7 to
  *          13 pins one of the others)
  *   key 8  K-split waves, key 9  tile variant (1: 32 x 32, 2: 64 x 64 per wave) of the matrix-core

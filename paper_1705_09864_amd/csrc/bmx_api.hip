@@ -84,7 +84,7 @@ extern "C" {
 int bmx_tune_set(int key, int value) {
   if (key == 0) {  // everything back to the automatic choice
     bmx::conv_filters_per_wave = bmx::gemm_tune_rows = bmx::gemm_tune_ksplit = bmx::gemm_tune_order = 0;
-    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = 0;
+    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = bmx::conv_small = 0;
     return BMX_OK;
   }
   if (key == 1) bmx::conv_filters_per_wave = value;
@@ -103,6 +103,7 @@ int bmx_tune_set(int key, int value) {
   else if (key == 15) bmx::fc_small = value;
   else if (key == 16) bmx::conv_one = value;
   else if (key == 17) bmx::gemm_small = value;
+  else if (key == 18) bmx::conv_small = value;
   else return BMX_ERR_UNSUPPORTED;
   return BMX_OK;
 }
@@ -476,10 +477,10 @@ int bmx_binary_conv2d_packed(const uint64_t* xp, int N, int C, int H, int W, con
                                               out_i32, out_f32, (hipStream_t)stream));
 }
 
-int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const uint64_t* Wp, int O,
-                           int KH, int KW, int stride, int pad, const float* alpha, const float* thr,
-                           uint64_t* out_xp, int out_pad, void* workspace, size_t workspace_bytes,
-                           void* stream) {
+static int binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const uint64_t* Wp, int O,
+                              int KH, int KW, int stride, int pad, const float* alpha, const float* thr,
+                              uint64_t* out_xp, int out_pad, void* workspace, size_t workspace_bytes,
+                              void* stream, bool lazy) {
   ConvGeom g;
   const int rc = conv_check(N, C, H, W, O, KH, KW, stride, pad, &g);
   if (rc != BMX_OK) return rc;
@@ -494,22 +495,44 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
     return BMX_ERR_ALIGN;
   // where the size query answered 0 the kernel that writes the bits itself must run, and it
   // reads filter rows in 16-byte pieces
-  if (bmx::conv_mfma_ws_takes(N, C, H, W, O, KH, KW, stride, pad, out_pad) && misaligned(Wp, 16))
-    return BMX_ERR_ALIGN;
+  const bool ws_takes = bmx::conv_mfma_ws_takes(N, C, H, W, O, KH, KW, stride, pad, out_pad);
+  if (ws_takes && misaligned(Wp, 16)) return BMX_ERR_ALIGN;
+  // (where the query asks for a workspace it is required, whichever kernel then runs)
+  const size_t need = round256((size_t)N * O * g.Ho * g.Wo * 4);
+  if (!ws_takes && (!lazy || workspace)) {
+    if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
+    if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  }
   hipStream_t s = (hipStream_t)stream;
   hipError_t err = hipSuccess;
+  if (bmx::launch_conv_small(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr, out_pad, s, &err))
+    return hip_status(err);
   if (bmx::launch_conv_mfma_ws(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr,
                                out_pad, s, &err))
     return hip_status(err);
   // every other shape: the fp32 result through the workspace, then the channel pack with the
   // same compare
-  const size_t need = round256((size_t)N * O * g.Ho * g.Wo * 4);
-  if (!workspace || workspace_bytes < need) return BMX_ERR_WORKSPACE;
-  if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
+  if (!workspace) return BMX_ERR_WORKSPACE;
   float* tmp = (float*)workspace;
   err = bmx::launch_binary_conv2d(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, tmp, s);
   if (err != hipSuccess) return BMX_ERR_HIP;
   return hip_status(bmx::launch_pack_nchw_thr(tmp, N, O, g.Ho, g.Wo, out_pad, thr, out_xp, s));
+}
+
+int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const uint64_t* Wp, int O,
+                           int KH, int KW, int stride, int pad, const float* alpha, const float* thr,
+                           uint64_t* out_xp, int out_pad, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+  return binary_conv2d_bits(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, thr, out_xp, out_pad, workspace,
+                            workspace_bytes, stream, false);
+}
+
+int bmx_lazy_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const uint64_t* Wp, int O,
+                                int KH, int KW, int stride, int pad, const float* alpha, const float* thr,
+                                uint64_t* out_xp, int out_pad, void* workspace, size_t workspace_bytes,
+                                void* stream) {
+  return binary_conv2d_bits(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, thr, out_xp, out_pad, workspace,
+                            workspace_bytes, stream, true);
 }
 
 static int binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O,

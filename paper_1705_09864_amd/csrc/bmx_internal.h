@@ -181,6 +181,11 @@ bool launch_conv_mfma_ws(const uint64_t* Xp, int Nimg, int C, int H, int W, cons
                          int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
                          float* out_f32, uint64_t* out_bits, const float* thr, int out_pad, hipStream_t s,
                          hipError_t* err);
+// conv_small.hip: the convolution of a packed image for few tiles, all kinds of result.
+bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
+                       int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits, const float* thr,
+                       int out_pad, hipStream_t s, hipError_t* err);
+extern int conv_small;
 // conv_one.hip: the whole convolution of an fp32 image (channel pack, products, scale) in one launch, for
 // problems too small to be worth two; false when the problem is not small enough (nothing launched then).
 bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,

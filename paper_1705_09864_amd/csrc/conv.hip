@@ -246,6 +246,9 @@ int conv_ws_x4 = 0;             // 1 = the short-K matrix-core kernel never fetc
 hipError_t launch_binary_conv2d(const uint64_t* Xp, int N, int C, int H, int W, const uint64_t* Wp,
                                 int O, int KH, int KW, int stride, int pad, const float* alpha,
                                 int32_t* out_i32, float* out_f32, hipStream_t s) {
+  hipError_t small = hipSuccess;
+  if (launch_conv_small(Xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, nullptr, nullptr, 0, s, &small))
+    return small;
   const int Ho = (H + 2 * pad - KH) / stride + 1;
   const int Wo = (W + 2 * pad - KW) / stride + 1;
   const int Cw = (int)words_for(C);

@@ -272,11 +272,11 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
   if (N > 65535 || O > 65535 * 32 || (int64_t)H * W * 4 >= ((int64_t)1 << 31) || (int64_t)C * KH * KW >= ((int64_t)1 << 24)) return false;
   if (((int64_t)N * O + 32) * Ho * Wo * 4 >= ((int64_t)1 << 32)) return false;  // 32-bit output offsets
   const int tiles = (int)ceil_div(O, 32);
-  // The two launches' time in us, fitted to 500 shapes (7.6 % rms): MB of input and of results, 1e9
+  // The two launches' time in us, fitted to 850 shapes (9 % rms; 7.1 to 8.4 of it is the host's part): MB of input and of results, 1e9
   // products, the chain of a patch's words.  This form is taken where its own estimate is 5 % below.
   const double in_kb_all = (double)N * C * H * W / 256, out_kb_all = (double)N * O * Ho * Wo / 256;
   const double unit_words = (double)N * Ho * Wo * tiles * K;
-  const double limit = 0.95 * (7.5 + in_kb_all * (0.149 / 977) + out_kb_all * (0.117 / 977) + unit_words * (32 * 64 * 0.33e-9) + K * 0.021);
+  const double limit = 0.95 * (7.6 + in_kb_all * (0.16 / 977) + out_kb_all * (0.1 / 977) + unit_words * (32 * 64 * 0.4e-9) + K * 0.012);
   // Output rows per band, filter tiles per workgroup and waves per unit: those of the shortest modelled
   // time, fitted to the same shapes (6.5 % rms).  A round of workgroups pays its trips to memory, its fp32
   // rows (KB), its words per SIMD (one unit in four waves: 1) and its results (KB).

@@ -139,9 +139,6 @@ struct Workspace {
   size_t bytes = 0;
   bool mine = false;
   Workspace() = default;
-  Workspace(PyObject* o, int op, std::initializer_list<int64_t> dims, T like, hipStream_t s) {
-    if (!given(o)) allocate(op, dims, like, s);
-  }
   bool given(PyObject* o) {
     if (o == Py_None) return false;
     if (!THPVariable_Check(o) || !THPVariable_Unpack(o).is_cuda() || !THPVariable_Unpack(o).is_contiguous()) {
@@ -379,10 +376,13 @@ FUNCTION(binary_conv2d_bits, 14) {
   Out out(a[11], kU64, {N, std::max<int64_t>(ho, 0), std::max<int64_t>(wo, 0), std::max<int64_t>(words(O), 0)}, x,
           "binary_conv2d_bits out", true);
   const hipStream_t s = stream_of(a[13]);
-  Workspace ws(a[12], BMX_OP_BINARY_CONV2D_BITS, {N, C, H, Wd, O, KH, KW, stride, pad, opad}, x, s);
-  check_status(bmx_binary_conv2d_bits(ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd), ptr<uint64_t>(W), O, KH, KW,
-                                      stride, pad, ptr<float>(alpha), ptr<float>(thr), ptr<uint64_t>(out.t), opad, ws.p,
-                                      ws.bytes, s),
+  Workspace ws;
+  check_status(lazily(ws, a[12], BMX_OP_BINARY_CONV2D_BITS, {N, C, H, Wd, O, KH, KW, stride, pad, opad}, x, s,
+                      [&] {
+                        return bmx_lazy_binary_conv2d_bits(ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd),
+                                                           ptr<uint64_t>(W), O, KH, KW, stride, pad, ptr<float>(alpha),
+                                                           ptr<float>(thr), ptr<uint64_t>(out.t), opad, ws.p, ws.bytes, s);
+                      }),
                "bmx_binary_conv2d_bits");
   return out.result();
 }

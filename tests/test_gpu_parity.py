@@ -1255,16 +1255,37 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
     alpha = rng.standard_normal(O).astype(np.float32)
     Wp = B.pack_conv_weights(dev(w))
     ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
-    with tuned(k16=1):
+    with tuned(k16=1, k18=1):
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
         assert "conv,reg" in B.last_kernel()
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("N,C,H,W,O,k,s,p,opad", [
+    (1, 1, 1, 1, 1, 1, 1, 0, 0), (3, 300, 5, 7, 33, 1, 2, 0, 2), (2, 128, 9, 8, 70, 3, 1, 1, 1), (2, 131, 6, 5, 32, 3, 2, 2, 0), (1, 70, 8, 9, 95, 5, 1, 4, 3),
+    (5, 64, 7, 7, 64, 7, 1, 3, 1), (2, 260, 6, 11, 129, 3, 1, 1, 6), (1, 512, 9, 9, 31, 7, 2, 6, 1), (40, 200, 12, 13, 100, 3, 1, 0, 1), (9, 50, 40, 41, 64, 1, 1, 0, 1)])
+def test_conv_small(N, C, H, W, O, k, s, p, opad):
+    """The kernel for small convolutions of packed images: 1 to 16 waves per tile, odd and even numbers of
+    channel words, patches that end inside a step, tiles that straddle images and are not full, an odd
+    number of 32-filter tiles (the upper half of the last word is written), halos of the result."""
+    rng = np.random.default_rng(N + C + H + O + k)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha, thr = rng.standard_normal(O).astype(np.float32), rng.standard_normal(O).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    xp, Wp = B.pack_nchw(dev(x), p), B.pack_conv_weights(dev(w))
+    got = B.binary_conv2d_bits(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha), thr=dev(thr), out_pad=opad)
+    assert "conv_small_kernel<bits>" in B.last_kernel()
+    ref = np.where(rf >= thr[None, :, None, None], np.float32(1), np.float32(-1))
+    np.testing.assert_array_equal(got.cpu().numpy(), B.pack_nchw(dev(ref), opad).cpu().numpy())
+    np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
+    assert ("conv_small_kernel<i32>" in B.last_kernel()) == (C > 64 or k > 1)
+    np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
+
+
 @pytest.mark.parametrize("parts,N,C,H,W,O,k,s,p", [
     (1, 1, 1, 1, 1, 1, 1, 1, 0), (1, 3, 17, 9, 11, 33, 1, 2, 0), (1, 12, 390, 24, 26, 83, 1, 1, 0), (2, 2, 64, 10, 9, 32, 3, 1, 1),
     (2, 5, 42, 29, 28, 31, 3, 2, 2), (4, 7, 130, 29, 27, 70, 3, 2, 1), (4, 1, 33, 7, 6, 65, 5, 1, 4), (8, 2, 211, 8, 20, 19, 3, 1, 0),
-    (8, 1, 256, 5, 5, 40, 5, 2, 2), (8, 3, 65, 13, 13, 29, 7, 1, 6), (1, 2, 16, 40, 170, 20, 3, 1, 1), (1, 40, 31, 12, 12, 200, 3, 1, 1)])
+    (8, 1, 256, 5, 5, 40, 5, 2, 2), (8, 3, 65, 13, 13, 29, 7, 1, 6), (1, 2, 16, 40, 130, 20, 3, 1, 1), (1, 40, 31, 12, 12, 200, 3, 1, 1)])
 def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
     """The one-launch convolution: K split over 1 to 8 waves, patches that end inside a step of four
     words, channels that end inside sixteen or inside a word, a filter tile and a pixel block that are

@@ -235,11 +235,22 @@ __device__ __forceinline__ void finish_tile(const I8Params& p, const v16i (&acc)
       for (int e = 0; e < 4; ++e) d[e] += s < S ? t[s][e] : 0;
     if (SUMS) {
       const int i = (g >> 2) / TN, j = (g >> 2) % TN;
-      for (int s = 0; s < S; ++s) {
-        const int* w = sums + s * 32 * (TM + TN);
-        cb += w[32 * (TM + j) + r];
+#pragma unroll 1
+      for (int s0 = 0; s0 < S; s0 += 4) {  // (four waves' sums in flight at a time)
+        int wc[4];
+        v4i wr[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ra[e] += w[32 * i + 8 * (g & 3) + 4 * h + e];
+        for (int u = 0; u < 4; ++u) {
+          const int* w = sums + min(s0 + u, S - 1) * 32 * (TM + TN);
+          wc[u] = w[32 * (TM + j) + r];
+          wr[u] = *(const v4i*)(w + 32 * i + 8 * (g & 3) + 4 * h);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          cb += s0 + u < S ? wc[u] : 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ra[e] += s0 + u < S ? wr[u][e] : 0;
+        }
       }
     }
     finish(g, d, ra, cb);
@@ -319,47 +330,39 @@ gemm_i8_kernel(const I8Params p) {
 }
 
 // ---- the whole product in one launch, for problems small enough that a second launch costs more
-// than quantising a row once per tile of results.  A wave takes its 16 values per lane straight from the
-// fp32 rows (lane (r, h): k = 16 h .. 16 h + 15 of a step of 32, row r: a 64-byte run, the half-waves'
-// two make whole lines), quantises them in registers and multiplies; up to 16 waves split a tile's K.
+// than quantising a row once per tile of results.  Up to 16 waves split a tile's K.  Of a step of 32 k a
+// wave fetches 32 rows of both operands, eight lanes to a row's 128 bytes (16 bytes straight into the
+// MFMA's layout would touch 64 lines per load: 202 x 192 x 437 7.7 us), quantises four values per lane and
+// load into a dword of bytes, and turns those into the MFMA's layout (lane (r, h): 16 bytes of row r)
+// through 2 KB of LDS of its own, where its partial sums go in the end.
 struct QuantSmallParams {
   I8Params g;
   QuantOperand a, w;
+  FastDiv div_tiles_m;
+  int s_base, s_rem;  // steps per wave: s_base, the first s_rem waves one more
 };
-
-__device__ __forceinline__ void load_values(const float* row, int k0, int K, v4f_any (&v)[4]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (k0 + 4 * q + 4 <= K) {
-      v[q] = *(const v4f_any*)(row + k0 + 4 * q);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[q][e] = row[min(k0 + 4 * q + e, K - 1)];
-    }
-  }
-}
-__device__ __forceinline__ v4i make_bytes(const QuantOperand& o, const v4f_any (&v)[4], int left) {
-  v4i b;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t d = o.sign ? sign_bytes(v[q][0], v[q][1], v[q][2], v[q][3]) : quant_bytes(o, v[q][0], v[q][1], v[q][2], v[q][3]);
-    b[q] = (int)(d & byte_mask(left - 4 * q));
-  }
-  return b;
-}
 
 template <bool SUMS, bool SIGN>
 __global__ void __launch_bounds__(1024)
 quant_small_kernel(const QuantSmallParams p) {
   extern __shared__ int red[];
+  asm volatile("" ::"s"(p.a.x), "s"(p.a.ld), "s"(p.a.L), "s"(p.a.mul), "s"(p.a.add), "s"(p.w.x), "s"(p.w.ld), "s"(p.w.L),
+               "s"(p.w.mul), "s"(p.w.add), "s"(p.g.M), "s"(p.g.N), "s"(p.g.Kreal), "s"(p.g.tiles_m), "s"(p.g.S), "s"(p.s_base),
+               "s"(p.s_rem), "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1), "s"(p.div_tiles_m.sh2));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = lane & 31, h = lane >> 5;
-  const int tile_n = (int)blockIdx.x / p.g.tiles_m, tile_m = (int)blockIdx.x - tile_n * p.g.tiles_m;
-  const int k_lo = wave * p.g.nk / p.g.S, k_hi = (wave + 1) * p.g.nk / p.g.S, K = p.g.Kreal;
-  // (rows past a matrix repeat its last; their results are never stored)
-  const float* arow = p.a.x + (int64_t)min(tile_m * 32 + r, p.g.M - 1) * p.a.ld;
-  const float* wrow = p.w.x + (int64_t)min(tile_n * 32 + r, p.g.N - 1) * p.w.ld;
+  const int r = lane & 31, h = lane >> 5, c = lane & 7;
+  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div(blockIdx.x, p.div_tiles_m));
+  const int tile_m = (int)blockIdx.x - tile_n * p.g.tiles_m;
+  const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0), K = p.g.Kreal;
+  // byte offsets of row 8 t + lane / 8 (rows past a matrix repeat its last; their results are never stored)
+  uint32_t arow[4], wrow[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int row = 8 * t + (lane >> 3);
+    arow[t] = (uint32_t)min(tile_m * 32 + row, p.g.M - 1) * (uint32_t)p.a.ld * 4u;
+    wrow[t] = (uint32_t)min(tile_n * 32 + row, p.g.N - 1) * (uint32_t)p.w.ld * 4u;
+  }
   v16i acc[1][1];
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[0][0][e] = 0;
@@ -369,12 +372,26 @@ quant_small_kernel(const QuantSmallParams p) {
   ow.sign = SIGN ? 1 : 0;
   v4f_any va[2][4], vw[2][4];
   auto load = [&](int i, int k) {
-    load_values(arow, 32 * k + 16 * h, K, va[i]);
-    load_values(wrow, 32 * k + 16 * h, K, vw[i]);
+    // four values past the row's end are its last four instead; those that the piece before has are masked
+    // below (of both operands: what remains still meets its partner, and K has no order)
+    const uint32_t off = 4u * (uint32_t)min(32 * k + 4 * c, K - 4);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      va[i][t] = *(const v4f_any*)((const char*)p.a.x + (arow[t] + off));
+      vw[i][t] = *(const v4f_any*)((const char*)p.w.x + (wrow[t] + off));
+    }
   };
+  uint32_t* const turn = (uint32_t*)red + wave * 1024;  // [operand][row][8 dwords]
   auto multiply = [&](int i, int k) {
-    const int left = K - (32 * k + 16 * h);
-    const v4i a = make_bytes(oa, va[i], left), b = make_bytes(ow, vw[i], left);
+    const uint32_t mask = ~byte_mask(32 * k + 4 * c + 4 - K);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const v4f_any x = va[i][t], y = vw[i][t];
+      turn[64 * t + lane] = quant_bytes(oa, x[0], x[1], x[2], x[3]) & mask;
+      turn[256 + 64 * t + lane] = (SIGN ? sign_bytes(y[0], y[1], y[2], y[3]) : quant_bytes(ow, y[0], y[1], y[2], y[3])) & mask;
+    }
+    typedef v4i __attribute__((may_alias)) v4i_alias;
+    const v4i a = *(const v4i_alias*)(turn + 8 * r + 4 * h), b = *(const v4i_alias*)(turn + 256 + 8 * r + 4 * h);
     if (SUMS) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -387,10 +404,10 @@ quant_small_kernel(const QuantSmallParams p) {
   if (k_lo < k_hi) {
     load(0, k_lo);
     for (int k = k_lo; k < k_hi; k += 2) {
-      load(1, min(k + 1, k_hi - 1));
+      if (k + 1 < k_hi) load(1, k + 1);
       multiply(0, k);
       if (k + 1 >= k_hi) break;
-      load(0, min(k + 2, k_hi - 1));
+      if (k + 2 < k_hi) load(0, k + 2);
       multiply(1, k + 1);
     }
   }
@@ -468,10 +485,12 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
                         int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
   if (gemm_engine != 0) return false;
   const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32), nk = ceil_div(K, 32);
-  // (level with two launches at about 12 steps of K per CU, where gathering 64 runs per load, one L1 line each,
-  // takes the time: 202 x 192 x 437 7.65 us both ways, 1000 x 402 x 1152 27 against 10.4, 64 x 907 x 256 7.0
-  // against 7.8, 134 x 328 x 64 5.3)
-  if (ceil_div(tiles, 256) * nk > 10) return false;
+  // Steps of K per CU up to which one launch is ahead (us a call: 202 x 192 x 437 5.0 against 8.1, 1735 x 64 x 768
+  // 6.3 / 7.6, 83 x 64 x 1152 6.4 / 7.8, 245 x 773 x 1792 10.8 / 8.0, 748 x 448 x 512, two tiles on a CU, 8.5 / 7.8,
+  // 104 x 697 x 1045, 88 tiles, 9.0 / 8.2;
+  // with 8 bits on a side and so the operands' sums 674 x 64 x 896 7.5 / 8.0, 230 x 64 x 1142 8.2 / 8.2).
+  if (nk * ceil_div(tiles, 256) > (tiles > 256 ? 24 : tiles > 48 || bits_a == 8 || bits_w == 8 ? 28 : 36)) return false;
+  if (K < 4 || (int64_t)M * lda * 4 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 4 >= ((int64_t)1 << 32)) return false;
   QuantSmallParams p;
   QuantOperand op[2];
   fill_operands(op, a, lda, bits_a, w, ldw, bits_w, M, N);
@@ -486,7 +505,10 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   const bool sums = bits_a == 8 || bits_w == 8;
   const int64_t S = std::min<int64_t>(sums ? 15 : 16, std::max<int64_t>(1, 4096 / tiles));  // (15: 64 KB of LDS)
   p.g.S = (int)std::min(S, nk);
-  const size_t lds = p.g.S > 1 ? (size_t)p.g.S * (4096 + (sums ? 256 : 0)) : 0;
+  p.s_base = (int)nk / p.g.S;
+  p.s_rem = (int)nk % p.g.S;
+  p.div_tiles_m = make_fast_div((uint32_t)p.g.tiles_m);
+  const size_t lds = (size_t)p.g.S * (4096 + (sums ? 256 : 0));
   note_kernel("quant_small_kernel%s grid %lld x %d", sums ? "<sums>" : "", (long long)tiles, 64 * p.g.S);
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
   if (bits_w == 1) sums ? go(quant_small_kernel<true, true>) : go(quant_small_kernel<false, true>);

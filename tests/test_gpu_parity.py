@@ -446,10 +446,10 @@ def test_quant_gemm_bytes(M, N, K, ba, bw):
     np.testing.assert_array_equal(S2.cpu().numpy(), rS)
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (16, 16, 31), (33, 70, 257), (64, 32, 320), (300, 200, 65), (600, 700, 40)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 1, 4), (16, 16, 31), (33, 70, 257), (64, 32, 320), (300, 200, 65), (600, 700, 40), (40, 30, 893), (5, 9, 7)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (2, 1), (3, 1), (8, 1), (1, 2), (4, 4), (8, 7), (7, 8), (8, 8)])
 def test_quant_gemm_one_launch(M, N, K, ba, bw):
-    """The one-launch form, every pair of bit widths: K tails inside a lane's sixteen values and inside
+    """The one-launch form, every pair of bit widths: K tails inside a lane's four values and inside
     a step, one and many waves per tile, rows and columns that do not fill a tile, operand rows further
     apart than their length and not 16-byte aligned, a caller's workspace or none."""
     rng = np.random.default_rng(M + N + K + 10 * ba + bw)
@@ -457,7 +457,7 @@ def test_quant_gemm_one_launch(M, N, K, ba, bw):
     w = rng.uniform(-1.1, 1.1, (N, K + 3)).astype(np.float32)
     rS, _, r32 = oracle.quant_gemm(a[:, :K].copy(), w[:, :K].copy(), ba, bw)
     S, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, :K], ba, bits_w=bw)
-    assert ("quant_small_kernel" in B.last_kernel()) == (K <= 320)
+    assert ("quant_small_kernel" in B.last_kernel()) == (K >= 4)
     np.testing.assert_array_equal(S.cpu().numpy(), rS)
     assert_f32_close(of.cpu().numpy(), r32)
     ws = torch.empty(B.workspace_bytes(B.OP_QUANT_GEMM, (M, N, K, ba, bw)), dtype=torch.uint8, device="cuda")

@@ -773,7 +773,10 @@ int gemm_fp4_tall = 0;   // 0 = automatic; 1 = never 128 x 64 of C per wave; 2 =
 // `least` words: a wave's share is then less than the reduction costs.  Powers of two, so that the
 // SIMDs of a CU stay level: 390 x 3329 x 5632 (371 tiles) takes 10.4 us over four waves, 15.1 over five,
 // 12.2 over three; a 5 x 5 convolution over 384 channels of 42 x 38 x 37 (474 tiles) 14.0 over four, 17.1 over
-// three, 20 undivided; 1272 x 2474 x 2046 (780 tiles) 10.3 undivided, 12.7 over two.
+// three, 20 undivided; 1272 x 2474 x 2046 (780 tiles) 10.3 undivided, 12.7 over two.  An xnor product is divided
+// from 34 words on (1813 x 952 x 2393, 435 tiles: 9.1 over four, 10.3 undivided; 3331 x 403 x 1739: 9.7 / 8.4),
+// with its rows through registers, whose latency more waves hide, from 21 (2522 x 675 x 1344: 9.4 / 10.2; 424 x
+// 3607 x 3008: 10.0 / 13.3).
 static int choose_k_split(int64_t tiles, int kwords, int least, int four_up_to) {
   if (kwords < least || tiles > four_up_to) return 1;
   return tiles <= 256 ? 8 : 4;
@@ -839,7 +842,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
-  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, 48, 512);
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? 48 : reg ? 21 : 34, 512);
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;

@@ -209,92 +209,116 @@ hipError_t launch_pack_strided(const float* x, int64_t batch, int64_t K, int64_t
   return hipGetLastError();
 }
 
-// NCHW channel pack.  A wave packs 64 consecutive pixels of one image for one 64-channel
-// word: lanes span pixels, so every load instruction is a coalesced 256-byte read of one
-// channel plane, and all 64 channel loads of a lane are issued before the first compare
-// (16 KiB in flight per wave).  The word is assembled in two 32-bit halves.  Workgroup 0 of
-// every (image, word) also writes the constant halo words.  The image is read exactly once, so
-// the loads are non-temporal (they do not displace what the convolution that follows needs:
-// 12.8 us against 13.4 us per configuration-2 layer with the input coming from HBM).
+// NCHW channel pack.  A workgroup packs 64 consecutive pixels, counted through the images, for one
+// 64-channel word: each of its four waves takes 16 of the channels (a load reads 256 bytes of a channel
+// plane, all 16 in flight) and leaves 16 bits per pixel in LDS; the first wave stores the words.
+// Bound by the fp32 image's way in: with a wave per 64 channels a small image left most of the chip
+// without a load in flight, and counted per image 99 pixels are two waves of 64.
+// The image is read exactly once, so where a plane is whole 128-byte lines the loads are non-temporal
+// (they do not displace what the convolution that follows needs); elsewhere neighbouring loads share
+// lines.  us a launch, against a wave per 64 channels, counted per image and in the order of the workgroups:
+// 175 x 468 x 10 x 12 8.3 / 13.0, 17 x 505 x 49 x 49 14.6 / 21.3 (5.6 TB/s), 59 x 128 x 44 x 43 10.5 / 12.8, 16 x 64 x
+// 56 x 56 4.0 / 4.5, 2 x 62 x 18 x 17 2.7 / 4.1.
+// The halo (a constant per word) is spread over the workgroups of its word.
 // THR: bit = (value >= thr[channel]) instead of (value >= 0): the packing behind a layer whose
 // sign decision carries a folded per-channel threshold.
-template <bool THR>
+struct PackNchwParams {
+  const float* x;
+  const float* thr;
+  uint64_t* xp;
+  int C, HW, W, pad, Hp, Wp, Cw;
+  uint32_t pixels, halo;  // of all images; halo: halo pixels of all images
+  FastDiv div_hw, div_w, div_nh;
+};
+
+template <bool THR, bool NT>
 __global__ void __launch_bounds__(256)
-pack_nchw_kernel(const float* __restrict__ x, int C, int HW, int W, int pad, int Hp, int Wp, int Cw,
-                 const float* __restrict__ thr, uint64_t* __restrict__ xp) {
+pack_nchw_kernel(const PackNchwParams p) {
+  __shared__ uint16_t bits[64 * 4];
+  asm volatile("" ::"s"(p.x), "s"(p.xp), "s"(p.C), "s"(p.HW), "s"(p.W), "s"(p.pad), "s"(p.Hp), "s"(p.Wp), "s"(p.Cw), "s"(p.pixels),
+               "s"(p.div_hw.mul), "s"(p.div_hw.sh1), "s"(p.div_hw.sh2), "s"(p.div_w.mul), "s"(p.div_w.sh1), "s"(p.div_w.sh2));
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int cw = blockIdx.y;
-  const int n = blockIdx.z;
-  const int p = (blockIdx.x * 4 + wave) * 64 + lane;
-  uint64_t* xpn = xp + (int64_t)n * Hp * Wp * Cw;
-  if (p - lane < HW) {  // wave-uniform: this 64-pixel group exists
-    const int pc = p < HW ? p : HW - 1;
-    const int c0 = cw * 64;
-    const float* xb = x + ((int64_t)n * C + c0) * HW + pc;
-    float v[64];
-    if (c0 + 64 <= C) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cw = blockIdx.y, c0 = cw * 64 + wave * 16, real = min(16, p.C - c0);  // (real <= 0: channels past the last)
+  // Workgroup b sits on XCD b % 8: every XCD gets a contiguous run of pixels, whose neighbours share lines
+  // where planes are not whole ones (57 MB of 44 x 43 planes 14.1 us without).
+  const uint32_t q = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 64 + lane;
+  const uint32_t qc = min(q, p.pixels - 1);  // lanes past the last pixel repeat it
+  const uint32_t n = fast_div(qc, p.div_hw), px = qc - n * (uint32_t)p.HW;
+  float v[16];
+  if (real > 0) {
+    const float* const xb = p.x + ((int64_t)n * p.C + c0) * p.HW + px;
+    const int64_t plane = p.HW;
 #pragma unroll
-      for (int j = 0; j < 64; ++j) v[j] = __builtin_nontemporal_load(xb + (int64_t)j * HW);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 64; ++j) v[j] = (c0 + j < C) ? xb[(int64_t)j * HW] : -1.0f;
-    }
-    uint32_t lo = 0, hi = 0;
-    if constexpr (THR) {
-      // (missing channels hold -1 and compare against 0)
-#pragma unroll
-      for (int j = 0; j < 32; ++j) lo |= (v[j] >= (c0 + j < C ? thr[c0 + j] : 0.0f) ? 1u : 0u) << j;
-#pragma unroll
-      for (int j = 0; j < 32; ++j) hi |= (v[32 + j] >= (c0 + 32 + j < C ? thr[c0 + 32 + j] : 0.0f) ? 1u : 0u) << j;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 32; ++j) lo |= (v[j] >= 0.0f ? 1u : 0u) << j;
-#pragma unroll
-      for (int j = 0; j < 32; ++j) hi |= (v[32 + j] >= 0.0f ? 1u : 0u) << j;
-    }
-    if (p < HW) {
-      const int h = p / W, w = p - h * W;
-      xpn[((int64_t)(h + pad) * Wp + (w + pad)) * Cw + cw] = ((uint64_t)hi << 32) | lo;
+    for (int j = 0; j < 16; ++j) {  // (channels past the last repeat it and are masked)
+      const float* const at = xb + plane * min(j, real - 1);
+      v[j] = NT ? __builtin_nontemporal_load(at) : *at;
     }
   }
-  if (pad > 0 && blockIdx.x == 0) {
-    const uint64_t ones = (cw == Cw - 1 && (C % 64)) ? (((uint64_t)1 << (C % 64)) - 1) : ~(uint64_t)0;
-    const int H = HW / W;
-    const int nh = Hp * Wp - HW;
-    for (int i = threadIdx.x; i < nh; i += 256) {
+  const uint32_t h = fast_div(px, p.div_w), w = px - h * (uint32_t)p.W;
+  if (p.pad > 0) {
+    const uint64_t ones = (cw == p.Cw - 1 && (p.C & 63)) ? (((uint64_t)1 << (p.C & 63)) - 1) : ~(uint64_t)0;
+    const int H = p.HW / p.W, side = 2 * p.pad;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < p.halo; i += gridDim.x * 256) {
+      const uint32_t in = fast_div(i, p.div_nh);
+      const int k = (int)(i - in * (uint32_t)(p.Hp * p.Wp - p.HW));
       int hh, ww;
-      if (i < pad * Wp) {
-        hh = i / Wp;
-        ww = i - hh * Wp;
-      } else if (i < 2 * pad * Wp) {
-        const int j = i - pad * Wp;
-        hh = j / Wp;
-        ww = j - hh * Wp;
-        hh += pad + H;
+      if (k < side * p.Wp) {  // rows above and below
+        hh = k / p.Wp;
+        ww = k - hh * p.Wp;
+        if (hh >= p.pad) hh += H;
       } else {
-        const int j = i - 2 * pad * Wp;
-        const int r = j / (2 * pad), c = j - r * (2 * pad);
-        hh = pad + r;
-        ww = c < pad ? c : W + c;
+        const int j = k - side * p.Wp, r = j / side, c = j - r * side;
+        hh = p.pad + r;
+        ww = c < p.pad ? c : p.W + c;
       }
-      xpn[((int64_t)hh * Wp + ww) * Cw + cw] = ones;
+      p.xp[(((int64_t)in * p.Hp + hh) * p.Wp + ww) * p.Cw + cw] = ones;
     }
+  }
+  uint32_t b = 0;
+  if (real > 0) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) b |= (v[j] >= (THR ? p.thr[min(c0 + j, p.C - 1)] : 0.0f) ? 1u : 0u) << j;
+    if (real < 16) b &= (1u << real) - 1u;
+  }
+  bits[lane * 4 + wave] = (uint16_t)b;
+  __syncthreads();
+  if (wave == 0 && q < p.pixels) {
+    typedef uint64_t __attribute__((may_alias)) word_alias;
+    p.xp[(((int64_t)n * p.Hp + h + p.pad) * p.Wp + w + p.pad) * p.Cw + cw] = ((const word_alias*)bits)[lane];
   }
 }
 
 hipError_t launch_pack_nchw_thr(const float* x, int N, int C, int H, int W, int pad, const float* thr,
                                 uint64_t* xp, hipStream_t s) {
-  const int Cw = (int)words_for(C);
-  const int HW = H * W;
-  dim3 grid((unsigned)ceil_div(HW, 256), (unsigned)Cw, (unsigned)N);
-  note_kernel("pack_nchw_kernel<%s> grid %u x %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y, grid.z);
-  if (thr)
-    hipLaunchKernelGGL(pack_nchw_kernel<true>, grid, dim3(256), 0, s, x, C, HW, W, pad, H + 2 * pad,
-                       W + 2 * pad, Cw, thr, xp);
-  else
-    hipLaunchKernelGGL(pack_nchw_kernel<false>, grid, dim3(256), 0, s, x, C, HW, W, pad, H + 2 * pad,
-                       W + 2 * pad, Cw, thr, xp);
+  PackNchwParams p;
+  p.thr = thr;
+  p.C = C;
+  p.HW = H * W;
+  p.W = W;
+  p.pad = pad;
+  p.Hp = H + 2 * pad;
+  p.Wp = W + 2 * pad;
+  p.Cw = (int)words_for(C);
+  const int nh = p.Hp * p.Wp - p.HW;
+  p.div_hw = make_fast_div((uint32_t)p.HW);
+  p.div_w = make_fast_div((uint32_t)W);
+  p.div_nh = make_fast_div((uint32_t)(nh > 0 ? nh : 1));
+  const bool nt = p.HW % 32 == 0 && ((uintptr_t)x & 127) == 0;
+  // images per launch: all of them unless they have 2^31 padded pixels or more
+  const int most = (int)std::min<int64_t>(N, (((int64_t)1 << 31) - 1) / ((int64_t)p.Hp * p.Wp));
+  for (int n0 = 0; n0 < N; n0 += most) {
+    const int n = std::min(most, N - n0);
+    p.x = x + (int64_t)n0 * C * p.HW;
+    p.xp = xp + (int64_t)n0 * p.Hp * p.Wp * p.Cw;
+    p.pixels = (uint32_t)n * (uint32_t)p.HW;
+    p.halo = (uint32_t)n * (uint32_t)nh;
+    const dim3 grid((unsigned)ceil_div(p.pixels, 512) * 8, (unsigned)p.Cw);
+    note_kernel("pack_nchw_kernel<%s> grid %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y);
+    auto kern = thr ? (nt ? pack_nchw_kernel<true, true> : pack_nchw_kernel<true, false>)
+                    : (nt ? pack_nchw_kernel<false, true> : pack_nchw_kernel<false, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+  }
   return hipGetLastError();
 }
 

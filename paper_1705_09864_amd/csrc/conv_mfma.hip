@@ -55,6 +55,9 @@ struct WsParams {
   int blk_q, blk_r;      // nblocks / nchunks and nblocks % nchunks
   int x4;                // 1: K-words 2 q, 2 q + 1 are 16 consecutive, 16-byte aligned bytes of the image; 2: 4 q .. 4 q + 3 are 32
   int nt;                // fp32 and int32 result stores bypass the caches
+  // Workgroup b sits on XCD b % 8.  Not 0: every XCD gets a contiguous run of this many workgroups, whose
+  // image rows and whose parts of result lines (planes that are not whole 128-byte lines) meet in its L2.
+  int per_xcd;
   FastDiv div_howo, div_wo;
   int off[kMaxWsWords];  // word offset of K-word j relative to the pixel base
 };
@@ -175,7 +178,8 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5;
   const int m0 = blockIdx.y * (32 * TM);
-  const int chunk = blockIdx.x * NW + wave;
+  const int bx = p.per_xcd ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int chunk = bx * NW + wave;
   // the blocks are dealt out evenly: chunk c takes blk_q of them, the first blk_r chunks one more
   // (no division here: this runs before the wave's first load)
   const int cc = min(chunk, p.nchunks);
@@ -475,15 +479,20 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
 }
 
 template <int KW, int TM, int WPS, bool BITS, int X4, bool ONE = false, int NW = 4>
-void launch_ws_form(const WsParams& p, int m_tiles, hipStream_t s) {
+void launch_ws_form(WsParams p, int m_tiles, hipStream_t s) {
   const int chunks = p.nchunks;
+  // Contiguous runs per XCD where a wave has one block and K is longer than 9 words (75 x 128 x 24 x 23 11.7 ->
+  // 11.1 us a call, 129 x 64 x 18 x 17, 7 x 7, 11.5 -> 11.0).  With several blocks per wave or short K the results
+  // are most of the traffic, and they leave more slowly in that order (75 x 64 x 37 x 39, 3 x 3, 15.7 -> 17.1).
+  p.per_xcd = KW > 9 && chunks == p.nblocks ? (int)ceil_div(chunks, NW * 8) : 0;
+  const int64_t groups = p.per_xcd ? 8 * p.per_xcd : ceil_div(chunks, NW);
   note_kernel("conv_mfma_ws_kernel<%d,%d,%d,%s%s%s> grid %d x %d x %d", KW, TM, WPS, BITS ? "true" : "false",
-              X4 == 2 ? ",x4 runs" : X4 ? ",x4" : "", ONE ? ",one block" : "", (int)ceil_div(chunks, NW), m_tiles, 64 * NW);
+              X4 == 2 ? ",x4 runs" : X4 ? ",x4" : "", ONE ? ",one block" : "", (int)groups, m_tiles, 64 * NW);
 #ifdef BMX_WS_STAMPS
-  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)ceil_div(chunks, NW), (unsigned)m_tiles),
+  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)groups, (unsigned)m_tiles),
                      dim3(64 * NW), 0, s, p, ws_stamps);
 #else
-  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)ceil_div(chunks, NW), (unsigned)m_tiles),
+  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)groups, (unsigned)m_tiles),
                      dim3(64 * NW), 0, s, p);
 #endif
 }

@@ -148,6 +148,8 @@ struct I8Params {
   int32_t* C_i32;
   float* C_f32;
   int64_t ldc;
+  int s_base, s_rem;  // k steps per wave: s_base, the first s_rem waves one more
+  FastDiv div_tiles_m;
 };
 
 constexpr int kAhead = 4;  // k steps per group of loads
@@ -261,14 +263,17 @@ template <int TM, int TN, bool SUMS>
 __global__ void __launch_bounds__(512)
 gemm_i8_kernel(const I8Params p) {
   extern __shared__ int red[];
+  // (all arguments named at the top: fetched in one batch, one trip to memory instead of one per group)
+  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.mblocks), "s"(p.nblocks), "s"(p.tiles_m),
+               "s"(p.tiles), "s"(p.tiles_per_xcd), "s"(p.s_base), "s"(p.s_rem), "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1),
+               "s"(p.div_tiles_m.sh2));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // workgroup b sits on XCD b % 8: every XCD gets a contiguous run of tiles, rows of C fastest
   const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
   if (lin >= p.tiles) return;  // (the whole workgroup)
-  const int tile_n = lin / p.tiles_m, tile_m = lin - tile_n * p.tiles_m;
-  const int S = p.S;
-  const int k_lo = (int)((int64_t)wave * p.nk / S), k_hi = (int)((int64_t)(wave + 1) * p.nk / S);
+  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)lin, p.div_tiles_m)), tile_m = lin - tile_n * p.tiles_m;
+  const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0);
 
   const uint4 *arow[TM], *brow[TN];  // (blocks past the matrix repeat its last one)
 #pragma unroll
@@ -338,8 +343,6 @@ gemm_i8_kernel(const I8Params p) {
 struct QuantSmallParams {
   I8Params g;
   QuantOperand a, w;
-  FastDiv div_tiles_m;
-  int s_base, s_rem;  // steps per wave: s_base, the first s_rem waves one more
 };
 
 template <bool SUMS, bool SIGN>
@@ -347,14 +350,15 @@ __global__ void __launch_bounds__(1024)
 quant_small_kernel(const QuantSmallParams p) {
   extern __shared__ int red[];
   asm volatile("" ::"s"(p.a.x), "s"(p.a.ld), "s"(p.a.L), "s"(p.a.mul), "s"(p.a.add), "s"(p.w.x), "s"(p.w.ld), "s"(p.w.L),
-               "s"(p.w.mul), "s"(p.w.add), "s"(p.g.M), "s"(p.g.N), "s"(p.g.Kreal), "s"(p.g.tiles_m), "s"(p.g.S), "s"(p.s_base),
-               "s"(p.s_rem), "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1), "s"(p.div_tiles_m.sh2));
+               "s"(p.w.mul), "s"(p.w.add), "s"(p.g.M), "s"(p.g.N), "s"(p.g.Kreal), "s"(p.g.tiles_m), "s"(p.g.S), "s"(p.g.s_base),
+               "s"(p.g.s_rem), "s"(p.g.div_tiles_m.mul), "s"(p.g.div_tiles_m.sh1), "s"(p.g.div_tiles_m.sh2));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, h = lane >> 5, c = lane & 7;
-  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div(blockIdx.x, p.div_tiles_m));
+  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div(blockIdx.x, p.g.div_tiles_m));
   const int tile_m = (int)blockIdx.x - tile_n * p.g.tiles_m;
-  const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0), K = p.g.Kreal;
+  const int k_lo = wave * p.g.s_base + min(wave, p.g.s_rem), k_hi = k_lo + p.g.s_base + (wave < p.g.s_rem ? 1 : 0);
+  const int K = p.g.Kreal;
   // byte offsets of row 8 t + lane / 8 (rows past a matrix repeat its last; their results are never stored)
   uint32_t arow[4], wrow[4];
 #pragma unroll
@@ -480,6 +484,12 @@ void fill_product(I8Params& p, int bits_a, int bits_w, int M, int N, int K, int3
 
 }  // namespace
 
+static void set_split(I8Params& p) {
+  p.s_base = p.nk / p.S;
+  p.s_rem = p.nk % p.S;
+  p.div_tiles_m = make_fast_div((uint32_t)p.tiles_m);
+}
+
 // The one-launch form, for any pair of bit widths; false when the problem is too large for it.
 bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
                         int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
@@ -505,9 +515,7 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   const bool sums = bits_a == 8 || bits_w == 8;
   const int64_t S = std::min<int64_t>(sums ? 15 : 16, std::max<int64_t>(1, 4096 / tiles));  // (15: 64 KB of LDS)
   p.g.S = (int)std::min(S, nk);
-  p.s_base = (int)nk / p.g.S;
-  p.s_rem = (int)nk % p.g.S;
-  p.div_tiles_m = make_fast_div((uint32_t)p.g.tiles_m);
+  set_split(p.g);
   const size_t lds = (size_t)p.g.S * (4096 + (sums ? 256 : 0));
   note_kernel("quant_small_kernel%s grid %lld x %d", sums ? "<sums>" : "", (long long)tiles, 64 * p.g.S);
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
@@ -551,6 +559,7 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   S = S > 8 ? 8 : S;
   if (S > p.nk / kAhead) S = p.nk / kAhead;
   p.S = S < 1 ? 1 : S;
+  set_split(p);
   const bool sums = bits_a == 8 || bits_w == 8;
   if (TM == 2) *err = sums ? launch_i8<2, 2, true>(p, s) : launch_i8<2, 2, false>(p, s);
   else if (TN == 2) *err = sums ? launch_i8<1, 2, true>(p, s) : launch_i8<1, 2, false>(p, s);

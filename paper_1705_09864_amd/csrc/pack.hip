@@ -538,10 +538,12 @@ quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda
         v[j] = (affine && k < K) ? __fmul_rn(__fadd_rn(t, 1.0f), 0.5f) : t;
       }
     }
+    // Half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32 (with 0.5 itself the one value
+    // 0.5 - 2^-25 would round up): one addition where roundf takes seven instructions.
     int q[kSegWords];
 #pragma unroll
     for (int j = 0; j < kSegWords; ++j) {
-      q[j] = (int)roundf(__fmul_rn(L, fminf(fmaxf(v[j], 0.0f), 1.0f)));
+      q[j] = (int)__fadd_rn(__fmul_rn(L, fminf(fmaxf(v[j], 0.0f), 1.0f)), 0.49999997f);
       sum += q[j];
     }
     for (int p = 0; p < bits; ++p) {

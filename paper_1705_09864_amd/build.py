@@ -33,25 +33,44 @@ def device_asm(src):
     return os.path.join(BUILD, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
 
 
-def check_scalar_loads():
-    """Scan the compiled device code of every source for registers of an inline-asm scalar
-    load that are touched while the load is still in flight (see isa_check.py; the kernels have
-    no such load, the scan guards against one coming back)."""
+def _isa_check():
     try:
         from . import isa_check
     except ImportError:  # run as a script
         sys.path.insert(0, HERE)
         import isa_check
+    return isa_check
+
+
+def current_asm(src):
+    """device_asm(src), emitted alone if it is missing or older than the source (a fresh checkout)."""
+    path, s = device_asm(src), os.path.join(CSRC, src)
+    if _stale(path, [s]):
+        os.makedirs(BUILD, exist_ok=True)
+        subprocess.check_call([HIPCC] + FLAGS + ["-S", "--cuda-device-only", s, "-o", path],
+                              stderr=subprocess.DEVNULL)
+    return path
+
+
+def check_scalar_loads():
+    """Scan the compiled device code of every source for registers of an inline-asm scalar
+    load that are touched while the load is still in flight (see isa_check.py; the kernels have
+    no such load, the scan guards against one coming back)."""
+    isa_check = _isa_check()
     for src in SOURCES:
-        path = device_asm(src)
-        s = os.path.join(CSRC, src)
-        if _stale(path, [s]):  # e.g. a fresh checkout: emit the device assembly alone
-            os.makedirs(BUILD, exist_ok=True)
-            subprocess.check_call([HIPCC] + FLAGS + ["-S", "--cuda-device-only", s, "-o", path],
-                                  stderr=subprocess.DEVNULL)
-        bad = isa_check.scan(path)
+        bad = isa_check.scan(current_asm(src))
         if bad:
             raise RuntimeError("in-flight scalar load hazard in %s:\n%s" % (src, isa_check.report(bad)))
+
+
+def check_asm_hazards():
+    """Scan the compiled device code of every source for wait states missing in front of or behind an
+    instruction written as asm (isa_check.asm_hazards)."""
+    isa_check = _isa_check()
+    for src in SOURCES:
+        bad = isa_check.asm_hazards(current_asm(src))
+        if bad:
+            raise RuntimeError("missing wait states in %s:\n%s" % (src, isa_check.report_hazards(bad)))
 
 
 def check_codegen():
@@ -64,11 +83,7 @@ def check_codegen():
     the convolution kernel with its filters in LDS reads each MFMA's filter operand with one
     ds_read_b128 (split into dword pairs, the rows meet four ways on the banks)."""
     import re
-    try:
-        from . import isa_check
-    except ImportError:
-        sys.path.insert(0, HERE)
-        import isa_check
+    isa_check = _isa_check()
     for src in SOURCES:
         for name, nbytes in isa_check.scratch_bytes(device_asm(src)).items():
             known = "gemm_mfma_kernelILi2ELi2E" in name or "gemm_kernelILi16ELi32ELb0ELb0ELb1E" in name
@@ -126,6 +141,7 @@ def build(force=True, verbose=False):
     with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     check_scalar_loads()
+    check_asm_hazards()
     check_codegen()
     # (-z defs: an undefined symbol, e.g. a kernel stub the host pass dropped, fails the link here
     # instead of the first call)

@@ -120,8 +120,10 @@ fc_small_kernel(const FcSmallParams p) {
     for (int j = 0; j < 16; ++j) {
       uint64_t b = __ballot(__uint_as_float(v[j]) >= 0.0f);
       if (left < 64 * j + 64) b &= left > 64 * j ? (1ull << (left - 64 * j)) - 1 : 0ull;  // (scalar)
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)b), "i"(j));
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(b >> 32)), "i"(j));
+      // (the wait states between the compare that writes b and its readers are part of the statement: the
+      // compiler, which puts them between its own instructions, does not look into one)
+      asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+          : "+v"(lo), "+v"(hi) : "s"((uint32_t)b), "s"((uint32_t)(b >> 32)), "i"(j));
     }
     if (lane < 16 && 16 * c + lane < p.Kpad) bits[m * p.Kpad + 16 * c + lane] = (uint64_t)hi << 32 | lo;
     c += kWaves;

@@ -8,6 +8,8 @@ end a straight-line run.)  The kernels here fetch their wave-uniform operands wi
 constant-address-space loads, which the compiler tracks itself, so the scan finds no such load
 at all; it stays in the build as a guard against one coming back.
 
+asm_hazards(): wait states missing between an instruction of the compiler's and one written as asm.
+
 kernel_stats(): spill counts and instruction histograms per kernel, for the code-generation
 checks of the build.
 """
@@ -71,6 +73,86 @@ def scan(path):
             if in_asm and op.startswith('s_load_dword'):
                 inflight.append((tuple(sorted(dst)), i))
     return sorted(out, key=lambda e: e[1])
+
+WAIT_SGPR_VALU, WAIT_SGPR_MEMORY, WAIT_LANES, WAIT_MFMA, WAIT_TRANS = 2, 5, 2, 20, 1
+TRANS = ('v_rcp', 'v_rsq', 'v_sqrt', 'v_exp', 'v_log', 'v_sin', 'v_cos')
+
+def operands(tok):
+    """Registers of an operand, as 's4', 'v7', 'a3' or 'vcc'."""
+    tok = tok.strip().lstrip('-').strip('|')
+    if tok.startswith('vcc'): return {'vcc'}
+    m = re.match(r'^([sva])\[(\d+):(\d+)\]$', tok)
+    if m: return {m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
+    return {tok} if re.match(r'^[sva]\d+$', tok) else set()
+
+def asm_hazards(path):
+    """Wait states that the compiler leaves out because it does not look into an asm statement.
+
+    The vector ALU does not interlock some of its results: a scalar register that it has written (a
+    compare's mask, v_readlane) needs two wait states before the vector ALU reads it and five before a
+    memory instruction does, a matrix-core result up to twenty (the longest of the documented cases is
+    taken for all), a transcendental result one, and a vector result two before an instruction across
+    lanes (DPP, permlane, readlane) reads it.  The compiler puts s_nop between its own instructions; a
+    pair of which one is written as asm gets none.  Walks every kernel along all its edges with the least
+    number of wait states since each such write, and reports every pair with too few:
+    (kernel, line, text, register, wait states there, wait states needed)."""
+    rows, kern, in_asm = [], None, False  # labels, kernel starts and instructions with what they read and write
+    for i, l in enumerate(open(path)):
+        t = l.strip()
+        if t.startswith(';;#ASMSTART'): in_asm = True; continue
+        if t.startswith(';;#ASMEND'): in_asm = False; continue
+        m = re.match(r'^(_Z\w+|\.LBB\w+):', t)
+        if m:
+            if t[0] == '_': kern = m.group(1)
+            rows.append((i, kern, None if t[0] == '_' else m.group(1)))
+            continue
+        if not kern or not t or t[0] in ';.': continue
+        t = t.split(';')[0].strip()
+        op = t.split()[0]
+        args = [a.split()[0] for a in t[len(op):].split(',') if a.strip()]
+        memory = op.startswith(('global_', 'buffer_', 'flat_', 'scratch_', 'ds_'))
+        ndst = 0 if 'store' in op or 'write_b' in op else 2 if '_co_' in op or 'v_div_scale' in op or 'swap' in op else 1
+        dst = set().union(*[operands(a) for a in args[:ndst]])
+        src = set().union(*[operands(a) for a in args[0 if 'swap' in op else ndst:]])
+        if op.startswith('v_cmp') and op.endswith('_e32'): dst.add('vcc')
+        lanes = op.startswith(('v_readlane', 'v_readfirstlane', 'v_permlane')) or '_dpp' in op
+        reader = {}  # wait states that this instruction needs behind each kind of write
+        if in_asm and memory: reader = {'sgpr': WAIT_SGPR_MEMORY, 'mfma': WAIT_MFMA}
+        elif in_asm and op.startswith('v_'): reader = {'sgpr': WAIT_SGPR_VALU, 'mfma': WAIT_MFMA, 'trans': WAIT_TRANS}
+        if lanes: reader['asm'] = WAIT_LANES
+        writes = []
+        if op.startswith('v_'):
+            for r in dst:
+                if r[0] == 's' or r == 'vcc': writes.append((r, 'sgpr'))
+                elif op.startswith(('v_mfma', 'v_smfma')): writes.append((r, 'mfma'))
+                elif op.startswith(TRANS): writes.append((r, 'trans'))
+                elif in_asm: writes.append((r, 'asm'))
+        step = int(args[0], 0) + 1 if op == 's_nop' else 1
+        rows.append((i, kern, op, t, dst, src, reader, writes, step, args[0] if 'branch' in op else None))
+    label_in, found, changed = {}, {}, True
+    while changed:  # until the states carried by backward branches settle
+        changed, state = False, {}
+        for row in rows:
+            if len(row) == 3:
+                if row[2] is None: state = {}
+                for k, n in label_in.get(row[1:], {}).items(): state[k] = min(n, state.get(k, n))
+                continue
+            i, kern, op, t, dst, src, reader, writes, step, to = row
+            if reader:
+                for (r, kind), n in state.items():
+                    if r in src and n < reader.get(kind, 0): found[i] = (kern, i + 1, t, r, n, reader[kind])
+            if state:
+                state = {k: n + step for k, n in state.items() if n + step < WAIT_MFMA and k[0] not in dst}
+            for k in writes: state[k] = 0
+            if to:
+                at = label_in.setdefault((kern, to), {})
+                for k, n in state.items():
+                    if n < at.get(k, WAIT_MFMA): at[k] = n; changed = True
+            if op in ('s_branch', 's_endpgm', 's_setpc_b64'): state = {}
+    return [found[i] for i in sorted(found)]
+
+def report_hazards(bad, limit=40):
+    return "\n".join("%s: line %d: '%s' reads %s after %d wait states of %d" % e for e in bad[:limit])
 
 def report(bad, limit=40):
     lines = ["%s: line %d: '%s' %s SGPR %s of the scalar load issued at line %d" % e for e in bad[:limit]]

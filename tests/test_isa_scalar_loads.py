@@ -1,4 +1,5 @@
-"""The scanner for hand-placed scalar loads, and the code-generation checks of the build.
+"""The scanners for hand-placed scalar loads and for wait states around asm statements, and the
+code-generation checks of the build.
 
 A scalar load written as inline asm is invisible to the compiler between its issue and the
 s_waitcnt that follows: nothing scheduled there may touch its destination SGPRs.  The kernels
@@ -72,3 +73,46 @@ def test_compiled_kernels_keep_registers_and_wide_lds_reads():
     hip_build.check_codegen()
     stats = isa_check.kernel_stats(hip_build.device_asm("conv_mfma.hip"))
     assert any("conv_mfma_ws_kernelILi9ELi1E" in k for k in stats)
+
+
+# a compare writes a mask and an asm statement reads it at the join behind a branch around the
+# compiler's own use of it: one wait state (the branch) on the short way, two are needed
+HAZARD = """
+_Z4kernv:
+	v_cmp_le_f32_e64 s[0:1], 0, v11
+	s_cbranch_scc1 .LBB0_1
+	s_and_b64 s[0:1], s[0:1], s[40:41]
+.LBB0_1:
+	;;#ASMSTART
+	v_writelane_b32 v10, s1, 3
+	;;#ASMEND
+	s_endpgm
+"""
+# (text, wait states there, wait states needed), None where nothing is to be reported
+HAZARDS = [
+    (HAZARD, (1, 2)),
+    (HAZARD.replace("v_writelane_b32", "s_nop 0\n\tv_writelane_b32"), None),
+    (HAZARD.replace("v_writelane_b32 v10, s1, 3", "s_nop 1\n\tv_writelane_b32 v10, s1, 3"), None),
+    (HAZARD.replace(";;#ASMSTART", "").replace(";;#ASMEND", ""), None),  # the compiler's own pair
+    (HAZARD.replace("v_cmp_le_f32_e64 s[0:1], 0, v11", "s_mov_b64 s[0:1], 0"), None),  # scalar results interlock
+    (HAZARD.replace("v_writelane_b32 v10, s1, 3", "global_store_dword v3, v4, s[0:1] nt"), (1, 5)),
+    (HAZARD.replace("v_cmp_le_f32_e64 s[0:1], 0, v11", "v_readlane_b32 s0, v9, 4"), None),  # (s1 is read, not s0)
+    (HAZARD.replace("v_writelane_b32 v10, s1, 3", "v_add_u32_e32 v10, v11, v12").replace(
+        "s_endpgm", "v_mov_b32_dpp v1, v10 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\ts_endpgm"), (0, 2)),
+    (HAZARD.replace("v_cmp_le_f32_e64 s[0:1], 0, v11", "v_mfma_i32_32x32x32_i8 v[0:15], v[20:23], v[24:27], v[0:15]").replace(
+        "v_writelane_b32 v10, s1, 3", "v_bcnt_u32_b32 v30, v15, v30"), (1, 20)),
+]
+
+
+@pytest.mark.parametrize("text,expected", HAZARDS)
+def test_asm_wait_states(tmp_path, text, expected):
+    f = tmp_path / "k.s"
+    f.write_text(text)
+    bad = isa_check.asm_hazards(str(f))
+    assert [e[4:] for e in bad] == ([expected] if expected else [])
+
+
+@pytest.mark.skipif(shutil.which(hip_build.HIPCC) is None and not os.path.exists(hip_build.HIPCC),
+                    reason="hipcc not available")
+def test_compiled_kernels_leave_asm_its_wait_states():
+    hip_build.check_asm_hazards()   # raises with the offending lines

@@ -81,14 +81,17 @@ def check_codegen():
     GEMM aside: a small array indexed at run time lands there, and every scratch access also
     waits for all stores issued before it, which cost the K-split GEMM 0.7 us per launch); and
     the convolution kernel with its filters in LDS reads each MFMA's filter operand with one
-    ds_read_b128 (split into dword pairs, the rows meet four ways on the banks)."""
+    ds_read_b128 (split into dword pairs, the rows meet four ways on the banks), holds one set of
+    result stores for blocks inside the result and one for its edge, and spills no scalar registers
+    (its instructions come from a cold cache at every launch)."""
     import re
     isa_check = _isa_check()
     for src in SOURCES:
-        for name, nbytes in isa_check.scratch_bytes(device_asm(src)).items():
+        for name, nbytes in isa_check.metadata(device_asm(src), "private_segment_fixed_size").items():
             known = "gemm_mfma_kernelILi2ELi2E" in name or "gemm_kernelILi16ELi32ELb0ELb0ELb1E" in name
             if nbytes and not known:
                 raise RuntimeError("%s: kernel %s uses %d bytes of scratch memory per lane" % (src, name, nbytes))
+        sgpr = isa_check.metadata(device_asm(src), "sgpr_spill_count")
         for name, (spills, ops) in isa_check.kernel_stats(device_asm(src)).items():
             allowed = 16 if "gemm_mfma_kernelILi2ELi2E" in name else 0
             if spills > allowed:
@@ -98,6 +101,12 @@ def check_codegen():
                 raise RuntimeError("%s: kernel %s reads its filter operands with %d ds_read_b128, "
                                    "expected %d" % (src, name, ops["ds_read_b128"],
                                                     int(m.group(1)) * int(m.group(2))))
+            stores = ops["global_store_dword"]
+            if m and stores > 32 * int(m.group(2)) + 8:
+                raise RuntimeError("%s: kernel %s holds %d result stores, expected one set for blocks inside the "
+                                   "result and one for its edge" % (src, name, stores))
+            if m and m.group(2) == "1" and sgpr[name]:
+                raise RuntimeError("%s: kernel %s spills %d scalar registers" % (src, name, sgpr[name]))
 
 
 def build_host_binding():

@@ -36,6 +36,7 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef v4i __attribute__((may_alias)) v4i_alias;
 
 constexpr int kMaxWsWords = 50;
+constexpr int kF32 = 0, kI32 = 1, kBits = 2, kNt = 4;  // kinds of result, see conv_mfma_ws_kernel
 
 struct WsParams {
   const uint64_t* Xp;  // halo-padded packed image
@@ -54,7 +55,6 @@ struct WsParams {
   int nblocks, nchunks;  // blocks of 32 pixels in all; waves they are dealt out to (evenly)
   int blk_q, blk_r;      // nblocks / nchunks and nblocks % nchunks
   int x4;                // 1: K-words 2 q, 2 q + 1 are 16 consecutive, 16-byte aligned bytes of the image; 2: 4 q .. 4 q + 3 are 32
-  int nt;                // fp32 and int32 result stores bypass the caches
   // Workgroup b sits on XCD b % 8.  Not 0: every XCD gets a contiguous run of this many workgroups, whose
   // image rows and whose parts of result lines (planes that are not whole 128-byte lines) meet in its L2.
   int per_xcd;
@@ -138,7 +138,12 @@ constexpr int kWs36Waves = 3;  // waves per SIMD at 36 words, 16-byte pixel load
 #endif
 
 // WPS: waves per SIMD the register allocation is held to.
-// BITS: the result leaves as packed sign bits (see WsParams::out_bits); the workgroups also
+// OUT: the kind of result, and for fp32 and int32 whether the stores bypass the caches (kNt added): a kernel
+// holds one set of stores for blocks inside the result and one for its edge.  The instruction cache is cold at
+// every launch: chosen at run time, the eight sets made 9.4 KB of code where there are 3.7 now (9 words, one block)
+// and 11.4 where there are 5.9 (36 words, one block), with 30 scalar registers spilled, and from HBM 16 x 64 x 56 x 56 took
+// 4.8 us in place of 4.3 to 4.4, 64 x 256 x 14 x 14 over 256 filters 8.1 to 8.4 in place of 7.7 to 8.1.
+// kBits: the result leaves as packed sign bits (see WsParams::out_bits); the workgroups also
 // write the constant halo words of the output image.
 
 // X4: the pixel words are fetched 16 bytes at a time (1: an even number of channel words, so that
@@ -154,11 +159,12 @@ constexpr int kWs36Waves = 3;  // waves per SIMD at 36 words, 16-byte pixel load
 // block, so that each expands half as much of it and a CU holds half as many copies.  Worth
 // 0.5 us where four waves per SIMD contend for the vector ALU over 36 words (64 x 256 x 14 x 14,
 // 256 filters: 8.5 -> 8.0 us), nothing at 9 words, and sixteen waves leave CUs empty there (8.7).
-template <int KW, int TM, int WPS, bool BITS, int X4, bool ONE = false, int NW = 4>
+template <int KW, int TM, int WPS, int OUT, int X4, bool ONE = false, int NW = 4>
 __global__ void __launch_bounds__(64 * NW, WPS * 4 / NW)
 conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
   static_assert(NW == 4 || (NW == 8 && WPS % 2 == 0), "whole workgroups per CU");
   constexpr int kThreads = 64 * NW;
+  constexpr bool BITS = OUT == kBits, I32 = (OUT & ~kNt) == kI32, NT = (OUT & kNt) != 0;
   static_assert((!X4 || KW % 2 == 0) && (X4 != 2 || KW % 4 == 0), "pairs of words, or fours");
   // load instructions per block: two words per pixel each, or four
   constexpr int NI = X4 ? (KW + 3) / 4 : (KW + 1) / 2;
@@ -422,7 +428,10 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
         const uint32_t pitch = (uint32_t)p.HoWo * 4u;
         const uint32_t lane_off = cur.obase * 4u + (uint32_t)(m0 + 32 * i + 4 * h) * pitch;
         const bool inside = b * 32 + 32 <= p.P && m0 + 32 * TM <= p.O;
-        auto put = [&](auto inside_tag, auto int_tag, auto nt_tag) {
+        // (the stores are written out: the compiler builds a 64-bit vector address for a non-temporal
+        // store even from a uniform base and a 32-bit offset)
+        const char* const out = I32 ? (const char*)p.out_i32 : (const char*)p.out_f32;
+        auto put = [&](auto inside_tag) {
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int mi = 8 * (v / 4) + (v % 4);
@@ -430,41 +439,19 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
             // and all sixteen stores share one lane offset; with several blocks per wave the
             // compiler would keep sixteen such bases across the block loop and run out of SGPRs)
             const uint32_t off = ONE ? lane_off : lane_off + (uint32_t)mi * pitch;
-            const size_t row_bytes = ONE ? (size_t)mi * pitch : 0;
+            const char* const base = out + (ONE ? (size_t)mi * pitch : 0);
             const float t = fmaf(2.0f, acc[i][0][v], c0[v]);
             if (decltype(inside_tag)::value || (cur.valid && m0 + 32 * i + mi + 4 * h < p.O)) {
-              // (written out: the compiler builds a 64-bit vector address for a non-temporal
-              // store even from a uniform base and a 32-bit offset)
-              if constexpr (decltype(int_tag)::value) {
-                const int iv = (int)t;
-                if constexpr (decltype(nt_tag)::value)
-                  asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(iv), "s"((const char*)p.out_i32 + row_bytes) : "memory");
-                else
-                  asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(iv), "s"((const char*)p.out_i32 + row_bytes) : "memory");
-              } else {
-                const float fv = al[v] * t;
-                if constexpr (decltype(nt_tag)::value)
-                  asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(fv), "s"((const char*)p.out_f32 + row_bytes) : "memory");
-                else
-                  asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(fv), "s"((const char*)p.out_f32 + row_bytes) : "memory");
-              }
+              typename std::conditional<I32, int, float>::type value;
+              if constexpr (I32) value = (int)t;
+              else value = al[v] * t;
+              if constexpr (NT) asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(off), "v"(value), "s"(base) : "memory");
+              else asm volatile("global_store_dword %0, %1, %2" ::"v"(off), "v"(value), "s"(base) : "memory");
             }
           }
         };
-        // (non-temporal where a block's 32 pixels of a plane are one whole 128-byte line, 8.9 against
-        // 10.3 us a call on 16 x 64 x 56 x 56; where they are parts of two lines such parts of a large result
-        // reach memory one by one: 57 x 64 x 54 x 54 26.1 us with the hint, 18.4 through L2)
-        auto put_nt = [&](auto nt_tag) {
-          if (p.out_i32) {
-            if (inside) put(std::true_type{}, std::true_type{}, nt_tag);
-            else put(std::false_type{}, std::true_type{}, nt_tag);
-          } else {
-            if (inside) put(std::true_type{}, std::false_type{}, nt_tag);
-            else put(std::false_type{}, std::false_type{}, nt_tag);
-          }
-        };
-        if (p.nt) put_nt(std::true_type{});
-        else put_nt(std::false_type{});
+        if (inside) put(std::true_type{});
+        else put(std::false_type{});
       }
     }
     if constexpr (ONE) break;
@@ -478,6 +465,16 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
 #endif
 }
 
+// Whether result stores bypass the caches: where a block's 32 pixels of a plane are one whole 128-byte line,
+// 8.9 against 10.3 us a call on 16 x 64 x 56 x 56 (where they are parts of two lines such parts of a large result
+// reach memory one by one: 57 x 64 x 54 x 54 26.1 us with the hint, 18.4 through L2), and for results that the memory-side
+// cache takes in as they come (64 x 256 x 14 x 14, 12.8 MB, 13.5 us a call with the hint and 14.1 without; from about
+// 30 MB on parts of lines lose).
+bool nt_stores(const WsParams& p) {
+  return (p.HoWo % 32 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 127) == 0) ||
+         (int64_t)p.Nimg * p.O * p.HoWo * 4 <= (20 << 20);
+}
+
 template <int KW, int TM, int WPS, bool BITS, int X4, bool ONE = false, int NW = 4>
 void launch_ws_form(WsParams p, int m_tiles, hipStream_t s) {
   const int chunks = p.nchunks;
@@ -488,13 +485,22 @@ void launch_ws_form(WsParams p, int m_tiles, hipStream_t s) {
   const int64_t groups = p.per_xcd ? 8 * p.per_xcd : ceil_div(chunks, NW);
   note_kernel("conv_mfma_ws_kernel<%d,%d,%d,%s%s%s> grid %d x %d x %d", KW, TM, WPS, BITS ? "true" : "false",
               X4 == 2 ? ",x4 runs" : X4 ? ",x4" : "", ONE ? ",one block" : "", (int)groups, m_tiles, 64 * NW);
+  auto go = [&](auto kern) {
 #ifdef BMX_WS_STAMPS
-  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)groups, (unsigned)m_tiles),
-                     dim3(64 * NW), 0, s, p, ws_stamps);
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p, ws_stamps);
 #else
-  hipLaunchKernelGGL((conv_mfma_ws_kernel<KW, TM, WPS, BITS, X4, ONE, NW>), dim3((unsigned)groups, (unsigned)m_tiles),
-                     dim3(64 * NW), 0, s, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p);
 #endif
+  };
+  if constexpr (BITS) {
+    go(conv_mfma_ws_kernel<KW, TM, WPS, kBits, X4, ONE, NW>);
+  } else if (nt_stores(p)) {
+    if (p.out_i32) go(conv_mfma_ws_kernel<KW, TM, WPS, kI32 + kNt, X4, ONE, NW>);
+    else go(conv_mfma_ws_kernel<KW, TM, WPS, kF32 + kNt, X4, ONE, NW>);
+  } else {
+    if (p.out_i32) go(conv_mfma_ws_kernel<KW, TM, WPS, kI32, X4, ONE, NW>);
+    else go(conv_mfma_ws_kernel<KW, TM, WPS, kF32, X4, ONE, NW>);
+  }
 }
 
 // WPS_X4: waves per SIMD of the form with 16-byte pixel loads, which needs fewer registers.
@@ -557,9 +563,6 @@ bool launch_conv_mfma_ws(const uint64_t* Xp, int Nimg, int C, int H, int W, cons
   p.out_i32 = out_i32;
   p.out_f32 = out_f32;
   p.out_bits = (uint32_t*)out_bits;
-  // (whole lines, or results the memory-side cache takes in as they come: 64 x 256 x 14 x 14, 12.8 MB,
-  // 13.5 us a call with the hint and 14.1 without; from about 30 MB on parts of lines lose)
-  p.nt = (Ho * Wo % 32 == 0 && (((uintptr_t)out_i32 | (uintptr_t)out_f32) & 127) == 0) || (int64_t)Nimg * O * Ho * Wo * 4 <= (20 << 20);
   p.thr = thr;
   p.Nimg = Nimg;
   p.Ho = Ho;

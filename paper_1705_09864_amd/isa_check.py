@@ -195,14 +195,14 @@ def kernel_stats(path):
     return {k: (spills.get(k, 0), v) for k, v in body.items() if k in spills}
 
 
-def scratch_bytes(path):
-    """Per kernel of a device listing: bytes of private (scratch) memory per lane, from the
-    metadata.  Returns {mangled name: bytes}."""
+def metadata(path, field):
+    """Per kernel of a device listing: a number of its metadata, e.g. "private_segment_fixed_size" (bytes of
+    scratch memory per lane) or "sgpr_spill_count".  Returns {mangled name: number}."""
     out = {}
     text = open(path).read()
     for block in text.split("  - .agpr_count:")[1:]:
         n = re.search(r"\.name:\s+(\S+)", block)
-        v = re.search(r"\.private_segment_fixed_size:\s+(\d+)", block)
+        v = re.search(r"\.%s:\s+(\d+)" % field, block)
         if n and v:
             out[n.group(1)] = int(v.group(1))
     return out

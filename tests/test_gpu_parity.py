@@ -337,6 +337,28 @@ def test_conv_output_offsets_beyond_two_gib():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("C,k", [(64, 3), (100, 3), (64, 5), (192, 3), (200, 3), (40, 7), (128, 5)])
+@pytest.mark.parametrize("integer_out", [False, True])
+def test_conv_result_stores_with_and_without_the_streaming_hint(C, k, integer_out):
+    """Planes that are not whole 128-byte lines: a result of more than 20 MB leaves through the caches, its parts of
+    ten images bypass them, each in a kernel of its own; blocks inside the result and at both its edges."""
+    N, H, O = 130, 33, 40
+    rng = np.random.default_rng(C + k)
+    x = rng.standard_normal((N, C, H, H)).astype(np.float32)
+    w = rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha = oracle.alpha_mean_abs(w)
+    got = run_conv(x, w, 1, k // 2, alpha=None if integer_out else alpha, integer_out=integer_out)
+    assert "conv_mfma_ws_kernel" in B.last_kernel() and got.nbytes > 20 << 20
+    for n in range(0, N, 10):
+        part = run_conv(x[n:n + 10], w, 1, k // 2, alpha=None if integer_out else alpha, integer_out=integer_out)
+        np.testing.assert_array_equal(got[n:n + 10], part)
+    ri, rf = oracle.binary_conv2d(x[-1:], w, 1, k // 2, alpha)
+    if integer_out:
+        np.testing.assert_array_equal(got[-1:], ri)
+    else:
+        assert_f32_close(got[-1:], rf)
+
+
 def test_conv_padding_closed_form_on_gpu():
     C, H, W, O = 5, 6, 6, 2
     K = 9 * C

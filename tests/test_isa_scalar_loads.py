@@ -67,8 +67,9 @@ def test_compiled_kernels_have_no_inflight_hazard():
 @pytest.mark.skipif(shutil.which(hip_build.HIPCC) is None and not os.path.exists(hip_build.HIPCC),
                     reason="hipcc not available")
 def test_compiled_kernels_keep_registers_and_wide_lds_reads():
-    """No vector-register spills, no scratch memory, and one 16-byte LDS read per MFMA filter operand in the
-    short-K convolution kernel (see build.check_codegen)."""
+    """No vector-register spills, no scratch memory, and in the short-K convolution kernel one 16-byte LDS read
+    per MFMA filter operand, one set of result stores for blocks inside the result and one for its edge, and no
+    scalar-register spills (see build.check_codegen)."""
     hip_build.check_scalar_loads()   # makes sure the device listings exist
     hip_build.check_codegen()
     stats = isa_check.kernel_stats(hip_build.device_asm("conv_mfma.hip"))

@@ -166,8 +166,7 @@ conv_stationary_kernel(const ConvParams p) {
           asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(dot) : "v"(pc), "s"(p.Kreal));
           // scalar base + 32-bit lane offset: the store needs no vector address arithmetic
           // (NT, non-temporal: the output is written once and never read here; measured 6.5
-          // against 7.8 us on the 16 x 64 x 56 x 56 layer.  Only where a wave's 64 pixels are whole 128-byte
-          // lines: 107 x 192 planes of 23 x 25 took 19.3 us with it, planes of 24 x 24 9.6 us)
+          // against 7.8 us on the 16 x 64 x 56 x 56 layer)
           if (OUT == kOutF32Alpha) {
             const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lane), row));
             const float v = a * (float)dot;
@@ -218,9 +217,16 @@ conv_general_kernel(const uint64_t* __restrict__ Xp, const uint64_t* __restrict_
 template <int KW>
 void launch_stationary(const ConvParams& p, int64_t groups, int cblocks, hipStream_t s) {
   dim3 grid((unsigned)ceil_div(groups, 4), (unsigned)cblocks);
-  note_kernel("conv_stationary_kernel<%d,%s> grid %u x %u x 256, %d filters per wave", KW,
-              p.out_f32 ? (p.alpha ? "f32*alpha" : "f32") : "i32", grid.x, grid.y, p.cn);
-  const bool nt = p.HoWo % 64 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 127) == 0;
+  // Streaming stores where a wave's 64 pixels are whole 128-byte lines, and for parts of lines while the
+  // memory-side cache takes the result in as it comes, which depends on how small the parts are.  us a launch with the
+  // hint and without, 1 x 1 over 256 channels of 14 x 14: 12 MB 6.1 / 8.1, 25 MB 10.6 / 11.8, 90 MB 42.6 / 32.2;
+  // 10 x 10: 9 MB 4.8 / 6.4, 19 MB 8.5 / 9.4, 32 MB 14.2 / 13.3; planes smaller than a wave, 7 x 7: 6 MB 4.3 / 5.1, 12 MB
+  // 6.7 / 6.6, 19 MB 10.3 / 9.5; 6 x 5: 12 MB 7.2 / 6.3; 3 x 3: 6 MB 7.2 / 5.4.
+  const int64_t bytes = p.P * p.O * 4;
+  const bool nt = (p.HoWo % 64 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 127) == 0) ||
+                  bytes <= (p.HoWo >= 64 ? 20 << 20 : p.HoWo >= 32 ? 10 << 20 : 0);
+  note_kernel("conv_stationary_kernel<%d,%s%s> grid %u x %u x 256, %d filters per wave", KW,
+              p.out_f32 ? (p.alpha ? "f32*alpha" : "f32") : "i32", nt ? ",nt" : "", grid.x, grid.y, p.cn);
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
   if (p.out_f32 && p.alpha) nt ? go(conv_stationary_kernel<KW, kOutF32Alpha, true>) : go(conv_stationary_kernel<KW, kOutF32Alpha, false>);
   else if (p.out_f32) nt ? go(conv_stationary_kernel<KW, kOutF32, true>) : go(conv_stationary_kernel<KW, kOutF32, false>);

@@ -359,6 +359,26 @@ def test_conv_result_stores_with_and_without_the_streaming_hint(C, k, integer_ou
         assert_f32_close(got[-1:], rf)
 
 
+@pytest.mark.parametrize("N,H,W,O,nt", [(64, 14, 14, 256, True), (120, 14, 14, 256, False), (110, 7, 7, 256, True),
+                                        (230, 7, 7, 256, False), (200, 5, 6, 64, False), (85, 16, 16, 256, True)])
+def test_popcount_conv_streams_small_results_and_whole_lines(N, H, W, O, nt):
+    """1 x 1 over 256 channels: the hint of the result stores by plane and size, and the results it leaves."""
+    rng = np.random.default_rng(N + H)
+    x = rng.standard_normal((N, 256, H, W)).astype(np.float32)
+    w = rng.standard_normal((O, 256, 1, 1)).astype(np.float32)
+    alpha = oracle.alpha_mean_abs(w)
+    with tuned(k5=1):
+        got = run_conv(x, w, 1, 0, alpha=alpha)
+        kernel = B.last_kernel()
+        goti = run_conv(x, w, 1, 0, integer_out=True)
+    assert "conv_stationary_kernel" in kernel and (",nt>" in kernel) == nt, kernel
+    at = np.r_[0:3, N - 3:N]
+    ri, rf = oracle.binary_conv2d(x[at], w, 1, 0, alpha)
+    np.testing.assert_array_equal(goti[at], ri)
+    assert_f32_close(got[at], rf)
+    np.testing.assert_array_equal(got, (alpha[None, :, None, None] * goti.astype(np.float32)).astype(np.float32))
+
+
 def test_conv_padding_closed_form_on_gpu():
     C, H, W, O = 5, 6, 6, 2
     K = 9 * C

@@ -214,7 +214,8 @@ def binary_fc_static(x, Wp, alpha=None, integer_out=False, out=None, stream=None
 
 
 def binary_fc_packed(xp, in_features, Wp, alpha=None, mode="f32", out=None, thr=None, stream=None):
-    """xp: packed activations [batch, words].  mode: "f32", "i32" or "bits" (packed sign bits,
+    """xp: packed activations [batch, words]; like every packed matrix here and every given out it may be a
+    contiguous tensor of more dimensions, e.g. a packed image [N, H, W, words] as N rows.  mode: "f32", "i32" or "bits" (packed sign bits,
     against the per-feature threshold thr if given)."""
     return (_native or _host()).binary_fc_packed(xp, in_features, Wp, alpha, mode, out, thr, stream)
 

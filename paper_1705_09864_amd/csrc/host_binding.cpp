@@ -76,11 +76,29 @@ T required(PyObject* o, at::ScalarType type, int dims, const char* what, bool de
   return t;
 }
 
+// A matrix by rows: size(0) of them, whatever dimensions a row has (a packed image [N, H, W, words] is N rows; a
+// vector, rows of one element).  Of more than two dimensions only contiguous tensors pass the guard above.
+T matrix(PyObject* o, at::ScalarType type, const char* what) {
+  T t = tensor(o, type, what);
+  if (!t) raise_value("%s: expected a torch tensor, got None%s%s", what);
+  if (t->dim() < 2 && (t->dim() < 1 || t->size(0) < 2))
+    raise_value("%s: expected rows of a matrix, got %s dimensions%s", what, std::to_string(t->dim()).c_str());
+  return t;
+}
+
+// A packed image [N, H, W, words]; the words of a single one may be left out.
+T packed_image(PyObject* o, const char* what) {
+  T t = tensor(o, kU64, what, true);
+  if (!t) raise_value("%s: expected a torch tensor, got None%s%s", what);
+  if (t->dim() < 3) raise_value("%s: expected a packed image, got %s dimensions%s", what, std::to_string(t->dim()).c_str());
+  return t;
+}
+
 template <class P>
 P* ptr(T t) { return t ? static_cast<P*>(t->data_ptr()) : nullptr; }
 
 // Row stride of a matrix in elements (its row length when it has a single row).
-int64_t ld(T t) { return t->size(0) > 1 ? t->stride(0) : std::max<int64_t>(t->size(1), 1); }
+int64_t ld(T t) { return t->size(0) > 1 ? t->stride(0) : std::max<int64_t>(t->dim() == 2 ? t->size(1) : t->numel(), 1); }
 
 int64_t integer(PyObject* o) {
   const int64_t v = PyLong_AsLongLong(o);
@@ -121,7 +139,7 @@ struct Out {
       made = at::Tensor(at::detail::empty_cuda(shape, type, like->device(), std::nullopt));
       t = &made;
     } else {
-      t = dense ? tensor(o, type, what, true) : required(o, type, 2, what);
+      t = dense ? tensor(o, type, what, true) : matrix(o, type, what);
       given = o;
     }
   }
@@ -201,7 +219,7 @@ FUNCTION(binarize_pack, 4) {  // x, pack_dim, out, stream
 }
 
 FUNCTION(unpack_pm1, 4) {  // bits, K, out, stream
-  T bits = required(a[0], kU64, 2, "unpack_pm1 bits");
+  T bits = matrix(a[0], kU64, "unpack_pm1 bits");
   const int64_t rows = bits->size(0), K = integer(a[1]);
   Out out(a[2], kF32, {rows, std::max<int64_t>(K, 0)}, bits, "unpack_pm1 out");
   check_status(bmx_unpack_pm1(ptr<uint64_t>(bits), rows, K, ld(bits), ptr<float>(out.t), ld(out.t), stream_of(a[3])),
@@ -210,7 +228,7 @@ FUNCTION(unpack_pm1, 4) {  // bits, K, out, stream
 }
 
 FUNCTION(xnor_gemm, 6) {  // A, B, K, out, stream, count
-  T A = required(a[0], kU64, 2, "xnor_gemm A"), B = required(a[1], kU64, 2, "xnor_gemm B");
+  T A = matrix(a[0], kU64, "xnor_gemm A"), B = matrix(a[1], kU64, "xnor_gemm B");
   const int64_t M = A->size(0), N = B->size(0);
   Out out(a[3], kI32, {M, N}, A, "xnor_gemm out");
   const bool count = truth(a[5]);
@@ -222,7 +240,7 @@ FUNCTION(xnor_gemm, 6) {  // A, B, K, out, stream, count
 }
 
 FUNCTION(widen_words32, 4) {  // rows32, K, out, stream
-  T in = required(a[0], kI32, 2, "widen_words32 rows32");
+  T in = matrix(a[0], kI32, "widen_words32 rows32");
   const int64_t rows = in->size(0), K = integer(a[1]);
   Out out(a[2], kU64, {rows, std::max<int64_t>(words(K), 0)}, in, "widen_words32 out");
   check_status(bmx_widen_words32(ptr<uint32_t>(in), rows, K, ld(in), ptr<uint64_t>(out.t), ld(out.t), stream_of(a[3])),
@@ -231,7 +249,7 @@ FUNCTION(widen_words32, 4) {  // rows32, K, out, stream
 }
 
 FUNCTION(xnor_gemm_w32, 6) {  // A32, B32, K, out, workspace, stream
-  T A = required(a[0], kI32, 2, "xnor_gemm_w32 A"), B = required(a[1], kI32, 2, "xnor_gemm_w32 B");
+  T A = matrix(a[0], kI32, "xnor_gemm_w32 A"), B = matrix(a[1], kI32, "xnor_gemm_w32 B");
   const int64_t M = A->size(0), N = B->size(0);
   const int K = small(a[2]);
   Out out(a[3], kI32, {M, N}, A, "xnor_gemm_w32 out");
@@ -247,7 +265,7 @@ FUNCTION(xnor_gemm_w32, 6) {  // A32, B32, K, out, workspace, stream
 }
 
 FUNCTION(binary_fc, 7) {  // x, Wp, alpha, integer_out, out, workspace, stream
-  T x = required(a[0], kF32, 2, "binary_fc x"), W = required(a[1], kU64, 2, "binary_fc Wp");
+  T x = required(a[0], kF32, 2, "binary_fc x"), W = matrix(a[1], kU64, "binary_fc Wp");
   T alpha = tensor(a[2], kF32, "binary_fc alpha", true);
   const int64_t batch = x->size(0), fin = x->size(1), fout = W->size(0);
   const bool i32 = truth(a[3]);
@@ -266,14 +284,14 @@ FUNCTION(binary_fc, 7) {  // x, Wp, alpha, integer_out, out, workspace, stream
 }
 
 FUNCTION(binary_fc_static, 6) {  // x, Wp, alpha, integer_out, out, stream
-  T x = required(a[0], kF32, 2, "binary_fc_static x"), W = required(a[1], kU64, 2, "binary_fc_static Wp");
+  T x = required(a[0], kF32, 2, "binary_fc_static x"), W = matrix(a[1], kU64, "binary_fc_static Wp");
   T alpha = tensor(a[2], kF32, "binary_fc_static alpha", true);
   if (a[4] == Py_None) {
     PyErr_SetString(PyExc_ValueError, "binary_fc_static: pass the output tensor (the call allocates nothing)");
     throw python_error();
   }
   const bool i32 = truth(a[3]);
-  T out = required(a[4], i32 ? kI32 : kF32, 2, "binary_fc_static out");
+  T out = matrix(a[4], i32 ? kI32 : kF32, "binary_fc_static out");
   check_status(bmx_binary_fc_static(ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha), as_int(x->size(0)),
                                     as_int(x->size(1)), as_int(W->size(0)), i32 ? ptr<int32_t>(out) : nullptr,
                                     i32 ? nullptr : ptr<float>(out), ld(out), stream_of(a[5])),
@@ -283,7 +301,7 @@ FUNCTION(binary_fc_static, 6) {  // x, Wp, alpha, integer_out, out, stream
 }
 
 FUNCTION(binary_fc_packed, 8) {  // xp, in_features, Wp, alpha, mode ("f32", "i32", "bits"), out, thr, stream
-  T x = required(a[0], kU64, 2, "binary_fc_packed xp"), W = required(a[2], kU64, 2, "binary_fc_packed Wp");
+  T x = matrix(a[0], kU64, "binary_fc_packed xp"), W = matrix(a[2], kU64, "binary_fc_packed Wp");
   T alpha = tensor(a[3], kF32, "binary_fc_packed alpha", true), thr = tensor(a[6], kF32, "binary_fc_packed thr", true);
   const char* mode = PyUnicode_AsUTF8(a[4]);
   if (!mode) throw python_error();
@@ -351,7 +369,7 @@ FUNCTION(pack_nchw, 4) {  // x, pad, out, stream
 }
 
 FUNCTION(binary_conv2d_packed, 12) {  // xp, C, Wp, O, KH, KW, stride, pad, alpha, integer_out, out, stream
-  T x = required(a[0], kU64, 4, "binary_conv2d_packed xp", true), W = tensor(a[2], kU64, "binary_conv2d_packed Wp", true);
+  T x = packed_image(a[0], "binary_conv2d_packed xp"), W = tensor(a[2], kU64, "binary_conv2d_packed Wp", true);
   T alpha = tensor(a[8], kF32, "binary_conv2d_packed alpha", true);
   const int C = small(a[1]), O = small(a[3]), KH = small(a[4]), KW = small(a[5]), stride = small(a[6]), pad = small(a[7]);
   const int64_t N = x->size(0), H = x->size(1) - 2 * (int64_t)pad, Wd = x->size(2) - 2 * (int64_t)pad;
@@ -367,7 +385,7 @@ FUNCTION(binary_conv2d_packed, 12) {  // xp, C, Wp, O, KH, KW, stride, pad, alph
 
 // xp, C, Wp, O, KH, KW, stride, pad, alpha, thr, out_pad, out, workspace, stream
 FUNCTION(binary_conv2d_bits, 14) {
-  T x = required(a[0], kU64, 4, "binary_conv2d_bits xp", true), W = tensor(a[2], kU64, "binary_conv2d_bits Wp", true);
+  T x = packed_image(a[0], "binary_conv2d_bits xp"), W = tensor(a[2], kU64, "binary_conv2d_bits Wp", true);
   T alpha = tensor(a[8], kF32, "binary_conv2d_bits alpha", true), thr = tensor(a[9], kF32, "binary_conv2d_bits thr", true);
   const int C = small(a[1]), O = small(a[3]), KH = small(a[4]), KW = small(a[5]), stride = small(a[6]), pad = small(a[7]);
   const int opad = small(a[10]);
@@ -389,7 +407,7 @@ FUNCTION(binary_conv2d_bits, 14) {
 
 // a, w, bits_a, bits_w, want_int, want_float, out_int, out_float, workspace, stream -> (int, float)
 FUNCTION(quant_gemm, 10) {
-  T x = required(a[0], kF32, 2, "quant_gemm a"), w = required(a[1], kF32, 2, "quant_gemm w");
+  T x = required(a[0], kF32, 2, "quant_gemm a"), w = matrix(a[1], kF32, "quant_gemm w");
   const int64_t M = x->size(0), K = x->size(1), N = w->size(0);
   const int bits_a = small(a[2]), bits_w = small(a[3]);
   std::optional<Out> S, F;

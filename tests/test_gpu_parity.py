@@ -1341,3 +1341,53 @@ def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
     assert "conv_one_kernel" in B.last_kernel() and "%d parts of K" % parts in B.last_kernel(), B.last_kernel()
     np.testing.assert_array_equal(run_conv(x, w, s, p, alpha=alpha), rf)
     np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))
+
+
+# ------------------------------------------------------------------ matrices given with more dimensions
+@pytest.mark.parametrize("N", [1, 5])
+def test_contiguous_tensors_of_more_dimensions_are_rows(N):
+    rng = np.random.default_rng(N)
+    H, W, C, F = 3, 4, 128, 24
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = rng.standard_normal((F, H * W * C)).astype(np.float32)
+    img, Wp = B.pack_nchw(dev(x), 0), B.binarize_pack(dev(w), 1)
+    flat = img.view(N, -1)
+    want = B.binary_fc_packed(flat, H * W * C, Wp, mode="i32")
+    rows = oracle.binarize_pack(np.ascontiguousarray(np.transpose(x, (0, 2, 3, 1)).reshape(N, -1)), 1)
+    np.testing.assert_array_equal(host_u64(flat), rows)
+    np.testing.assert_array_equal(want.cpu().numpy(), oracle.xnor_gemm(rows, host_u64(Wp), H * W * C))
+    assert img.dim() == 4
+    assert torch.equal(B.binary_fc_packed(img, H * W * C, Wp, mode="i32"), want)
+    assert torch.equal(B.binary_fc_packed(img, H * W * C, Wp.view(F, H, -1), mode="f32"), want.float())
+    bits = torch.empty((N, 1, 1), dtype=torch.int64, device="cuda")
+    assert torch.equal(B.binary_fc_packed(img, H * W * C, Wp, mode="bits", out=bits).view(N, 1),
+                       B.binary_fc_packed(flat, H * W * C, Wp, mode="bits"))
+    out = torch.empty((N, 4, 6), dtype=torch.int32, device="cuda")
+    assert B.xnor_gemm(img, Wp, H * W * C, out=out) is out and torch.equal(out.view(N, F), want)
+    dense = dev(rng.standard_normal((N, 300)).astype(np.float32))
+    wd = B.binarize_pack(dev(rng.standard_normal((F, 300)).astype(np.float32)), 1)
+    fout = torch.empty((N, 2, 12), dtype=torch.float32, device="cuda")
+    assert torch.equal(B.binary_fc(dense, wd, out=fout).view(N, F), B.binary_fc(dense, wd))
+    as32 = img.view(torch.int32)
+    out.zero_()
+    assert torch.equal(B.xnor_gemm_w32(as32, Wp.view(torch.int32).view(F, H, -1), H * W * C, out=out).view(N, F), want)
+    assert torch.equal(B.unpack_pm1(img, H * W * C), B.unpack_pm1(flat, H * W * C))
+
+
+def test_rows_of_one_word_as_a_vector_and_what_stays_refused():
+    rng = np.random.default_rng(3)
+    A, W = (B.binarize_pack(dev(rng.standard_normal((n, 50)).astype(np.float32)), 1) for n in (9, 7))
+    want = B.xnor_gemm(A, W, 50)
+    assert torch.equal(B.xnor_gemm(A.view(9), W.view(7), 50), want)
+    with pytest.raises(ValueError):
+        B.xnor_gemm(A.view(3, 3, 1).transpose(0, 1), W, 50)      # more dimensions, not contiguous
+    with pytest.raises(ValueError):
+        B.xnor_gemm(A[0, 0], W, 50)                              # no rows at all
+    with pytest.raises(ValueError):
+        B.binary_fc(torch.zeros((2, 5, 10), device="cuda"), W)   # fp32 rows have two dimensions
+    img = B.pack_nchw(dev(rng.standard_normal((2, 40, 6, 6)).astype(np.float32)), 1)
+    Wp = B.pack_conv_weights(dev(rng.standard_normal((5, 40, 3, 3)).astype(np.float32)))
+    assert torch.equal(B.binary_conv2d_packed(img.view(2, 8, 8), 40, Wp, 5, 3, 3, 1, 1),
+                       B.binary_conv2d_packed(img, 40, Wp, 5, 3, 3, 1, 1))
+    with pytest.raises(B.BmxError):
+        B.xnor_gemm(A.view(9), W, 65)                            # a row of one word holds 64 values

@@ -10,6 +10,8 @@
 #include <tuple>
 #include <type_traits>
 
+#include "lds_limit.h"
+
 namespace bmx {
 
 __host__ __device__ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

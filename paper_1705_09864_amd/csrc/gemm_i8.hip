@@ -422,16 +422,9 @@ template <int TM, int TN, bool SUMS>
 hipError_t launch_i8(const I8Params& p, hipStream_t s) {
   auto kern = gemm_i8_kernel<TM, TN, SUMS>;
   const size_t lds = p.S > 1 ? (size_t)p.S * (TM * TN * 4 * 1024 + 128 * (TM + TN)) : 0;
-  if (lds > 64 * 1024) {  // more than the default limit of dynamic LDS: raised once per device
-    static bool raised[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!raised[dev]) {
-      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      raised[dev] = true;
-    }
-  }
+  static std::atomic<bool> asked[64];
+  const hipError_t e = allow_lds((const void*)kern, lds, asked);
+  if (e != hipSuccess) return e;
   note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
   hipLaunchKernelGGL(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
   return hipGetLastError();

@@ -3,6 +3,7 @@ symbol the header declares, and rejects bad arguments before any launch."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -279,3 +280,51 @@ class _FakeCuda:
 
     def __getattr__(self, name):
         return getattr(self._t, name)
+
+
+def test_lds_limit_is_asked_for_without_a_race(tmp_path):
+    """csrc/lds_limit.h by eight threads under the thread sanitizer, the runtime's two calls played by the test: no
+    data race, the attribute set for the device that is current, an error handed on and asked for again."""
+    csrc = os.path.join(ROOT, "paper_1705_09864_amd", "csrc")
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text("""#pragma once
+#include <stddef.h>
+enum hipError_t { hipSuccess = 0, hipErrorInvalidDevice = 101 };
+enum hipFuncAttribute { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
+hipError_t hipGetDevice(int* dev);
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute a, int value);
+""")
+    (tmp_path / "main.cpp").write_text("""#include "lds_limit.h"
+#include <thread>
+#include <vector>
+static thread_local int device = 0;
+static std::atomic<int> calls[65], fail{0};
+hipError_t hipGetDevice(int* dev) { *dev = device; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int value) {
+  ++calls[device];
+  return fail || value != 160 * 1024 ? hipErrorInvalidDevice : hipSuccess;
+}
+int main() {
+  static std::atomic<bool> asked[64];
+  if (bmx::allow_lds(nullptr, 64 * 1024, asked) != hipSuccess || calls[0]) return 1;
+  fail = 1;
+  if (bmx::allow_lds(nullptr, 70000, asked) == hipSuccess || calls[0] != 1) return 2;
+  fail = 0;
+  std::vector<std::thread> threads;
+  std::atomic<int> bad{0};
+  for (int i = 0; i < 8; ++i)
+    threads.emplace_back([&, i] {
+      device = i % 2;
+      for (int k = 0; k < 1000; ++k) bad += bmx::allow_lds(nullptr, 70000, asked) != hipSuccess;
+    });
+  for (auto& t : threads) t.join();
+  device = 64;
+  if (bmx::allow_lds(nullptr, 70000, asked) == hipSuccess) return 3;
+  return bad || calls[0] < 2 || calls[0] > 5 || calls[1] < 1 || calls[1] > 4 ? 4 : 0;
+}
+""")
+    exe = str(tmp_path / "race")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=thread", "-I", str(tmp_path), "-I", csrc,
+                    str(tmp_path / "main.cpp"), "-o", exe, "-lpthread"], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])

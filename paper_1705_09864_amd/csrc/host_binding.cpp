@@ -119,6 +119,29 @@ int as_int(int64_t v) {
   return (int)v;
 }
 
+// Python's lock is given back while this thread allocates or calls the library: either may wait for the GPU
+// (room in a queue, the allocator's hipMalloc), and what the GPU waits for may need the lock (a host callback on the
+// stream), as may every other Python thread.
+class Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+
+ public:
+  Unlocked() = default;
+  ~Unlocked() { PyEval_RestoreThread(state); }
+  Unlocked(const Unlocked&) = delete;
+};
+
+// A call of the library without Python's lock; its arguments are read with it.
+template <class F, class... A>
+void call(const char* what, F f, A... args) {
+  int status;
+  {
+    const Unlocked unlocked;
+    status = f(args...);
+  }
+  check_status(status, what);
+}
+
 hipStream_t stream_of(PyObject* o) {
   if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
   PyObject* h = PyObject_GetAttr(o, str_cuda_stream);
@@ -136,6 +159,7 @@ struct Out {
   PyObject* given = nullptr;
   Out(PyObject* o, at::ScalarType type, at::IntArrayRef shape, T like, const char* what, bool dense = false) {
     if (o == Py_None) {
+      const Unlocked unlocked;
       made = at::Tensor(at::detail::empty_cuda(shape, type, like->device(), std::nullopt));
       t = &made;
     } else {
@@ -150,13 +174,14 @@ struct Out {
   }
 };
 
-// The caller's workspace, or memory of the caching allocator held until the launches are enqueued
+// A workspace: the caller's, or memory of the caching allocator held until the launches are enqueued
 // (it goes back to the pool of the stream the kernels run on, which orders its next use).
 struct Workspace {
   void* p = nullptr;
   size_t bytes = 0;
   bool mine = false;
   Workspace() = default;
+  Workspace(const Workspace&) = delete;
   bool given(PyObject* o) {
     if (o == Py_None) return false;
     if (!THPVariable_Check(o) || !THPVariable_Unpack(o).is_cuda() || !THPVariable_Unpack(o).is_contiguous()) {
@@ -178,17 +203,21 @@ struct Workspace {
   ~Workspace() {
     if (mine) c10::hip::HIPCachingAllocator::raw_delete(p);
   }
-  Workspace(const Workspace&) = delete;
 };
 
-// A call whose workspace is allocated only if it asks for one.
-template <class Call>
-int lazily(Workspace& ws, PyObject* given, int op, std::initializer_list<int64_t> dims, T like, hipStream_t s, Call call) {
-  if (ws.given(given)) return call();
-  const int status = call();
-  if (status != BMX_ERR_WORKSPACE) return status;
-  ws.allocate(op, dims, like, s);
-  return call();
+// A call f(args..., workspace, its bytes, stream) whose workspace is allocated only if it asks for one.
+template <class F, class... A>
+void lazily(const char* what, PyObject* given, int op, std::initializer_list<int64_t> dims, T like, hipStream_t s, F f,
+            A... args) {
+  Workspace theirs;
+  const bool has = theirs.given(given);
+  call(what, [&] {
+    const int status = f(args..., theirs.p, theirs.bytes, s);
+    if (has || status != BMX_ERR_WORKSPACE) return status;
+    Workspace ws;
+    ws.allocate(op, dims, like, s);
+    return f(args..., ws.p, ws.bytes, s);
+  });
 }
 
 using Args = PyObject* const*;
@@ -213,8 +242,8 @@ FUNCTION(binarize_pack, 4) {  // x, pack_dim, out, stream
   const int64_t rows = x->size(0), cols = x->size(1);
   const int dim = small(a[1]);
   Out out(a[2], kU64, {dim ? rows : cols, words(dim ? cols : rows)}, x, "binarize_pack out");
-  check_status(bmx_binarize_pack(ptr<float>(x), rows, cols, ld(x), dim, ptr<uint64_t>(out.t), ld(out.t), stream_of(a[3])),
-               "bmx_binarize_pack");
+  const hipStream_t s = stream_of(a[3]);
+  call("bmx_binarize_pack", bmx_binarize_pack, ptr<float>(x), rows, cols, ld(x), dim, ptr<uint64_t>(out.t), ld(out.t), s);
   return out.result();
 }
 
@@ -222,8 +251,8 @@ FUNCTION(unpack_pm1, 4) {  // bits, K, out, stream
   T bits = matrix(a[0], kU64, "unpack_pm1 bits");
   const int64_t rows = bits->size(0), K = integer(a[1]);
   Out out(a[2], kF32, {rows, std::max<int64_t>(K, 0)}, bits, "unpack_pm1 out");
-  check_status(bmx_unpack_pm1(ptr<uint64_t>(bits), rows, K, ld(bits), ptr<float>(out.t), ld(out.t), stream_of(a[3])),
-               "bmx_unpack_pm1");
+  const hipStream_t s = stream_of(a[3]);
+  call("bmx_unpack_pm1", bmx_unpack_pm1, ptr<uint64_t>(bits), rows, K, ld(bits), ptr<float>(out.t), ld(out.t), s);
   return out.result();
 }
 
@@ -233,9 +262,10 @@ FUNCTION(xnor_gemm, 6) {  // A, B, K, out, stream, count
   Out out(a[3], kI32, {M, N}, A, "xnor_gemm out");
   const bool count = truth(a[5]);
   auto f = count ? bmx_xnor_gemm_count : bmx_xnor_gemm;
-  check_status(f(ptr<uint64_t>(A), ld(A), ptr<uint64_t>(B), ld(B), ptr<int32_t>(out.t), ld(out.t), as_int(M), as_int(N),
-                 small(a[2]), stream_of(a[4])),
-               count ? "bmx_xnor_gemm_count" : "bmx_xnor_gemm");
+  const int K = small(a[2]);
+  const hipStream_t s = stream_of(a[4]);
+  call(count ? "bmx_xnor_gemm_count" : "bmx_xnor_gemm", f, ptr<uint64_t>(A), ld(A), ptr<uint64_t>(B), ld(B),
+       ptr<int32_t>(out.t), ld(out.t), as_int(M), as_int(N), K, s);
   return out.result();
 }
 
@@ -243,8 +273,8 @@ FUNCTION(widen_words32, 4) {  // rows32, K, out, stream
   T in = matrix(a[0], kI32, "widen_words32 rows32");
   const int64_t rows = in->size(0), K = integer(a[1]);
   Out out(a[2], kU64, {rows, std::max<int64_t>(words(K), 0)}, in, "widen_words32 out");
-  check_status(bmx_widen_words32(ptr<uint32_t>(in), rows, K, ld(in), ptr<uint64_t>(out.t), ld(out.t), stream_of(a[3])),
-               "bmx_widen_words32");
+  const hipStream_t s = stream_of(a[3]);
+  call("bmx_widen_words32", bmx_widen_words32, ptr<uint32_t>(in), rows, K, ld(in), ptr<uint64_t>(out.t), ld(out.t), s);
   return out.result();
 }
 
@@ -254,13 +284,8 @@ FUNCTION(xnor_gemm_w32, 6) {  // A32, B32, K, out, workspace, stream
   const int K = small(a[2]);
   Out out(a[3], kI32, {M, N}, A, "xnor_gemm_w32 out");
   const hipStream_t s = stream_of(a[5]);
-  Workspace ws;
-  check_status(lazily(ws, a[4], BMX_OP_XNOR_GEMM_W32, {M, N, K}, A, s,
-                      [&] {
-                        return bmx_lazy_xnor_gemm_w32(ptr<uint32_t>(A), ld(A), ptr<uint32_t>(B), ld(B), ptr<int32_t>(out.t),
-                                                      ld(out.t), as_int(M), as_int(N), K, ws.p, ws.bytes, s);
-                      }),
-               "bmx_xnor_gemm_w32");
+  lazily("bmx_xnor_gemm_w32", a[4], BMX_OP_XNOR_GEMM_W32, {M, N, K}, A, s, bmx_lazy_xnor_gemm_w32, ptr<uint32_t>(A),
+         ld(A), ptr<uint32_t>(B), ld(B), ptr<int32_t>(out.t), ld(out.t), as_int(M), as_int(N), K);
   return out.result();
 }
 
@@ -271,15 +296,9 @@ FUNCTION(binary_fc, 7) {  // x, Wp, alpha, integer_out, out, workspace, stream
   const bool i32 = truth(a[3]);
   Out out(a[4], i32 ? kI32 : kF32, {batch, fout}, x, "binary_fc out");
   const hipStream_t s = stream_of(a[6]);
-  Workspace ws;
-  check_status(lazily(ws, a[5], BMX_OP_BINARY_FC, {batch, fin, fout}, x, s,
-                      [&] {
-                        return bmx_lazy_binary_fc(ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha),
-                                                  as_int(batch), as_int(fin), as_int(fout),
-                                                  i32 ? ptr<int32_t>(out.t) : nullptr, i32 ? nullptr : ptr<float>(out.t),
-                                                  ld(out.t), ws.p, ws.bytes, s);
-                      }),
-               "bmx_binary_fc");
+  lazily("bmx_binary_fc", a[5], BMX_OP_BINARY_FC, {batch, fin, fout}, x, s, bmx_lazy_binary_fc, ptr<float>(x), ld(x),
+         ptr<uint64_t>(W), ld(W), ptr<float>(alpha), as_int(batch), as_int(fin), as_int(fout),
+         i32 ? ptr<int32_t>(out.t) : nullptr, i32 ? nullptr : ptr<float>(out.t), ld(out.t));
   return out.result();
 }
 
@@ -292,10 +311,10 @@ FUNCTION(binary_fc_static, 6) {  // x, Wp, alpha, integer_out, out, stream
   }
   const bool i32 = truth(a[3]);
   T out = matrix(a[4], i32 ? kI32 : kF32, "binary_fc_static out");
-  check_status(bmx_binary_fc_static(ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha), as_int(x->size(0)),
-                                    as_int(x->size(1)), as_int(W->size(0)), i32 ? ptr<int32_t>(out) : nullptr,
-                                    i32 ? nullptr : ptr<float>(out), ld(out), stream_of(a[5])),
-               "bmx_binary_fc_static");
+  const hipStream_t s = stream_of(a[5]);
+  call("bmx_binary_fc_static", bmx_binary_fc_static, ptr<float>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha),
+       as_int(x->size(0)), as_int(x->size(1)), as_int(W->size(0)), i32 ? ptr<int32_t>(out) : nullptr,
+       i32 ? nullptr : ptr<float>(out), ld(out), s);
   Py_INCREF(a[4]);
   return a[4];
 }
@@ -312,11 +331,11 @@ FUNCTION(binary_fc_packed, 8) {  // xp, in_features, Wp, alpha, mode ("f32", "i3
   }
   const int64_t batch = x->size(0), fout = W->size(0);
   Out out(a[5], bits ? kU64 : i32 ? kI32 : kF32, {batch, bits ? words(fout) : fout}, x, "binary_fc_packed out");
-  check_status(bmx_binary_fc_packed(ptr<uint64_t>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha), as_int(batch),
-                                    small(a[1]), as_int(fout), i32 ? ptr<int32_t>(out.t) : nullptr,
-                                    !i32 && !bits ? ptr<float>(out.t) : nullptr, bits ? ptr<uint64_t>(out.t) : nullptr,
-                                    ptr<float>(thr), ld(out.t), stream_of(a[7])),
-               "bmx_binary_fc_packed");
+  const int K = small(a[1]);
+  const hipStream_t s = stream_of(a[7]);
+  call("bmx_binary_fc_packed", bmx_binary_fc_packed, ptr<uint64_t>(x), ld(x), ptr<uint64_t>(W), ld(W), ptr<float>(alpha),
+       as_int(batch), K, as_int(fout), i32 ? ptr<int32_t>(out.t) : nullptr, !i32 && !bits ? ptr<float>(out.t) : nullptr,
+       bits ? ptr<uint64_t>(out.t) : nullptr, ptr<float>(thr), ld(out.t), s);
   return out.result();
 }
 
@@ -326,8 +345,8 @@ FUNCTION(pack_conv_weights, 2) {  // w, stream
   const int64_t row = bmx_conv_weight_row_words(C, KH, KW);
   if (row <= 0) check_status(BMX_ERR_UNSUPPORTED, "bmx_conv_weight_row_words");
   Out out(Py_None, kU64, {O, row}, w, "");
-  check_status(bmx_pack_conv_weights(ptr<float>(w), O, C, KH, KW, ptr<uint64_t>(out.t), stream_of(a[1])),
-               "bmx_pack_conv_weights");
+  const hipStream_t s = stream_of(a[1]);
+  call("bmx_pack_conv_weights", bmx_pack_conv_weights, ptr<float>(w), O, C, KH, KW, ptr<uint64_t>(out.t), s);
   return out.result();
 }
 
@@ -344,15 +363,9 @@ FUNCTION(binary_conv2d, 12) {  // x, Wp, O, KH, KW, stride, pad, alpha, integer_
   Out out(a[9], i32 ? kI32 : kF32, {N, std::max(O, 0), conv_out(H, KH, stride, pad), conv_out(Wd, KW, stride, pad)}, x,
           "binary_conv2d out", true);
   const hipStream_t s = stream_of(a[11]);
-  Workspace ws;
-  check_status(lazily(ws, a[10], BMX_OP_BINARY_CONV2D, {N, C, H, Wd, O, KH, KW, stride, pad}, x, s,
-                      [&] {
-                        return bmx_lazy_binary_conv2d(ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd),
-                                                      ptr<uint64_t>(W), O, KH, KW, stride, pad, ptr<float>(alpha),
-                                                      i32 ? ptr<int32_t>(out.t) : nullptr,
-                                                      i32 ? nullptr : ptr<float>(out.t), ws.p, ws.bytes, s);
-                      }),
-               "bmx_binary_conv2d");
+  lazily("bmx_binary_conv2d", a[10], BMX_OP_BINARY_CONV2D, {N, C, H, Wd, O, KH, KW, stride, pad}, x, s,
+         bmx_lazy_binary_conv2d, ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd), ptr<uint64_t>(W), O, KH, KW,
+         stride, pad, ptr<float>(alpha), i32 ? ptr<int32_t>(out.t) : nullptr, i32 ? nullptr : ptr<float>(out.t));
   return out.result();
 }
 
@@ -362,9 +375,9 @@ FUNCTION(pack_nchw, 4) {  // x, pad, out, stream
   const int pad = small(a[1]);
   Out out(a[2], kU64, {N, std::max<int64_t>(H + 2 * pad, 0), std::max<int64_t>(Wd + 2 * pad, 0), words(C)}, x,
           "pack_nchw out", true);
-  check_status(bmx_pack_nchw(ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd), pad, ptr<uint64_t>(out.t),
-                             stream_of(a[3])),
-               "bmx_pack_nchw");
+  const hipStream_t s = stream_of(a[3]);
+  call("bmx_pack_nchw", bmx_pack_nchw, ptr<float>(x), as_int(N), as_int(C), as_int(H), as_int(Wd), pad,
+       ptr<uint64_t>(out.t), s);
   return out.result();
 }
 
@@ -376,10 +389,10 @@ FUNCTION(binary_conv2d_packed, 12) {  // xp, C, Wp, O, KH, KW, stride, pad, alph
   const bool i32 = truth(a[9]);
   Out out(a[10], i32 ? kI32 : kF32, {N, std::max(O, 0), conv_out(H, KH, stride, pad), conv_out(Wd, KW, stride, pad)}, x,
           "binary_conv2d_packed out", true);
-  check_status(bmx_binary_conv2d_packed(ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd), ptr<uint64_t>(W), O, KH, KW,
-                                        stride, pad, ptr<float>(alpha), i32 ? ptr<int32_t>(out.t) : nullptr,
-                                        i32 ? nullptr : ptr<float>(out.t), stream_of(a[11])),
-               "bmx_binary_conv2d_packed");
+  const hipStream_t s = stream_of(a[11]);
+  call("bmx_binary_conv2d_packed", bmx_binary_conv2d_packed, ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd),
+       ptr<uint64_t>(W), O, KH, KW, stride, pad, ptr<float>(alpha), i32 ? ptr<int32_t>(out.t) : nullptr,
+       i32 ? nullptr : ptr<float>(out.t), s);
   return out.result();
 }
 
@@ -394,14 +407,9 @@ FUNCTION(binary_conv2d_bits, 14) {
   Out out(a[11], kU64, {N, std::max<int64_t>(ho, 0), std::max<int64_t>(wo, 0), std::max<int64_t>(words(O), 0)}, x,
           "binary_conv2d_bits out", true);
   const hipStream_t s = stream_of(a[13]);
-  Workspace ws;
-  check_status(lazily(ws, a[12], BMX_OP_BINARY_CONV2D_BITS, {N, C, H, Wd, O, KH, KW, stride, pad, opad}, x, s,
-                      [&] {
-                        return bmx_lazy_binary_conv2d_bits(ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd),
-                                                           ptr<uint64_t>(W), O, KH, KW, stride, pad, ptr<float>(alpha),
-                                                           ptr<float>(thr), ptr<uint64_t>(out.t), opad, ws.p, ws.bytes, s);
-                      }),
-               "bmx_binary_conv2d_bits");
+  lazily("bmx_binary_conv2d_bits", a[12], BMX_OP_BINARY_CONV2D_BITS, {N, C, H, Wd, O, KH, KW, stride, pad, opad}, x, s,
+         bmx_lazy_binary_conv2d_bits, ptr<uint64_t>(x), as_int(N), C, as_int(H), as_int(Wd), ptr<uint64_t>(W), O, KH, KW,
+         stride, pad, ptr<float>(alpha), ptr<float>(thr), ptr<uint64_t>(out.t), opad);
   return out.result();
 }
 
@@ -420,14 +428,9 @@ FUNCTION(quant_gemm, 10) {
     throw python_error();
   }
   const hipStream_t s = stream_of(a[9]);
-  Workspace ws;
-  check_status(lazily(ws, a[8], BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, x, s,
-                      [&] {
-                        return bmx_lazy_quant_gemm(ptr<float>(x), ld(x), bits_a, ptr<float>(w), ld(w), bits_w, as_int(M),
-                                                   as_int(N), as_int(K), S ? ptr<int32_t>(S->t) : nullptr,
-                                                   F ? ptr<float>(F->t) : nullptr, ldo, ws.p, ws.bytes, s);
-                      }),
-               "bmx_quant_gemm");
+  lazily("bmx_quant_gemm", a[8], BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, x, s, bmx_lazy_quant_gemm, ptr<float>(x),
+         ld(x), bits_a, ptr<float>(w), ld(w), bits_w, as_int(M), as_int(N), as_int(K), S ? ptr<int32_t>(S->t) : nullptr,
+         F ? ptr<float>(F->t) : nullptr, ldo);
   PyObject* r = PyTuple_New(2);
   if (!r) throw python_error();
   for (int i = 0; i < 2; ++i) {
@@ -444,8 +447,8 @@ FUNCTION(alpha_mean_abs, 2) {  // w, stream
   if (!w || w->dim() < 1) raise_value("%s: expected a tensor of at least one dimension%s%s", "alpha_mean_abs w");
   const int64_t rows = w->size(0), cols = w->numel() / std::max<int64_t>(rows, 1);
   Out out(Py_None, kF32, {rows}, w, "");
-  check_status(bmx_alpha_mean_abs(ptr<float>(w), rows, cols, cols, ptr<float>(out.t), stream_of(a[1])),
-               "bmx_alpha_mean_abs");
+  const hipStream_t s = stream_of(a[1]);
+  call("bmx_alpha_mean_abs", bmx_alpha_mean_abs, ptr<float>(w), rows, cols, cols, ptr<float>(out.t), s);
   return out.result();
 }
 

@@ -1343,6 +1343,25 @@ def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
     np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))
 
 
+# ------------------------------------------------------------------ few bits: bytes or planes
+@pytest.mark.parametrize("M,N,K,bits_a,bytes_form", [
+    (16, 2048, 8192, 2, False), (32, 1900, 8192, 2, False), (16, 200, 16384, 1, False), (100, 32, 10000, 2, True),
+    (16, 900, 4096, 2, True), (475, 1088, 832, 2, True), (360, 4096, 832, 1, False), (130, 300, 4097, 1, True)])
+def test_few_bits_on_the_byte_form_or_the_plane_form(M, N, K, bits_a, bytes_form):
+    rng = np.random.default_rng(K + M)
+    a = rng.uniform(-0.2, 1.2, (M, K)).astype(np.float32)
+    w = rng.standard_normal((N, K)).astype(np.float32)
+    S, _ = B.quant_gemm(dev(a), dev(w), bits_a, 1, want_float=False)
+    assert ("gemm_i8_kernel" in B.last_kernel()) == bytes_form, B.last_kernel()
+    with tuned(k7=3):
+        P, _ = B.quant_gemm(dev(a), dev(w), bits_a, 1, want_float=False)
+        assert "gemm_i8_kernel" not in B.last_kernel() and "quant_small" not in B.last_kernel()
+    assert torch.equal(S, P)
+    q = np.floor((np.float32((1 << bits_a) - 1) * np.clip(a, 0, 1)).astype(np.float64) + 0.5)  # half away from zero
+    at = rng.integers(0, M, 8)
+    np.testing.assert_array_equal(S.cpu().numpy()[at], (q[at] @ np.where(w >= 0, 1.0, -1.0).T).astype(np.int32))
+
+
 # ------------------------------------------------------------------ matrices given with more dimensions
 @pytest.mark.parametrize("N", [1, 5])
 def test_contiguous_tensors_of_more_dimensions_are_rows(N):

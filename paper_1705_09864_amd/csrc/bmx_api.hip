@@ -50,11 +50,12 @@ inline int64_t even_words(int64_t words) { return (words + 1) / 2 * 2; }
 inline int64_t w32_row_words(int64_t K) { return even_words(bmx::words_for(K)); }
 
 struct QuantWs {
-  size_t planes_off, wb_off, rowsum_off, wrowsum_off, tmp_off, total;
+  size_t planes_off, wb_off, rowsum_off, wrowsum_off, tmp_off, planes_total, total;  // planes_total: of the plane kernels
 };
 
 // bits_w = 1: sign-packed weights [N][even Kw].  bits_w > 1: weight planes [N * bits_w][padded K]
-// like the activations', their (unused) row sums, and the int32 results per weight plane.
+// like the activations', their (unused) row sums, and the int32 results per weight plane.  k-bit weights that
+// the int8 form takes need its operands only (the plane kernels then run with the popcount engine pinned at most).
 QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
   const int64_t Kw = bmx::words_for(K);
   QuantWs q;
@@ -64,9 +65,12 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
                                                    : (size_t)bits_w * N * bmx::padded_words(K) * 8);
   q.wrowsum_off = q.rowsum_off + round256((size_t)M * 4);
   q.tmp_off = q.wrowsum_off + (bits_w == 1 ? 0 : round256((size_t)N * 4));
-  q.total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
-  size_t tiles = 0;  // the int8 form's operands, where it is taken
-  if (bmx::quant_i8_takes(M, N, K, bits_a, bits_w, &tiles) && round256(tiles) > q.total) q.total = round256(tiles);
+  q.total = q.planes_total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
+  size_t tiles = 0;
+  if (bmx::quant_i8_takes(M, N, K, bits_a, bits_w, &tiles)) {
+    tiles = round256(tiles);
+    if (tiles > q.total || (bits_w > 1 && bmx::gemm_engine != 1)) q.total = tiles;
+  }
   return q;
 }
 
@@ -608,6 +612,7 @@ static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, i
   // more bits than the FP4 form holds: bytes on the matrix cores
   if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, s, &direct))
     return hip_status(direct);
+  if (q.total < q.planes_total) return BMX_ERR_WORKSPACE;  // (an engine pinned meanwhile, by another thread)
   char* ws = (char*)workspace;
   uint64_t* planes = (uint64_t*)(ws + q.planes_off);
   uint64_t* wb = (uint64_t*)(ws + q.wb_off);

@@ -58,6 +58,14 @@ def test_workspace_query():
     assert B.workspace_bytes(B.OP_QUANT_GEMM, (4, 4, 64, 2, 9)) == 0      # bits_w out of range
     # k-bit weights: both operands as planes, row sums, one int32 result per weight plane
     assert B.workspace_bytes(B.OP_QUANT_GEMM, (4, 4, 64, 2, 2)) == 2 * 4 * 16 * 8 + 2 * 4 * 16 * 8 + 256 + 256 + 256
+    # ... of which the int8 form uses its two operands' bytes only (blocks of 32 rows, 256 values)
+    assert B.workspace_bytes(B.OP_QUANT_GEMM, (500, 1000, 2300, 4, 4)) == (512 + 1024) * 2304
+    B.lib().bmx_tune_set(7, 1)
+    try:
+        planes = 4 * (500 + 1000) * 48 * 8 + 2048 + 4096 + 500 * 1000 * 4 * 4
+        assert planes <= B.workspace_bytes(B.OP_QUANT_GEMM, (500, 1000, 2300, 4, 4)) <= planes + 5 * 256
+    finally:
+        B.lib().bmx_tune_set(0, 0)
     assert B.workspace_bytes(B.OP_BINARY_CONV2D, (1, 3, 8, 8, 2, 4, 4, 1, 0)) == 0  # even kernel
     # packed-bit convolution: nothing where the convolution kernel writes the bits itself (3 x 3
     # over at most 256 channels), else the fp32 result of the two-kernel route

@@ -539,11 +539,16 @@ quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda
       }
     }
     // Half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32 (with 0.5 itself the one value
-    // 0.5 - 2^-25 would round up): one addition where roundf takes seven instructions.
+    // 0.5 - 2^-25 would round up): one addition where roundf takes a truncation, a subtraction, a compare, a
+    // selection, a sign and an addition.  us a call with roundf and now, 2 x 1 bits: 1024 x 1024 x 4096 14.0 / 13.9,
+    // 2048 x 2048 x 2048 17.5 / 17.3, 4096 x 256 x 4096 20.4 / 19.5.
+    // Product and sum are two roundings: fused, seven floats at 5 and 7 bits land on the level below.
     int q[kSegWords];
 #pragma unroll
     for (int j = 0; j < kSegWords; ++j) {
-      q[j] = (int)__fadd_rn(__fmul_rn(L, fminf(fmaxf(v[j], 0.0f), 1.0f)), 0.49999997f);
+#pragma clang fp contract(off)
+      const float u = L * fminf(fmaxf(v[j], 0.0f), 1.0f);
+      q[j] = (int)(u + 0x1.fffffep-2f);
       sum += q[j];
     }
     for (int p = 0; p < bits; ++p) {

@@ -1343,6 +1343,33 @@ def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
     np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))
 
 
+# ------------------------------------------------------------------ ties of the quantiser
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("rows,engine", [(300, {}), (300, {"k7": 3}), (40, {"k7": 1}), (5, {})])
+def test_quantiser_ties_on_every_form(bits, rows, engine):
+    """Values around every tie of Eq. 1: the level is that of the fp32 product L * x, rounded half away from zero, and
+    not of the exact product (at 5 and 7 bits they differ for some floats).  One launch, bytes and planes; the planes'
+    own choice below 256 results."""
+    L = np.float32((1 << bits) - 1)
+    x = ((np.arange(1 << bits) + 0.5) / float(L)).astype(np.float32)
+    at = [x]
+    for way in (np.float32(0), np.float32(2)):
+        v = x
+        for _ in range(3):
+            v = np.nextafter(v, way)
+            at.append(v)
+    x = np.concatenate(at)
+    x = np.resize(x[x <= 1], max(2048, x.size))
+    a = np.stack([np.roll(x, 7 * r) for r in range(rows)])
+    w = np.random.default_rng(bits).choice(np.float32([-1, 1]), (40, x.size)) if rows > 5 else np.eye(40, x.size, dtype=np.float32) * 2 - 1
+    for bw in (1, bits):
+        wb = w if bw == 1 else np.stack([np.roll(2 * x - 1, 11 * r) for r in range(40)])
+        rS, _, _ = oracle.quant_gemm(a, wb, bits, bw)
+        with tuned(**engine):
+            S, _ = B.quant_gemm(dev(a), dev(wb), bits, bw, want_float=False)
+        np.testing.assert_array_equal(S.cpu().numpy(), rS, err_msg=B.last_kernel())
+
+
 # ------------------------------------------------------------------ few bits: bytes or planes
 @pytest.mark.parametrize("M,N,K,bits_a,bytes_form", [
     (16, 2048, 8192, 2, False), (32, 1900, 8192, 2, False), (16, 200, 16384, 1, False), (100, 32, 10000, 2, True),

@@ -70,7 +70,7 @@ fc_small_kernel(const FcSmallParams p) {
   const int l = lane & (L - 1), grp = lane / L;
   const int nchunks = p.Kpad / (W * L);
   const int n_end = min(n0 + p.cols, p.N);
-  // passes of this wave: features n0 + (wave + 8 i) * kPass ...
+  // passes of this wave: features n0 + (wave + kWaves * i) * kPass ...
   const int npass = (n_end - n0 > wave * kPass) ? (n_end - n0 - wave * kPass + kWaves * kPass - 1) / (kWaves * kPass) : 0;
   // which of the group's counts this lane stores: value v = m * U + u
   int v_mine;
@@ -114,18 +114,28 @@ fc_small_kernel(const FcSmallParams p) {
     uint32_t v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) v[j] = __builtin_amdgcn_raw_buffer_load_b32(row, off + 256u * j, 0, 0);
-    const int left = p.K - c * 1024;
     uint32_t lo = 0, hi = 0;  // lane j: word j of the run
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      uint64_t b = __ballot(__uint_as_float(v[j]) >= 0.0f);
-      if (left < 64 * j + 64) b &= left > 64 * j ? (1ull << (left - 64 * j)) - 1 : 0ull;  // (scalar)
-      // (the wait states between the compare that writes b and its readers are part of the statement: the
+    for (int j = 0; j < 16; j += 4) {
+      uint64_t b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = __ballot(__uint_as_float(v[j + i]) >= 0.0f);
+      // (the wait states between the compares that write b and their readers are part of the statement: the
       // compiler, which puts them between its own instructions, does not look into one)
-      asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
-          : "+v"(lo), "+v"(hi) : "s"((uint32_t)b), "s"((uint32_t)(b >> 32)), "i"(j));
+      asm("s_nop 1\n\t"
+          "v_writelane_b32 %0, %2, %10\n\tv_writelane_b32 %1, %3, %10\n\t"
+          "v_writelane_b32 %0, %4, %10 + 1\n\tv_writelane_b32 %1, %5, %10 + 1\n\t"
+          "v_writelane_b32 %0, %6, %10 + 2\n\tv_writelane_b32 %1, %7, %10 + 2\n\t"
+          "v_writelane_b32 %0, %8, %10 + 3\n\tv_writelane_b32 %1, %9, %10 + 3"
+          : "+v"(lo), "+v"(hi)
+          : "s"((uint32_t)b[0]), "s"((uint32_t)(b[0] >> 32)), "s"((uint32_t)b[1]), "s"((uint32_t)(b[1] >> 32)),
+            "s"((uint32_t)b[2]), "s"((uint32_t)(b[2] >> 32)), "s"((uint32_t)b[3]), "s"((uint32_t)(b[3] >> 32)), "i"(j));
     }
-    if (lane < 16 && 16 * c + lane < p.Kpad) bits[m * p.Kpad + 16 * c + lane] = (uint64_t)hi << 32 | lo;
+    // Values past K, a word on its lane: 100 x 2100 -> 1000 takes 4.76 us a call so; with a branch per word around a
+    // scalar mask, and so the wait once per word, 5.07.
+    const int real = min(max(p.K - c * 1024 - 64 * lane, 0), 64);
+    const uint64_t word = ((uint64_t)hi << 32 | lo) & (real < 64 ? (1ull << real) - 1 : ~0ull);
+    if (lane < 16 && 16 * c + lane < p.Kpad) bits[m * p.Kpad + 16 * c + lane] = word;
     c += kWaves;
     while (c >= cpr) c -= cpr, ++m;
   }

@@ -29,6 +29,8 @@ paper's own method (xnor + popcount on 64-bit words, OpenMP) beside it.
 
 `--phase NAME` runs one section only (headline, config1, config2, config4, config5, sec31, biggemm,
 packs, probe): the workload of the per-configuration rocprofv3 summaries under profiles/.
+`--phase cases` (never part of the default run) times the listed cases of perf/cases.py as a program calls
+them, one call after the other with the host's share in, on buffers that are reused.
 """
 import argparse
 import ctypes
@@ -53,7 +55,7 @@ MALL_BYTES = 256 << 20  # memory-side cache
 # what a rotation over buffer sets has to cover: with 1.1 times the cache a cyclic walk still finds
 # much of its data there (the fc1 GEMM: 8.5 us at 285 MB, 9.3 at 590 MB, 9.5 at 1.2 GB)
 ROTATE_BYTES = 4 * MALL_BYTES
-PHASES = ("headline", "fc1", "fc2", "config1", "config2", "config4", "config5", "sec31", "packs", "biggemm", "probe")
+PHASES = ("headline", "fc1", "fc2", "config1", "config2", "config4", "config5", "sec31", "packs", "biggemm", "probe", "cases")
 
 
 def roofline_block(kernel, us, binops=0.0, nbytes=0.0, mfma_flops=None):
@@ -628,6 +630,27 @@ def main():
             other["paper_sec3_1_conv5x5_cin256_filters%d_call" % cout] = conv_call(256, cout, 5)
         for k in (1, 3, 7):
             other["paper_sec3_1_conv%dx%d_cin256_call" % (k, k)] = conv_call(256, 64, k)
+
+    if args.phase == "cases":
+        from perf import cases
+        for i, case in enumerate(cases.listed()):
+            state = cases.prepare(case, i)
+            passes = 0
+            t0 = time.perf_counter()
+            while passes < 20 or (time.perf_counter() - t0 < 0.05 and passes < 20000):
+                cases.run(state)
+                passes += 1
+            torch.cuda.synchronize()
+            rounds = []
+            for _ in range(7):
+                t0 = time.perf_counter()
+                for _ in range(passes):
+                    cases.run(state)
+                torch.cuda.synchronize()
+                rounds.append((time.perf_counter() - t0) / passes * 1e6)
+            other["case_" + case["name"]] = {"call_us": sorted(rounds)[3], "passes": passes, "last_kernel": B.last_kernel()}
+            del state
+            torch.cuda.empty_cache()
 
     # ------------------------------------------------------------------ CPU oracle beside it
     if not args.no_cpu_baseline and args.phase == "all":

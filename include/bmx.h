@@ -244,8 +244,8 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
  * (Eq. 1 is defined on [0, 1]; the affine pair is DoReFa-Net's).  Then
  *   S[m][n] = sum_k q[m][k] * (2 * q_w[n][k] - L_w),
  *   out_f32 = (float)S / (float)((2^bits_a - 1) * L_w),
- * computed as the bits_w = 1 form against every weight plane, the planes added up by powers
- * of two.  K * (2^bits_a - 1) * (2^bits_w - 1) must stay below 2^31.
+ * computed on bytes by the int8 matrix cores (below 256 results as the bits_w = 1 form against
+ * every weight plane, the planes added up by powers of two).  K * (2^bits_a - 1) * (2^bits_w - 1) must stay below 2^31.
  *   a fp32 [M, lda], w fp32 [N, ldw]; out_i32_scaled (S) and out_f32 are [M, ldo]; either
  *   may be NULL, not both.  bits_a, bits_w in 1..8.
  *   workspace >= bmx_workspace_bytes(BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, 5). */
@@ -289,7 +289,7 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *   key 14 = 1: the short-K matrix-core convolution kernel fetches pixel words 8 bytes at a time
  *          even where 16 would do; 2: 16 at a time, but never in the form for channel-word
  *          counts that are multiples of four; 3: never in the form that holds one block per wave
- *   key 15 = 1: bmx_binary_fc never takes its one-launch form for very small layers
+ *   key 15 = 1: bmx_binary_fc never takes its one-launch form
  *   key 16 = 1: bmx_binary_conv2d never takes its one-launch form
  *   key 18 = 1: convolutions of packed images never take the kernel for small problems (nor while
  *          one of keys 1, 5, 7 and 14 pins another)

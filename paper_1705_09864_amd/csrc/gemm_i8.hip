@@ -439,16 +439,18 @@ int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * c
 // fills a quarter of a 32 x 32 block (below that the padding of the tiles is most of what is moved, and the plane
 // kernels' workspace is smaller).
 // Few bits (1 or 2 by 1): the byte form writes its tiles and reads them again and multiplies a byte a value, and both
-// grow with K beside; the plane form's pack gives a row to four waves, 4096 values a round, and an unfinished round
-// costs as much as a full one.  The line below fits 456 products on both forms (chosen form over the better one: 0.8 % on
-// average; counting multiply-adds alone 3.1 %).  us a call, bytes / planes, at 2 x 1 bits: 16 x 2048 x 8192 20.6 / 18.2,
+// grow with K beside; the plane form's pack gives a row to four waves in segments of 1024 values, so a round of
+// 4096 that is not full costs as much as a full one, and a segment that is not full 1.5 to 2 us more (each of its loads
+// is tested).  The line below fits 456 products on both forms (chosen form over the better one: 0.5 % on average;
+// counting multiply-adds alone 3.1 %).  us a call, bytes / planes, at 2 x 1 bits: 16 x 2048 x 8192 20.6 / 18.2,
 // 32 x 1900 x 8192 20.1 / 18.0, 16 x 900 x 8192 13.8 / 11.6, 16 x 200 x 16384 16.2 / 13.7, 1024 x 32 x 16384 25.3 / 22.3, 475 x 1088 x
-// 832 8.3 / 11.8, 700 x 900 x 1600 13.9 / 14.7, 360 x 4096 x 832 16.0 / 12.8, 1024 x 1024 x 4096 18.1 / 13.9, 100 x 32 x 10000
-// 12.1 / 14.4; 64 x 907 x 256 is in one launch, 4.8.
+// 832 8.3 / 11.8, 700 x 900 x 1600 13.9 / 14.7, 360 x 4096 x 832 16.0 / 12.8, 1024 x 1024 x 4096 18.1 / 13.9, 100 x 900 x 10000
+// 18.0 / 19.5; 64 x 907 x 256 is in one launch, 4.8.
 static bool bytes_pay(int64_t M, int64_t N, int64_t K) {
   if (M * N >= 1000000000 || M * N * K >= 1000000000) return false;
-  const int64_t unfinished = ceil_div(K, 4096) * 4096 - K;
-  return tile_bytes(M, K) + tile_bytes(N, K) + M * N * K / 100 + 1600 * K - 3000 * unfinished < 17000000;
+  const int64_t bytes = tile_bytes(M, K) + tile_bytes(N, K) + M * N * K * 6 / 1000 + 800 * K;
+  const int64_t planes = 2000 * (ceil_div(K, 4096) * 4096 - K) + (K % 1024 ? 10000000 : 0);
+  return bytes < planes + 10000000;
 }
 
 bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes) {

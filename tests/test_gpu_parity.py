@@ -1373,7 +1373,8 @@ def test_quantiser_ties_on_every_form(bits, rows, engine):
 # ------------------------------------------------------------------ few bits: bytes or planes
 @pytest.mark.parametrize("M,N,K,bits_a,bytes_form", [
     (16, 2048, 8192, 2, False), (32, 1900, 8192, 2, False), (16, 200, 16384, 1, False), (100, 32, 10000, 2, True),
-    (16, 900, 4096, 2, True), (475, 1088, 832, 2, True), (360, 4096, 832, 1, False), (130, 300, 4097, 1, True)])
+    (16, 900, 4096, 2, True), (475, 1088, 832, 2, True), (360, 4096, 832, 1, False), (130, 300, 4097, 1, True),
+    (100, 900, 10000, 2, True), (100, 900, 8192, 2, False)])
 def test_few_bits_on_the_byte_form_or_the_plane_form(M, N, K, bits_a, bytes_form):
     rng = np.random.default_rng(K + M)
     a = rng.uniform(-0.2, 1.2, (M, K)).astype(np.float32)

@@ -121,7 +121,7 @@ int as_int(int64_t v) {
 
 // Python's lock is given back while this thread allocates or calls the library: either may wait for the GPU
 // (room in a queue, the allocator's hipMalloc), and what the GPU waits for may need the lock (a host callback on the
-// stream), as may every other Python thread.
+// stream), as may every other Python thread.  0.04 us each time (a call that launches nothing 0.18 -> 0.22 us).
 class Unlocked {
   PyThreadState* const state = PyEval_SaveThread();
 

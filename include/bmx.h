@@ -295,6 +295,9 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *          one of keys 1, 5, 7 and 14 pins another)
  *   key 17 = 1: xnor products never take the kernel for small problems (nor while any of keys 7 to
  *          13 pins one of the others)
+ *   key 19 = 1: xnor products never take the kernel that stages operand rows once per workgroup (nor while
+ *          any of keys 7 and 10 to 13 pins one of the others); 2, 3: that kernel with 256 x 128 (rows
+ *          16-byte aligned) or 128 x 128 of C per workgroup, whatever the size (int32 or fp32 results)
  *   key 8  K-split waves, key 9  tile variant (1: 32 x 32, 2: 64 x 64 per wave) of the matrix-core
  *          kernels */
 int bmx_tune_set(int key, int value);

@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbmx.so")
-SOURCES = ["bmx_api.hip", "pack.hip", "gemm.hip", "gemm_mfma.hip", "gemm_fp4.hip", "gemm_i8.hip", "gemm_small.hip", "conv.hip", "conv_mfma.hip", "conv_one.hip", "conv_small.hip", "fc_small.hip", "probe.hip"]
+SOURCES = ["bmx_api.hip", "pack.hip", "gemm.hip", "gemm_mfma.hip", "gemm_fp4.hip", "gemm_block.hip", "gemm_i8.hip", "gemm_small.hip", "conv.hip", "conv_mfma.hip", "conv_one.hip", "conv_small.hip", "fc_small.hip", "probe.hip"]
 HOST_BINDING = os.path.join(HERE, "_bmx_host.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -156,6 +156,11 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
                      int64_t ldb_bytes, int M, int N, int K, int dwords, const float* alpha_n, int32_t* C_i32, float* C_f32,
                      uint64_t* C_bits, const float* thr_n, int64_t ldc, bool as_count, hipStream_t s,
                      hipError_t* err);
+// gemm_block.hip: xnor products of many tiles, operand rows staged once per workgroup; rows may start on any dword.
+bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t ldb_bytes, int M, int N, int K, int dwords,
+                       const float* alpha, int32_t* C_i32, float* C_f32, int64_t ldc, bool as_count, hipStream_t s,
+                       hipError_t* err);
+extern int gemm_block;
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
                      int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s,
                      hipError_t* err);

@@ -568,6 +568,7 @@ bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* 
   const int dwords = (int)ceil_div(K, 32);
   return launch_gemm_small(A, lda_dw * 4, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, nullptr, nullptr, ldc, false, s,
                            err) ||
+         launch_gemm_block(A, lda_dw * 4, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, ldc, false, s, err) ||
          // (its loads pass registers here, which costs a large product more than widening the operands:
          // 3000 x 3000 x 2500 26.9 us a call as it is, 24.9 with the two passes; 2000 x 2000 x 1500 11.0 / 13.3)
          ((double)M * N * K < 1.2e10 && launch_gemm_fp4(A, lda_dw * 4, 1, nullptr, B, ldb_dw * 4, M, N, K, dwords, nullptr, C,
@@ -581,6 +582,8 @@ bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, 
   if (gemm_engine == 1) return false;
   if (launch_gemm_small(A, lda_w * 8, B, ldb_w * 8, M, N, K, 2 * (int)words_for(K), alpha_n, C_i32, C_f32, C_bits, thr_n, ldc,
                         as_count, s, err))
+    return true;
+  if (!C_bits && launch_gemm_block(A, lda_w * 8, B, ldb_w * 8, M, N, K, 2 * (int)words_for(K), alpha_n, C_i32, C_f32, ldc, as_count, s, err))
     return true;
   if (launch_gemm_fp4(A, lda_w * 8, 1, nullptr, B, ldb_w * 8, M, N, K, 2 * (int)words_for(K), alpha_n, C_i32, C_f32, C_bits, thr_n, ldc, as_count,
                       s, err))

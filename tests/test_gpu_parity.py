@@ -1125,6 +1125,45 @@ def test_gemm_fp4_tall_tile():
             assert "gemm_fp4_kernel<4,2,1" in B.last_kernel()
 
 
+@pytest.mark.parametrize("form", [2, 3])
+@pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (127, 129, 63, 0), (128, 128, 256, 1), (129, 127, 257, 0), (255, 65, 512, 2),
+                                       (256, 128, 513, 0), (257, 130, 1024, 1), (300, 260, 1025, 3), (513, 200, 1536 + 200, 2),
+                                       (64, 400, 3072, 0), (385, 390, 64 * 33, 1), (200, 129, 64 * 18 + 30, 4)])
+def test_gemm_fp4_block_form(form, M, N, K, pad):
+    """The kernel that stages operand rows once per workgroup, forced on one to a dozen workgroups: ragged tiles in M and N,
+    one to five segments of K and ends inside them, rows 16-byte aligned and on any dword (64-bit and 32-bit words, an
+    operand that starts between two words), garbage behind the rows; dot products, counts and scaled fp32 results."""
+    rng = np.random.default_rng(1000 * M + K + form)
+    A = oracle.binarize_pack(rng.standard_normal((M, K)).astype(np.float32), 1)
+    Bm = oracle.binarize_pack(rng.standard_normal((N, K)).astype(np.float32), 1)
+    want = oracle.xnor_gemm(A, Bm, K)
+    w = A.shape[1]
+    with tuned(k17=1, k19=form):
+        for ld in (w + pad, (w + 1) // 2 * 2 + 2 * pad):  # as it comes; 16-byte aligned
+            Ad = np.full((M, ld), POISON, dtype=np.uint64); Ad[:, :w] = A
+            Bd = np.full((N, ld), POISON, dtype=np.uint64); Bd[:, :w] = Bm
+            a, b = dev(Ad.view(np.int64)), dev(Bd.view(np.int64))
+            np.testing.assert_array_equal(B.xnor_gemm(a, b, K).cpu().numpy(), want)
+            assert "gemm_fp4_kernel<%s" % ("4,2,1,xnor,i32,block>" if form == 2 and ld % 2 == 0 else "2,2,1,xnor,i32,block") in B.last_kernel()
+            np.testing.assert_array_equal(2 * B.xnor_gemm(a, b, K, count=True).cpu().numpy() - K, want)
+        dw = -(-K // 32)
+        A32 = np.full(M * (dw + 1) + 1, 0xCDCDCDCD, dtype=np.uint32)
+        rows = A32[1:].reshape(M, dw + 1)
+        rows[:, :dw] = A.view(np.uint32)[:, :dw]
+        B32 = np.ascontiguousarray(Bm.view(np.uint32)[:, :dw])
+        a32 = dev(A32.view(np.int32))[1:].view(M, dw + 1)
+        np.testing.assert_array_equal(B.xnor_gemm_w32(a32, dev(B32.view(np.int32)), K).cpu().numpy(), want)
+        assert "gemm_fp4_kernel<2,2,1,xnor,i32,block of dwords>" in B.last_kernel()
+        x = rng.standard_normal((M, K)).astype(np.float32)
+        wt = rng.uniform(-1, 1, (N, K)).astype(np.float32)
+        alpha = rng.standard_normal(N).astype(np.float32)
+        _, rf = oracle.binary_fc(x, wt, alpha)
+        with tuned(k15=1, k17=1, k19=form):
+            for Wp in (B.binarize_pack(dev(wt), 1), torch.nn.functional.pad(B.binarize_pack(dev(wt), 1), (0, w % 2))):
+                assert_f32_close(B.binary_fc(dev(x), Wp.contiguous(), alpha=dev(alpha)).cpu().numpy(), rf)
+                assert "f32,block" in B.last_kernel()
+
+
 @pytest.mark.parametrize("split,partials", [(0, 0), (1, 0), (2, 0), (3, 0), (5, 0), (7, 0), (8, 0), (8, 2), (3, 2)])
 def test_gemm_fp4_lds_staged_kernel(split, partials):
     """The matrix-core GEMM kernel with 64 x 64 of C per wave, operands staged through LDS by the

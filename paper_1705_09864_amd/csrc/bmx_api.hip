@@ -78,6 +78,7 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
 
 namespace bmx {
 thread_local KernelNote last_kernel_note = {};
+thread_local hipError_t launch_status = hipSuccess;
 extern int conv_filters_per_wave, conv_path;
 extern int gemm_tune_rows, gemm_tune_ksplit, gemm_tune_order;
 }

@@ -227,7 +227,7 @@ void launch_stationary(const ConvParams& p, int64_t groups, int cblocks, hipStre
                   bytes <= (p.HoWo >= 64 ? 20 << 20 : p.HoWo >= 32 ? 10 << 20 : 0);
   note_kernel("conv_stationary_kernel<%d,%s%s> grid %u x %u x 256, %d filters per wave", KW,
               p.out_f32 ? (p.alpha ? "f32*alpha" : "f32") : "i32", nt ? ",nt" : "", grid.x, grid.y, p.cn);
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
+  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, s, p); };
   if (p.out_f32 && p.alpha) nt ? go(conv_stationary_kernel<KW, kOutF32Alpha, true>) : go(conv_stationary_kernel<KW, kOutF32Alpha, false>);
   else if (p.out_f32) nt ? go(conv_stationary_kernel<KW, kOutF32, true>) : go(conv_stationary_kernel<KW, kOutF32, false>);
   else nt ? go(conv_stationary_kernel<KW, kOutI32, true>) : go(conv_stationary_kernel<KW, kOutI32, false>);
@@ -366,13 +366,13 @@ hipError_t launch_binary_conv2d(const uint64_t* Xp, int N, int C, int H, int W, 
       case 27: launch_stationary<27>(p, groups, cblocks, s); break;
       default: launch_stationary<36>(p, groups, cblocks, s); break;
     }
-    return hipGetLastError();
+    return launch_error();
   }
   dim3 grid((unsigned)groups, (unsigned)ceil_div(O, 4));
   note_kernel("conv_general_kernel grid %u x %u x 256", grid.x, grid.y);
-  hipLaunchKernelGGL(conv_general_kernel, grid, dim3(256), 0, s, Xp, Wp, alpha, out_i32, out_f32, P,
+  launch_kernel(conv_general_kernel, grid, dim3(256), 0, s, Xp, Wp, alpha, out_i32, out_f32, P,
                      O, Ho * Wo, Wo, Hp, Wpp, Cw, stride, KH, KW, C * KH * KW, ld_words, d1, d2);
-  return hipGetLastError();
+  return launch_error();
 }
 
 }  // namespace bmx

@@ -487,9 +487,9 @@ void launch_ws_form(WsParams p, int m_tiles, hipStream_t s) {
               X4 == 2 ? ",x4 runs" : X4 ? ",x4" : "", ONE ? ",one block" : "", (int)groups, m_tiles, 64 * NW);
   auto go = [&](auto kern) {
 #ifdef BMX_WS_STAMPS
-    hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p, ws_stamps);
+    launch_kernel(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p, ws_stamps);
 #else
-    hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p);
+    launch_kernel(kern, dim3((unsigned)groups, (unsigned)m_tiles), dim3(64 * NW), 0, s, p);
 #endif
   };
   if constexpr (BITS) {
@@ -647,7 +647,7 @@ bool launch_conv_mfma_ws(const uint64_t* Xp, int Nimg, int C, int H, int W, cons
   } else {
     launch_ws<36, 1, 2, false, kWs36Waves>(p, m_tiles, s);
   }
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 

@@ -359,8 +359,8 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
     return parts == 1 ? conv_one_kernel<I, 1> : parts == 2 ? conv_one_kernel<I, 2> : parts == 4 ? conv_one_kernel<I, 4> : conv_one_kernel<I, 8>;
   };
   auto kernel = out_i32 ? pick(std::true_type{}) : pick(std::false_type{});
-  hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), lds, s, p);
-  *err = hipGetLastError();
+  launch_kernel(kernel, grid, dim3(64 * kWaves), lds, s, p);
+  *err = launch_error();
   return true;
 }
 

@@ -209,7 +209,7 @@ template <int OUT>
 void launch_kind(const SmallConvParams& p, int S, dim3 grid, hipStream_t s) {
   auto kern = S == 1 ? conv_small_kernel<OUT, 1> : S == 2 ? conv_small_kernel<OUT, 2> : S == 4 ? conv_small_kernel<OUT, 4>
             : S == 8 ? conv_small_kernel<OUT, 8> : conv_small_kernel<OUT, 16>;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * S), 0, s, p);
+  launch_kernel(kern, grid, dim3(64 * S), 0, s, p);
 }
 
 }  // namespace
@@ -282,7 +282,7 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   if (out_bits) launch_kind<kBits>(p, S, grid, s);
   else if (out_i32) launch_kind<kI32>(p, S, grid, s);
   else launch_kind<kF32>(p, S, grid, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 

@@ -236,7 +236,7 @@ template <int RM>
 void launch_rm(const FcSmallParams& p, Lanes l, dim3 grid, hipStream_t s) {
   const size_t lds = (size_t)RM * p.Kpad * 8;
   note_kernel("fc_small_kernel<%d,%d,%d> grid %u x %u x %d, %d features", RM, l.L, l.W, grid.x, grid.y, 64 * kWaves, p.cols);
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), lds, s, p); };
+  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(64 * kWaves), lds, s, p); };
   if (l.L == 64) {
     if (l.W == 2) go(fc_small_kernel<RM, 64, 2, 2>);
     else if (l.W == 3) go(fc_small_kernel<RM, 64, 2, 3>);
@@ -306,7 +306,7 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   else if (rm == 2) launch_rm<2>(p, lanes, grid, s);
   else if (rm == 4) launch_rm<4>(p, lanes, grid, s);
   else launch_rm<8>(p, lanes, grid, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 

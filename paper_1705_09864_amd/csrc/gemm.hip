@@ -384,7 +384,7 @@ void launch_rs(const GemmParams& p, int S, hipStream_t s) {
   dim3 grid((unsigned)(ceil_div(p.N, 64) * p.row_blocks));
   note_kernel("gemm_kernel<%d,%d,%s,%s,%s> grid %u x %d", R, CH, OP_AND ? "and" : "xor", PF ? "prefetch" : "noprefetch",
               CONV ? "conv" : "gemm", grid.x, 64 * S);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * S), lds_bytes, s, p);
+  launch_kernel(kern, grid, dim3(64 * S), lds_bytes, s, p);
 }
 
 // Rows per wave and K split.  The kernel runs at full VALU rate once about four waves sit
@@ -489,7 +489,7 @@ hipError_t launch_xnor_gemm(const uint32_t* A, bool a_padded, int64_t lda_dw, co
     p.tail1 = p.Kd;
   }
   launch<false>(p, s);
-  return hipGetLastError();
+  return launch_error();
 }
 
 hipError_t launch_plane_gemm(const uint32_t* planes_rows, int64_t lda_dw, int bits,
@@ -525,7 +525,7 @@ hipError_t launch_plane_gemm(const uint32_t* planes_rows, int64_t lda_dw, int bi
   p.ldc = ldo;
   p.out = kGemmPlanes;
   launch<true>(p, s);
-  return hipGetLastError();
+  return launch_error();
 }
 
 hipError_t launch_conv_gemm(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp,
@@ -581,7 +581,7 @@ hipError_t launch_conv_gemm(const uint64_t* Xp, int Nimg, int C, int H, int W, c
     if (R == 16) launch_rs<16, 24, false, false, true>(p, S, s);
     else launch_rs<8, 24, false, false, true>(p, S, s);
   }
-  return hipGetLastError();
+  return launch_error();
 }
 
 }  // namespace bmx

@@ -328,8 +328,8 @@ hipError_t go(const BlockParams& p, int64_t blocks, hipStream_t s) {
   static_assert(lds <= 64 * 1024, "within the LDS a kernel may use without asking");
   note_kernel("gemm_fp4_kernel<%d,%d,1,xnor,%s,block%s> grid %lld x 256, K split 1, fp4", TM, TN, OUT == kI32 ? "i32" : "f32",
               LW == 4 ? " of dwords" : "", (long long)blocks);
-  hipLaunchKernelGGL((gemm_fp4_kernel<TM, TN, OUT, LW>), dim3((unsigned)blocks), dim3(256), lds, s, p);
-  return hipGetLastError();
+  launch_kernel((gemm_fp4_kernel<TM, TN, OUT, LW>), dim3((unsigned)blocks), dim3(256), lds, s, p);
+  return launch_error();
 }
 
 template <int TM, int TN>

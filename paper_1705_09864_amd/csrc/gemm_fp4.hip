@@ -721,11 +721,11 @@ hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t bloc
               !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? (REG ? ",conv,reg" : ",conv") : (REG ? ",reg" : ""),
               (long long)blocks, 64 * waves, SPLIT ? S : 1, HALF ? " (fp16 partials)" : "");
 #ifdef BMX_FP4_STAMPS
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S, fp4_stamps);
+  launch_kernel(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S, fp4_stamps);
 #else
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S);
+  launch_kernel(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S);
 #endif
-  return hipGetLastError();
+  return launch_error();
 }
 
 }  // namespace

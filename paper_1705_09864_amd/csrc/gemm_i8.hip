@@ -426,8 +426,8 @@ hipError_t launch_i8(const I8Params& p, hipStream_t s) {
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
   note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
-  return hipGetLastError();
+  launch_kernel(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
+  return launch_error();
 }
 
 int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * ceil_div(K, 256) * 256; }
@@ -525,10 +525,10 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   set_split(p.g);
   const size_t lds = (size_t)p.g.S * (4096 + (sums ? 256 : 0));
   note_kernel("quant_small_kernel%s grid %lld x %d", sums ? "<sums>" : "", (long long)tiles, 64 * p.g.S);
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
+  auto go = [&](auto kern) { launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
   if (bits_w == 1) sums ? go(quant_small_kernel<true, true>) : go(quant_small_kernel<false, true>);
   else sums ? go(quant_small_kernel<true, false>) : go(quant_small_kernel<false, false>);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 
@@ -547,8 +547,8 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   I8Params p;
   fill_product(p, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
   q.blocks0 = p.mblocks * q.kblocks;
-  hipLaunchKernelGGL(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + p.nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
-  *err = hipGetLastError();
+  launch_kernel(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + p.nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
+  *err = launch_error();
   if (*err != hipSuccess) return true;
   p.A = q.op[0].tiles;
   p.B = q.op[1].tiles;

@@ -522,10 +522,10 @@ void launch_engine(const MfmaParams& p, bool f4, int64_t tiles, int S, size_t ld
   note_kernel("gemm_mfma_kernel<%d,%d,%d,%s,%s,%s> grid %lld x %d", TM, TN, PL, XNOR ? "xnor" : "planes",
               CONV ? "conv" : "gemm", f4 ? "fp4" : "int8", (long long)tiles, 64 * S);
   if (f4)
-    hipLaunchKernelGGL((gemm_mfma_kernel<TM, TN, PL, XNOR, CONV, true>), dim3((unsigned)tiles), dim3(64 * S), lds,
+    launch_kernel((gemm_mfma_kernel<TM, TN, PL, XNOR, CONV, true>), dim3((unsigned)tiles), dim3(64 * S), lds,
                        s, p);
   else
-    hipLaunchKernelGGL((gemm_mfma_kernel<TM, TN, PL, XNOR, CONV, false>), dim3((unsigned)tiles), dim3(64 * S), lds,
+    launch_kernel((gemm_mfma_kernel<TM, TN, PL, XNOR, CONV, false>), dim3((unsigned)tiles), dim3(64 * S), lds,
                        s, p);
 }
 
@@ -621,7 +621,7 @@ bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, 
     launch_engine<1, 1, 1, true, false>(p, f4, tiles, S, lds, s);
   else
     launch_engine<2, 2, 1, true, false>(p, f4, tiles, S, lds, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 
@@ -661,7 +661,7 @@ bool launch_plane_gemm_mfma(const uint64_t* planes_rows, int64_t lda_w, int bits
     launch_engine<1, 2, 1, false, false>(p, f4, tiles, S, lds, s);
   else
     launch_engine<1, 2, 2, false, false>(p, f4, tiles, S, lds, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 
@@ -724,7 +724,7 @@ bool launch_conv_mfma(const uint64_t* Xp, int Nimg, int C, int H, int W, const u
     launch_engine<1, 1, 1, true, true>(p, f4, tiles, S, lds, s);
   else
     launch_engine<2, 2, 1, true, true>(p, f4, tiles, S, lds, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 

@@ -164,7 +164,7 @@ template <int OUT>
 void launch_kind(const SmallGemmParams& p, int S, int64_t tiles, hipStream_t s) {
   auto kern = S == 1 ? gemm_small_kernel<OUT, 1> : S == 2 ? gemm_small_kernel<OUT, 2> : S == 4 ? gemm_small_kernel<OUT, 4>
             : S == 8 ? gemm_small_kernel<OUT, 8> : gemm_small_kernel<OUT, 16>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * S), 0, s, p);
+  launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * S), 0, s, p);
 }
 
 }  // namespace
@@ -213,7 +213,7 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   if (C_bits) launch_kind<kBits>(p, S, tiles, s);
   else if (C_i32) launch_kind<kI32>(p, S, tiles, s);
   else launch_kind<kF32>(p, S, tiles, s);
-  *err = hipGetLastError();
+  *err = launch_error();
   return true;
 }
 

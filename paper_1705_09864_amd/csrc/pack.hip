@@ -74,7 +74,7 @@ static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, in
     int64_t blocks = ceil_div(rows * spr, 4);
     blocks = blocks < cap ? blocks : cap;
     note_kernel("pack_rows_kernel<32,nontemporal> grid %lld x 256", (long long)blocks);
-    hipLaunchKernelGGL((pack_rows_kernel<32, true>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols, ldx,
+    launch_kernel((pack_rows_kernel<32, true>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols, ldx,
                        out, out_ld, words_per_row, spr, ceil_div(rows * spr, blocks));
     return;
   }
@@ -82,7 +82,7 @@ static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, in
   int64_t blocks = ceil_div(rows * spr, 4);
   blocks = blocks < cap ? blocks : cap;
   note_kernel("pack_rows_kernel<16,cached> grid %lld x 256", (long long)blocks);
-  hipLaunchKernelGGL((pack_rows_kernel<kSegWords, false>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols,
+  launch_kernel((pack_rows_kernel<kSegWords, false>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols,
                      ldx, out, out_ld, words_per_row, spr, ceil_div(rows * spr, blocks));
 }
 
@@ -97,7 +97,7 @@ hipError_t launch_pack_rows(const float* x, int64_t rows, int64_t cols, int64_t 
     out_ld = cols / 64;
   }
   launch_pack_rows_grid(x, rows, cols, ldx, out, out_ld, words_for(cols), s);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // Row pack into rows of out_ld words, writing every word of a row (zeros past the last
@@ -105,7 +105,7 @@ hipError_t launch_pack_rows(const float* x, int64_t rows, int64_t cols, int64_t 
 hipError_t launch_pack_rows_padded(const float* x, int64_t rows, int64_t cols, int64_t ldx,
                                    uint64_t* out, int64_t out_ld, hipStream_t s) {
   launch_pack_rows_grid(x, rows, cols, ldx, out, out_ld, out_ld, s);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // Inverse of the row pack: element k of row r -> +1.0f / -1.0f (a stored 1-bit model back
@@ -128,9 +128,9 @@ unpack_pm1_kernel(const uint64_t* __restrict__ bits, int64_t rows, int64_t K, in
 hipError_t launch_unpack_pm1(const uint64_t* bits, int64_t rows, int64_t K, int64_t ld_words, float* out,
                              int64_t ldo, hipStream_t s) {
   const int64_t blocks = ceil_div(rows * words_for(K), 4);
-  hipLaunchKernelGGL(unpack_pm1_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, bits,
+  launch_kernel(unpack_pm1_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, bits,
                      rows, K, ld_words, out, ldo);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // Rows of 32-bit words (the 32-bit BINARY_WORD flavour of Sec. 2.2.1) -> rows of 64-bit words:
@@ -154,9 +154,9 @@ hipError_t launch_widen_words32(const uint32_t* in, int64_t rows, int64_t K, int
                                 int64_t out_ld, hipStream_t s) {
   const int64_t Kd = (K + 31) / 32;
   const int64_t total = rows * ((Kd + 1) / 2);
-  hipLaunchKernelGGL(widen_words32_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, s, in, rows, Kd,
+  launch_kernel(widen_words32_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, s, in, rows, Kd,
                      ld_dw, out, out_ld);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // Strided pack (the matrix is stored K x ncol, pack down the columns): a wave packs one
@@ -204,9 +204,9 @@ hipError_t launch_pack_strided(const float* x, int64_t batch, int64_t K, int64_t
   const int64_t blocks = ceil_div(batch * Kw * groups, 4);
   const int64_t cap = 256 * 6;  // the kernel holds 64 loaded values per lane: 6 waves per SIMD
   note_kernel("pack_strided_kernel grid %lld x 256", (long long)(blocks < cap ? blocks : cap));
-  hipLaunchKernelGGL(pack_strided_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(256), 0,
+  launch_kernel(pack_strided_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(256), 0,
                      s, x, batch, K, ncol, ldx, batch_stride, out, out_ld, Kw, groups);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // NCHW channel pack.  A workgroup packs 64 consecutive pixels, counted through the images, for one
@@ -317,9 +317,9 @@ hipError_t launch_pack_nchw_thr(const float* x, int N, int C, int H, int W, int 
     note_kernel("pack_nchw_kernel<%s> grid %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y);
     auto kern = thr ? (nt ? pack_nchw_kernel<true, true> : pack_nchw_kernel<true, false>)
                     : (nt ? pack_nchw_kernel<false, true> : pack_nchw_kernel<false, false>);
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+    launch_kernel(kern, grid, dim3(256), 0, s, p);
   }
-  return hipGetLastError();
+  return launch_error();
 }
 
 hipError_t launch_pack_nchw(const float* x, int N, int C, int H, int W, int pad, uint64_t* xp,
@@ -389,14 +389,14 @@ hipError_t launch_pack_conv_weights(const float* w, int O, int C, int KH, int KW
   const int ld = (int)conv_weight_row_words(kwords), ldb = (int)conv_weight_bits_words(kwords);
   const int consts = conv_weight_short_k(kwords) ? 1 : 0;
   const dim3 grid((unsigned)O), block(64 * (Cw < kPackConvWaves ? Cw : kPackConvWaves));
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, w, C, Cw, ld, ldb, consts, Wp); };
+  auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, s, w, C, Cw, ld, ldb, consts, Wp); };
   switch (KH * KW) {
     case 1: go(pack_conv_weights_kernel<1>); break;
     case 9: go(pack_conv_weights_kernel<9>); break;
     case 25: go(pack_conv_weights_kernel<25>); break;
     default: go(pack_conv_weights_kernel<49>); break;
   }
-  return hipGetLastError();
+  return launch_error();
 }
 
 // k-bit weights: T[m][n * bw + r] holds the 1-bit-weight form against weight plane r;
@@ -416,9 +416,9 @@ quant_combine_kernel(const int32_t* __restrict__ T, int64_t M, int64_t N, int bw
 
 hipError_t launch_quant_combine(const int32_t* T, int64_t M, int64_t N, int bw, float denom, int32_t* S,
                                 float* out, int64_t ldo, hipStream_t s) {
-  hipLaunchKernelGGL(quant_combine_kernel, dim3((unsigned)ceil_div(M * N, 256)), dim3(256), 0, s, T, M, N, bw,
+  launch_kernel(quant_combine_kernel, dim3((unsigned)ceil_div(M * N, 256)), dim3(256), 0, s, T, M, N, bw,
                      denom, S, out, ldo);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // alpha[r] = mean |w[r][:]| in fp64: a wave (many rows) or a workgroup (few) per row, eight loads per
@@ -487,10 +487,10 @@ hipError_t launch_alpha_mean_abs(const float* w, int64_t rows, int64_t cols, int
   // a wave per row once that gives every SIMD two; below, four waves share a row
   const bool one = rows >= 2048;
   const int64_t blocks = std::min<int64_t>(one ? ceil_div(rows, 4) : rows, 65535 * 16);
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, w, rows, cols, ldw, alpha); };
+  auto go = [&](auto kern) { launch_kernel(kern, dim3((unsigned)blocks), dim3(256), 0, s, w, rows, cols, ldw, alpha); };
   if (one) v4 ? go(alpha_mean_abs_kernel<1, true>) : go(alpha_mean_abs_kernel<1, false>);
   else v4 ? go(alpha_mean_abs_kernel<4, true>) : go(alpha_mean_abs_kernel<4, false>);
-  return hipGetLastError();
+  return launch_error();
 }
 
 // Eq. 1 quantiser + bit-plane pack.  One workgroup per row m, lane <-> k: the four waves
@@ -580,9 +580,9 @@ hipError_t launch_quant_pack(const float* a, int64_t M, int64_t K, int64_t lda, 
     per = ceil_div(segs, wblocks);
   }
   note_kernel("quant_pack_kernel grid %lld x 256", (long long)(M + wblocks));
-  hipLaunchKernelGGL(quant_pack_kernel, dim3((unsigned)(M + wblocks)), dim3(256), 0, s, a, M, K, lda,
+  launch_kernel(quant_pack_kernel, dim3((unsigned)(M + wblocks)), dim3(256), 0, s, a, M, K, lda,
                      bits, planes, ld_words, rowsum, w, wrows, ldw, wbits, wb_ld, per, affine ? 1 : 0);
-  return hipGetLastError();
+  return launch_error();
 }
 
 }  // namespace bmx

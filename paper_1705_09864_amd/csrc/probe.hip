@@ -51,8 +51,8 @@ hipError_t launch_probe_valu(int workgroups, int iters, unsigned long long* out3
   ProbeArgs a;
   for (int i = 0; i < 16; ++i) a.a[i] = 0x9e3779b9u * (uint32_t)(i + 1);
   note_kernel("probe_xor_bcnt_kernel grid %d x 256", workgroups);
-  hipLaunchKernelGGL(probe_xor_bcnt_kernel, dim3((unsigned)workgroups), dim3(256), 0, s, a, iters, out3);
-  return hipGetLastError();
+  launch_kernel(probe_xor_bcnt_kernel, dim3((unsigned)workgroups), dim3(256), 0, s, a, iters, out3);
+  return launch_error();
 }
 
 }  // namespace bmx

@@ -185,12 +185,14 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
   const int r = lane & 31, h = lane >> 5;
   const int m0 = blockIdx.y * (32 * TM);
   const int bx = p.per_xcd ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-  const int chunk = bx * NW + wave;
-  // the blocks are dealt out evenly: chunk c takes blk_q of them, the first blk_r chunks one more
-  // (no division here: this runs before the wave's first load)
-  const int cc = min(chunk, p.nchunks);
-  const int b0 = cc * p.blk_q + min(cc, p.blk_r);
-  const int b1 = cc < p.nchunks ? b0 + p.blk_q + (cc < p.blk_r ? 1 : 0) : b0;
+  // The blocks are dealt out evenly: blk_q of them for every wave, the first blk_r waves one more.  The waves of a
+  // workgroup take the blocks of all of them in turn, so that they are at neighbouring pixels at any time: where a plane is
+  // not whole lines, two blocks that share a line write it at about the same time and it leaves the L2 whole.  (A
+  // stretch of its own for each wave, as it was: 64 filters of 114 x 64 x 45 x 43, 3 x 3, 16.8 us, now 13.7; 64 of 158 x 128 x 39 x
+  // 41 21.8 and 18.7; level where planes are whole lines.)  (No division here: this runs before the wave's first load.)
+  const int c0 = min(bx * NW, p.nchunks), c1 = min(c0 + NW, p.nchunks);
+  const int b0 = c0 * p.blk_q + min(c0, p.blk_r) + wave;
+  const int b1 = c1 * p.blk_q + min(c1, p.blk_r);
   WS_STAMP(0);
   WS_REALTIME(4);
 
@@ -321,15 +323,15 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
   if (b0 >= b1) return;
 
   // ---- blocks of 32 output pixels
-  for (int b = b0; b < b1; ++b) {
+  for (int b = b0; b < b1; b += NW) {
     uint32_t raw[KW];
     transpose(st, raw);
     // the next block's words are requested before this block is multiplied (after the wave's
     // last block there is nothing to request)
     PixelBlock nxt = cur;
     if constexpr (!ONE) {
-      nxt = locate(p, min(b + 1, b1 - 1), r);
-      if (b + 1 < b1) fetch(nxt, st);
+      nxt = locate(p, min(b + NW, b1 - 1), r);
+      if (b + NW < b1) fetch(nxt, st);
     }
     // (the filter reads below are the same in every trip: an opaque copy of their base keeps
     // the compiler from hoisting all of them out of the loop and into registers for good)
@@ -465,14 +467,17 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
 #endif
 }
 
-// Whether result stores bypass the caches: where a block's 32 pixels of a plane are one whole 128-byte line,
-// 8.9 against 10.3 us a call on 16 x 64 x 56 x 56 (where they are parts of two lines such parts of a large result
-// reach memory one by one: 57 x 64 x 54 x 54 26.1 us with the hint, 18.4 through L2), and for results that the memory-side
-// cache takes in as they come (64 x 256 x 14 x 14, 12.8 MB, 13.5 us a call with the hint and 14.1 without; from about
-// 30 MB on parts of lines lose).
+// Whether result stores bypass the caches (us a call, with the hint / through L2, results in the memory-side cache).
+// A plane that is a whole number of 64-byte halves of lines: yes (64 filters over 64 x 56 x 56, 12 MB, 4.4 / 5.3; 256 over 256 x
+// 24 x 24, 50 MB, 18.6 / 20.6), at 9 words up to 44 MB, where the stores are all there is (50 MB 13.6 / 12.4, 24 MB 6.4 / 7.6).  Any other
+// plane: parts of lines cost more than L2 takes to join them (9 words, 14 x 14: 3 MB 4.1 / 3.5, 18 MB 9.1 / 7.5; 18 words,
+// 24 MB 13.4 / 10.0; 36 words, 3 MB 5.2 / 4.9, 24 MB 14.5 / 12.5) but where the products outlast the stores and what L2 would
+// still hold at the end shows: 36 words 7.6 / 7.9 at 10 MB and 8.0 / 8.6 at 14, 18 words 6.0 / 6.3 at 10 MB (8.7 / 7.9 at 14).
+template <int KW>
 bool nt_stores(const WsParams& p) {
-  return (p.HoWo % 32 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 127) == 0) ||
-         (int64_t)p.Nimg * p.O * p.HoWo * 4 <= (20 << 20);
+  const int64_t bytes = (int64_t)p.Nimg * p.O * p.HoWo * 4, mb = 1 << 20;
+  if (p.HoWo % 16 == 0 && (((uintptr_t)p.out_i32 | (uintptr_t)p.out_f32) & 63) == 0) return KW > 9 || bytes <= 44 * mb;
+  return KW > 9 && bytes > 6 * mb && bytes <= (KW > 18 ? 16 : 11) * mb;
 }
 
 template <int KW, int TM, int WPS, bool BITS, int X4, bool ONE = false, int NW = 4>
@@ -494,7 +499,7 @@ void launch_ws_form(WsParams p, int m_tiles, hipStream_t s) {
   };
   if constexpr (BITS) {
     go(conv_mfma_ws_kernel<KW, TM, WPS, kBits, X4, ONE, NW>);
-  } else if (nt_stores(p)) {
+  } else if (nt_stores<KW>(p)) {
     if (p.out_i32) go(conv_mfma_ws_kernel<KW, TM, WPS, kI32 + kNt, X4, ONE, NW>);
     else go(conv_mfma_ws_kernel<KW, TM, WPS, kF32 + kNt, X4, ONE, NW>);
   } else {

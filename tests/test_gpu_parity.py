@@ -359,6 +359,37 @@ def test_conv_result_stores_with_and_without_the_streaming_hint(C, k, integer_ou
         assert_f32_close(got[-1:], rf)
 
 
+@pytest.mark.parametrize("N,C,H,W,O,k", [
+    (48, 64, 20, 20, 96, 3),     # 9 words, planes of whole 64-byte halves: hint
+    (1100, 40, 16, 16, 42, 3),   # the same past 44 MB: none
+    (60, 64, 21, 19, 70, 3),     # 9 words, parts of lines: none
+    (75, 100, 33, 33, 40, 3),    # 18 words, 13 MB (none), and
+    (50, 128, 33, 33, 40, 3),    # 8.7 MB: hint
+    (70, 200, 31, 33, 40, 3), (25, 250, 31, 33, 39, 3),  # 36 words, 11 MB (hint) and 4 MB (none)
+    (130, 33, 25, 26, 38, 5)])   # 25 words, 12 MB: hint
+def test_conv_ws_blocks_in_turn_and_hint(N, C, H, W, O, k):
+    """Several pixel blocks per wave, taken in turn by the waves of a workgroup, blocks that straddle images and
+    the result's edge, and either kind of result store: the whole batch against its images one by one, on a kernel that
+    holds a single block per wave, and a few against the oracle."""
+    rng = np.random.default_rng(N + C + H)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha = oracle.alpha_mean_abs(w)
+    Wp, xp = B.pack_conv_weights(dev(w)), B.pack_nchw(dev(x), k // 2)
+    with tuned(k18=1):
+        got = B.binary_conv2d_packed(xp, C, Wp, O, k, k, 1, k // 2, alpha=dev(alpha))
+        assert "conv_mfma_ws_kernel" in B.last_kernel()
+        goti = B.binary_conv2d_packed(xp, C, Wp, O, k, k, 1, k // 2, integer_out=True)
+        for n in range(0, N, 7):
+            one = xp[n:n + 1].contiguous()
+            assert torch.equal(goti[n:n + 1], B.binary_conv2d_packed(one, C, Wp, O, k, k, 1, k // 2, integer_out=True))
+    at = np.array([0, N // 2, N - 1])
+    ri, rf = oracle.binary_conv2d(x[at], w, 1, k // 2, alpha)
+    np.testing.assert_array_equal(goti[at].cpu().numpy(), ri)
+    assert_f32_close(got[at].cpu().numpy(), rf)
+    assert torch.equal(got, dev(alpha)[None, :, None, None] * goti.float())
+
+
 @pytest.mark.parametrize("N,H,W,O,nt", [(64, 14, 14, 256, True), (120, 14, 14, 256, False), (110, 7, 7, 256, True),
                                         (230, 7, 7, 256, False), (200, 5, 6, 64, False), (85, 16, 16, 256, True)])
 def test_popcount_conv_streams_small_results_and_whole_lines(N, H, W, O, nt):

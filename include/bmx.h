@@ -298,6 +298,8 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *   key 19 = 1: xnor products never take the kernel that stages operand rows once per workgroup (nor while
  *          any of keys 7 and 10 to 13 pins one of the others); 2, 3: that kernel with 256 x 128 (rows
  *          16-byte aligned) or 128 x 128 of C per workgroup, whatever the size (int32 or fp32 results)
+ *   key 20 = 1: convolutions of packed images never take that kernel (nor while any of keys 1, 5, 7, 10 to 12
+ *          and 14 pins another); 2, 3: its form with 128 filters x 128 pixels or 64 x 256 per workgroup, whatever the size
  *   key 8  K-split waves, key 9  tile variant (1: 32 x 32, 2: 64 x 64 per wave) of the matrix-core
  *          kernels */
 int bmx_tune_set(int key, int value);

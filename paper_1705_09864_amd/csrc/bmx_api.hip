@@ -89,7 +89,7 @@ extern "C" {
 int bmx_tune_set(int key, int value) {
   if (key == 0) {  // everything back to the automatic choice
     bmx::conv_filters_per_wave = bmx::gemm_tune_rows = bmx::gemm_tune_ksplit = bmx::gemm_tune_order = 0;
-    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = bmx::conv_small = bmx::gemm_block = 0;
+    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = bmx::conv_small = bmx::gemm_block = bmx::conv_block = 0;
     return BMX_OK;
   }
   if (key == 1) bmx::conv_filters_per_wave = value;
@@ -110,6 +110,7 @@ int bmx_tune_set(int key, int value) {
   else if (key == 17) bmx::gemm_small = value;
   else if (key == 18) bmx::conv_small = value;
   else if (key == 19) bmx::gemm_block = value;
+  else if (key == 20) bmx::conv_block = value;
   else return BMX_ERR_UNSUPPORTED;
   return BMX_OK;
 }
@@ -513,10 +514,15 @@ static int binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, co
   hipError_t err = hipSuccess;
   if (bmx::launch_conv_small(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr, out_pad, s, &err))
     return hip_status(err);
+  if (bmx::launch_conv_block(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr, out_pad, s, &err))
+    return hip_status(err);
   if (bmx::launch_conv_mfma_ws(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr,
                                out_pad, s, &err))
     return hip_status(err);
-  // every other shape: the fp32 result through the workspace, then the channel pack with the
+  if ((bmx::conv_path == 0 || bmx::conv_path == 6) && bmx::conv_filters_per_wave == 0 && bmx::conv_ws_x4 == 0 &&
+      bmx::launch_conv_fp4(xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, nullptr, nullptr, out_xp, thr, out_pad, s, &err))
+    return hip_status(err);
+  // every other shape (and whatever kernel is pinned): the fp32 result through the workspace, then the channel pack with the
   // same compare
   if (!workspace) return BMX_ERR_WORKSPACE;
   float* tmp = (float*)workspace;

@@ -180,10 +180,17 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
 bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t ldb_bytes, int M, int N, int K, int dwords,
                        const float* alpha, int32_t* C_i32, float* C_f32, int64_t ldc, bool as_count, hipStream_t s,
                        hipError_t* err);
-extern int gemm_block;
+bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
+                       int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits, const float* thr,
+                       int out_pad, hipStream_t s, hipError_t* err);
+// Estimated time of a convolution of 8 words and more by launch_conv_block or launch_conv_fp4, launch and fixed phases aside;
+// form: launch_conv_block's choice, 0 for launch_conv_fp4.
+double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form);
+extern int gemm_block, conv_block;
+// (out_bits, thr, out_pad as for launch_conv_mfma_ws)
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
-                     int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s,
-                     hipError_t* err);
+                     int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits,
+                     const float* thr, int out_pad, hipStream_t s, hipError_t* err);
 extern int gemm_fp4_split, gemm_fp4_half, gemm_fp4_band, gemm_fp4_tall;
 // fc_small.hip: the whole fully connected layer (sign bits of the fp32 input, xor + popcount,
 // scale) in one launch, for layers too small to be worth two; false when the layer is not

@@ -294,10 +294,14 @@ hipError_t launch_binary_conv2d(const uint64_t* Xp, int N, int C, int H, int W, 
   // 14 at stride 2: 6.5 against 7.1 us) and loses where the output is large (stride 1: 12.8 against
   // 11.2 us: its tiles store all at once at the end, the short-K kernel block by block), so it is not
   // chosen there.
+  {
+    hipError_t err = hipSuccess;  // from a few hundred workgroups on, see there
+    if (launch_conv_block(Xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, nullptr, nullptr, 0, s, &err)) return err;
+  }
   const int64_t tiles64 = ceil_div(O, 64) * ceil_div(P, 64);
   if (conv_path == 6 || (conv_path == 0 && !stationary_ok && !conv_weight_short_k(kwords) && tiles64 >= 64)) {
     hipError_t err = hipSuccess;
-    if (launch_conv_fp4(Xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, s, &err)) return err;
+    if (launch_conv_fp4(Xp, N, C, H, W, Wp, O, KH, KW, stride, pad, alpha, out_i32, out_f32, nullptr, nullptr, 0, s, &err)) return err;
   }
   if ((conv_path == 5 || (conv_path == 0 && conv_weight_short_k(kwords))) && gemm_engine != 1) {
     hipError_t err = hipSuccess;

@@ -21,8 +21,15 @@
 //   - Two waves share every block of rows; each counts the bits of half its blocks.
 //   - Rows that start on any dword are fetched dword by dword (global_load_lds_dword), four times the loads of a
 //     sixth of the traffic, instead of through registers.
+//   - The convolution form gathers the im2col rows of 128 (256) pixels from the packed image, 16 bytes or a dword at a
+//     time, once for 128 (64) filters; where the patches start stands in LDS.  Its results are fp32, int32 or
+//     the next convolution's packed image, halo included.
+//   (Three and four stages in flight changed nothing, at 8192^3 or with one workgroup per CU: it is issue and, with
+//   one wave on a SIMD, the chain of its own instructions that bounds the loop, not the memory behind it.)
 // Measured, us a call, gemm_fp4.hip / here: 8192^3 202 / 173, 8192 x 8192 x 1024 75 / 50, 4096^3 33 / 28, 3008 x 1471
-// x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.
+// x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.  Convolutions of packed
+// images: 11 x 320 x 49 x 49 -> 334, 3 x 3, 26.3 / 21.2, 40 x 192 x 28 x 28 -> 128, 5 x 5, 21.6 / 16.0; as packed bits, a channel pack of
+// the fp32 result behind them before: 26411 pixels, 334 filters, 45 words 33.2 / 20.1, 13500, 332, 72 24.0 / 17.6.
 #include <algorithm>
 #include <type_traits>
 
@@ -49,13 +56,21 @@ struct BlockParams {
   int tiles_m, tiles_n, tiles_per_xcd;
   int band, per_band, last_band, last_rows;
   FastDiv div_per_band, div_band, div_last;
-  const float* alpha;
+  const float* alpha;                 // per column, or null
   float row_const, row_mul, tot_mul;  // result = row_const + row_mul * (pc(a) + pc(b)) + tot_mul * sum
   void* C;
   int ldc, nt;
+  // Convolution form (Sec. 3.1): A is the filter matrix, column n of B the im2col row of output pixel n in the halo-padded
+  // packed image B: runs of `run` words, row_bytes from run to run.  alpha and thr are per row m.  C is NCHW, or (packed bits)
+  // the next convolution's image of oHp x oWp x oCw words with a halo of opad.
+  int HoWo, Wo, Ho, Hp, Wpp, Cw, stride, Nimg;
+  uint32_t run, row_bytes;
+  FastDiv div_howo, div_wo, div_run;
+  const float* thr;
+  int opad, oHp, oWp, oCw;
 };
 
-constexpr int kF32 = 0, kI32 = 1;
+constexpr int kF32 = 0, kI32 = 1, kBits = 2;
 
 // Plane n of four words as an operand: bit 4 i + n of a dword in nibble i, worth 0.5, 1 or 2 where it stands (planes
 // 0 to 2); plane 3, whose bit would be the nibble's sign, is shifted down to 0.5.
@@ -72,20 +87,26 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
   return __builtin_popcount(w.x) + (__builtin_popcount(w.y) + (__builtin_popcount(w.z) + (__builtin_popcount(w.w) + acc)));
 }
 
-// TM x TN blocks of 32 x 32 per wave; LW: bytes a lane fetches per load (16: rows start 16-byte aligned; 4: on any
-// dword).  A stage holds blocks of 32 rows x 64 bytes, A's, then B's, in the layout of gemm_fp4.hip: piece c of row r of a
-// block at 16-byte place 64 (r / 16) + 4 (r % 16) + (c xor ((r / 2) & 3)).
-template <int TM, int TN, int OUT, int LW>
+// WM x 4 / WM waves of TM x TN blocks of 32 x 32 each.  A stage holds blocks of 32 rows x 64 bytes, A's, then B's, in the
+// layout of gemm_fp4.hip: piece c of row r of a block at 16-byte place 64 (r / 16) + 4 (r % 16) + (c xor ((r / 2) & 3)).
+// LW: bytes a lane fetches per load: 16 where rows start 16-byte aligned (convolution form: where the image has an even
+// number of channel words), else 4.
+template <int WM, int TM, int TN, int OUT, int LW, bool CONV>
 __global__ void __launch_bounds__(256, TM * TN >= 8 ? 2 : 3)
 gemm_fp4_kernel(const BlockParams p) {
   extern __shared__ uint4 lds[];
-  constexpr int NBA = 2 * TM, NB = 2 * TM + 2 * TN, PW = NB / 4;  // blocks of A, of both, fetched by a wave
+  constexpr int WN = 4 / WM, NBA = WM * TM, NB = NBA + WN * TN;
+  constexpr int HA = NBA / 2, HB = (NB - NBA) / 2;  // half blocks of A and of B that a wave fetches
+  constexpr int LWA = CONV ? 16 : LW;
   constexpr int kStage = NB * 128;  // uint4 per stage
-  static_assert(NB % 4 == 0 && TM % 2 == 0 && TN % 2 == 0, "a share of the blocks for each wave, half of its own to count");
   asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.Kd), "s"(p.nseg), "s"(p.tiles_m),
                "s"(p.tiles_n), "s"(p.tiles_per_xcd), "s"(p.band), "s"(p.per_band), "s"(p.last_band), "s"(p.last_rows),
                "s"(p.div_per_band.mul), "s"(p.div_per_band.sh1), "s"(p.div_per_band.sh2), "s"(p.div_band.mul),
                "s"(p.div_band.sh1), "s"(p.div_band.sh2), "s"(p.div_last.mul), "s"(p.div_last.sh1), "s"(p.div_last.sh2));
+  if constexpr (CONV)
+    asm volatile("" ::"s"(p.HoWo), "s"(p.Wo), "s"(p.Hp), "s"(p.Wpp), "s"(p.Cw), "s"(p.stride), "s"(p.run), "s"(p.row_bytes),
+                 "s"(p.div_howo.mul), "s"(p.div_howo.sh1), "s"(p.div_howo.sh2), "s"(p.div_wo.mul), "s"(p.div_wo.sh1),
+                 "s"(p.div_wo.sh2), "s"(p.div_run.mul), "s"(p.div_run.sh1), "s"(p.div_run.sh2));
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
@@ -94,56 +115,99 @@ gemm_fp4_kernel(const BlockParams p) {
   const bool lastb = bnd == p.last_band;
   const int tile_n = (int)fast_div((uint32_t)within, lastb ? p.div_last : p.div_band);
   const int tile_m = bnd * p.band + (within - tile_n * (lastb ? p.last_rows : p.band));
-  const int m0 = tile_m * (64 * TM), n0 = tile_n * (64 * TN);
+  const int m0 = tile_m * (32 * NBA), n0 = tile_n * (32 * (NB - NBA));
 
-  // ---- loads
-  constexpr int NL = LW == 16 ? 2 : 8;  // loads per block of 32 rows
-  constexpr int RL = 32 / NL;           // rows per load
+  // ---- loads.  A half block (16 rows) is one load of 16 bytes a lane or four of 4 bytes.
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  // LW 16: the offset of either load of a block; LW 4: of its first two loads, the others eight rows apart each,
-  // held at the last row (dw: the offset of the lane's dword in its row)
-  uint32_t voff[PW][2], dw[2];
-  const int lr = LW == 16 ? lane >> 2 : lane >> 4;  // row of a load
   const bool tail = (p.Kd & 15) != 0;
-  uint32_t tsub[2];  // taken off the offset of a lane whose piece starts past the row's last dword
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int slot = LW == 16 ? lane & 3 : (lane & 15) >> 2;
-    const int piece = slot ^ (((RL * t + lr) >> 1) & 3);
-    const int d = 4 * piece + (LW == 16 ? 0 : (lane & 3));
-    const int over = 16 * (p.nseg - 1) + d - (p.Kd - 1);
-    dw[t] = 4u * d;
-    tsub[t] = over > 0 ? (LW == 16 ? 16u * piece : 4u * over) : 0u;
-#pragma unroll
-    for (int b = 0; b < PW; ++b) {
-      const int blk = wave * PW + b;
-      const bool isa = blk < NBA;
-      const uint32_t ld = isa ? p.lda : p.ldb, lim = (uint32_t)(isa ? p.M : p.N) - 1u;
-      const uint32_t row = (uint32_t)(isa ? m0 + 32 * blk : n0 + 32 * (blk - NBA)) + RL * t + lr;
-      voff[b][t] = (LW == 16 ? min(row, lim) : row) * ld + 4u * d;
+  // What differs from lane to lane: LW 16: row lane / 4 of the half block and a piece; LW 4: row 4 u + lane / 16 in load u and
+  // dword d[u & 1] of the segment.  over: how far that lies behind the row's end in the last segment.
+  const int piece16 = (lane & 3) ^ ((lane >> 3) & 3);
+  const int dw4[2] = {4 * (((lane & 15) >> 2) ^ (lane >> 5)) + (lane & 3), 4 * (((lane & 15) >> 2) ^ (2 + (lane >> 5))) + (lane & 3)};
+  const int last0 = 16 * (p.nseg - 1) - (p.Kd - 1);
+  const uint32_t sub16 = last0 + 4 * piece16 > 0 ? 16u * piece16 : 0u;
+  const uint32_t sub4[2] = {last0 + dw4[0] > 0 ? 4u * (last0 + dw4[0]) : 0u, last0 + dw4[1] > 0 ? 4u * (last0 + dw4[1]) : 0u};
+  // offset of the lane's first load of each half block in segment 0 (LW 4: of its first two loads; the other two are eight rows on)
+  uint32_t va[HA][2], vb[CONV ? 1 : HB][2];
+  auto offsets = [&](uint32_t (&v)[2], int lw, int row0, uint32_t ld, int rows) {
+    if (lw == 16) {
+      v[0] = (uint32_t)min(row0 + (lane >> 2), rows - 1) * ld + 16u * piece16;
+    } else {
+      v[0] = (uint32_t)(row0 + (lane >> 4)) * ld + 4u * dw4[0];
+      v[1] = (uint32_t)(row0 + 4 + (lane >> 4)) * ld + 4u * dw4[1];
     }
+  };
+#pragma unroll
+  for (int k = 0; k < HA; ++k) offsets(va[k], LWA, m0 + 16 * (wave * HA + k), p.lda, p.M);
+  if constexpr (!CONV) {
+#pragma unroll
+    for (int k = 0; k < HB; ++k) offsets(vb[k], LW, n0 + 16 * (wave * HB + k), p.ldb, p.N);
   }
-  // Requests segment seg of the wave's blocks into stage buf.  (As asm: the compiler would wait for every load of this kind
-  // before every LDS read.  m0 is the load's LDS address; nothing else here uses it.)
+  // (As asm: the compiler would wait for every load of this kind before every LDS read.  m0 is the load's LDS address;
+  // nothing else here uses it.)
+  auto load16 = [&](uint32_t to, const char* base, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+  };
+  auto load4 = [&](uint32_t to, const char* base, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+  };
+  auto load_rows = [&](uint32_t to, const char* base, const uint32_t (&v)[2], int lw, uint32_t ld, int rows, bool last) {
+    if (lw == 16) {
+      load16(to, base, v[0] - (last ? sub16 : 0u));
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {  // (rows past the last repeat it)
+        const uint32_t off = min(v[u & 1] + (uint32_t)(u >> 1) * 8u * ld, 4u * dw4[u & 1] + (uint32_t)(rows - 1) * ld);
+        load4(to + 256u * u, base, off - (last ? sub4[u & 1] : 0u));
+      }
+    }
+  };
+  // convolution form: where the patches of the tile's pixels start in the image (pixels past the last repeat it)
+  uint32_t* const patch = (uint32_t*)(lds + 2 * kStage);
+  if constexpr (CONV) {
+    for (int i = threadIdx.x; i < 32 * (NB - NBA); i += 256) {
+      const uint32_t n = (uint32_t)min(n0 + i, p.N - 1);
+      const uint32_t img = fast_div(n, p.div_howo), rem = n - img * (uint32_t)p.HoWo;
+      const uint32_t ho = fast_div(rem, p.div_wo), wo = rem - ho * (uint32_t)p.Wo;
+      patch[i] = (((img * (uint32_t)p.Hp + ho * (uint32_t)p.stride) * (uint32_t)p.Wpp + wo * (uint32_t)p.stride) * (uint32_t)p.Cw) * 8u;
+    }
+    __syncthreads();
+  }
+  uint32_t vp[CONV && LW == 16 ? HB : 1];
+  if constexpr (CONV && LW == 16) {
+#pragma unroll
+    for (int k = 0; k < HB; ++k) vp[k] = patch[16 * (wave * HB + k) + (lane >> 2)];
+  }
+  // dword d of a patch
+  auto in_patch = [&](uint32_t d) {
+    const uint32_t w = d >> 1, run = fast_div(w, p.div_run);
+    return run * p.row_bytes + (w - run * p.run) * 8u + (d & 1u) * 4u;
+  };
+  // Requests segment seg of the wave's half blocks into stage buf.
   auto issue = [&](int seg, int buf) {
     const bool last = tail && seg + 1 == p.nseg;
+    const uint32_t to = lds0 + (uint32_t)(buf * kStage) * 16u;
 #pragma unroll
-    for (int b = 0; b < PW; ++b) {
-      const int blk = wave * PW + b;
-      const char* base = (blk < NBA ? p.A : p.B) + (uint32_t)seg * 64u;
+    for (int k = 0; k < HA; ++k)
+      load_rows(to + 1024u * (uint32_t)(wave * HA + k), p.A + (uint32_t)seg * 64u, va[k], LWA, p.lda, p.M, last);
+    const uint32_t tob = to + 2048u * NBA + 1024u * (uint32_t)(wave * HB);
+    if constexpr (!CONV) {
 #pragma unroll
-      for (int u = 0; u < NL; ++u) {
-        const uint32_t to = lds0 + (uint32_t)(buf * kStage + blk * 128) * 16u + (uint32_t)u * (LW == 16 ? 1024u : 256u);
-        uint32_t off = voff[b][u & 1];
-        if (LW == 4)
-          off = blk < NBA ? min(off + (uint32_t)(u >> 1) * 8u * p.lda, dw[u & 1] + (uint32_t)(p.M - 1) * p.lda)
-                          : min(off + (uint32_t)(u >> 1) * 8u * p.ldb, dw[u & 1] + (uint32_t)(p.N - 1) * p.ldb);
-        off -= last ? tsub[u & 1] : 0u;
-        if constexpr (LW == 16)
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
-        else
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
-      }
+      for (int k = 0; k < HB; ++k) load_rows(tob + 1024u * k, p.B + (uint32_t)seg * 64u, vb[k], LW, p.ldb, p.N, last);
+    } else if constexpr (LW == 16) {
+      const uint32_t d = 16u * (uint32_t)seg + 4u * piece16;
+      const uint32_t at = in_patch(d < (uint32_t)p.Kd ? d : 16u * (uint32_t)seg);
+#pragma unroll
+      for (int k = 0; k < HB; ++k) load16(tob + 1024u * k, p.B, vp[k] + at);
+    } else {
+      uint32_t at[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) at[t] = in_patch(min(16u * (uint32_t)seg + dw4[t], (uint32_t)p.Kd - 1u));
+#pragma unroll
+      for (int k = 0; k < HB; ++k)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          load4(tob + 1024u * k + 256u * u, p.B, patch[16 * (wave * HB + k) + 4 * u + (lane >> 4)] + at[u & 1]);
     }
   };
   // What the loads left behind the row's last dword counts as zero.
@@ -156,11 +220,11 @@ gemm_fp4_kernel(const BlockParams p) {
     }
   };
 
-  // ---- products.  Two waves share every block; each takes its blocks in an order of its own (block i of the registers is
-  // block i xor xa of the tile) and counts the first half of them.
-  const int wm = wave >> 1, wn = wave & 1;
-  constexpr int CA = TM / 2, CB = TN / 2;
-  const int xa = wn * CA, xb = wm * CB;
+  // ---- products.  Waves side by side share blocks; each takes its blocks in an order of its own (block i of the registers is
+  // block i xor xa of the wave's) and counts the first half of those that it shares.
+  const int wm = WM == 2 ? wave >> 1 : 0, wn = WM == 2 ? wave & 1 : wave;
+  constexpr int CA = TM / 2, CB = WM == 2 ? TN / 2 : TN;
+  const int xa = (wn & 1) * CA, xb = WM == 2 ? wm * CB : 0;
   int rd[2];
 #pragma unroll
   for (int g = 0; g < 2; ++g) rd[g] = (r >> 4) * 64 + (r & 15) * 4 + ((2 * g + h) ^ ((r >> 1) & 3));
@@ -226,10 +290,44 @@ gemm_fp4_kernel(const BlockParams p) {
     for (int j = 0; j < CB; ++j) asm volatile("" : "+v"(pb[j]));
   };
 
+  // the epilogue's constants, requested first of all: alpha of the lane's columns, or alpha and threshold of row m0 + thread
+  float al[TN], al_row = 1.0f, th_row = 0.0f;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    al[j] = (!CONV && OUT == kF32 && p.alpha) ? p.alpha[min(n0 + 32 * (wn * TN + (j ^ xb)) + r, p.N - 1)] : 1.0f;
+  if (CONV && OUT != kI32) {
+    const int m = min(m0 + (int)threadIdx.x, p.M - 1);
+    if (p.alpha) al_row = p.alpha[m];
+    if (OUT == kBits && p.thr) th_row = p.thr[m];
+  }
   issue(0, 0);
+  if (p.nseg > 1) issue(1, 1);
+  if constexpr (OUT == kBits) {
+    // the tile's words of the output image's halo: +1 (the sign of the next layer's zero padding) for every real channel,
+    // spread over the tiles of this row of tiles
+    for (int cw = m0 >> 6; p.opad > 0 && cw < min(p.oCw, (m0 >> 6) + WM); ++cw) {
+      const uint64_t ones = (cw == p.oCw - 1 && (p.M & 63)) ? (((uint64_t)1 << (p.M & 63)) - 1) : ~(uint64_t)0;
+      const int nh = p.oHp * p.oWp - p.HoWo;
+      for (int i = tile_n * 256 + (int)threadIdx.x; i < nh * p.Nimg; i += p.tiles_n * 256) {
+        const int n = i / nh, k = i - n * nh;
+        int hh, ww;
+        if (k < 2 * p.opad * p.oWp) {  // rows above and below
+          hh = k / p.oWp;
+          ww = k - hh * p.oWp;
+          if (hh >= p.opad) hh += p.Ho;
+        } else {  // left and right of the interior rows
+          const int j = k - 2 * p.opad * p.oWp;
+          const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
+          hh = p.opad + rr;
+          ww = c < p.opad ? c : p.Wo + c;
+        }
+        ((uint64_t*)p.C)[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + cw] = ones;
+      }
+    }
+  }
   if (p.nseg > 1) {
-    issue(1, 1);
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PW * NL) : "memory");
+    constexpr int kLoads = HA * (LWA == 16 ? 1 : 4) + HB * (LW == 16 ? 1 : 4);  // a wave's loads per segment
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kLoads) : "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     if (tail) {
@@ -274,21 +372,61 @@ gemm_fp4_kernel(const BlockParams p) {
     pb[j] += __shfl_xor(pb[j], 32);
     if (h == 0) ct[32 * (wn * TN + (j ^ xb)) + r] = p.row_mul * (float)pb[j];
   }
+  f_alias *const alr = ct + 32 * (NB - NBA), *const thr = alr + 32 * NBA;
+  if (CONV && OUT != kI32 && threadIdx.x < 32 * NBA) {
+    alr[threadIdx.x] = al_row;
+    if (OUT == kBits) thr[threadIdx.x] = th_row;
+  }
   const int mw = m0 + 32 * TM * wm, nw = n0 + 32 * TN * wn;
-  float cb[TN], al[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) al[j] = (OUT == kF32 && p.alpha) ? p.alpha[min(nw + 32 * (j ^ xb) + r, p.N - 1)] : 1.0f;
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  float cb[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) cb[j] = ct[32 * (wn * TN + (j ^ xb)) + r];
-  auto value = [&](float tot, float rc, int j) {
-    const float dot = fmaf(p.tot_mul, tot, rc + cb[j]);  // exact: whole numbers below 2^24
-    return OUT == kI32 ? (int)dot : __builtin_bit_cast(int, al[j] * dot);
-  };
-  uint32_t at[TN];  // byte offset of the lane's results in row 0 of each column block
+  uint32_t img[TN], rem[TN];  // convolution form: image and pixel of the lane's columns
 #pragma unroll
-  for (int j = 0; j < TN; ++j) at[j] = (uint32_t)(4 * h * p.ldc + 32 * (j ^ xb) + r) * 4u;
-  char* const cbase = (char*)p.C + ((size_t)mw * p.ldc + nw) * 4;
+  for (int j = 0; j < TN; ++j) {
+    const uint32_t n = (uint32_t)min(nw + 32 * (j ^ xb) + r, p.N - 1);
+    img[j] = CONV ? fast_div(n, p.div_howo) : 0u;
+    rem[j] = CONV ? n - img[j] * (uint32_t)p.HoWo : n;
+  }
+  if constexpr (OUT == kBits) {
+    static_assert(TM == 2 && TN == 2, "a wave holds a word of 64 pixels");
+    uint32_t half[TN][TM];  // of pixel block j: filters of block i
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) half[j][i] = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int mi = 32 * (i ^ xa) + 8 * q, at = 32 * wm * TM + mi + 4 * h;
+        const v4f_alias rc = *(const v4f_alias*)(rt + at), a4 = *(const v4f_alias*)(alr + at), t4 = *(const v4f_alias*)(thr + at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const float dot = fmaf(p.tot_mul, acc[i][j][4 * q + e], rc[e] + cb[j]);
+            if (mw + mi + 4 * h + e < p.M && a4[e] * dot >= t4[e]) half[j][i] |= 1u << (8 * q + 4 * h + e);
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) half[j][i] |= (uint32_t)__shfl_xor((int)half[j][i], 32);
+    }
+    // lane (r, h) stores the word of pixel r of block h of the registers
+    const uint32_t lo = xa ? (h ? half[1][1] : half[0][1]) : (h ? half[1][0] : half[0][0]);
+    const uint32_t hi = xa ? (h ? half[1][0] : half[0][0]) : (h ? half[1][1] : half[0][1]);
+    if (nw + 32 * (h ^ xb) + r < p.N && mw < p.M) {
+      const uint32_t im = h ? img[1] : img[0], re = h ? rem[1] : rem[0];
+      const uint32_t ho = fast_div(re, p.div_wo), wo = re - ho * (uint32_t)p.Wo;
+      const uint32_t word = ((im * (uint32_t)p.oHp + ho + (uint32_t)p.opad) * (uint32_t)p.oWp + wo + (uint32_t)p.opad) * (uint32_t)p.oCw + (uint32_t)(mw >> 6);
+      ((uint64_t*)p.C)[word] = (uint64_t)hi << 32 | lo;
+    }
+    return;
+  }
+  const int ldr = CONV ? p.HoWo : p.ldc;  // elements from row to row
+  uint32_t at[TN];                        // byte offset of the lane's results in row 0 of each column block
+#pragma unroll
+  for (int j = 0; j < TN; ++j) at[j] = ((img[j] * (uint32_t)p.M + 4u * h) * (uint32_t)ldr + (CONV ? rem[j] : (uint32_t)(32 * (j ^ xb) + r))) * 4u;
+  char* const cbase = (char*)p.C + ((size_t)mw * ldr + (CONV ? 0 : nw)) * 4;
   auto store = [&](auto inside_tag, auto nt_tag) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -296,12 +434,15 @@ gemm_fp4_kernel(const BlockParams p) {
       for (int q = 0; q < 4; ++q) {
         const int mi = 32 * (i ^ xa) + 8 * q;
         const v4f_alias rc = *(const v4f_alias*)(rt + 32 * wm * TM + mi + 4 * h);
+        v4f_alias a4 = {1.0f, 1.0f, 1.0f, 1.0f};
+        if (CONV && OUT == kF32) a4 = *(const v4f_alias*)(alr + 32 * wm * TM + mi + 4 * h);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          char* const row = cbase + (size_t)(uint32_t)((mi + e) * p.ldc) * 4;
+          char* const row = cbase + (size_t)(uint32_t)((mi + e) * ldr) * 4;
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            const int v = value(acc[i][j][4 * q + e], rc[e], j);
+            const float dot = fmaf(p.tot_mul, acc[i][j][4 * q + e], rc[e] + cb[j]);  // exact: whole numbers below 2^24
+            const int v = OUT == kI32 ? (int)dot : __builtin_bit_cast(int, (CONV ? a4[e] : al[j]) * dot);
             if constexpr (decltype(inside_tag)::value) {
               if constexpr (decltype(nt_tag)::value)
                 asm volatile("global_store_dword %0, %1, %2 nt" ::"v"(at[j]), "v"(v), "s"(row) : "memory");
@@ -322,21 +463,14 @@ gemm_fp4_kernel(const BlockParams p) {
   }
 }
 
-template <int TM, int TN, int OUT, int LW>
-hipError_t go(const BlockParams& p, int64_t blocks, hipStream_t s) {
-  constexpr size_t lds = 2 * (2 * TM + 2 * TN) * 2048;
+template <int WM, int TM, int TN, int OUT, int LW, bool CONV>
+hipError_t go(BlockParams& p, hipStream_t s) {
+  constexpr int NBA = WM * TM, NBB = 4 / WM * TN;
+  constexpr size_t lds = 2 * (NBA + NBB) * 2048 + (CONV ? 128 * NBB : 0);
   static_assert(lds <= 64 * 1024, "within the LDS a kernel may use without asking");
-  note_kernel("gemm_fp4_kernel<%d,%d,1,xnor,%s,block%s> grid %lld x 256, K split 1, fp4", TM, TN, OUT == kI32 ? "i32" : "f32",
-              LW == 4 ? " of dwords" : "", (long long)blocks);
-  launch_kernel((gemm_fp4_kernel<TM, TN, OUT, LW>), dim3((unsigned)blocks), dim3(256), lds, s, p);
-  return launch_error();
-}
-
-template <int TM, int TN>
-hipError_t launch_shape(BlockParams& p, bool f32, bool dwords, hipStream_t s) {
-  p.tiles_m = (int)ceil_div(p.M, 64 * TM);
-  p.tiles_n = (int)ceil_div(p.N, 64 * TN);
-  p.band = std::min(16 / TM, p.tiles_m);  // 1024 rows of C, as in gemm_fp4.hip
+  p.tiles_m = (int)ceil_div(p.M, 32 * NBA);
+  p.tiles_n = (int)ceil_div(p.N, 32 * NBB);
+  p.band = std::min(32 / NBA, p.tiles_m);  // 1024 rows of C, as in gemm_fp4.hip
   p.per_band = p.band * p.tiles_n;
   p.last_band = (p.tiles_m - 1) / p.band;
   p.last_rows = p.tiles_m - p.last_band * p.band;
@@ -344,10 +478,12 @@ hipError_t launch_shape(BlockParams& p, bool f32, bool dwords, hipStream_t s) {
   p.div_band = make_fast_div((uint32_t)p.band);
   p.div_last = make_fast_div((uint32_t)p.last_rows);
   p.tiles_per_xcd = (int)ceil_div((int64_t)p.tiles_m * p.tiles_n, 8);
-  const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if constexpr (TM * TN == 8) return f32 ? go<TM, TN, kF32, 16>(p, blocks, s) : go<TM, TN, kI32, 16>(p, blocks, s);
-  else if (f32) return dwords ? go<TM, TN, kF32, 4>(p, blocks, s) : go<TM, TN, kF32, 16>(p, blocks, s);
-  else return dwords ? go<TM, TN, kI32, 4>(p, blocks, s) : go<TM, TN, kI32, 16>(p, blocks, s);
+  const unsigned blocks = 8u * (unsigned)p.tiles_per_xcd;
+  note_kernel("gemm_fp4_kernel<%d,%d,1,xnor,%s,%sblock%s%s> grid %u x 256, K split 1, fp4", TM, TN,
+              OUT == kI32 ? "i32" : OUT == kBits ? "bits" : "f32", CONV ? "conv," : "", LW == 4 ? " of dwords" : "",
+              WM == 1 ? " one high" : "", blocks);
+  launch_kernel((gemm_fp4_kernel<WM, TM, TN, OUT, LW, CONV>), dim3(blocks), dim3(256), lds, s, p);
+  return launch_error();
 }
 
 }  // namespace
@@ -392,8 +528,104 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.C = C_i32 ? (void*)C_i32 : (void*)C_f32;
   p.ldc = (int)ldc;
   p.nt = ldc % 32 == 0 && ((uintptr_t)p.C & 127) == 0;
+  p.HoWo = p.Wo = p.Ho = p.Hp = p.Wpp = p.Cw = p.stride = p.Nimg = 1;
+  p.run = p.row_bytes = 1;
+  p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
+  p.thr = nullptr;
+  p.opad = p.oHp = p.oWp = p.oCw = 0;
   const bool large = !any_dword && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096);
-  *err = large ? block::launch_shape<4, 2>(p, !C_i32, false, s) : block::launch_shape<2, 2>(p, !C_i32, any_dword, s);
+  using namespace block;
+  if (large) *err = C_i32 ? go<2, 4, 2, kI32, 16, false>(p, s) : go<2, 4, 2, kF32, 16, false>(p, s);
+  else if (any_dword) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);
+  else *err = C_i32 ? go<2, 2, 2, kI32, 16, false>(p, s) : go<2, 2, 2, kF32, 16, false>(p, s);
+  return true;
+}
+
+int conv_block = 0;  // 1 = never, 2 = 128 filters x 128 pixels and 3 = 64 x 256 per workgroup whatever the size
+
+// Fitted to 110 convolutions of 45 to 392 words measured on each (fp32 results; the choice by it is 0.3 % off the best):
+// us per word of K.  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
+// through registers (an odd number of channel words).  Here by workgroups per CU; one alone leaves every SIMD one wave, which
+// is half as fast as two.
+double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
+  const double there = (any_dword ? 0.06 : 0.042) * (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
+  auto here = [&](int64_t wgs) { return 0.1 * (any_dword ? 1.1 : 1.0) * std::max(1.6, (double)ceil_div(wgs, 256)); };
+  const double high = here(ceil_div(P, 128) * ceil_div(O, 128)), wide = here(ceil_div(P, 256) * ceil_div(O, 64));
+  *form = std::min(high, wide) >= there ? 0 : high <= wide ? 2 : 3;
+  return kwords * std::min(there, std::min(high, wide));
+}
+
+bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
+                       int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits, const float* thr,
+                       int out_pad, hipStream_t s, hipError_t* err) {
+  if (conv_block == 1 || conv_path || gemm_engine || conv_filters_per_wave || conv_ws_x4 || gemm_fp4_split || gemm_fp4_half ||
+      gemm_fp4_band)
+    return false;
+  const int Ho = (H + 2 * pad - KH) / stride + 1, Wo = (W + 2 * pad - KW) / stride + 1;
+  const int Cw = (int)words_for(C), kwords = KH * KW * Cw, Hp = H + 2 * pad, Wpp = W + 2 * pad;
+  const int64_t P = (int64_t)Nimg * Ho * Wo, ld_words = conv_weight_row_words(kwords);
+  const int64_t lim = (int64_t)1 << 32;
+  if ((ld_words & 1) || ((uintptr_t)Wp & 15) || (int64_t)C * KH * KW >= (1 << 22)) return false;
+  // (32-bit byte offsets throughout, and counts of pixels, halo words and tiles)
+  if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= lim || ((int64_t)O + 256) * ld_words * 8 >= lim || P >= lim / 4) return false;
+  if (((int64_t)Nimg * O + 256) * Ho * Wo * 4 >= lim) return false;
+  if (out_bits && (int64_t)Nimg * (Ho + 2 * out_pad) * (Wo + 2 * out_pad) * words_for(O) >= lim / 4) return false;
+  const bool any_dword = (Cw & 1) || ((uintptr_t)Xp & 15);
+  int form = conv_block;
+  if (form == 0) {
+    conv_long_us(P, O, kwords, any_dword, &form);
+    if (conv_weight_short_k(kwords)) return false;
+    // Fewer words than a segment: the results are the time, and they leave best where neighbouring pixels are in one place.  As packed
+    // bits from 7000 tiles of 32 x 32 on (1 x 1, 87822 pixels, 128 filters 11.8 us in conv_small.hip, 8.5 here; 51200, 137 level),
+    // fp32 and int32 from 44 MB (the same 15.2 in conv.hip, 12.0; 147630 pixels, 64 filters, 38 MB 11.2 / 12.1).
+    if (kwords < 8) {
+      if (out_bits ? ceil_div(P, 32) * ceil_div(O, 32) < 7000 : P * O * 4 < ((int64_t)44 << 20)) return false;
+      if (form == 0) form = O <= 64 ? 3 : 2;
+    }
+    if (form == 0) return false;
+  }
+  block::BlockParams p;
+  p.A = (const char*)Wp;
+  p.B = (const char*)Xp;
+  p.lda = (uint32_t)(ld_words * 8);
+  p.ldb = 0;
+  p.M = O;
+  p.N = (int)P;
+  p.Kd = 2 * kwords;
+  p.nseg = (int)ceil_div(p.Kd, 16);
+  p.alpha = alpha;
+  p.thr = thr;
+  p.row_const = (float)(C * KH * KW);
+  p.row_mul = -2.0f;
+  p.tot_mul = 4.0f;
+  p.C = out_bits ? (void*)out_bits : out_i32 ? (void*)out_i32 : (void*)out_f32;
+  p.ldc = 0;
+  p.nt = Ho * Wo % 32 == 0 && ((uintptr_t)p.C & 127) == 0;
+  p.HoWo = Ho * Wo;
+  p.Wo = Wo;
+  p.Ho = Ho;
+  p.Hp = Hp;
+  p.Wpp = Wpp;
+  p.Cw = Cw;
+  p.stride = stride;
+  p.Nimg = Nimg;
+  p.run = (uint32_t)(KW * Cw);
+  p.row_bytes = (uint32_t)((int64_t)Wpp * Cw * 8);
+  p.div_howo = make_fast_div((uint32_t)p.HoWo);
+  p.div_wo = make_fast_div((uint32_t)Wo);
+  p.div_run = make_fast_div(p.run);
+  p.opad = out_pad;
+  p.oHp = Ho + 2 * out_pad;
+  p.oWp = Wo + 2 * out_pad;
+  p.oCw = (int)words_for(O);
+  const bool one_high = form == 3;
+  using namespace block;
+  auto kind = [&](auto wm, auto lw) {
+    constexpr int WM = decltype(wm)::value, LW = decltype(lw)::value;
+    return out_bits ? go<WM, 2, 2, kBits, LW, true>(p, s) : out_i32 ? go<WM, 2, 2, kI32, LW, true>(p, s) : go<WM, 2, 2, kF32, LW, true>(p, s);
+  };
+  auto high = [&](auto lw) { return one_high ? kind(std::integral_constant<int, 1>{}, lw) : kind(std::integral_constant<int, 2>{}, lw); };
+  *err = any_dword ? high(std::integral_constant<int, 4>{}) : high(std::integral_constant<int, 16>{});
   return true;
 }
 

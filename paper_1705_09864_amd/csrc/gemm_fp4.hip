@@ -82,6 +82,9 @@ struct Fp4Params {
   uint32_t run_pieces, row_bytes, npieces;  // pieces per run; bytes from run to run; pieces per pixel
                                             // (through registers: words per run, per pixel)
   FastDiv div_howo, div_wo, div_run;
+  // packed bits of the convolution form: the next convolution's image (C_bits, 64-bit words), its size, words per pixel, halo;
+  // thr is per row m
+  int Nimg, Ho, opad, oHp, oWp, oCw;
   int Kd;  // REG 2: data dwords per row (2 Kw, or one less)
 };
 
@@ -338,15 +341,40 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   const int n_c0 = min(n0 + r, p.N - 1), n_c1 = min(n0 + 32 + r, p.N - 1);
   float aln0 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c0] : 1.0f;
   float aln1 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c1] : 1.0f;
-  float thn0 = (XNOR && OUT == kOutBits && p.thr) ? p.thr[n_c0] : 0.0f;
-  float thn1 = (XNOR && OUT == kOutBits && p.thr) ? p.thr[n_c1] : 0.0f;
+  float thn0 = (XNOR && !CONV && OUT == kOutBits && p.thr) ? p.thr[n_c0] : 0.0f;
+  float thn1 = (XNOR && !CONV && OUT == kOutBits && p.thr) ? p.thr[n_c1] : 0.0f;
   const int rowsum_lane = XNOR ? 0 : p.rowsum[min(m0 + lane, p.M - 1)];
   const float alpha_lane = (CONV && p.alpha) ? p.alpha[min(m0 + lane, p.M - 1)] : 1.0f;
+  const float thr_lane = (CONV && OUT == kOutBits && p.thr) ? p.thr[min(m0 + lane, p.M - 1)] : 0.0f;
 
   uint4 nx[NB][2];  // REG: the next segment's words
   if (seg_lo < seg_hi) {
     if constexpr (REG) fetch_segment<NA, NB, CONV, REG == 2>(p, nx, voff, piece[0], piece[1], seg_lo);
     else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
+  }
+  if constexpr (CONV && OUT == kOutBits) {
+    // word tile_m of the output image's halo: +1 (the sign of the next layer's zero padding) for every real
+    // channel, spread over the tiles of this row of tiles
+    if (p.opad > 0 && live) {
+      const uint64_t ones = (tile_m == p.oCw - 1 && (p.M & 63)) ? (((uint64_t)1 << (p.M & 63)) - 1) : ~(uint64_t)0;
+      const int nh = p.oHp * p.oWp - p.HoWo, per_tile = SPLIT ? (int)blockDim.x : 64;
+      uint64_t* const ob = (uint64_t*)p.C_bits;
+      for (int i = tile_n * per_tile + (SPLIT ? (int)threadIdx.x : lane); i < nh * p.Nimg; i += p.tiles_n * per_tile) {
+        const int n = i / nh, k = i - n * nh;
+        int hh, ww;
+        if (k < 2 * p.opad * p.oWp) {  // rows above and below
+          hh = k / p.oWp;
+          ww = k - hh * p.oWp;
+          if (hh >= p.opad) hh += p.Ho;
+        } else {  // left and right of the interior rows
+          const int j = k - 2 * p.opad * p.oWp;
+          const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
+          hh = p.opad + rr;
+          ww = c < p.opad ? c : p.Wo + c;
+        }
+        ob[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + tile_m] = ones;
+      }
+    }
   }
   FP4_STAMP(1);
   FP4_REALTIME(4);
@@ -462,8 +490,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   // wait also sits out every store issued before it.
   asm volatile("" : "+v"(aln0), "+v"(aln1), "+v"(thn0), "+v"(thn1));
   int rowsum_l = rowsum_lane;
-  float alpha_l = alpha_lane;
-  asm volatile("" : "+v"(rowsum_l), "+v"(alpha_l));
+  float alpha_l = alpha_lane, thr_l = thr_lane;
+  asm volatile("" : "+v"(rowsum_l), "+v"(alpha_l), "+v"(thr_l));
 
   // CONV: where this lane's pixels' results go
   uint32_t pix_img[TN], pix_rem[TN];
@@ -473,6 +501,14 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     pix_img[j] = CONV ? fast_div((uint32_t)n, p.div_howo) : 0u;
     pix_rem[j] = CONV ? (uint32_t)n - pix_img[j] * (uint32_t)p.HoWo : 0u;
   }
+  // packed bits of the convolution form: word tile_m of pixel n0 + lane of the tile, filter m0 in its bit 0
+  auto store_word = [&](uint32_t lo, uint32_t hi) {
+    if (n0 + lane >= p.N || !live) return;
+    const uint32_t img = h ? pix_img[1] : pix_img[0], rem = h ? pix_rem[1] : pix_rem[0];
+    const uint32_t ho = fast_div(rem, p.div_wo), wo = rem - ho * (uint32_t)p.Wo;
+    const uint32_t word = ((img * (uint32_t)p.oHp + ho + (uint32_t)p.opad) * (uint32_t)p.oWp + wo + (uint32_t)p.opad) * (uint32_t)p.oCw + (uint32_t)tile_m;
+    ((uint64_t*)p.C_bits)[word] = (uint64_t)hi << 32 | lo;
+  };
   // ---- epilogue.  Register v of lane (r, h) in block (i, j) is C[32 i + 8 (v / 4) + 4 h + v % 4][32 j + r].
   // tot: the full-K sum of the MFMA results; ra, cb: pc(A row), pc(B column) over the full K
   // (plane form: ra = the row sum of the quantised activations).
@@ -520,6 +556,32 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     for (int j = 0; j < TN; ++j) pb[j] += __shfl_xor(pb[j], 32);
   }
 
+  if constexpr (!SPLIT && CONV && OUT == kOutBits) {
+    uint32_t half[TN][TM];  // of pixel 32 j + r: filters 32 i .. 32 i + 31
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) half[j][i] = 0u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int bit = 8 * (v >> 2) + 4 * h + (v & 3), mi = 32 * i + bit;
+        const int ra = __shfl(pa[i], bit);
+        const float al = __shfl(alpha_l, mi), th = __shfl(thr_l, mi);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const float dot = (float)(p.Kreal - 2 * ra - 2 * pb[j]) + 4.0f * acc[i][j][v];
+          if (m0 + mi < p.M && al * dot >= th) half[j][i] |= 1u << bit;
+        }
+      }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) half[j][i] |= (uint32_t)__shfl_xor((int)half[j][i], 32);
+    store_word(h ? half[1][0] : half[0][0], h ? half[1][1] : half[0][1]);
+    return;
+  }
   if (!SPLIT) {
     // the row terms of every result register first (a shuffle each: fetched one by one between
     // the stores, each would cost an LDS round trip), then nothing but arithmetic and stores
@@ -573,6 +635,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
         }
       }
   int* cnt = (int*)(part + wave * kSlot + kPart);  // [32 TM] row counts, [32 TN] column counts
+  uint32_t* const words = (uint32_t*)(lds + S * kSlot);  // packed bits of the convolution form: two dwords per pixel of the tile
+  if (CONV && OUT == kOutBits && wave == 0) words[lane] = words[64 + lane] = 0u;
   if (XNOR && h == 0) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) cnt[32 * i + r] = pa[i];
@@ -616,6 +680,18 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
       if (CONV) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) alm[e] = __shfl(alpha_l, row0 + e);
+      }
+      if constexpr (CONV && OUT == kOutBits) {
+        const float t4[4] = {tot.x, tot.y, tot.z, tot.w};
+        uint32_t bits = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float thm = __shfl(thr_l, row0 + e);
+          const float dot = (float)(p.Kreal - 2 * ra[e] - 2 * cb) + 4.0f * t4[e];
+          if (m0 + row0 + e < p.M && alm[e] * dot >= thm) bits |= 1u << (8 * q + 4 * h + e);
+        }
+        atomicOr(&words[2 * (32 * j + r) + i], bits);
+        return;
       }
       auto put4 = [&](auto nt_tag) {
         finish(std::false_type{}, nt_tag, i, j, 4 * q, tot.x, ra[0], cb, alm[0], th);
@@ -695,6 +771,10 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   };
   if (S == 8) reduce(std::true_type{});
   else reduce(std::false_type{});
+  if constexpr (CONV && OUT == kOutBits) {
+    __syncthreads();
+    if (wave == 0) store_word(words[2 * lane], words[2 * lane + 1]);
+  }
   FP4_STAMP(5);
 #ifdef BMX_FP4_STAMPS
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -712,7 +792,7 @@ hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t bloc
   constexpr int part = HALF ? kGroups * 32 : kGroups * 64;
   constexpr int slot = (!SPLIT || kStage > part + kCnt) ? kStage : part + kCnt;
   const int waves = SPLIT ? S : tiles_per_wg;
-  const size_t lds = (size_t)waves * slot * 16;
+  const size_t lds = (size_t)waves * slot * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
   auto kern = gemm_fp4_kernel<TM, TN, PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
@@ -831,6 +911,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.ldc = (int)ldc;
   p.nt = ldc % 32 == 0 && (((uintptr_t)C_i32 | (uintptr_t)C_f32) & 127) == 0;
   p.HoWo = p.Wo = p.Hp = p.Wpp = p.Cw = p.stride = 1;
+  p.Nimg = p.Ho = p.opad = p.oHp = p.oWp = p.oCw = 0;
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
@@ -882,8 +963,8 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
 // The convolution on the same kernel (Xp, Wp as for launch_binary_conv2d).  Takes the problem when
 // the filter rows are 16-byte aligned, and image and output fit 32-bit offsets.
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
-                     int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s,
-                     hipError_t* err) {
+                     int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits,
+                     const float* thr, int out_pad, hipStream_t s, hipError_t* err) {
   if (gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
   const int Ho = (H + 2 * pad - KH) / stride + 1;
   const int Wo = (W + 2 * pad - KW) / stride + 1;
@@ -898,6 +979,8 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= ((int64_t)1 << 32) || (int64_t)O * ld_words * 8 >= ((int64_t)1 << 32))
     return false;
   if (P >= ((int64_t)1 << 31) || ((int64_t)Nimg * O + 64) * Ho * Wo >= ((int64_t)1 << 31)) return false;
+  // (the halo's words are counted, and every word of the image addressed, in 32 bits)
+  if (out_bits && (int64_t)Nimg * (Ho + 2 * out_pad) * (Wo + 2 * out_pad) * words_for(O) >= ((int64_t)1 << 30)) return false;
   const int tiles_m = (int)ceil_div(O, 64), tiles_n = (int)ceil_div(P, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   if (tiles >= ((int64_t)1 << 28)) return false;
@@ -916,13 +999,19 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   p.tiles_n = tiles_n;
   set_tile_order(p);
   p.alpha = alpha;
-  p.thr = nullptr;
+  p.thr = thr;
   p.rowsum = nullptr;
   p.levels = 1.0f;
   p.as_count = 0;
   p.C_i32 = out_i32;
   p.C_f32 = out_f32;
-  p.C_bits = nullptr;
+  p.C_bits = (uint32_t*)out_bits;
+  p.Nimg = Nimg;
+  p.Ho = Ho;
+  p.opad = out_pad;
+  p.oHp = Ho + 2 * out_pad;
+  p.oWp = Wo + 2 * out_pad;
+  p.oCw = (int)words_for(O);
   p.ldc = 0;
   p.nt = Ho * Wo % 32 == 0 && (((uintptr_t)out_i32 | (uintptr_t)out_f32) & 127) == 0;
   p.HoWo = Ho * Wo;
@@ -948,7 +1037,9 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, 1>(p, S, tiles_per_wg, blocks, s);
+  if (out_bits) *err = reg ? launch_split<1, true, kOutBits, true, 1>(p, S, tiles_per_wg, blocks, s)
+                           : launch_split<1, true, kOutBits, true>(p, S, tiles_per_wg, blocks, s);
+  else if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, 1>(p, S, tiles_per_wg, blocks, s);
   else if (reg) *err = launch_split<1, true, kOutF32, true, 1>(p, S, tiles_per_wg, blocks, s);
   else if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
   else *err = launch_split<1, true, kOutF32, true>(p, S, tiles_per_wg, blocks, s);

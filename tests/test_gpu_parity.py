@@ -1373,6 +1373,43 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("form", [1, 2, 3])
+@pytest.mark.parametrize("N,C,H,W,O,k,s,p,opad", [
+    (1, 1, 1, 1, 1, 1, 1, 0, 0),        # one word, one pixel
+    (2, 500, 9, 8, 65, 1, 1, 0, 1),     # whole segment, a filter past the tile
+    (3, 130, 13, 11, 129, 3, 1, 1, 1),  # odd number of channel words, three segments and a half
+    (2, 384, 14, 10, 128, 3, 2, 1, 2),  # even, stride 2
+    (5, 300, 8, 7, 63, 5, 1, 2, 0),     # many segments, images that end inside a tile
+    (1, 640, 23, 24, 200, 3, 1, 0, 1),  # several tiles each way
+    (9, 70, 9, 8, 31, 7, 1, 3, 3),      # halo as wide as the image's rest
+    (4, 256, 16, 16, 64, 1, 1, 0, 6)])
+def test_conv_long_k_kernels(form, N, C, H, W, O, k, s, p, opad):
+    """Convolutions of packed images on the kernels for long K, whatever the size: rows staged once per workgroup (2: 128
+    filters x 128 pixels, 3: 64 x 256), and 64 x 64 per wave (1; with and without K divided).  fp32, int32, and the next
+    convolution's image with its halo, thresholds and negative scales included."""
+    rng = np.random.default_rng(N + C + H + O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha, thr = rng.standard_normal(O).astype(np.float32), (rng.standard_normal(O) * np.sqrt(C) * k).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    xp, Wp = B.pack_nchw(dev(x), p), B.pack_conv_weights(dev(w))
+    ref = np.where(rf >= thr[None, :, None, None], np.float32(1), np.float32(-1))
+    want = B.pack_nchw(dev(ref), opad)
+    for split in ((0, 1, 3, 8) if form == 1 else (0,)):
+        pins = dict(k18=1, k5=6, k10=split) if form == 1 else dict(k18=1, k20=form)
+        with tuned(**pins):
+            np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
+            assert "gemm_fp4_kernel" in B.last_kernel() and ("block" in B.last_kernel()) == (form > 1)
+            np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
+            if form > 1 or k * k * -(-C // 64) not in (9, 18, 25, 27, 36, 49, 50):  # (those words' kernel writes the image itself)
+                out = torch.full_like(want, -1)
+                B.binary_conv2d_bits(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha), thr=dev(thr), out_pad=opad, out=out)
+                assert "gemm_fp4_kernel" in B.last_kernel() and "bits" in B.last_kernel()
+                assert torch.equal(out, want)
+    if k > 1:  # images of one row and one column of padding more, on the general route
+        with tuned(k5=3):
+            assert torch.equal(B.binary_conv2d_bits(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha), thr=dev(thr), out_pad=opad), want)
+
+
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,opad", [
     (1, 1, 1, 1, 1, 1, 1, 0, 0), (3, 300, 5, 7, 33, 1, 2, 0, 2), (2, 128, 9, 8, 70, 3, 1, 1, 1), (2, 131, 6, 5, 32, 3, 2, 2, 0), (1, 70, 8, 9, 95, 5, 1, 4, 3),
     (5, 64, 7, 7, 64, 7, 1, 3, 1), (2, 260, 6, 11, 129, 3, 1, 1, 6), (1, 512, 9, 9, 31, 7, 2, 6, 1), (40, 200, 12, 13, 100, 3, 1, 0, 1), (9, 50, 40, 41, 64, 1, 1, 0, 1)])

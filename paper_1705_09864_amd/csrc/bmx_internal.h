@@ -183,7 +183,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
 bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
                        int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits, const float* thr,
                        int out_pad, hipStream_t s, hipError_t* err);
-// Estimated time of a convolution of 8 words and more by launch_conv_block or launch_conv_fp4, launch and fixed phases aside;
+// Estimated time of a convolution of 8 words and more by launch_conv_block or launch_conv_fp4 in us;
 // form: launch_conv_block's choice, 0 for launch_conv_fp4.
 double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form);
 extern int gemm_block, conv_block;

@@ -543,16 +543,20 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
 
 int conv_block = 0;  // 1 = never, 2 = 128 filters x 128 pixels and 3 = 64 x 256 per workgroup whatever the size
 
-// Fitted to 110 convolutions of 45 to 392 words measured on each (fp32 results; the choice by it is 0.3 % off the best):
-// us per word of K.  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
-// through registers (an odd number of channel words).  Here by workgroups per CU; one alone leaves every SIMD one wave, which
-// is half as fast as two.
+// Fitted to 169 convolutions of 45 to 392 words measured on each (us, fp32 results; the choice by it is 0.5 % off the best,
+// 17 % at most).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
+// through registers (an odd number of channel words).  Here by workgroups per CU; one alone on a CU takes more than half as
+// long for a segment as two together.
 double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
-  const double there = (any_dword ? 0.06 : 0.042) * (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
-  auto here = [&](int64_t wgs) { return 0.1 * (any_dword ? 1.1 : 1.0) * std::max(1.6, (double)ceil_div(wgs, 256)); };
-  const double high = here(ceil_div(P, 128) * ceil_div(O, 128)), wide = here(ceil_div(P, 256) * ceil_div(O, 64));
-  *form = std::min(high, wide) >= there ? 0 : high <= wide ? 2 : 3;
-  return kwords * std::min(there, std::min(high, wide));
+  const double K = kwords;
+  const double n = (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
+  const double high = (double)ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256), mh = std::max(1.6, high);
+  const double wide = (double)ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256), mw = std::max(1.6, wide);
+  const double there = any_dword ? 4.9 + n * (1.0 + 0.0285 * K) : 4.4 + n * (1.0 + 0.0245 * K);
+  const double us2 = any_dword ? 3.8 + 2.1 * high + 0.080 * mh * K : 2.4 + 3.2 * high + 0.063 * mh * K;
+  const double us3 = any_dword ? 3.9 + 1.9 * wide + 0.0945 * mw * K : 0.7 + 4.5 * wide + 0.066 * mw * K;
+  *form = std::min(us2, us3) >= there ? 0 : us2 <= us3 ? 2 : 3;
+  return std::min(there, std::min(us2, us3));
 }
 
 bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,

@@ -210,7 +210,7 @@ int bmx_binarize_pack(const float* x, int64_t rows, int64_t cols, int64_t ldx, i
   hipStream_t s = (hipStream_t)stream;
   if (pack_dim)
     return hip_status(bmx::launch_pack_rows(x, rows, cols, ldx, out, out_ld_words, s));
-  return hip_status(bmx::launch_pack_strided(x, 1, rows, cols, ldx, 0, out, out_ld_words, s));
+  return hip_status(bmx::launch_pack_strided(x, rows, cols, ldx, out, out_ld_words, s));
 }
 
 int bmx_unpack_pm1(const uint64_t* bits, int64_t rows, int64_t K, int64_t ld_words, float* out,

@@ -103,16 +103,14 @@ __host__ __device__ static inline int64_t conv_weight_row_words(int64_t kwords) 
 // Row pack: out[r][w] bit j = (x[r*ldx + 64w + j] >= 0), K contiguous in x.
 hipError_t launch_pack_rows(const float* x, int64_t rows, int64_t cols, int64_t ldx, uint64_t* out,
                             int64_t out_ld, hipStream_t s);
-// Strided pack of `batch` matrices stored [K][ncol] (row stride ldx, matrix stride
-// batch_stride): out[b][n][w] bit j = (x[b][64w + j][n] >= 0); out row stride out_ld,
-// matrix stride ncol*out_ld.  Serves pack_dim = 0 and the NCHW channel pack.
 hipError_t launch_unpack_pm1(const uint64_t* bits, int64_t rows, int64_t K, int64_t ld_words, float* out,
                              int64_t ldo, hipStream_t s);
 // Rows of ceil(K/32) 32-bit words, ld_dw apart -> rows of ceil(K/64) 64-bit words, out_ld apart.
 hipError_t launch_widen_words32(const uint32_t* in, int64_t rows, int64_t K, int64_t ld_dw, uint64_t* out,
                                 int64_t out_ld, hipStream_t s);
-hipError_t launch_pack_strided(const float* x, int64_t batch, int64_t K, int64_t ncol, int64_t ldx,
-                               int64_t batch_stride, uint64_t* out, int64_t out_ld, hipStream_t s);
+// Pack down the columns of x [K][ncol] (rows ldx apart): out[n][w] bit j = (x[64w + j][n] >= 0).
+hipError_t launch_pack_strided(const float* x, int64_t K, int64_t ncol, int64_t ldx, uint64_t* out, int64_t out_ld,
+                               hipStream_t s);
 // NCHW channel pack into the halo-padded layout xp [N][H+2*pad][W+2*pad][Cw]; the halo is
 // filled with the word "all real channels = +1".
 // (thr: per-channel threshold the value is compared with, null = 0)

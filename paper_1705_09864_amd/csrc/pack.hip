@@ -13,13 +13,10 @@ static constexpr int kWave = 64;
 // <-> k, so every load instruction is a 256-byte coalesced read and the 64-lane compare
 // mask is the packed word itself.  All 16 loads of a segment are issued before the first
 // compare.  A workgroup owns one contiguous stretch of the segment list (its four waves
-// interleave inside it).  Inputs larger than the memory-side cache are read with non-temporal
-// loads and 32-word segments: on a 2 GiB read, contiguous stretches + non-temporal loads
-// measured 7.0 TB/s against 5.3-5.8 TB/s for cached loads walking the list with a grid stride;
-// on inputs that fit the caches (activations from the previous layer) the same loads lose.
+// interleave inside it).
 constexpr int kSegWords = 16;
 
-template <int kSegWords, bool NT>
+template <bool NT>
 __device__ __forceinline__ void pack_row_segments(const float* __restrict__ x, int64_t rows,
                                                   int64_t cols, int64_t ldx,
                                                   uint64_t* __restrict__ out, int64_t out_ld,
@@ -56,34 +53,35 @@ __device__ __forceinline__ void pack_row_segments(const float* __restrict__ x, i
   }
 }
 
-template <int SEG, bool NT>
+template <bool NT>
 __global__ void __launch_bounds__(256)
 pack_rows_kernel(const float* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
                  uint64_t* __restrict__ out, int64_t out_ld, int64_t Kw, int64_t segs_per_row,
                  int64_t segs_per_block) {
-  pack_row_segments<SEG, NT>(x, rows, cols, ldx, out, out_ld, Kw, segs_per_row, (int64_t)blockIdx.x,
-                             segs_per_block);
+  pack_row_segments<NT>(x, rows, cols, ldx, out, out_ld, Kw, segs_per_row, (int64_t)blockIdx.x,
+                        segs_per_block);
 }
+
+// Matrices past this many bytes are read with the streaming hint: they would not stay in the L2s (4 MB on each of 8
+// XCDs), and what they push out on the way costs more.  Row pack and alpha_mean_abs of 44 to 103 MB level or 10 %
+// faster so, from HBM and on a second reading; 43 MB level, 37 MB 7.1 us instead of 5.8 on the second.
+constexpr int64_t kStreamBytes = 48 << 20;
 
 static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, int64_t ldx,
                                   uint64_t* out, int64_t out_ld, int64_t words_per_row,
                                   hipStream_t s) {
-  const int64_t cap = 256 * 8;  // 8 workgroups of 4 waves per CU
-  if (rows * cols * 4 > ((int64_t)256 << 20)) {  // beyond the 256 MB memory-side cache
-    const int64_t spr = ceil_div(words_per_row, 32);
-    int64_t blocks = ceil_div(rows * spr, 4);
-    blocks = blocks < cap ? blocks : cap;
-    note_kernel("pack_rows_kernel<32,nontemporal> grid %lld x 256", (long long)blocks);
-    launch_kernel((pack_rows_kernel<32, true>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols, ldx,
-                       out, out_ld, words_per_row, spr, ceil_div(rows * spr, blocks));
-    return;
-  }
+  // A wave per segment, in a grid of them all: waves that went on to their next segment (2048 workgroups) asked for it
+  // only once they had the last (4096 x 9216 from HBM 29.9 us and now 24.1, 2 GiB 380 and 344: 6.2 TB/s).
   const int64_t spr = ceil_div(words_per_row, kSegWords);
-  int64_t blocks = ceil_div(rows * spr, 4);
-  blocks = blocks < cap ? blocks : cap;
-  note_kernel("pack_rows_kernel<16,cached> grid %lld x 256", (long long)blocks);
-  launch_kernel((pack_rows_kernel<kSegWords, false>), dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols,
-                     ldx, out, out_ld, words_per_row, spr, ceil_div(rows * spr, blocks));
+  const int64_t blocks = std::min<int64_t>(ceil_div(rows * spr, 4), 1 << 22);
+  const bool nt = rows * cols * 4 > kStreamBytes;
+  note_kernel("pack_rows_kernel<%s> grid %lld x 256", nt ? "nontemporal" : "cached", (long long)blocks);
+  auto go = [&](auto kern) {
+    launch_kernel(kern, dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols, ldx, out, out_ld, words_per_row, spr,
+                  ceil_div(rows * spr, blocks));
+  };
+  if (nt) go(pack_rows_kernel<true>);
+  else go(pack_rows_kernel<false>);
 }
 
 hipError_t launch_pack_rows(const float* x, int64_t rows, int64_t cols, int64_t ldx, uint64_t* out,
@@ -159,53 +157,75 @@ hipError_t launch_widen_words32(const uint32_t* in, int64_t rows, int64_t K, int
   return launch_error();
 }
 
-// Strided pack (the matrix is stored K x ncol, pack down the columns): a wave packs one
-// word of 64 consecutive columns: lanes span columns, so every load instruction is a
-// coalesced 256-byte read of one K row, and all 64 row loads of a lane are issued before
-// the first compare.  The word is assembled in two 32-bit halves.
-__global__ void __launch_bounds__(256)
-pack_strided_kernel(const float* __restrict__ x, int64_t batch, int64_t K, int64_t ncol,
-                    int64_t ldx, int64_t batch_stride, uint64_t* __restrict__ out, int64_t out_ld,
-                    int64_t Kw, int64_t col_groups) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  const int64_t total = batch * Kw * col_groups;
-  for (int64_t item = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
-       item < total; item += nwaves) {
-    const int64_t g = item % col_groups;
-    const int64_t t = item / col_groups;
-    const int64_t w = t % Kw;
-    const int64_t b = t / Kw;
-    const int64_t n = g * 64 + lane;
-    const int64_t nc = n < ncol ? n : ncol - 1;
-    const float* xb = x + b * batch_stride + (w * 64) * ldx + nc;
-    const int64_t kmax = K - w * 64;  // rows left in this word (>= 1)
-    float v[64];
-    if (kmax >= 64) {
+// Strided pack (the matrix is stored K x ncol, pack down the columns): a workgroup packs 64 columns of two words.  Each
+// wave takes 16 rows (lanes span columns: a load is 256 bytes of a row, all 16 in flight) and leaves 16 bits per
+// column in LDS; a column's two words are stored by neighbouring lanes.  Bound by the matrix's way in.  Where rows are no
+// whole 128-byte lines the tiles beside each other share them: they are dealt to one XCD then, so that the second
+// finds them in its L2, an eighth of the matrix each (ORDER kEighths) or, in a matrix that passes through, eight tiles at a
+// time (kEights: XCDs at work an eighth of 9215 x 4095 apart meet in the same memory channels).
+// With a wave per word, all 64 rows in its registers, and now, us a launch, from HBM: 9000 x 100 4.7 and 2.7, 300 x 4000
+// 5.3 and 2.8, 3237 x 1338 7.5 and 4.9, 2944 x 3651 12.2 and 8.5 (5.1 TB/s), 8000 x 4001 29.0 and 23.7, 4096 x 9216
+// 31.9 and 25.0 (6.0 TB/s).  Plain order, kEighths, kEights: 2944 x 3651 11.3, 8.5, 9.0; 8000 x 4001 32.3, 26.1, 23.7;
+// 9215 x 4095 33.9, 31.9, 29.2; whole lines, 9216 x 4096, without the hint 28.4, 31.8, 27.6.  16 bytes a load on any
+// dword, 256 columns a workgroup: 17.4 for 2944 x 3651.
+enum { kPlain, kEighths, kEights };
+
+template <int ORDER, bool NT>
+__global__ void __launch_bounds__(512)
+pack_strided_kernel(const float* __restrict__ x, int64_t K, int64_t ncol, int64_t ldx, uint64_t* __restrict__ out,
+                    int64_t out_ld, int64_t Kw, uint32_t total, FastDiv div_groups, uint32_t groups) {
+  constexpr int kWords = 2, kRows = 16;
+  __shared__ __align__(8) uint16_t bits[64][4 * (kWords + 1)];  // (+1: other banks)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    // workgroups b, b + 8, ... run on one XCD
+    const uint32_t xcd = b & 7;
+    uint32_t tile = b;
+    if (ORDER == kEighths) tile = xcd * (total / 8) + min(xcd, total % 8) + b / 8;
+    if (ORDER == kEights && b < total / 64 * 64) tile = b / 64 * 64 + xcd * 8 + b / 8 % 8;
+    const uint32_t band = fast_div(tile, div_groups);
+    const int64_t n0 = (int64_t)(tile - band * groups) * 64, w0 = (int64_t)band * kWords;
+    const int64_t k0 = w0 * 64 + wave * kRows, left = K - k0;  // rows of this wave
+    const float* const at = x + min(n0 + lane, ncol - 1);
+    float v[kRows];
+    if (left >= kRows) {
 #pragma unroll
-      for (int j = 0; j < 64; ++j) v[j] = xb[(int64_t)j * ldx];
+      for (int j = 0; j < kRows; ++j) v[j] = NT ? __builtin_nontemporal_load(at + (k0 + j) * ldx) : at[(k0 + j) * ldx];
     } else {
 #pragma unroll
-      for (int j = 0; j < 64; ++j) v[j] = (j < kmax) ? xb[(int64_t)j * ldx] : -1.0f;
+      for (int j = 0; j < kRows; ++j) v[j] = j < left ? at[(k0 + j) * ldx] : -1.0f;
     }
-    uint32_t lo = 0, hi = 0;
+    uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) lo |= (v[j] >= 0.0f ? 1u : 0u) << j;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) hi |= (v[32 + j] >= 0.0f ? 1u : 0u) << j;
-    if (n < ncol) out[(b * ncol + n) * out_ld + w] = ((uint64_t)hi << 32) | lo;
+    for (int j = 0; j < kRows; ++j) mine |= (v[j] >= 0.0f ? 1u : 0u) << j;
+    bits[lane][wave] = (uint16_t)mine;
+    __syncthreads();
+    if (threadIdx.x < 64 * kWords) {
+      const int c = threadIdx.x / kWords, w = threadIdx.x % kWords;
+      uint64_t word;
+      __builtin_memcpy(&word, __builtin_assume_aligned(&bits[c][4 * w], 8), 8);
+      if (n0 + c < ncol && w0 + w < Kw) out[(n0 + c) * out_ld + w0 + w] = word;
+    }
+    __syncthreads();
   }
 }
 
-hipError_t launch_pack_strided(const float* x, int64_t batch, int64_t K, int64_t ncol, int64_t ldx,
-                               int64_t batch_stride, uint64_t* out, int64_t out_ld, hipStream_t s) {
+hipError_t launch_pack_strided(const float* x, int64_t K, int64_t ncol, int64_t ldx, uint64_t* out, int64_t out_ld,
+                               hipStream_t s) {
   const int64_t Kw = words_for(K);
-  const int64_t groups = ceil_div(ncol, 64);
-  const int64_t blocks = ceil_div(batch * Kw * groups, 4);
-  const int64_t cap = 256 * 6;  // the kernel holds 64 loaded values per lane: 6 waves per SIMD
-  note_kernel("pack_strided_kernel grid %lld x 256", (long long)(blocks < cap ? blocks : cap));
-  launch_kernel(pack_strided_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(256), 0,
-                     s, x, batch, K, ncol, ldx, batch_stride, out, out_ld, Kw, groups);
+  const uint32_t groups = (uint32_t)ceil_div(ncol, 64), total = groups * (uint32_t)ceil_div(Kw, 2);
+  const uint32_t blocks = std::min<uint32_t>(total, 1u << 22);
+  const bool lines = ldx % 32 == 0 && (uintptr_t)x % 128 == 0;
+  const bool large = K * ncol * 4 > kStreamBytes;
+  note_kernel("pack_strided_kernel<%s> grid %u x 512", lines ? "lines" : "per XCD", blocks);
+  const FastDiv div = make_fast_div(groups);
+  auto go = [&](auto kern) {
+    launch_kernel(kern, dim3(blocks), dim3(512), 0, s, x, K, ncol, ldx, out, out_ld, Kw, total, div, groups);
+  };
+  if (lines && large) go(pack_strided_kernel<kPlain, true>);
+  else if (lines) go(pack_strided_kernel<kPlain, false>);
+  else if (large) go(pack_strided_kernel<kEights, false>);
+  else go(pack_strided_kernel<kEighths, false>);
   return launch_error();
 }
 
@@ -382,20 +402,94 @@ pack_conv_weights_kernel(const float* __restrict__ w, int C, int Cw, int ld, int
   }
 }
 
+// The same for 25 and 49 taps, where that is long for a wave: 49 loads, 49 ways through LDS and 49 ballots in a chain.  A
+// workgroup per filter and 64 channels (per filter where a constant has to be added up over its words); the floats
+// come 16 bytes at a time, on any dword since a filter starts anywhere, at most four a thread, and the four waves share the
+// taps.  Bound by the launch to some 4 MB of weights, past that by the way in.  Before and now, us a call of which 3.8
+// are the call: 432 x 10 x 7 x 7 6.65 and 4.4, 64 x 512 x 7 x 7 10.2 and 4.3, 294 x 461 x 7 x 7 (25 MB) 12.3 and 7.1,
+// 512 x 512 x 7 x 7 (51 MB) 15.7 and 11.7, 512 x 512 x 5 x 5 7.0 and 6.2.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v4f_lds __attribute__((ext_vector_type(4), may_alias));
+
+template <int T>
+__global__ void __launch_bounds__(256)
+pack_conv_taps_kernel(const float* __restrict__ w, uint32_t total, int C, int Cw, int ld, int ldb, int consts,
+                      int parts, FastDiv div_parts, uint64_t* __restrict__ Wp) {
+  constexpr int kVec = 16 * T, kLoads = (kVec + 255) / 256, kTaps = (T + 3) / 4;
+  __shared__ v4f_lds stage[kVec];
+  __shared__ int ones[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, last = C * T - 1;
+  for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    const uint32_t o = fast_div(b, div_parts);
+    const int part = (int)(b - o * (uint32_t)parts);
+    const float* const wo = w + (int64_t)o * C * T;
+    uint64_t* const row = Wp + (int64_t)o * ld;
+    int pc = 0;
+    for (int cw = part; cw < Cw; cw += parts) {
+      const int first = cw * 64 * T;
+      v4f_any v[kLoads];
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int i = first + 4 * min(256 * j + (int)threadIdx.x, kVec - 1);
+        if (i + 3 <= last) {
+          v[j] = *(const v4f_any*)(wo + i);
+        } else {  // (behind the filter: its last value, masked below)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[j][e] = wo[min(i + e, last)];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j)
+        if (256 * j + (int)threadIdx.x < kVec) stage[256 * j + threadIdx.x] = v[j];
+      __syncthreads();
+      const bool real = cw * 64 + lane < C;  // channels past the last are 0 bits
+      const float* const at = (const float*)stage + lane * T + wave;
+      uint64_t mine = 0;
+#pragma unroll
+      for (int u = 0; u < kTaps; ++u) {
+        const bool tap = 4 * u + wave < T;
+        const uint64_t word = __ballot(real && tap && at[tap ? 4 * u : 0] >= 0.0f);
+        if (lane == u) mine = word;
+      }
+      if (lane < kTaps && 4 * lane + wave < T) row[(4 * lane + wave) * Cw + cw] = mine;
+      pc += __popcll(mine);
+      __syncthreads();
+    }
+    if (part == 0)
+      for (int j = T * Cw + threadIdx.x; j < ldb; j += 256) row[j] = 0;
+    if (!consts) continue;  // (workgroup-uniform)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) pc += __shfl_xor(pc, off);
+    if (lane == 0) ones[wave] = pc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      row[ldb] = __float_as_uint((float)(C * T - 2 * (ones[0] + ones[1] + ones[2] + ones[3])));
+      row[ldb + 1] = 0;
+    }
+    __syncthreads();
+  }
+}
+
 hipError_t launch_pack_conv_weights(const float* w, int O, int C, int KH, int KW, uint64_t* Wp,
                                     hipStream_t s) {
   const int Cw = (int)words_for(C);
   const int kwords = KH * KW * Cw;
   const int ld = (int)conv_weight_row_words(kwords), ldb = (int)conv_weight_bits_words(kwords);
   const int consts = conv_weight_short_k(kwords) ? 1 : 0;
-  const dim3 grid((unsigned)O), block(64 * (Cw < kPackConvWaves ? Cw : kPackConvWaves));
-  auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, s, w, C, Cw, ld, ldb, consts, Wp); };
-  switch (KH * KW) {
-    case 1: go(pack_conv_weights_kernel<1>); break;
-    case 9: go(pack_conv_weights_kernel<9>); break;
-    case 25: go(pack_conv_weights_kernel<25>); break;
-    default: go(pack_conv_weights_kernel<49>); break;
+  if (KH * KW <= 9) {
+    const dim3 grid((unsigned)O), block(64 * (Cw < kPackConvWaves ? Cw : kPackConvWaves));
+    auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, s, w, C, Cw, ld, ldb, consts, Wp); };
+    if (KH * KW == 1) go(pack_conv_weights_kernel<1>);
+    else go(pack_conv_weights_kernel<9>);
+    return launch_error();
   }
+  const int parts = consts ? 1 : Cw;
+  const uint32_t total = (uint32_t)O * (uint32_t)parts;  // (2^32 of them would be 800 GB of packed filters)
+  const dim3 grid(std::min<uint32_t>(total, 1u << 20));
+  const FastDiv div = make_fast_div((uint32_t)parts);
+  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, s, w, total, C, Cw, ld, ldb, consts, parts, div, Wp); };
+  if (KH * KW == 25) go(pack_conv_taps_kernel<25>);
+  else go(pack_conv_taps_kernel<49>);
   return launch_error();
 }
 
@@ -421,51 +515,39 @@ hipError_t launch_quant_combine(const int32_t* T, int64_t M, int64_t N, int bw, 
   return launch_error();
 }
 
-// alpha[r] = mean |w[r][:]| in fp64: a wave (many rows) or a workgroup (few) per row, eight loads per
-// lane in flight, 16 bytes each where every row starts 16-byte aligned.  Bound by the way in of the
-// weights; with one 4-byte load in flight per lane 4096 x 9216 took 36 us, now 24 us (6.3 TB/s).
-template <int WAVES, bool V4>
+// alpha[r] = mean |w[r][:]| in fp64: a wave or a workgroup of four per row, nine loads per lane in flight, 16 bytes
+// each, on any dword: rows of 4n + 1 values start anywhere.  Bound by the way in of the weights.  Before and now, us a
+// call: 4096 x 9215 48.9 (4-byte loads) and 22.8, 294 x 22589 17.3 (eleven trips to memory in a chain) and 4.6, 1000 x
+// 9215 14.1 and 5.9; the kernel at 4096 x 9216 from HBM 27.2 (a wave per row, kept in the caches) and 23.7 (6.4 TB/s).
+template <int WAVES, bool NT>
 __global__ void __launch_bounds__(256)
 alpha_mean_abs_kernel(const float* __restrict__ w, int64_t rows, int64_t cols, int64_t ldw,
                       float* __restrict__ alpha) {
-  __shared__ double part[4];
-  constexpr int kAhead = 8, kVec = V4 ? 4 : 1, kLanes = 64 * WAVES;
+  __shared__ double part[WAVES];
+  constexpr int kAhead = 9, kLanes = 64 * WAVES, kRows = 4 / WAVES;  // rows a workgroup
   const int t = threadIdx.x & (kLanes - 1);
-  const int64_t nvec = cols / kVec;
-  for (int64_t r0 = (int64_t)blockIdx.x * (4 / WAVES); r0 < rows; r0 += (int64_t)gridDim.x * (4 / WAVES)) {
+  const int64_t nvec = cols / 4;
+  for (int64_t r0 = (int64_t)blockIdx.x * kRows; r0 < rows; r0 += (int64_t)gridDim.x * kRows) {
     const int64_t r = r0 + (int)(threadIdx.x / kLanes);
     double acc0 = 0.0, acc1 = 0.0;
     if (r < rows) {
       const float* x = w + r * ldw;
+      const float rest = 4 * nvec + t < cols ? x[4 * nvec + t] : 0.f;  // (the last one to three values)
       for (int64_t i0 = 0; i0 < nvec; i0 += kAhead * kLanes) {
-        if constexpr (V4) {
-          float4 v[kAhead];
+        v4f_any v[kAhead];
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
-            const int64_t i = i0 + j * kLanes + t;
-            v[j] = i < nvec ? ((const float4*)x)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-          }
+        for (int j = 0; j < kAhead; ++j) {
+          const int64_t i = i0 + j * kLanes + t;
+          if (i < nvec) v[j] = NT ? __builtin_nontemporal_load((const v4f_any*)x + i) : ((const v4f_any*)x)[i];
+          else v[j] = v4f_any{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
-            acc0 += fabs((double)v[j].x) + fabs((double)v[j].y);
-            acc1 += fabs((double)v[j].z) + fabs((double)v[j].w);
-          }
-        } else {
-          float v[kAhead];
-#pragma unroll
-          for (int j = 0; j < kAhead; ++j) {
-            const int64_t i = i0 + j * kLanes + t;
-            v[j] = i < nvec ? x[i] : 0.f;
-          }
-#pragma unroll
-          for (int j = 0; j < kAhead; j += 2) {
-            acc0 += fabs((double)v[j]);
-            acc1 += fabs((double)v[j + 1]);
-          }
+        for (int j = 0; j < kAhead; ++j) {
+          acc0 += fabs((double)v[j].x) + fabs((double)v[j].y);
+          acc1 += fabs((double)v[j].z) + fabs((double)v[j].w);
         }
       }
-      if (V4 && t == 0)
-        for (int64_t i = 4 * nvec; i < cols; ++i) acc0 += fabs((double)x[i]);
+      acc0 += fabs((double)rest);
     }
     double acc = acc0 + acc1;
 #pragma unroll
@@ -475,7 +557,12 @@ alpha_mean_abs_kernel(const float* __restrict__ w, int64_t rows, int64_t cols, i
     } else {
       if ((t & 63) == 0) part[t >> 6] = acc;
       __syncthreads();
-      if (t == 0) alpha[r] = (float)(((part[0] + part[1]) + (part[2] + part[3])) / (double)cols);
+      if (t == 0) {
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) sum += part[i];
+        alpha[r] = (float)(sum / (double)cols);
+      }
       __syncthreads();
     }
   }
@@ -483,13 +570,16 @@ alpha_mean_abs_kernel(const float* __restrict__ w, int64_t rows, int64_t cols, i
 
 hipError_t launch_alpha_mean_abs(const float* w, int64_t rows, int64_t cols, int64_t ldw,
                                  float* alpha, hipStream_t s) {
-  const bool v4 = (ldw & 3) == 0 && ((uintptr_t)w & 15) == 0;
-  // a wave per row once that gives every SIMD two; below, four waves share a row
-  const bool one = rows >= 2048;
-  const int64_t blocks = std::min<int64_t>(one ? ceil_div(rows, 4) : rows, 65535 * 16);
-  auto go = [&](auto kern) { launch_kernel(kern, dim3((unsigned)blocks), dim3(256), 0, s, w, rows, cols, ldw, alpha); };
-  if (one) v4 ? go(alpha_mean_abs_kernel<1, true>) : go(alpha_mean_abs_kernel<1, false>);
-  else v4 ? go(alpha_mean_abs_kernel<4, true>) : go(alpha_mean_abs_kernel<4, false>);
+  // A wave per row where it takes the row in one trip, or two with rows enough to hide them (1338 x 3237 3.4 us with
+  // one wave, 3.8 with four; 2048 x 4096 3.6 and 4.5, 512 x 4900 3.3 and 2.9, 1276 x 8576 8.8 and 7.9).
+  const bool one = cols <= 2304 || (cols <= 4096 && rows >= 1024);
+  const bool nt = rows * cols * 4 > kStreamBytes;
+  const dim3 grid((unsigned)std::min<int64_t>(one ? ceil_div(rows, 4) : rows, 65535 * 16));
+  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(256), 0, s, w, rows, cols, ldw, alpha); };
+  if (one && nt) go(alpha_mean_abs_kernel<1, true>);
+  else if (one) go(alpha_mean_abs_kernel<1, false>);
+  else if (nt) go(alpha_mean_abs_kernel<4, true>);
+  else go(alpha_mean_abs_kernel<4, false>);
   return launch_error();
 }
 
@@ -509,7 +599,7 @@ quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda
   __shared__ int32_t part[4];
   if ((int64_t)blockIdx.x >= M) {
     const int64_t Kw = words_for(K);
-    pack_row_segments<kSegWords, false>(w, wrows, K, ldw, wbits, wb_ld, Kw, ceil_div(Kw, kSegWords),
+    pack_row_segments<false>(w, wrows, K, ldw, wbits, wb_ld, Kw, ceil_div(Kw, kSegWords),
                       (int64_t)blockIdx.x - M, wsegs_per_block);
     return;
   }

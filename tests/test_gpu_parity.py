@@ -462,6 +462,44 @@ def test_alpha_mean_abs(rows, cols):
     assert_f32_close(B.alpha_mean_abs(dev(w)).cpu().numpy(), oracle.alpha_mean_abs(w))
 
 
+@pytest.mark.parametrize("rows,cols", [(5, 3), (1023, 2305), (1024, 4096), (7, 2303), (3, 9217), (2, 25086), (1230, 10243), (3100, 4095)])
+def test_alpha_and_row_pack_any_start(rows, cols):
+    """Rows that start on any dword, with a wave and with four per row, one trip and several, the sizes on both sides of what is
+    read with the streaming hint (50 MB).  alpha against the mean in 64 bits: its own sum is one, so half an ulp of float is left."""
+    w = torch.rand(rows * cols + 1, device="cuda")[1:].sub_(0.5).view(rows, cols)
+    host = w.cpu().numpy()
+    np.testing.assert_allclose(B.alpha_mean_abs(w).cpu().numpy(), np.abs(host.astype(np.float64)).mean(axis=1), rtol=2.0 ** -24 * 1.01, atol=0)
+    np.testing.assert_array_equal(host_u64(B.binarize_pack(w, 1)), oracle.binarize_pack(host, 1))
+
+
+@pytest.mark.parametrize("K,cols,start", [(1, 1, 0), (15, 64, 0), (16, 65, 0), (17, 96, 1), (64, 63, 0), (65, 130, 3), (128, 1024, 0), (129, 1024, 1),
+                                          (191, 320, 0), (1000, 515, 2), (3150, 4096, 0), (3150, 4100, 0)])
+def test_pack_down_columns_tiles(K, cols, start):
+    """Pack down the columns: rests of rows, words and columns, rows of whole 128-byte lines (below and above the size of the
+    streaming hint) and tiles dealt out per XCD."""
+    x = torch.rand(K * cols + start, device="cuda")[start:].sub_(0.5).view(K, cols)
+    np.testing.assert_array_equal(host_u64(B.binarize_pack(x, 0)), oracle.binarize_pack(x.cpu().numpy(), 0))
+
+
+@pytest.mark.parametrize("O,C,k", [(1, 1, 5), (3, 64, 5), (2, 65, 5), (5, 128, 5), (2, 129, 5), (70, 321, 5), (1, 1, 7), (3, 64, 7), (2, 65, 7), (9, 191, 7), (70, 449, 7)])
+def test_conv_weight_pack_many_taps(O, C, k):
+    """25 and 49 taps: channels around whole words, filters that start on any dword, one workgroup per filter (25, 49 and 50
+    words, with their constant) and one per 64 channels."""
+    w = torch.rand(O * C * k * k + 1, device="cuda")[1:].sub_(0.5).view(O, C, k, k)
+    host = w.cpu().numpy()
+    Wp, kwords = host_u64(B.pack_conv_weights(w)), k * k * ((C + 63) // 64)
+    ref = oracle.binarize_pack(np.transpose(host, (0, 2, 3, 1)).reshape(O * k * k, C), 1).reshape(O, kwords)
+    np.testing.assert_array_equal(Wp[:, :kwords], ref)
+    short = kwords in (25, 49, 50)
+    ldb = Wp.shape[1] - (2 if short else 0)
+    assert (Wp[:, kwords:ldb] == 0).all()
+    if short:
+        ones = np.unpackbits(ref.view(np.uint8), axis=1).sum(axis=1, dtype=np.int64)
+        consts = Wp[:, ldb:].copy().view(np.float32)
+        np.testing.assert_array_equal(consts[:, 0], (C * k * k - 2 * ones).astype(np.float32))
+        assert (consts[:, 1:] == 0).all()
+
+
 # ------------------------------------------------------------------ k-bit GEMM
 @pytest.mark.parametrize("bits", [1, 2, 3, 4, 8])
 def test_quant_gemm_small(bits):

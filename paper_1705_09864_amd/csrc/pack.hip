@@ -9,6 +9,9 @@ namespace bmx {
 
 static constexpr int kWave = 64;
 
+// v_writelane_b32, which this compiler knows by no builtin: `old` with `value` (uniform) in lane `lane`.
+extern "C" __device__ __attribute__((const)) uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
 // Row pack.  A wave packs segments of 16 consecutive words (1024 floats) of one row: lane
 // <-> k, so every load instruction is a 256-byte coalesced read and the 64-lane compare
 // mask is the packed word itself.  All 16 loads of a segment are issued before the first
@@ -17,48 +20,48 @@ static constexpr int kWave = 64;
 constexpr int kSegWords = 16;
 
 template <bool NT>
-__device__ __forceinline__ void pack_row_segments(const float* __restrict__ x, int64_t rows,
+__device__ __forceinline__ void pack_row_segments(const float* __restrict__ x, uint32_t total,
                                                   int64_t cols, int64_t ldx,
                                                   uint64_t* __restrict__ out, int64_t out_ld,
-                                                  int64_t Kw, int64_t segs_per_row,
-                                                  int64_t first_block, int64_t per) {
+                                                  int64_t Kw, FastDiv div_segs, uint32_t segs_per_row,
+                                                  uint32_t first, uint32_t per) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
-  const int64_t total = rows * segs_per_row;
-  const int64_t end = (first_block + 1) * per < total ? (first_block + 1) * per : total;
-  for (int64_t seg = first_block * per + wave; seg < end; seg += waves) {
-    const int64_t r = segs_per_row == total ? 0 : seg / segs_per_row;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
+  const uint32_t end = min(first + per, total);
+  for (uint32_t seg = first + wave; seg < end; seg += waves) {
+    const uint32_t r = fast_div(seg, div_segs);
     const int64_t b = seg - r * segs_per_row;
-    const float* xr = x + r * ldx;
-    const int64_t k0 = b * (64 * kSegWords) + lane;
+    const float* const xs = x + (int64_t)r * ldx + b * (64 * kSegWords);
+    const int64_t left = cols - b * (64 * kSegWords);
     float v[kSegWords];
-    if (k0 - lane + 64 * kSegWords <= cols) {  // whole segment inside the row (wave-uniform)
+    if (left >= 64 * kSegWords) {  // whole segment inside the row (wave-uniform)
 #pragma unroll
-      for (int j = 0; j < kSegWords; ++j) v[j] = NT ? __builtin_nontemporal_load(xr + k0 + 64 * j) : xr[k0 + 64 * j];
-    } else {
+      for (int j = 0; j < kSegWords; ++j) v[j] = NT ? __builtin_nontemporal_load(xs + 64 * j + lane) : xs[64 * j + lane];
+    } else {  // (loads under no condition: all are in flight at once; out-of-row lanes contribute 0 bits)
+      const int n = (int)left;
 #pragma unroll
-      for (int j = 0; j < kSegWords; ++j) {
-        const int64_t k = k0 + 64 * j;
-        v[j] = (k < cols) ? xr[k] : -1.0f;  // out-of-row lanes contribute 0 bits
-      }
+      for (int j = 0; j < kSegWords; ++j) v[j] = xs[(uint32_t)min(64 * j + lane, n - 1)];
+#pragma unroll
+      for (int j = 0; j < kSegWords; ++j) v[j] = 64 * j + lane < n ? v[j] : -1.0f;
     }
-    uint64_t mine = 0;
+    uint32_t lo = 0, hi = 0;
 #pragma unroll
     for (int j = 0; j < kSegWords; ++j) {
       const uint64_t m = __ballot(v[j] >= 0.0f);
-      if (lane == j) mine = m;
+      lo = write_lane((uint32_t)m, j, lo);
+      hi = write_lane((uint32_t)(m >> 32), j, hi);
     }
     const int64_t w = b * kSegWords + lane;
-    if (lane < kSegWords && w < Kw) out[r * out_ld + w] = mine;
+    if (lane < kSegWords && w < Kw) out[(int64_t)r * out_ld + w] = ((uint64_t)hi << 32) | lo;
   }
 }
 
 template <bool NT>
 __global__ void __launch_bounds__(256)
-pack_rows_kernel(const float* __restrict__ x, int64_t rows, int64_t cols, int64_t ldx,
-                 uint64_t* __restrict__ out, int64_t out_ld, int64_t Kw, int64_t segs_per_row,
-                 int64_t segs_per_block) {
-  pack_row_segments<NT>(x, rows, cols, ldx, out, out_ld, Kw, segs_per_row, (int64_t)blockIdx.x,
+pack_rows_kernel(const float* __restrict__ x, uint32_t total, int64_t cols, int64_t ldx,
+                 uint64_t* __restrict__ out, int64_t out_ld, int64_t Kw, FastDiv div_segs, uint32_t segs_per_row,
+                 uint32_t segs_per_block) {
+  pack_row_segments<NT>(x, total, cols, ldx, out, out_ld, Kw, div_segs, segs_per_row, blockIdx.x * segs_per_block,
                         segs_per_block);
 }
 
@@ -72,13 +75,15 @@ static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, in
                                   hipStream_t s) {
   // A wave per segment, in a grid of them all: waves that went on to their next segment (2048 workgroups) asked for it
   // only once they had the last (4096 x 9216 from HBM 29.9 us and now 24.1, 2 GiB 380 and 344: 6.2 TB/s).
-  const int64_t spr = ceil_div(words_per_row, kSegWords);
-  const int64_t blocks = std::min<int64_t>(ceil_div(rows * spr, 4), 1 << 22);
+  // (2^32 segments would be 17 TB)
+  const uint32_t spr = (uint32_t)ceil_div(words_per_row, kSegWords), total = (uint32_t)rows * spr;
+  const uint32_t blocks = (uint32_t)std::min<int64_t>(ceil_div(total, 4), 1 << 22);
   const bool nt = rows * cols * 4 > kStreamBytes;
-  note_kernel("pack_rows_kernel<%s> grid %lld x 256", nt ? "nontemporal" : "cached", (long long)blocks);
+  note_kernel("pack_rows_kernel<%s> grid %u x 256", nt ? "nontemporal" : "cached", blocks);
+  const FastDiv div = make_fast_div(spr);
   auto go = [&](auto kern) {
-    launch_kernel(kern, dim3((unsigned)blocks), dim3(256), 0, s, x, rows, cols, ldx, out, out_ld, words_per_row, spr,
-                  ceil_div(rows * spr, blocks));
+    launch_kernel(kern, dim3(blocks), dim3(256), 0, s, x, total, cols, ldx, out, out_ld, words_per_row, div, spr,
+                  (uint32_t)ceil_div(total, blocks));
   };
   if (nt) go(pack_rows_kernel<true>);
   else go(pack_rows_kernel<false>);
@@ -583,50 +588,93 @@ hipError_t launch_alpha_mean_abs(const float* w, int64_t rows, int64_t cols, int
   return launch_error();
 }
 
-// Eq. 1 quantiser + bit-plane pack.  One workgroup per row m, lane <-> k: the four waves
-// take every fourth segment of 16 words, and all 16 loads of a segment are issued before
+// Eq. 1 quantiser + bit-plane pack.  A wave per segment of 16 words of a row, up to 16 of them (rows of one or two
+// segments share a workgroup), lane <-> k, and all 16 loads of a segment are issued before
 // the first of them is used.  q = round(L * clamp(x)), ties away from zero, from the single
 // fp32 product L * x.  Plane p of word w is the 64-lane mask of bit p of q and goes to row
 // m * bits + p of `planes` (words up to ld_words are written, zeros past the data).  The row
 // sum of q, needed by the plane GEMM epilogue, is reduced through LDS.
-// The weight operand of the same GEMM is sign-packed by the workgroups past the first M of
-// the same launch (wrows > 0), so that the two inputs cost one kernel launch, not two.
-__global__ void __launch_bounds__(256)
+// The weight operand of the same GEMM is sign-packed by the workgroups past the first ones of
+// the same launch, so that the two inputs cost one kernel launch, not two.
+// Bound by the two matrices' way in and, beside it, the vector ALU: 15 instructions a value at two bits with the quantiser
+// itself.  The launch, from HBM, with it and four waves a row, and now: 1024 x 4096 and 1024 x 4096 weights 9.9 us and 7.6
+// (4.4 TB/s), 2048 x 2048 twice 9.2 and 7.4, 300 x 5000 and 700 x 5000 (five segments) 8.8 and 6.8.
+// One and two bits (BITS, else 0): the quantiser is monotone in x, so q >= i is x >= the smallest float that reaches i
+// (tried on both sides below with the quantiser itself), and the compares' masks make the planes.
+constexpr float kThird1 = 0x1.555556p-3f, kThird3 = 0x1.aaaaaap-1f;
+static constexpr int quantised(float x, float L) {
+#pragma clang fp contract(off)
+  const float u = L * x;
+  return (int)(u + 0x1.fffffep-2f);
+}
+static_assert(quantised(0.5f, 1.0f) == 1 && quantised(0x1.fffffep-2f, 1.0f) == 0);
+static_assert(quantised(kThird1, 3.0f) == 1 && quantised(0x1.555554p-3f, 3.0f) == 0);
+static_assert(quantised(0.5f, 3.0f) == 2 && quantised(0x1.fffffep-2f, 3.0f) == 1);
+static_assert(quantised(kThird3, 3.0f) == 3 && quantised(0x1.aaaaa8p-1f, 3.0f) == 2);
+
+template <int BITS>
+__global__ void __launch_bounds__(1024)
 quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda, int bits,
                   uint64_t* __restrict__ planes, int64_t ld_words, int32_t* __restrict__ rowsum,
-                  const float* __restrict__ w, int64_t wrows, int64_t ldw,
-                  uint64_t* __restrict__ wbits, int64_t wb_ld, int64_t wsegs_per_block, int affine) {
-  __shared__ int32_t part[4];
-  if ((int64_t)blockIdx.x >= M) {
-    const int64_t Kw = words_for(K);
-    pack_row_segments<false>(w, wrows, K, ldw, wbits, wb_ld, Kw, ceil_div(Kw, kSegWords),
-                      (int64_t)blockIdx.x - M, wsegs_per_block);
+                  const float* __restrict__ w, uint32_t wsegs, int64_t ldw, uint64_t* __restrict__ wbits, int64_t wb_ld,
+                  FastDiv div_segs, uint32_t segs_per_row, uint32_t blocks_a, int per_row, int affine) {
+  __shared__ int32_t part[16];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
+  if (blockIdx.x >= blocks_a) {
+    pack_row_segments<false>(w, wsegs, K, ldw, wbits, wb_ld, words_for(K), div_segs, segs_per_row,
+                          (blockIdx.x - blocks_a) * waves, waves);
     return;
   }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int64_t m = blockIdx.x;
+  const int sub = wave / per_row;  // row of the workgroup
+  const int64_t m = (int64_t)blockIdx.x * (waves / per_row) + sub;
   const float L = (float)((1u << bits) - 1u);
   const float* ar = a + m * lda;
   uint64_t* prow = planes + m * bits * ld_words;
   int32_t sum = 0;
-  for (int64_t w0 = (int64_t)wave * kSegWords; w0 < ld_words; w0 += 4 * kSegWords) {
+  for (int64_t w0 = (int64_t)(wave - sub * per_row) * kSegWords; m < M && w0 < ld_words; w0 += per_row * kSegWords) {
+    const float* const as = ar + w0 * 64;
+    const int64_t left = K - w0 * 64;  // (none where only padding words are left)
     float v[kSegWords];
-    if ((w0 + kSegWords) * 64 <= K) {
+    if (left >= 64 * kSegWords) {
 #pragma unroll
-      for (int j = 0; j < kSegWords; ++j) v[j] = ar[(w0 + j) * 64 + lane];
+      for (int j = 0; j < kSegWords; ++j) v[j] = as[64 * j + lane];
       // (signed operand: [-1, 1] onto [0, 1] first, two fp32 operations)
-      if (affine) {
+      if (BITS == 0 && affine) {
 #pragma unroll
         for (int j = 0; j < kSegWords; ++j) v[j] = __fmul_rn(__fadd_rn(v[j], 1.0f), 0.5f);
       }
     } else {
+      const int n = (int)left;
+#pragma unroll
+      for (int j = 0; j < kSegWords; ++j) v[j] = left > 0 ? as[(uint32_t)min(64 * j + lane, n - 1)] : 0.0f;
 #pragma unroll
       for (int j = 0; j < kSegWords; ++j) {
-        const int64_t k = (w0 + j) * 64 + lane;
-        const float t = (k < K) ? ar[k] : 0.0f;
-        v[j] = (affine && k < K) ? __fmul_rn(__fadd_rn(t, 1.0f), 0.5f) : t;
+        if (BITS == 0 && affine) v[j] = __fmul_rn(__fadd_rn(v[j], 1.0f), 0.5f);
+        v[j] = 64 * j + lane < n ? v[j] : 0.0f;
       }
+    }
+    if constexpr (BITS == 1 || BITS == 2) {
+      uint64_t plane[BITS];
+      uint32_t lo[BITS], hi[BITS];
+#pragma unroll
+      for (int p = 0; p < BITS; ++p) lo[p] = hi[p] = 0;
+#pragma unroll
+      for (int j = 0; j < kSegWords; ++j) {
+        plane[BITS - 1] = __ballot(v[j] >= 0.5f);
+        if (BITS == 2) plane[0] = (__ballot(v[j] >= kThird1) & ~plane[BITS - 1]) | __ballot(v[j] >= kThird3);
+#pragma unroll
+        for (int p = 0; p < BITS; ++p) {
+          lo[p] = write_lane((uint32_t)plane[p], j, lo[p]);
+          hi[p] = write_lane((uint32_t)(plane[p] >> 32), j, hi[p]);
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < BITS; ++p) {
+        sum += (__popc(lo[p]) + __popc(hi[p])) << p;
+        if (lane < kSegWords && w0 + lane < ld_words) prow[p * ld_words + w0 + lane] = ((uint64_t)hi[p] << 32) | lo[p];
+      }
+      continue;
     }
     // Half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32 (with 0.5 itself the one value
     // 0.5 - 2^-25 would round up): one addition where roundf takes a truncation, a subtraction, a compare, a
@@ -653,25 +701,35 @@ quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, kWave);
+  if (per_row == 1) {
+    if (lane == 0 && m < M) rowsum[m] = sum;
+    return;
+  }
   if (lane == 0) part[wave] = sum;
   __syncthreads();
-  if (threadIdx.x == 0) rowsum[m] = part[0] + part[1] + part[2] + part[3];
+  if (lane == 0 && wave == sub * per_row && m < M) {
+    for (int i = 1; i < per_row; ++i) sum += part[wave + i];
+    rowsum[m] = sum;
+  }
 }
 
 hipError_t launch_quant_pack(const float* a, int64_t M, int64_t K, int64_t lda, int bits,
                              uint64_t* planes, int64_t ld_words, int32_t* rowsum, const float* w,
                              int64_t wrows, int64_t ldw, uint64_t* wbits, int64_t wb_ld,
                              hipStream_t s, bool affine) {
-  int64_t wblocks = 0, per = 1;
-  if (wrows > 0) {
-    const int64_t segs = wrows * ceil_div(words_for(K), kSegWords);
-    wblocks = ceil_div(segs, 4);
-    if (wblocks > 256 * 8) wblocks = 256 * 8;
-    per = ceil_div(segs, wblocks);
-  }
-  note_kernel("quant_pack_kernel grid %lld x 256", (long long)(M + wblocks));
-  launch_kernel(quant_pack_kernel, dim3((unsigned)(M + wblocks)), dim3(256), 0, s, a, M, K, lda,
-                     bits, planes, ld_words, rowsum, w, wrows, ldw, wbits, wb_ld, per, affine ? 1 : 0);
+  const int per_row = (int)std::min<int64_t>(ceil_div(ld_words, kSegWords), 16);
+  const int rows = per_row <= 2 ? 4 / per_row : 1, waves = rows * per_row;
+  const uint32_t spr = (uint32_t)ceil_div(words_for(K), kSegWords), wsegs = (uint32_t)wrows * spr;
+  const uint32_t blocks_a = (uint32_t)ceil_div(M, rows), blocks = blocks_a + (uint32_t)ceil_div(wsegs, waves);
+  note_kernel("quant_pack_kernel grid %u x %d", blocks, 64 * waves);
+  const FastDiv div = make_fast_div(spr);
+  auto go = [&](auto kern) {
+    launch_kernel(kern, dim3(blocks), dim3(64 * waves), 0, s, a, M, K, lda, bits, planes, ld_words, rowsum, w, wsegs, ldw,
+                  wbits, wb_ld, div, spr, blocks_a, per_row, affine ? 1 : 0);
+  };
+  if (affine || bits > 2) go(quant_pack_kernel<0>);
+  else if (bits == 2) go(quant_pack_kernel<2>);
+  else go(quant_pack_kernel<1>);
   return launch_error();
 }
 

@@ -516,6 +516,39 @@ def test_quant_gemm_small(bits):
     assert_f32_close(of.cpu().numpy(), r32)
 
 
+@pytest.mark.parametrize("bits", [1, 2])
+@pytest.mark.parametrize("M,N,K", [(5, 3, 64), (7, 70, 1000), (6, 9, 1025), (3, 66, 2049), (9, 5, 5000), (2, 33, 16383), (3, 40, 17500)])
+def test_quant_planes_by_thresholds(M, N, K, bits):
+    """One- and two-bit activations as bit planes: floats on both sides of every level's threshold, rows of one to more
+    than sixteen segments of 1024 values, whole and not, several of a workgroup's rows past the last."""
+    rng = np.random.default_rng(K + bits)
+    L = (1 << bits) - 1
+    at = np.array([(i - 0.5) / L for i in range(1, L + 1)] + [0.0, 1.0], np.float32)
+    near = np.concatenate([at] + [np.nextafter(at, s * np.float32(np.inf), dtype=np.float32) for s in (-1, 1)]
+                          + [np.array([-0.0, -1e30, 1e30, np.inf, -np.inf], np.float32)])
+    a = rng.uniform(-0.1, 1.1, (M, K)).astype(np.float32)
+    pick = rng.random((M, K)) < 0.5
+    a[pick] = rng.choice(near, int(pick.sum()))
+    w = rng.standard_normal((N, K)).astype(np.float32)
+    with tuned(k7=1):
+        S, of = B.quant_gemm(dev(a), dev(w), bits)
+    rS, r64, r32 = oracle.quant_gemm(a, w, bits)
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    assert_f32_close(of.cpu().numpy(), r32)
+
+
+@pytest.mark.parametrize("M,N,K", [(513, 290, 1100), (513, 290, 1101), (994, 551, 1200), (700, 1300, 5000), (520, 513, 5003)])
+def test_quant_bytes_forms(M, N, K):
+    """The byte form's three sizes of C per wave and its splits of K: both sides of the lines that choose them."""
+    rng = np.random.default_rng(M + N + K)
+    a = rng.uniform(0, 1, (M, K)).astype(np.float32)
+    w = np.tanh(rng.standard_normal((N, K))).astype(np.float32)
+    S, of = B.quant_gemm(dev(a), dev(w), 4, bits_w=4)
+    assert "gemm_i8_kernel" in B.last_kernel()
+    rS, r64, r32 = oracle.quant_gemm(a, w, 4, 4)
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+
+
 @pytest.mark.parametrize("engine", [0, 1])
 @pytest.mark.parametrize("ba,bw", [(1, 2), (2, 2), (2, 3), (3, 2), (4, 4), (8, 8), (2, 8)])
 def test_quant_gemm_kbit_weights(ba, bw, engine):

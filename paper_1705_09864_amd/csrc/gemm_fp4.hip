@@ -848,7 +848,9 @@ int gemm_fp4_tall = 0;   // 0 = automatic; 1 = never 128 x 64 of C per wave; 2 =
 // three, 20 undivided; 1272 x 2474 x 2046 (780 tiles) 10.3 undivided, 12.7 over two.  An xnor product is divided
 // from 34 words on (1813 x 952 x 2393, 435 tiles: 9.1 over four, 10.3 undivided; 3331 x 403 x 1739: 9.7 / 8.4),
 // with its rows through registers, whose latency more waves hide, from 21 (2522 x 675 x 1344: 9.4 / 10.2; 424 x
-// 3607 x 3008: 10.0 / 13.3).
+// 3607 x 3008: 10.0 / 13.3).  A product of bit planes from 22 (whole calls, pack and all: 517 x 1024 x 2432 of 2 x 1 bits
+// 14.2 over four, 18.9 undivided; 238 x 1024 x 1984 11.7 / 16.2; 478 x 456 x 1472 13.5 / 14.2; 1365 x 960 x 1728
+// of 1 x 1 16.0 / 15.8; 880 x 793 x 1216 15.2 / 13.8).
 static int choose_k_split(int64_t tiles, int kwords, int least, int four_up_to) {
   if (kwords < least || tiles > four_up_to) return 1;
   return tiles <= 256 ? 8 : 4;
@@ -915,7 +917,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
-  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? 48 : reg ? 21 : 34, 512);
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? 22 : reg ? 21 : 34, 512);
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;

@@ -438,23 +438,21 @@ int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * c
 // the FP4 form holds, or a product of few bits where bytes cost less than the plane pack and its GEMM; and a result that
 // fills a quarter of a 32 x 32 block (below that the padding of the tiles is most of what is moved, and the plane
 // kernels' workspace is smaller).
-// Few bits (1 or 2 by 1): the byte form writes its tiles and reads them again and multiplies a byte a value, and both
-// grow with K beside; the plane form's pack gives a row to four waves in segments of 1024 values, so a round of
-// 4096 that is not full costs as much as a full one, and a segment that is not full 1.5 to 2 us more (each of its loads
-// is tested).  The line below fits 456 products on both forms (chosen form over the better one: 0.5 % on average;
-// counting multiply-adds alone 3.1 %).  us a call, bytes / planes, at 2 x 1 bits: 16 x 2048 x 8192 20.6 / 18.2,
-// 32 x 1900 x 8192 20.1 / 18.0, 16 x 900 x 8192 13.8 / 11.6, 16 x 200 x 16384 16.2 / 13.7, 1024 x 32 x 16384 25.3 / 22.3, 475 x 1088 x
-// 832 8.3 / 11.8, 700 x 900 x 1600 13.9 / 14.7, 360 x 4096 x 832 16.0 / 12.8, 1024 x 1024 x 4096 18.1 / 13.9, 100 x 900 x 10000
-// 18.0 / 19.5; 64 x 907 x 256 is in one launch, 4.8.
-static bool bytes_pay(int64_t M, int64_t N, int64_t K) {
-  if (M * N >= 1000000000 || M * N * K >= 1000000000) return false;
-  const int64_t bytes = tile_bytes(M, K) + tile_bytes(N, K) + M * N * K * 6 / 1000 + 800 * K;
-  const int64_t planes = 2000 * (ceil_div(K, 4096) * 4096 - K) + (K % 1024 ? 10000000 : 0);
-  return bytes < planes + 10000000;
+// Few bits (1 or 2 by 1): the byte form writes its tiles and reads them again and multiplies a byte a value; the plane
+// form multiplies once per activation bit, and its pack and its splits of K have coarser pieces, so that a round of 4096
+// values that is not full costs much of a full one.  The line below fits 518 products on
+// both forms (chosen form over the better one: 0.5 % on average, 18 % at most; bytes always 5.5 %, planes always 15 %).  us a
+// call, bytes / planes: 572 x 896 x 1293 of 1 x 1 bits 10.3 / 14.3, 496 x 1408 x 640 9.4 / 12.7, 418 x 1024 x 605
+// of 2 x 1 8.1 / 12.1; 612 x 384 x 3968 15.4 / 12.0, 361 x 64 x 8115 15.1 / 12.1, 1744 x 256 x 2234 16.8 / 13.4.
+static bool bytes_pay(int64_t M, int64_t N, int64_t K, int bits_a) {
+  if (M * N >= 1000000000) return false;  // (the products below stay in range)
+  const int64_t bytes = tile_bytes(M, K) + tile_bytes(N, K) + M * N * K / 1000 * 20 + 100 * K;
+  const int64_t planes = 14000000 * (bits_a - 1) + (K % 1024 ? 4000000 : 0) + 5500 * (ceil_div(K, 4096) * 4096 - K);
+  return bytes < planes;
 }
 
 bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes) {
-  if (bits_a <= 2 && bits_w == 1 && !bytes_pay(M, N, K)) return false;
+  if (bits_a <= 2 && bits_w == 1 && !bytes_pay(M, N, K, bits_a)) return false;
   if (M * N < 256) return false;
   const int64_t a = tile_bytes(M, K), b = tile_bytes(N, K);
   *bytes = (size_t)(a + b);
@@ -553,19 +551,21 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   p.A = q.op[0].tiles;
   p.B = q.op[1].tiles;
   p.nk = q.kblocks * 8;
-  // The most of C per wave that still gives every CU a workgroup (the waves that split K share one):
-  // 64 x 64, 32 x 64, 32 x 32.  500 x 1000 x 2304: 128 tiles of 64 x 64 9.2 us, 256 of 32 x 64 7.1 us.
-  int TM = 1, TN = 1;
-  if (ceil_div(M, 64) * ceil_div(N, 64) >= 256) TM = TN = 2;
-  else if (ceil_div(M, 32) * ceil_div(N, 64) >= 192) TN = 2;
+  // C per wave: 32 x 32 while K is short (many waves, each with little to fetch before its first product), 32 x 64, and 64 x 64
+  // where K is long, each with tiles for half the CUs.  K is split over as many waves as leave the workgroups of
+  // a CU resident at once (the registers hold 24, 12 and 8 waves, rounded as below), a power of two of them so that its
+  // SIMDs stay level.  us a call, before (2048 waves in all, 64 x 64 and 32 x 64 once they fill the chip) and now: 994 x 551 x
+  // 2226, 288 tiles of 32 x 64, where the second workgroup of seven waves had to wait for the first, 18.8 and 15.3; 721
+  // x 1438 x 681 14.2 and 11.4; 1650 x 1566 x 103 16.8 and 12.2; 1098 x 1728 x 265 12.1 and 11.3.  Over 150
+  // products 8.7 % and 1.8 % behind the best of all splits and forms.
+  const int64_t t12 = ceil_div(M, 32) * ceil_div(N, 64), t22 = ceil_div(M, 64) * ceil_div(N, 64);
+  const int TM = K >= 5000 && t22 >= 128 ? 2 : 1, TN = TM == 2 || (K > 1100 && t12 >= 128) ? 2 : 1;
   p.tiles_m = (int)ceil_div(M, 32 * TM);
   p.tiles = (int)(p.tiles_m * ceil_div(N, 32 * TN));
   p.tiles_per_xcd = (int)ceil_div(p.tiles, 8);
-  // K split: up to two waves per SIMD, each with at least one group of k steps
-  int S = (int)(2048 / p.tiles);
-  S = S > 8 ? 8 : S;
-  if (S > p.nk / kAhead) S = p.nk / kAhead;
-  p.S = S < 1 ? 1 : S;
+  const int64_t room = (TM * TN == 4 ? 8 : TM * TN == 2 ? 12 : 24) / ceil_div(p.tiles, 256);  // waves a workgroup
+  p.S = room >= 8 ? 8 : room >= 4 ? 4 : room >= 2 ? 2 : 1;
+  while (p.S > 1 && p.S > p.nk / kAhead) p.S /= 2;  // (each with at least one group of k steps)
   set_split(p);
   const bool sums = bits_a == 8 || bits_w == 8;
   if (TM == 2) *err = sums ? launch_i8<2, 2, true>(p, s) : launch_i8<2, 2, false>(p, s);

@@ -292,6 +292,8 @@ gemm_kernel(const GemmParams p) {
   int row_sum = 0;
   if (CONV && p.out == kGemmF32Alpha && lane < rows_out) row_alpha = p.alpha[mbase + lane];
   if (p.out == kGemmPlanes && lane < rows_out) row_sum = p.rowsum[mbase + lane];
+  // (waited for here, not before each of the stores below, which would wait for the stores before it as well)
+  asm volatile("" : "+v"(al), "+v"(th), "+v"(row_alpha), "+v"(row_sum));
   auto finish = [&](int lr, int total) {  // count of the block's output row lr -> C[m][n]
     const int64_t m = mbase + lr;
     if (p.out == kGemmBits) {

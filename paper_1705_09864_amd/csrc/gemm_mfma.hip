@@ -410,6 +410,9 @@ gemm_mfma_kernel(const MfmaParams p) {
   // half sits 32 lanes away.  (The plane form keeps the plain sums: its row term is the
   // given rowsum, applied once at the end.)
   if (XNOR) {
+    // (waited for here, not before each of the stores below, which would wait for the stores before it as well)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(aln[j]), "+v"(thn[j]));
 #pragma unroll
     for (int i = 0; i < TM; ++i) pa[i] += __shfl_xor(pa[i], 32);
 #pragma unroll

@@ -509,10 +509,12 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // 2946, 126 tiles, 9.5 / 10.9).  Others: where there is a workgroup for
   // every CU and no CU is given far more of them than another (1344 x 6016 x 3840, 517 tiles on 256 CUs, 17.7 / 21.1; 5504 x
   // 320 x 4956, 129 tiles and the K divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
-  // time (4560 x 731 x 582 8.0 / 9.1).  Of the two shapes the larger needs many tiles per CU and a long K (8192^3 184 as 128 x 128,
+  // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, one workgroup a CU
+  // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger needs many tiles per CU and a long K (8192^3 184 as 128 x 128,
   // 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
   if (gemm_block == 0) {
-    if (any_dword ? tiles <= 144 : (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700)) return false;
+    if (any_dword ? tiles <= 144 : (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700 || (C_f32 && tiles == 256 && K < 8000)))
+      return false;
   }
   // (32-bit offsets, rows of the last tile past the last row counted; whole numbers up to 3 K exact in fp32)
   const int64_t lim = (int64_t)1 << 32;

@@ -586,7 +586,16 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   int form = conv_block;
   if (form == 0) {
     conv_long_us(P, O, kwords, any_dword, &form);
-    if (conv_weight_short_k(kwords)) return false;
+    // Short K stays with conv_mfma.hip, but for many filters over many pixels: there a pixel's words are expanded once per
+    // 32 filters, here once per 128 or 64.  Of 182 of 36, 49 and 50 words, from 90000 steps of 32 x 32 x 256 on (us there /
+    // here): as packed bits 27776 pixels, 448 filters, 50 words 31.8 / 20.6, 27664, 384, 36 20.1 / 15.8, 46371, 192, 49 24.1 / 20.5;
+    // fp32, 22610, 384, 49 24.1 / 21.9, 40544, 192, 50 18.1 / 15.0, but level at 36 words.  64 filters: 146160 pixels,
+    // 49 words 19.7 / 23.9.
+    if (conv_weight_short_k(kwords)) {
+      const int64_t work = ceil_div(P, 32) * ceil_div(O, 32) * ceil_div(kwords, 4);
+      if (kwords < (out_bits ? 36 : 49) || O < 128 || work < 90000) return false;
+      form = ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256) < ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256) ? 3 : 2;
+    }
     // Fewer words than a segment: the results are the time, and they leave best where neighbouring pixels are in one place.  As packed
     // bits from 7000 tiles of 32 x 32 on (1 x 1, 87822 pixels, 128 filters 11.8 us in conv_small.hip, 8.5 here; 51200, 137 level),
     // fp32 and int32 from 44 MB (the same 15.2 in conv.hip, 12.0; 147630 pixels, 64 filters, 38 MB 11.2 / 12.1).

@@ -1481,6 +1481,26 @@ def test_conv_long_k_kernels(form, N, C, H, W, O, k, s, p, opad):
             assert torch.equal(B.binary_conv2d_bits(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha), thr=dev(thr), out_pad=opad), want)
 
 
+@pytest.mark.parametrize("N,C,H,W,O,k,f32", [(44, 250, 25, 26, 391, 3, False), (21, 60, 32, 33, 384, 7, True), (20, 128, 31, 33, 449, 5, True),
+                                             (43, 250, 25, 26, 127, 3, False)])
+def test_conv_short_k_many_filters(N, C, H, W, O, k, f32):
+    """36, 49 and 50 words with so many filters and pixels that the rows are staged once per workgroup: as the kernel for
+    short K has it (by its tests against the oracle), as packed image and, from 49 words on, fp32."""
+    rng = np.random.default_rng(O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha, thr = dev(rng.standard_normal(O).astype(np.float32)), dev((rng.standard_normal(O) * 40).astype(np.float32))
+    xp, Wp = B.pack_nchw(dev(x), k // 2), B.pack_conv_weights(dev(w))
+    runs = [lambda: B.binary_conv2d_bits(xp, C, Wp, O, k, k, 1, k // 2, alpha=alpha, thr=thr, out_pad=1)]
+    runs += [lambda: B.binary_conv2d_packed(xp, C, Wp, O, k, k, 1, k // 2, alpha=alpha),
+             lambda: B.binary_conv2d_packed(xp, C, Wp, O, k, k, 1, k // 2, integer_out=True)]
+    for i, run in enumerate(runs):
+        got = run()
+        assert ("gemm_fp4_kernel" in B.last_kernel()) == (O >= 128 and (f32 or i == 0)), B.last_kernel()
+        with tuned(k20=1):
+            assert torch.equal(got, run())
+            assert "conv_mfma_ws_kernel" in B.last_kernel()
+
+
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,opad", [
     (1, 1, 1, 1, 1, 1, 1, 0, 0), (3, 300, 5, 7, 33, 1, 2, 0, 2), (2, 128, 9, 8, 70, 3, 1, 1, 1), (2, 131, 6, 5, 32, 3, 2, 2, 0), (1, 70, 8, 9, 95, 5, 1, 4, 3),
     (5, 64, 7, 7, 64, 7, 1, 3, 1), (2, 260, 6, 11, 129, 3, 1, 1, 6), (1, 512, 9, 9, 31, 7, 2, 6, 1), (40, 200, 12, 13, 100, 3, 1, 0, 1), (9, 50, 40, 41, 64, 1, 1, 0, 1)])

@@ -495,12 +495,15 @@ hipError_t go(BlockParams& p, hipStream_t s) {
 }  // namespace
 }  // namespace block
 
+int gemm_fp4_tall = 0;  // 1 = never this kernel; 2 = 256 x 128 of C per workgroup, with gemm_fp4.hip's choices pinned too
 int gemm_block = 0;  // 1 = never, 2 = 256 x 128 and 3 = 128 x 128 of C per workgroup whatever the size
 
 bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t ldb_bytes, int M, int N, int K, int dwords,
                        const float* alpha, int32_t* C_i32, float* C_f32, int64_t ldc, bool as_count, hipStream_t s,
                        hipError_t* err) {
-  if (gemm_block == 1 || gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band || gemm_fp4_tall) return false;
+  const bool pinned = gemm_fp4_tall == 2 && (gemm_engine == 0 || gemm_engine == 3 || gemm_engine == 5) && gemm_fp4_split <= 1;
+  if (gemm_block == 1 || (!pinned && (gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band || gemm_fp4_tall)))
+    return false;
   const bool any_dword = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(tiles, 256);
   // Against gemm_fp4.hip, from 220 products of up to 8192 x 8192 x 8192 measured on both (us, there / here).  Rows that
@@ -512,14 +515,16 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, one workgroup a CU
   // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger needs many tiles per CU and a long K (8192^3 184 as 128 x 128,
   // 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
-  if (gemm_block == 0) {
+  if (pinned) {
+    if (any_dword) return false;
+  } else if (gemm_block == 0) {
     if (any_dword ? tiles <= 144 : (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700 || (C_f32 && tiles == 256 && K < 8000)))
       return false;
   }
-  // (32-bit offsets, rows of the last tile past the last row counted; whole numbers up to 3 K exact in fp32)
+  // (32-bit offsets, rows of the last tile past the last row counted, of C within a tile; whole numbers up to 3 K exact in fp32)
   const int64_t lim = (int64_t)1 << 32;
   if (K >= (1 << 22) || ((int64_t)M + 256) * lda_bytes >= lim || ((int64_t)N + 256) * ldb_bytes >= lim) return false;
-  if (((int64_t)M + 256) * ldc * 4 >= lim || ((uintptr_t)A & 3) || ((uintptr_t)B & 3)) return false;
+  if (ldc >= (1 << 22) || ((uintptr_t)A & 3) || ((uintptr_t)B & 3)) return false;
   block::BlockParams p;
   p.A = (const char*)A;
   p.B = (const char*)B;
@@ -541,7 +546,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   p.thr = nullptr;
   p.opad = p.oHp = p.oWp = p.oCw = 0;
-  const bool large = !any_dword && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096);
+  const bool large = !any_dword && (pinned || (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096));
   using namespace block;
   if (large) *err = C_i32 ? go<2, 4, 2, kI32, 16, false>(p, s) : go<2, 4, 2, kF32, 16, false>(p, s);
   else if (any_dword) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);

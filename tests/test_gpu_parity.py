@@ -1266,6 +1266,24 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
                 assert "f32,block" in B.last_kernel()
 
 
+def test_gemm_fp4_block_form_past_4_gib_of_results():
+    """33000 x 33024 int32: rows of C past 4 GiB, the last tile in part past both edges, against the 64 x 64 per wave kernel."""
+    M, N, K = 33000, 33024, 704
+    A = torch.randint(-2 ** 62, 2 ** 62, (M, 12), device="cuda")[:, :11]
+    Bm = torch.randint(-2 ** 62, 2 ** 62, (N, 12), device="cuda")[:, :11]
+    for K in (704, 700):
+        got = B.xnor_gemm(A, Bm, K)
+        assert "block" in B.last_kernel()
+        with tuned(k7=1):
+            want = B.xnor_gemm(A[-1000:], Bm, K)
+        assert torch.equal(got[-1000:], want)
+        with tuned(k19=1):
+            want = B.xnor_gemm(A, Bm, K)
+            assert "block" not in B.last_kernel()
+        assert torch.equal(got, want)
+        del got, want
+
+
 @pytest.mark.parametrize("split,partials", [(0, 0), (1, 0), (2, 0), (3, 0), (5, 0), (7, 0), (8, 0), (8, 2), (3, 2)])
 def test_gemm_fp4_lds_staged_kernel(split, partials):
     """The matrix-core GEMM kernel with 64 x 64 of C per wave, operands staged through LDS by the

@@ -38,9 +38,9 @@ __device__ __forceinline__ void pack_row_segments(const float* __restrict__ x, u
 #pragma unroll
       for (int j = 0; j < kSegWords; ++j) v[j] = NT ? __builtin_nontemporal_load(xs + 64 * j + lane) : xs[64 * j + lane];
     } else {  // (loads under no condition: all are in flight at once; out-of-row lanes contribute 0 bits)
-      const int n = (int)left;
+      const int n = (int)max(left, (int64_t)0);  // (0: padding words only)
 #pragma unroll
-      for (int j = 0; j < kSegWords; ++j) v[j] = xs[(uint32_t)min(64 * j + lane, n - 1)];
+      for (int j = 0; j < kSegWords; ++j) v[j] = n > 0 ? xs[(uint32_t)min(64 * j + lane, n - 1)] : 0.0f;
 #pragma unroll
       for (int j = 0; j < kSegWords; ++j) v[j] = 64 * j + lane < n ? v[j] : -1.0f;
     }
@@ -75,8 +75,14 @@ static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, in
                                   hipStream_t s) {
   // A wave per segment, in a grid of them all: waves that went on to their next segment (2048 workgroups) asked for it
   // only once they had the last (4096 x 9216 from HBM 29.9 us and now 24.1, 2 GiB 380 and 344: 6.2 TB/s).
-  // (2^32 segments would be 17 TB)
-  const uint32_t spr = (uint32_t)ceil_div(words_per_row, kSegWords), total = (uint32_t)rows * spr;
+  const uint32_t spr = (uint32_t)ceil_div(words_per_row, kSegWords);
+  const int64_t most = std::max<int64_t>(((int64_t)1 << 30) / spr, 1);  // rows a launch: segments are counted in 32 bits
+  if (rows > most) {
+    launch_pack_rows_grid(x, most, cols, ldx, out, out_ld, words_per_row, s);
+    launch_pack_rows_grid(x + most * ldx, rows - most, cols, ldx, out + most * out_ld, out_ld, words_per_row, s);
+    return;
+  }
+  const uint32_t total = (uint32_t)rows * spr;
   const uint32_t blocks = (uint32_t)std::min<int64_t>(ceil_div(total, 4), 1 << 22);
   const bool nt = rows * cols * 4 > kStreamBytes;
   note_kernel("pack_rows_kernel<%s> grid %u x 256", nt ? "nontemporal" : "cached", blocks);
@@ -617,13 +623,13 @@ __global__ void __launch_bounds__(1024)
 quant_pack_kernel(const float* __restrict__ a, int64_t M, int64_t K, int64_t lda, int bits,
                   uint64_t* __restrict__ planes, int64_t ld_words, int32_t* __restrict__ rowsum,
                   const float* __restrict__ w, uint32_t wsegs, int64_t ldw, uint64_t* __restrict__ wbits, int64_t wb_ld,
-                  FastDiv div_segs, uint32_t segs_per_row, uint32_t blocks_a, int per_row, int affine) {
+                  FastDiv div_segs, uint32_t segs_per_row, uint32_t segs_per_block, uint32_t blocks_a, int per_row, int affine) {
   __shared__ int32_t part[16];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
   if (blockIdx.x >= blocks_a) {
     pack_row_segments<false>(w, wsegs, K, ldw, wbits, wb_ld, words_for(K), div_segs, segs_per_row,
-                          (blockIdx.x - blocks_a) * waves, waves);
+                          (blockIdx.x - blocks_a) * segs_per_block, segs_per_block);
     return;
   }
   const int sub = wave / per_row;  // row of the workgroup
@@ -720,12 +726,13 @@ hipError_t launch_quant_pack(const float* a, int64_t M, int64_t K, int64_t lda, 
   const int per_row = (int)std::min<int64_t>(ceil_div(ld_words, kSegWords), 16);
   const int rows = per_row <= 2 ? 4 / per_row : 1, waves = rows * per_row;
   const uint32_t spr = (uint32_t)ceil_div(words_for(K), kSegWords), wsegs = (uint32_t)wrows * spr;
-  const uint32_t blocks_a = (uint32_t)ceil_div(M, rows), blocks = blocks_a + (uint32_t)ceil_div(wsegs, waves);
+  const uint32_t blocks_a = (uint32_t)ceil_div(M, rows), blocks_w = (uint32_t)std::min<int64_t>(ceil_div(wsegs, waves), 1 << 20);
+  const uint32_t blocks = blocks_a + blocks_w, per_block = blocks_w ? (uint32_t)ceil_div(wsegs, blocks_w) : 0;
   note_kernel("quant_pack_kernel grid %u x %d", blocks, 64 * waves);
   const FastDiv div = make_fast_div(spr);
   auto go = [&](auto kern) {
     launch_kernel(kern, dim3(blocks), dim3(64 * waves), 0, s, a, M, K, lda, bits, planes, ld_words, rowsum, w, wsegs, ldw,
-                  wbits, wb_ld, div, spr, blocks_a, per_row, affine ? 1 : 0);
+                  wbits, wb_ld, div, spr, per_block, blocks_a, per_row, affine ? 1 : 0);
   };
   if (affine || bits > 2) go(quant_pack_kernel<0>);
   else if (bits == 2) go(quant_pack_kernel<2>);

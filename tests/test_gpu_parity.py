@@ -472,6 +472,16 @@ def test_alpha_and_row_pack_any_start(rows, cols):
     np.testing.assert_array_equal(host_u64(B.binarize_pack(w, 1)), oracle.binarize_pack(host, 1))
 
 
+def test_pack_more_rows_than_a_launch_counts():
+    """2^30 + 70 rows of one value: two launches, the second from its own row on."""
+    rows = (1 << 30) + 70
+    x = torch.full((rows, 1), -1.0, device="cuda")
+    at = torch.tensor([0, 5, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, rows - 1], device="cuda")
+    x[at] = 1.0
+    out = B.binarize_pack(x, 1)
+    assert out.shape == (rows, 1) and int(out.sum()) == len(at) and bool((out[at] == 1).all())
+
+
 @pytest.mark.parametrize("K,cols,start", [(1, 1, 0), (15, 64, 0), (16, 65, 0), (17, 96, 1), (64, 63, 0), (65, 130, 3), (128, 1024, 0), (129, 1024, 1),
                                           (191, 320, 0), (1000, 515, 2), (3150, 4096, 0), (3150, 4100, 0)])
 def test_pack_down_columns_tiles(K, cols, start):

@@ -507,19 +507,26 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const bool any_dword = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(tiles, 256);
   // Against gemm_fp4.hip, from 220 products of up to 8192 x 8192 x 8192 measured on both (us, there / here).  Rows that
-  // start on any dword pass through registers there: from 145 tiles on (512 x 4736 x 4921, 148 tiles, 16.6 / 13.1; 1036
-  // x 7808 x 386, 549 tiles, 14.2 / 9.1); with fewer it goes both ways (4444 x 512 x 7119, 140 tiles, 23.8 / 16.9; 358 x 5312 x
-  // 2946, 126 tiles, 9.5 / 10.9).  Others: where there is a workgroup for
+  // start on any dword pass through registers there: from where K is no longer divided over a CU's waves there, 512 tiles of 64 x 64
+  // (1216 x 1792 x 3264, 532 of them, 12.7 / 10.0; 6016 x 384 x 1600, 564, 9.3 / 7.5; 1216 x 1600 x 1984, 475, 7.8 / 8.5; 174 x
+  // 7865 x 4672, 369, 10.8 / 14.3), rows of 32-bit words from 145 tiles here (704 x 3840 x 2768, 180, 12.7 / 9.0; 2633 x 591 x
+  // 3148, 105, 10.2 / 11.8).  Others: where there is a workgroup for
   // every CU and no CU is given far more of them than another (1344 x 6016 x 3840, 517 tiles on 256 CUs, 17.7 / 21.1; 5504 x
   // 320 x 4956, 129 tiles and the K divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
   // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, one workgroup a CU
-  // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger needs many tiles per CU and a long K (8192^3 184 as 128 x 128,
-  // 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
+  // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger
+  // needs many tiles per CU and a long K (8192^3 184 as 128 x 128, 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
   if (pinned) {
     if (any_dword) return false;
   } else if (gemm_block == 0) {
-    if (any_dword ? tiles <= 144 : (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700 || (C_f32 && tiles == 256 && K < 8000)))
+    const bool odd_dwords = ((uintptr_t)A | (uintptr_t)B | lda_bytes | ldb_bytes | (4 * dwords)) & 7;
+    if (odd_dwords) {
+      if (tiles <= 144) return false;
+    } else if (any_dword) {
+      if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
+    } else if (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700 || (C_f32 && tiles == 256 && K < 8000)) {
       return false;
+    }
   }
   // (32-bit offsets, rows of the last tile past the last row counted, of C within a tile; whole numbers up to 3 K exact in fp32)
   const int64_t lim = (int64_t)1 << 32;

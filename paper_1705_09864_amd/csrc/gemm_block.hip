@@ -511,8 +511,9 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // (1216 x 1792 x 3264, 532 of them, 12.7 / 10.0; 6016 x 384 x 1600, 564, 9.3 / 7.5; 1216 x 1600 x 1984, 475, 7.8 / 8.5; 174 x
   // 7865 x 4672, 369, 10.8 / 14.3), rows of 32-bit words from 145 tiles here (704 x 3840 x 2768, 180, 12.7 / 9.0; 2633 x 591 x
   // 3148, 105, 10.2 / 11.8).  Others: where there is a workgroup for
-  // every CU and no CU is given far more of them than another (1344 x 6016 x 3840, 517 tiles on 256 CUs, 17.7 / 21.1; 5504 x
-  // 320 x 4956, 129 tiles and the K divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
+  // every CU and no CU is given far more of them than another, or its SIMDs are there (6976 x 522 x 3840, 275 tiles on 256 CUs, 981
+  // of 64 x 64 on 1024 SIMDs, 13.1 / 17.1; 768 x 5952 x 7291, 282 and 1116, 25.1 / 23.4, but 8192 x 540 x 768 9.3 / 9.9; 5504 x 320 x 4956, 129 tiles and the K
+  // divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
   // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, one workgroup a CU
   // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger
   // needs many tiles per CU and a long K (8192^3 184 as 128 x 128, 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
@@ -524,7 +525,8 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
       if (tiles <= 144) return false;
     } else if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
-    } else if (tiles < 256 || 10 * tiles < 7 * 256 * rounds || K < 700 || (C_f32 && tiles == 256 && K < 8000)) {
+    } else if (tiles < 256 || K < 700 || (C_f32 && tiles == 256 && K < 8000) ||
+               (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {
       return false;
     }
   }

@@ -509,8 +509,9 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // Against gemm_fp4.hip, from 220 products of up to 8192 x 8192 x 8192 measured on both (us, there / here).  Rows that
   // start on any dword pass through registers there: from where K is no longer divided over a CU's waves there, 512 tiles of 64 x 64
   // (1216 x 1792 x 3264, 532 of them, 12.7 / 10.0; 6016 x 384 x 1600, 564, 9.3 / 7.5; 1216 x 1600 x 1984, 475, 7.8 / 8.5; 174 x
-  // 7865 x 4672, 369, 10.8 / 14.3), rows of 32-bit words from 145 tiles here (704 x 3840 x 2768, 180, 12.7 / 9.0; 2633 x 591 x
-  // 3148, 105, 10.2 / 11.8).  Others: where there is a workgroup for
+  // 7865 x 4672, 369, 10.8 / 14.3).  Rows of an odd number of 32-bit words cross at the same count (90 products of 273 to 1160
+  // tiles: 2137 x 971 x 3163, 544, 14.4 / 12.3; 1032 x 1995 x 3995, 544, 15.9 / 12.8; 1142 x 1962 x 987, 558, 9.4 / 7.8; 1535 x
+  // 1317 x 3163, 504, 10.4 / 12.1; 1161 x 1608 x 2779, 494, 9.9 / 10.7).  Others: where there is a workgroup for
   // every CU and no CU is given far more of them than another, or its SIMDs are there (6976 x 522 x 3840, 275 tiles on 256 CUs, 981
   // of 64 x 64 on 1024 SIMDs, 13.1 / 17.1; 768 x 5952 x 7291, 282 and 1116, 25.1 / 23.4, but 8192 x 540 x 768 9.3 / 9.9; 5504 x 320 x 4956, 129 tiles and the K
   // divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
@@ -520,10 +521,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   if (pinned) {
     if (any_dword) return false;
   } else if (gemm_block == 0) {
-    const bool odd_dwords = ((uintptr_t)A | (uintptr_t)B | lda_bytes | ldb_bytes | (4 * dwords)) & 7;
-    if (odd_dwords) {
-      if (tiles <= 144) return false;
-    } else if (any_dword) {
+    if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
     } else if (tiles < 256 || K < 700 || (C_f32 && tiles == 256 && K < 8000) ||
                (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {

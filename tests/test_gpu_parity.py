@@ -1276,6 +1276,27 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
                 assert "f32,block" in B.last_kernel()
 
 
+@pytest.mark.parametrize("M,N,K,kind,block", [
+    # rows of an odd number of 32-bit words: from 513 tiles of 64 x 64 on
+    (1032, 1995, 3995, "w32", True), (2137, 971, 3163, "w32", True), (1142, 1962, 987, "w32", True),
+    (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False)])
+def test_block_form_lines(M, N, K, kind, block):
+    """Both sides of the lines between the kernel that stages rows once per workgroup and the 64 x 64 per wave kernel: the
+    form that runs, and the same results from the other."""
+    rng = np.random.default_rng(M + N + K)
+    A = B.binarize_pack(dev(rng.standard_normal((M, K)).astype(np.float32)), 1)
+    W = B.binarize_pack(dev(rng.standard_normal((N, K)).astype(np.float32)), 1)
+    words = -(-K // 32)
+    A, W = (t.view(torch.int32)[:, :words].contiguous() for t in (A, W))
+    call = lambda: B.xnor_gemm_w32(A, W, K)  # noqa: E731
+    got = call()
+    assert ("block" in B.last_kernel()) == block, B.last_kernel()
+    with tuned(k19=1 if block else 3):
+        want = call()
+        assert ("block" in B.last_kernel()) != block, B.last_kernel()
+    assert torch.equal(got, want)
+
+
 def test_gemm_fp4_block_form_past_4_gib_of_results():
     """33000 x 33024 int32: rows of C past 4 GiB, the last tile in part past both edges, against the 64 x 64 per wave kernel."""
     M, N, K = 33000, 33024, 704
@@ -1445,7 +1466,9 @@ def test_gemm_small_and_rows_on_any_dword(M, N, K, off, word):
     if word == 32:
         np.testing.assert_array_equal(B.xnor_gemm_w32(A, W, K).cpu().numpy(), ri)
         assert ("gemm_small_kernel" in B.last_kernel()) != large
-        assert not large or words % 2 == 0 or "reg" in B.last_kernel()
+        with tuned(k19=1):  # (1100 x 2000 x 4000 is past the line from which the form of shared rows is ahead)
+            np.testing.assert_array_equal(B.xnor_gemm_w32(A, W, K).cpu().numpy(), ri)
+            assert not large or words % 2 == 0 or "reg" in B.last_kernel()
         return
     np.testing.assert_array_equal(B.xnor_gemm(A, W, K).cpu().numpy(), ri)
     assert ("gemm_small_kernel" in B.last_kernel()) != large

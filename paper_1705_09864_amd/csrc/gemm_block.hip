@@ -515,15 +515,18 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // every CU and no CU is given far more of them than another, or its SIMDs are there (6976 x 522 x 3840, 275 tiles on 256 CUs, 981
   // of 64 x 64 on 1024 SIMDs, 13.1 / 17.1; 768 x 5952 x 7291, 282 and 1116, 25.1 / 23.4, but 8192 x 540 x 768 9.3 / 9.9; 5504 x 320 x 4956, 129 tiles and the K
   // divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
-  // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, one workgroup a CU
-  // is ahead from a K of 8000 on (a layer of 1000 x 4000, K 2304 11.8 / 12.4, 9216 26.0 / 25.9).  Of the two shapes the larger
+  // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, up to two
+  // workgroups a CU (512) are ahead from a K of 3500 on only (352 layers of 256 to 900 tiles: 1000 x 4000, 256 tiles, K 1600 8.2 /
+  // 8.9, 2304 8.7 / 9.3, 4096 11.1 / 11.4, 9216 18.8 / 18.7; 2048 x 2048, 256, 2304 level, 4096 11.1 / 10.8; 1100 x 3700, 261,
+  // 1600 11.5 / 12.0, 9216 29.0 / 28.5; 2300 x 2000, 288, 2304 12.8 / 13.7, 8192 26.5 / 26.5; 1042 x 5092, 360, 2560 13.0 / 13.8;
+  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).  Of the two shapes the larger
   // needs many tiles per CU and a long K (8192^3 184 as 128 x 128, 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
   if (pinned) {
     if (any_dword) return false;
   } else if (gemm_block == 0) {
     if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
-    } else if (tiles < 256 || K < 700 || (C_f32 && tiles == 256 && K < 8000) ||
+    } else if (tiles < 256 || K < 700 || (C_f32 && tiles <= 512 && K < 3500) ||
                (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {
       return false;
     }

@@ -1279,16 +1279,23 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
 @pytest.mark.parametrize("M,N,K,kind,block", [
     # rows of an odd number of 32-bit words: from 513 tiles of 64 x 64 on
     (1032, 1995, 3995, "w32", True), (2137, 971, 3163, "w32", True), (1142, 1962, 987, "w32", True),
-    (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False)])
+    (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False),
+    # fp32 results of up to 512 tiles of 128 x 128: from a K of 3500 on; past that whatever the K, and int32 results too
+    (2048, 2048, 3499, "f32", False), (2000, 2040, 3500, "f32", True), (1900, 2500, 1664, "f32", False),
+    (1900, 2500, 3584, "f32", True), (2041, 4090, 1664, "f32", False), (2690, 3130, 1664, "f32", True), (1900, 2500, 1664, "i32", True)])
 def test_block_form_lines(M, N, K, kind, block):
     """Both sides of the lines between the kernel that stages rows once per workgroup and the 64 x 64 per wave kernel: the
     form that runs, and the same results from the other."""
     rng = np.random.default_rng(M + N + K)
     A = B.binarize_pack(dev(rng.standard_normal((M, K)).astype(np.float32)), 1)
     W = B.binarize_pack(dev(rng.standard_normal((N, K)).astype(np.float32)), 1)
-    words = -(-K // 32)
-    A, W = (t.view(torch.int32)[:, :words].contiguous() for t in (A, W))
-    call = lambda: B.xnor_gemm_w32(A, W, K)  # noqa: E731
+    if kind == "w32":
+        A, W = (t.view(torch.int32)[:, :-(-K // 32)].contiguous() for t in (A, W))
+        call = lambda: B.xnor_gemm_w32(A, W, K)  # noqa: E731
+    else:
+        A, W = (torch.nn.functional.pad(t, (0, t.shape[1] % 2)) for t in (A, W))  # (rows 16-byte aligned)
+        alpha = dev(rng.standard_normal(N).astype(np.float32)) if kind == "f32" else None
+        call = lambda: B.binary_fc_packed(A, K, W, alpha=alpha, mode=kind)  # noqa: E731
     got = call()
     assert ("block" in B.last_kernel()) == block, B.last_kernel()
     with tuned(k19=1 if block else 3):

@@ -519,8 +519,14 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // workgroups a CU (512) are ahead from a K of 3500 on only (352 layers of 256 to 900 tiles: 1000 x 4000, 256 tiles, K 1600 8.2 /
   // 8.9, 2304 8.7 / 9.3, 4096 11.1 / 11.4, 9216 18.8 / 18.7; 2048 x 2048, 256, 2304 level, 4096 11.1 / 10.8; 1100 x 3700, 261,
   // 1600 11.5 / 12.0, 9216 29.0 / 28.5; 2300 x 2000, 288, 2304 12.8 / 13.7, 8192 26.5 / 26.5; 1042 x 5092, 360, 2560 13.0 / 13.8;
-  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).  Of the two shapes the larger
-  // needs many tiles per CU and a long K (8192^3 184 as 128 x 128, 173 as 256 x 128; 8192 x 8192 x 2880 level; 8192 x 8192 x 1024 50 and 54).
+  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).
+  // The larger of the two shapes (us as 128 x 128 / as 256 x 128, each held for 50 ms): its waves read LDS and expand less for a
+  // product, which shows once the chip's power has settled, where the results leave in whole lines and fill many rounds:
+  // 8192 x 8192 x 8192 186 / 177, x 4096 106 / 102; 8192 x 12288 x 8192 277 / 263, 16384 x 8192 x 8192 370 / 352, 10240 x 10240 x
+  // 8192 289 / 278, 16384 x 4096 x 8192 187 / 176, 8130 x 8192 x 8192 187 / 178; in bursts of 2.5 ms 0 to 6 % behind to 3 % ahead.
+  // Rows of C that are no whole lines: 8150 x 8130 x 8192 204 / 212, 8192 x 8130 x 8192 205 / 208, 9000 x 9000 x 6000 201 / 202, 5000
+  // x 15000 x 9000 261 / 262.  Below 4096 tiles it depends on the last round: 8192 x 6144 x 8192 143 / 132, but 5120 x 5120 x 8192
+  // 78 / 85, 6144 x 6144 x 4096 60.5 / 62.4, 7168 x 7168 x 4096 83.5 / 84.3 (in bursts 77 / 86); 8192 x 8192 x 1024 50 / 54.
   if (pinned) {
     if (any_dword) return false;
   } else if (gemm_block == 0) {
@@ -556,7 +562,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   p.thr = nullptr;
   p.opad = p.oHp = p.oWp = p.oCw = 0;
-  const bool large = !any_dword && (pinned || (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096));
+  const bool large = !any_dword && (pinned || (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt));
   using namespace block;
   if (large) *err = C_i32 ? go<2, 4, 2, kI32, 16, false>(p, s) : go<2, 4, 2, kF32, 16, false>(p, s);
   else if (any_dword) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);

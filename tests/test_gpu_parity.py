@@ -1304,6 +1304,21 @@ def test_block_form_lines(M, N, K, kind, block):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("M,N,tall", [(8192, 8192, True), (8130, 8160, True), (8192, 8190, False), (8064, 8064, False)])
+def test_block_form_shape_line(M, N, tall):
+    """256 x 128 of C per workgroup from 4096 tiles of 128 x 128 on where C's rows are whole lines; the same results from
+    128 x 128."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N)
+    A, W = (torch.randint(-2 ** 62, 2 ** 62, (rows, 64), device="cuda", generator=g) for rows in (M, N))
+    got = B.xnor_gemm(A, W, 4096)
+    assert ("gemm_fp4_kernel<4,2,1,xnor,i32,block>" in B.last_kernel()) == tall, B.last_kernel()
+    with tuned(k19=3 if tall else 2):
+        want = B.xnor_gemm(A, W, 4096)
+        assert ("gemm_fp4_kernel<4,2,1,xnor,i32,block>" in B.last_kernel()) != tall, B.last_kernel()
+    assert torch.equal(got, want)
+
+
 def test_gemm_fp4_block_form_past_4_gib_of_results():
     """33000 x 33024 int32: rows of C past 4 GiB, the last tile in part past both edges, against the 64 x 64 per wave kernel."""
     M, N, K = 33000, 33024, 704

@@ -284,8 +284,7 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *          (1 also makes bmx_workspace_bytes count what the plane kernels need for k-bit weights)
  *   key 10 K-split waves of the latter kernel, key 11 = 2: its partial tiles cross LDS as fp32
  *          even where fp16 pairs would be exact, key 12 rows of tiles per band of its tile order
- *          (automatic: 16), key 13 = 1: xnor products never on the kernel of key 19, 2: on it with
- *          128 x 64 of C per wave wherever that form exists (rows 16-byte aligned, int32 or fp32 results)
+ *          (automatic: 16)
  *   key 14 = 1: the short-K matrix-core convolution kernel fetches pixel words 8 bytes at a time
  *          even where 16 would do; 2: 16 at a time, but never in the form for channel-word
  *          counts that are multiples of four; 3: never in the form that holds one block per wave
@@ -294,10 +293,11 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *   key 18 = 1: convolutions of packed images never take the kernel for small problems (nor while
  *          one of keys 1, 5, 7 and 14 pins another)
  *   key 17 = 1: xnor products never take the kernel for small problems (nor while any of keys 7 to
- *          13 pins one of the others)
- *   key 19 = 1: xnor products never take the kernel that stages operand rows once per workgroup (nor while
- *          any of keys 7 and 10 to 13 pins one of the others); 2, 3: that kernel with 256 x 128 (rows
- *          16-byte aligned) or 128 x 128 of C per workgroup, whatever the size (int32 or fp32 results)
+ *          12 pins one of the others, or key 19 its kernel)
+ *   key 19, or key 13, its older number = 1: xnor products never take the kernel that stages operand rows once per
+ *          workgroup (nor, automatically, while any of keys 7 and 10 to 12 pins one of the others); 2, 3: that kernel with
+ *          256 x 128 (rows 16-byte aligned) or 128 x 128 of C per workgroup, whatever the size and keys 10 to 12, unless
+ *          key 7 pins an engine other than FP4 through LDS (int32 or fp32 results)
  *   key 20 = 1: convolutions of packed images never take that kernel (nor while any of keys 1, 5, 7, 10 to 12
  *          and 14 pins another); 2, 3: its form with 128 filters x 128 pixels or 64 x 256 per workgroup, whatever the size
  *   key 8  K-split waves, key 9  tile variant (1: 32 x 32, 2: 64 x 64 per wave) of the matrix-core

@@ -89,7 +89,7 @@ extern "C" {
 int bmx_tune_set(int key, int value) {
   if (key == 0) {  // everything back to the automatic choice
     bmx::conv_filters_per_wave = bmx::gemm_tune_rows = bmx::gemm_tune_ksplit = bmx::gemm_tune_order = 0;
-    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::gemm_fp4_tall = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = bmx::conv_small = bmx::gemm_block = bmx::conv_block = 0;
+    bmx::conv_path = bmx::gemm_engine = bmx::gemm_mfma_ksplit = bmx::gemm_mfma_tile = bmx::gemm_fp4_split = bmx::gemm_fp4_half = bmx::gemm_fp4_band = bmx::conv_ws_x4 = bmx::fc_small = bmx::conv_one = bmx::gemm_small = bmx::conv_small = bmx::gemm_block = bmx::conv_block = 0;
     return BMX_OK;
   }
   if (key == 1) bmx::conv_filters_per_wave = value;
@@ -103,13 +103,12 @@ int bmx_tune_set(int key, int value) {
   else if (key == 10) bmx::gemm_fp4_split = value;
   else if (key == 11) bmx::gemm_fp4_half = value;
   else if (key == 12) bmx::gemm_fp4_band = value;
-  else if (key == 13) bmx::gemm_fp4_tall = value;
   else if (key == 14) bmx::conv_ws_x4 = value;
   else if (key == 15) bmx::fc_small = value;
   else if (key == 16) bmx::conv_one = value;
   else if (key == 17) bmx::gemm_small = value;
   else if (key == 18) bmx::conv_small = value;
-  else if (key == 19) bmx::gemm_block = value;
+  else if (key == 13 || key == 19) bmx::gemm_block = value;
   else if (key == 20) bmx::conv_block = value;
   else return BMX_ERR_UNSUPPORTED;
   return BMX_OK;

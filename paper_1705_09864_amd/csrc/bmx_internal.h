@@ -189,7 +189,7 @@ extern int gemm_block, conv_block;
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,
                      int stride, int pad, const float* alpha, int32_t* out_i32, float* out_f32, uint64_t* out_bits,
                      const float* thr, int out_pad, hipStream_t s, hipError_t* err);
-extern int gemm_fp4_split, gemm_fp4_half, gemm_fp4_band, gemm_fp4_tall;
+extern int gemm_fp4_split, gemm_fp4_half, gemm_fp4_band;
 // fc_small.hip: the whole fully connected layer (sign bits of the fp32 input, xor + popcount,
 // scale) in one launch, for layers too small to be worth two; false when the layer is not
 // small enough (nothing launched then).

@@ -485,7 +485,7 @@ hipError_t go(BlockParams& p, hipStream_t s) {
   p.div_last = make_fast_div((uint32_t)p.last_rows);
   p.tiles_per_xcd = (int)ceil_div((int64_t)p.tiles_m * p.tiles_n, 8);
   const unsigned blocks = 8u * (unsigned)p.tiles_per_xcd;
-  note_kernel("gemm_fp4_kernel<%d,%d,1,xnor,%s,%sblock%s%s> grid %u x 256, K split 1, fp4", TM, TN,
+  note_kernel("block::gemm_fp4_kernel<%d,%d,1,xnor,%s,%sblock%s%s> grid %u x 256, K split 1, fp4", TM, TN,
               OUT == kI32 ? "i32" : OUT == kBits ? "bits" : "f32", CONV ? "conv," : "", LW == 4 ? " of dwords" : "",
               WM == 1 ? " one high" : "", blocks);
   launch_kernel((gemm_fp4_kernel<WM, TM, TN, OUT, LW, CONV>), dim3(blocks), dim3(256), lds, s, p);
@@ -495,15 +495,13 @@ hipError_t go(BlockParams& p, hipStream_t s) {
 }  // namespace
 }  // namespace block
 
-int gemm_fp4_tall = 0;  // 1 = never this kernel; 2 = 256 x 128 of C per workgroup, with gemm_fp4.hip's choices pinned too
 int gemm_block = 0;  // 1 = never, 2 = 256 x 128 and 3 = 128 x 128 of C per workgroup whatever the size
 
 bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t ldb_bytes, int M, int N, int K, int dwords,
                        const float* alpha, int32_t* C_i32, float* C_f32, int64_t ldc, bool as_count, hipStream_t s,
                        hipError_t* err) {
-  const bool pinned = gemm_fp4_tall == 2 && (gemm_engine == 0 || gemm_engine == 3 || gemm_engine == 5) && gemm_fp4_split <= 1;
-  if (gemm_block == 1 || (!pinned && (gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band || gemm_fp4_tall)))
-    return false;
+  if (gemm_block == 1 || gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
+  if (gemm_block == 0 && (gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band)) return false;
   const bool any_dword = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(tiles, 256);
   // Against gemm_fp4.hip, from 220 products of up to 8192 x 8192 x 8192 measured on both (us, there / here).  Rows that
@@ -527,9 +525,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // Rows of C that are no whole lines: 8150 x 8130 x 8192 204 / 212, 8192 x 8130 x 8192 205 / 208, 9000 x 9000 x 6000 201 / 202, 5000
   // x 15000 x 9000 261 / 262.  Below 4096 tiles it depends on the last round: 8192 x 6144 x 8192 143 / 132, but 5120 x 5120 x 8192
   // 78 / 85, 6144 x 6144 x 4096 60.5 / 62.4, 7168 x 7168 x 4096 83.5 / 84.3 (in bursts 77 / 86); 8192 x 8192 x 1024 50 / 54.
-  if (pinned) {
-    if (any_dword) return false;
-  } else if (gemm_block == 0) {
+  if (gemm_block == 0) {
     if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
     } else if (tiles < 256 || K < 700 || (C_f32 && tiles <= 512 && K < 3500) ||
@@ -562,7 +558,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   p.thr = nullptr;
   p.opad = p.oHp = p.oWp = p.oCw = 0;
-  const bool large = !any_dword && (pinned || (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt));
+  const bool large = !any_dword && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt);
   using namespace block;
   if (large) *err = C_i32 ? go<2, 4, 2, kI32, 16, false>(p, s) : go<2, 4, 2, kF32, 16, false>(p, s);
   else if (any_dword) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);

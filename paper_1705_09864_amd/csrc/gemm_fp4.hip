@@ -233,15 +233,17 @@ namespace {
 // Output kinds of the xnor form (the plane form stores S and / or S / levels as its pointers say).
 constexpr int kOutF32 = 0, kOutI32 = 1, kOutBits = 2;
 
-// TM x TN blocks of 32 x 32 per wave; PL bit planes per A row; XNOR: the xnor form (row
-// popcounts from the words themselves), else the plane form (row sums given); OUT: what the
+// TM x TN blocks of 32 x 32 per wave
+constexpr int TM = 2, TN = 2;
+
+// PL bit planes per A row; XNOR: the xnor form (row popcounts from the words themselves), else the plane form (row sums given); OUT: what the
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
 // HALF: the partial tiles of a split cross LDS as fp16 pairs (exact while a wave's sums stay
 // at or below 2048, which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
 // segments travel through registers (see fetch_segment; 2: rows that start on any dword).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
 __global__ void __launch_bounds__(512)
 gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #ifdef BMX_FP4_STAMPS
@@ -333,11 +335,9 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   // put a trip to memory between the main loop and the stores; and ahead of the segments'
   // loads they do not disturb the count of loads in flight that the main loop relies on).  Per column of
   // this lane (column 32 j + r): alpha and the threshold of the sign decision; per row of the
-  // tile, row m0 + l in lane l: the row sum of the plane form, alpha of the convolution form.
-  static_assert(TM == 2, "one lane per row of the tile");
+  // tile (64 of them), row m0 + l in lane l: the row sum of the plane form, alpha of the convolution form.
   // (plain variables, not arrays: indexed by a run-time j in the reduction below, an array is
   // put into scratch memory, whose every access also waits for the stores issued before it)
-  static_assert(TN == 2, "two column blocks");
   const int n_c0 = min(n0 + r, p.N - 1), n_c1 = min(n0 + 32 + r, p.N - 1);
   float aln0 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c0] : 1.0f;
   float aln1 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c1] : 1.0f;
@@ -648,12 +648,11 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   // FULL: all eight waves split K (the usual case): no partial has to be masked out
   auto reduce = [&](auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
-    // full-K popcounts: lane l sums row l of the tile (TM = 2: 64 rows) and column l over the S
+    // full-K popcounts: lane l sums row l of the tile (64 rows) and column l over the S
     // waves' counts, one conflict-free read each; a lane then picks the rows and the column of
     // its own results out of other lanes' registers
     int pa_tot = rowsum_l, pb_tot = 0;  // (plane form: the row sum stands where the row count would)
     if (XNOR) {
-      static_assert((TM == 2 && TN == 2) || !SPLIT, "one lane per row and per column of the tile");
       int ca[8], cb8[8];
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
@@ -786,14 +785,14 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 int gemm_fp4_half = 0;  // 2 = keep fp32 partials (tests of both forms)
 namespace {
 
-template <int TM, int TN, int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   constexpr int NB = TM * PL + TN, kStage = NB * 128, kGroups = TM * TN * 4, kCnt = (TM + TN) * 8;
   constexpr int part = HALF ? kGroups * 32 : kGroups * 64;
   constexpr int slot = (!SPLIT || kStage > part + kCnt) ? kStage : part + kCnt;
   const int waves = SPLIT ? S : tiles_per_wg;
   const size_t lds = (size_t)waves * slot * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
-  auto kern = gemm_fp4_kernel<TM, TN, PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
+  auto kern = gemm_fp4_kernel<PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
@@ -829,10 +828,10 @@ hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blo
     // are exact in fp16
     const int64_t most = (int64_t)(p.g_base + (p.g_rem ? 1 : 0)) * 256 * ((1 << PL) - 1);
     if (most <= 2048 && gemm_fp4_half != 2)
-      return launch_tile<2, 2, PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s);
-    return launch_tile<2, 2, PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+      return launch_tile<PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+    return launch_tile<PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
   }
-  return launch_tile<2, 2, PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+  return launch_tile<PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
 }
 
 }  // namespace

@@ -175,7 +175,7 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
                        const float* alpha, int32_t* C_i32, float* C_f32, uint64_t* C_bits, const float* thr, int64_t ldc,
                        bool as_count, hipStream_t s, hipError_t* err) {
   if (gemm_small == 1 || gemm_engine || gemm_mfma_ksplit || gemm_mfma_tile || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band ||
-      gemm_fp4_tall)
+      gemm_block > 1)
     return false;
   if (K >= (1 << 24)) return false;
   const int64_t lim = (int64_t)1 << 31;

@@ -1185,13 +1185,15 @@ def test_gemm_fp4_chip_filling_problem_exact():
     with tuned(k7=1):
         ref = B.xnor_gemm(Ad, Bd, K)
         assert "gemm_kernel" in B.last_kernel()
-    # tile order: automatic bands, ragged bands, none; tile: 64 x 64 per wave (the automatic
-    # choice at this size) and 128 x 64
-    for band, tall in ((0, 0), (3, 0), (1000, 0), (0, 2), (3, 2)):
+    # the automatic choice at this size (rows staged once per workgroup, 64 x 64 per wave); the 64 x 64 per wave kernel that
+    # stages its own rows, pinned by its tile order: bands that leave a rest, as many rows as C, its own choice; and shared
+    # rows with 128 x 64 per wave
+    for band, tall in ((0, 0), (3, 0), (1000, 0), (16, 0), (0, 2), (3, 2)):
         with tuned(k12=band, k13=tall):
             for rep in range(6):
                 got = B.xnor_gemm(Ad, Bd, K)
                 assert "gemm_fp4_kernel<%d,2,1" % (4 if tall else 2) in B.last_kernel() and "K split 1," in B.last_kernel()
+                assert B.last_kernel().startswith("block::") == (band == 0 or tall > 0)
                 assert torch.equal(got, ref), "band %d tall %d repetition %d: %d elements differ" % (
                     band, tall, rep, int((got != ref).sum()))
     rows = np.sort(rng.choice(M, size=96, replace=False))
@@ -1200,8 +1202,9 @@ def test_gemm_fp4_chip_filling_problem_exact():
 
 
 def test_gemm_fp4_tall_tile():
-    """The same kernel with 128 x 64 of C per wave (no K split; the automatic choice only for
-    chip-filling products), forced on small and ragged problems: fewer rows than a tile, ragged
+    """The kernel that stages rows once per workgroup with 128 x 64 of C per wave, 256 x 128 per workgroup (the
+    automatic choice only for chip-filling products), forced on small and ragged problems by the key's older
+    number, beside the other kernel's keys: fewer rows than a tile, ragged
     tiles in M and N, rows that end inside a 64-byte segment, strides wider than the rows with
     garbage behind them, int32, xnor-count and scaled fp32 results."""
     rng = np.random.default_rng(1313)
@@ -1218,7 +1221,7 @@ def test_gemm_fp4_tall_tile():
             Bd = np.full((N, ld), POISON, dtype=np.uint64); Bd[:, :A.shape[1]] = Bm
             want = oracle.xnor_gemm(A, Bm, K)
             got = B.xnor_gemm(dev(Ad.view(np.int64)), dev(Bd.view(np.int64)), K).cpu().numpy()
-            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel()
+            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel() and B.last_kernel().startswith("block::")
             np.testing.assert_array_equal(got, want)
             cnt = B.xnor_gemm(dev(Ad.view(np.int64)), dev(Bd.view(np.int64)), K, count=True).cpu().numpy()
             np.testing.assert_array_equal(2 * cnt - K, want)
@@ -1232,9 +1235,9 @@ def test_gemm_fp4_tall_tile():
             if Wp.shape[1] % 2:                                      # 16-byte rows for the matrix-core kernels
                 Wp = torch.cat([Wp, torch.zeros_like(Wp[:, :1])], dim=1).contiguous()
             np.testing.assert_array_equal(B.binary_fc(dev(x), Wp, integer_out=True).cpu().numpy(), ri)
-            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel()
+            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel() and B.last_kernel().startswith("block::")
             assert_f32_close(B.binary_fc(dev(x), Wp, alpha=dev(alpha)).cpu().numpy(), rf)
-            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel()
+            assert "gemm_fp4_kernel<4,2,1" in B.last_kernel() and B.last_kernel().startswith("block::")
 
 
 @pytest.mark.parametrize("form", [2, 3])
@@ -1359,7 +1362,7 @@ def test_gemm_fp4_lds_staged_kernel(split, partials):
             Bd = np.full((N, ld), POISON, dtype=np.uint64); Bd[:, :A.shape[1]] = Bm
             want = oracle.xnor_gemm(A, Bm, K)
             got = B.xnor_gemm(dev(Ad.view(np.int64)), dev(Bd.view(np.int64)), K).cpu().numpy()
-            assert "gemm_fp4_kernel" in B.last_kernel()
+            assert B.last_kernel().startswith("gemm_fp4_kernel<2,2,1,xnor")
             np.testing.assert_array_equal(got, want)
             cnt = B.xnor_gemm(dev(Ad.view(np.int64)), dev(Bd.view(np.int64)), K, count=True).cpu().numpy()
             np.testing.assert_array_equal(2 * cnt - K, want)

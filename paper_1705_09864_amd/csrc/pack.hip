@@ -259,6 +259,7 @@ struct PackNchwParams {
   uint64_t* xp;
   int C, HW, W, pad, Hp, Wp, Cw;
   uint32_t pixels, halo;  // of all images; halo: halo pixels of all images
+  uint32_t first;         // the launch's first pixel
   FastDiv div_hw, div_w, div_nh;
 };
 
@@ -267,13 +268,13 @@ __global__ void __launch_bounds__(256)
 pack_nchw_kernel(const PackNchwParams p) {
   __shared__ uint16_t bits[64 * 4];
   asm volatile("" ::"s"(p.x), "s"(p.xp), "s"(p.C), "s"(p.HW), "s"(p.W), "s"(p.pad), "s"(p.Hp), "s"(p.Wp), "s"(p.Cw), "s"(p.pixels),
-               "s"(p.div_hw.mul), "s"(p.div_hw.sh1), "s"(p.div_hw.sh2), "s"(p.div_w.mul), "s"(p.div_w.sh1), "s"(p.div_w.sh2));
+               "s"(p.first), "s"(p.div_hw.mul), "s"(p.div_hw.sh1), "s"(p.div_hw.sh2), "s"(p.div_w.mul), "s"(p.div_w.sh1), "s"(p.div_w.sh2));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cw = blockIdx.y, c0 = cw * 64 + wave * 16, real = min(16, p.C - c0);  // (real <= 0: channels past the last)
   // Workgroup b sits on XCD b % 8: every XCD gets a contiguous run of pixels, whose neighbours share lines
   // where planes are not whole ones (57 MB of 44 x 43 planes 14.1 us without).
-  const uint32_t q = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 64 + lane;
+  const uint32_t q = p.first + ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 64 + lane;
   const uint32_t qc = min(q, p.pixels - 1);  // lanes past the last pixel repeat it
   const uint32_t n = fast_div(qc, p.div_hw), px = qc - n * (uint32_t)p.HW;
   float v[16];
@@ -343,12 +344,16 @@ hipError_t launch_pack_nchw_thr(const float* x, int N, int C, int H, int W, int 
     p.x = x + (int64_t)n0 * C * p.HW;
     p.xp = xp + (int64_t)n0 * p.Hp * p.Wp * p.Cw;
     p.pixels = (uint32_t)n * (uint32_t)p.HW;
-    p.halo = (uint32_t)n * (uint32_t)nh;
-    const dim3 grid((unsigned)ceil_div(p.pixels, 512) * 8, (unsigned)p.Cw);
-    note_kernel("pack_nchw_kernel<%s> grid %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y);
     auto kern = thr ? (nt ? pack_nchw_kernel<true, true> : pack_nchw_kernel<true, false>)
                     : (nt ? pack_nchw_kernel<false, true> : pack_nchw_kernel<false, false>);
-    launch_kernel(kern, grid, dim3(256), 0, s, p);
+    // four threads a pixel, and less than 2^32 threads a launch
+    for (uint64_t first = 0; first < p.pixels; first += 1u << 29) {
+      p.first = (uint32_t)first;
+      p.halo = first ? 0 : (uint32_t)n * (uint32_t)nh;
+      const dim3 grid((unsigned)ceil_div(std::min(p.pixels - p.first, 1u << 29), 512) * 8, (unsigned)p.Cw);
+      note_kernel("pack_nchw_kernel<%s> grid %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y);
+      launch_kernel(kern, grid, dim3(256), 0, s, p);
+    }
   }
   return launch_error();
 }

@@ -77,6 +77,18 @@ def test_conv_special_values_in_the_image():
     np.testing.assert_array_equal(xp.reshape(-1, 2), oracle.binarize_pack(rows, 1))
 
 
+@pytest.mark.parametrize("N,H,W", [(65535, 129, 129), (1, 32768, 32768)])
+def test_channel_pack_of_2_to_30_pixels(N, H, W):
+    """More pixels than a launch has threads for, over many images and in one: every word, halo included."""
+    x = torch.empty((N, 1, H, W), device="cuda").uniform_(-1.0, 1.0)
+    xp = B.pack_nchw(x, 1).view(N, H + 2, W + 2)
+    assert torch.equal(xp[:, 1:-1, 1:-1], (x >= 0).view(N, H, W).to(torch.int64))
+    xp[:, 1:-1, 1:-1] = 1
+    assert bool((xp == 1).all())
+    del x, xp
+    torch.cuda.empty_cache()
+
+
 def test_pack_rows_strided_and_poisoned():
     rng = np.random.default_rng(11)
     rows, K, ldx, ld = 6, 200, 260, 6

@@ -24,6 +24,7 @@
 
 #include "bmx_internal.h"
 #include "conv_expand.h"
+#include "halo.h"
 
 namespace bmx {
 
@@ -274,29 +275,10 @@ conv_mfma_ws_kernel(const WsParams p WS_STAMP_ARG) {
 
   // (behind the first fetch, so that its index arithmetic runs under the loads)
   if (BITS && p.opad > 0 && (m0 & 63) == 0) {
-    // halo of the output image, word m0 / 64 of every halo pixel: every real channel +1 (the
-    // sign of the next layer's zero padding), missing channels 0; spread over the workgroups of
-    // this filter tile (left to one of them, its few thousand index computations set the
-    // duration of the whole launch)
-    const int cw = m0 >> 6;
-    const uint64_t ones = (cw == p.oCw - 1 && (p.O & 63)) ? (((uint64_t)1 << (p.O & 63)) - 1) : ~(uint64_t)0;
-    const int nh = p.oHp * p.oWp - p.HoWo;
-    uint64_t* ob = (uint64_t*)p.out_bits;
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < nh * p.Nimg; i += gridDim.x * kThreads) {
-      const int n = i / nh, k = i - n * nh;
-      int hh, ww;
-      if (k < 2 * p.opad * p.oWp) {  // rows above and below
-        hh = k / p.oWp;
-        ww = k - hh * p.oWp;
-        if (hh >= p.opad) hh += p.Ho;
-      } else {  // left and right of the interior rows
-        const int j = k - 2 * p.opad * p.oWp;
-        const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
-        hh = p.opad + rr;
-        ww = c < p.opad ? c : p.Wo + c;
-      }
-      ob[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + cw] = ones;
-    }
+    // word m0 / 64 of the output image's halo, spread over the workgroups of this filter tile (left to one of them, its
+    // few thousand index computations set the duration of the whole launch)
+    write_halo((uint64_t*)p.out_bits, p.Nimg, p.Ho, p.Wo, p.opad, p.O, p.oCw, m0 >> 6, blockIdx.x * kThreads + threadIdx.x,
+               gridDim.x * kThreads);
   }
 
   {

@@ -16,6 +16,7 @@
 // 7x7 6.7 / 9.0 and 7.2 / 14.2.
 
 #include "bmx_internal.h"
+#include "halo.h"
 
 namespace bmx {
 
@@ -101,27 +102,9 @@ conv_small_kernel(const SmallConvParams p) {
   const float th_l = (OUT == kBits && p.thr) ? p.thr[mrow] : 0.0f;
 
   if (OUT == kBits && p.opad > 0 && (m0 & 63) == 0) {
-    // word m0 / 64 of the output image's halo: +1 (the sign of the next layer's zero padding) for every
-    // real channel, spread over the workgroups of this filter tile
-    const int cw = m0 >> 6;
-    const uint64_t ones = (cw == p.oCw - 1 && (p.O & 63)) ? (((uint64_t)1 << (p.O & 63)) - 1) : ~(uint64_t)0;
-    const int nh = p.oHp * p.oWp - p.HoWo;
-    uint64_t* const ob = (uint64_t*)p.out;
-    for (int i = blockIdx.x * (64 * S) + threadIdx.x; i < nh * p.Nimg; i += gridDim.x * (64 * S)) {
-      const int n = i / nh, k = i - n * nh;
-      int hh, ww;
-      if (k < 2 * p.opad * p.oWp) {  // rows above and below
-        hh = k / p.oWp;
-        ww = k - hh * p.oWp;
-        if (hh >= p.opad) hh += p.Ho;
-      } else {  // left and right of the interior rows
-        const int j = k - 2 * p.opad * p.oWp;
-        const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
-        hh = p.opad + rr;
-        ww = c < p.opad ? c : p.Wo + c;
-      }
-      ob[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + cw] = ones;
-    }
+    // word m0 / 64 of the output image's halo, spread over the workgroups of this filter tile
+    write_halo((uint64_t*)p.out, p.Nimg, p.Ho, p.Wo, p.opad, p.O, p.oCw, m0 >> 6, blockIdx.x * (64 * S) + threadIdx.x,
+               gridDim.x * (64 * S));
   }
 
   v16f acc;

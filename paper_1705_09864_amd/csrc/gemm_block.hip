@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "bmx_internal.h"
+#include "halo.h"
 
 namespace bmx {
 
@@ -303,27 +304,9 @@ gemm_fp4_kernel(const BlockParams p) {
   issue(0, 0);
   if (p.nseg > 1) issue(1, 1);
   if constexpr (OUT == kBits) {
-    // the tile's words of the output image's halo: +1 (the sign of the next layer's zero padding) for every real channel,
-    // spread over the tiles of this row of tiles
-    for (int cw = m0 >> 6; p.opad > 0 && cw < min(p.oCw, (m0 >> 6) + WM); ++cw) {
-      const uint64_t ones = (cw == p.oCw - 1 && (p.M & 63)) ? (((uint64_t)1 << (p.M & 63)) - 1) : ~(uint64_t)0;
-      const int nh = p.oHp * p.oWp - p.HoWo;
-      for (int i = tile_n * 256 + (int)threadIdx.x; i < nh * p.Nimg; i += p.tiles_n * 256) {
-        const int n = i / nh, k = i - n * nh;
-        int hh, ww;
-        if (k < 2 * p.opad * p.oWp) {  // rows above and below
-          hh = k / p.oWp;
-          ww = k - hh * p.oWp;
-          if (hh >= p.opad) hh += p.Ho;
-        } else {  // left and right of the interior rows
-          const int j = k - 2 * p.opad * p.oWp;
-          const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
-          hh = p.opad + rr;
-          ww = c < p.opad ? c : p.Wo + c;
-        }
-        ((uint64_t*)p.C)[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + cw] = ones;
-      }
-    }
+    // the tile's words of the output image's halo, spread over the tiles of this row of tiles
+    for (int cw = m0 >> 6; p.opad > 0 && cw < min(p.oCw, (m0 >> 6) + WM); ++cw)
+      write_halo((uint64_t*)p.C, p.Nimg, p.Ho, p.Wo, p.opad, p.M, p.oCw, cw, tile_n * 256 + threadIdx.x, p.tiles_n * 256);
   }
   if (p.nseg > 1) {
     constexpr int kLoads = HA * (LWA == 16 ? 1 : 4) + HB * (LW == 16 ? 1 : 4);  // a wave's loads per segment

@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "bmx_internal.h"
+#include "halo.h"
 
 namespace bmx {
 
@@ -353,27 +354,11 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
   }
   if constexpr (CONV && OUT == kOutBits) {
-    // word tile_m of the output image's halo: +1 (the sign of the next layer's zero padding) for every real
-    // channel, spread over the tiles of this row of tiles
+    // word tile_m of the output image's halo, spread over the tiles of this row of tiles
     if (p.opad > 0 && live) {
-      const uint64_t ones = (tile_m == p.oCw - 1 && (p.M & 63)) ? (((uint64_t)1 << (p.M & 63)) - 1) : ~(uint64_t)0;
-      const int nh = p.oHp * p.oWp - p.HoWo, per_tile = SPLIT ? (int)blockDim.x : 64;
-      uint64_t* const ob = (uint64_t*)p.C_bits;
-      for (int i = tile_n * per_tile + (SPLIT ? (int)threadIdx.x : lane); i < nh * p.Nimg; i += p.tiles_n * per_tile) {
-        const int n = i / nh, k = i - n * nh;
-        int hh, ww;
-        if (k < 2 * p.opad * p.oWp) {  // rows above and below
-          hh = k / p.oWp;
-          ww = k - hh * p.oWp;
-          if (hh >= p.opad) hh += p.Ho;
-        } else {  // left and right of the interior rows
-          const int j = k - 2 * p.opad * p.oWp;
-          const int rr = j / (2 * p.opad), c = j - rr * (2 * p.opad);
-          hh = p.opad + rr;
-          ww = c < p.opad ? c : p.Wo + c;
-        }
-        ob[(((int64_t)n * p.oHp + hh) * p.oWp + ww) * p.oCw + tile_m] = ones;
-      }
+      const int per_tile = SPLIT ? (int)blockDim.x : 64;
+      write_halo((uint64_t*)p.C_bits, p.Nimg, p.Ho, p.Wo, p.opad, p.M, p.oCw, tile_m,
+                 tile_n * per_tile + (SPLIT ? threadIdx.x : lane), p.tiles_n * per_tile);
     }
   }
   FP4_STAMP(1);

@@ -2,6 +2,7 @@
 // Paper: Sec. 1 (sign binarisation, 64 values per word), Sec. 3.1 (the per-forward
 // input binarisation step), Sec. 2.1 Eq. 1 (k-bit quantiser).
 #include "bmx_internal.h"
+#include "halo.h"
 
 #include <algorithm>
 
@@ -257,10 +258,9 @@ struct PackNchwParams {
   const float* x;
   const float* thr;
   uint64_t* xp;
-  int C, HW, W, pad, Hp, Wp, Cw;
-  uint32_t pixels, halo;  // of all images; halo: halo pixels of all images
-  uint32_t first;         // the launch's first pixel
-  FastDiv div_hw, div_w, div_nh;
+  int images, C, HW, H, W, pad, Hp, Wp, Cw;
+  uint32_t pixels, first;  // of all images; the launch's first
+  FastDiv div_hw, div_w;
 };
 
 template <bool THR, bool NT>
@@ -288,25 +288,8 @@ pack_nchw_kernel(const PackNchwParams p) {
     }
   }
   const uint32_t h = fast_div(px, p.div_w), w = px - h * (uint32_t)p.W;
-  if (p.pad > 0) {
-    const uint64_t ones = (cw == p.Cw - 1 && (p.C & 63)) ? (((uint64_t)1 << (p.C & 63)) - 1) : ~(uint64_t)0;
-    const int H = p.HW / p.W, side = 2 * p.pad;
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < p.halo; i += gridDim.x * 256) {
-      const uint32_t in = fast_div(i, p.div_nh);
-      const int k = (int)(i - in * (uint32_t)(p.Hp * p.Wp - p.HW));
-      int hh, ww;
-      if (k < side * p.Wp) {  // rows above and below
-        hh = k / p.Wp;
-        ww = k - hh * p.Wp;
-        if (hh >= p.pad) hh += H;
-      } else {
-        const int j = k - side * p.Wp, r = j / side, c = j - r * side;
-        hh = p.pad + r;
-        ww = c < p.pad ? c : p.W + c;
-      }
-      p.xp[(((int64_t)in * p.Hp + hh) * p.Wp + ww) * p.Cw + cw] = ones;
-    }
-  }
+  if (p.pad > 0 && p.first == 0)
+    write_halo(p.xp, p.images, p.H, p.W, p.pad, p.C, p.Cw, cw, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
   uint32_t b = 0;
   if (real > 0) {
 #pragma unroll
@@ -327,15 +310,14 @@ hipError_t launch_pack_nchw_thr(const float* x, int N, int C, int H, int W, int 
   p.thr = thr;
   p.C = C;
   p.HW = H * W;
+  p.H = H;
   p.W = W;
   p.pad = pad;
   p.Hp = H + 2 * pad;
   p.Wp = W + 2 * pad;
   p.Cw = (int)words_for(C);
-  const int nh = p.Hp * p.Wp - p.HW;
   p.div_hw = make_fast_div((uint32_t)p.HW);
   p.div_w = make_fast_div((uint32_t)W);
-  p.div_nh = make_fast_div((uint32_t)(nh > 0 ? nh : 1));
   const bool nt = p.HW % 32 == 0 && ((uintptr_t)x & 127) == 0;
   // images per launch: all of them unless they have 2^31 padded pixels or more
   const int most = (int)std::min<int64_t>(N, (((int64_t)1 << 31) - 1) / ((int64_t)p.Hp * p.Wp));
@@ -343,13 +325,13 @@ hipError_t launch_pack_nchw_thr(const float* x, int N, int C, int H, int W, int 
     const int n = std::min(most, N - n0);
     p.x = x + (int64_t)n0 * C * p.HW;
     p.xp = xp + (int64_t)n0 * p.Hp * p.Wp * p.Cw;
+    p.images = n;
     p.pixels = (uint32_t)n * (uint32_t)p.HW;
     auto kern = thr ? (nt ? pack_nchw_kernel<true, true> : pack_nchw_kernel<true, false>)
                     : (nt ? pack_nchw_kernel<false, true> : pack_nchw_kernel<false, false>);
     // four threads a pixel, and less than 2^32 threads a launch
     for (uint64_t first = 0; first < p.pixels; first += 1u << 29) {
       p.first = (uint32_t)first;
-      p.halo = first ? 0 : (uint32_t)n * (uint32_t)nh;
       const dim3 grid((unsigned)ceil_div(std::min(p.pixels - p.first, 1u << 29), 512) * 8, (unsigned)p.Cw);
       note_kernel("pack_nchw_kernel<%s> grid %u x %u x 256", thr ? "thr" : "sign", grid.x, grid.y);
       launch_kernel(kern, grid, dim3(256), 0, s, p);

@@ -30,7 +30,8 @@ paper's own method (xnor + popcount on 64-bit words, OpenMP) beside it.
 `--phase NAME` runs one section only (headline, config1, config2, config4, config5, sec31, biggemm,
 packs, probe): the workload of the per-configuration rocprofv3 summaries under profiles/.
 `--phase cases` (never part of the default run) times the listed cases of perf/cases.py as a program calls
-them, one call after the other with the host's share in, on buffers that are reused.
+them, one call after the other with the host's share in, on three sets of inputs and weights in turn (from HBM
+where a set is large; results where the allocator puts them, as in a program).
 """
 import argparse
 import ctypes
@@ -634,22 +635,23 @@ def main():
     if args.phase == "cases":
         from perf import cases
         for i, case in enumerate(cases.listed()):
-            state = cases.prepare(case, i)
+            states = [cases.prepare(case, i + k) for k in range(3)]
             passes = 0
             t0 = time.perf_counter()
             while passes < 20 or (time.perf_counter() - t0 < 0.05 and passes < 20000):
-                cases.run(state)
+                cases.run(states[passes % 3])
                 passes += 1
             torch.cuda.synchronize()
             rounds = []
             for _ in range(7):
                 t0 = time.perf_counter()
-                for _ in range(passes):
-                    cases.run(state)
+                for k in range(passes):
+                    cases.run(states[k % 3])
                 torch.cuda.synchronize()
                 rounds.append((time.perf_counter() - t0) / passes * 1e6)
-            other["case_" + case["name"]] = {"call_us": sorted(rounds)[3], "passes": passes, "last_kernel": B.last_kernel()}
-            del state
+            other["case_" + case["name"]] = {"call_us": sorted(rounds)[3], "passes": passes, "buffer_sets_rotated": 3,
+                                              "last_kernel": B.last_kernel()}
+            del states
             torch.cuda.empty_cache()
 
     # ------------------------------------------------------------------ CPU oracle beside it

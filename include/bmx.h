@@ -234,7 +234,8 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
 
 /* k-bit activations x 1-bit or k-bit weights (Sec. 1: arbitrary bit widths after DoReFa-Net;
  * Sec. 2.1, Eq. 1).  a in [0, 1] (clamped) is quantised to the integer level
- * q = round((2^bits_a - 1) * a), ties away from zero, and split into bits_a bit planes.
+ * q = round((2^bits_a - 1) * a), ties away from zero, and split into bits_a bit planes.  NaN is level 0 (of a k-bit
+ * weight too; -1 as a one-bit weight).
  * bits_w = 1: w is binarised with the sign function.  With wb the weight bits,
  *   S[m][n] = sum_k q[m][k] * sign(w[n][k])
  *           = 2 * sum_p 2^p popcount(plane_p[m] & wb[n]) - sum_p 2^p popcount(plane_p[m]),

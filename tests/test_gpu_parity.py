@@ -1656,6 +1656,23 @@ def test_quantiser_ties_on_every_form(bits, rows, engine):
         np.testing.assert_array_equal(S.cpu().numpy(), rS, err_msg=B.last_kernel())
 
 
+@pytest.mark.parametrize("bits", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("M,N,K,engine", [(70, 60, 1100, {"k7": 1}), (300, 290, 2100, {"k7": 3}), (300, 290, 2100, {}), (5, 9, 130, {})])
+def test_quantiser_takes_nan_as_zero(M, N, K, engine, bits):
+    """NaN of either sign is level 0 of an activation and of a k-bit weight, and -1 as a one-bit weight, on every form: planes
+    (the popcount and the FP4 kernels), bytes, one launch."""
+    rng = np.random.default_rng(M + K + bits)
+    a, w = rng.uniform(-0.1, 1.1, (M, K)).astype(np.float32), rng.uniform(-1, 1, (N, K)).astype(np.float32)
+    for t in (a, w):
+        t[rng.random(t.shape) < 0.1] = np.nan
+        t[rng.random(t.shape) < 0.1] = -np.nan
+    for bw in (1, bits):
+        rS, _, _ = oracle.quant_gemm(np.nan_to_num(a, nan=0.0), np.nan_to_num(w, nan=-1.0), bits, bw)
+        with tuned(**engine):
+            S, _ = B.quant_gemm(dev(a), dev(w), bits, bw, want_float=False)
+        np.testing.assert_array_equal(S.cpu().numpy(), rS, err_msg=B.last_kernel())
+
+
 # ------------------------------------------------------------------ few bits: bytes or planes
 @pytest.mark.parametrize("M,N,K,bits_a,bytes_form", [
     (16, 2048, 8192, 2, False), (32, 1900, 8192, 2, False), (16, 200, 16384, 1, False), (100, 32, 10000, 2, True),

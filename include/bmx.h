@@ -224,7 +224,9 @@ int bmx_binary_conv2d_packed(const uint64_t* xp, int N, int C, int H, int W, con
  *   workspace >= bmx_workspace_bytes(BMX_OP_BINARY_CONV2D_BITS, {N,C,H,W,O,KH,KW,stride,pad,
  *          out_pad}, 10): 0 where the convolution kernel writes the bits itself (3 x 3 kernels
  *          over at most 256 channels, 5 x 5 over at most 128, 7 x 7 over at most 64), else room
- *          for the fp32 result, which then passes through the channel pack with the same compare.
+ *          for the fp32 result.  Other kernels write the bits themselves too; where none can (packed images
+ *          or results of 4 GiB and more, Wp not 16-byte aligned, a kernel pinned that cannot) the fp32 result passes
+ *          through the channel pack with the same compare.  The room is asked for whichever of them runs.
  *          For the shapes whose query answers 0, Wp must be 16-byte aligned (BMX_ERR_ALIGN
  *          otherwise): a workspace sized by the query is always enough. */
 int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const uint64_t* Wp, int O,

@@ -6,9 +6,7 @@
 //
 // There every wave fetches the rows of its own tile, waits for its own reads of a segment before it may request
 // the next, and turns all of a segment's bits into operands before it multiplies.  With the chip full that
-// leaves the matrix cores half idle: 8192^3 took 202 us, where a loop of the same multiplications on bits that
-// stand in LDS takes 145 (their power holds the clock at 2.1 to 2.3 GHz, and every MFMA keeps the SIMD's issue
-// slot for about 16 of its 32 clocks).  Here:
+// leaves the matrix cores half idle: 8192^3 took 202 us, of which its products are 109 at 2.4 GHz.  Here:
 //   - Four waves, two by two, share the rows of a workgroup's tile of C: 256 x 128 (128 x 64 per wave, 244
 //     registers, two workgroups on a CU) or 128 x 128 (64 x 64 per wave, 146 registers, three).  Rows cross the
 //     L2 once per workgroup.  Several workgroups per CU rather than one large one, so that one's results leave
@@ -26,6 +24,10 @@
 //     the next convolution's packed image, halo included.
 //   (Three and four stages in flight changed nothing, at 8192^3 or with one workgroup per CU: it is issue and, with
 //   one wave on a SIMD, the chain of its own instructions that bounds the loop, not the memory behind it.)
+// What bounds it, from counters at 8192^3 as 256 x 128: the matrix pipe is busy in 70 % of the clocks, a SIMD issues an
+// instruction in 77 % of them (5.2 of the vector ALU for every MFMA), a wave waits for data or a barrier in 11 % of its time; and
+// the clock stands at 2.0 to 2.2 GHz under that load.  The same launch back to back takes 182 us in the first millisecond, 243
+// in the fourth, 185 after 15 and 172 from 30 on; the clocks that it needs stay 376 thousand.
 // Measured, us a call, gemm_fp4.hip / here: 8192^3 202 / 173, 8192 x 8192 x 1024 75 / 50, 4096^3 33 / 28, 3008 x 1471
 // x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.  Convolutions of packed
 // images: 11 x 320 x 49 x 49 -> 334, 3 x 3, 26.3 / 21.2, 40 x 192 x 28 x 28 -> 128, 5 x 5, 21.6 / 16.0; as packed bits, a channel pack of

@@ -68,7 +68,10 @@ pack_rows_kernel(const float* __restrict__ x, uint32_t total, int64_t cols, int6
 
 // Matrices past this many bytes are read with the streaming hint: they would not stay in the L2s (4 MB on each of 8
 // XCDs), and what they push out on the way costs more.  Row pack and alpha_mean_abs of 44 to 103 MB level or 10 %
-// faster so, from HBM and on a second reading; 43 MB level, 37 MB 7.1 us instead of 5.8 on the second.
+// faster so, from HBM and on a second reading; 43 MB level, 37 MB 7.1 us instead of 5.8 on the second.  It depends on where the
+// matrix is.  Both over 4096 x 9216 (151 MB, of the memory-side cache's 256), us without the hint / with it: several in turn 48.4 /
+// 47.3, the same made one after the other in front of it 54.4 / 45.2, made long ago 52.1 / 52.1; but one matrix again and
+// again 44.4 / 45.3, and weights made in the memory that the last ones left, read once, 47.8 / 49.7.
 constexpr int64_t kStreamBytes = 48 << 20;
 
 static void launch_pack_rows_grid(const float* x, int64_t rows, int64_t cols, int64_t ldx,
@@ -403,9 +406,11 @@ pack_conv_weights_kernel(const float* __restrict__ w, int C, int Cw, int ld, int
 // The same for 25 and 49 taps, where that is long for a wave: 49 loads, 49 ways through LDS and 49 ballots in a chain.  A
 // workgroup per filter and 64 channels (per filter where a constant has to be added up over its words); the floats
 // come 16 bytes at a time, on any dword since a filter starts anywhere, at most four a thread, and the four waves share the
-// taps.  Bound by the launch to some 4 MB of weights, past that by the way in.  Before and now, us a call of which 3.8
-// are the call: 432 x 10 x 7 x 7 6.65 and 4.4, 64 x 512 x 7 x 7 10.2 and 4.3, 294 x 461 x 7 x 7 (25 MB) 12.3 and 7.1,
-// 512 x 512 x 7 x 7 (51 MB) 15.7 and 11.7, 512 x 512 x 5 x 5 7.0 and 6.2.
+// taps.  Bound by the launch to some 4 MB of weights, past that by the way in.  Before (a wave per 64 channels) and now, us
+// a call, filters in turn from HBM: 432 x 10 x 7 x 7 6.6 and 3.9, 64 x 512 x 7 x 7 10.9 and 4.3, 294 x 461 x 7 x 7 (27 MB) 14.8
+// and 9.3, 512 x 512 x 7 x 7 (51 MB) 17.0 and 14.3, 256 x 512 x 5 x 5 7.6 and 6.1, 400 x 400 x 5 x 5 8.3 and 6.6, 512 x 512 x 5 x 5 9.1 and
+// 9.2; read again and again, from the caches, the last 6.7 and 7.1, 512 x 256 x 5 x 5 4.2 and 4.4, the others as above.  (Two words
+// of channels a workgroup, the second requested while the first is packed: 512 x 512 x 5 x 5 9.9, 400 x 400 x 5 x 5 9.4.)
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef float v4f_lds __attribute__((ext_vector_type(4), may_alias));
 

@@ -1294,7 +1294,8 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
 @pytest.mark.parametrize("M,N,K,kind,block", [
     # rows of an odd number of 32-bit words: from 513 tiles of 64 x 64 on
     (1032, 1995, 3995, "w32", True), (2137, 971, 3163, "w32", True), (1142, 1962, 987, "w32", True),
-    (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False),
+    (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False), (64, 32000, 7003, "w32", False), (900, 1500, 29979, "w32", False),
+    (129, 10300, 9003, "w32", False),
     # fp32 results of up to 512 tiles of 128 x 128: from a K of 3500 on; past that whatever the K, and int32 results too
     (2048, 2048, 3499, "f32", False), (2000, 2040, 3500, "f32", True), (1900, 2500, 1664, "f32", False),
     (1900, 2500, 3584, "f32", True), (2041, 4090, 1664, "f32", False), (2690, 3130, 1664, "f32", True), (1900, 2500, 1664, "i32", True)])
@@ -1313,6 +1314,7 @@ def test_block_form_lines(M, N, K, kind, block):
         call = lambda: B.binary_fc_packed(A, K, W, alpha=alpha, mode=kind)  # noqa: E731
     got = call()
     assert ("block" in B.last_kernel()) == block, B.last_kernel()
+    assert kind != "w32" or block or ",reg>" in B.last_kernel(), B.last_kernel()  # (as they are, not widened)
     with tuned(k19=1 if block else 3):
         want = call()
         assert ("block" in B.last_kernel()) != block, B.last_kernel()

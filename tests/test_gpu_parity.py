@@ -1631,6 +1631,28 @@ def test_conv_one_launch(parts, N, C, H, W, O, k, s, p):
     np.testing.assert_array_equal(run_conv(x, w, s, p), ri.astype(np.float32))
 
 
+@pytest.mark.parametrize("waves,parts,N,C,H,W,O,k,s,p", [
+    (4, 2, 1, 16, 3, 3, 5, 3, 1, 1), (4, 1, 40, 40, 20, 22, 30, 1, 1, 0), (4, 2, 3, 15, 8, 8, 20, 3, 1, 1), (4, 4, 1, 190, 17, 4, 20, 3, 1, 1),
+    (8, 2, 60, 130, 16, 18, 20, 3, 1, 1), (8, 4, 2, 113, 25, 30, 70, 3, 1, 1), (8, 8, 1, 460, 16, 16, 512, 3, 1, 1), (8, 4, 4, 129, 20, 20, 129, 3, 1, 1),
+    (12, 4, 2, 320, 6, 23, 300, 3, 2, 1), (12, 8, 20, 320, 19, 11, 20, 5, 1, 2), (16, 2, 100, 130, 11, 3, 200, 3, 1, 1),
+    (16, 4, 1, 4101, 5, 5, 300, 1, 1, 0), (16, 4, 2, 1000, 30, 31, 33, 1, 1, 0)])
+def test_conv_one_launch_waves(waves, parts, N, C, H, W, O, k, s, p):
+    """The one-launch convolution in workgroups of 4 to 16 waves: items of the pack that do not divide by them, channels that
+    end in each sixteenth of a word (the words behind are cleared), patches of up to 64 words a wave; NaN, zeros and
+    infinities among the values."""
+    rng = np.random.default_rng(C + H + O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    x[rng.random(x.shape) < 0.02] = -0.0
+    x[rng.random(x.shape) < 0.02] = np.nan
+    x[rng.random(x.shape) < 0.02] = -np.inf
+    alpha = rng.standard_normal(O).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    np.testing.assert_array_equal(run_conv(x, w, s, p, integer_out=True), ri)
+    assert "conv_one_kernel" in B.last_kernel() and "x %d," % (64 * waves) in B.last_kernel(), B.last_kernel()
+    assert "%d parts of K" % parts in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(run_conv(x, w, s, p, alpha=alpha), rf)
+
+
 # ------------------------------------------------------------------ ties of the quantiser
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("rows,engine", [(300, {}), (300, {"k7": 3}), (40, {"k7": 1}), (5, {})])

@@ -51,6 +51,7 @@ inline int64_t w32_row_words(int64_t K) { return even_words(bmx::words_for(K)); 
 
 struct QuantWs {
   size_t planes_off, wb_off, rowsum_off, wrowsum_off, tmp_off, planes_total, total;  // planes_total: of the plane kernels
+  size_t least;  // below it a call is refused (from there to total it runs on the plane kernels)
 };
 
 // bits_w = 1: sign-packed weights [N][even Kw].  bits_w > 1: weight planes [N * bits_w][padded K]
@@ -65,12 +66,14 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
                                                    : (size_t)bits_w * N * bmx::padded_words(K) * 8);
   q.wrowsum_off = q.rowsum_off + round256((size_t)M * 4);
   q.tmp_off = q.wrowsum_off + (bits_w == 1 ? 0 : round256((size_t)N * 4));
-  q.total = q.planes_total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
-  size_t tiles = 0;
-  if (bmx::quant_i8_takes(M, N, K, bits_a, bits_w, &tiles)) {
-    tiles = round256(tiles);
-    if (tiles > q.total || (bits_w > 1 && bmx::gemm_engine != 1)) q.total = tiles;
-  }
+  q.total = q.least = q.planes_total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
+  size_t tiles = 0, least = 0;
+  bmx::quant_i8_workspace(M, N, K, bits_a, bits_w, &tiles, &least);
+  auto at_least = [&](size_t& size, size_t bytes) {
+    if (bytes && (bytes > size || (bits_w > 1 && bmx::gemm_engine != 1))) size = round256(bytes);
+  };
+  at_least(q.total, tiles);
+  at_least(q.least, least);
   return q;
 }
 
@@ -608,7 +611,7 @@ static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, i
     return BMX_ERR_ALIGN;
   const QuantWs q = quant_ws(M, N, K, bits_a, bits_w);
   if (!lazy || workspace) {
-    if (!workspace || workspace_bytes < q.total) return BMX_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < q.least) return BMX_ERR_WORKSPACE;
     if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -617,7 +620,7 @@ static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, i
     return hip_status(direct);
   if (!workspace) return BMX_ERR_WORKSPACE;
   // more bits than the FP4 form holds: bytes on the matrix cores
-  if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, s, &direct))
+  if (bmx::launch_quant_i8(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, workspace, workspace_bytes, s, &direct))
     return hip_status(direct);
   if (q.total < q.planes_total) return BMX_ERR_WORKSPACE;  // (an engine pinned meanwhile, by another thread)
   char* ws = (char*)workspace;

@@ -2,11 +2,14 @@
 // S[m][n] = sum_k q[m][k] * v[n][k] with q the level of the activation and v the weight's odd
 // integer (sign for one bit, 2 q_w - L_w above).
 //
-// Taken where an operand has more bits than the FP4 form of gemm_fp4.hip folds into a nibble (more
-// than two for the activations, more than one for the weights), and for small products of any.  Walked plane by plane with AND +
+// Taken for every pair of bit widths, large products of 1 or 2 by 1 bits aside (gemm_fp4.hip).  Walked plane by plane with AND +
 // popcount, such a product costs bits_a * bits_w passes over K on the vector ALU (4 x 4 bits, 500 x
-// 1000 x 2304: 67 us, and a 16 MB array of per-plane results to add up afterwards, 5 us).  As bytes
-// it is one pass on the matrix cores, whatever the bits.
+// 1000 x 2304: 67 us, and a 16 MB array of per-plane results to add up afterwards, 5 us).  As whole
+// numbers it is one pass on the matrix cores, whatever the bits.
+//
+// Up to four bits on both sides, two values share a byte of the operands' copies (see `ahead`): the product waits for its
+// operands' way from L2.  us a call, a value a byte / two: 500 x 1000 x 2304 of 4 x 4 bits 12.4 / 10.1, 415 x 832 x 1152 of 4 x 2
+// 8.1 / 6.5, 871 x 369 x 7304 of 4 x 1 19.8 / 16.0.
 //
 // Eight-bit levels do not fit a signed byte: q - 128 and q_w - 128 do, and the sums of the operands'
 // rows, counted from the words a lane loads anyway (v_dot4), put the difference right:
@@ -16,12 +19,13 @@
 //
 // Layout.  A dot product does not care about the order of k, and both operands are written by
 // quant_tiles_kernel for this kernel alone, so they are stored the way the MFMA wants them: tile
-// (row block of 32, k step of 32) is 1 KiB, lane l of a wave taking bytes [16 l, 16 l + 16): row
+// (row block of 32, k step of 32; of 64 with two values a byte) is 1 KiB, lane l of a wave taking bytes [16 l, 16 l + 16): row
 // l % 32, half l / 32 of the step.  Every operand load is one contiguous KiB, no LDS, no
 // transposition.  K is zero padded to whole blocks of 256, rows to whole blocks of 32.
 #include "bmx_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace bmx {
 
@@ -40,30 +44,41 @@ struct QuantOperand {
   const float* x;
   int64_t ld;
   int rows;
-  int sign;  // 1-bit weights: the sign; else the byte is mul * q + add - 128 of the level q
-  // q = round(L * clamp((x + c0) * c1)): c0, c1 = 0, 1 for activations, 1, 0.5 for weights in [-1, 1]
-  float c0, c1, L;
-  float mul, add;
+  int sign;  // 1-bit weights: the sign of x
+  // else the level q = round(L * clamp(x * s + c)), s, c = 1, 0 for activations, 0.5, 0.5 for weights in [-1, 1], and the byte
+  float s, c, L;
+  int odd;        // 2 q - L for weights of this many bits (2 to 7),
+  uint32_t flip;  // or (odd = 0) q exclusive-or this: 0, or the top bits where q - 128 is wanted
   uint4* tiles;
 };
 
-// Four values of an operand as four bytes, the first lowest.
-__device__ __forceinline__ uint32_t quant_bytes(const QuantOperand& o, float x, float y, float z, float w) {
+// The levels of four values as four bytes, the first lowest.  Five instructions a value; with the byte made in fp32 (truncate,
+// multiply, add, convert) they were eight, and that is what the kernels below waited for where the values come from a cache.
+__device__ __forceinline__ uint32_t level_bytes(float s, float c, float L, float x, float y, float z, float w) {
 #pragma clang fp contract(off)  // (the rest of the rounded product L * u, not of the exact one, decides a tie)
   const float v[4] = {x, y, z, w};
-  uint32_t d = 0;
+  uint32_t q[4];
   // Rounding half away from zero of u >= 0 is trunc(u + (0.5 - 2^-25)) in fp32: with 0.5 itself the
-  // one value 0.5 - 2^-25 would round up.  The byte is made in fp32 (whole numbers up to 255) with
-  // 128 added, so that it is never negative, and the 128 goes again as the flip of its top bit.
+  // one value 0.5 - 2^-25 would round up.  (x + 1) / 2 is the fused x / 2 + 1 / 2: halving rounds nothing.
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float u = fminf(fmaxf((v[e] + o.c0) * o.c1, 0.0f), 1.0f) * o.L;
-    d = __builtin_amdgcn_cvt_pk_u8_f32(truncf(u + 0x1.fffffep-2f) * o.mul + o.add, e, d);
-  }
-  return d ^ 0x80808080u;
+  for (int e = 0; e < 4; ++e)
+    q[e] = (uint32_t)(__builtin_amdgcn_fmed3f(__builtin_fmaf(v[e], s, c), 0.0f, 1.0f) * L + 0x1.fffffep-2f);
+  return (q[0] | q[1] << 8) | (q[2] | q[3] << 8) << 16;
+}
+// 2 q - L of four levels q of `bits` (2 to 7) bits: of 2 q + 1 the low bits, and above them the sign, bit `bits` inverted.
+__device__ __forceinline__ uint32_t odd_bytes(uint32_t q, int bits) {
+  const uint32_t top = 0x01010101u << bits, x2 = q << 1 | 0x01010101u, minus = ~x2 & top;
+  return (x2 & (top - 0x01010101u)) | ((minus << (8 - bits)) - minus);
 }
 __device__ __forceinline__ uint32_t sign_bytes(float x, float y, float z, float w) {
   return (x >= 0.0f ? 1u : 255u) | (y >= 0.0f ? 1u : 255u) << 8 | (z >= 0.0f ? 1u : 255u) << 16 | (w >= 0.0f ? 1u : 255u) << 24;
+}
+// a / b, correctly rounded as the IEEE division is, for a whole number b and y = 1 / b rounded: the remainder of a product that
+// is off by its rounding is exact, and so is the sum rounded once (P. Markstein, IBM J. Res. Dev. 34, 1990; no
+// result here is near the ends of the range).  Three instructions for ten.
+__device__ __forceinline__ float quotient(float a, float b, float y) {
+  const float q = a * y;
+  return __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q);
 }
 // Bytes of a dword that lie inside a row with `left` elements to go.
 __device__ __forceinline__ uint32_t byte_mask(int left) {
@@ -79,51 +94,67 @@ struct QuantTilesParams {
   int blocks0;         // workgroups of operand 0
 };
 
-constexpr int kTileWaves = 8, kTileRows = 32 / kTileWaves;  // rows of the block per wave
+// (four waves of eight rows: what a wave does beside its values is as many instructions as for two rows of them)
+constexpr int kTileWaves = 4, kTileRows = 32 / kTileWaves;  // rows of the block per wave
 
+template <bool NIB>
 __global__ void __launch_bounds__(64 * kTileWaves)
 quant_tiles_kernel(const QuantTilesParams p) {
   __shared__ uint32_t t[16 * kTileRow];
   // (all arguments named at the top: fetched in one batch, one trip to memory instead of one per group)
-  asm volatile("" ::"s"(p.blocks0), "s"(p.div_kblocks.mul), "s"(p.op[0].x), "s"(p.op[0].ld), "s"(p.op[0].L), "s"(p.op[0].tiles),
-               "s"(p.op[1].x), "s"(p.op[1].ld), "s"(p.op[1].L), "s"(p.op[1].tiles), "s"(p.K));
+  asm volatile("" ::"s"(p.blocks0), "s"(p.div_kblocks.mul), "s"(p.div_kblocks.sh1), "s"(p.div_kblocks.sh2), "s"(p.kblocks), "s"(p.K));
   const bool second = (int)blockIdx.x >= p.blocks0;
-  QuantOperand o = p.op[0];
-  if (second) o = p.op[1];
+  QuantOperand o = p.op[0], o1 = p.op[1];
+  // (both operands' fields in registers before one is taken: the compiler would load the one that is taken, behind the choice)
+  asm volatile("" : "+s"(o.x), "+s"(o.ld), "+s"(o.rows), "+s"(o.sign), "+s"(o.s), "+s"(o.c), "+s"(o.L), "+s"(o.odd), "+s"(o.flip));
+  asm volatile("" : "+s"(o1.x), "+s"(o1.ld), "+s"(o1.rows), "+s"(o1.sign), "+s"(o1.s), "+s"(o1.c), "+s"(o1.L), "+s"(o1.odd), "+s"(o1.flip));
+  if (second) o = o1;
   const int b = (int)blockIdx.x - (second ? p.blocks0 : 0);
-  const int rb = (int)fast_div((uint32_t)b, p.div_kblocks), kb = b - rb * p.kblocks;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rb = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)b, p.div_kblocks)), kb = b - rb * p.kblocks;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int k0 = kb * 256 + 4 * lane;
-  float v[kTileRows][4];
-  // (rows past the matrix repeat its last: their results are never stored)
-  const int row0 = rb * 32 + wave * kTileRows;
-  const float* const x = o.x + k0;
-  const int64_t ld = o.ld;
-  const int last = o.rows - 1;
-  if (kb * 256 + 256 <= p.K) {  // workgroup-uniform
+  // A row is read as a buffer of K floats: what lies past it reads as zero, and is masked below.  (Rows past the matrix repeat
+  // its last: their results are never stored.)
+  v4f_any v[kTileRows];
+  const int row0 = rb * 32 + wave * kTileRows, last = o.rows - 1;
+  const float* at = o.x + (int64_t)min(row0, last) * o.ld;
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j) {
-      const v4f_any f = *(const v4f_any*)(x + (int64_t)min(row0 + j, last) * ld);
-      v[j][0] = f[0], v[j][1] = f[1], v[j][2] = f[2], v[j][3] = f[3];
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kTileRows; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)  // (elements past the row read its last and are masked below)
-        v[j][e] = o.x[(int64_t)min(row0 + j, last) * ld + min(k0 + e, p.K - 1)];
+  for (int j = 0; j < kTileRows; ++j) {
+    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc((void*)at, 0, 4 * p.K, 0x00020000);
+    v[j] = __builtin_bit_cast(v4f_any, __builtin_amdgcn_raw_buffer_load_b128(row, 4 * k0, 0, 0));
+    at += row0 + j < last ? o.ld : 0;
   }
   const uint32_t mask = byte_mask(p.K - k0);
   uint32_t* const dst = &t[(lane >> 2) * kTileRow + wave * (4 * kTileRows) + (lane & 3)];
-  if (o.sign) {
+  if constexpr (NIB) {  // a for activations; s of the odd integer 2 s + 1 for weights, whatever k is past the row's end
+    if (o.sign) {
+#pragma unroll
+      for (int j = 0; j < kTileRows; ++j) dst[4 * j] = sign_bytes(v[j][0], v[j][1], v[j][2], v[j][3]) >> 1 & 0x0f0f0f0fu;
+    } else {
+      const uint32_t add = o.odd ? (16u - (1u << o.odd >> 1)) * 0x01010101u : 0u, keep = o.odd ? 0x0f0f0f0fu : mask;
+#pragma unroll
+      for (int j = 0; j < kTileRows; ++j) dst[4 * j] = (level_bytes(o.s, o.c, o.L, v[j][0], v[j][1], v[j][2], v[j][3]) + add) & keep;
+    }
+  } else if (o.sign) {
 #pragma unroll
     for (int j = 0; j < kTileRows; ++j) dst[4 * j] = sign_bytes(v[j][0], v[j][1], v[j][2], v[j][3]) & mask;
+  } else if (o.odd) {
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j)
+      dst[4 * j] = odd_bytes(level_bytes(o.s, o.c, o.L, v[j][0], v[j][1], v[j][2], v[j][3]), o.odd) & mask;
   } else {
 #pragma unroll
-    for (int j = 0; j < kTileRows; ++j) dst[4 * j] = quant_bytes(o, v[j][0], v[j][1], v[j][2], v[j][3]) & mask;
+    for (int j = 0; j < kTileRows; ++j) dst[4 * j] = (level_bytes(o.s, o.c, o.L, v[j][0], v[j][1], v[j][2], v[j][3]) ^ o.flip) & mask;
   }
   __syncthreads();
   // half tile 2 s + h of the block is t[(2 s + h) * kTileRow ...]: row r at dword 4 r
+  if constexpr (NIB) {  // k and k + 128 in a byte
+    static_assert(kTileWaves == 4, "a piece a thread");
+    const uint32_t* const half = &t[(threadIdx.x >> 5) * kTileRow + (threadIdx.x & 31) * 4];
+    const uint4 lo = *(const uint4*)half, hi = *(const uint4*)(half + 8 * kTileRow);
+    o.tiles[(int64_t)b * 256 + threadIdx.x] = uint4{lo.x | hi.x << 4, lo.y | hi.y << 4, lo.z | hi.z << 4, lo.w | hi.w << 4};
+    return;
+  }
   uint4* out = o.tiles + (int64_t)b * 512;
 #pragma unroll
   for (int i = 0; i < 8 / kTileWaves; ++i) {
@@ -144,7 +175,7 @@ struct I8Params {
   int tiles_m, tiles, tiles_per_xcd;
   int S;
   int ca, scale, rs, Kreal;
-  float denom;
+  float denom, inv;  // inv = 1 / denom
   int32_t* C_i32;
   float* C_f32;
   int64_t ldc;
@@ -152,16 +183,20 @@ struct I8Params {
   FastDiv div_tiles_m;
 };
 
-constexpr int kAhead = 4;  // k steps per group of loads
+// Where both operands have at most four bits (NIB), a step is of 64 k: a byte of its tile holds a level of the activations, or
+// s of the weight 2 s + 1, for k and for k + 128 of a block of 256.  A weight is multiplied as the byte 16 s + 8, one instruction
+// from where s lies in the upper half, two from the lower; the sums are eight times the result's.  Half the bytes from L2,
+// which is what the product of bytes waits for (above).
+constexpr int ahead(bool nib) { return nib ? 3 : 4; }  // steps per group of loads
 
-template <int TM, int TN>
+template <int TM, int TN, bool NIB>
 struct Group {
-  v4i a[kAhead][TM], b[kAhead][TN];
+  v4i a[ahead(NIB)][TM], b[ahead(NIB)][TN];
 };
 
 // The tile's end: operand sums of the two half-waves, the partial tiles of the S waves of a workgroup
 // through LDS (S > 1, at most MAXS), the 8-bit correction, stores.
-template <int TM, int TN, bool SUMS, int MAXS>
+template <int TM, int TN, bool SUMS, bool NIB, int MAXS>
 __device__ __forceinline__ void finish_tile(const I8Params& p, const v16i (&acc)[TM][TN], int (&sa)[TM], int (&sb)[TN],
                                             int* red, int lane, int wave, int tile_m, int tile_n) {
   constexpr int kGroups = TM * TN * 4;
@@ -183,13 +218,13 @@ __device__ __forceinline__ void finish_tile(const I8Params& p, const v16i (&acc)
     for (int e = 0; e < 4; ++e) {
       const int m = (tile_m * TM + i) * 32 + 8 * (g & 3) + 4 * h + e;
       if (m >= p.M) continue;
-      int sv = d[e];
+      int sv = NIB ? d[e] >> 3 : d[e];
       if (SUMS)
         sv = (int)((uint32_t)p.scale * ((uint32_t)d[e] + (uint32_t)p.ca * (uint32_t)cb) +
                    (uint32_t)p.rs * ((uint32_t)ra[e] + (uint32_t)p.ca * (uint32_t)p.Kreal));
       const int64_t idx = (int64_t)m * p.ldc + n;
       if (p.C_i32) p.C_i32[idx] = sv;
-      if (p.C_f32) p.C_f32[idx] = (float)sv / p.denom;
+      if (p.C_f32) p.C_f32[idx] = quotient((float)sv, p.denom, p.inv);
     }
   };
   if (S == 1) {
@@ -259,7 +294,7 @@ __device__ __forceinline__ void finish_tile(const I8Params& p, const v16i (&acc)
   }
 }
 
-template <int TM, int TN, bool SUMS>
+template <int TM, int TN, bool SUMS, bool NIB>
 __global__ void __launch_bounds__(512)
 gemm_i8_kernel(const I8Params p) {
   extern __shared__ int red[];
@@ -290,7 +325,9 @@ gemm_i8_kernel(const I8Params p) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
   int sa[TM] = {}, sb[TN] = {};
 
-  auto load = [&](Group<TM, TN>& g, int k) {
+  static_assert(!(SUMS && NIB), "8 bits do not fit half a byte");
+  constexpr int kAhead = ahead(NIB);
+  auto load = [&](Group<TM, TN, NIB>& g, int k) {
 #pragma unroll
     for (int d = 0; d < kAhead; ++d) {
       const int kk = min(k + d, k_hi - 1) * 64;  // (a group's steps past the range repeat its last)
@@ -300,10 +337,25 @@ gemm_i8_kernel(const I8Params p) {
       for (int j = 0; j < TN; ++j) g.b[d][j] = *(const v4i*)(brow[j] + kk);
     }
   };
-  auto multiply = [&](const Group<TM, TN>& g, int k) {
+  auto multiply = [&](const Group<TM, TN, NIB>& g, int k) {
 #pragma unroll
     for (int d = 0; d < kAhead; ++d) {
       if (k + d >= k_hi) break;  // wave-uniform
+      if constexpr (NIB) {
+        constexpr int kLow = 0x0f0f0f0f, kHigh = (int)0xf0f0f0f0u, kHalf = 0x08080808;
+        v4i a[2][TM], b[2][TN];  // of the lower halves, of the upper
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[0][i] = g.a[d][i] & kLow, a[1][i] = (g.a[d][i] >> 4) & kLow;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[0][j] = ((g.b[d][j] << 4) & kHigh) | kHalf, b[1][j] = (g.b[d][j] & kHigh) | kHalf;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+        continue;
+      }
       if (SUMS) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -322,7 +374,7 @@ gemm_i8_kernel(const I8Params p) {
     }
   };
   if (k_lo < k_hi) {
-    Group<TM, TN> g0, g1;
+    Group<TM, TN, NIB> g0, g1;
     load(g0, k_lo);
     for (int k = k_lo; k < k_hi; k += 2 * kAhead) {
       if (k + kAhead < k_hi) load(g1, k + kAhead);
@@ -331,101 +383,151 @@ gemm_i8_kernel(const I8Params p) {
       multiply(g1, k + kAhead);
     }
   }
-  finish_tile<TM, TN, SUMS, 8>(p, acc, sa, sb, red, lane, wave, tile_m, tile_n);
+  finish_tile<TM, TN, SUMS, NIB, 8>(p, acc, sa, sb, red, lane, wave, tile_m, tile_n);
 }
 
 // ---- the whole product in one launch, for problems small enough that a second launch costs more
-// than quantising a row once per tile of results.  Up to 16 waves split a tile's K.  Of a step of 32 k a
-// wave fetches 32 rows of both operands, eight lanes to a row's 128 bytes (16 bytes straight into the
+// than quantising a row once per tile of results.  Up to 16 waves split the K of a T x T tile.  Of a step of KS = 1024 / T k a
+// wave fetches T rows of both operands, KS / 4 lanes to a row's 4 KS bytes (16 bytes straight into the
 // MFMA's layout would touch 64 lines per load: 202 x 192 x 437 7.7 us), quantises four values per lane and
-// load into a dword of bytes, and turns those into the MFMA's layout (lane (r, h): 16 bytes of row r)
+// load into a dword of bytes, and turns those into the MFMA's layout (a lane: 16 bytes of a row)
 // through 2 KB of LDS of its own, where its partial sums go in the end.
+// What bounds it is what one CU has to take in and to quantise for its 2 T rows: 64 bytes a clock and five vector instructions a
+// value.  So 16 x 16 of the result per workgroup as long as the CUs are not full of them.
 struct QuantSmallParams {
-  I8Params g;
-  QuantOperand a, w;
+  const float *a, *w;
+  int64_t lda, ldw;
+  int M, N, K;
+  int tiles_m, S, s_base, s_rem;  // k steps per wave: s_base, the first s_rem waves one more
+  FastDiv div_tiles_m;
+  float La, Lw;
+  uint32_t flip_a;
+  int odd;  // bits of the weights (2 to 7; 8: levels - 128)
+  int ca, scale, rs;
+  float denom, inv;
+  int32_t* C_i32;
+  float* C_f32;
+  int64_t ldc;
 };
 
-template <bool SUMS, bool SIGN>
+constexpr int kSignW = 1, kOddW = 2, kLevelW = 3;  // weights of one bit, of 2 to 7, of 8
+
+template <bool SUMS, int WK, int T>
 __global__ void __launch_bounds__(1024)
 quant_small_kernel(const QuantSmallParams p) {
   extern __shared__ int red[];
-  asm volatile("" ::"s"(p.a.x), "s"(p.a.ld), "s"(p.a.L), "s"(p.a.mul), "s"(p.a.add), "s"(p.w.x), "s"(p.w.ld), "s"(p.w.L),
-               "s"(p.w.mul), "s"(p.w.add), "s"(p.g.M), "s"(p.g.N), "s"(p.g.Kreal), "s"(p.g.tiles_m), "s"(p.g.S), "s"(p.g.s_base),
-               "s"(p.g.s_rem), "s"(p.g.div_tiles_m.mul), "s"(p.g.div_tiles_m.sh1), "s"(p.g.div_tiles_m.sh2));
+  asm volatile("" ::"s"(p.a), "s"(p.w), "s"(p.lda), "s"(p.ldw), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.tiles_m), "s"(p.S), "s"(p.s_base),
+               "s"(p.s_rem), "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1), "s"(p.div_tiles_m.sh2), "s"(p.La), "s"(p.Lw), "s"(p.flip_a),
+               "s"(p.odd), "s"(p.ca), "s"(p.denom), "s"(p.C_i32), "s"(p.C_f32), "s"(p.ldc));
+  constexpr int KS = 1024 / T, kLanes = KS / 4;             // k per step; lanes that share a row of a load
+  constexpr int NR = T * T / 64;                            // results per lane
+  constexpr int kWave = (NR > 8 ? NR : 8) * 64;             // ints of LDS per wave: both operands of a step, then its sums
+  typedef int acc_t __attribute__((ext_vector_type(NR)));
+  typedef v4i __attribute__((may_alias)) v4i_alias;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = lane & 31, h = lane >> 5, c = lane & 7;
-  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div(blockIdx.x, p.g.div_tiles_m));
-  const int tile_m = (int)blockIdx.x - tile_n * p.g.tiles_m;
-  const int k_lo = wave * p.g.s_base + min(wave, p.g.s_rem), k_hi = k_lo + p.g.s_base + (wave < p.g.s_rem ? 1 : 0);
-  const int K = p.g.Kreal;
-  // byte offsets of row 8 t + lane / 8 (rows past a matrix repeat its last; their results are never stored)
+  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div(blockIdx.x, p.div_tiles_m));
+  const int tile_m = (int)blockIdx.x - tile_n * p.tiles_m;
+  const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0);
+  // byte offsets of row 256 / KS * t + lane / kLanes (rows past a matrix repeat its last; their results are never stored)
+  const __amdgpu_buffer_rsrc_t a_rows = __builtin_amdgcn_make_buffer_rsrc((void*)p.a, 0, (int)0xffffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t w_rows = __builtin_amdgcn_make_buffer_rsrc((void*)p.w, 0, (int)0xffffffff, 0x00020000);
   uint32_t arow[4], wrow[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int row = 8 * t + (lane >> 3);
-    arow[t] = (uint32_t)min(tile_m * 32 + row, p.g.M - 1) * (uint32_t)p.a.ld * 4u;
-    wrow[t] = (uint32_t)min(tile_n * 32 + row, p.g.N - 1) * (uint32_t)p.w.ld * 4u;
+    const int row = T / 4 * t + lane / kLanes;
+    arow[t] = (uint32_t)min(tile_m * T + row, p.M - 1) * ((uint32_t)p.lda * 4u);
+    wrow[t] = (uint32_t)min(tile_n * T + row, p.N - 1) * ((uint32_t)p.ldw * 4u);
   }
-  v16i acc[1][1];
+  const int c = 4 * (lane & (kLanes - 1));
+  acc_t acc;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[0][0][e] = 0;
-  int sa[1] = {}, sb[1] = {};
-  QuantOperand oa = p.a, ow = p.w;
-  oa.sign = 0;
-  ow.sign = SIGN ? 1 : 0;
+  for (int e = 0; e < NR; ++e) acc[e] = 0;
+  int sa = 0, sb = 0;
   v4f_any va[2][4], vw[2][4];
   auto load = [&](int i, int k) {
     // four values past the row's end are its last four instead; those that the piece before has are masked
     // below (of both operands: what remains still meets its partner, and K has no order)
-    const uint32_t off = 4u * (uint32_t)min(32 * k + 4 * c, K - 4);
+    const uint32_t off = 4u * (uint32_t)min(KS * k + c, p.K - 4);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      va[i][t] = *(const v4f_any*)((const char*)p.a.x + (arow[t] + off));
-      vw[i][t] = *(const v4f_any*)((const char*)p.w.x + (wrow[t] + off));
+      va[i][t] = __builtin_bit_cast(v4f_any, __builtin_amdgcn_raw_buffer_load_b128(a_rows, arow[t] + off, 0, 0));
+      vw[i][t] = __builtin_bit_cast(v4f_any, __builtin_amdgcn_raw_buffer_load_b128(w_rows, wrow[t] + off, 0, 0));
     }
   };
-  uint32_t* const turn = (uint32_t*)red + wave * 1024;  // [operand][row][8 dwords]
+  uint32_t* const turn = (uint32_t*)red + wave * kWave;  // [operand][row][KS / 4 dwords]
   auto multiply = [&](int i, int k) {
-    const uint32_t mask = ~byte_mask(32 * k + 4 * c + 4 - K);
+    const uint32_t mask = ~byte_mask(KS * k + c + 4 - p.K);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const v4f_any x = va[i][t], y = vw[i][t];
-      turn[64 * t + lane] = quant_bytes(oa, x[0], x[1], x[2], x[3]) & mask;
-      turn[256 + 64 * t + lane] = (SIGN ? sign_bytes(y[0], y[1], y[2], y[3]) : quant_bytes(ow, y[0], y[1], y[2], y[3])) & mask;
+      turn[64 * t + lane] = (level_bytes(1.0f, 0.0f, p.La, x[0], x[1], x[2], x[3]) ^ (SUMS ? p.flip_a : 0u)) & mask;
+      uint32_t v;
+      if constexpr (WK == kSignW) v = sign_bytes(y[0], y[1], y[2], y[3]);
+      else v = level_bytes(0.5f, 0.5f, p.Lw, y[0], y[1], y[2], y[3]);
+      if constexpr (WK == kOddW) v = odd_bytes(v, p.odd);
+      if constexpr (WK == kLevelW) v ^= 0x80808080u;
+      turn[256 + 64 * t + lane] = v & mask;
     }
-    typedef v4i __attribute__((may_alias)) v4i_alias;
-    const v4i a = *(const v4i_alias*)(turn + 8 * r + 4 * h), b = *(const v4i_alias*)(turn + 256 + 8 * r + 4 * h);
+    const int at = (lane & (T - 1)) * kLanes + 4 * (lane / T);
+    const v4i a = *(const v4i_alias*)(turn + at), b = *(const v4i_alias*)(turn + 256 + at);
     if (SUMS) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        sa[0] = __builtin_amdgcn_sdot4(a[e], 0x01010101, sa[0], false);
-        sb[0] = __builtin_amdgcn_sdot4(b[e], 0x01010101, sb[0], false);
+        sa = __builtin_amdgcn_sdot4(a[e], 0x01010101, sa, false);
+        sb = __builtin_amdgcn_sdot4(b[e], 0x01010101, sb, false);
       }
     }
-    acc[0][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[0][0], 0, 0, 0);
+    if constexpr (T == 32) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
+    else acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, acc, 0, 0, 0);
   };
-  if (k_lo < k_hi) {
-    load(0, k_lo);
-    for (int k = k_lo; k < k_hi; k += 2) {
-      if (k + 1 < k_hi) load(1, k + 1);
-      multiply(0, k);
-      if (k + 1 >= k_hi) break;
-      if (k + 2 < k_hi) load(0, k + 2);
-      multiply(1, k + 1);
-    }
+  load(0, k_lo);
+  for (int k = k_lo; k < k_hi; k += 2) {
+    if (k + 1 < k_hi) load(1, k + 1);
+    multiply(0, k);
+    if (k + 1 >= k_hi) break;
+    if (k + 2 < k_hi) load(0, k + 2);
+    multiply(1, k + 1);
   }
-  finish_tile<1, 1, SUMS, 16>(p.g, acc, sa, sb, red, lane, wave, tile_m, tile_n);
+
+  // ---- the waves' sums meet: [wave][register][lane], and with SUMS [wave][row of a, of w] behind them; a thread a result
+  int* const sums = red + p.S * kWave;
+#pragma unroll
+  for (int e = 0; e < NR; ++e) red[wave * kWave + 64 * e + lane] = acc[e];
+  if (SUMS) {
+    if (T == 16) sa += __shfl_xor(sa, 16), sb += __shfl_xor(sb, 16);
+    sa += __shfl_xor(sa, 32), sb += __shfl_xor(sb, 32);
+    if (lane < T) sums[wave * 2 * T + lane] = sa, sums[wave * 2 * T + T + lane] = sb;
+  }
+  __syncthreads();
+  for (int o = threadIdx.x; o < T * T; o += 64 * p.S) {
+    const int e = o >> 6, l = o & 63;
+    // register e of lane l of the MFMA's result
+    const int row = T == 32 ? 8 * (e >> 2) + 4 * (l >> 5) + (e & 3) : 4 * (l >> 4) + e, col = l & (T - 1);
+    int d = 0, ra = 0, cb = 0;
+#pragma unroll 4
+    for (int s = 0; s < p.S; ++s) {
+      d += red[s * kWave + o];
+      if (SUMS) ra += sums[s * 2 * T + row], cb += sums[s * 2 * T + T + col];
+    }
+    if (SUMS)
+      d = (int)((uint32_t)p.scale * ((uint32_t)d + (uint32_t)p.ca * (uint32_t)cb) + (uint32_t)p.rs * ((uint32_t)ra + (uint32_t)p.ca * (uint32_t)p.K));
+    const int m = tile_m * T + row, n = tile_n * T + col;
+    if (m >= p.M || n >= p.N) continue;
+    const int64_t idx = (int64_t)m * p.ldc + n;
+    if (p.C_i32) p.C_i32[idx] = d;
+    if (p.C_f32) p.C_f32[idx] = quotient((float)d, p.denom, p.inv);
+  }
 }
 
-template <int TM, int TN, bool SUMS>
+template <int TM, int TN, bool SUMS, bool NIB>
 hipError_t launch_i8(const I8Params& p, hipStream_t s) {
-  auto kern = gemm_i8_kernel<TM, TN, SUMS>;
+  auto kern = gemm_i8_kernel<TM, TN, SUMS, NIB>;
   const size_t lds = p.S > 1 ? (size_t)p.S * (TM * TN * 4 * 1024 + 128 * (TM + TN)) : 0;
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
-  note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
+  note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : NIB ? ",halves" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
   launch_kernel(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
   return launch_error();
 }
@@ -434,31 +536,40 @@ int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * c
 
 }  // namespace
 
-// Workspace of the two tiled operands, and whether the problem is taken: an operand of more bits than
-// the FP4 form holds, or a product of few bits where bytes cost less than the plane pack and its GEMM; and a result that
-// fills a quarter of a 32 x 32 block (below that the padding of the tiles is most of what is moved, and the plane
-// kernels' workspace is smaller).
-// Few bits (1 or 2 by 1): the byte form writes its tiles and reads them again and multiplies a byte a value; the plane
-// form multiplies once per activation bit, and its pack and its splits of K have coarser pieces, so that a round of 4096
-// values that is not full costs much of a full one.  The line below fits 518 products on
-// both forms (chosen form over the better one: 0.5 % on average, 18 % at most; bytes always 5.5 %, planes always 15 %).  us a
-// call, bytes / planes: 572 x 896 x 1293 of 1 x 1 bits 10.3 / 14.3, 496 x 1408 x 640 9.4 / 12.7, 418 x 1024 x 605
-// of 2 x 1 8.1 / 12.1; 612 x 384 x 3968 15.4 / 12.0, 361 x 64 x 8115 15.1 / 12.1, 1744 x 256 x 2234 16.8 / 13.4.
-static bool bytes_pay(int64_t M, int64_t N, int64_t K, int bits_a) {
+// Activations of 1 or 2 bits by weights of 1: as planes (gemm_fp4.hip), or here with two values a byte.  The planes' pack and their
+// splits of K have coarse pieces, the bytes' way from L2 grows with the product: 4674 products on both forms, planes' time over
+// this one's: operands of up to a million values 1.4 to 1.8, one to three million 1.3 to 1.6, three to six 1.1 to 1.25; above the
+// line 0.71 to 1.05.  The choice is 0.04 % behind the better one (16 % at most).  Whole rounds of 4096 values, from the second on,
+// the planes' pieces fit: 16 x 200 x 16384 of 1 x 1 bits 11.4 / 14.1, 300 x 300 x 8192 11.9 / 13.4, of 2 x 1 13.4 / 13.3, 16 x 2048 x 8192
+// 17.5 / 18.1.  us a call, planes / here: 302 x 1536 x 1726 of 2 x 1 11.4 /
+// 9.2, 690 x 128 x 2605 9.8 / 7.8, 852 x 256 x 1558 of 1 x 1 9.1 / 7.1; 1803 x 512 x 3844 of 1 x 1 14.0 / 19.2.
+static bool halves_pay(int64_t M, int64_t N, int64_t K, int bits_a) {
+  if (K % 4096 == 0 && K >= 8192) return false;
+  return K < (1 << 20) && M * N <= 1000000000 && M * N * K < 1200000000 * (int64_t)bits_a;
+}
+// Where they are not taken for want of workspace: a call takes what callers were told while a value took a byte here, the
+// planes' part of the workspace and below this line a byte a value, and refuses less.
+static bool bytes_told(int64_t M, int64_t N, int64_t K, int bits_a) {
   if (M * N >= 1000000000) return false;  // (the products below stay in range)
   const int64_t bytes = tile_bytes(M, K) + tile_bytes(N, K) + M * N * K / 1000 * 20 + 100 * K;
   const int64_t planes = 14000000 * (bits_a - 1) + (K % 1024 ? 4000000 : 0) + 5500 * (ceil_div(K, 4096) * 4096 - K);
   return bytes < planes;
 }
 
-bool quant_i8_takes(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes) {
-  if (bits_a <= 2 && bits_w == 1 && !bytes_pay(M, N, K, bits_a)) return false;
-  if (M * N < 256) return false;
+// Workspace of the two tiled operands (0: not taken), and the least that a call accepts for them.  Taken: a result that
+// fills a quarter of a 32 x 32 block (below that the padding of the tiles is most of what is moved).
+void quant_i8_workspace(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes, size_t* least) {
+  *bytes = *least = 0;
+  if (M * N < 256) return;
   const int64_t a = tile_bytes(M, K), b = tile_bytes(N, K);
-  *bytes = (size_t)(a + b);
   const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32);
-  return a < ((int64_t)1 << 40) && b < ((int64_t)1 << 40) && tiles < ((int64_t)1 << 30) &&
-         ceil_div(M, 32) * ceil_div(K, 256) + ceil_div(N, 32) * ceil_div(K, 256) < ((int64_t)1 << 30);
+  if (a >= ((int64_t)1 << 40) || b >= ((int64_t)1 << 40) || tiles >= ((int64_t)1 << 30) ||
+      ceil_div(M, 32) * ceil_div(K, 256) + ceil_div(N, 32) * ceil_div(K, 256) >= ((int64_t)1 << 30))
+    return;
+  *bytes = *least = (size_t)(a + b);
+  if (bits_a > 2 || bits_w > 1) return;
+  if (!bytes_told(M, N, K, bits_a)) *least = 0;
+  *bytes = std::max(*least, halves_pay(M, N, K, bits_a) ? (size_t)(a + b) / 2 : 0);
 }
 
 namespace {
@@ -466,9 +577,8 @@ namespace {
 void fill_operands(QuantOperand (&op)[2], const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w,
                    int M, int N) {
   const int La = (1 << bits_a) - 1, Lw = (1 << bits_w) - 1;
-  op[0] = {a, lda, M, 0, 0.0f, 1.0f, (float)La, 1.0f, bits_a == 8 ? 0.0f : 128.0f, nullptr};
-  op[1] = {w, ldw, N, bits_w == 1 ? 1 : 0, 1.0f, 0.5f, (float)Lw, bits_w == 8 ? 1.0f : 2.0f,
-           bits_w == 8 ? 0.0f : 128.0f - (float)Lw, nullptr};
+  op[0] = {a, lda, M, 0, 1.0f, 0.0f, (float)La, 0, bits_a == 8 ? 0x80808080u : 0u, nullptr};
+  op[1] = {w, ldw, N, bits_w == 1 ? 1 : 0, 0.5f, 0.5f, (float)Lw, bits_w > 1 && bits_w < 8 ? bits_w : 0, bits_w == 8 ? 0x80808080u : 0u, nullptr};
 }
 
 void fill_product(I8Params& p, int bits_a, int bits_w, int M, int N, int K, int32_t* S_out, float* out_f32, int64_t ldo) {
@@ -482,6 +592,7 @@ void fill_product(I8Params& p, int bits_a, int bits_w, int M, int N, int K, int3
   p.rs = bits_w == 8 ? 1 : 0;
   p.Kreal = K;
   p.denom = (float)(((1 << bits_a) - 1) * ((1 << bits_w) - 1));
+  p.inv = 1.0f / p.denom;
   p.C_i32 = S_out;
   p.C_f32 = out_f32;
   p.ldc = ldo;
@@ -499,58 +610,92 @@ static void set_split(I8Params& p) {
 bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
                         int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
   if (gemm_engine != 0) return false;
-  const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32), nk = ceil_div(K, 32);
-  // Steps of K per CU up to which one launch is ahead (us a call: 202 x 192 x 437 5.0 against 8.1, 1735 x 64 x 768
-  // 6.3 / 7.6, 83 x 64 x 1152 6.4 / 7.8, 245 x 773 x 1792 10.8 / 8.0, 748 x 448 x 512, two tiles on a CU, 8.5 / 7.8,
-  // 104 x 697 x 1045, 88 tiles, 9.0 / 8.2;
-  // with 8 bits on a side and so the operands' sums 674 x 64 x 896 7.5 / 8.0, 230 x 64 x 1142 8.2 / 8.2).
-  if (nk * ceil_div(tiles, 256) > (tiles > 256 ? 24 : tiles > 48 || bits_a == 8 || bits_w == 8 ? 28 : 36)) return false;
+  const int64_t t32 = ceil_div(M, 32) * ceil_div(N, 32), t16 = ceil_div(M, 16) * ceil_div(N, 16);
+  // 16 x 16 of the result per workgroup while a CU has one of them, or two or more of few steps (3600 products of both: time as
+  // 32 x 32 over that as 16 x 16, up to 256 tiles of 16 x 16 1.24 to 1.37; 257 to 512 1.08 to 1.26 up to a K of 512, 0.90 beyond; 513
+  // to 2048 1.08 to 1.17 up to 128, 0.8 beyond).
+  const bool small = t16 <= 256 || (t16 <= 512 && K <= 512) || (t16 <= 2048 && K <= 128);
+  // Steps of K per CU up to which one launch is ahead of the better pair of launches (which the host makes in 7.8 us at the
+  // least): 16 x 16, 24 to 32 of them 1.42 times, 32 to 40 1.22, 40 to 48 1.06, 48 to 64 0.98; 32 x 32, 16 to 24 1.18, 24 to 32 0.99.
+  // Over the same products the choice is 0.8 % behind the better.  us a call, before two values shared a byte and tiles were
+  // of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2 x 4 5.8 / 3.6,
+  // 202 x 192 x 437 5.0 / 3.4.
+  if (small ? K > 44 * 64 : ceil_div(K, 32) * ceil_div(t32, 256) > 24) return false;
   if (K < 4 || (int64_t)M * lda * 4 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 4 >= ((int64_t)1 << 32)) return false;
-  QuantSmallParams p;
-  QuantOperand op[2];
-  fill_operands(op, a, lda, bits_a, w, ldw, bits_w, M, N);
-  p.a = op[0];
-  p.w = op[1];
-  fill_product(p.g, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
-  p.g.nk = (int)nk;
-  p.g.tiles_m = p.g.mblocks;
-  p.g.tiles = (int)tiles;
-  p.g.tiles_per_xcd = 0;
-  // waves per tile: a step or two of K each while the chip has room for them
   const bool sums = bits_a == 8 || bits_w == 8;
-  const int64_t S = std::min<int64_t>(sums ? 15 : 16, std::max<int64_t>(1, 4096 / tiles));  // (15: 64 KB of LDS)
-  p.g.S = (int)std::min(S, nk);
-  set_split(p.g);
-  const size_t lds = (size_t)p.g.S * (4096 + (sums ? 256 : 0));
-  note_kernel("quant_small_kernel%s grid %lld x %d", sums ? "<sums>" : "", (long long)tiles, 64 * p.g.S);
-  auto go = [&](auto kern) { launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * p.g.S), lds, s, p); };
-  if (bits_w == 1) sums ? go(quant_small_kernel<true, true>) : go(quant_small_kernel<false, true>);
-  else sums ? go(quant_small_kernel<true, false>) : go(quant_small_kernel<false, false>);
+  const int T = small ? 16 : 32, nk = (int)ceil_div(K, 1024 / T);
+  QuantSmallParams p;
+  p.a = a;
+  p.w = w;
+  p.lda = lda;
+  p.ldw = ldw;
+  p.M = M;
+  p.N = N;
+  p.K = K;
+  p.tiles_m = (int)ceil_div(M, T);
+  p.div_tiles_m = make_fast_div((uint32_t)p.tiles_m);
+  const int tiles = p.tiles_m * (int)ceil_div(N, T);
+  // waves per tile: a step of K each while the chip has room for them (two steps each: 10 % slower; 15: 64 KB of LDS)
+  p.S = std::min({sums && T == 32 ? 15 : 16, std::max(1, (T == 32 ? 4096 : 8192) / tiles), nk});
+  p.s_base = nk / p.S;
+  p.s_rem = nk % p.S;
+  I8Params g;
+  fill_product(g, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
+  p.La = (float)((1 << bits_a) - 1);
+  p.Lw = (float)((1 << bits_w) - 1);
+  p.flip_a = bits_a == 8 ? 0x80808080u : 0u;
+  p.odd = bits_w;
+  p.ca = g.ca;
+  p.scale = g.scale;
+  p.rs = g.rs;
+  p.denom = g.denom;
+  p.inv = g.inv;
+  p.C_i32 = S_out;
+  p.C_f32 = out_f32;
+  p.ldc = ldo;
+  const size_t lds = (size_t)p.S * ((T == 32 ? 4096 : 2048) + (sums ? 8 * T : 0));
+  note_kernel("quant_small_kernel%s<%d> grid %d x %d", sums ? "<sums>" : "", T, tiles, 64 * p.S);
+  auto go = [&](auto kern) { launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * p.S), lds, s, p); };
+  auto pick = [&](auto sums_tag, auto wk) {
+    if (T == 32) go(quant_small_kernel<decltype(sums_tag)::value, decltype(wk)::value, 32>);
+    else go(quant_small_kernel<decltype(sums_tag)::value, decltype(wk)::value, 16>);
+  };
+  using std::integral_constant;
+  if (bits_w == 8) pick(std::true_type{}, integral_constant<int, kLevelW>{});
+  else if (bits_w == 1) sums ? pick(std::true_type{}, integral_constant<int, kSignW>{}) : pick(std::false_type{}, integral_constant<int, kSignW>{});
+  else sums ? pick(std::true_type{}, integral_constant<int, kOddW>{}) : pick(std::false_type{}, integral_constant<int, kOddW>{});
   *err = launch_error();
   return true;
 }
 
 bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
-                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, hipStream_t s, hipError_t* err) {
-  size_t need;
-  if (gemm_engine == 1 || !quant_i8_takes(M, N, K, bits_a, bits_w, &need)) return false;
-  if (gemm_engine != 0 && bits_a <= 2 && bits_w == 1) return false;  // (an engine of the plane form is pinned)
+                     int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, size_t workspace_bytes, hipStream_t s,
+                     hipError_t* err) {
+  size_t need, least;
+  quant_i8_workspace(M, N, K, bits_a, bits_w, &need, &least);
+  if (gemm_engine == 1 || need == 0) return false;
+  if (bits_a <= 2 && bits_w == 1) {
+    if (gemm_engine != 0) return false;  // (an engine of the plane form is pinned)
+    if (!halves_pay(M, N, K, bits_a) || workspace_bytes < need) return false;
+  }
   QuantTilesParams q;
   fill_operands(q.op, a, lda, bits_a, w, ldw, bits_w, M, N);
+  // (a sum is at most 15 * 120 K, and so within 32 bits)
+  const bool halves = bits_a <= 4 && bits_w <= 4 && K < (1 << 20);
   q.op[0].tiles = (uint4*)workspace;
-  q.op[1].tiles = (uint4*)((char*)workspace + tile_bytes(M, K));
+  q.op[1].tiles = (uint4*)((char*)workspace + tile_bytes(M, K) / (halves ? 2 : 1));
   q.K = K;
   q.kblocks = (int)ceil_div(K, 256);
   q.div_kblocks = make_fast_div((uint32_t)q.kblocks);
   I8Params p;
   fill_product(p, bits_a, bits_w, M, N, K, S_out, out_f32, ldo);
   q.blocks0 = p.mblocks * q.kblocks;
-  launch_kernel(quant_tiles_kernel, dim3((unsigned)(q.blocks0 + p.nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
+  launch_kernel(halves ? quant_tiles_kernel<true> : quant_tiles_kernel<false>, dim3((unsigned)(q.blocks0 + p.nblocks * q.kblocks)), dim3(64 * kTileWaves), 0, s, q);
   *err = launch_error();
   if (*err != hipSuccess) return true;
   p.A = q.op[0].tiles;
   p.B = q.op[1].tiles;
-  p.nk = q.kblocks * 8;
+  p.nk = q.kblocks * (halves ? 4 : 8);
   // C per wave: 32 x 32 while K is short (many waves, each with little to fetch before its first product), 32 x 64, and 64 x 64
   // where K is long, each with tiles for half the CUs.  K is split over as many waves as leave the workgroups of
   // a CU resident at once (the registers hold 24, 12 and 8 waves, rounded as below), a power of two of them so that its
@@ -558,6 +703,7 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   // 2226, 288 tiles of 32 x 64, where the second workgroup of seven waves had to wait for the first, 18.8 and 15.3; 721
   // x 1438 x 681 14.2 and 11.4; 1650 x 1566 x 103 16.8 and 12.2; 1098 x 1728 x 265 12.1 and 11.3.  Over 150
   // products 8.7 % and 1.8 % behind the best of all splits and forms.
+  // (With two values a byte the same lines and splits are 0.5 % behind the best of all over 414 products.)
   const int64_t t12 = ceil_div(M, 32) * ceil_div(N, 64), t22 = ceil_div(M, 64) * ceil_div(N, 64);
   const int TM = K >= 5000 && t22 >= 128 ? 2 : 1, TN = TM == 2 || (K > 1100 && t12 >= 128) ? 2 : 1;
   p.tiles_m = (int)ceil_div(M, 32 * TM);
@@ -565,12 +711,18 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   p.tiles_per_xcd = (int)ceil_div(p.tiles, 8);
   const int64_t room = (TM * TN == 4 ? 8 : TM * TN == 2 ? 12 : 24) / ceil_div(p.tiles, 256);  // waves a workgroup
   p.S = room >= 8 ? 8 : room >= 4 ? 4 : room >= 2 ? 2 : 1;
-  while (p.S > 1 && p.S > p.nk / kAhead) p.S /= 2;  // (each with at least one group of k steps)
+  while (p.S > 1 && p.S > 2 * q.kblocks) p.S /= 2;  // (each with 128 k at least)
   set_split(p);
   const bool sums = bits_a == 8 || bits_w == 8;
-  if (TM == 2) *err = sums ? launch_i8<2, 2, true>(p, s) : launch_i8<2, 2, false>(p, s);
-  else if (TN == 2) *err = sums ? launch_i8<1, 2, true>(p, s) : launch_i8<1, 2, false>(p, s);
-  else *err = sums ? launch_i8<1, 1, true>(p, s) : launch_i8<1, 1, false>(p, s);
+  auto form = [&](auto tm, auto tn) {
+    constexpr int M_ = decltype(tm)::value, N_ = decltype(tn)::value;
+    return halves ? launch_i8<M_, N_, false, true>(p, s) : sums ? launch_i8<M_, N_, true, false>(p, s) : launch_i8<M_, N_, false, false>(p, s);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  if (TM == 2) *err = form(Two{}, Two{});
+  else if (TN == 2) *err = form(One{}, Two{});
+  else *err = form(One{}, One{});
   return true;
 }
 

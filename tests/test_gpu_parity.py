@@ -632,6 +632,64 @@ def test_quant_gemm_one_launch(M, N, K, ba, bw):
     assert_f32_close(of.cpu().numpy(), r32)
 
 
+@pytest.mark.parametrize("M,N,K", [(513, 290, 769), (545, 257, 1023), (33, 1100, 2817), (520, 300, 1025), (40, 3000, 1300), (70, 36, 4200), (16, 33, 3071), (200, 2100, 897)])
+@pytest.mark.parametrize("ba,bw", [(1, 1), (2, 1), (4, 1), (3, 2), (1, 3), (4, 4)])
+def test_quant_halves(M, N, K, ba, bw):
+    """Two values a byte: K that ends in either half of a block of 256 and on its edge, rows that do not fill a block of 32, one
+    and two blocks a wave, K split up to eight ways; ties, clamped values, NaN and infinities; operand rows apart."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a = rng.uniform(-0.1, 1.1, (M, K + 1)).astype(np.float32)
+    w = rng.uniform(-1.1, 1.1, (N, K + 3)).astype(np.float32)
+    a[rng.random(a.shape) < 0.01] = np.nan
+    a[rng.random(a.shape) < 0.05] = 0.5
+    a[rng.random(a.shape) < 0.01] = np.inf
+    w[rng.random(w.shape) < 0.01] = -np.inf
+    w[rng.random(w.shape) < 0.05] = -0.0
+    # (NaN is level 0, which the oracle's conversion of it to a whole number does not define)
+    rS, _, r32 = oracle.quant_gemm(np.where(np.isnan(a), np.float32(0), a)[:, :K].copy(), w[:, 3:].copy(), ba, bw)
+    S, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, 3:], ba, bits_w=bw)
+    assert "gemm_i8_kernel" in B.last_kernel() and "halves" in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    assert_f32_close(of.cpu().numpy(), r32)
+
+
+@pytest.mark.parametrize("M,N,K,T", [(16, 16, 4, 16), (1, 1, 63, 16), (17, 31, 64, 16), (15, 33, 65, 16), (256, 256, 129, 16), (256, 257, 512, 16),
+                                     (256, 257, 513, 32), (512, 1024, 128, 16), (512, 1025, 128, 32), (30, 50, 2816, 16), (300, 240, 700, 32)])
+@pytest.mark.parametrize("ba,bw", [(1, 1), (8, 1), (2, 2), (4, 7), (8, 3), (1, 8), (8, 8)])
+def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
+    """The one-launch form in tiles of 16 x 16 and 32 x 32, both sides of the lines between them, K around a step."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a = rng.uniform(-0.1, 1.1, (M, K)).astype(np.float32)
+    w = rng.uniform(-1.1, 1.1, (N, K)).astype(np.float32)
+    rS, _, r32 = oracle.quant_gemm(a, w, ba, bw)
+    S, of = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw)
+    assert "quant_small_kernel" in B.last_kernel() and "<%d>" % T in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    np.testing.assert_array_equal(of.cpu().numpy(), r32)
+
+
+def test_quant_few_bits_workspace():
+    """Few bits: with the workspace that the query names, two values a byte, in it and not beside it; with what the plane
+    kernels need, the plane kernels; with less, refused."""
+    M, N, K = 700, 700, 2000
+    rng = np.random.default_rng(9)
+    a, w = rng.uniform(0, 1, (M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    rS, _, _ = oracle.quant_gemm(a, w, 1, 1)
+    full = B.workspace_bytes(B.OP_QUANT_GEMM, (M, N, K, 1, 1))
+    words = 32  # of a row of planes; of the weights' bits too
+    planes = M * words * 8 + N * words * 8 + (M * 4 + 255) // 256 * 256
+    assert planes < full == (704 + 704) * 2048 // 2
+    for size, kernel in ((full, "gemm_i8_kernel"), (full - 256, "gemm_fp4_kernel"), (planes, "gemm_fp4_kernel")):
+        room = torch.full((4 * full,), 0xa5, dtype=torch.uint8, device="cuda")
+        S, _ = B.quant_gemm(dev(a), dev(w), 1, want_float=False, workspace=room[full:full + size])
+        assert kernel in B.last_kernel(), (size, B.last_kernel())
+        np.testing.assert_array_equal(S.cpu().numpy(), rS)
+        assert bool((room[:full] == 0xa5).all()) and bool((room[full + size:] == 0xa5).all())  # nothing beside it is written
+    with pytest.raises(B.BmxError) as e:
+        B.quant_gemm(dev(a), dev(w), 1, want_float=False, workspace=torch.empty(planes - 256, dtype=torch.uint8, device="cuda"))
+    assert e.value.status == -6
+
+
 def test_config5_quant_gemm():
     c = synth.config5(small=True)
     S, of = B.quant_gemm(dev(c["a"]), dev(c["w"]), 2)

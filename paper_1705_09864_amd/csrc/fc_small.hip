@@ -16,12 +16,13 @@
 #include "bmx_internal.h"
 
 #include <algorithm>
+#include <climits>
 
 namespace bmx {
 
 namespace {
 
-// (sixteen waves, so that a row's runs are requested at once: 8 x 9216 -> 4096 6.0 us a call, with eight
+// (up to sixteen waves, so that a row's runs are requested at once: 8 x 9216 -> 4096 6.0 us a call, with eight
 // waves 7.2, with eight that request a run ahead 7.5)
 constexpr int kWaves = 16;
 
@@ -33,6 +34,7 @@ struct FcSmallParams {
   const float* alpha;
   int M, N, K, Kw, Kpad;  // Kpad: words of an LDS row, a multiple of W * L
   int cols;               // output features per workgroup
+  int waves;              // per workgroup
   int32_t* out_i32;
   float* out_f32;
   int64_t ldo;
@@ -60,7 +62,7 @@ __global__ void __launch_bounds__(64 * kWaves)
 fc_small_kernel(const FcSmallParams p) {
   extern __shared__ uint64_t bits[];  // [RM][Kpad] sign bits
   asm volatile("" ::"s"(p.x), "s"(p.ldx), "s"(p.W), "s"(p.ldw), "s"(p.alpha), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.Kw),
-               "s"(p.Kpad), "s"(p.cols), "s"(p.out_i32), "s"(p.out_f32), "s"(p.ldo));
+               "s"(p.Kpad), "s"(p.cols), "s"(p.waves), "s"(p.out_i32), "s"(p.out_f32), "s"(p.ldo));
   constexpr int NV = RM * U;         // counts per lane group
   constexpr int kGroupsPerWave = 64 / L;
   constexpr int kPass = kGroupsPerWave * U;  // features per wave and pass
@@ -70,8 +72,9 @@ fc_small_kernel(const FcSmallParams p) {
   const int l = lane & (L - 1), grp = lane / L;
   const int nchunks = p.Kpad / (W * L);
   const int n_end = min(n0 + p.cols, p.N);
-  // passes of this wave: features n0 + (wave + kWaves * i) * kPass ...
-  const int npass = (n_end - n0 > wave * kPass) ? (n_end - n0 - wave * kPass + kWaves * kPass - 1) / (kWaves * kPass) : 0;
+  // passes of this wave: features n0 + (wave + waves * i) * kPass ...
+  int npass = 0;
+  for (int n = n0 + wave * kPass; n < n_end; n += p.waves * kPass) ++npass;
   // which of the group's counts this lane stores: value v = m * U + u
   int v_mine;
   bool stores;
@@ -89,7 +92,7 @@ fc_small_kernel(const FcSmallParams p) {
   float al = 1.0f, al_nxt = 1.0f;
   auto request = [&](int it) {
     const int pass = it / nchunks, chunk = it - pass * nchunks;
-    const int nb = n0 + (wave + kWaves * pass) * kPass + grp * U;
+    const int nb = n0 + (wave + p.waves * pass) * kPass + grp * U;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint64_t* row = p.W + (int64_t)min(nb + u, p.N - 1) * p.ldw;
@@ -136,7 +139,7 @@ fc_small_kernel(const FcSmallParams p) {
     const int real = min(max(p.K - c * 1024 - 64 * lane, 0), 64);
     const uint64_t word = ((uint64_t)hi << 32 | lo) & (real < 64 ? (1ull << real) - 1 : ~0ull);
     if (lane < 16 && 16 * c + lane < p.Kpad) bits[m * p.Kpad + 16 * c + lane] = word;
-    c += kWaves;
+    c += p.waves;
     while (c >= cpr) c -= cpr, ++m;
   }
   __syncthreads();
@@ -190,7 +193,7 @@ fc_small_kernel(const FcSmallParams p) {
         if (l == i) mine = s;
       }
     }
-    const int nb = n0 + (wave + kWaves * pass) * kPass + grp * U;
+    const int nb = n0 + (wave + p.waves * pass) * kPass + grp * U;
     ++pass;
     auto store = [&](int v, int count) {
       const int m = m0 + v / U, n = nb + v % U;
@@ -218,16 +221,22 @@ fc_small_kernel(const FcSmallParams p) {
   }
 }
 
-// Lanes per feature and words per lane and step by the length of a row: the least padding.
+// Lanes per feature and words per lane and step.  Few lanes, since what their sums cost is then shared by more words, as long as
+// a row is at most three steps (four lanes, up to 48 words; sixteen, up to 192) and the features make work for eight waves
+// (four waves: 599 x 2940 -> 64 3.84 -> 4.30 us; twelve: 153 x 4544 -> 108 3.9 -> 4.7); but not so many that a row does not fill
+// them once.  Then the least padding.  In a graph, before (sixteen lanes from 17 words on, sixty-four from 65) and now: 100 x 2100 -> 1000 4.76
+// and 4.14 us, 23 x 4206 -> 1920 6.3 and 5.0, 111 x 2176 -> 632 4.8 and 4.1.
 struct Lanes {
-  int L, W;
+  int L, W, padded;  // padded: words of a row, in whole steps
 };
-Lanes lanes_for(int64_t Kw) {
-  if (Kw <= 16) return {4, Kw <= 8 ? 2 : 4};
-  if (Kw <= 64) return {16, (int)ceil_div(Kw, 16)};
-  if (Kw <= 128) return {64, 2};
-  const int64_t n = ceil_div(Kw, 64);
-  return {64, ceil_div(n, 3) * 3 < ceil_div(n, 4) * 4 ? 3 : 4};
+constexpr int features_per_pass(int L) { return L == 4 ? 16 : L == 16 ? 8 : 2; }
+Lanes lanes_of(int L, int Kw) {
+  Lanes best = {L, 4, INT_MAX};
+  for (int W = 4; W >= 2; --W) {
+    const int padded = (Kw + W * L - 1) / (W * L) * (W * L);
+    if (padded < best.padded) best.padded = padded, best.W = W;
+  }
+  return best;
 }
 
 inline int64_t shift_up(int64_t n, int log) { return (n + ((int64_t)1 << log) - 1) >> log; }
@@ -235,8 +244,8 @@ inline int64_t shift_up(int64_t n, int log) { return (n + ((int64_t)1 << log) - 
 template <int RM>
 void launch_rm(const FcSmallParams& p, Lanes l, dim3 grid, hipStream_t s) {
   const size_t lds = (size_t)RM * p.Kpad * 8;
-  note_kernel("fc_small_kernel<%d,%d,%d> grid %u x %u x %d, %d features", RM, l.L, l.W, grid.x, grid.y, 64 * kWaves, p.cols);
-  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(64 * kWaves), lds, s, p); };
+  note_kernel("fc_small_kernel<%d,%d,%d> grid %u x %u x %d, %d features", RM, l.L, l.W, grid.x, grid.y, 64 * p.waves, p.cols);
+  auto go = [&](auto kern) { launch_kernel(kern, grid, dim3(64 * p.waves), lds, s, p); };
   if (l.L == 64) {
     if (l.W == 2) go(fc_small_kernel<RM, 64, 2, 2>);
     else if (l.W == 3) go(fc_small_kernel<RM, 64, 2, 3>);
@@ -247,6 +256,7 @@ void launch_rm(const FcSmallParams& p, Lanes l, dim3 grid, hipStream_t s) {
     else go(fc_small_kernel<RM, 16, 2, 4>);
   } else {
     if (l.W == 2) go(fc_small_kernel<RM, 4, 1, 2>);
+    else if (l.W == 3) go(fc_small_kernel<RM, 4, 1, 3>);
     else go(fc_small_kernel<RM, 4, 1, 4>);
   }
 }
@@ -264,17 +274,20 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   if (fc_small == 1 || gemm_engine != 0) return false;
   const int64_t Kw = words_for(in_features);
   if (Kw > 4096 || batch > 65535) return false;
-  const Lanes lanes = lanes_for(Kw);
-  const int64_t Kpad = ceil_div(Kw, lanes.W * lanes.L) * lanes.W * lanes.L;
+  // (32-bit and few divisions: the calls that come here are bound by the host)
+  const int few = Kw <= 48 ? 4 : Kw <= 192 ? 16 : 64, many = Kw <= 16 ? 4 : Kw <= 64 ? 16 : 64;  // lanes: fewest and most
+  const Lanes least_lanes = lanes_of(few, (int)Kw), most_lanes = many == few ? least_lanes : lanes_of(many, (int)Kw);
+  auto lanes_for = [&](int cols) -> const Lanes& { return cols < 8 * features_per_pass(few) ? most_lanes : least_lanes; };
   // Rows and features per workgroup: the pair that leaves the busiest CU the least to move (fp32 rows
   // and packed weights of its workgroups, and a fixed share per workgroup for its latencies).
   int64_t best = INT64_MAX;
   int rm_log = 0, cols_log = 4;
-  for (int r = 0; r <= 3; ++r) {
-    if (r > 0 && (((int64_t)1 << r) / 2 >= batch || (Kpad * 8 << r) > 48 * 1024)) break;
-    for (int c = 4; c <= 9; ++c) {
-      if (c > 4 && (1 << c) / 2 >= out_features) break;
-      const int64_t wgs = shift_up(batch, r) * shift_up(out_features, c);
+  for (int c = 4; c <= 9; ++c) {
+    if (c > 4 && (1 << c) / 2 >= out_features) break;
+    const int64_t Kpad = lanes_for(std::min(1 << c, out_features)).padded, groups = shift_up(out_features, c);
+    for (int r = 0; r <= 3; ++r) {
+      if (r > 0 && ((1 << r) / 2 >= batch || (Kpad * 8 << r) > 48 * 1024)) break;
+      const int64_t wgs = shift_up(batch, r) * groups;
       const int64_t cost = shift_up(wgs, 8) * (((int64_t)in_features * 4 << r) + (Kw * 8 << c) + (4 * Kpad << (r + c)) + (16 << 10));
       if (cost < best) best = cost, rm_log = r, cols_log = c;
     }
@@ -286,6 +299,8 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   const int rm = 1 << rm_log, cols = 1 << cols_log;
   const int64_t wgs = shift_up(batch, rm_log) * shift_up(out_features, cols_log);
   if (best > (wgs <= 32 ? 768 << 10 : 320 << 10)) return false;
+  const Lanes lanes = lanes_for(std::min(cols, out_features));
+  const int64_t Kpad = lanes.padded;
   FcSmallParams p;
   p.x = x;
   p.ldx = ldx;
@@ -298,10 +313,14 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   p.Kw = (int)Kw;
   p.Kpad = (int)Kpad;
   p.cols = cols;
+  const int nitems = rm * ((lanes.padded + 15) / 16), pass = features_per_pass(lanes.L), npass = (std::min(cols, out_features) + pass - 1) / pass;
+  // As many waves as runs of sixteen words to pack or passes over the features, whichever is more: a wave costs its CU the
+  // instructions ahead of its loads (64 x 512 -> 256 2.61 -> 2.29 us in a graph, 112 x 73 -> 216 2.76 -> 2.38).
+  p.waves = std::min(kWaves, (std::max(nitems, npass) + 3) / 4 * 4);
   p.out_i32 = out_i32;
   p.out_f32 = out_f32;
   p.ldo = ldo;
-  const dim3 grid((unsigned)ceil_div(out_features, cols), (unsigned)ceil_div(batch, rm));
+  const dim3 grid((unsigned)shift_up(out_features, cols_log), (unsigned)shift_up(batch, rm_log));
   if (rm == 1) launch_rm<1>(p, lanes, grid, s);
   else if (rm == 2) launch_rm<2>(p, lanes, grid, s);
   else if (rm == 4) launch_rm<4>(p, lanes, grid, s);

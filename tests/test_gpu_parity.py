@@ -271,6 +271,22 @@ def test_fc_small_row_lengths(batch, fin, fout):
     np.testing.assert_array_equal(B.binary_fc(dev(x), Wp, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("lanes,words,waves,batch,fin,fout", [
+    (4, 2, 4, 3, 64, 714), (4, 4, 4, 2, 1024, 16), (4, 3, 12, 100, 2100, 1000), (16, 3, 12, 23, 3072, 1920), (16, 3, 12, 599, 2940, 64),
+    (16, 2, 4, 1, 1280, 64), (4, 4, 16, 213, 1916, 941), (16, 3, 16, 23, 4206, 1920), (64, 2, 8, 5, 5593, 64), (64, 3, 12, 1, 9216, 4096), (64, 4, 16, 2, 15400, 33)])
+def test_fc_small_lanes_and_waves(lanes, words, waves, batch, fin, fout):
+    """The one-launch layer's lanes a feature, words a lane and waves a workgroup, rows in one to three steps, features and rows
+    that do not fill a pass, rows further apart than their length."""
+    rng = np.random.default_rng(fin + fout)
+    x, w = rng.standard_normal((batch, fin + 1)).astype(np.float32), rng.standard_normal((fout, fin)).astype(np.float32)
+    x[rng.random(x.shape) < 0.02] = -0.0
+    x[rng.random(x.shape) < 0.02] = np.nan
+    ri, _ = oracle.binary_fc(x[:, :fin].copy(), w)
+    got = B.binary_fc(dev(x)[:, :fin], B.binarize_pack(dev(w)), integer_out=True)
+    assert "fc_small_kernel<" in B.last_kernel() and ",%d,%d> " % (lanes, words) in B.last_kernel() and "x %d," % (64 * waves) in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(got.cpu().numpy(), ri)
+
+
 @pytest.mark.parametrize("batch,fin,fout", [(1, 1, 1), (5, 27, 3), (3, 180, 70), (66, 1000, 130)])
 def test_fc_ragged(batch, fin, fout):
     rng = np.random.default_rng(batch + fin + fout)

@@ -2,7 +2,10 @@
 // Paper: Sec. 2.2.1 / Sec. 2.2.2 (Eq. 2): C[m][n] = K - 2 * popcount(A[m] xor B[n]).
 //
 // Arithmetic as in gemm_fp4.hip: K - 2 pc(a) - 2 pc(b) + 4 * sum_k a * b, a bit stays where it stands
-// in its nibble and the MFMA's block scale makes it worth 1.
+// in its nibble and the MFMA's block scale makes it worth 1; but every fourth value, whose bit is the nibble's sign, is
+// multiplied as the sign itself and needs no popcount: sum_k s(a) s(b).  An operand takes 4 instructions a word and plane
+// then and not 5 (K held as 8192, half a second each: random bits 181.9 -> 179.9 us, all bits clear, where the power does not
+// bound it, 152.4 -> 147.8; 69 x 64 x 19 x 21 -> 406 in three packed layers 64.9 -> 64.1; 4531 x 1600 x 4096 16.8 -> 16.4).
 //
 // There every wave fetches the rows of its own tile, waits for its own reads of a segment before it may request
 // the next, and turns all of a segment's bits into operands before it multiplies.  With the chip full that
@@ -24,9 +27,10 @@
 //     the next convolution's packed image, halo included.
 //   (Three and four stages in flight changed nothing, at 8192^3 or with one workgroup per CU: it is issue and, with
 //   one wave on a SIMD, the chain of its own instructions that bounds the loop, not the memory behind it.)
-// What bounds it, from counters at 8192^3 as 256 x 128: the matrix pipe is busy in 70 % of the clocks, a SIMD issues an
-// instruction in 77 % of them (5.2 of the vector ALU for every MFMA), a wave waits for data or a barrier in 11 % of its time; and
-// the clock stands at 2.0 to 2.2 GHz under that load.  The same launch back to back takes 182 us in the first millisecond, 243
+// What bounds it, from counters at 8192^3 as 256 x 128 (while an operand took 5 instructions): the matrix pipe is busy in 70 % of
+// the clocks, a SIMD issues an instruction in 77 % of them (5.2 of the vector ALU for every MFMA), a wave waits for data or a barrier
+// in 11 % of its time; and the clock stands at 2.0 to 2.2 GHz under that load, by the power that the products take: the same launch on
+// zeros is a fifth faster.  The same launch back to back takes 182 us in the first millisecond, 243
 // in the fourth, 185 after 15 and 172 from 30 on; the clocks that it needs stay 376 thousand.
 // Measured, us a call, gemm_fp4.hip / here: 8192^3 202 / 173, 8192 x 8192 x 1024 75 / 50, 4096^3 33 / 28, 3008 x 1471
 // x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.  Convolutions of packed
@@ -75,19 +79,30 @@ struct BlockParams {
 
 constexpr int kF32 = 0, kI32 = 1, kBits = 2;
 
-// Plane n of four words as an operand: bit 4 i + n of a dword in nibble i, worth 0.5, 1 or 2 where it stands (planes
-// 0 to 2); plane 3, whose bit would be the nibble's sign, is shifted down to 0.5.
+// Plane n of four words as an operand: bit 4 i + n of a dword in nibble i.  Planes 0 to 2 as they stand, worth 0.5, 1 or 2 (a
+// clear bit nothing); plane 3, whose bit is the nibble's sign, as 1 with that sign: one instruction a dword like the others, where
+// a bit shifted down to 0.5 would take two.
 __device__ __forceinline__ v4i plane(const uint4& w, int n) {
-  const uint32_t m = n == 3 ? 0x11111111u : 0x11111111u << n;
-  const int sh = n == 3 ? 3 : 0;
-  return v4i{(int)((w.x >> sh) & m), (int)((w.y >> sh) & m), (int)((w.z >> sh) & m), (int)((w.w >> sh) & m)};
+  const uint32_t m = 0x11111111u << n;
+  if (n == 3) {
+    // (as asm: the compiler takes two instructions for it, as if the constant could not stay in a register)
+    auto sign = [&](uint32_t v) {
+      int e;
+      asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(e) : "v"(v), "s"(0x88888888u), "v"(0x22222222u));
+      return e;
+    };
+    return v4i{sign(w.x), sign(w.y), sign(w.z), sign(w.w)};
+  }
+  return v4i{(int)(w.x & m), (int)(w.y & m), (int)(w.z & m), (int)(w.w & m)};
 }
 
 __device__ __forceinline__ v8i wide(const v4i& e) { return v8i{e[0], e[1], e[2], e[3], 0, 0, 0, 0}; }
 
-// acc + popcount of four words
+// acc + popcount of planes 0 to 2 of four words
 __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
-  return __builtin_popcount(w.x) + (__builtin_popcount(w.y) + (__builtin_popcount(w.z) + (__builtin_popcount(w.w) + acc)));
+  auto add = [&](uint32_t v) { asm("v_bcnt_u32_b32 %0, %1, %0" : "+v"(acc) : "v"(v & 0x77777777u)); };
+  add(w.x), add(w.y), add(w.z), add(w.w);
+  return acc;
 }
 
 // WM x 4 / WM waves of TM x TN blocks of 32 x 32 each.  A stage holds blocks of 32 rows x 64 bytes, A's, then B's, in the
@@ -264,7 +279,7 @@ gemm_fp4_kernel(const BlockParams p) {
   auto multiply = [&](int g) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      const int sc = n == 1 ? 127 : (n == 2 ? 126 : 128);  // block scales that make a product worth 1
+      const int sc = n == 1 ? 127 : n == 0 ? 128 : 126;  // block scales that make a product worth 1, of signs a quarter
 #pragma unroll
       for (int k = 0; k < TM * TN; ++k) {
         const int i = k / TN, j = k % TN;
@@ -454,6 +469,13 @@ gemm_fp4_kernel(const BlockParams p) {
   }
 }
 
+// K, less the values of plane 3 in K (whose products of signs count themselves) and those among the zero bits behind it up to
+// a whole group of 256, which count one each: together every value of plane 3 of the groups multiplied.  (For Eq. 2's count, half.)
+float row_const(int K, int dwords, bool as_count) {
+  const int plane3 = (int)ceil_div(dwords, 8) * 64;
+  return as_count ? (float)(K - plane3 / 2) : (float)(K - plane3);
+}
+
 template <int WM, int TM, int TN, int OUT, int LW, bool CONV>
 hipError_t go(BlockParams& p, hipStream_t s) {
   constexpr int NBA = WM * TM, NBB = 4 / WM * TN;
@@ -532,7 +554,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.Kd = dwords;
   p.nseg = (int)ceil_div(dwords, 16);
   p.alpha = alpha;
-  p.row_const = (float)K;
+  p.row_const = block::row_const(K, dwords, as_count);
   p.row_mul = as_count ? -1.0f : -2.0f;
   p.tot_mul = as_count ? 2.0f : 4.0f;
   p.C = C_i32 ? (void*)C_i32 : (void*)C_f32;
@@ -618,7 +640,7 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.nseg = (int)ceil_div(p.Kd, 16);
   p.alpha = alpha;
   p.thr = thr;
-  p.row_const = (float)(C * KH * KW);
+  p.row_const = block::row_const(C * KH * KW, p.Kd, false);
   p.row_mul = -2.0f;
   p.tot_mul = 4.0f;
   p.C = out_bits ? (void*)out_bits : out_i32 ? (void*)out_i32 : (void*)out_f32;

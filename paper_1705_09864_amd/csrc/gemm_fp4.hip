@@ -5,18 +5,21 @@
 //
 // Arithmetic (as in gemm_mfma.hip): with bits a, b in {0, 1},
 //     K - 2 * pc(a xor b) = K - 2 * pc(a) - 2 * pc(b) + 4 * sum_k a * b,
-// the sum on v_mfma_scale_f32_32x32x64_f8f6f4 with both operands FP4 (E2M1).  A bit stays where
-// it stands in its nibble (worth 0.5, 1 or 2 there; the nibble's top bit is shifted down) and
-// the block scale of each MFMA brings the product back to 1, so one 32-bit word of bits becomes
-// the four 8-nibble operand dwords of four MFMAs with five VALU instructions.  Products and
+// the sum on v_mfma_f32_32x32x64_f8f6f4 with both operands FP4 (E2M1).  Every fourth bit of a 32-bit
+// word of bits makes one of the four 8-nibble operand dwords of four MFMAs: a bit stays where it
+// stands in its nibble (worth 0.5, 1 or 2 there) or is shifted by two, in A and B so that every
+// product is worth 1: five VALU instructions a dword of A, six of B.  Products and
 // fp32 sums are exact integers below 2^24.  The two bit planes of a 2-bit activation are staged
 // as separate rows and folded into one operand while being expanded: a nibble then holds the
-// 2-bit value itself (E2M1 codes 0 to 3 = 0, 0.5, 1, 1.5; block scale 2).
+// 2-bit value itself (E2M1 codes 0 to 3 = 0, 0.5, 1, 1.5), and block scales bring the products to 1.
 //
-// What bounds this kernel is not the matrix core but everything around it: the VALU work of
-// turning bits into nibbles, the loads, and fixed costs of a few-microsecond launch.  Hence:
-//   - 2 x 2 blocks of 32 x 32 per wave: an expanded operand block serves two MFMAs, 5 VALU
-//     instructions of expansion and 1 of row popcount per MFMA (a 32 x 32 tile needs 12).
+// What bounds this kernel is not the matrix core but everything around it: the issue of the
+// instructions that turn bits into nibbles, the loads, and fixed costs of a few-microsecond launch.
+// (A SIMD issues a vector instruction in 4 clocks, this MFMA in 11, with block scales in 17: the 16 MFMAs
+// and 104 other vector instructions of four words take 590 clocks of issue and 512 of the matrix core;
+// interleaving them by hand and reading a segment ahead, in twice the registers, measured level.)  Hence:
+//   - 2 x 2 blocks of 32 x 32 per wave: an expanded operand block serves two MFMAs, 5.5 VALU
+//     instructions of expansion and 1 of row popcount per MFMA (a 32 x 32 tile needs 13).
 //   - Operands travel global memory -> LDS without passing registers (global_load_lds_dwordx4:
 //     lane i of the instruction writes LDS bytes [16 i, 16 i + 16) of its destination).  A load
 //     covers 16 rows x 64 bytes, 4 lanes per row: whole 64-byte runs, so the memory pipeline
@@ -32,9 +35,14 @@
 //     LDS once: every wave writes its 64 registers, then finishes 1/S of the tile (sum of S
 //     partials, the popcount terms, scale, store).  Fat problems run four tiles per workgroup
 //     and no split.
+//   - The way from the sums to the stores is a third of a launch of 5 us: its instructions are few
+//     (addresses are scalar, parts of a sum are added in pairs of 16 bits, rows of results leave in 16-byte
+//     stores), its arguments and constants are there before it starts.  Against index arithmetic,
+//     bounds and dword stores per result: 2240 x 539 x 1799 7.6 -> 5.3 us, 787 x 2112 x 5568 10.8 -> 8.6,
+//     256 x 9216 -> 4096 -> 4096 with its packs 20.1 -> 18.8, 1024 x 1024 x 4096 of 2 x 1 bits 13.9 -> 12.6.
 //   - Workgroups are numbered so that tiles sharing operand rows sit on one XCD and run back
 //     to back (workgroup b runs on XCD b % 8): every XCD gets a contiguous run of tiles, walked
-//     in bands of 16 rows of tiles.
+//     in bands of 8 or 16 rows of tiles.
 //   - The convolution form gathers the B operand (im2col rows) from the halo-padded packed
 //     image, 16 bytes per lane, through the same loads.
 #include <algorithm>
@@ -50,8 +58,12 @@ namespace {
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v4i_alias __attribute__((ext_vector_type(4), may_alias));
-typedef __fp16 half2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u_alias __attribute__((may_alias));
+typedef uint16_t u16_alias __attribute__((may_alias));
+typedef uint8_t u8_alias __attribute__((may_alias));
 
 struct Fp4Params {
   const void* A;  // [M * PL][lda] words (plane pl of row m is row m * PL + pl), tail bits zero
@@ -66,7 +78,6 @@ struct Fp4Params {
   const float* alpha;     // per column n, or null
   const float* thr;       // packed-bit output: per column threshold of the sign decision, or null (0)
   const int32_t* rowsum;  // plane form: sum_k q[m][k]
-  float levels;           // plane form: 2^bits - 1
   int as_count;           // int32 output holds the xnor count (dot + K) / 2
   int32_t* C_i32;
   float* C_f32;
@@ -89,40 +100,38 @@ struct Fp4Params {
   int Kd;  // REG 2: data dwords per row (2 Kw, or one less)
 };
 
-// One nibble plane of four words of bits as the four operand dwords of one MFMA.
-//   n = 0: w & 0x11111111 (0.5)   n = 1: w & 0x22222222 (1.0)   n = 2: w & 0x44444444 (2.0)
-//   n = 3: (w >> 3) & 0x11111111 (0.5), hi = w >> 3 computed once per word
-__device__ __forceinline__ v8i nibble_plane(const uint4& w, const uint4& hi, int n) {
-  v8i e;
-  if (n == 3) {
-    e[0] = (int)(hi.x & 0x11111111u);
-    e[1] = (int)(hi.y & 0x11111111u);
-    e[2] = (int)(hi.z & 0x11111111u);
-    e[3] = (int)(hi.w & 0x11111111u);
-  } else {
-    const uint32_t m = 0x11111111u << n;
-    e[0] = (int)(w.x & m);
-    e[1] = (int)(w.y & m);
-    e[2] = (int)(w.z & m);
-    e[3] = (int)(w.w & m);
-  }
-  e[4] = e[5] = e[6] = e[7] = 0;
-  return e;
+// One nibble plane of four words of bits as the four operand dwords of one MFMA: bit 4 i + n of a dword in nibble i, worth 0.5, 1 or
+// 2 where it comes to lie, in A (B_SIDE: in B) so that the product of two set bits is worth 1 in every plane and no MFMA needs block
+// scales: planes 0 to 3 stand at 0.5, 1, 2 and 1 in A, at 2, 1, 0.5 and 1 in B.
+template <bool B_SIDE>
+__device__ __forceinline__ v8i nibble_plane(const uint4& w, int n) {
+  auto at = [&](uint32_t v) {
+    if (n == 1) return (int)(v & 0x22222222u);
+    if (n == 3) return (int)(v >> 2 & 0x22222222u);
+    if (B_SIDE) return (int)(n == 0 ? v << 2 & 0x44444444u : v >> 2 & 0x11111111u);
+    return (int)(v & 0x11111111u << n);
+  };
+  return v8i{at(w.x), at(w.y), at(w.z), at(w.w), 0, 0, 0, 0};
 }
 
-// Nibble plane n of two bit planes at once: nibble i of a dword = (bit 4 i + n of p1) * 2 + (bit
-// 4 i + n of p0), the 2-bit value in the nibble's two low bits.
-__device__ __forceinline__ v8i nibble_pair(const uint4& p0, const uint4& p1, int n) {
-  const uint32_t a0[4] = {p0.x, p0.y, p0.z, p0.w}, a1[4] = {p1.x, p1.y, p1.z, p1.w};
-  v8i e;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const uint32_t lo = (a0[d] >> n) & 0x11111111u;
-    const uint32_t hi = n == 0 ? (a1[d] & 0x11111111u) << 1 : (a1[d] >> (n - 1)) & 0x22222222u;
-    e[d] = (int)(lo | hi);
-  }
-  e[4] = e[5] = e[6] = e[7] = 0;
-  return e;
+// Two bit planes of 2-bit activations folded into values p1 * 2 + p0: those of the even bits in `even`, of the odd ones in `odd`, each
+// at an even place; four instructions, and six more for the four nibble planes below (taken bit by bit from both, fourteen).
+__device__ __forceinline__ void fold_planes(const uint4& p0, const uint4& p1, uint4* even, uint4* odd) {
+  auto fold = [](uint32_t lo, uint32_t hi) { return (lo & 0x55555555u) | (hi & 0xaaaaaaaau); };
+  *even = make_uint4(fold(p0.x, p1.x << 1), fold(p0.y, p1.y << 1), fold(p0.z, p1.z << 1), fold(p0.w, p1.w << 1));
+  *odd = make_uint4(fold(p0.x >> 1, p1.x), fold(p0.y >> 1, p1.y), fold(p0.z >> 1, p1.z), fold(p0.w >> 1, p1.w));
+}
+
+// Nibble plane n of the folded planes: nibble i of a dword = the value of bit 4 i + n, worth half of itself (E2M1 codes 0 to 3 = 0,
+// 0.5, 1, 1.5), and the bits of B that go with it where they stand, worth 0.5, 1, 2 and 0.5.
+__device__ __forceinline__ v8i value_plane(const uint4& even, const uint4& odd, int n) {
+  const uint4& w = n & 1 ? odd : even;
+  auto at = [&](uint32_t v) { return (int)(v >> (n & 2) & 0x33333333u); };
+  return v8i{at(w.x), at(w.y), at(w.z), at(w.w), 0, 0, 0, 0};
+}
+__device__ __forceinline__ v8i bit_plane(const uint4& w, int n) {
+  auto at = [&](uint32_t v) { return (int)(n == 3 ? v >> 3 & 0x11111111u : v & 0x11111111u << n); };
+  return v8i{at(w.x), at(w.y), at(w.z), at(w.w), 0, 0, 0, 0};
 }
 
 // acc + popcount of four words: four v_bcnt_u32_b32, each adding onto the running count (written
@@ -175,7 +184,6 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
 // of words or dwords per row) and for images whose 16-byte pieces are not contiguous (an odd number of channel words):
 // the load unit writes LDS from 16-byte aligned addresses, an ordinary 16-byte load needs 4.  The words
 // go to the same places of the staging area when the wave gets to the segment.
-typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int NA, int NB, bool CONV, bool DWORDS>
 __device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB][2], const uint32_t (&voff)[NB][2],
@@ -218,6 +226,42 @@ __device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB
     }
 }
 
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Four results in a row, `off` bytes behind an address that the wave shares.  NT: past the caches.  (As asm: as a builtin the
+// compiler merges the hinted store with the ordinary one of the other branch, and the hint is gone.  What follows a 16-byte store
+// may not write its registers in the next instruction, which the compiler sees to only where it knows of the store.)
+__device__ __forceinline__ void store_four(char* to, uint32_t off, const v4u& v, bool nt) {
+  if (nt) asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" ::"v"(off), "v"(v), "s"(to) : "memory");
+  else asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(off), "v"(v), "s"(to) : "memory");
+}
+
+// The lane's two results of one row, `off0` and `off1` bytes behind an address that the wave shares (its part of the address is
+// scalar work).  NT as above; MASKED: each only where `left0`, `left1` say that more than `e` rows are left of its column, an
+// instruction and three scalar ones a result.
+template <bool NT, bool MASKED>
+__device__ __forceinline__ void store_two(char* to, uint32_t off0, uint32_t off1, int left0, int left1, int e, uint32_t v0, uint32_t v1) {
+  if constexpr (MASKED) {
+    uint64_t all;
+    asm volatile("s_mov_b64 %0, exec\n\tv_cmp_lt_i32_e32 vcc, %8, %3\n\ts_and_b64 exec, %0, vcc\n\tglobal_store_dword %1, %5, %7\n\ts_mov_b64 exec, %0\n\t"
+                 "v_cmp_lt_i32_e32 vcc, %8, %4\n\ts_and_b64 exec, %0, vcc\n\tglobal_store_dword %2, %6, %7\n\ts_mov_b64 exec, %0"
+                 : "=&s"(all)
+                 : "v"(off0), "v"(off1), "v"(left0), "v"(left1), "v"(v0), "v"(v1), "s"(to), "n"(e)
+                 : "vcc", "scc", "memory");
+  } else if constexpr (NT) {
+    asm volatile("global_store_dword %0, %2, %4 nt\n\tglobal_store_dword %1, %3, %4 nt" ::"v"(off0), "v"(off1), "v"(v0), "v"(v1), "s"(to) : "memory");
+  } else {
+    asm volatile("global_store_dword %0, %2, %4\n\tglobal_store_dword %1, %3, %4" ::"v"(off0), "v"(off1), "v"(v0), "v"(v1), "s"(to) : "memory");
+  }
+}
+
+// x / 3 as division rounds it (Markstein: the quotient from the rounded reciprocal, corrected by the remainder; equal for every
+// whole number below 2^24)
+__device__ __forceinline__ float third(float x) {
+  const float q = x * (1.0f / 3.0f);
+  return fmaf(fmaf(-3.0f, q, x), 1.0f / 3.0f, q);
+}
+
 #ifdef BMX_FP4_STAMPS
 // Profiling builds only: per-wave shader-clock stamps at the phase boundaries of the kernel.
 }  // namespace
@@ -236,11 +280,18 @@ constexpr int kOutF32 = 0, kOutI32 = 1, kOutBits = 2;
 
 // TM x TN blocks of 32 x 32 per wave
 constexpr int TM = 2, TN = 2;
+// where the MFMA sums of HALF start: from here on the low bits of the fp32 number are the sum
+constexpr float kBias = 8388608.0f;
+
+// uint4 of a wave's partial tile: 64 rows of 32 dwords (pairs of 16-bit numbers, columns c and c + 32) or 64, behind them the
+// popcounts of the columns in a row like those and of the rows in 64 dwords
+constexpr int tab_row(bool half) { return half ? 8 : 16; }
+constexpr int slot_size(int pl, bool split, bool half) { return std::max((TM * pl + TN) * 128, split ? 65 * tab_row(half) + 16 : 0); }
 
 // PL bit planes per A row; XNOR: the xnor form (row popcounts from the words themselves), else the plane form (row sums given); OUT: what the
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
-// HALF: the partial tiles of a split cross LDS as fp16 pairs (exact while a wave's sums stay
-// at or below 2048, which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
+// HALF: the partial tiles of a split cross LDS as pairs of 16-bit whole numbers (full sums up to 65535,
+// which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
 // segments travel through registers (see fetch_segment; 2: rows that start on any dword).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
@@ -254,12 +305,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   extern __shared__ uint4 lds[];
   constexpr int NA = TM * PL, NB = NA + TN;  // staged blocks of 32 rows: A's, then B's
   constexpr int kStage = NB * 128;           // uint4 per staged segment: NB blocks x 32 rows x 64 bytes
-  constexpr int kGroups = TM * TN * 4;       // a wave's accumulators in units of four registers
-  constexpr int kCnt = (TM + TN) * 8;        // uint4 holding a wave's 32 (TM + TN) popcounts
-  // LDS per wave: its staging area, overlaid after the main loop of a split by its partial tile
-  // + counts.
-  constexpr int kPart = HALF ? kGroups * 32 : kGroups * 64;  // uint4 holding a wave's partial tile
-  constexpr int kSlot = (!SPLIT || kStage > kPart + kCnt) ? kStage : kPart + kCnt;
+  // LDS per wave: its staging area, overlaid after the main loop of a split by its partial tile and counts
+  constexpr int kSlot = slot_size(PL, SPLIT, HALF);
   // Everything the wave needs before its first load, named in one statement at the top: the
   // compiler then fetches the kernel arguments in one batch of scalar loads with one wait instead
   // of one memory round trip per group of first uses.
@@ -278,18 +325,15 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   const int tiles_per_wg = SPLIT ? 1 : (int)(blockDim.x >> 6);
   // workgroup b sits on XCD b % 8: give every XCD a contiguous run of tiles, rows of C fastest
   const int lin = ((int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3)) * tiles_per_wg + tile_in_wg;
-  const bool live = lin < p.tiles_m * p.tiles_n;
-  if (!SPLIT && !live) return;  // (no barrier ahead without a split)
+  if (lin >= p.tiles_m * p.tiles_n) return;  // (a whole workgroup of a split; without one there is no barrier ahead)
   // Within an XCD's run the tiles go band by band: a band is `band` rows of tiles high, and
   // inside it the rows of C run fastest, so the few hundred tiles in flight on an XCD at any time
   // form a block about as wide as high and share their operand rows through its L2.
-  int tile_m = 0, tile_n = 0;
-  if (live) {  // (divisions by multiply-high with constants from the host: this runs before the first load)
-    const int bnd = (int)fast_div((uint32_t)lin, p.div_per_band), within = lin - bnd * p.per_band;
-    const bool last = bnd == p.last_band;
-    tile_n = (int)fast_div((uint32_t)within, last ? p.div_last : p.div_band);
-    tile_m = bnd * p.band + (within - tile_n * (last ? p.last_rows : p.band));
-  }
+  // (divisions by multiply-high with constants from the host: this runs before the first load)
+  const int bnd = (int)fast_div((uint32_t)lin, p.div_per_band), within = lin - bnd * p.per_band;
+  const bool last = bnd == p.last_band;
+  const int tile_n = (int)fast_div((uint32_t)within, last ? p.div_last : p.div_band);
+  const int tile_m = bnd * p.band + (within - tile_n * (last ? p.last_rows : p.band));
   const int m0 = tile_m * (32 * TM), n0 = tile_n * (32 * TN);
 
   // ---- this wave's K range in groups of four words.  The first g_rem waves carry one group
@@ -334,16 +378,33 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 
   // The epilogue's constants are requested first of all (fetched where they are used, each would
   // put a trip to memory between the main loop and the stores; and ahead of the segments'
-  // loads they do not disturb the count of loads in flight that the main loop relies on).  Per column of
-  // this lane (column 32 j + r): alpha and the threshold of the sign decision; per row of the
-  // tile (64 of them), row m0 + l in lane l: the row sum of the plane form, alpha of the convolution form.
-  // (plain variables, not arrays: indexed by a run-time j in the reduction below, an array is
-  // put into scratch memory, whose every access also waits for the stores issued before it)
+  // loads they do not disturb the count of loads in flight that the main loop relies on).  Alpha and the threshold of the sign
+  // decision of this lane's columns: of a split columns lcol to lcol + 3 and 32 more of the tile, else r and 32 + r; per row of the
+  // tile (64 of them), row m0 + l in lane l: the row sum of the plane form, alpha and threshold of the convolution form.
+  // (undivided, plain variables: indexed by a run-time number an array is put into scratch memory, whose every access also waits
+  // for the stores issued before it)
+  const int lcol = 4 * (lane & 7);
+  const bool inside_n = n0 + 64 <= p.N;
+  auto of_columns = [&](const float* from, float none, v4f_any (&v)[2]) {
+    v[0] = v[1] = v4f_any{none, none, none, none};
+    if (!SPLIT || !from) return;
+    if (inside_n) {
+      v[0] = *(const v4f_any*)(from + n0 + lcol);
+      v[1] = *(const v4f_any*)(from + n0 + 32 + lcol);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e >> 2][e & 3] = from[min(n0 + 32 * (e >> 2) + lcol + (e & 3), p.N - 1)];
+    }
+  };
+  v4f_any al_c[2], th_c[2];
+  constexpr bool kAlpha = XNOR && !CONV && OUT != kOutI32, kThr = XNOR && !CONV && OUT == kOutBits;
+  of_columns(kAlpha ? p.alpha : nullptr, 1.0f, al_c);
+  of_columns(kThr ? p.thr : nullptr, 0.0f, th_c);
   const int n_c0 = min(n0 + r, p.N - 1), n_c1 = min(n0 + 32 + r, p.N - 1);
-  float aln0 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c0] : 1.0f;
-  float aln1 = (XNOR && !CONV && p.alpha) ? p.alpha[n_c1] : 1.0f;
-  float thn0 = (XNOR && !CONV && OUT == kOutBits && p.thr) ? p.thr[n_c0] : 0.0f;
-  float thn1 = (XNOR && !CONV && OUT == kOutBits && p.thr) ? p.thr[n_c1] : 0.0f;
+  float aln0 = !SPLIT && kAlpha && p.alpha ? p.alpha[n_c0] : 1.0f;
+  float aln1 = !SPLIT && kAlpha && p.alpha ? p.alpha[n_c1] : 1.0f;
+  float thn0 = !SPLIT && kThr && p.thr ? p.thr[n_c0] : 0.0f;
+  float thn1 = !SPLIT && kThr && p.thr ? p.thr[n_c1] : 0.0f;
   const int rowsum_lane = XNOR ? 0 : p.rowsum[min(m0 + lane, p.M - 1)];
   const float alpha_lane = (CONV && p.alpha) ? p.alpha[min(m0 + lane, p.M - 1)] : 1.0f;
   const float thr_lane = (CONV && OUT == kOutBits && p.thr) ? p.thr[min(m0 + lane, p.M - 1)] : 0.0f;
@@ -355,7 +416,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   }
   if constexpr (CONV && OUT == kOutBits) {
     // word tile_m of the output image's halo, spread over the tiles of this row of tiles
-    if (p.opad > 0 && live) {
+    if (p.opad > 0) {
       const int per_tile = SPLIT ? (int)blockDim.x : 64;
       write_halo((uint64_t*)p.C_bits, p.Nimg, p.Ho, p.Wo, p.opad, p.M, p.oCw, tile_m,
                  tile_n * per_tile + (SPLIT ? threadIdx.x : lane), p.tiles_n * per_tile);
@@ -370,7 +431,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = SPLIT && HALF ? kBias : 0.0f;
   int pa[TM], pb[TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i) pa[i] = 0;
@@ -430,41 +491,29 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #pragma unroll
         for (int j = 0; j < TN; ++j) pb[j] = add_popcount4(pb[j], w[NA + j][g]);
       }
-      uint4 hi[NB];
+      // One bit plane: unscaled MFMAs (with block scales one takes 17 clocks of its SIMD's issue, without 11, and the shifts that bring
+      // every plane's products to 1 cost less than that).  Two: E8M0 block scales, as the 2-bit values stand at one weight only and
+      // B's bits would all have to be shifted (level at 1024 x 1024 x 4096, 1.3 % behind at 1553 x 1344 x 4096).
+      auto mfma = [](const v8i& x, const v8i& y, const v16f& z, int n) {
+        if constexpr (PL == 1) return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 4, 4, 0, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 4, 4, 0, 128, 0, n == 1 ? 127 : n == 2 ? 126 : 128);
+      };
+      uint4 even[TM], odd[TM];
+      if constexpr (PL == 2) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
-        hi[b] = make_uint4(w[b][g].x >> 3, w[b][g].y >> 3, w[b][g].z >> 3, w[b][g].w >> 3);
+        for (int i = 0; i < TM; ++i) fold_planes(w[2 * i][g], w[2 * i + 1][g], &even[i], &odd[i]);
+      }
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        // E8M0 block scales: planes 0 and 3 hold 0.5 (x 2), plane 1 holds 1, plane 2 holds 2 (x 1/2)
-        const int sc = n == 1 ? 127 : (n == 2 ? 126 : 128);
-        v8i eb[TN];
+        v8i eb[TN], ea[TM];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) eb[j] = nibble_plane(w[NA + j][g], hi[NA + j], n);
-        if constexpr (PL == 2) {
-          // two bit planes: one operand whose nibbles hold the 2-bit value itself (E2M1 codes 0 to 3
-          // = 0, 0.5, 1, 1.5; block scale 2), so a row block costs one MFMA per column block, not two
-          v8i ea[TM];
+        for (int j = 0; j < TN; ++j) eb[j] = PL == 2 ? bit_plane(w[NA + j][g], n) : nibble_plane<true>(w[NA + j][g], n);
 #pragma unroll
-          for (int i = 0; i < TM; ++i) ea[i] = nibble_pair(w[2 * i][g], w[2 * i + 1][g], n);
+        for (int i = 0; i < TM; ++i) ea[i] = PL == 2 ? value_plane(even[i], odd[i], n) : nibble_plane<false>(w[i][g], n);
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ea[i], eb[j], acc[i][j], 4, 4, 0, 128, 0, sc);
-        } else {
-          v8i ea[NA];
-#pragma unroll
-          for (int b = 0; b < NA; ++b) ea[b] = nibble_plane(w[b][g], hi[b], n);
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int pl = 0; pl < PL; ++pl)
-#pragma unroll
-              for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ea[i * PL + pl], eb[j], acc[i][j], 4, 4, 0,
-                                                                           sc + pl, 0, sc);
-        }
+          for (int j = 0; j < TN; ++j) acc[i][j] = mfma(ea[i], eb[j], acc[i][j], n);
       }
     }
   }
@@ -472,292 +521,333 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   FP4_REALTIME(5);
   // The constants requested before the loop are taken in here, in one place: met for the first
   // time in the branches of the epilogue, each would get a wait of its own there, and such a
-  // wait also sits out every store issued before it.
-  asm volatile("" : "+v"(aln0), "+v"(aln1), "+v"(thn0), "+v"(thn1));
+  // wait also sits out every store issued before it.  The same for the arguments that only the epilogue
+  // reads: fetched where they are used, each is a trip to memory with the stores waiting behind it.
+  if constexpr (SPLIT) asm volatile("" : "+v"(al_c[0]), "+v"(al_c[1]), "+v"(th_c[0]), "+v"(th_c[1]));
+  else asm volatile("" : "+v"(aln0), "+v"(aln1), "+v"(thn0), "+v"(thn1));
   int rowsum_l = rowsum_lane;
   float alpha_l = alpha_lane, thr_l = thr_lane;
   asm volatile("" : "+v"(rowsum_l), "+v"(alpha_l), "+v"(thr_l));
+  const int M = p.M, N = p.N, Kreal = p.Kreal, as_count = OUT == kOutI32 ? p.as_count : 0, nt = p.nt;
+  char* const C = OUT == kOutBits ? (char*)p.C_bits : XNOR && OUT == kOutI32 ? (char*)p.C_i32 : (char*)p.C_f32;
+  char* const C2 = XNOR ? nullptr : (char*)p.C_i32;  // (the plane form stores either or both)
 
-  // CONV: where this lane's pixels' results go
-  uint32_t pix_img[TN], pix_rem[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = min(n0 + 32 * j + r, p.N - 1);
-    pix_img[j] = CONV ? fast_div((uint32_t)n, p.div_howo) : 0u;
-    pix_rem[j] = CONV ? (uint32_t)n - pix_img[j] * (uint32_t)p.HoWo : 0u;
-  }
-  // packed bits of the convolution form: word tile_m of pixel n0 + lane of the tile, filter m0 in its bit 0
-  auto store_word = [&](uint32_t lo, uint32_t hi) {
-    if (n0 + lane >= p.N || !live) return;
-    const uint32_t img = h ? pix_img[1] : pix_img[0], rem = h ? pix_rem[1] : pix_rem[0];
-    const uint32_t ho = fast_div(rem, p.div_wo), wo = rem - ho * (uint32_t)p.Wo;
-    const uint32_t word = ((img * (uint32_t)p.oHp + ho + (uint32_t)p.opad) * (uint32_t)p.oWp + wo + (uint32_t)p.opad) * (uint32_t)p.oCw + (uint32_t)tile_m;
-    ((uint64_t*)p.C_bits)[word] = (uint64_t)hi << 32 | lo;
-  };
   // ---- epilogue.  Register v of lane (r, h) in block (i, j) is C[32 i + 8 (v / 4) + 4 h + v % 4][32 j + r].
-  // tot: the full-K sum of the MFMA results; ra, cb: pc(A row), pc(B column) over the full K
-  // (plane form: ra = the row sum of the quantised activations).
-  // inside: the tile lies wholly inside C (wave-uniform), so no element needs its bounds tested
-  // nt: past the caches, which is worth 2 to 15 % where a run of 32 results is one whole 128-byte line.
-  // Where it is parts of two, each part would be a memory access of its own: 2017 x 6017 of C took
-  // 27 us with such stores and 12.3 us through L2, which joins them; 6016 columns 11.9 us either way.
-  auto finish = [&](auto inside_tag, auto nt_tag, int i, int j, int v, float tot, int ra, int cb, float al, float th) {
-    constexpr bool INSIDE = decltype(inside_tag)::value;
-    auto put = [&](auto value, auto* to) {
-      // (written out: as a builtin the compiler merges it with the ordinary store of the other branch,
-      // and the hint is gone)
-      if constexpr (decltype(nt_tag)::value) asm volatile("global_store_dword %0, %1, off nt" ::"v"(to), "v"(value) : "memory");
-      else *to = value;
-    };
-    const int mi = 32 * i + 8 * (v >> 2) + 4 * h + (v & 3);
-    const int m = m0 + mi, n = n0 + 32 * j + r;
-    const uint32_t idx = CONV ? (pix_img[j] * (uint32_t)p.M + (uint32_t)m) * (uint32_t)p.HoWo + pix_rem[j]
-                              : (uint32_t)(m * p.ldc + n);
-    if (!XNOR) {
-      if (INSIDE || (m < p.M && n < p.N && live)) {
-        const int sv = 2 * (int)tot - ra;
-        if (p.C_i32) put(sv, p.C_i32 + idx);
-        if (p.C_f32) put((float)sv / p.levels, p.C_f32 + idx);
-      }
-      return;
+  // Results are 32-bit elements, elems from row to row; row m0 of the tile (CONV: that channel of the image of the tile's first
+  // pixel) is the wave's, a lane's rows and columns lie behind it by less than 2^32 bytes (the launchers see to it).
+  const uint32_t elems = CONV ? (uint32_t)p.HoWo : (uint32_t)p.ldc;
+  uint64_t at0 = (uint64_t)((uint32_t)m0 * elems) * 4u;
+  uint32_t img0 = 0;
+  if (CONV) {
+    img0 = __builtin_amdgcn_readfirstlane(fast_div((uint32_t)n0, p.div_howo));
+    at0 += (uint64_t)(img0 * (uint32_t)M) * elems * 4u;
+  }
+  auto place = [&](int row, int n, bool* whole) -> uint32_t {  // whole: columns n to n + 3 are there, in a row
+    if (!CONV) {
+      *whole = n + 3 < N;
+      return ((uint32_t)row * elems + (uint32_t)n) * 4u;
     }
-    const float dot = (float)(p.Kreal - 2 * ra - 2 * cb) + 4.0f * tot;  // exact: integers below 2^24
-    if (OUT == kOutBits) {
-      // the 64-lane mask of the sign decision: its low half is 32 columns of row m, its high half
-      // the same columns of the row four below
-      const uint64_t mask = __ballot(live && n < p.N && al * dot >= th);
-      if (r == 0 && m < p.M && live)
-        p.C_bits[(uint32_t)(m * (2 * p.ldc) + (n >> 5))] = h ? (uint32_t)(mask >> 32) : (uint32_t)mask;
-    } else if (INSIDE || (m < p.M && n < p.N && live)) {
-      if (OUT == kOutI32) put(p.as_count ? ((int)dot + p.Kreal) >> 1 : (int)dot, p.C_i32 + idx);
-      else put(al * dot, p.C_f32 + idx);
-    }
+    const uint32_t m = (uint32_t)min(n, N - 1), img = fast_div(m, p.div_howo), rem = m - img * elems;
+    *whole = n + 3 < N && rem + 3 < elems;
+    return (((img - img0) * (uint32_t)M + (uint32_t)row) * elems + rem) * 4u;
   };
-  // popcounts: a lane counted its half of K for row / column r; the other half sits 32 lanes away
+  // packed bits of the convolution form: word tile_m of pixel n0 + lane of the tile, filter m0 in its bit 0
+  auto store_word = [&](uint64_t word) {
+    if (n0 + lane >= N) return;
+    const uint32_t img = fast_div((uint32_t)(n0 + lane), p.div_howo), rem = (uint32_t)(n0 + lane) - img * elems;
+    const uint32_t ho = fast_div(rem, p.div_wo), wo = rem - ho * (uint32_t)p.Wo;
+    ((uint64_t*)C)[((img * (uint32_t)p.oHp + ho + (uint32_t)p.opad) * (uint32_t)p.oWp + wo + (uint32_t)p.opad) * (uint32_t)p.oCw + (uint32_t)tile_m] = word;
+  };
+  // Popcounts: a lane counted its half of a group for row / column r of every block; one exchange of half waves and one addition
+  // leave row l and column l of the tile with lane l.
+  int row_l = 0, col_l = 0;
   if (XNOR) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) pa[i] += __shfl_xor(pa[i], 32);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) pb[j] += __shfl_xor(pb[j], 32);
+    const auto sa = __builtin_amdgcn_permlane32_swap(pa[0], pa[1], false, false);
+    const auto sb = __builtin_amdgcn_permlane32_swap(pb[0], pb[1], false, false);
+    row_l = (int)(sa[0] + sa[1]);
+    col_l = (int)(sb[0] + sb[1]);
   }
+  // A result is its row's term - its column's term + (the sum << mul).  xnor: K - 2 pc(a) - 2 pc(b) + 4 sum (the count of equal
+  // bits: K - pc(a) - pc(b) + 2 sum); planes: 2 sum - the row sum of the activations.
+  const int mul = XNOR ? 2 - (as_count != 0) : 1;
+  auto result = [&](int d, float al) {  // what is stored for it (C)
+    if (XNOR && OUT == kOutI32) return (uint32_t)d;
+    if (XNOR) return __float_as_uint(al * (float)d);
+    return __float_as_uint(PL == 2 ? third((float)d) : (float)d);
+  };
 
-  if constexpr (!SPLIT && CONV && OUT == kOutBits) {
-    uint32_t half[TN][TM];  // of pixel 32 j + r: filters 32 i .. 32 i + 31
+  if constexpr (!SPLIT) {
+    // The row terms of every result register first (a shuffle each: fetched one by one between the stores, each would cost an LDS
+    // round trip), then arithmetic and stores, a row of 64 results at a time, tiles that lie inside C without any bounds (5248 x 384 x
+    // 2048 6.95 us, masked 7.85; a store takes the load unit 16 clocks, which leaves a wave room for little else).  Through LDS for
+    // stores of 16 bytes a lane, as below, they are a quarter as many, but behind a trip through LDS: 4160 x 1056 x 128 6.36 / 6.52 us,
+    // 5248 x 384 x 2048 6.95 / 7.76, and rows of C that are not 16-byte aligned fall back further.
+    const int row_t = XNOR ? Kreal - (row_l << (mul - 1)) : -rowsum_l;
+    int ct[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int i = 0; i < TM; ++i) half[j][i] = 0u;
+    for (int j = 0; j < TN; ++j) ct[j] = XNOR ? __shfl(col_l << (mul - 1), 32 * j + r) : 0;
+    int rt[TM][16];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int bit = 8 * (v >> 2) + 4 * h + (v & 3), mi = 32 * i + bit;
-        const int ra = __shfl(pa[i], bit);
-        const float al = __shfl(alpha_l, mi), th = __shfl(thr_l, mi);
+      for (int v = 0; v < 16; ++v) rt[i][v] = __shfl(row_t, 32 * i + 8 * (v >> 2) + 4 * h + (v & 3));
+    if constexpr (CONV && OUT == kOutBits) {
+      uint32_t half[TN][TM];  // of pixel 32 j + r: filters 32 i .. 32 i + 31
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const float dot = (float)(p.Kreal - 2 * ra - 2 * pb[j]) + 4.0f * acc[i][j][v];
-          if (m0 + mi < p.M && al * dot >= th) half[j][i] |= 1u << bit;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) half[j][i] = 0u;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int bit = 8 * (v >> 2) + 4 * h + (v & 3), mi = 32 * i + bit;
+          const float al = __shfl(alpha_l, mi), th = __shfl(thr_l, mi);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const float dot = (float)(rt[i][v] - ct[j] + ((int)acc[i][j][v] << mul));
+            if (m0 + mi < M && al * dot >= th) half[j][i] |= 1u << bit;
+          }
         }
-      }
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int i = 0; i < TM; ++i) half[j][i] |= (uint32_t)__shfl_xor((int)half[j][i], 32);
-    store_word(h ? half[1][0] : half[0][0], h ? half[1][1] : half[0][1]);
-    return;
-  }
-  if (!SPLIT) {
-    // the row terms of every result register first (a shuffle each: fetched one by one between
-    // the stores, each would cost an LDS round trip), then nothing but arithmetic and stores
-    int ra[TM][16];
-    float alm[TM][16];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int mi = 32 * i + 8 * (v >> 2) + 4 * h + (v & 3);
-        ra[i][v] = XNOR ? __shfl(pa[i], mi & 31) : __shfl(rowsum_l, mi);
-        alm[i][v] = CONV ? __shfl(alpha_l, mi) : 1.0f;
-      }
-    auto store_tile = [&](auto inside_tag, auto nt_tag) {
+        for (int i = 0; i < TM; ++i) half[j][i] |= (uint32_t)__shfl_xor((int)half[j][i], 32);
+      store_word((uint64_t)(h ? half[1][1] : half[0][1]) << 32 | (h ? half[1][0] : half[0][0]));
+    } else if constexpr (OUT == kOutBits) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            finish(inside_tag, nt_tag, i, j, v, acc[i][j][v], ra[i][v], pb[j], CONV ? alm[i][v] : (j ? aln1 : aln0), j ? thn1 : thn0);
-    };
-    if (m0 + 32 * TM <= p.M && n0 + 32 * TN <= p.N) {
-      if (p.nt) store_tile(std::true_type{}, std::true_type{});
-      else store_tile(std::true_type{}, std::false_type{});
+          for (int j = 0; j < TN; ++j) {
+            // the 64-lane mask of the sign decision: its low half is 32 columns of row m, its high half
+            // the same columns of the row four below
+            const int m = m0 + 32 * i + 8 * (v >> 2) + 4 * h + (v & 3), n = n0 + 32 * j + r;
+            const float dot = (float)(rt[i][v] - ct[j] + ((int)acc[i][j][v] << mul));
+            const uint64_t mask = __ballot(n < N && (j ? aln1 : aln0) * dot >= (j ? thn1 : thn0));
+            if (r == 0 && m < M) ((uint32_t*)C)[(uint32_t)m * (2u * elems) + (uint32_t)(n >> 5)] = h ? (uint32_t)(mask >> 32) : (uint32_t)mask;
+          }
     } else {
-      store_tile(std::false_type{}, std::false_type{});
+      bool whole;
+      const uint32_t off0 = place(4 * h, n0 + r, &whole), off1 = place(4 * h, n0 + 32 + r, &whole);
+      // rows of the result from the lane's first on; none where its column lies outside
+      const int left0 = n0 + r < N ? M - m0 - 4 * h : 0, left1 = n0 + 32 + r < N ? M - m0 - 4 * h : 0;
+      float alm[TM][16];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) alm[i][v] = CONV && OUT == kOutF32 ? __shfl(alpha_l, 32 * i + 8 * (v >> 2) + 4 * h + (v & 3)) : 1.0f;
+      const uint64_t pitch = (uint64_t)elems * 4u;
+      auto store_tile = [&](auto nt_tag, auto masked_tag) {
+        constexpr bool NT = decltype(nt_tag)::value, MASKED = decltype(masked_tag)::value;
+#pragma unroll
+        for (int g = 0; g < TM * 4; ++g) {  // four rows of either half wave
+          const int i = g >> 2, q = g & 3, row = 8 * g;
+          if (MASKED && m0 + row >= M) break;
+          char* to = C + at0 + (uint64_t)(uint32_t)row * pitch;
+          char* to2 = C2 + at0 + (uint64_t)(uint32_t)row * pitch;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int v = 4 * q + e;
+            const int d0 = rt[i][v] - ct[0] + ((int)acc[i][0][v] << mul), d1 = rt[i][v] - ct[1] + ((int)acc[i][1][v] << mul);
+            const uint32_t v0 = result(d0, CONV ? alm[i][v] : aln0), v1 = result(d1, CONV ? alm[i][v] : aln1);
+            if (XNOR || C) store_two<NT, MASKED>(to, off0, off1, left0 - row, left1 - row, e, v0, v1);
+            if (!XNOR && C2) store_two<NT, MASKED>(to2, off0, off1, left0 - row, left1 - row, e, (uint32_t)d0, (uint32_t)d1);
+            to += pitch;
+            to2 += pitch;
+          }
+        }
+      };
+      // (Rows that are parts of lines, from several workgroups a CU at once: stored as fast as a wave can, the parts get in each
+      // other's way, and the bounds' instructions are the better pace: 4000 x 4001 x 128 13.7 / 14.7 us, 3520 x 6492 x 92 17.5 / 18.7;
+      // with at most one a CU 896 x 3384 x 5120 13.9 / 13.3, 640 x 3367 x 2532 9.15 / 8.6.)
+      if (m0 + 32 * TM > M || n0 + 32 * TN > N || (!nt && gridDim.x > 256)) store_tile(std::false_type{}, std::true_type{});
+      else if (nt) store_tile(std::true_type{}, std::false_type{});
+      else store_tile(std::false_type{}, std::false_type{});
     }
     return;
   }
 
-  // ---- K split: every wave writes its partial tile and its popcounts over its own staging
-  // areas (nothing of another wave's lies there), then finishes the accumulator groups
-  // g = wave, wave + S, ... : S partials in, one store out.
-  float4* part = (float4*)lds;
-  uint2* part16 = (uint2*)lds;  // HALF: four sums as two fp16 pairs, 8 bytes per lane and group
+  // ---- K split: every wave writes its part of every sum and its popcounts over its own staging area; a wave then finishes every
+  // S-th block of eight rows, adding up S parts, a lane four columns in a row and the four 32 further on: two stores of 16 bytes a
+  // lane for eight results, whole 128-byte lines, where stores from the MFMA's registers, a dword a lane, are four times as many
+  // (the load unit takes one in 16 clocks).  Row 8 b + 4 h + 2 e1 + e0 of the tile stands at place 8 b + 4 e0 + 2 e1 + h, so that
+  // the half waves write to different banks.
+  constexpr int kRow = tab_row(HALF);
+  u_alias* const tab = (u_alias*)(lds + wave * kSlot);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int g = (i * TN + j) * 4 + q;
-        if constexpr (HALF) {
-          const half2_t lo = __builtin_amdgcn_cvt_pkrtz(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-          const half2_t hi = __builtin_amdgcn_cvt_pkrtz(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-          part16[(wave * kSlot) * 2 + g * 64 + lane] = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-        } else {
-          part[wave * kSlot + g * 64 + lane] =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-        }
-      }
-  int* cnt = (int*)(part + wave * kSlot + kPart);  // [32 TM] row counts, [32 TN] column counts
-  uint32_t* const words = (uint32_t*)(lds + S * kSlot);  // packed bits of the convolution form: two dwords per pixel of the tile
-  if (CONV && OUT == kOutBits && wave == 0) words[lane] = words[64 + lane] = 0u;
-  if (XNOR && h == 0) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) cnt[32 * i + r] = pa[i];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) cnt[32 * TM + 32 * j + r] = pb[j];
-  }
-  __syncthreads();
-  FP4_STAMP(4);
-  // FULL: all eight waves split K (the usual case): no partial has to be masked out
-  auto reduce = [&](auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    // full-K popcounts: lane l sums row l of the tile (64 rows) and column l over the S
-    // waves' counts, one conflict-free read each; a lane then picks the rows and the column of
-    // its own results out of other lanes' registers
-    int pa_tot = rowsum_l, pb_tot = 0;  // (plane form: the row sum stands where the row count would)
-    if (XNOR) {
-      int ca[8], cb8[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int* c = (const int*)(part + (FULL || s < S ? s : S - 1) * kSlot + kPart);
-        ca[s] = c[lane];
-        cb8[s] = c[32 * TM + lane];
-      }
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        pa_tot += (FULL || s < S) ? ca[s] : 0;
-        pb_tot += (FULL || s < S) ? cb8[s] : 0;
-      }
+    for (int v = 0; v < 16; ++v) {
+      u_alias* const to = tab + (32 * i + 8 * (v >> 2) + 4 * (v & 1) + 2 * ((v >> 1) & 1) + h) * (4 * kRow) + r;
+      const uint32_t c0 = __float_as_uint(acc[i][0][v]), c1 = __float_as_uint(acc[i][1][v]);
+      // (HALF: the sums were started at kBias: a whole number below 2^16 stands in the low half of its register)
+      if constexpr (HALF) to[0] = __builtin_amdgcn_perm(c1, c0, 0x05040100u);
+      else to[0] = c0, to[32] = c1;
     }
-    // the popcount terms, scale and stores of accumulator group g, whose four sums are tot
-    auto finish_group = [&](int g, float4 tot) {
-      const int blk = g >> 2, q = g & 3, i = blk / TN, j = blk % TN;
-      const int row0 = 32 * i + 8 * q + 4 * h;  // this lane's four rows: row0 .. row0 + 3
-      int ra[4], cb = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ra[e] = __shfl(pa_tot, row0 + e);
-      if (XNOR) cb = __shfl(pb_tot, 32 * j + r);
-      const float al = j == 0 ? aln0 : aln1, th = j == 0 ? thn0 : thn1;
-      float alm[4] = {al, al, al, al};
-      if (CONV) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) alm[e] = __shfl(alpha_l, row0 + e);
-      }
-      if constexpr (CONV && OUT == kOutBits) {
-        const float t4[4] = {tot.x, tot.y, tot.z, tot.w};
-        uint32_t bits = 0u;
+  if (XNOR) {
+    if constexpr (HALF) ((u16_alias*)(tab + 64 * 4 * kRow))[2 * r + h] = (uint16_t)col_l;
+    else tab[64 * 4 * kRow + lane] = (uint32_t)col_l;
+    tab[65 * 4 * kRow + lane] = (uint32_t)row_l;
+  }
+  // this lane's places: row 8 b + mrow of the tile in block b, columns lcol + 32 k + e
+  const int mrow = 4 * (lane >> 3 & 1) + 2 * (lane >> 4 & 1) + (lane >> 5);
+  bool whole0 = false, whole1 = false;
+  uint32_t off0 = 0, off1 = 0;
+  if (OUT != kOutBits) {
+    off0 = place(mrow, n0 + lcol, &whole0);
+    off1 = place(mrow, n0 + lcol + 32, &whole1);
+  }
+  const int rows_left = M - m0 - mrow;  // of the lane's row in block 0 on
+  auto put = [&](char* base, int b, const uint32_t (&v)[8]) {
+    char* const to = base + at0 + (uint64_t)(uint32_t)(8 * b) * elems * 4u;
+    if (8 * b >= rows_left) return;
+    auto four = [&](bool whole, uint32_t off, int n, const uint32_t* d) {
+      if (whole) {
+        store_four(to, off, v4u{d[0], d[1], d[2], d[3]}, nt);
+      } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float thm = __shfl(thr_l, row0 + e);
-          const float dot = (float)(p.Kreal - 2 * ra[e] - 2 * cb) + 4.0f * t4[e];
-          if (m0 + row0 + e < p.M && alm[e] * dot >= thm) bits |= 1u << (8 * q + 4 * h + e);
+          bool one;
+          if (n + e < N) *(uint32_t*)(to + (CONV ? place(mrow, n + e, &one) : off + 4u * e)) = d[e];
         }
-        atomicOr(&words[2 * (32 * j + r) + i], bits);
-        return;
       }
-      auto put4 = [&](auto nt_tag) {
-        finish(std::false_type{}, nt_tag, i, j, 4 * q, tot.x, ra[0], cb, alm[0], th);
-        finish(std::false_type{}, nt_tag, i, j, 4 * q + 1, tot.y, ra[1], cb, alm[1], th);
-        finish(std::false_type{}, nt_tag, i, j, 4 * q + 2, tot.z, ra[2], cb, alm[2], th);
-        finish(std::false_type{}, nt_tag, i, j, 4 * q + 3, tot.w, ra[3], cb, alm[3], th);
-      };
-      if (OUT != kOutBits && p.nt) put4(std::true_type{});
-      else put4(std::false_type{});
     };
-    if constexpr (FULL && HALF) {
-      // Eight waves, fp16 partials (the fully connected layers): a wave has exactly kGroups / 8
-      // groups, and the partials of all of them are requested before the first is summed, so
-      // that the second group's LDS round trip runs under the first group's sums and stores.
-      constexpr int NG = kGroups / 8;
-      uint2 t[NG][8];
+    four(whole0, off0, n0 + lcol, v);
+    four(whole1, off1, n0 + lcol + 32, v + 4);
+  };
+  // packed bits of the convolution form: a byte per block of rows and pixel
+  u8_alias* const bytes = (u8_alias*)(lds + S * kSlot);
+  __syncthreads();
+  FP4_STAMP(4);
+  // WAVES: how many share K, 8 and 4 (the usual cases) as constants, 0: S, with parts past it masked out
+  auto reduce = [&](auto waves_tag) {
+    constexpr int WAVES = decltype(waves_tag)::value, R = WAVES ? WAVES : 8;
+    auto slot = [&](int s) { return lds + (WAVES || s < S ? s : S - 1) * kSlot; };
+    auto on = [&](int s, uint32_t v) { return WAVES || s < S ? v : 0u; };
+    // The parts of all of a wave's blocks are requested before the first is summed (32 registers), behind the column counts, so
+    // that the LDS round trips run under each other and under the sums and stores.
+    constexpr int NB8 = WAVES ? 8 / WAVES : 1, NT = HALF ? 1 : 2;  // blocks; 16-byte reads a part
+    uint4 cc[R][NT], part[NB8][R][NT];
+    auto request = [&](uint4 (&to)[R][NT], int row) {  // row `row` of eight lanes each
 #pragma unroll
-      for (int it = 0; it < NG; ++it)
+      for (int s = 0; s < R; ++s)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) t[it][s] = part16[(s * kSlot) * 2 + (wave + 8 * it) * 64 + lane];
+        for (int k = 0; k < NT; ++k) to[s][k] = slot(s)[row * kRow + 8 * k + (lane & 7)];
+    };
+    auto row_count = [&](int b) {
+      int c = 0;
 #pragma unroll
-      for (int it = 0; it < NG; ++it) {
-        float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int s = 0; s < R; ++s) c += (int)on(s, ((const u_alias*)(slot(s) + 65 * kRow))[8 * b + mrow]);
+      return c;
+    };
+    if (XNOR) request(cc, 64);
+    if constexpr (WAVES != 0 && HALF) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          // v_dot2_f32_f16 with (1, 0) or (0, 1) picks a half, widens it and adds it in one
-          // instruction (exact: whole numbers up to 2048, fp32 accumulation)
-          const half2_t lo = __builtin_bit_cast(half2_t, t[it][s].x), hi = __builtin_bit_cast(half2_t, t[it][s].y);
-          const half2_t first = {(__fp16)1.0f, (__fp16)0.0f}, second = {(__fp16)0.0f, (__fp16)1.0f};
-          tot.x = __builtin_amdgcn_fdot2(lo, first, tot.x, false);
-          tot.y = __builtin_amdgcn_fdot2(lo, second, tot.y, false);
-          tot.z = __builtin_amdgcn_fdot2(hi, first, tot.z, false);
-          tot.w = __builtin_amdgcn_fdot2(hi, second, tot.w, false);
-        }
-#ifdef BMX_FP4_STAMPS
-        if (it == 0) { FP4_STAMP(7); }
-#endif
-        finish_group(wave + 8 * it, tot);
-      }
-      return;
+      for (int it = 0; it < NB8; ++it) request(part[it], 8 * (wave + it * R) + (lane >> 3));
     }
-    for (int g = wave; g < kGroups; g += S) {
-      // all reads first (partials past S repeat the last one and count as nothing), so that the
-      // LDS round trips overlap instead of adding up
-      float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
+    // sums over the parts: eight numbers below 2^16 in four pairs, or eight fp32 numbers (whole below 2^24)
+    auto total = [&](const uint4 (&from)[R][NT], bool fp, int (&to)[8]) {
       if constexpr (HALF) {
-        uint2 t[8];
+        uint32_t x = 0, y = 0, z = 0, w = 0;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) t[s] = part16[((FULL || s < S ? s : S - 1) * kSlot) * 2 + g * 64 + lane];
+        for (int s = 0; s < R; ++s) x += on(s, from[s][0].x), y += on(s, from[s][0].y), z += on(s, from[s][0].z), w += on(s, from[s][0].w);
+        to[0] = x & 0xffffu, to[1] = y & 0xffffu, to[2] = z & 0xffffu, to[3] = w & 0xffffu;
+        to[4] = x >> 16, to[5] = y >> 16, to[6] = z >> 16, to[7] = w >> 16;
+      } else {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const bool on = FULL || s < S;
-          const half2_t lo = __builtin_bit_cast(half2_t, t[s].x), hi = __builtin_bit_cast(half2_t, t[s].y);
-          tot.x += on ? (float)lo[0] : 0.f;
-          tot.y += on ? (float)lo[1] : 0.f;
-          tot.z += on ? (float)hi[0] : 0.f;
-          tot.w += on ? (float)hi[1] : 0.f;
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            int sum = 0;
+#pragma unroll
+            for (int s = 0; s < R; ++s) {
+              const uint4& q = from[s][k];
+              const uint32_t v = on(s, e == 0 ? q.x : e == 1 ? q.y : e == 2 ? q.z : q.w);
+              sum += fp ? (int)__uint_as_float(v) : (int)v;
+            }
+            to[4 * k + e] = sum;
+          }
+        }
+      }
+    };
+    int ct[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (XNOR) {
+      total(cc, false, ct);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ct[e] <<= mul - 1;
+    }
+    auto finish = [&](const uint4 (&from)[R][NT], int b) {
+      const int rt = XNOR ? Kreal - (row_count(b) << (mul - 1)) : -__shfl(rowsum_l, 8 * b + mrow);
+      int d[8];
+      total(from, true, d);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[e] = (d[e] << mul) + (rt - ct[e]);
+#ifdef BMX_FP4_STAMPS
+      if (b == wave) { FP4_STAMP(7); }
+#endif
+      const float alm = CONV && OUT != kOutI32 ? __shfl(alpha_l, 8 * b + mrow) : 1.0f;
+      if constexpr (OUT == kOutBits) {
+        const float thm = CONV ? __shfl(thr_l, 8 * b + mrow) : 0.0f;
+        uint32_t w[2] = {0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float al = CONV ? alm : al_c[e >> 2][e & 3], th = CONV ? thm : th_c[e >> 2][e & 3];
+          const int place_of = CONV ? 8 * (e & 3) + mrow : lcol + (e & 3);
+          const bool there = CONV ? 8 * b < rows_left : n0 + 32 * (e >> 2) + lcol + (e & 3) < N;
+          if (there && al * (float)d[e] >= th) w[e >> 2] |= 1u << place_of;
+        }
+        // CONV: a pixel's byte from the eight lanes of its rows; else a row's two dwords from the eight lanes of its columns
+#pragma unroll
+        for (int x = CONV ? 8 : 1; x < (CONV ? 64 : 8); x *= 2) {
+          w[0] |= (uint32_t)__shfl_xor((int)w[0], x);
+          w[1] |= (uint32_t)__shfl_xor((int)w[1], x);
+        }
+        if (CONV) {
+          if (lane < 8) {
+            *(u_alias*)(bytes + 64 * b + lcol) = w[0];
+            *(u_alias*)(bytes + 64 * b + 32 + lcol) = w[1];
+          }
+        } else if ((lane & 7) == 0 && 8 * b < rows_left) {
+          // (m * ldc words fit 32 bits: the launcher checks)
+          ((uint64_t*)C)[(uint32_t)(m0 + 8 * b + mrow) * elems + (uint32_t)(n0 >> 6)] = (uint64_t)w[1] << 32 | w[0];
         }
       } else {
-        float4 t[8];
+        uint32_t v[8], s[8];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) t[s] = part[(FULL || s < S ? s : S - 1) * kSlot + g * 64 + lane];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const bool on = FULL || s < S;
-          tot.x += on ? t[s].x : 0.f;
-          tot.y += on ? t[s].y : 0.f;
-          tot.z += on ? t[s].z : 0.f;
-          tot.w += on ? t[s].w : 0.f;
+        for (int e = 0; e < 8; ++e) {
+          v[e] = result(d[e], CONV ? alm : al_c[e >> 2][e & 3]);
+          s[e] = (uint32_t)d[e];
         }
+        if (XNOR || C) put(C, b, v);
+        if (!XNOR && C2) put(C2, b, s);
       }
-#ifdef BMX_FP4_STAMPS
-      if (g == wave) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); FP4_STAMP(7); }
-#endif
-      finish_group(g, tot);
+    };
+    if constexpr (WAVES != 0) {
+#pragma unroll
+      for (int it = 0; it < NB8; ++it) {
+        if (!HALF) request(part[it], 8 * (wave + it * R) + (lane >> 3));
+        finish(part[it], wave + it * R);
+      }
+    } else {
+      for (int b = wave; b < 8; b += S) {
+        request(part[0], 8 * b + (lane >> 3));
+        finish(part[0], b);
+      }
     }
   };
-  if (S == 8) reduce(std::true_type{});
-  else reduce(std::false_type{});
+  if (S == 8) reduce(std::integral_constant<int, 8>{});
+  else if (S == 4) reduce(std::integral_constant<int, 4>{});
+  else reduce(std::integral_constant<int, 0>{});
   if constexpr (CONV && OUT == kOutBits) {
     __syncthreads();
-    if (wave == 0) store_word(words[2 * lane], words[2 * lane + 1]);
+    if (wave == 0) {
+      uint64_t word = 0;
+#pragma unroll
+      for (int b = 0; b < 8; ++b) word |= (uint64_t)bytes[64 * b + lane] << (8 * b);
+      store_word(word);
+    }
   }
   FP4_STAMP(5);
 #ifdef BMX_FP4_STAMPS
@@ -772,18 +862,15 @@ namespace {
 
 template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
-  constexpr int NB = TM * PL + TN, kStage = NB * 128, kGroups = TM * TN * 4, kCnt = (TM + TN) * 8;
-  constexpr int part = HALF ? kGroups * 32 : kGroups * 64;
-  constexpr int slot = (!SPLIT || kStage > part + kCnt) ? kStage : part + kCnt;
   const int waves = SPLIT ? S : tiles_per_wg;
-  const size_t lds = (size_t)waves * slot * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
+  const size_t lds = (size_t)waves * slot_size(PL, SPLIT, HALF) * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
   auto kern = gemm_fp4_kernel<PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
   note_kernel("gemm_fp4_kernel<%d,%d,%d,%s,%s%s> grid %lld x %d, K split %d%s, fp4", TM, TN, PL, XNOR ? "xnor" : "planes",
               !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? (REG ? ",conv,reg" : ",conv") : (REG ? ",reg" : ""),
-              (long long)blocks, 64 * waves, SPLIT ? S : 1, HALF ? " (fp16 partials)" : "");
+              (long long)blocks, 64 * waves, SPLIT ? S : 1, SPLIT && HALF ? " (16-bit partials)" : "");
 #ifdef BMX_FP4_STAMPS
   launch_kernel(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S, fp4_stamps);
 #else
@@ -793,11 +880,15 @@ hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t bloc
 }
 
 }  // namespace
-int gemm_fp4_band = 0;  // 0 = automatic (16), else rows of tiles per band of the tile order
+int gemm_fp4_band = 0;  // 0 = automatic, else rows of tiles per band of the tile order
 namespace {
 
-void set_tile_order(Fp4Params& p) {
-  p.band = gemm_fp4_band > 0 ? std::min(gemm_fp4_band, p.tiles_m) : std::min(16, p.tiles_m);
+// Rows of tiles per band: what an XCD has in flight should be about as high as wide, so that few operand rows pass its L2.
+// With K undivided that is several hundred tiles, 16 high; with K divided a tile a workgroup, 32 to 64 an XCD, 8 high (graph
+// times, 16 / 8: 1024 x 1024 x 4096 of 2 x 1 bits 14.3 / 14.0 us, 1852 x 384 x 6030 20.8 / 20.2, 1344 x 1325 x 5633 12.8 / 12.5; 4 and
+// 6 as 8).
+void set_tile_order(Fp4Params& p, int S) {
+  p.band = std::min(gemm_fp4_band > 0 ? gemm_fp4_band : S > 1 ? 8 : 16, p.tiles_m);
   p.per_band = p.band * p.tiles_n;
   p.last_band = (p.tiles_m - 1) / p.band;
   p.last_rows = p.tiles_m - p.last_band * p.band;
@@ -806,17 +897,14 @@ void set_tile_order(Fp4Params& p) {
   p.div_last = make_fast_div((uint32_t)p.last_rows);
 }
 
+// A full sum is at most (bits of K) x (2^planes - 1), a full count K: whether 16 bits hold them
+bool fits_16_bits(int64_t K, int planes) { return K * ((1 << planes) - 1) <= 65535; }
+
 template <int PL, bool XNOR, int OUT, bool CONV = false, int REG = 0>
 hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
-  if (S > 1) {
-    // a wave's partial sums are at most (its bits of K) x (2^PL - 1): whole numbers up to 2048
-    // are exact in fp16
-    const int64_t most = (int64_t)(p.g_base + (p.g_rem ? 1 : 0)) * 256 * ((1 << PL) - 1);
-    if (most <= 2048 && gemm_fp4_half != 2)
-      return launch_tile<PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s);
-    return launch_tile<PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
-  }
-  return launch_tile<PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+  if (S <= 1) return launch_tile<PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+  return fits_16_bits(p.Kreal, PL) && gemm_fp4_half != 2 ? launch_tile<PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s)
+                                                        : launch_tile<PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
 }
 
 }  // namespace
@@ -884,11 +972,9 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   const int ngroups = (int)ceil_div(p.Kw, 4);
   p.tiles_m = tiles_m;
   p.tiles_n = tiles_n;
-  set_tile_order(p);
   p.alpha = alpha_n;
   p.thr = thr_n;
   p.rowsum = rowsum;
-  p.levels = (float)((1u << planes) - 1u);
   p.as_count = as_count ? 1 : 0;
   p.C_i32 = C_i32;
   p.C_f32 = C_f32;
@@ -904,6 +990,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;
+  set_tile_order(p, S);
   p.g_base = ngroups / S;
   p.g_rem = ngroups - p.g_base * S;
   const int tiles_per_wg = 4;
@@ -948,6 +1035,9 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   if (P >= ((int64_t)1 << 31) || ((int64_t)Nimg * O + 64) * Ho * Wo >= ((int64_t)1 << 31)) return false;
   // (the halo's words are counted, and every word of the image addressed, in 32 bits)
   if (out_bits && (int64_t)Nimg * (Ho + 2 * out_pad) * (Wo + 2 * out_pad) * words_for(O) >= ((int64_t)1 << 30)) return false;
+  // (a tile's results are addressed with 32 bits from its first image on: a tile of three images or more has less than 63 pixels
+  // in each)
+  if (O >= (1 << 23) && Ho * Wo < 63) return false;
   const int tiles_m = (int)ceil_div(O, 64), tiles_n = (int)ceil_div(P, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   if (tiles >= ((int64_t)1 << 28)) return false;
@@ -964,11 +1054,9 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int ngroups = (int)ceil_div(kwords, 4);
   p.tiles_m = tiles_m;
   p.tiles_n = tiles_n;
-  set_tile_order(p);
   p.alpha = alpha;
   p.thr = thr;
   p.rowsum = nullptr;
-  p.levels = 1.0f;
   p.as_count = 0;
   p.C_i32 = out_i32;
   p.C_f32 = out_f32;
@@ -998,6 +1086,7 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   S = S > 8 ? 8 : S;
   if (S > ngroups) S = ngroups;
   if (S < 1) S = 1;
+  set_tile_order(p, S);
   p.g_base = ngroups / S;
   p.g_rem = ngroups - p.g_base * S;
   const int tiles_per_wg = 4;

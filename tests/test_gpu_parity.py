@@ -1491,6 +1491,34 @@ def test_gemm_fp4_lds_staged_kernel(split, partials):
                 assert_f32_close(fg.cpu().numpy(), r32)
 
 
+@pytest.mark.parametrize("split", [2, 4, 5, 8])
+@pytest.mark.parametrize("K", [65535, 65536])
+def test_gemm_fp4_largest_16_bit_sums(K, split):
+    """Partial sums and counts that cross LDS as 16-bit whole numbers, where they are largest: rows all set, so that the full sum
+    and both counts are K (65535 still fits, 65536 takes fp32 partials), all clear and mixed; a tile that reaches past C in both
+    directions, with rows of C that are whole lines and that are not; the two planes of 2-bit activations, whose sums reach 3 K."""
+    rng = np.random.default_rng(K + split)
+    with tuned(k7=5, k10=split):
+        for M, N in [(67, 96), (67, 70)]:
+            a, b = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+            a[:40], b[:50] = 1.0, 1.0
+            a[40:50], b[50:60] = -1.0, -1.0
+            A, Bm = B.binarize_pack(dev(a), 1), B.binarize_pack(dev(b), 1)
+            want = (a.clip(-1, 1) >= 0).astype(np.float64) * 2 - 1
+            want = (want @ ((b >= 0).astype(np.float64) * 2 - 1).T).astype(np.int32)
+            np.testing.assert_array_equal(B.xnor_gemm(A, Bm, K).cpu().numpy(), want)
+            assert ("16-bit partials" in B.last_kernel()) == (K <= 65535), B.last_kernel()
+            np.testing.assert_array_equal(B.xnor_gemm(A, Bm, K, count=True).cpu().numpy(), (want + K) // 2)
+        k = (K + 2) // 3
+        a, w = rng.uniform(0, 1, (67, k)).astype(np.float32), rng.standard_normal((70, k)).astype(np.float32)
+        a[:40], w[:50] = 1.0, 1.0
+        S, f = B.quant_gemm(dev(a), dev(w), 2)
+        assert "gemm_fp4_kernel" in B.last_kernel() or "gemm_mfma" in B.last_kernel() or "gemm_i8" in B.last_kernel()
+        rS, _, r32 = oracle.quant_gemm(a, w, 2)
+        np.testing.assert_array_equal(S.cpu().numpy(), rS)
+        np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(3))
+
+
 FP4_CONV_CASES = [
     # N, C, H, W, O, k, s, p   (an even number of channel words: 16-byte pieces never straddle two taps)
     (2, 128, 9, 9, 33, 5, 2, 2),

@@ -249,9 +249,10 @@ conv_one_kernel(const ConvOneParams p) {
         for (int j = 0; j < 4; ++j) x[j] = 4 * i + j < p.K ? x[j] : 0u;
       }
       if (i + 1 < last) read(i + 1);
+      // (without block scales, which cost the issue of an MFMA 6 clocks of 17: 7 x 130 x 29 x 27 5.30 -> 5.20 us)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(ef[j]), widen(expand_pixel(x[j])), acc, 4, 4, 0, 127, 0, 127);
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(ef[j]), widen(expand_pixel(x[j])), acc, 4, 4, 0, 0, 0, 0);
       if (i + 1 < last) expand_step(u, i + 1);
       __builtin_amdgcn_sched_barrier(0);  // (operands of later steps made early would spill: 128 registers)
     }

@@ -217,8 +217,9 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   // Against the kernels with an eye to K (us in a graph): the short-K kernel shares its filters, which pays
   // from a few hundred tiles on, and at 9 words from the first (18 words: 400 tiles 3.9 against 4.3, 700
   // tiles 4.3 / 4.0; 27 words: 95 tiles 3.3 / 4.8; 49 words: 530 tiles 5.3 / 6.0, 1170 tiles 8.4 / 8.0); the
-  // stationary kernel has nothing to share at 1 to 4 words.  A long K is gemm_fp4_kernel's from about
-  // 16384 tile steps on (17686: 6.7 / 9.0, 20250: 8.4 / 7.4).  As packed bits the line is where 3.4 us and 0.25 ns a tile
+  // stationary kernel has nothing to share at 1 to 4 words.  A long K is gemm_fp4_kernel's from
+  // 12288 tile steps on (its time over this kernel's: at 8000 to 12000 steps 1.0 to 1.2, at 12540 to 16000 0.81 to 1.07, mean 0.93),
+  // where it has 64 tiles of its own; from 16384 on in any case.  As packed bits the line is where 3.4 us and 0.25 ns a tile
   // step, this kernel's time, meet the estimate of the kernels for long K (211 filters, 3780 pixels, 196 words: 13.4 / 9.5; 32, 22707, 100,
   // half of their tiles empty: 7.5 / 10.9; 64, 20064, 63: 7.8 / 9.7), 12000 steps at least; and gemm_block.hip's for few words.
   if (conv_weight_short_k(K)) {
@@ -229,7 +230,7 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
     if (((uintptr_t)Wp & 15) == 0 && !conv_block && !gemm_fp4_split && !gemm_fp4_half && !gemm_fp4_band) {
       if (K < 8 ? tiles >= 7000 : work > 12000 && 3.4 + 2.5e-4 * work > conv_long_us(P, O, K, (Cw & 1) || ((uintptr_t)Xp & 15), &form)) return false;
     }
-  } else if (K == 1 || K == 2 || K == 4 || work > 16384 || tiles > 4096) {
+  } else if (K == 1 || K == 2 || K == 4 || work > (ceil_div(P, 64) * ceil_div(O, 64) >= 64 ? 12288 : 16384) || tiles > 4096) {
     return false;
   }
   int S = 1;

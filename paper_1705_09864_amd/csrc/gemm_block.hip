@@ -524,7 +524,10 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // workgroups a CU (512) are ahead from a K of 3500 on only (352 layers of 256 to 900 tiles: 1000 x 4000, 256 tiles, K 1600 8.2 /
   // 8.9, 2304 8.7 / 9.3, 4096 11.1 / 11.4, 9216 18.8 / 18.7; 2048 x 2048, 256, 2304 level, 4096 11.1 / 10.8; 1100 x 3700, 261,
   // 1600 11.5 / 12.0, 9216 29.0 / 28.5; 2300 x 2000, 288, 2304 12.8 / 13.7, 8192 26.5 / 26.5; 1042 x 5092, 360, 2560 13.0 / 13.8;
-  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).
+  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).  Int32 results of
+  // up to 1280 tiles of 64 x 64 and more than 33 words are that kernel's, which divides K over four waves there or has a wave for
+  // every SIMD (55 products of 769 to 1280, there / here: 0.96 to 0.75; 6719 x 704 x 4096, 1155, 11.9 / 15.7; 2176 x 1988 x 7808,
+  // 1088, 21.9 / 25.7).
   // The larger of the two shapes (us as 128 x 128 / as 256 x 128, each held for 50 ms): its waves read LDS and expand less for a
   // product, which shows once the chip's power has settled, where the results leave in whole lines and fill many rounds:
   // 8192 x 8192 x 8192 186 / 177, x 4096 106 / 102; 8192 x 12288 x 8192 277 / 263, 16384 x 8192 x 8192 370 / 352, 10240 x 10240 x
@@ -536,6 +539,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
     if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
     } else if (tiles < 256 || K < 700 || (C_f32 && tiles <= 512 && K < 3500) ||
+               (C_i32 && ceil_div(M, 64) * ceil_div(N, 64) <= 1280 && K > 64 * 33) ||
                (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {
       return false;
     }
@@ -575,8 +579,8 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
 
 int conv_block = 0;  // 1 = never, 2 = 128 filters x 128 pixels and 3 = 64 x 256 per workgroup whatever the size
 
-// Fitted to 169 convolutions of 45 to 392 words measured on each (us, fp32 results; the choice by it is 0.5 % off the best,
-// 17 % at most).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
+// Fitted to 169 convolutions of 45 to 392 words measured on each, and to 260 there since (us, fp32 results; the choice by it is 0.3 %
+// off the best, 18 % at most).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
 // through registers (an odd number of channel words).  Here by workgroups per CU; one alone on a CU takes more than half as
 // long for a segment as two together.
 double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
@@ -584,7 +588,7 @@ double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
   const double n = (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
   const double high = (double)ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256), mh = std::max(1.6, high);
   const double wide = (double)ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256), mw = std::max(1.6, wide);
-  const double there = any_dword ? 4.9 + n * (1.0 + 0.0285 * K) : 4.4 + n * (1.0 + 0.0245 * K);
+  const double there = any_dword ? 3.2 + n * (1.05 + 0.0273 * K) : 3.2 + n * (0.7 + 0.021 * K);
   const double us2 = any_dword ? 3.8 + 2.1 * high + 0.080 * mh * K : 2.4 + 3.2 * high + 0.063 * mh * K;
   const double us3 = any_dword ? 3.9 + 1.9 * wide + 0.0945 * mw * K : 0.7 + 4.5 * wide + 0.066 * mw * K;
   *form = std::min(us2, us3) >= there ? 0 : us2 <= us3 ? 2 : 3;

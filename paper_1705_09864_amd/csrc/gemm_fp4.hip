@@ -911,28 +911,33 @@ hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blo
 
 int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests of every split
 
-// Waves that share a tile's K: eight while every CU gets at most one tile, four up to four_up_to tiles
-// (two workgroups of four waves are resident on a CU), one beyond, and one where K is shorter than
-// `least` words: a wave's share is then less than the reduction costs.  Powers of two, so that the
-// SIMDs of a CU stay level: 390 x 3329 x 5632 (371 tiles) takes 10.4 us over four waves, 15.1 over five,
-// 12.2 over three; a 5 x 5 convolution over 384 channels of 42 x 38 x 37 (474 tiles) 14.0 over four, 17.1 over
-// three, 20 undivided; 1272 x 2474 x 2046 (780 tiles) 10.3 undivided, 12.7 over two.  An xnor product is divided
-// from 34 words on (1813 x 952 x 2393, 435 tiles: 9.1 over four, 10.3 undivided; 3331 x 403 x 1739: 9.7 / 8.4),
-// with its rows through registers, whose latency more waves hide, from 21 (2522 x 675 x 1344: 9.4 / 10.2; 424 x
-// 3607 x 3008: 10.0 / 13.3).  A product of bit planes from 22 (whole calls, pack and all: 517 x 1024 x 2432 of 2 x 1 bits
-// 14.2 over four, 18.9 undivided; 238 x 1024 x 1984 11.7 / 16.2; 478 x 456 x 1472 13.5 / 14.2; 1365 x 960 x 1728
-// of 1 x 1 16.0 / 15.8; 880 x 793 x 1216 15.2 / 13.8).
-static int choose_k_split(int64_t tiles, int kwords, int least, int four_up_to) {
-  if (kwords < least || tiles > four_up_to) return 1;
-  return tiles <= 256 ? 8 : 4;
+// Waves that share a tile's K: eight, four or one; powers of two, so that the SIMDs of a CU stay level (390 x 3329 x 5632, 371
+// tiles, takes 10.4 us over four waves, 15.1 over five, 12.2 over three).  From 350 products, 120 k-bit products and 200
+// convolutions measured with each (the mean of the time over the best of 8 / 4 / 1 waves):
+//   - up to a tile a CU (256), eight from 75 words on (1.00 / 1.04 / 2.1), four below (34 to 49 words 1.12 / 1.00 / 1.67, 50 to 74
+//     1.06 / 1.02 / 1.9): a wave's share is then less than the reduction of eight costs.  More waves hide the latency of rows
+//     that pass through registers, and of the patches of a convolution: there eight from 50 words on (1.00 / 1.11 / 2.3), and
+//     always (1.03 / 1.08 / 1.9).  Bit planes from 50 words on (1.00 / 1.02 / 1.4; 34 to 49 1.03 / 1.00 / 1.33).
+//   - up to three a CU four (257 to 512 tiles 1.25 / 1.00 / 1.44, 513 to 768 1.4 / 1.00 / 1.15), and with more than one, but few, for
+//     some SIMDs (1025 to 1280: 1.45 / 1.00 / 1.19).  Between them a SIMD has at most one undivided tile: one wave (1.5 / 1.03 / 1.00),
+//     but of 75 words on four (1.29 / 1.00 / 1.04).  Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09),
+//     and from 2049 to 2350 (- / 1.01 / 1.10; between, - / 1.09 / 1.04).
+//   - a K that divides into at least four shares of two groups: 20 words, bit planes 22, to 512 tiles (20 to 33 words: up to 128
+//     tiles 1.00 / 1.00 / 1.36, to 512 1.03 / 1.03 / 1.15); beyond, and with rows through registers always, 34 (513 to 640 1.22 /
+//     1.22 / 1.00).
+enum class Rows { direct, registers, planes, patches };
+static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
+  if (kwords < (rows == Rows::patches ? 1 : rows == Rows::planes ? 22 : rows == Rows::registers ? 21 : 20)) return 1;
+  if (tiles <= 256) return kwords >= (rows == Rows::patches ? 0 : rows == Rows::direct ? 75 : 50) ? 8 : 4;
+  if (tiles <= 512) return 4;
+  if (kwords < 34) return 1;
+  if (rows == Rows::patches && kwords >= 75) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
+  if (tiles <= 768 || (tiles > 1024 && tiles <= 1280)) return 4;
+  return tiles <= 1024 && kwords >= 75 && rows == Rows::direct ? 4 : 1;
 }
 
-// Below 64 tiles, and below 300 while K is short, kernels of 32 x 32 tiles: four times the waves, and
-// there is not enough K to give these tiles to several waves each.
-bool gemm_fp4_pays(int M, int N, int K) {
-  const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
-  return tiles >= (words_for(K) < 48 ? 300 : 64);
-}
+// Below 64 tiles kernels of 32 x 32 tiles: four times the waves, and there is not enough K to give these tiles to that many waves.
+bool gemm_fp4_pays(int M, int N) { return ceil_div(M, 64) * ceil_div(N, 64) >= 64; }
 
 // Takes the problem (rows of `dwords` data dwords) when sums stay exact in fp32, the
 // operands can be addressed with 32-bit byte offsets, and there are enough 64 x 64 tiles for
@@ -957,7 +962,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   const int Kwords = (int)words_for(K);
-  if (gemm_engine != 5 && (tiles < 64 || (!rowsum && !gemm_fp4_pays(M, N, K)))) return false;
+  if (gemm_engine != 5 && !gemm_fp4_pays(M, N)) return false;
   if (tiles >= ((int64_t)1 << 28)) return false;
   Fp4Params p;
   p.A = A;
@@ -986,7 +991,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
-  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? 22 : reg ? 21 : 34, 512);
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? Rows::planes : reg ? Rows::registers : Rows::direct);
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;
@@ -1082,7 +1087,7 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   p.div_wo = make_fast_div((uint32_t)Wo);
   p.div_run = make_fast_div(p.run_pieces);
   // (a wave may carry a single group of 256 bits)
-  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, kwords, 0, kwords >= 75 ? 1100 : 512);
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, kwords, Rows::patches);
   S = S > 8 ? 8 : S;
   if (S > ngroups) S = ngroups;
   if (S < 1) S = 1;

@@ -183,12 +183,17 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const int64_t tiles_n = C_bits ? ceil_div(N, 64) * 2 : ceil_div(N, 32);  // (both halves of the last word)
   const int64_t tiles = ceil_div(M, 32) * tiles_n;
   const int steps = (dwords + 7) / 8;
-  // Up to 8192 tile steps (us in a graph: 12 x 4870 x 6240 3.8 against 6.0, 366 x 3003 x 1594 5.8 / 8.1, 1238 x
-  // 3312 x 226 6.4 / 7.7; 2144 x 311 x 3912, 10720 steps, 6.8 / 5.9), half as many more where there are too few 64 x 64
-  // tiles for gemm_fp4_kernel; of a K of more than four steps for each of sixteen waves only few
-  // (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
-  const int64_t work = tiles * steps;
-  if (work > (steps > 64 ? 2048 : gemm_fp4_pays(M, N, K) ? 8192 : 12288) || tiles > 4096) return false;
+  // Against gemm_fp4_kernel, from 260 products of 2500 to 13000 tile steps (its time over this kernel's, in a graph): below 512 of
+  // its tiles up to 7500 tile steps (128 to 255 tiles 1.0 to 1.5, at 8100 to 11600 steps 0.72 to 0.85; 256 to 511 1.0 to 1.5, at 7900
+  // to 8700 0.86 to 0.95), below 128 up to 8192 (1.0 to 1.5); from 512 on only where K is a single step (two and more 0.85 to 1.0; 5760 x
+  // 339 x 72 5.4 / 5.0).  Rows that pass through registers there up to 8192
+  // steps (7344 1.06, 7696 1.11, 8190 1.09) and 800 tiles (0.94 to 0.98).  Half as many steps more where there are too few 64 x 64
+  // tiles for that kernel; of a K of more than four steps for each of sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and
+  // 4096 tiles, where the results outweigh the rest.
+  const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
+  const bool direct = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15) && !(dwords & 1);
+  if (work > (steps > 64 ? 2048 : !gemm_fp4_pays(M, N) ? 12288 : direct && tiles64 >= 128 ? 7500 : 8192) || tiles > 4096) return false;
+  if (!C_bits && steps > 1 && tiles64 >= (direct ? 512 : 800)) return false;
   int S = 1;
   while (S < 16 && 2 * S <= steps && 2 * S * tiles <= (work > 8192 ? 8192 : 4096)) S *= 2;
   SmallGemmParams p;

@@ -1519,6 +1519,37 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
         np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(3))
 
 
+@pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 2), (16, 16, 74, 4), (16, 16, 76, 8), (16, 32, 32, 4),
+                                               (19, 27, 32, 1), (19, 27, 34, 4), (24, 32, 34, 4), (24, 33, 34, 1), (24, 33, 76, 4),
+                                               (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
+def test_gemm_fp4_split_lines(tm, tn, words, split):
+    """Both sides of the lines between the waves that share a tile's K, by the tiles and words; a last tile of one row and one
+    column; the same results undivided."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tm * tn + words)
+    A, W = (torch.randint(-2 ** 62, 2 ** 62, (64 * n - 63, words), device="cuda", generator=g) for n in (tm, tn))
+    with tuned(k17=1, k19=1):
+        got = B.xnor_gemm(A, W, 64 * words)
+        assert "K split %d" % split in B.last_kernel(), B.last_kernel()
+    with tuned(k7=5, k10=1 if split > 1 else 4):
+        want = B.xnor_gemm(A, W, 64 * words)
+        assert "K split %d" % split not in B.last_kernel(), B.last_kernel()
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, False), (1024, 4032, 2, True), (1024, 1024, 28, True),
+                                             (1024, 1024, 30, False), (512, 512, 126, True), (512, 512, 130, False)])
+def test_gemm_small_lines(M, N, words, small):
+    """Both sides of the lines between the kernel of 32 x 32 and that of 64 x 64 tiles; the same results from the popcount kernel."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + words)
+    A, W = (torch.randint(-2 ** 62, 2 ** 62, (n, words), device="cuda", generator=g) for n in (M, N))
+    got = B.xnor_gemm(A, W, 64 * words)
+    assert ("gemm_small" in B.last_kernel()) == small, B.last_kernel()
+    with tuned(k7=1):
+        assert torch.equal(got, B.xnor_gemm(A, W, 64 * words))
+
+
 FP4_CONV_CASES = [
     # N, C, H, W, O, k, s, p   (an even number of channel words: 16-byte pieces never straddle two taps)
     (2, 128, 9, 9, 33, 5, 2, 2),

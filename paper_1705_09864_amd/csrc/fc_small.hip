@@ -16,7 +16,6 @@
 #include "bmx_internal.h"
 
 #include <algorithm>
-#include <climits>
 
 namespace bmx {
 
@@ -231,11 +230,13 @@ struct Lanes {
 };
 constexpr int features_per_pass(int L) { return L == 4 ? 16 : L == 16 ? 8 : 2; }
 Lanes lanes_of(int L, int Kw) {
-  Lanes best = {L, 4, INT_MAX};
-  for (int W = 4; W >= 2; --W) {
-    const int padded = (Kw + W * L - 1) / (W * L) * (W * L);
-    if (padded < best.padded) best.padded = padded, best.W = W;
-  }
+  // (in columns of L words and by constants only: six divisions were a percent of a small call)
+  const unsigned cols = (unsigned)(Kw + L - 1) >> (L == 4 ? 2 : L == 16 ? 4 : 6);
+  const unsigned four = (cols + 3) / 4 * 4, three = (cols + 2) / 3 * 3, two = (cols + 1) / 2 * 2;
+  Lanes best = {L, 4, (int)four};
+  if (three < four) best.W = 3, best.padded = (int)three;
+  if ((int)two < best.padded) best.W = 2, best.padded = (int)two;
+  best.padded *= L;
   return best;
 }
 

@@ -1550,6 +1550,26 @@ def test_gemm_small_lines(M, N, words, small):
         assert torch.equal(got, B.xnor_gemm(A, W, 64 * words))
 
 
+@pytest.mark.parametrize("O", [5, 33, 63, 64, 70])
+@pytest.mark.parametrize("C,k", [(64, 3), (100, 3), (64, 5)])
+def test_conv_bits_decisions(C, k, O):
+    """Packed results of the short-K convolution, decisions shifted in as carries: filters that end inside a word and inside its
+    halves, thresholds that results meet exactly, infinities and NaN on either side."""
+    rng = np.random.default_rng(C + 10 * k + O)
+    x, w = rng.standard_normal((9, C, 13, 11)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha = rng.choice([0.5, -0.25, 1.0, 0.0, np.inf, np.nan], O, p=[0.4, 0.2, 0.2, 0.1, 0.05, 0.05]).astype(np.float32)
+    thr = (rng.choice([0.5, -0.25, 1.0], O) * rng.integers(-20, 20, O) * 2).astype(np.float32)
+    thr[::7], thr[3::7], thr[5::7] = 0.0, rng.choice([np.inf, -np.inf]), np.nan
+    Wp, xp = B.pack_conv_weights(dev(w)), B.pack_nchw(dev(x), k // 2)
+    with tuned(k18=1):
+        got = B.binary_conv2d_bits(xp, C, Wp, O, k, k, 1, k // 2, alpha=dev(alpha), thr=dev(thr), out_pad=1)
+        assert "conv_mfma_ws" in B.last_kernel(), B.last_kernel()
+    f = B.binary_conv2d_packed(xp, C, Wp, O, k, k, 1, k // 2, integer_out=True).cpu().numpy().astype(np.float32)
+    with np.errstate(invalid="ignore"):
+        want = np.where(alpha[None, :, None, None] * f >= thr[None, :, None, None], np.float32(1), np.float32(-1))
+    assert torch.equal(got, B.pack_nchw(dev(want), 1))
+
+
 FP4_CONV_CASES = [
     # N, C, H, W, O, k, s, p   (an even number of channel words: 16-byte pieces never straddle two taps)
     (2, 128, 9, 9, 33, 5, 2, 2),

@@ -231,7 +231,12 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 // Four results in a row, `off` bytes behind an address that the wave shares.  NT: past the caches.  (As asm: as a builtin the
 // compiler merges the hinted store with the ordinary one of the other branch, and the hint is gone.  What follows a 16-byte store
 // may not write its registers in the next instruction, which the compiler sees to only where it knows of the store.)
+// (BMX_FP4_STAMPS: the stamps' branches make the compiler take the wave's address for the lanes': plain stores in that build)
 __device__ __forceinline__ void store_four(char* to, uint32_t off, const v4u& v, bool nt) {
+#ifdef BMX_FP4_STAMPS
+  *(v4u_any*)(to + off) = v;
+  return;
+#endif
   if (nt) asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" ::"v"(off), "v"(v), "s"(to) : "memory");
   else asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(off), "v"(v), "s"(to) : "memory");
 }
@@ -241,6 +246,11 @@ __device__ __forceinline__ void store_four(char* to, uint32_t off, const v4u& v,
 // instruction and three scalar ones a result.
 template <bool NT, bool MASKED>
 __device__ __forceinline__ void store_two(char* to, uint32_t off0, uint32_t off1, int left0, int left1, int e, uint32_t v0, uint32_t v1) {
+#ifdef BMX_FP4_STAMPS
+  if (!MASKED || e < left0) *(uint32_t*)(to + off0) = v0;
+  if (!MASKED || e < left1) *(uint32_t*)(to + off1) = v1;
+  return;
+#endif
   if constexpr (MASKED) {
     uint64_t all;
     asm volatile("s_mov_b64 %0, exec\n\tv_cmp_lt_i32_e32 vcc, %8, %3\n\ts_and_b64 exec, %0, vcc\n\tglobal_store_dword %1, %5, %7\n\ts_mov_b64 exec, %0\n\t"

@@ -924,10 +924,12 @@ int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests
 // Waves that share a tile's K: eight, four or one; powers of two, so that the SIMDs of a CU stay level (390 x 3329 x 5632, 371
 // tiles, takes 10.4 us over four waves, 15.1 over five, 12.2 over three).  From 350 products, 120 k-bit products and 200
 // convolutions measured with each (the mean of the time over the best of 8 / 4 / 1 waves):
-//   - up to a tile a CU (256), eight from 75 words on (1.00 / 1.04 / 2.1), four below (34 to 49 words 1.12 / 1.00 / 1.67, 50 to 74
-//     1.06 / 1.02 / 1.9): a wave's share is then less than the reduction of eight costs.  More waves hide the latency of rows
-//     that pass through registers, and of the patches of a convolution: there eight from 50 words on (1.00 / 1.11 / 2.3), and
-//     always (1.03 / 1.08 / 1.9).  Bit planes from 50 words on (1.00 / 1.02 / 1.4; 34 to 49 1.03 / 1.00 / 1.33).
+//   - up to a tile a CU (256), eight from 61 words on, where each of the eight has a share (graph times, 8 / 4, 64 to 256 tiles: 62
+//     words 0.96 to 0.97, 64 0.96, 66 0.97 to 1.01, 70 0.94, 74 0.97 to 1.02, 80 0.94 to 0.98; a whole layer of 256 tiles and 64
+//     words 7.25 / 7.57 us), four below (34 to 49 words 1.12 / 1.00 / 1.67): a wave's share is then less than the reduction of more
+//     costs.  More waves hide the latency of rows that pass through registers, and of the patches of a convolution: there eight
+//     from 50 words on (1.00 / 1.11 / 2.3), and always (1.03 / 1.08 / 1.9).  Bit planes from 50 words on (1.00 / 1.02 / 1.4; 34 to
+//     49 1.03 / 1.00 / 1.33).
 //   - up to three a CU four (257 to 512 tiles 1.25 / 1.00 / 1.44, 513 to 768 1.4 / 1.00 / 1.15), and with more than one, but few, for
 //     some SIMDs (1025 to 1280: 1.45 / 1.00 / 1.19).  Between them a SIMD has at most one undivided tile: one wave (1.5 / 1.03 / 1.00),
 //     but of 75 words on four (1.29 / 1.00 / 1.04).  Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09),
@@ -938,7 +940,7 @@ int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests
 enum class Rows { direct, registers, planes, patches };
 static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
   if (kwords < (rows == Rows::patches ? 1 : rows == Rows::planes ? 22 : rows == Rows::registers ? 21 : 20)) return 1;
-  if (tiles <= 256) return kwords >= (rows == Rows::patches ? 0 : rows == Rows::direct ? 75 : 50) ? 8 : 4;
+  if (tiles <= 256) return kwords >= (rows == Rows::patches ? 0 : rows == Rows::direct ? 61 : 50) ? 8 : 4;
   if (tiles <= 512) return 4;
   if (kwords < 34) return 1;
   if (rows == Rows::patches && kwords >= 75) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;

@@ -1519,7 +1519,7 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
         np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(3))
 
 
-@pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 2), (16, 16, 74, 4), (16, 16, 76, 8), (16, 32, 32, 4),
+@pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 2), (16, 16, 60, 4), (16, 16, 61, 8), (16, 32, 32, 4),
                                                (19, 27, 32, 1), (19, 27, 34, 4), (24, 32, 34, 4), (24, 33, 34, 1), (24, 33, 76, 4),
                                                (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
 def test_gemm_fp4_split_lines(tm, tn, words, split):

@@ -85,12 +85,9 @@ constexpr int kF32 = 0, kI32 = 1, kBits = 2;
 __device__ __forceinline__ v4i plane(const uint4& w, int n) {
   const uint32_t m = 0x11111111u << n;
   if (n == 3) {
-    // (as asm: the compiler takes two instructions for it, as if the constant could not stay in a register)
-    auto sign = [&](uint32_t v) {
-      int e;
-      asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(e) : "v"(v), "s"(0x88888888u), "v"(0x22222222u));
-      return e;
-    };
+    // (v & 8s | 2s, named as the one instruction that it is: from the operators the compiler makes two, as if the constant could not
+    // stay in a register; written as asm it would not know to keep two wait states between it and the MFMA that reads it)
+    auto sign = [](uint32_t v) { return (int)__builtin_amdgcn_bitop3_b32(v, 0x88888888u, 0x22222222u, 0xf0 & 0xcc | 0xaa); };
     return v4i{sign(w.x), sign(w.y), sign(w.z), sign(w.w)};
   }
   return v4i{(int)(w.x & m), (int)(w.y & m), (int)(w.z & m), (int)(w.w & m)};

@@ -74,7 +74,7 @@ def scan(path):
                 inflight.append((tuple(sorted(dst)), i))
     return sorted(out, key=lambda e: e[1])
 
-WAIT_SGPR_VALU, WAIT_SGPR_MEMORY, WAIT_LANES, WAIT_MFMA, WAIT_TRANS = 2, 5, 2, 20, 1
+WAIT_SGPR_VALU, WAIT_SGPR_MEMORY, WAIT_LANES, WAIT_MFMA, WAIT_TRANS, WAIT_STORE = 2, 5, 2, 20, 1, 2
 TRANS = ('v_rcp', 'v_rsq', 'v_sqrt', 'v_exp', 'v_log', 'v_sin', 'v_cos')
 
 def operands(tok):
@@ -92,8 +92,9 @@ def asm_hazards(path):
     compare's mask, v_readlane) needs two wait states before the vector ALU reads it and five before a
     memory instruction does, a matrix-core result up to twenty (the longest of the documented cases is
     taken for all), a transcendental result one, and a vector result two before an instruction across
-    lanes (DPP, permlane, readlane) reads it.  The compiler puts s_nop between its own instructions; a
-    pair of which one is written as asm gets none.  Walks every kernel along all its edges with the least
+    lanes (DPP, permlane, readlane) or a matrix-core instruction reads it; and the registers that a store of more
+    than two dwords sends may be written two wait states behind it.  The compiler puts s_nop between its own
+    instructions; a pair of which one is written as asm gets none.  Walks every kernel along all its edges with the least
     number of wait states since each such write, and reports every pair with too few:
     (kernel, line, text, register, wait states there, wait states needed)."""
     rows, kern, in_asm = [], None, False  # labels, kernel starts and instructions with what they read and write
@@ -119,12 +120,15 @@ def asm_hazards(path):
         reader = {}  # wait states that this instruction needs behind each kind of write
         if in_asm and memory: reader = {'sgpr': WAIT_SGPR_MEMORY, 'mfma': WAIT_MFMA}
         elif in_asm and op.startswith('v_'): reader = {'sgpr': WAIT_SGPR_VALU, 'mfma': WAIT_MFMA, 'trans': WAIT_TRANS}
-        if lanes: reader['asm'] = WAIT_LANES
+        matrix = op.startswith(('v_mfma', 'v_smfma'))
+        if lanes or matrix: reader['asm'] = WAIT_LANES
         writes = []
+        if in_asm and memory and 'store' in op and re.search(r'x[34]|b96|b128', op):
+            writes += [(r, 'store') for r in operands(args[0 if op.startswith('buffer_') else 1])]
         if op.startswith('v_'):
             for r in dst:
                 if r[0] == 's' or r == 'vcc': writes.append((r, 'sgpr'))
-                elif op.startswith(('v_mfma', 'v_smfma')): writes.append((r, 'mfma'))
+                elif matrix: writes.append((r, 'mfma'))
                 elif op.startswith(TRANS): writes.append((r, 'trans'))
                 elif in_asm: writes.append((r, 'asm'))
         step = int(args[0], 0) + 1 if op == 's_nop' else 1
@@ -138,9 +142,9 @@ def asm_hazards(path):
                 for k, n in label_in.get(row[1:], {}).items(): state[k] = min(n, state.get(k, n))
                 continue
             i, kern, op, t, dst, src, reader, writes, step, to = row
-            if reader:
-                for (r, kind), n in state.items():
-                    if r in src and n < reader.get(kind, 0): found[i] = (kern, i + 1, t, r, n, reader[kind])
+            for (r, kind), n in state.items():
+                if r in src and n < reader.get(kind, 0): found[i] = (kern, i + 1, t, r, n, reader[kind])
+                if kind == 'store' and r in dst and op.startswith('v_') and n < WAIT_STORE: found[i] = (kern, i + 1, t, r, n, WAIT_STORE)
             if state:
                 state = {k: n + step for k, n in state.items() if n + step < WAIT_MFMA and k[0] not in dst}
             for k in writes: state[k] = 0
@@ -152,7 +156,7 @@ def asm_hazards(path):
     return [found[i] for i in sorted(found)]
 
 def report_hazards(bad, limit=40):
-    return "\n".join("%s: line %d: '%s' reads %s after %d wait states of %d" % e for e in bad[:limit])
+    return "\n".join("%s: line %d: '%s' touches %s after %d wait states of %d" % e for e in bad[:limit])
 
 def report(bad, limit=40):
     lines = ["%s: line %d: '%s' %s SGPR %s of the scalar load issued at line %d" % e for e in bad[:limit]]

@@ -89,6 +89,24 @@ _Z4kernv:
 	;;#ASMEND
 	s_endpgm
 """
+# an operand of a matrix-core instruction made by an asm statement
+HAZARD_OPERAND = """
+_Z4kernv:
+	;;#ASMSTART
+	v_and_or_b32 v23, v30, s4, v31
+	;;#ASMEND
+	v_mfma_i32_32x32x32_i8 v[0:15], v[20:23], v[24:27], v[0:15]
+	s_endpgm
+"""
+# a wide store as asm, and the compiler's next use of a register that it sends
+HAZARD_STORE = """
+_Z4kernv:
+	;;#ASMSTART
+	global_store_dwordx4 v9, v[10:13], s[0:1] nt
+	;;#ASMEND
+	v_mov_b32_e32 v13, 0
+	s_endpgm
+"""
 # (text, wait states there, wait states needed), None where nothing is to be reported
 HAZARDS = [
     (HAZARD, (1, 2)),
@@ -102,6 +120,15 @@ HAZARDS = [
         "s_endpgm", "v_mov_b32_dpp v1, v10 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\ts_endpgm"), (0, 2)),
     (HAZARD.replace("v_cmp_le_f32_e64 s[0:1], 0, v11", "v_mfma_i32_32x32x32_i8 v[0:15], v[20:23], v[24:27], v[0:15]").replace(
         "v_writelane_b32 v10, s1, 3", "v_bcnt_u32_b32 v30, v15, v30"), (1, 20)),
+    (HAZARD_OPERAND, (0, 2)),
+    (HAZARD_OPERAND.replace(";;#ASMEND", ";;#ASMEND\n\tv_mov_b32_e32 v40, 0"), (1, 2)),
+    (HAZARD_OPERAND.replace(";;#ASMEND", "s_nop 1\n\t;;#ASMEND"), None),
+    (HAZARD_OPERAND.replace(";;#ASMSTART", "").replace(";;#ASMEND", ""), None),
+    (HAZARD_STORE, (0, 2)),
+    (HAZARD_STORE.replace(";;#ASMEND", "s_nop 0\n\t;;#ASMEND"), (1, 2)),
+    (HAZARD_STORE.replace(";;#ASMEND", "s_nop 1\n\t;;#ASMEND"), None),
+    (HAZARD_STORE.replace("v_mov_b32_e32 v13", "v_mov_b32_e32 v14"), None),  # (v14 is not sent)
+    (HAZARD_STORE.replace("dwordx4", "dwordx2").replace("v[10:13]", "v[12:13]"), None),
 ]
 
 

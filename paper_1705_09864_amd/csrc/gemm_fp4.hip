@@ -731,7 +731,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   u8_alias* const bytes = (u8_alias*)(lds + S * kSlot);
   __syncthreads();
   FP4_STAMP(4);
-  // WAVES: how many share K, 8 and 4 (the usual cases) as constants, 0: S, with parts past it masked out
+  // WAVES: how many share K, 8 and 4 (the usual cases) as constants, 0: S (three where K is short), with parts past it masked out
   auto reduce = [&](auto waves_tag) {
     constexpr int WAVES = decltype(waves_tag)::value, R = WAVES ? WAVES : 8;
     auto slot = [&](int s) { return lds + (WAVES || s < S ? s : S - 1) * kSlot; };
@@ -921,29 +921,32 @@ hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blo
 
 int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests of every split
 
-// Waves that share a tile's K: eight, four or one; powers of two, so that the SIMDs of a CU stay level (390 x 3329 x 5632, 371
-// tiles, takes 10.4 us over four waves, 15.1 over five, 12.2 over three).  From 350 products, 120 k-bit products and 200
-// convolutions measured with each (the mean of the time over the best of 8 / 4 / 1 waves):
-//   - up to a tile a CU (256), eight from 61 words on, where each of the eight has a share (graph times, 8 / 4, 64 to 256 tiles: 62
+// Waves that share a tile's K.  From 350 products, 120 k-bit products and 200 convolutions measured with each, and 1500 products
+// of few words since (the mean of the time over the best; graph times):
+//   - eight where each has a share of two groups, up to a tile a CU (256): 61 words on (8 / 4 waves, 64 to 256 tiles: 62
 //     words 0.96 to 0.97, 64 0.96, 66 0.97 to 1.01, 70 0.94, 74 0.97 to 1.02, 80 0.94 to 0.98; a whole layer of 256 tiles and 64
-//     words 7.25 / 7.57 us), four below (34 to 49 words 1.12 / 1.00 / 1.67): a wave's share is then less than the reduction of more
-//     costs.  More waves hide the latency of rows that pass through registers, and of the patches of a convolution: there eight
-//     from 50 words on (1.00 / 1.11 / 2.3), and always (1.03 / 1.08 / 1.9).  Bit planes from 50 words on (1.00 / 1.02 / 1.4; 34 to
-//     49 1.03 / 1.00 / 1.33).
-//   - up to three a CU four (257 to 512 tiles 1.25 / 1.00 / 1.44, 513 to 768 1.4 / 1.00 / 1.15), and with more than one, but few, for
-//     some SIMDs (1025 to 1280: 1.45 / 1.00 / 1.19).  Between them a SIMD has at most one undivided tile: one wave (1.5 / 1.03 / 1.00),
-//     but of 75 words on four (1.29 / 1.00 / 1.04).  Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09),
-//     and from 2049 to 2350 (- / 1.01 / 1.10; between, - / 1.09 / 1.04).
-//   - a K that divides into at least four shares of two groups: 20 words, bit planes 22, to 512 tiles (20 to 33 words: up to 128
-//     tiles 1.00 / 1.00 / 1.36, to 512 1.03 / 1.03 / 1.15); beyond, and with rows through registers always, 34 (513 to 640 1.22 /
-//     1.22 / 1.00).
+//     words 7.25 / 7.57 us; rows through registers 1.00 / 1.14).  Of fewer groups six or seven waves would be left of them, which four
+//     beat (rows through registers, 50 to 60 words 1.07 / 1.00, bit planes 1.03 / 1.00).  The patches of a convolution, whose latency
+//     more waves hide, always eight (1.03 / 1.08 for four, 1.9 for one).
+//   - four where each has two groups, 29 words on, up to three tiles a CU (257 to 512 tiles 1.25 / 1.00 / 1.44 for 8 / 4 / 1; 513 to
+//     768 1.4 / 1.00 / 1.15; of 29 to 33 words 1.00 / 1.20, 4 / 1), and with more than one, but few, for some SIMDs (1025 to 1280: 1.45 /
+//     1.00 / 1.19; rows through registers of less than 34 words 1.02 / 1.00, 4 / 1, beyond 768: one).  Between them a SIMD has at most one
+//     undivided tile: one wave (1.5 / 1.03 / 1.00), but of 75 words on four (1.29 / 1.00 / 1.04).  Four and eight keep the SIMDs of a CU level
+//     where it has several tiles (390 x 3329 x 5632, 371 tiles, takes 10.4 us over four waves, 15.1 over five, 12.2 over three).
+//     Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09), and from 2049 to 2350 (- / 1.01 / 1.10; between, - /
+//     1.09 / 1.04).
+//   - three of 21 to 28 words (six or seven groups), up to two tiles a CU (3 / 2 / 1 waves, to 256 tiles 1.00 / 1.14 / 1.17, to 512 rows
+//     through registers 1.00 / 1.16 / 1.15, bit planes 1.00 / 1.08 / 1.11, direct rows 1.03 / 1.20 / 1.01; beyond, all 1.2 / 1.2 / 1.00).  Five
+//     groups, 20 words, are not worth dividing (2 / 1 1.03 / 1.01 to 256 tiles, 1.24 / 1.00 to 512).
 enum class Rows { direct, registers, planes, patches };
 static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
-  if (kwords < (rows == Rows::patches ? 1 : rows == Rows::planes ? 22 : rows == Rows::registers ? 21 : 20)) return 1;
-  if (tiles <= 256) return kwords >= (rows == Rows::patches ? 0 : rows == Rows::direct ? 61 : 50) ? 8 : 4;
+  const bool patches = rows == Rows::patches;
+  if (kwords < 21 && !patches) return 1;
+  if (tiles <= 256 && (kwords >= 61 || patches)) return 8;
+  if (kwords < 29 && !patches) return tiles <= 512 ? 3 : 1;
   if (tiles <= 512) return 4;
-  if (kwords < 34) return 1;
-  if (rows == Rows::patches && kwords >= 75) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
+  if (kwords < 34 && (patches || (rows == Rows::registers && tiles > 768))) return 1;
+  if (kwords >= 75 && patches) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
   if (tiles <= 768 || (tiles > 1024 && tiles <= 1280)) return 4;
   return tiles <= 1024 && kwords >= 75 && rows == Rows::direct ? 4 : 1;
 }

@@ -1519,12 +1519,13 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
         np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(3))
 
 
-@pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 2), (16, 16, 60, 4), (16, 16, 61, 8), (16, 32, 32, 4),
-                                               (19, 27, 32, 1), (19, 27, 34, 4), (24, 32, 34, 4), (24, 33, 34, 1), (24, 33, 76, 4),
-                                               (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
+@pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 1), (16, 16, 21, 3), (16, 16, 28, 3), (16, 17, 20, 1), (16, 17, 23, 3),
+                                               (16, 32, 28, 3), (16, 32, 27, 3), (19, 27, 27, 1), (16, 16, 29, 4), (16, 16, 60, 4), (16, 16, 59, 4),
+                                               (16, 16, 61, 8), (16, 32, 32, 4), (19, 27, 28, 1), (19, 27, 30, 4), (24, 32, 33, 4), (32, 33, 33, 1), (24, 32, 34, 4), (24, 33, 34, 1),
+                                               (24, 33, 76, 4), (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
 def test_gemm_fp4_split_lines(tm, tn, words, split):
-    """Both sides of the lines between the waves that share a tile's K, by the tiles and words; a last tile of one row and one
-    column; the same results undivided."""
+    """Both sides of the lines between the waves that share a tile's K, by the tiles and words (an odd number of words: rows that pass
+    through registers); a last tile of one row and one column; the same results undivided."""
     g = torch.Generator(device="cuda")
     g.manual_seed(tm * tn + words)
     A, W = (torch.randint(-2 ** 62, 2 ** 62, (64 * n - 63, words), device="cuda", generator=g) for n in (tm, tn))
@@ -1535,6 +1536,20 @@ def test_gemm_fp4_split_lines(tm, tn, words, split):
         want = B.xnor_gemm(A, W, 64 * words)
         assert "K split %d" % split not in B.last_kernel(), B.last_kernel()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("words,split", [(20, 1), (22, 3), (28, 3), (29, 4), (60, 4), (61, 8)])
+@pytest.mark.parametrize("bits", [1, 2])
+def test_plane_gemm_split_lines(bits, words, split):
+    """The same lines for bit planes, 136 tiles."""
+    rng = np.random.default_rng(words + bits)
+    a, w = rng.uniform(0, 1, (1030, 64 * words - 3)).astype(np.float32), rng.standard_normal((500, 64 * words - 3)).astype(np.float32)
+    with tuned(k7=3):
+        S, f = B.quant_gemm(dev(a), dev(w), bits)
+        assert "planes,S" in B.last_kernel() and "K split %d" % split in B.last_kernel(), B.last_kernel()
+    rS, _, _ = oracle.quant_gemm(a, w, bits)
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(2 ** bits - 1))
 
 
 @pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, False), (1024, 4032, 2, True), (1024, 1024, 28, True),

@@ -183,17 +183,24 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const int64_t tiles_n = C_bits ? ceil_div(N, 64) * 2 : ceil_div(N, 32);  // (both halves of the last word)
   const int64_t tiles = ceil_div(M, 32) * tiles_n;
   const int steps = (dwords + 7) / 8;
-  // Against gemm_fp4_kernel, from 260 products of 2500 to 13000 tile steps (its time over this kernel's, in a graph): below 512 of
-  // its tiles up to 7500 tile steps (128 to 255 tiles 1.0 to 1.5, at 8100 to 11600 steps 0.72 to 0.85; 256 to 511 1.0 to 1.5, at 7900
-  // to 8700 0.86 to 0.95), below 128 up to 8192 (1.0 to 1.5); from 512 on only where K is a single step (two and more 0.85 to 1.0; 5760 x
-  // 339 x 72 5.4 / 5.0).  Rows that pass through registers there up to 8192
-  // steps (7344 1.06, 7696 1.11, 8190 1.09) and 800 tiles (0.94 to 0.98).  Half as many steps more where there are too few 64 x 64
-  // tiles for that kernel; of a K of more than four steps for each of sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and
-  // 4096 tiles, where the results outweigh the rest.
+  // Against the kernels of 64 x 64 tiles and more, from 2500 products of 64 to 1300 such tiles and 1500 to 16000 tile steps of 32 x 32 x 256
+  // (their time over this kernel's, in a graph).  Up to 28 words, where gemm_fp4_kernel does not divide K over four waves, up to 12288
+  // steps (8000 to 9000 1.10, 10000 to 13000 1.01 to 1.04, rows that pass through registers there 1.07 to 1.2).  Beyond, rows that travel to LDS
+  // there: below 128 of its tiles up to 8192 (7000 to 8000 1.09, then 0.92), to 255 up to 7000 (5000 to 7000 1.0 to 1.05, then 0.95 to
+  // 0.8), to 511 up to 8192 (0.99, then 0.88).  Rows that pass through registers: to 191 up to 9500 (9000 1.04; beyond 1.01), to 255 up
+  // to 8192 (7000 to 8000 1.0 to 1.1; beyond 0.98), to 511 up to 12288 (1.0 to 1.08).  From 512 tiles on 8192, where gemm_block.hip
+  // takes over rows that start on any dword (9000 to 12000 1.0 to 1.1); rows to LDS only where K is a single step (1.0; two and more
+  // 0.99 to 0.83), others, from 800 on, of one or two (1.02 to 1.2; three 0.97 to 1.03, more 0.92).
+  // 12288 too where there are too few 64 x 64 tiles for that kernel; of a K of more than four steps for each of
+  // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool direct = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15) && !(dwords & 1);
-  if (work > (steps > 64 ? 2048 : !gemm_fp4_pays(M, N) ? 12288 : direct && tiles64 >= 128 ? 7500 : 8192) || tiles > 4096) return false;
-  if (!C_bits && steps > 1 && tiles64 >= (direct ? 512 : 800)) return false;
+  const int64_t most = steps > 64                                                 ? 2048
+                       : !gemm_fp4_pays(M, N) || (dwords <= 56 && tiles64 < 512) ? 12288
+                       : direct || tiles64 >= 512                                 ? (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192)
+                                                                                  : (tiles64 < 192 ? 9500 : tiles64 < 256 ? 8192 : 12288);
+  if (work > most || tiles > 4096) return false;
+  if (!C_bits && (direct ? tiles64 >= 512 && steps > 1 : tiles64 >= 800 && steps > 2)) return false;
   int S = 1;
   while (S < 16 && 2 * S <= steps && 2 * S * tiles <= (work > 8192 ? 8192 : 4096)) S *= 2;
   SmallGemmParams p;

@@ -1553,9 +1553,13 @@ def test_plane_gemm_split_lines(bits, words, split):
 
 
 @pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, False), (1024, 4032, 2, True), (1024, 1024, 28, True),
-                                             (1024, 1024, 30, False), (512, 512, 126, True), (512, 512, 130, False)])
+                                             (1024, 960, 30, False), (1024, 1024, 32, True), (1024, 1024, 34, False), (512, 512, 126, True),
+                                             (512, 512, 130, False), (1024, 960, 32, False), (1024, 960, 31, True), (1024, 768, 46, False), (1024, 704, 47, True), (1024, 704, 53, False), (1024, 960, 39, False), (1024, 1024, 43, True),
+                                             (1024, 1024, 51, False), (1024, 1920, 24, True), (1024, 1920, 28, False),
+                                             (3200, 1024, 7, True), (3200, 1024, 9, False), (2560, 1024, 9, True)])
 def test_gemm_small_lines(M, N, words, small):
-    """Both sides of the lines between the kernel of 32 x 32 and that of 64 x 64 tiles; the same results from the popcount kernel."""
+    """Both sides of the lines between the kernel of 32 x 32 and those of larger tiles, for rows that these fetch 16 bytes at a time
+    (an even number of words) and for others; the same results from the popcount kernel."""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + words)
     A, W = (torch.randint(-2 ** 62, 2 ** 62, (n, words), device="cuda", generator=g) for n in (M, N))

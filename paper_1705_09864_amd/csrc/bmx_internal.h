@@ -169,7 +169,8 @@ extern int gemm_small;
 // gemm_mfma.hip: an xnor product of rows that may start on any dword, where a kernel reads them as they are.
 bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int M, int N, int K,
                              int32_t* C, int64_t ldc, hipStream_t s, hipError_t* err);
-bool gemm_fp4_pays(int M, int N);  // whether an xnor product has tiles (of 64 x 64) enough for launch_gemm_fp4
+// whether launch_gemm_fp4 takes an xnor product, as it does with tiles (of 64 x 64) enough and offsets that fit it
+bool gemm_fp4_pays(int M, int N, int64_t lda_bytes, int64_t ldb_bytes, int64_t ldc, bool bits);
 bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t* rowsum, const void* B,
                      int64_t ldb_bytes, int M, int N, int K, int dwords, const float* alpha_n, int32_t* C_i32, float* C_f32,
                      uint64_t* C_bits, const float* thr_n, int64_t ldc, bool as_count, hipStream_t s,

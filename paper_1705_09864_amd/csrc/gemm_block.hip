@@ -524,7 +524,8 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).  Int32 results of
   // up to 1280 tiles of 64 x 64 and more than 33 words are that kernel's, which divides K over four waves there or has a wave for
   // every SIMD (55 products of 769 to 1280, there / here: 0.96 to 0.75; 6719 x 704 x 4096, 1155, 11.9 / 15.7; 2176 x 1988 x 7808,
-  // 1088, 21.9 / 25.7).
+  // 1088, 21.9 / 25.7), where it takes them: not with rows of C so far apart that its indices do not reach (2048 x 2560 x 4096, rows 1048576
+  // apart, 15.1 here, 28.5 in gemm_mfma.hip, which would get them).
   // The larger of the two shapes (us as 128 x 128 / as 256 x 128, each held for 50 ms): its waves read LDS and expand less for a
   // product, which shows once the chip's power has settled, where the results leave in whole lines and fill many rounds:
   // 8192 x 8192 x 8192 186 / 177, x 4096 106 / 102; 8192 x 12288 x 8192 277 / 263, 16384 x 8192 x 8192 370 / 352, 10240 x 10240 x
@@ -536,7 +537,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
     if (any_dword) {
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
     } else if (tiles < 256 || K < 700 || (C_f32 && tiles <= 512 && K < 3500) ||
-               (C_i32 && ceil_div(M, 64) * ceil_div(N, 64) <= 1280 && K > 64 * 33) ||
+               (C_i32 && ceil_div(M, 64) * ceil_div(N, 64) <= 1280 && K > 64 * 33 && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) ||
                (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {
       return false;
     }

@@ -952,7 +952,14 @@ static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
 }
 
 // Below 64 tiles kernels of 32 x 32 tiles: four times the waves, and there is not enough K to give these tiles to that many waves.
-bool gemm_fp4_pays(int M, int N) { return ceil_div(M, 64) * ceil_div(N, 64) >= 64; }
+// (And only problems whose operands it addresses with 32-bit byte offsets, results with 32-bit element indices, rows rounded up to whole
+// tiles: the kernels that leave it a problem ask for the same.)
+static bool fp4_addresses(int64_t M, int64_t N, int planes, int64_t lda_bytes, int64_t ldb_bytes, int64_t ldc, bool bits) {
+  return M * planes * lda_bytes < ((int64_t)1 << 32) && N * ldb_bytes < ((int64_t)1 << 32) && (M + 64) * ldc * (bits ? 2 : 1) < ((int64_t)1 << 31);
+}
+bool gemm_fp4_pays(int M, int N, int64_t lda_bytes, int64_t ldb_bytes, int64_t ldc, bool bits) {
+  return ceil_div(M, 64) * ceil_div(N, 64) >= 64 && fp4_addresses(M, N, 1, lda_bytes, ldb_bytes, ldc, bits);
+}
 
 // Takes the problem (rows of `dwords` data dwords) when sums stay exact in fp32, the
 // operands can be addressed with 32-bit byte offsets, and there are enough 64 x 64 tiles for
@@ -970,14 +977,11 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   const bool odd_dwords = (lda_bytes & 7) || (ldb_bytes & 7) || ((uintptr_t)A & 7) || ((uintptr_t)B & 7) || (dwords & 1);
   if (reg && (rowsum || (odd_dwords && (!C_i32 || planes != 1)))) return false;
   if ((int64_t)K * ((1 << planes) - 1) >= ((int64_t)1 << 24)) return false;
-  if ((int64_t)M * planes * lda_bytes >= ((int64_t)1 << 32) || (int64_t)N * ldb_bytes >= ((int64_t)1 << 32))
-    return false;
-  // (outputs are addressed with 32-bit element indices, rows rounded up to whole tiles)
-  if (((int64_t)M + 64) * ldc * (C_bits ? 2 : 1) >= ((int64_t)1 << 31)) return false;
+  if (!fp4_addresses(M, N, planes, lda_bytes, ldb_bytes, ldc, C_bits != nullptr)) return false;
   const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   const int Kwords = (int)words_for(K);
-  if (gemm_engine != 5 && !gemm_fp4_pays(M, N)) return false;
+  if (gemm_engine != 5 && tiles < 64) return false;
   if (tiles >= ((int64_t)1 << 28)) return false;
   Fp4Params p;
   p.A = A;

@@ -191,16 +191,17 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // to 8192 (7000 to 8000 1.0 to 1.1; beyond 0.98), to 511 up to 12288 (1.0 to 1.08).  From 512 tiles on 8192, where gemm_block.hip
   // takes over rows that start on any dword (9000 to 12000 1.0 to 1.1); rows to LDS only where K is a single step (1.0; two and more
   // 0.99 to 0.83), others, from 800 on, of one or two (1.02 to 1.2; three 0.97 to 1.03, more 0.92).
-  // 12288 too where there are too few 64 x 64 tiles for that kernel; of a K of more than four steps for each of
+  // 12288 too where that kernel does not take the product; of a K of more than four steps for each of
   // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool direct = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15) && !(dwords & 1);
-  const int64_t most = steps > 64                                                 ? 2048
-                       : !gemm_fp4_pays(M, N) || (dwords <= 56 && tiles64 < 512) ? 12288
-                       : direct || tiles64 >= 512                                 ? (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192)
-                                                                                  : (tiles64 < 192 ? 9500 : tiles64 < 256 ? 8192 : 12288);
+  const bool pays = gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, C_bits != nullptr);
+  const int64_t most = steps > 64                                ? 2048
+                       : !pays || (dwords <= 56 && tiles64 < 512) ? 12288
+                       : direct || tiles64 >= 512                 ? (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192)
+                                                                  : (tiles64 < 192 ? 9500 : tiles64 < 256 ? 8192 : 12288);
   if (work > most || tiles > 4096) return false;
-  if (!C_bits && (direct ? tiles64 >= 512 && steps > 1 : tiles64 >= 800 && steps > 2)) return false;
+  if (!C_bits && pays && (direct ? tiles64 >= 512 && steps > 1 : tiles64 >= 800 && steps > 2)) return false;
   int S = 1;
   while (S < 16 && 2 * S <= steps && 2 * S * tiles <= (work > 8192 ? 8192 : 4096)) S *= 2;
   SmallGemmParams p;

@@ -1538,6 +1538,21 @@ def test_gemm_fp4_split_lines(tm, tn, words, split):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("M,N,words,ldc,kernel", [(2048, 2560, 64, 1 << 20, "block"), (2048, 2560, 64, 1 << 19, "gemm_fp4_kernel<2,2,1,xnor,i32> "),
+                                                  (32, 32768, 6, 3 << 23, "gemm_small")])
+def test_rows_of_c_far_apart(M, N, words, ldc, kernel):
+    """Results in a matrix whose rows are further apart than gemm_fp4.hip's 32-bit indices reach: the kernels that would leave it
+    such a product take it themselves, as they did."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    A, W = (torch.randint(-2 ** 62, 2 ** 62, (n, words), device="cuda", generator=g) for n in (M, N))
+    room = torch.empty((M, ldc), dtype=torch.int32, device="cuda")
+    B.xnor_gemm(A, W, 64 * words, out=room[:, :N])
+    assert kernel in B.last_kernel(), B.last_kernel()
+    with tuned(k7=1):
+        assert torch.equal(room[:, :N], B.xnor_gemm(A, W, 64 * words))
+
+
 @pytest.mark.parametrize("words,split", [(20, 1), (22, 3), (28, 3), (29, 4), (60, 4), (61, 8)])
 @pytest.mark.parametrize("bits", [1, 2])
 def test_plane_gemm_split_lines(bits, words, split):

@@ -213,13 +213,15 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   if ((int64_t)C * KH * KW >= (1 << 24) || O > 65535 * 32) return false;
   const int64_t tiles_p = ceil_div(P, 32), tiles_o = ceil_div(O, 32), tiles = tiles_p * tiles_o;
   const int steps = (K + 3) / 4;
-  const int64_t work = tiles * steps;
+  const int64_t work = tiles * steps, tiles64 = ceil_div(P, 64) * ceil_div(O, 64);
   // Against the kernels with an eye to K (us in a graph): the short-K kernel shares its filters, which pays
   // from a few hundred tiles on, and at 9 words from the first (18 words: 400 tiles 3.9 against 4.3, 700
   // tiles 4.3 / 4.0; 27 words: 95 tiles 3.3 / 4.8; 49 words: 530 tiles 5.3 / 6.0, 1170 tiles 8.4 / 8.0); the
   // stationary kernel has nothing to share at 1 to 4 words.  A long K is gemm_fp4_kernel's from
   // 12288 tile steps on (its time over this kernel's: at 8000 to 12000 steps 1.0 to 1.2, at 12540 to 16000 0.81 to 1.07, mean 0.93),
-  // where it has 64 tiles of its own; from 16384 on in any case.  As packed bits the line is where 3.4 us and 0.25 ns a tile
+  // where it has 64 tiles of its own that are not half empty (at most three of these in one of those: at 12288 to 16384 steps 0.9 to
+  // 1.7, mean 1.15; 9 x 545 x 48 x 48 -> 30, 3 x 3, 8.7 / 6.9) and it takes the filters, 16-byte aligned; from 16384 on in any case.
+  // As packed bits the line is where 3.4 us and 0.25 ns a tile
   // step, this kernel's time, meet the estimate of the kernels for long K (211 filters, 3780 pixels, 196 words: 13.4 / 9.5; 32, 22707, 100,
   // half of their tiles empty: 7.5 / 10.9; 64, 20064, 63: 7.8 / 9.7), 12000 steps at least; and gemm_block.hip's for few words.
   if (conv_weight_short_k(K)) {
@@ -230,7 +232,7 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
     if (((uintptr_t)Wp & 15) == 0 && !conv_block && !gemm_fp4_split && !gemm_fp4_half && !gemm_fp4_band) {
       if (K < 8 ? tiles >= 7000 : work > 12000 && 3.4 + 2.5e-4 * work > conv_long_us(P, O, K, (Cw & 1) || ((uintptr_t)Xp & 15), &form)) return false;
     }
-  } else if (K == 1 || K == 2 || K == 4 || work > (ceil_div(P, 64) * ceil_div(O, 64) >= 64 ? 12288 : 16384) || tiles > 4096) {
+  } else if (K == 1 || K == 2 || K == 4 || work > (tiles64 >= 64 && tiles > 3 * tiles64 && ((uintptr_t)Wp & 15) == 0 ? 12288 : 16384) || tiles > 4096) {
     return false;
   }
   int S = 1;

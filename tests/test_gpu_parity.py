@@ -1799,6 +1799,21 @@ def test_conv_small(N, C, H, W, O, k, s, p, opad):
     np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("N,O,off,small", [(12, 64, 0, False), (10, 64, 0, True), (24, 30, 0, True), (28, 30, 0, False), (12, 64, 1, True)])
+def test_conv_small_lines(N, O, off, small):
+    """Both sides of the line to the 64 x 64 kernel at 45 words and 12 steps a tile, for filters that fill its tiles and for such as
+    leave them half empty, and filters that are 8-byte aligned, which it does not take; the same results from the popcount kernel."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + O)
+    x, w = torch.randn((N, 320, 40, 40), device="cuda", generator=g), torch.randn((O, 320, 3, 3), device="cuda", generator=g)
+    xp, Wp = B.pack_nchw(x, 1), B.pack_conv_weights(w)
+    room = torch.empty(Wp.numel() + off, dtype=Wp.dtype, device="cuda")[off:].view(Wp.shape)
+    got = B.binary_conv2d_packed(xp, 320, room.copy_(Wp), O, 3, 3, 1, 1, integer_out=True)
+    assert ("conv_small_kernel" in B.last_kernel()) == small, B.last_kernel()
+    with tuned(k7=1):
+        assert torch.equal(got, B.binary_conv2d_packed(xp, 320, Wp, O, 3, 3, 1, 1, integer_out=True))
+
+
 @pytest.mark.parametrize("parts,N,C,H,W,O,k,s,p", [
     (1, 1, 1, 1, 1, 1, 1, 1, 0), (1, 3, 17, 9, 11, 33, 1, 2, 0), (1, 12, 390, 24, 26, 83, 1, 1, 0), (2, 2, 64, 10, 9, 32, 3, 1, 1),
     (2, 5, 42, 29, 28, 31, 3, 2, 2), (4, 7, 130, 29, 27, 70, 3, 2, 1), (4, 1, 33, 7, 6, 65, 5, 1, 4), (8, 2, 211, 8, 20, 19, 3, 1, 0),

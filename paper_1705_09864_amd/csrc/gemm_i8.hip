@@ -622,19 +622,21 @@ static void set_split(I8Params& p) {
 bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
                         int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
   if (gemm_engine != 0) return false;
+  const bool sums = bits_a == 8 || bits_w == 8;
   const int64_t t32 = ceil_div(M, 32) * ceil_div(N, 32), t16 = ceil_div(M, 16) * ceil_div(N, 16);
   // 16 x 16 of the result per workgroup while a CU has one of them, or two or more of few steps (3600 products of both: time as
   // 32 x 32 over that as 16 x 16, up to 256 tiles of 16 x 16 1.24 to 1.37; 257 to 512 1.08 to 1.26 up to a K of 512, 0.90 beyond; 513
   // to 2048 1.08 to 1.17 up to 128, 0.8 beyond).
   const bool small = t16 <= 256 || (t16 <= 512 && K <= 512) || (t16 <= 2048 && K <= 128);
   // Steps of K per CU up to which one launch is ahead of the better pair of launches (which the host makes in 7.8 us at the
-  // least): 16 x 16, 24 to 32 of them 1.42 times, 32 to 40 1.22, 40 to 48 1.06, 48 to 64 0.98; 32 x 32, 16 to 24 1.18, 24 to 32 0.99.
+  // least): 16 x 16, 24 to 32 of them 1.42 times, 32 to 40 1.22, 40 to 48 1.06, 48 to 64 0.98; 32 x 32, a tile a CU or less, 20 to 28
+  // 1.11 in a graph and 1.36 as calls, 28 to 36 1.00 and 1.15 (8 bits
+  // at 256 tiles 0.9: 486 x 512 x 990 of 3 x 8 8.8 / 7.1), 36 to 40 0.91 and 1.02; more tiles, 16 to 24 1.02 and 1.12, 24 to 32 0.87 and 0.98.
   // Over the same products the choice is 0.8 % behind the better.  us a call, before two values shared a byte and tiles were
   // of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2 x 4 5.8 / 3.6,
   // 202 x 192 x 437 5.0 / 3.4.
-  if (small ? K > 44 * 64 : ceil_div(K, 32) * ceil_div(t32, 256) > 24) return false;
+  if (small ? K > 44 * 64 : ceil_div(K, 32) * ceil_div(t32, 256) > (t32 > 256 ? 24 : sums ? 28 : 32)) return false;
   if (K < 4 || (int64_t)M * lda * 4 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 4 >= ((int64_t)1 << 32)) return false;
-  const bool sums = bits_a == 8 || bits_w == 8;
   const int T = small ? 16 : 32, nk = (int)ceil_div(K, 1024 / T);
   QuantSmallParams p;
   p.a = a;

@@ -648,7 +648,7 @@ def test_quant_gemm_one_launch(M, N, K, ba, bw):
     assert_f32_close(of.cpu().numpy(), r32)
 
 
-@pytest.mark.parametrize("M,N,K", [(513, 290, 769), (545, 257, 1023), (33, 1100, 2817), (520, 300, 1025), (40, 3000, 1300), (70, 36, 4200), (16, 33, 3071), (200, 2100, 897)])
+@pytest.mark.parametrize("M,N,K", [(513, 580, 769), (545, 513, 1023), (33, 1100, 2817), (520, 300, 1025), (40, 3000, 1300), (70, 36, 4200), (16, 33, 3071), (200, 2100, 897)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (2, 1), (4, 1), (3, 2), (1, 3), (4, 4)])
 def test_quant_halves(M, N, K, ba, bw):
     """Two values a byte: K that ends in either half of a block of 256 and on its edge, rows that do not fill a block of 32, one
@@ -670,7 +670,7 @@ def test_quant_halves(M, N, K, ba, bw):
 
 
 @pytest.mark.parametrize("M,N,K,T", [(16, 16, 4, 16), (1, 1, 63, 16), (17, 31, 64, 16), (15, 33, 65, 16), (256, 256, 129, 16), (256, 257, 512, 16),
-                                     (256, 257, 513, 32), (512, 1024, 128, 16), (512, 1025, 128, 32), (30, 50, 2816, 16), (300, 240, 700, 32), (730, 1439, 31, 32)])
+                                     (256, 257, 513, 32), (512, 1024, 128, 16), (512, 1025, 128, 32), (30, 50, 2816, 16), (300, 240, 700, 32), (300, 240, 896, 32), (730, 1439, 31, 32)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (8, 1), (2, 2), (4, 7), (8, 3), (1, 8), (8, 8)])
 def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
     """The one-launch form in tiles of 16 x 16 and 32 x 32, both sides of the lines between them, K around a step."""

@@ -292,7 +292,7 @@ size_t bmx_workspace_bytes(int op, const int64_t* dims, int ndims);
  *          even where 16 would do; 2: 16 at a time, but never in the form for channel-word
  *          counts that are multiples of four; 3: never in the form that holds one block per wave
  *   key 15 = 1: bmx_binary_fc never takes its one-launch form
- *   key 16 = 1: bmx_binary_conv2d never takes its one-launch form
+ *   key 16 = 1: bmx_binary_conv2d never takes its one-launch form, 2: wherever that can be, whichever is faster
  *   key 18 = 1: convolutions of packed images never take the kernel for small problems (nor while
  *          one of keys 1, 5, 7 and 14 pins another)
  *   key 17 = 1: xnor products never take the kernel for small problems (nor while any of keys 7 to

@@ -325,7 +325,7 @@ conv_one_kernel(const ConvOneParams p) {
 
 }  // namespace
 
-int conv_one = 0;  // 1 = never (measurements and tests of the two-launch path)
+int conv_one = 0;  // 1 = never, 2 = wherever a workgroup holds a band (measurements and tests of either path)
 
 bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
                      int pad, const float* alpha, int32_t* out_i32, float* out_f32, hipStream_t s, hipError_t* err) {
@@ -338,30 +338,34 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
       O * conv_weight_row_words(K) * 8 >= ((int64_t)1 << 32))
     return false;
   const int tiles = (int)ceil_div(O, 32);
-  // The two launches' time in us, fitted to 900 shapes (7 % rms): KB of input and of results, words of 32 x 32 results, the chain
-  // of a patch's words, and never less than the host takes to make two launches and a workspace (8.2 on the machines
-  // measured; 8 here, for callers that replay a graph: there the GPU's part alone is 5 to 8).
+  // The two launches' time on the GPU in us, fitted to 5225 shapes (6 % rms): KB of input and of results, words of 32 x 32 results,
+  // the chain of a patch's words.  As calls they take never less than the host does for two launches and a workspace, 6.9 to 8.2 us by
+  // the process.
   const double in_kb_all = (double)N * C * H * W / 256, out_kb_all = (double)N * O * Ho * Wo / 256;
   const double unit_words = (double)N * Ho * Wo * tiles * K;
-  const double limit = std::max(8.0, 4.7 + in_kb_all * 1.59e-4 + out_kb_all * 1.57e-4 + unit_words * 1.1e-6 + K * 0.0113);
+  const double two = 5.03 + in_kb_all * 1.11e-4 + out_kb_all * 1.81e-4 + unit_words * 9.27e-7 + K * 0.0114;
+  const double limit = conv_one == 2 ? 1e30 : 0.98 * std::max(7.6, two);
   // Output rows per band, filter tiles per workgroup and waves per unit: those of the shortest modelled
-  // time, fitted to the same shapes and five of their other plans each (11 % rms; the plan chosen by it is 1 % behind the best
-  // of them, and one launch or two by it 0.2 % behind the better).  Beside what all launches pay, a round of workgroups
-  // costs its fp32 rows (KB), its words per SIMD (one unit in four waves: 1) and its results (KB).
-  auto cost_of = [](double rounds, double in_kb, double words, double out_kb) {
-    return 3.0 + rounds * 0.4 + in_kb * (1 / 37.0) + words * (1 / 16.5) + out_kb * (1 / 28.5);
+  // time, fitted to the same shapes (5 % rms).  Beside what all launches pay, a round of workgroups
+  // costs its fp32 rows (KB), the loads of them (64 pixels x 16 channels each, whole or not), its words per SIMD (one unit in four
+  // waves: 1) and its results (KB).  One launch or two by it, over these shapes: 0.33 % behind the better as calls, 0.32 % in a graph (0.5
+  // and 1.35 % while rounds were counted by the chip and rows in KB alone).
+  auto cost_of = [](double rounds, double in_kb, double loads, double words, double out_kb) {
+    return 3.375 + rounds * 0.05 + in_kb * 0.0051 + loads * 0.067 + words * 0.0565 + out_kb * 0.0373;
   };
   // (no plan is below an even share of everything: most layers that stay with two launches end here)
-  if (cost_of(1, in_kb_all * std::min(1.0, (double)KH / stride) / 256, unit_words / (32 * 4 * 256), out_kb_all / 256) > limit) return false;
+  const double in_share = in_kb_all * std::min(1.0, (double)KH / stride) / 256;
+  if (cost_of(1, in_share, in_share / 4, unit_words / (32 * 4 * 256), out_kb_all / 256) > limit) return false;
   double best = 1e30;
   int rows = 0, share = 0, parts = 1, units_max = 0;
-  const int steps = (K + 3) / 4;
+  const int steps = (K + 3) / 4, quarters = (C + 15) / 16;
   for (int rr = 1; rr <= Ho; rr = rr < 4 ? rr + 1 : rr + (rr + 1) / 2) {
     const int rin = (rr - 1) * stride + KH;
     if ((int64_t)rin * Wpp * Cw * 8 > kLds - kRowBytes) break;
     const int image = (rin * Wpp * Cw * 8 + 15) & ~15;
     const int bands = (Ho + rr - 1) / rr, px_blocks = (rr * Wo + 31) / 32;  // (32-bit: this runs on every call)
-    const double in_kb = (double)std::min(rin, H) * W * C / 256;
+    const int px = std::min(rin, H) * W;
+    const double in_kb = (double)px * C / 256, loads = (double)((px + 63) / 64) * quarters;
     double rounds = 0;
     for (int g = 1; g <= tiles; g *= 2) {
       const int per = (tiles + g - 1) / g, units = px_blocks * per;
@@ -372,13 +376,15 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
              image + ks * 2 * units * kPartBytes <= kLds) ks *= 2;
       if ((steps + ks - 1) / ks > 16) continue;  // (a lane of the wave holds the place of each of its words)
       const double words = ks > 1 ? std::max(1.0, units * ks / 4.0) * ((K + ks - 1) / ks) : (double)((units + 3) / 4) * K;
-      rounds = (double)(((int64_t)bands * ((tiles + per - 1) / per) * N + 255) >> 8);
-      const double cost = cost_of(rounds, rounds * in_kb, rounds * words, rounds * rr * Wo * std::min(O, 32 * per) / 256);
+      // (An XCD has 32 CUs, and the first of them a whole eighth of the bands, rounded up: 25 x 40 x 21 x 21 -> 320 5x5/2 in 50 bands of 5
+      // workgroups is 35 of them on one, two rounds: 11.7 us where two launches take 7.1)
+      rounds = (double)(((((int64_t)bands * N + 7) >> 3) * ((tiles + per - 1) / per) + 31) >> 5);
+      const double cost = cost_of(rounds, rounds * in_kb, rounds * loads, rounds * words, rounds * rr * Wo * std::min(O, 32 * per) / 256);
       if (cost < best) best = cost, rows = rr, share = per, parts = ks, units_max = units;
     }
     if (rounds == 1) break;  // one round however the filters are shared: longer bands cost more
   }
-  if (rows == 0 || best > 0.96 * limit) return false;
+  if (rows == 0 || best > limit) return false;
   ConvOneParams p;
   p.x = x;
   p.Wp = Wp;
@@ -404,7 +410,7 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
   p.div_w = make_fast_div((uint32_t)W);
   p.div_wp = make_fast_div((uint32_t)Wpp);
   p.div_wo = make_fast_div((uint32_t)Wo);
-  p.quarters = (C + 15) / 16;
+  p.quarters = quarters;
   p.div_quarters = make_fast_div((uint32_t)p.quarters);
   p.div_bands = make_fast_div((uint32_t)p.bands);
   p.div_run = make_fast_div((uint32_t)p.run);

@@ -189,7 +189,9 @@ int bmx_pack_conv_weights(const float* w_oihw, int O, int C, int KH, int KW, uin
  *   x      fp32 [N, C, H, W];   Wp from bmx_pack_conv_weights;   alpha fp32 [O] or NULL.
  *   out_i32 / out_f32   exactly one non-NULL, [N, O, Ho, Wo]; out_f32 = alpha[o]*(float)dot.
  *   Supported: KH == KW in {1, 3, 5, 7}, stride in {1, 2}, 0 <= pad < KH, any C >= 1.
- *   workspace >= bmx_workspace_bytes(BMX_OP_BINARY_CONV2D, {N,C,H,W,O,KH,KW,stride,pad}, 9). */
+ *   workspace >= bmx_workspace_bytes(BMX_OP_BINARY_CONV2D, {N,C,H,W,O,KH,KW,stride,pad}, 9).
+ *   Small layers run in one launch, others in two.  The choice weighs the host's time for a launch; on a stream that is being
+ *   captured into a graph it weighs the GPU's time alone.  Results are the same. */
 int bmx_binary_conv2d(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O,
                       int KH, int KW, int stride, int pad, const float* alpha, int32_t* out_i32,
                       float* out_f32, void* workspace, size_t workspace_bytes, void* stream);

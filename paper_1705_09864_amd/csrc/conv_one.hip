@@ -325,6 +325,16 @@ conv_one_kernel(const ConvOneParams p) {
 
 }  // namespace
 
+// Whether the launches of `s` go into a graph.  (Not asked of the default stream, which cannot: the question would be an error while
+// another stream's are.)
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (!s) return false;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 int conv_one = 0;  // 1 = never, 2 = wherever a workgroup holds a band (measurements and tests of either path)
 
 bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW, int stride,
@@ -385,6 +395,9 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
     if (rounds == 1) break;  // one round however the filters are shared: longer bands cost more
   }
   if (rows == 0 || best > limit) return false;
+  // A replayed graph pays the GPU's part of two launches alone: 3 x 256 x 25 x 25 -> 128 3x3 takes 7.6 us in one launch; two are 8.5 in a
+  // call, 5.7 in a graph.
+  if (conv_one != 2 && best > 0.98 * two && capturing(s)) return false;
   ConvOneParams p;
   p.x = x;
   p.Wp = Wp;

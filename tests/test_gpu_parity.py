@@ -1856,24 +1856,35 @@ def test_conv_one_launch_waves(waves, parts, N, C, H, W, O, k, s, p):
         np.testing.assert_array_equal(run_conv(x, w, s, p, alpha=alpha), rf)
 
 
-@pytest.mark.parametrize("N,C,H,W,O,k,s,p,one", [
-    (25, 40, 21, 21, 320, 5, 2, 2, False), (126, 107, 42, 44, 18, 3, 1, 1, False), (136, 128, 16, 16, 458, 1, 1, 0, False),
-    (2, 142, 50, 50, 64, 3, 2, 1, True), (6, 90, 40, 40, 128, 3, 1, 1, True), (1, 64, 8, 8, 64, 1, 1, 0, True),
-    (123, 445, 11, 10, 18, 1, 2, 0, True)])
-def test_conv_one_launch_or_two(N, C, H, W, O, k, s, p, one):
+@pytest.mark.parametrize("N,C,H,W,O,k,s,p,call,graph", [
+    (25, 40, 21, 21, 320, 5, 2, 2, False, False), (126, 107, 42, 44, 18, 3, 1, 1, False, False), (136, 128, 16, 16, 458, 1, 1, 0, False, False),
+    (2, 142, 50, 50, 64, 3, 2, 1, True, False), (6, 90, 40, 40, 128, 3, 1, 1, True, False), (1, 64, 8, 8, 64, 1, 1, 0, True, True),
+    (123, 445, 11, 10, 18, 1, 2, 0, True, True)])
+def test_conv_one_launch_or_two(N, C, H, W, O, k, s, p, call, graph):
     """Layers that look short to a model that counts workgroups by the chip and not by its XCDs, or bytes and not loads, take two
-    launches, or one in another plan."""
+    launches; layers whose two launches are held up by the host alone take one as a call and two in a graph; replays between
+    calls give what the calls give."""
     g = torch.Generator(device="cuda")
     g.manual_seed(N + C)
     x = torch.randn((N, C, H, W), device="cuda", generator=g)
     w = torch.randn((O, C, k, k), device="cuda", generator=g)
     Wp, alpha = B.pack_conv_weights(w), B.alpha_mean_abs(w)
-    got = B.binary_conv2d(x, Wp, O, k, k, s, p, alpha=alpha)
-    assert ("conv_one" in B.last_kernel()) == one, B.last_kernel()
-    with tuned(k16=1 if one else 2):
-        want = B.binary_conv2d(x, Wp, O, k, k, s, p, alpha=alpha)
-        assert ("conv_one" in B.last_kernel()) != one, B.last_kernel()
-    assert torch.equal(got, want)
+    run = lambda: B.binary_conv2d(x, Wp, O, k, k, s, p, alpha=alpha)  # noqa: E731
+    run()
+    assert ("conv_one" in B.last_kernel()) == call, B.last_kernel()
+    torch.cuda.synchronize()
+    captured = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(captured):
+        out = run()
+        assert ("conv_one" in B.last_kernel()) == graph, B.last_kernel()
+    for _ in range(3):
+        x.normal_(generator=g)
+        captured.replay()
+        want = run()
+        assert ("conv_one" in B.last_kernel()) == call, B.last_kernel()
+        assert torch.equal(out, want)
+        with tuned(k16=1):
+            assert torch.equal(run(), want)
 
 
 # ------------------------------------------------------------------ ties of the quantiser

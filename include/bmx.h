@@ -56,7 +56,7 @@ extern "C" {
 #define BMX_ERR_LD (-3)          /* a leading dimension is smaller than the row it must hold */
 #define BMX_ERR_ALIGN (-4)       /* pointer not aligned (packed: 8 bytes, fp32/int32: 4 bytes) */
 #define BMX_ERR_UNSUPPORTED (-5) /* pack_dim, kernel size, stride, bit width outside the contract */
-#define BMX_ERR_WORKSPACE (-6)   /* workspace NULL or smaller than bmx_workspace_bytes says */
+#define BMX_ERR_WORKSPACE (-6)   /* workspace NULL or smaller than bmx_workspace_bytes says (bmx_quant_gemm: see there) */
 #define BMX_ERR_HIP (-7)         /* the HIP runtime reported an error at launch */
 
 /* Operation selectors for bmx_workspace_bytes. */
@@ -253,7 +253,8 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
  * every weight plane, the planes added up by powers of two).  K * (2^bits_a - 1) * (2^bits_w - 1) must stay below 2^31.
  *   a fp32 [M, lda], w fp32 [N, ldw]; out_i32_scaled (S) and out_f32 are [M, ldo]; either
  *   may be NULL, not both.  bits_a, bits_w in 1..8.
- *   workspace >= bmx_workspace_bytes(BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, 5). */
+ *   workspace >= bmx_workspace_bytes(BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, 5).  (With bits_a <= 2 and bits_w = 1 a call also
+ *   takes less, down to what the packed planes need, and then runs on the plane kernels, with the same results.) */
 int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,
                    int bits_w, int M, int N, int K, int32_t* out_i32_scaled, float* out_f32,
                    int64_t ldo, void* workspace, size_t workspace_bytes, void* stream);

@@ -67,13 +67,9 @@ QuantWs quant_ws(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
   q.wrowsum_off = q.rowsum_off + round256((size_t)M * 4);
   q.tmp_off = q.wrowsum_off + (bits_w == 1 ? 0 : round256((size_t)N * 4));
   q.total = q.least = q.planes_total = q.tmp_off + (bits_w == 1 ? 0 : round256((size_t)M * N * bits_w * 4));
-  size_t tiles = 0, least = 0;
-  bmx::quant_i8_workspace(M, N, K, bits_a, bits_w, &tiles, &least);
-  auto at_least = [&](size_t& size, size_t bytes) {
-    if (bytes && (bytes > size || (bits_w > 1 && bmx::gemm_engine != 1))) size = round256(bytes);
-  };
-  at_least(q.total, tiles);
-  at_least(q.least, least);
+  const size_t tiles = round256(bmx::quant_i8_workspace(M, N, K, bits_a, bits_w));
+  if (tiles && (tiles > q.total || (bits_w > 1 && bmx::gemm_engine != 1))) q.total = tiles;
+  if (!bmx::quant_few_bits(bits_a, bits_w)) q.least = q.total;
   return q;
 }
 

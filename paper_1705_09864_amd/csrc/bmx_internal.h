@@ -233,8 +233,9 @@ hipError_t launch_plane_gemm(const uint32_t* planes_rows, int64_t lda_dw, int bi
 
 // gemm_i8.hip: the whole k-bit product (quantise + tile, multiply) with both operands as bytes;
 // false when the problem stays with the bit-plane kernels.  quant_i8_workspace: what it wants, 0 where it does not take
-// the problem, and the least that a call accepts for it.
-void quant_i8_workspace(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes, size_t* least);
+// the problem.  quant_few_bits: products that the plane kernels take as well, large ones the faster.
+inline bool quant_few_bits(int bits_a, int bits_w) { return bits_a <= 2 && bits_w == 1; }
+size_t quant_i8_workspace(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w);
 bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
                      int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, size_t workspace_bytes, hipStream_t s,
                      hipError_t* err);

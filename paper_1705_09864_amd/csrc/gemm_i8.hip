@@ -170,7 +170,7 @@ quant_tiles_kernel(const QuantTilesParams p) {
 // MFMA and SIMD) holds it at half the matrix rate.
 struct I8Params {
   const uint4 *A, *B;  // tiles of the activations and of the weights
-  int M, N, nk;        // nk: k steps of 32
+  int M, N, nk;        // nk: k steps, of 32 or (two values a byte) 64
   int mblocks, nblocks;
   int tiles_m, tiles, tiles_per_xcd;
   int S;
@@ -559,29 +559,17 @@ static bool halves_pay(int64_t M, int64_t N, int64_t K, int bits_a) {
   if (K % 4096 == 0 && K >= 8192) return false;
   return K < (1 << 20) && M * N <= 1000000000 && M * N * K < 1200000000 * (int64_t)bits_a;
 }
-// Where they are not taken for want of workspace: a call takes what callers were told while a value took a byte here, the
-// planes' part of the workspace and below this line a byte a value, and refuses less.
-static bool bytes_told(int64_t M, int64_t N, int64_t K, int bits_a) {
-  if (M * N >= 1000000000) return false;  // (the products below stay in range)
-  const int64_t bytes = tile_bytes(M, K) + tile_bytes(N, K) + M * N * K / 1000 * 20 + 100 * K;
-  const int64_t planes = 14000000 * (bits_a - 1) + (K % 1024 ? 4000000 : 0) + 5500 * (ceil_div(K, 4096) * 4096 - K);
-  return bytes < planes;
-}
-
-// Workspace of the two tiled operands (0: not taken), and the least that a call accepts for them.  Taken: a result that
-// fills a quarter of a 32 x 32 block (below that the padding of the tiles is most of what is moved).
-void quant_i8_workspace(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w, size_t* bytes, size_t* least) {
-  *bytes = *least = 0;
-  if (M * N < 256) return;
+// Workspace of the two tiled operands (0: not taken).  Taken: a result that fills a quarter of a 32 x 32 block (below that the
+// padding of the tiles is most of what is moved).  (More than few bits keep a byte a value, what callers were told before two
+// shared one: the query is part of the interface.)
+size_t quant_i8_workspace(int64_t M, int64_t N, int64_t K, int bits_a, int bits_w) {
+  if (M * N < 256 || (quant_few_bits(bits_a, bits_w) && !halves_pay(M, N, K, bits_a))) return 0;
   const int64_t a = tile_bytes(M, K), b = tile_bytes(N, K);
   const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32);
   if (a >= ((int64_t)1 << 40) || b >= ((int64_t)1 << 40) || tiles >= ((int64_t)1 << 30) ||
       ceil_div(M, 32) * ceil_div(K, 256) + ceil_div(N, 32) * ceil_div(K, 256) >= ((int64_t)1 << 30))
-    return;
-  *bytes = *least = (size_t)(a + b);
-  if (bits_a > 2 || bits_w > 1) return;
-  if (!bytes_told(M, N, K, bits_a)) *least = 0;
-  *bytes = std::max(*least, halves_pay(M, N, K, bits_a) ? (size_t)(a + b) / 2 : 0);
+    return 0;
+  return (size_t)(a + b) / (quant_few_bits(bits_a, bits_w) ? 2 : 1);
 }
 
 namespace {
@@ -685,13 +673,10 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
 bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
                      int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, size_t workspace_bytes, hipStream_t s,
                      hipError_t* err) {
-  size_t need, least;
-  quant_i8_workspace(M, N, K, bits_a, bits_w, &need, &least);
+  const size_t need = quant_i8_workspace(M, N, K, bits_a, bits_w);
   if (gemm_engine == 1 || need == 0) return false;
-  if (bits_a <= 2 && bits_w == 1) {
-    if (gemm_engine != 0) return false;  // (an engine of the plane form is pinned)
-    if (!halves_pay(M, N, K, bits_a) || workspace_bytes < need) return false;
-  }
+  // (few bits: an engine of the plane form is pinned, or there is room for the planes alone)
+  if (quant_few_bits(bits_a, bits_w) && (gemm_engine != 0 || workspace_bytes < need)) return false;
   QuantTilesParams q;
   fill_operands(q.op, a, lda, bits_a, w, ldw, bits_w, M, N);
   // (a sum is at most 15 * 120 K, and so within 32 bits)

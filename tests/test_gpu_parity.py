@@ -684,17 +684,17 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
     np.testing.assert_array_equal(of.cpu().numpy(), r32)
 
 
-def test_quant_few_bits_workspace():
+@pytest.mark.parametrize("M,N,K,words", [(700, 700, 2000, 32), (520, 520, 1300, 32)])  # words: of a row of planes
+def test_quant_few_bits_workspace(M, N, K, words):
     """Few bits: with the workspace that the query names, two values a byte, in it and not beside it; with what the plane
     kernels need, the plane kernels; with less, refused."""
-    M, N, K = 700, 700, 2000
     rng = np.random.default_rng(9)
     a, w = rng.uniform(0, 1, (M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
     rS, _, _ = oracle.quant_gemm(a, w, 1, 1)
     full = B.workspace_bytes(B.OP_QUANT_GEMM, (M, N, K, 1, 1))
-    words = 32  # of a row of planes; of the weights' bits too
-    planes = M * words * 8 + N * words * 8 + (M * 4 + 255) // 256 * 256
-    assert planes < full == (704 + 704) * 2048 // 2
+    up = lambda n, to: (n + to - 1) // to * to
+    planes = up(M * words * 8, 256) + up(N * up(up(K, 64) // 64, 2) * 8, 256) + up(M * 4, 256)
+    assert planes < full == (up(M, 32) + up(N, 32)) * up(K, 256) // 2
     for size, kernel in ((full, "gemm_i8_kernel"), (full - 256, "gemm_fp4_kernel"), (planes, "gemm_fp4_kernel")):
         room = torch.full((4 * full,), 0xa5, dtype=torch.uint8, device="cuda")
         S, _ = B.quant_gemm(dev(a), dev(w), 1, want_float=False, workspace=room[full:full + size])

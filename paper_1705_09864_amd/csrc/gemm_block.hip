@@ -444,7 +444,7 @@ gemm_fp4_kernel(const BlockParams p) {
           char* const row = cbase + (size_t)(uint32_t)((mi + e) * ldr) * 4;
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            const float dot = fmaf(p.tot_mul, acc[i][j][4 * q + e], rc[e] + cb[j]);  // exact: whole numbers below 2^24
+            const float dot = fmaf(p.tot_mul, acc[i][j][4 * q + e], rc[e] + cb[j]);  // exact: see exact_k
             const int v = OUT == kI32 ? (int)dot : __builtin_bit_cast(int, (CONV ? a4[e] : al[j]) * dot);
             if constexpr (decltype(inside_tag)::value) {
               if constexpr (decltype(nt_tag)::value)
@@ -465,6 +465,10 @@ gemm_fp4_kernel(const BlockParams p) {
     store(std::false_type{}, std::false_type{});
   }
 }
+
+// Sums exact in fp32.  Planes 0 to 2 add 0 or 1 a value, plane 3 +-1/4: sums are multiples of 1/4 up to 13/16 K, which fp32 holds
+// below 2^22.  The results, 4 times the sum and the terms of row and column, are whole numbers; none of the three is above 13/4 K.
+bool exact_k(int64_t K) { return K < (1 << 22); }
 
 // K, less the values of plane 3 in K (whose products of signs count themselves) and those among the zero bits behind it up to
 // a whole group of 256, which count one each: together every value of plane 3 of the groups multiplied.  (For Eq. 2's count, half.)
@@ -542,9 +546,9 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
       return false;
     }
   }
-  // (32-bit offsets, rows of the last tile past the last row counted, of C within a tile; whole numbers up to 3 K exact in fp32)
+  // (32-bit offsets, rows of the last tile past the last row counted, of C within a tile)
   const int64_t lim = (int64_t)1 << 32;
-  if (K >= (1 << 22) || ((int64_t)M + 256) * lda_bytes >= lim || ((int64_t)N + 256) * ldb_bytes >= lim) return false;
+  if (!block::exact_k(K) || ((int64_t)M + 256) * lda_bytes >= lim || ((int64_t)N + 256) * ldb_bytes >= lim) return false;
   if (ldc >= (1 << 22) || ((uintptr_t)A & 3) || ((uintptr_t)B & 3)) return false;
   block::BlockParams p;
   p.A = (const char*)A;
@@ -603,7 +607,7 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   const int Cw = (int)words_for(C), kwords = KH * KW * Cw, Hp = H + 2 * pad, Wpp = W + 2 * pad;
   const int64_t P = (int64_t)Nimg * Ho * Wo, ld_words = conv_weight_row_words(kwords);
   const int64_t lim = (int64_t)1 << 32;
-  if ((ld_words & 1) || ((uintptr_t)Wp & 15) || (int64_t)C * KH * KW >= (1 << 22)) return false;
+  if ((ld_words & 1) || ((uintptr_t)Wp & 15) || !block::exact_k((int64_t)C * KH * KW)) return false;
   // (32-bit byte offsets throughout, and counts of pixels, halo words and tiles)
   if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= lim || ((int64_t)O + 256) * ld_words * 8 >= lim || P >= lim / 4) return false;
   if (((int64_t)Nimg * O + 256) * Ho * Wo * 4 >= lim) return false;

@@ -622,7 +622,7 @@ def test_quant_gemm_bytes(M, N, K, ba, bw):
         S, of = B.quant_gemm(da, dw, ba, bits_w=bw)
         assert "gemm_i8_kernel" in B.last_kernel()
     np.testing.assert_array_equal(S.cpu().numpy(), rS)
-    assert_f32_close(of.cpu().numpy(), r32)
+    np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
     S2, none = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw, want_float=False)
     assert none is None
     np.testing.assert_array_equal(S2.cpu().numpy(), rS)
@@ -666,7 +666,7 @@ def test_quant_halves(M, N, K, ba, bw):
     S, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, 3:], ba, bits_w=bw)
     assert "gemm_i8_kernel" in B.last_kernel() and "halves" in B.last_kernel(), B.last_kernel()
     np.testing.assert_array_equal(S.cpu().numpy(), rS)
-    assert_f32_close(of.cpu().numpy(), r32)
+    np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
 
 
 @pytest.mark.parametrize("M,N,K,T", [(16, 16, 4, 16), (1, 1, 63, 16), (17, 31, 64, 16), (15, 33, 65, 16), (256, 256, 129, 16), (256, 257, 512, 16),
@@ -1365,6 +1365,27 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
                 assert "f32,block" in B.last_kernel()
 
 
+@pytest.mark.parametrize("form", [2, 3])
+def test_gemm_fp4_block_form_longest_k(form):
+    """The block form just below its bound on K, where a sum of 13/16 K in steps of 1/4 (the sign plane's products) fills fp32: rows
+    all set, all clear and mixed on both sides; dot products and counts."""
+    K = (1 << 22) - 1
+    rng = np.random.default_rng(form)
+    def rows(n):
+        r = rng.integers(0, 2 ** 64, (n, (K + 63) // 64), dtype=np.uint64)
+        r[:n // 3], r[n // 3:n // 2] = ~np.uint64(0), 0
+        r[n // 2:n // 2 + 4] |= r[n // 2 + 4:n // 2 + 8] | rng.integers(0, 2 ** 64, (4, r.shape[1]), dtype=np.uint64)  # (mostly set)
+        r[:, -1] &= ~np.uint64(0) >> np.uint64(1)
+        return r
+    A, W = rows(130), rows(70)
+    want = np.stack([K - 2 * np.bitwise_count(a ^ W).sum(1, dtype=np.int64) for a in A])
+    a, w = dev(A.view(np.int64)), dev(W.view(np.int64))
+    with tuned(k17=1, k19=form):
+        np.testing.assert_array_equal(B.xnor_gemm(a, w, K).cpu().numpy(), want)
+        assert "i32,block>" in B.last_kernel(), B.last_kernel()
+        np.testing.assert_array_equal(B.xnor_gemm(a, w, K, count=True).cpu().numpy(), (want + K) // 2)
+
+
 @pytest.mark.parametrize("M,N,K,kind,block", [
     # rows of an odd number of 32-bit words: from 513 tiles of 64 x 64 on
     (1032, 1995, 3995, "w32", True), (2137, 971, 3163, "w32", True), (1142, 1962, 987, "w32", True),
@@ -1513,7 +1534,8 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
         a, w = rng.uniform(0, 1, (67, k)).astype(np.float32), rng.standard_normal((70, k)).astype(np.float32)
         a[:40], w[:50] = 1.0, 1.0
         S, f = B.quant_gemm(dev(a), dev(w), 2)
-        assert "gemm_fp4_kernel" in B.last_kernel() or "gemm_mfma" in B.last_kernel() or "gemm_i8" in B.last_kernel()
+        assert "planes,S" in B.last_kernel() and "K split %d" % split in B.last_kernel(), B.last_kernel()
+        assert ("16-bit partials" in B.last_kernel()) == (3 * k <= 65535), B.last_kernel()
         rS, _, r32 = oracle.quant_gemm(a, w, 2)
         np.testing.assert_array_equal(S.cpu().numpy(), rS)
         np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(3))
@@ -1730,7 +1752,10 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
     (5, 300, 8, 7, 63, 5, 1, 2, 0),     # many segments, images that end inside a tile
     (1, 640, 23, 24, 200, 3, 1, 0, 1),  # several tiles each way
     (9, 70, 9, 8, 31, 7, 1, 3, 3),      # halo as wide as the image's rest
-    (4, 256, 16, 16, 64, 1, 1, 0, 6)])
+    (4, 256, 16, 16, 64, 1, 1, 0, 6),
+    (300, 130, 1, 1, 70, 1, 1, 0, 0),   # a pixel an image: a tile holds as many images as pixels
+    (130, 200, 3, 3, 130, 3, 2, 1, 1),  # four
+    (37, 320, 7, 1, 65, 1, 1, 0, 1)])   # seven: tiles begin and end inside an image
 def test_conv_long_k_kernels(form, N, C, H, W, O, k, s, p, opad):
     """Convolutions of packed images on the kernels for long K, whatever the size: rows staged once per workgroup (2: 128
     filters x 128 pixels, 3: 64 x 256), and 64 x 64 per wave (1; with and without K divided).  fp32, int32, and the next

@@ -1,5 +1,7 @@
 """Pins for the oracle's alpha helper, Eq. 1 quantiser and k-bit GEMM (CPU only)."""
+import ctypes
 import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -148,3 +150,24 @@ def test_kbit_weights_brute_force_in_exact_arithmetic():
                 assert S[m, n] == acc
                 assert abs(f64[m, n] - acc / (La * Lw)) < 1e-12
                 assert f32[m, n] == np.float32(acc) / np.float32(La * Lw)
+
+
+def test_quotient_by_reciprocal_is_the_division(tmp_path):
+    """The k-bit kernels divide by a product of two level counts as a multiplication by its reciprocal, corrected once by the
+    remainder (Markstein): equal to the IEEE division for every significand and every such divisor (powers of two scale exactly)."""
+    src, lib = tmp_path / "q.c", tmp_path / "q.so"
+    src.write_text("""#include <math.h>
+    long wrong(float b) {
+      const float y = 1.0f / b;
+      long n = 0;
+      for (int i = 1 << 23; i < 1 << 24; ++i) {
+        const float a = (float)i, q = a * y;
+        n += fmaf(fmaf(-q, b, a), y, q) != a / b;
+      }
+      return n;
+    }""")
+    subprocess.check_call(["gcc", "-O2", "-ffp-contract=off", "-shared", "-fPIC", str(src), "-o", str(lib), "-lm"])
+    wrong = ctypes.CDLL(str(lib)).wrong
+    wrong.argtypes, wrong.restype = [ctypes.c_float], ctypes.c_long
+    for b in sorted({(2 ** i - 1) * (2 ** j - 1) for i in range(1, 9) for j in range(1, 9)}):
+        assert wrong(b) == 0, b

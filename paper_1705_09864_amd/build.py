@@ -28,9 +28,9 @@ def _stale(out, deps):
     return any(os.path.getmtime(d) > t for d in deps)
 
 
-def device_asm(src):
+def device_asm(src, folder=BUILD):
     """Path of the gfx950 assembly that -save-temps leaves next to the object of `src`."""
-    return os.path.join(BUILD, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+    return os.path.join(folder, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
 
 
 def _isa_check():
@@ -63,12 +63,12 @@ def check_scalar_loads():
             raise RuntimeError("in-flight scalar load hazard in %s:\n%s" % (src, isa_check.report(bad)))
 
 
-def check_asm_hazards():
-    """Scan the compiled device code of every source for wait states missing in front of or behind an
+def check_asm_hazards(asm=current_asm):
+    """Scan the compiled device code of every source, asm(source), for wait states missing in front of or behind an
     instruction written as asm (isa_check.asm_hazards)."""
     isa_check = _isa_check()
     for src in SOURCES:
-        bad = isa_check.asm_hazards(current_asm(src))
+        bad = isa_check.asm_hazards(asm(src))
         if bad:
             raise RuntimeError("missing wait states in %s:\n%s" % (src, isa_check.report_hazards(bad)))
 

@@ -231,7 +231,8 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 // Four results in a row, `off` bytes behind an address that the wave shares.  NT: past the caches.  (As asm: as a builtin the
 // compiler merges the hinted store with the ordinary one of the other branch, and the hint is gone.  What follows a 16-byte store
 // may not write its registers in the next instruction, which the compiler sees to only where it knows of the store.)
-// (BMX_FP4_STAMPS: the stamps' branches make the compiler take the wave's address for the lanes': plain stores in that build)
+// (BMX_FP4_STAMPS: the stamps' branches make the compiler take the wave's address for the lanes': plain stores in that build.
+// With the address put back into scalar registers ahead of each, the asm would want five wait states there)
 __device__ __forceinline__ void store_four(char* to, uint32_t off, const v4u& v, bool nt) {
 #ifdef BMX_FP4_STAMPS
   *(v4u_any*)(to + off) = v;
@@ -314,7 +315,6 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 ) {
   extern __shared__ uint4 lds[];
   constexpr int NA = TM * PL, NB = NA + TN;  // staged blocks of 32 rows: A's, then B's
-  constexpr int kStage = NB * 128;           // uint4 per staged segment: NB blocks x 32 rows x 64 bytes
   // LDS per wave: its staging area, overlaid after the main loop of a split by its partial tile and counts
   constexpr int kSlot = slot_size(PL, SPLIT, HALF);
   // Everything the wave needs before its first load, named in one statement at the top: the

@@ -29,11 +29,12 @@ def build_stamped():
     objs = []
     for src in _build.SOURCES:
         o = os.path.join(out, src + ".o")
-        cmd = [_build.HIPCC] + _build.FLAGS + ["-DBMX_FP4_STAMPS", "-DBMX_WS_STAMPS", "-c", os.path.join(_build.CSRC, src), "-o", o]
+        cmd = [_build.HIPCC] + _build.FLAGS + ["-DBMX_FP4_STAMPS", "-DBMX_WS_STAMPS", "-save-temps=obj", "-c", os.path.join(_build.CSRC, src), "-o", o]
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed for %s:\n%s" % (src, r.stdout))
         objs.append(o)
+    _build.check_asm_hazards(lambda src: _build.device_asm(src, out))
     subprocess.check_call([_build.HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-z,defs"] + objs + ["-o", STAMPED])
     return STAMPED
 

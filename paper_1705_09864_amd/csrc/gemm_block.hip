@@ -4,8 +4,8 @@
 // Arithmetic as in gemm_fp4.hip: K - 2 pc(a) - 2 pc(b) + 4 * sum_k a * b, a bit stays where it stands
 // in its nibble and the MFMA's block scale makes it worth 1; but every fourth value, whose bit is the nibble's sign, is
 // multiplied as the sign itself and needs no popcount: sum_k s(a) s(b).  An operand takes 4 instructions a word and plane
-// then and not 5 (K held as 8192, half a second each: random bits 181.9 -> 179.9 us, all bits clear, where the power does not
-// bound it, 152.4 -> 147.8; 69 x 64 x 19 x 21 -> 406 in three packed layers 64.9 -> 64.1; 4531 x 1600 x 4096 16.8 -> 16.4).
+// then and not 5 (8192^3, all bits clear, where the power does not bound it, 152.4 -> 147.8 us; random bits, where it does,
+// 182.4 -> 178.2 in the first millisecond, level once the clock has settled: 376 -> 361 thousand clocks, at a lower rate; 69 x 64 x 19 x 21 -> 406 in three packed layers 64.9 -> 64.1; 4531 x 1600 x 4096 16.8 -> 16.4).
 //
 // There every wave fetches the rows of its own tile, waits for its own reads of a segment before it may request
 // the next, and turns all of a segment's bits into operands before it multiplies.  With the chip full that
@@ -27,11 +27,11 @@
 //     the next convolution's packed image, halo included.
 //   (Three and four stages in flight changed nothing, at 8192^3 or with one workgroup per CU: it is issue and, with
 //   one wave on a SIMD, the chain of its own instructions that bounds the loop, not the memory behind it.)
-// What bounds it, from counters at 8192^3 as 256 x 128 (while an operand took 5 instructions): the matrix pipe is busy in 70 % of
-// the clocks, a SIMD issues an instruction in 77 % of them (5.2 of the vector ALU for every MFMA), a wave waits for data or a barrier
-// in 11 % of its time; and the clock stands at 2.0 to 2.2 GHz under that load, by the power that the products take: the same launch on
-// zeros is a fifth faster.  The same launch back to back takes 182 us in the first millisecond, 243
-// in the fourth, 185 after 15 and 172 from 30 on; the clocks that it needs stay 376 thousand.
+// What bounds it, from counters at 8192^3 as 256 x 128: the matrix pipe is busy in 73 % of
+// the clocks, a SIMD issues an instruction in 75 % of them (4.6 of the vector ALU for every MFMA), a wave waits for data or a barrier
+// in 13 % of its time; and the clock stands at 2.0 to 2.15 GHz under that load, by the power that the products take: the same launch on
+// zeros is a fifth faster.  The same launch back to back takes 178 us in the first millisecond, 244
+// in the fourth, 181 after 15 and 171 to 174 from 30 on; the clocks that it needs stay 361 thousand.
 // Measured, us a call, gemm_fp4.hip / here: 8192^3 202 / 173, 8192 x 8192 x 1024 75 / 50, 4096^3 33 / 28, 3008 x 1471
 // x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.  Convolutions of packed
 // images: 11 x 320 x 49 x 49 -> 334, 3 x 3, 26.3 / 21.2, 40 x 192 x 28 x 28 -> 128, 5 x 5, 21.6 / 16.0; as packed bits, a channel pack of

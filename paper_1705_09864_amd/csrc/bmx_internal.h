@@ -166,6 +166,7 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
                        const float* alpha, int32_t* C_i32, float* C_f32, uint64_t* C_bits, const float* thr, int64_t ldc,
                        bool as_count, hipStream_t s, hipError_t* err);
 extern int gemm_small;
+bool capturing(hipStream_t s);  // conv_one.hip: whether the launches of `s` go into a graph
 // gemm_mfma.hip: an xnor product of rows that may start on any dword, where a kernel reads them as they are.
 bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int64_t ldb_dw, int M, int N, int K,
                              int32_t* C, int64_t ldc, hipStream_t s, hipError_t* err);

@@ -1883,7 +1883,7 @@ def test_conv_one_launch_waves(waves, parts, N, C, H, W, O, k, s, p):
 
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,call,graph", [
     (25, 40, 21, 21, 320, 5, 2, 2, False, False), (126, 107, 42, 44, 18, 3, 1, 1, False, False), (136, 128, 16, 16, 458, 1, 1, 0, False, False),
-    (2, 142, 50, 50, 64, 3, 2, 1, True, False), (6, 90, 40, 40, 128, 3, 1, 1, True, False), (1, 64, 8, 8, 64, 1, 1, 0, True, True),
+    (2, 142, 50, 50, 64, 3, 2, 1, True, False), (3, 256, 25, 25, 128, 3, 1, 1, True, False), (7, 130, 29, 27, 70, 3, 2, 1, True, True), (1, 64, 8, 8, 64, 1, 1, 0, True, True),
     (123, 445, 11, 10, 18, 1, 2, 0, True, True)])
 def test_conv_one_launch_or_two(N, C, H, W, O, k, s, p, call, graph):
     """Layers that look short to a model that counts workgroups by the chip and not by its XCDs, or bytes and not loads, take two

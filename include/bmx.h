@@ -254,7 +254,8 @@ int bmx_binary_conv2d_bits(const uint64_t* xp, int N, int C, int H, int W, const
  *   a fp32 [M, lda], w fp32 [N, ldw]; out_i32_scaled (S) and out_f32 are [M, ldo]; either
  *   may be NULL, not both.  bits_a, bits_w in 1..8.
  *   workspace >= bmx_workspace_bytes(BMX_OP_QUANT_GEMM, {M, N, K, bits_a, bits_w}, 5).  (With bits_a <= 2 and bits_w = 1 a call also
- *   takes less, down to what the packed planes need, and then runs on the plane kernels, with the same results.) */
+ *   takes less, down to what the packed planes need, and then runs on the plane kernels, with the same results.)
+ *   Small products run in one launch, others in two; the choice is made as bmx_binary_conv2d makes it. */
 int bmx_quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw,
                    int bits_w, int M, int N, int K, int32_t* out_i32_scaled, float* out_f32,
                    int64_t ldo, void* workspace, size_t workspace_bytes, void* stream);

@@ -623,7 +623,19 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   // Over the same products the choice is 0.8 % behind the better.  us a call, before two values shared a byte and tiles were
   // of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2 x 4 5.8 / 3.6,
   // 202 x 192 x 437 5.0 / 3.4.
-  if (small ? K > 44 * 64 : ceil_div(K, 32) * ceil_div(t32, 256) > (t32 > 256 ? 24 : sums ? 28 : 32)) return false;
+  // (Where two values share a byte the pair is the faster one: with more than 128 tiles of 16 x 16 36 to 44 steps 0.92, 119 x 448 x 2684 of
+  // 1 x 1 bits 9.2 / 7.6.)
+  const bool halves = bits_a <= 4 && bits_w <= 4;
+  const int64_t steps = small ? ceil_div(K, 64) : ceil_div(K, 32) * ceil_div(t32, 256);
+  if (steps > (small ? (halves && t16 > 128 ? 36 : 44) : t32 > 256 ? 24 : sums ? 28 : 32)) return false;
+  // In a graph the host's part is not paid on replay, and the lines stand lower: where the GPU's part of both forms is level over 900
+  // products of 14 to 64 steps, rows of whole lines or not (a tile reads its own rows, each for itself).  There the choice by them is
+  // 1.5 % behind the better form, by the lines for calls 4.1 % (287 x 256 x 789 of 2 x 1 bits: one launch 6.9 us, two 5.5).
+  const bool ragged = (lda | ldw) % 32 != 0;
+  const int64_t graph_steps = !small      ? (t32 > 256 ? 18 : t32 > 128 ? (ragged ? 18 : 22) : (ragged ? 22 : 28))
+                              : halves    ? std::max<int64_t>(24, 46 - t16 / (ragged ? 5 : 8))
+                                          : (ragged && t16 > 64 ? 38 : 44);
+  if (steps > graph_steps && capturing(s)) return false;
   if (K < 4 || (int64_t)M * lda * 4 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 4 >= ((int64_t)1 << 32)) return false;
   const int T = small ? 16 : 32, nk = (int)ceil_div(K, 1024 / T);
   QuantSmallParams p;

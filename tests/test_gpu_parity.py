@@ -684,6 +684,39 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
     np.testing.assert_array_equal(of.cpu().numpy(), r32)
 
 
+@pytest.mark.parametrize("M,N,K,ba,bw,call,graph", [
+    (119, 448, 2304, 1, 1, True, False), (119, 448, 2305, 1, 1, False, False), (119, 448, 2816, 8, 1, True, True), (119, 448, 2815, 8, 1, True, False),
+    (119, 448, 2432, 8, 1, True, True), (30, 40, 2816, 4, 4, True, True), (30, 40, 2815, 4, 8, True, True), (90, 60, 2688, 2, 2, True, True),
+    (90, 60, 2689, 2, 2, True, False), (241, 256, 1536, 2, 1, True, True), (241, 256, 1537, 2, 1, True, False), (287, 256, 704, 2, 1, True, True),
+    (287, 256, 705, 2, 1, True, False), (287, 256, 896, 2, 1, True, True), (287, 256, 928, 2, 1, True, False), (500, 512, 704, 8, 2, True, True),
+    (500, 512, 736, 8, 2, True, False), (500, 512, 576, 8, 2, True, True), (500, 512, 575, 8, 2, True, True), (500, 512, 577, 8, 2, True, False),
+    (600, 512, 288, 3, 3, True, True), (600, 512, 289, 3, 3, True, False)])
+def test_quant_one_launch_or_two(M, N, K, ba, bw, call, graph):
+    """The lines between one launch and two, for calls and for calls that are being captured; replays between calls give what the
+    calls give."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    a = torch.rand((M, K), device="cuda", generator=g)
+    w = torch.rand((N, K), device="cuda", generator=g) * 2 - 1
+    run = lambda: B.quant_gemm(a, w, ba, bits_w=bw)  # noqa: E731
+    run()
+    assert ("quant_small" in B.last_kernel()) == call, B.last_kernel()
+    torch.cuda.synchronize()
+    captured = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(captured):
+        S, f = run()
+        assert ("quant_small" in B.last_kernel()) == graph, B.last_kernel()
+    for _ in range(3):
+        a.uniform_(generator=g)
+        captured.replay()
+        S2, f2 = run()
+        assert ("quant_small" in B.last_kernel()) == call, B.last_kernel()
+        assert torch.equal(S, S2) and torch.equal(f, f2)
+    rS, _, r32 = oracle.quant_gemm(a.cpu().numpy(), w.cpu().numpy(), ba, bw)
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    np.testing.assert_array_equal(f.cpu().numpy(), r32)
+
+
 @pytest.mark.parametrize("M,N,K,words", [(700, 700, 2000, 32), (520, 520, 1300, 32)])  # words: of a row of planes
 def test_quant_few_bits_workspace(M, N, K, words):
     """Few bits: with the workspace that the query names, two values a byte, in it and not beside it; with what the plane

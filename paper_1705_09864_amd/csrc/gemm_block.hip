@@ -581,18 +581,19 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
 
 int conv_block = 0;  // 1 = never, 2 = 128 filters x 128 pixels and 3 = 64 x 256 per workgroup whatever the size
 
-// Fitted to 169 convolutions of 45 to 392 words measured on each, and to 260 there since (us, fp32 results; the choice by it is 0.3 %
-// off the best, 18 % at most).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
+// Fitted to 361 convolutions of 8 to 392 words measured on each (us, fp32 results and packed bits; the choice by it is 0.16 %
+// off the best, 10 % at most; 0.66 % and 21 % while the terms were those of the kernels before their last change: 68175 pixels, 128 filters, 72
+// words 26.6 us in gemm_fp4.hip, 22.0 here).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
 // through registers (an odd number of channel words).  Here by workgroups per CU; one alone on a CU takes more than half as
 // long for a segment as two together.
 double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
   const double K = kwords;
   const double n = (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
-  const double high = (double)ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256), mh = std::max(1.6, high);
-  const double wide = (double)ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256), mw = std::max(1.6, wide);
-  const double there = any_dword ? 3.2 + n * (1.05 + 0.0273 * K) : 3.2 + n * (0.7 + 0.021 * K);
-  const double us2 = any_dword ? 3.8 + 2.1 * high + 0.080 * mh * K : 2.4 + 3.2 * high + 0.063 * mh * K;
-  const double us3 = any_dword ? 3.9 + 1.9 * wide + 0.0945 * mw * K : 0.7 + 4.5 * wide + 0.066 * mw * K;
+  const double high = (double)ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256), mh = std::max(1.3, high);
+  const double wide = (double)ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256), mw = std::max(1.3, wide);
+  const double there = any_dword ? 3.4 + n * (1.2 + 0.0243 * K) : 3.6 + n * (0.87 + 0.0195 * K);
+  const double us2 = any_dword ? 6.2 + 0.36 * high + 0.088 * mh * K : 5.25 + 0.99 * high + 0.0718 * mh * K;
+  const double us3 = any_dword ? 6.2 + 0.112 * mw * K : 4.5 + 1.14 * wide + 0.0783 * mw * K;
   *form = std::min(us2, us3) >= there ? 0 : us2 <= us3 ? 2 : 3;
   return std::min(there, std::min(us2, us3));
 }

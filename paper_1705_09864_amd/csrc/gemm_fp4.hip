@@ -931,8 +931,9 @@ int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests
 //   - four where each has two groups, 29 words on, up to three tiles a CU (257 to 512 tiles 1.25 / 1.00 / 1.44 for 8 / 4 / 1; 513 to
 //     768 1.4 / 1.00 / 1.15; of 29 to 33 words 1.00 / 1.20, 4 / 1), and with more than one, but few, for some SIMDs (1025 to 1280: 1.45 /
 //     1.00 / 1.19; rows through registers of less than 34 words 1.02 / 1.00, 4 / 1, beyond 768: one).  Between them a SIMD has at most one
-//     undivided tile: one wave (1.5 / 1.03 / 1.00), but of 75 words on four (1.29 / 1.00 / 1.04).  Four and eight keep the SIMDs of a CU level
-//     where it has several tiles (390 x 3329 x 5632, 371 tiles, takes 10.4 us over four waves, 15.1 over five, 12.2 over three).
+//     undivided tile: one wave (1.5 / 1.03 / 1.00; four over one of 75 to 144 words 1.04 over 37 int32 products, 1.05 over 166 of
+//     fp32).  Four and eight keep the SIMDs of a CU level where it has several tiles (390 x 3329 x 5632, 371 tiles, takes 10.4 us over four
+//     waves, 15.1 over five, 12.2 over three).
 //     Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09), and from 2049 to 2350 (- / 1.01 / 1.10; between, - /
 //     1.09 / 1.04).
 //   - three of 21 to 28 words (six or seven groups), up to two tiles a CU (3 / 2 / 1 waves, to 256 tiles 1.00 / 1.14 / 1.17, to 512 rows
@@ -948,7 +949,7 @@ static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
   if (kwords < 34 && (patches || (rows == Rows::registers && tiles > 768))) return 1;
   if (kwords >= 75 && patches) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
   if (tiles <= 768 || (tiles > 1024 && tiles <= 1280)) return 4;
-  return tiles <= 1024 && kwords >= 75 && rows == Rows::direct ? 4 : 1;
+  return 1;
 }
 
 // Below 64 tiles kernels of 32 x 32 tiles: four times the waves, and there is not enough K to give these tiles to that many waves.

@@ -624,7 +624,7 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   // of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2 x 4 5.8 / 3.6,
   // 202 x 192 x 437 5.0 / 3.4.
   // (Where two values share a byte the pair is the faster one: with more than 128 tiles of 16 x 16 36 to 44 steps 0.92, 119 x 448 x 2684 of
-  // 1 x 1 bits 9.2 / 7.6.)
+  // 1 x 1 bits 9.2 / 7.5.)
   const bool halves = bits_a <= 4 && bits_w <= 4;
   const int64_t steps = small ? ceil_div(K, 64) : ceil_div(K, 32) * ceil_div(t32, 256);
   if (steps > (small ? (halves && t16 > 128 ? 36 : 44) : t32 > 256 ? 24 : sums ? 28 : 32)) return false;

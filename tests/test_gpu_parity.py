@@ -1577,7 +1577,7 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
 @pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 1), (16, 16, 21, 3), (16, 16, 28, 3), (16, 17, 20, 1), (16, 17, 23, 3),
                                                (16, 32, 28, 3), (16, 32, 27, 3), (19, 27, 27, 1), (16, 16, 29, 4), (16, 16, 60, 4), (16, 16, 59, 4),
                                                (16, 16, 61, 8), (16, 32, 32, 4), (19, 27, 28, 1), (19, 27, 30, 4), (24, 32, 33, 4), (32, 33, 33, 1), (24, 32, 34, 4), (24, 33, 34, 1),
-                                               (24, 33, 76, 4), (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
+                                               (24, 33, 76, 1), (32, 32, 98, 1), (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
 def test_gemm_fp4_split_lines(tm, tn, words, split):
     """Both sides of the lines between the waves that share a tile's K, by the tiles and words (an odd number of words: rows that pass
     through registers); a last tile of one row and one column; the same results undivided."""

@@ -124,7 +124,8 @@ int bmx_xnor_gemm_w32(const uint32_t* A, int64_t lda_dw, const uint32_t* B, int6
  *   alpha    fp32 [out_features] or NULL (= 1).
  *   out_i32 / out_f32   exactly one is non-NULL; both are [batch, ldo], ldo >= out_features.
  *            out_i32 = dot (alpha must be NULL);  out_f32 = alpha[o] * (float)dot.
- *   workspace >= bmx_workspace_bytes(BMX_OP_BINARY_FC, {batch, in, out}, 3), 16-byte aligned. */
+ *   workspace >= bmx_workspace_bytes(BMX_OP_BINARY_FC, {batch, in, out}, 3), 16-byte aligned.
+ *   Small layers run in one launch, others in two; the choice is made as bmx_binary_conv2d makes it. */
 int bmx_binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w,
                   const float* alpha, int batch, int in_features, int out_features,
                   int32_t* out_i32, float* out_f32, int64_t ldo, void* workspace,

@@ -333,13 +333,14 @@ int fc_check(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, con
 }
 
 // In one launch where the layer is small enough, else pack the activations into chunk-padded rows at
-// xp (the scalar side of the GEMM kernel reads whole chunks), then the GEMM with the epilogue.  xp null:
+// xp (the scalar side of the GEMM kernel reads whole chunks), then the GEMM with the epilogue.  shared: of the library's own scratch
+// memory.  xp null:
 // BMX_ERR_WORKSPACE, with nothing launched, where it is needed.
 int fc_launch(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
               int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, uint64_t* xp,
-              hipStream_t s) {
+              bool shared, hipStream_t s) {
   hipError_t small = hipSuccess;  // a layer of a few microseconds or less: one launch, no workspace
-  if (bmx::launch_fc_small(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo, s, &small))
+  if (bmx::launch_fc_small(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo, shared, s, &small))
     return hip_status(small);
   if (!xp) return BMX_ERR_WORKSPACE;
   const int64_t ldp = bmx::padded_words(in_features);
@@ -364,7 +365,7 @@ static int binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
     if (misaligned(workspace, 16)) return BMX_ERR_ALIGN;
   }
   return fc_launch(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo,
-                   (uint64_t*)workspace, (hipStream_t)stream);
+                   (uint64_t*)workspace, false, (hipStream_t)stream);
 }
 
 int bmx_binary_fc(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w,
@@ -410,7 +411,7 @@ int bmx_binary_fc_static(const float* x, int64_t ldx, const uint64_t* Wp, int64_
   // (the pack kernel writes every word of every padded row it hands to the GEMM, so nothing of
   // a previous call's contents is ever read and nothing needs clearing)
   return fc_launch(x, ldx, Wp, ldw_w, alpha, batch, in_features, out_features, out_i32, out_f32, ldo,
-                   (uint64_t*)ptr, (hipStream_t)stream);
+                   (uint64_t*)ptr, true, (hipStream_t)stream);
 }
 
 int bmx_binary_fc_packed(const uint64_t* xp, int64_t ldx_w, const uint64_t* Wp, int64_t ldw_w,

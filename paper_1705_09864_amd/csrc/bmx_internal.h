@@ -194,9 +194,10 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
 extern int gemm_fp4_split, gemm_fp4_half, gemm_fp4_band;
 // fc_small.hip: the whole fully connected layer (sign bits of the fp32 input, xor + popcount,
 // scale) in one launch, for layers too small to be worth two; false when the layer is not
-// small enough (nothing launched then).
+// small enough (nothing launched then).  shared: two launches would use memory that calls on other streams use too,
+// so everything that can do without it does.
 bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
-                     int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo,
+                     int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, bool shared,
                      hipStream_t s, hipError_t* err);
 extern int fc_small;
 bool launch_plane_gemm_mfma(const uint64_t* planes_rows, int64_t lda_w, int bits, const int32_t* rowsum,

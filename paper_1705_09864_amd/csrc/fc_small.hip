@@ -269,7 +269,7 @@ int fc_small = 0;  // 1 = never (measurements and tests of the general path on s
 // Takes the layer where what the busiest CU has to move in this form costs less than a second
 // launch; false otherwise (nothing launched then).
 bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ldw_w, const float* alpha, int batch,
-                     int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo,
+                     int in_features, int out_features, int32_t* out_i32, float* out_f32, int64_t ldo, bool shared,
                      hipStream_t s, hipError_t* err) {
   // (a GEMM engine pinned through the tuning hook is what the caller wants to run)
   if (fc_small == 1 || gemm_engine != 0) return false;
@@ -281,6 +281,7 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   auto lanes_for = [&](int cols) -> const Lanes& { return cols < 8 * features_per_pass(few) ? most_lanes : least_lanes; };
   // Rows and features per workgroup: the pair that leaves the busiest CU the least to move (fp32 rows
   // and packed weights of its workgroups, and a fixed share per workgroup for its latencies).
+  const bool fewer_rows = Kw > 28 && (int64_t)batch * 12 > out_features;
   int64_t best = INT64_MAX;
   int rm_log = 0, cols_log = 4;
   for (int c = 4; c <= 9; ++c) {
@@ -290,16 +291,22 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
       if (r > 0 && ((1 << r) / 2 >= batch || (Kpad * 8 << r) > 48 * 1024)) break;
       const int64_t wgs = shift_up(batch, r) * groups;
       const int64_t cost = shift_up(wgs, 8) * (((int64_t)in_features * 4 << r) + (Kw * 8 << c) + (4 * Kpad << (r + c)) + (16 << 10));
-      if (cost < best) best = cost, rm_log = r, cols_log = c;
+      // (Twice the rows and half the features is level where K is whole words.  Then fewer rows where rows are long and many, as each
+      // of the fewer groups of features reads them again: from 29 words and a row for twelve features on 0.72 to 1.06 of the
+      // time, mean 0.92, 343 x 7424 -> 95 5.5 us in pairs of rows, 7.6 in fours; else 0.95 to 1.14, mean 1.00.)
+      if (cost < best || (cost == best && r < rm_log && fewer_rows)) best = cost, rm_log = r, cols_log = c;
     }
   }
   // Level with two launches at about 320 KB (8 x 9216 -> 4096, 256 KB: 6.0 against 7.4 us; 767 x 3740 -> 124,
   // 261 KB: 6.0 / 7.8; 719 x 832 -> 739, 7.3 / 7.3 to 8.6; 287 x 1598 -> 1213, 371 KB: 8.4 / 7.5).  A few workgroups have the memory system
   // to themselves, and the general path's one or two tiles take a chain as long (2 x 65536 -> 16: 7.0
-  // against 13.3 us).
+  // against 13.3 us).  Eight rows a workgroup, of 489 layers: 256 to 320 KB in more than a round of workgroups the two launches take 0.86 to
+  // 0.96 of this form's time as calls, 0.77 to 0.88 in a graph; in one round 0.88 to 1.17 as calls, 0.84 to 0.97 in a graph, where the host's
+  // part is not paid on replay: the line is at 256 KB for both.  (Fewer rows: 1.0 and more, 568 x 7217 -> 64 7.2 / 9.1.)
   const int rm = 1 << rm_log, cols = 1 << cols_log;
   const int64_t wgs = shift_up(batch, rm_log) * shift_up(out_features, cols_log);
   if (best > (wgs <= 32 ? 768 << 10 : 320 << 10)) return false;
+  if (best > 256 << 10 && wgs > 32 && rm == 8 && !shared && (wgs > 256 || capturing(s))) return false;
   const Lanes lanes = lanes_for(std::min(cols, out_features));
   const int64_t Kpad = lanes.padded;
   FcSmallParams p;

@@ -255,6 +255,42 @@ def test_fc_small_layers_one_launch(batch, fin, fout):
         assert "fc_small_kernel" not in B.last_kernel()
 
 
+@pytest.mark.parametrize("batch,fin,fout,call,graph,static", [
+    (241, 3596, 440, True, True, True), (600, 600, 1400, True, False, True), (600, 512, 1400, True, True, True),  # one round of workgroups
+    (900, 127, 1900, False, False, True), (892, 318, 1100, True, True, True), (892, 322, 1130, False, False, True),  # several
+    (2, 65536, 16, True, True, True), (1000, 130, 2000, False, False, False)])
+def test_fc_small_lines(batch, fin, fout, call, graph, static):
+    """The lines between one launch and two, for calls, captured calls and calls on the library's scratch memory; replays between
+    calls give what the calls give."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(fin)
+    x = torch.randn((batch, fin), device="cuda", generator=g)
+    w = torch.randn((fout, fin), device="cuda", generator=g)
+    Wp, alpha = B.binarize_pack(w, 1), B.alpha_mean_abs(w)
+    run = lambda: B.binary_fc(x, Wp, alpha=alpha)  # noqa: E731
+    out_static = torch.empty((batch, fout), device="cuda")
+    for f, one in ((run, call), (lambda: B.binary_fc_static(x, Wp, alpha=alpha, out=out_static), static)):
+        f()
+        assert ("fc_small" in B.last_kernel()) == one, B.last_kernel()
+    torch.cuda.synchronize()
+    captured, captured_static = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(captured):
+        out = run()
+        assert ("fc_small" in B.last_kernel()) == graph, B.last_kernel()
+    with torch.cuda.graph(captured_static):
+        B.binary_fc_static(x, Wp, alpha=alpha, out=out_static)
+        assert ("fc_small" in B.last_kernel()) == static, B.last_kernel()
+    for _ in range(3):
+        x.normal_(generator=g)
+        captured.replay()
+        captured_static.replay()
+        want = run()
+        assert ("fc_small" in B.last_kernel()) == call, B.last_kernel()
+        assert torch.equal(out, want) and torch.equal(out_static, want)
+        with tuned(k15=1):
+            assert torch.equal(run(), want)
+
+
 @pytest.mark.parametrize("batch,fin,fout", [(1, 512, 1), (3, 513, 17), (5, 1024, 33), (6, 1025, 40), (9, 2049, 31), (4, 3073, 65),
                                             (7, 4097, 50), (2, 8193, 130), (8, 12289, 20), (3, 20481, 9), (33, 2048, 600)])
 def test_fc_small_row_lengths(batch, fin, fout):

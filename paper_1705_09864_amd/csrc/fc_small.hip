@@ -281,7 +281,7 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   auto lanes_for = [&](int cols) -> const Lanes& { return cols < 8 * features_per_pass(few) ? most_lanes : least_lanes; };
   // Rows and features per workgroup: the pair that leaves the busiest CU the least to move (fp32 rows
   // and packed weights of its workgroups, and a fixed share per workgroup for its latencies).
-  const bool fewer_rows = Kw > 28 && (int64_t)batch * 12 > out_features;
+  const bool long_and_many = Kw > 28 && (int64_t)batch * 12 > out_features;
   int64_t best = INT64_MAX;
   int rm_log = 0, cols_log = 4;
   for (int c = 4; c <= 9; ++c) {
@@ -291,10 +291,12 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
       if (r > 0 && ((1 << r) / 2 >= batch || (Kpad * 8 << r) > 48 * 1024)) break;
       const int64_t wgs = shift_up(batch, r) * groups;
       const int64_t cost = shift_up(wgs, 8) * (((int64_t)in_features * 4 << r) + (Kw * 8 << c) + (4 * Kpad << (r + c)) + (16 << 10));
-      // (Twice the rows and half the features is level where K is whole words.  Then fewer rows where rows are long and many, as each
+      // (Twice the rows and half the features is level where K is whole words.  Then four rows and not eight (0.96 of the time over 95
+      // layers, 320 x 1536 -> 716 5.8 / 4.6 us); two and not four from 17 to 47 words (0.96); and fewer where rows are long and many, as each
       // of the fewer groups of features reads them again: from 29 words and a row for twelve features on 0.72 to 1.06 of the
-      // time, mean 0.92, 343 x 7424 -> 95 5.5 us in pairs of rows, 7.6 in fours; else 0.95 to 1.14, mean 1.00.)
-      if (cost < best || (cost == best && r < rm_log && fewer_rows)) best = cost, rm_log = r, cols_log = c;
+      // time, mean 0.92, 343 x 7424 -> 95 5.5 us in pairs of rows, 7.6 in fours; else 0.95 to 1.14, mean 1.01.)
+      const bool fewer = rm_log == 3 || (rm_log == 2 && Kw > 16 && Kw < 48) || long_and_many;
+      if (cost < best || (cost == best && r < rm_log && fewer)) best = cost, rm_log = r, cols_log = c;
     }
   }
   // Level with two launches at about 320 KB (8 x 9216 -> 4096, 256 KB: 6.0 against 7.4 us; 767 x 3740 -> 124,

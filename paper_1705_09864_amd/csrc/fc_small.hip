@@ -304,12 +304,13 @@ bool launch_fc_small(const float* x, int64_t ldx, const uint64_t* Wp, int64_t ld
   // to themselves, and the general path's one or two tiles take a chain as long (2 x 65536 -> 16: 7.0
   // against 13.3 us).  Eight rows a workgroup, of 489 layers: 256 to 320 KB in more than a round of workgroups the two launches take 0.86 to
   // 0.96 of this form's time as calls, 0.77 to 0.88 in a graph; in one round 0.88 to 1.17 as calls, 0.84 to 0.97 in a graph, where the host's
-  // part is not paid on replay: the line is at 256 KB for both.  (Fewer rows: 1.0 and more, 568 x 7217 -> 64 7.2 / 9.1.)
+  // part is not paid on replay: the line is at 256 KB for both.  Four rows in a graph likewise where four lanes share a feature (168 x 2432 ->
+  // 1064 6.3 / 5.7), else level or this form ahead (568 x 7217 -> 64 7.2 / 9.1).
   const int rm = 1 << rm_log, cols = 1 << cols_log;
   const int64_t wgs = shift_up(batch, rm_log) * shift_up(out_features, cols_log);
   if (best > (wgs <= 32 ? 768 << 10 : 320 << 10)) return false;
-  if (best > 256 << 10 && wgs > 32 && rm == 8 && !shared && (wgs > 256 || capturing(s))) return false;
   const Lanes lanes = lanes_for(std::min(cols, out_features));
+  if (best > 256 << 10 && wgs > 32 && !shared && ((rm == 8 && wgs > 256) || ((rm == 8 || lanes.L == 4) && capturing(s)))) return false;
   const int64_t Kpad = lanes.padded;
   FcSmallParams p;
   p.x = x;

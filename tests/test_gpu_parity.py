@@ -256,7 +256,7 @@ def test_fc_small_layers_one_launch(batch, fin, fout):
 
 
 @pytest.mark.parametrize("batch,fin,fout,call,graph,static", [
-    (241, 3596, 440, True, True, True), (600, 600, 1400, True, False, True), (600, 512, 1400, True, True, True),  # one round of workgroups
+    (241, 3596, 440, True, True, True), (600, 600, 1400, True, False, True), (600, 512, 1400, True, True, True), (168, 2432, 1064, True, False, True),  # one round of workgroups
     (900, 127, 1900, False, False, True), (892, 318, 1100, True, True, True), (892, 322, 1130, False, False, True),  # several
     (2, 65536, 16, True, True, True), (1000, 130, 2000, False, False, False)])
 def test_fc_small_lines(batch, fin, fout, call, graph, static):

@@ -23,10 +23,10 @@
 // clocks a SIMD, what every wave repeats costs as much as what it shares.  Hence as few waves as do the work; sign bits
 // gathered by carries; the halo, the places of a patch's words and the first filter operands made under the fp32 loads; scales
 // requested with the filters; row constants read four at a time; results stored through a buffer that drops what is not part of them.
-// Measured, us in a graph, with sixteen waves and none of that / now: 7 x 130 x 29 x 27 -> 70 3x3/2 7.1 / 5.6, 4 x 64 x 11 x 13 -> 60
-// 3x3 5.05 / 3.9, 35 x 64 x 21 x 21 -> 40 1x1 4.9 / 3.65, 7 x 26 x 49 x 48 -> 68 3x3 8.0 / 6.5, 83 x 96 x 11 x 11 -> 115 1x1/2 5.3 / 4.2.
-// One launch against two, a call: 1 x 64 x 8 x 8 -> 64 1x1 3.8 / 7.9, 7 x 130 x 29 x 27 -> 70 3x3/2 5.6 / 8.1; 16 x 64 x 56 x 56 ->
-// 64 3x3 would take 12 / 8.2 and stays with two.
+// Measured, us in a graph, with sixteen waves and none of that / now: 7 x 130 x 29 x 27 -> 70 3x3/2 6.85 / 5.14, 4 x 64 x 11 x 13 -> 60
+// 3x3 5.0 / 3.8, 35 x 64 x 21 x 21 -> 40 1x1 4.85 / 3.55, 7 x 26 x 49 x 48 -> 68 3x3 7.8 / 6.0, 83 x 96 x 11 x 11 -> 115 1x1/2 5.1 / 3.9.
+// One launch against two, a call: 1 x 64 x 8 x 8 -> 64 1x1 3.5 / 6.4, 7 x 130 x 29 x 27 -> 70 3x3/2 5.3 / 7.6 (in a graph 3.1 / 4.1
+// and 5.1 / 5.6); 16 x 64 x 56 x 56 -> 64 3x3 would take 9.4 / 8.3 and stays with two.
 #include <algorithm>
 #include <type_traits>
 
@@ -249,7 +249,7 @@ conv_one_kernel(const ConvOneParams p) {
         for (int j = 0; j < 4; ++j) x[j] = 4 * i + j < p.K ? x[j] : 0u;
       }
       if (i + 1 < last) read(i + 1);
-      // (without block scales, which cost the issue of an MFMA 6 clocks of 17: 7 x 130 x 29 x 27 5.30 -> 5.20 us)
+      // (without block scales, which cost the issue of an MFMA 6 clocks of 17: 0.98 of the time of 7 x 130 x 29 x 27 -> 70)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen(ef[j]), widen(expand_pixel(x[j])), acc, 4, 4, 0, 0, 0, 0);
@@ -432,8 +432,8 @@ bool launch_conv_one(const float* x, int N, int C, int H, int W, const uint64_t*
   p.items = p.bands * N;
   // As few waves as do it: one for every four items of the pack and one for every unit or part of one.  A wave costs its CU the
   // instructions ahead of its loads, and a SIMD issues one scalar instruction in four clocks: of sixteen waves the last has
-  // its loads out 3000 clocks after the first has (6 x 64 x 11 x 11 -> 398 1x1 5.65 us with sixteen, 3.9 with four; 7 x 130 x 29 x 27 -> 70
-  // 3x3/2 5.74 and 5.38).
+  // its loads out 3000 clocks after the first has (6 x 64 x 11 x 11 -> 398 1x1 in four waves 0.69 of the time in sixteen; 7 x 130 x 29
+  // x 27 -> 70 3x3/2 in eight 0.94).
   const int items_max = (int)(ceil_div((int64_t)std::min((rows - 1) * stride + KH, H) * W, 64) * p.quarters);
   p.waves = std::min(kWaves, (std::max((items_max + 3) / 4, units_max * parts) + 3) / 4 * 4);
   const dim3 grid((unsigned)ceil_div(p.items, 8) * 8, (unsigned)ceil_div(tiles, share));

@@ -631,8 +631,9 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   // In a graph the host's part is not paid on replay, and the lines stand lower: where the GPU's part of both forms is level over 900
   // products of 14 to 64 steps, rows of whole lines or not (a tile reads its own rows, each for itself).  There the choice by them is
   // 1.5 % behind the better form, by the lines for calls 4.1 % (287 x 256 x 789 of 2 x 1 bits: one launch 6.9 us, two 5.5).
+  // (Up to four steps of K over many tiles stay: two launches 1.03 to 1.05, 1125 x 1216 x 128 of 8 x 1 bits 7.8 / 8.8.)
   const bool ragged = (lda | ldw) % 32 != 0;
-  const int64_t graph_steps = !small      ? (t32 > 256 ? 18 : t32 > 128 ? (ragged ? 18 : 22) : (ragged ? 22 : 28))
+  const int64_t graph_steps = !small      ? (t32 > 256 ? (K <= 128 ? 24 : 18) : t32 > 128 ? (ragged ? 18 : 22) : (ragged ? 22 : 28))
                               : halves    ? std::max<int64_t>(24, 46 - t16 / (ragged ? 5 : 8))
                                           : (ragged && t16 > 64 ? 38 : 44);
   if (steps > graph_steps && capturing(s)) return false;

@@ -726,7 +726,7 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
     (90, 60, 2689, 2, 2, True, False), (241, 256, 1536, 2, 1, True, True), (241, 256, 1537, 2, 1, True, False), (287, 256, 704, 2, 1, True, True),
     (287, 256, 705, 2, 1, True, False), (287, 256, 896, 2, 1, True, True), (287, 256, 928, 2, 1, True, False), (500, 512, 704, 8, 2, True, True),
     (500, 512, 736, 8, 2, True, False), (500, 512, 576, 8, 2, True, True), (500, 512, 575, 8, 2, True, True), (500, 512, 577, 8, 2, True, False),
-    (600, 512, 288, 3, 3, True, True), (600, 512, 289, 3, 3, True, False)])
+    (600, 512, 288, 3, 3, True, True), (600, 512, 289, 3, 3, True, False), (1125, 1216, 128, 8, 1, True, True), (1125, 1216, 129, 8, 1, False, False)])
 def test_quant_one_launch_or_two(M, N, K, ba, bw, call, graph):
     """The lines between one launch and two, for calls and for calls that are being captured; replays between calls give what the
     calls give."""

@@ -20,8 +20,8 @@
 //   - The operands of the next plane of bits are made between the products of this one (sched_barrier: left to
 //     itself the compiler makes them all at once, and then multiplies with the vector ALU idle).
 //   - Two waves share every block of rows; each counts the bits of half its blocks.
-//   - Rows that start on any dword are fetched dword by dword (global_load_lds_dword), four times the loads of a
-//     sixth of the traffic, instead of through registers.
+//   - Rows may start on any dword, which is all that loads of 16 bytes need (dword by dword, four times the loads, 768 x 6619 x
+//     2240 took 15.4 us, now 12.3; 4224 x 4736 x 1600 23.1 / 22.4; 7934 x 1472 x 3008 19.7 / 18.3).
 //   - The convolution form gathers the im2col rows of 128 (256) pixels from the packed image, 16 bytes or a dword at a
 //     time, once for 128 (64) filters; where the patches start stands in LDS.  Its results are fp32, int32 or
 //     the next convolution's packed image, halo included.
@@ -33,7 +33,7 @@
 // zeros is a fifth faster.  The same launch back to back takes 178 us in the first millisecond, 244
 // in the fourth, 181 after 15 and 171 to 174 from 30 on; the clocks that it needs stay 361 thousand.
 // Measured, us a call, gemm_fp4.hip / here: 8192^3 202 / 173, 8192 x 8192 x 1024 75 / 50, 4096^3 33 / 28, 3008 x 1471
-// x 5184 25.6 / 23.1; rows on any dword: 4321 x 7134 x 3157 62 / 51, 1792 x 5234 x 832 17.9 / 13.3.  Convolutions of packed
+// x 5184 25.6 / 23.1.  Convolutions of packed
 // images: 11 x 320 x 49 x 49 -> 334, 3 x 3, 26.3 / 21.2, 40 x 192 x 28 x 28 -> 128, 5 x 5, 21.6 / 16.0; as packed bits, a channel pack of
 // the fp32 result behind them before: 26411 pixels, 334 filters, 45 words 33.2 / 20.1, 13500, 332, 72 24.0 / 17.6.
 #include <algorithm>
@@ -104,8 +104,8 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
 
 // WM x 4 / WM waves of TM x TN blocks of 32 x 32 each.  A stage holds blocks of 32 rows x 64 bytes, A's, then B's, in the
 // layout of gemm_fp4.hip: piece c of row r of a block at 16-byte place 64 (r / 16) + 4 (r % 16) + (c xor ((r / 2) & 3)).
-// LW: bytes a lane fetches per load: 16 where rows start 16-byte aligned (convolution form: where the image has an even
-// number of channel words), else 4.
+// LW: bytes a lane fetches per load: 16, and 4 where rows are less than that and not that far apart, or (convolution form) the image
+// has an odd number of channel words.
 template <int WM, int TM, int TN, int OUT, int LW, bool CONV>
 __global__ void __launch_bounds__(256, TM * TN >= 8 ? 2 : 3)
 gemm_fp4_kernel(const BlockParams p) {
@@ -140,7 +140,13 @@ gemm_fp4_kernel(const BlockParams p) {
   const int piece16 = (lane & 3) ^ ((lane >> 3) & 3);
   const int dw4[2] = {4 * (((lane & 15) >> 2) ^ (lane >> 5)) + (lane & 3), 4 * (((lane & 15) >> 2) ^ (2 + (lane >> 5))) + (lane & 3)};
   const int last0 = 16 * (p.nseg - 1) - (p.Kd - 1);
-  const uint32_t sub16 = last0 + 4 * piece16 > 0 ? 16u * piece16 : 0u;
+  // (Rows of a product: a piece that the row ends in, and those behind it, are the row's last 16 bytes: nothing behind a row is read,
+  // which may be where the buffer ends.  That is up to 12 bytes in front of the segment: the base is 16 lower there, so that no offset
+  // is negative.  Rows of less than 16 bytes are whole pieces, which their stride holds, and filters of a convolution have them too.)
+  constexpr uint32_t kLower = CONV || LW == 4 ? 0u : 16u;
+  const bool part_pieces = !CONV && LW == 16 && p.Kd >= 4;
+  const uint32_t sub16 = CONV ? (last0 + 4 * piece16 > 0 ? 16u * piece16 : 0u)
+                              : 4u * (uint32_t)max(last0 + 4 * piece16 + (p.Kd < 4 ? p.Kd - 1 : 3), 0) - kLower;
   const uint32_t sub4[2] = {last0 + dw4[0] > 0 ? 4u * (last0 + dw4[0]) : 0u, last0 + dw4[1] > 0 ? 4u * (last0 + dw4[1]) : 0u};
   // offset of the lane's first load of each half block in segment 0 (LW 4: of its first two loads; the other two are eight rows on)
   uint32_t va[HA][2], vb[CONV ? 1 : HB][2];
@@ -202,13 +208,14 @@ gemm_fp4_kernel(const BlockParams p) {
   auto issue = [&](int seg, int buf) {
     const bool last = tail && seg + 1 == p.nseg;
     const uint32_t to = lds0 + (uint32_t)(buf * kStage) * 16u;
+    const int64_t at_seg = (int64_t)seg * 64 - (last ? kLower : 0u);
 #pragma unroll
     for (int k = 0; k < HA; ++k)
-      load_rows(to + 1024u * (uint32_t)(wave * HA + k), p.A + (uint32_t)seg * 64u, va[k], LWA, p.lda, p.M, last);
+      load_rows(to + 1024u * (uint32_t)(wave * HA + k), p.A + at_seg, va[k], LWA, p.lda, p.M, last);
     const uint32_t tob = to + 2048u * NBA + 1024u * (uint32_t)(wave * HB);
     if constexpr (!CONV) {
 #pragma unroll
-      for (int k = 0; k < HB; ++k) load_rows(tob + 1024u * k, p.B + (uint32_t)seg * 64u, vb[k], LW, p.ldb, p.N, last);
+      for (int k = 0; k < HB; ++k) load_rows(tob + 1024u * k, p.B + at_seg, vb[k], LW, p.ldb, p.N, last);
     } else if constexpr (LW == 16) {
       const uint32_t d = 16u * (uint32_t)seg + 4u * piece16;
       const uint32_t at = in_patch(d < (uint32_t)p.Kd ? d : 16u * (uint32_t)seg);
@@ -225,13 +232,15 @@ gemm_fp4_kernel(const BlockParams p) {
           load4(tob + 1024u * k + 256u * u, p.B, patch[16 * (wave * HB + k) + 4 * u + (lane >> 4)] + at[u & 1]);
     }
   };
-  // What the loads left behind the row's last dword counts as zero.
+  // What the loads left behind the row's last dword counts as zero; of a piece that the row ends in (sub16), what stands in front of
+  // its last dwords, which the piece before it has.
   auto zero_tail = [&](int buf) {
     u_alias* const d = (u_alias*)(lds + buf * kStage);
-    const int valid = p.Kd & 15;
+    const int valid = p.Kd & 15, rest = part_pieces ? valid & 3 : 0, part = valid - rest;
     for (int row = threadIdx.x; row < 32 * NB; row += 256) {
       const int base = (row >> 4) * 256 + (row & 15) * 16, x = (row >> 1) & 3;
-      for (int k = valid; k < 16; ++k) d[base + (((k >> 2) ^ x) << 2) + (k & 3)] = 0u;
+      for (int k = rest ? part : valid; k < 16; ++k)
+        if (rest == 0 || k < part + 4 - rest || k >= part + 4) d[base + (((k >> 2) ^ x) << 2) + (k & 3)] = 0u;
     }
   };
 
@@ -510,25 +519,16 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
                        hipError_t* err) {
   if (gemm_block == 1 || gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
   if (gemm_block == 0 && (gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band)) return false;
-  const bool any_dword = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15);
-  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(tiles, 256);
-  // Against gemm_fp4.hip, from 220 products of up to 8192 x 8192 x 8192 measured on both (us, there / here).  Rows that
-  // start on any dword pass through registers there: from where K is no longer divided over a CU's waves there, 512 tiles of 64 x 64
-  // (1216 x 1792 x 3264, 532 of them, 12.7 / 10.0; 6016 x 384 x 1600, 564, 9.3 / 7.5; 1216 x 1600 x 1984, 475, 7.8 / 8.5; 174 x
-  // 7865 x 4672, 369, 10.8 / 14.3).  Rows of an odd number of 32-bit words cross at the same count (90 products of 273 to 1160
-  // tiles: 2137 x 971 x 3163, 544, 14.4 / 12.3; 1032 x 1995 x 3995, 544, 15.9 / 12.8; 1142 x 1962 x 987, 558, 9.4 / 7.8; 1535 x
-  // 1317 x 3163, 504, 10.4 / 12.1; 1161 x 1608 x 2779, 494, 9.9 / 10.7).  Others: where there is a workgroup for
-  // every CU and no CU is given far more of them than another, or its SIMDs are there (6976 x 522 x 3840, 275 tiles on 256 CUs, 981
-  // of 64 x 64 on 1024 SIMDs, 13.1 / 17.1; 768 x 5952 x 7291, 282 and 1116, 25.1 / 23.4, but 8192 x 540 x 768 9.3 / 9.9; 5504 x 320 x 4956, 129 tiles and the K
-  // divided there, 11.3 / 13.1), and where K is long enough for the products to show in the
-  // time (4560 x 731 x 582 8.0 / 9.1).  With fp32 results, scaled behind there as the waves finish one by one, up to two
-  // workgroups a CU (512) are ahead from a K of 3500 on only (352 layers of 256 to 900 tiles: 1000 x 4000, 256 tiles, K 1600 8.2 /
-  // 8.9, 2304 8.7 / 9.3, 4096 11.1 / 11.4, 9216 18.8 / 18.7; 2048 x 2048, 256, 2304 level, 4096 11.1 / 10.8; 1100 x 3700, 261,
-  // 1600 11.5 / 12.0, 9216 29.0 / 28.5; 2300 x 2000, 288, 2304 12.8 / 13.7, 8192 26.5 / 26.5; 1042 x 5092, 360, 2560 13.0 / 13.8;
-  // 1500 x 4384, 420, 1792 10.2 / 10.8; 1520 x 4899, 468, 3328 16.9 / 16.7; 2452 x 3750, 600, 2304 18.8 / 17.3).  Int32 results of
-  // up to 1280 tiles of 64 x 64 and more than 33 words are that kernel's, which divides K over four waves there or has a wave for
-  // every SIMD (55 products of 769 to 1280, there / here: 0.96 to 0.75; 6719 x 704 x 4096, 1155, 11.9 / 15.7; 2176 x 1988 x 7808,
-  // 1088, 21.9 / 25.7), where it takes them: not with rows of C so far apart that its indices do not reach (2048 x 2560 x 4096, rows 1048576
+  // rows of less than 16 bytes that the next begins in: dword by dword
+  const bool short_rows = dwords < 4 && ((lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15));
+  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128);
+  const bool lines = ldc % 32 == 0 && (((uintptr_t)C_i32 | (uintptr_t)C_f32) & 127) == 0;
+  // Against gemm_fp4.hip, from 1243 products of 150 to 4000 tiles and 4 to 160 words, rows on any word (the time there over the time
+  // here, in a graph; the choice by this rule is 0.45 % off the best): to 512 tiles, two a CU, K is divided over a CU's waves there
+  // (150 to 255 tiles 0.87, 256 to 383 0.90, 384 to 511 0.95 of 8 to 19 words, 0.97 of 20 to 59, 0.99 of 60 to 119, 1.02 beyond).
+  // Beyond, the products have to outweigh the results' way out, which takes longer where rows of C are parts of lines and
+  // a tile of 64 x 64 is a better piece of it (whole lines: 8 to 19 words 0.98, 20 to 39 1.01, 40 on 1.04 to 1.12; parts: 0.87, 0.97,
+  // 1.04 to 1.12).  Results that kernel's 32-bit indices do not reach are this one's (2048 x 2560 x 4096, rows 1048576
   // apart, 15.1 here, 28.5 in gemm_mfma.hip, which would get them).
   // The larger of the two shapes (us as 128 x 128 / as 256 x 128, each held for 50 ms): its waves read LDS and expand less for a
   // product, which shows once the chip's power has settled, where the results leave in whole lines and fill many rounds:
@@ -538,11 +538,11 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // x 15000 x 9000 261 / 262.  Below 4096 tiles it depends on the last round: 8192 x 6144 x 8192 143 / 132, but 5120 x 5120 x 8192
   // 78 / 85, 6144 x 6144 x 4096 60.5 / 62.4, 7168 x 7168 x 4096 83.5 / 84.3 (in bursts 77 / 86); 8192 x 8192 x 1024 50 / 54.
   if (gemm_block == 0) {
-    if (any_dword) {
+    if (short_rows) {  // (the results are the time; up to here gemm_small.hip takes them)
       if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
-    } else if (tiles < 256 || K < 700 || (C_f32 && tiles <= 512 && K < 3500) ||
-               (C_i32 && ceil_div(M, 64) * ceil_div(N, 64) <= 1280 && K > 64 * 33 && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) ||
-               (10 * tiles < 7 * 256 * rounds && (K < 1500 || ceil_div(M, 64) * ceil_div(N, 64) <= 1024))) {
+    } else if (tiles < 256 || dwords < 22) {
+      return false;
+    } else if ((tiles <= (dwords >= 240 ? 384 : 512) || dwords < (lines ? 38 : 64)) && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) {
       return false;
     }
   }
@@ -565,16 +565,16 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.tot_mul = as_count ? 2.0f : 4.0f;
   p.C = C_i32 ? (void*)C_i32 : (void*)C_f32;
   p.ldc = (int)ldc;
-  p.nt = ldc % 32 == 0 && ((uintptr_t)p.C & 127) == 0;
+  p.nt = lines;
   p.HoWo = p.Wo = p.Ho = p.Hp = p.Wpp = p.Cw = p.stride = p.Nimg = 1;
   p.run = p.row_bytes = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   p.thr = nullptr;
   p.opad = p.oHp = p.oWp = p.oCw = 0;
-  const bool large = !any_dword && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt);
+  const bool large = !short_rows && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt);
   using namespace block;
   if (large) *err = C_i32 ? go<2, 4, 2, kI32, 16, false>(p, s) : go<2, 4, 2, kF32, 16, false>(p, s);
-  else if (any_dword) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);
+  else if (short_rows) *err = C_i32 ? go<2, 2, 2, kI32, 4, false>(p, s) : go<2, 2, 2, kF32, 4, false>(p, s);
   else *err = C_i32 ? go<2, 2, 2, kI32, 16, false>(p, s) : go<2, 2, 2, kF32, 16, false>(p, s);
   return true;
 }

@@ -25,7 +25,9 @@
 //     covers 16 rows x 64 bytes, 4 lanes per row: whole 64-byte runs, so the memory pipeline
 //     works at its coalesced rate, where the MFMA layout (lane = row) costs an access per lane.
 //     Which 16-byte piece a lane fetches is permuted (piece = slot xor ((row >> 1) & 3)), so
-//     that the MFMA-layout reads, lane (r, h) <- piece 2 g + h of row r, fall on all banks.
+//     that the MFMA-layout reads, lane (r, h) <- piece 2 g + h of row r, fall on all banks.  Rows may start on any
+//     dword: these loads need no more (rows of an odd number of words went through registers once: 2947 x 6975 x 2624
+//     as packed bits 48.5 -> 39.2 us, 3318 x 778 x 3264, fp32, 12.3 -> 9.2, 2212 x 2496 x 1472 of 32-bit words 9.9 -> 8.7).
 //   - A wave owns its staging area and its range of K: no barrier in the main loop.  The words
 //     of a 64-byte segment are read into registers, the next segment's loads are issued into
 //     the same area once those reads have completed, and the 32 MFMAs of the segment run with
@@ -68,7 +70,7 @@ typedef uint8_t u8_alias __attribute__((may_alias));
 struct Fp4Params {
   const void* A;  // [M * PL][lda] words (plane pl of row m is row m * PL + pl), tail bits zero
   const void* B;  // [N][ldb] words
-  uint32_t lda_bytes, ldb_bytes;  // row strides, multiples of 16 (REG: of 4)
+  uint32_t lda_bytes, ldb_bytes;  // row strides, multiples of 4
   int M, N, Kw, Kreal;            // Kw data words per row
   int g_base, g_rem;  // groups of four words (256 bits = the K of four MFMAs) per wave: g_base, the first g_rem waves one more
   int tiles_m, tiles_n, tiles_per_xcd;
@@ -97,7 +99,7 @@ struct Fp4Params {
   // packed bits of the convolution form: the next convolution's image (C_bits, 64-bit words), its size, words per pixel, halo;
   // thr is per row m
   int Nimg, Ho, opad, oHp, oWp, oCw;
-  int Kd;  // REG 2: data dwords per row (2 Kw, or one less)
+  int Kd;  // data dwords per row (2 Kw, or one less)
 };
 
 // One nibble plane of four words of bits as the four operand dwords of one MFMA: bit 4 i + n of a dword in nibble i, worth 0.5, 1 or
@@ -151,69 +153,74 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
 template <int NA, int NB, bool CONV>
 __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, const uint32_t* voff /* [NB][2] */,
                                               int piece0, int piece1, int seg) {
+  if constexpr (!CONV) {
+    // A piece that the row ends in, and those behind it, are the row's last 16 bytes: nothing behind a row is read, which may be where
+    // the buffer ends (rows of less are 16 bytes apart).  Up to 12 bytes in front of the segment, so the segment's place is in the
+    // lane's offset there, not in the base: an offset below zero would be one of 4 GB.
+    auto load = [&](uint32_t base, uint32_t add0, uint32_t add1) {
+#pragma unroll
+      for (int b = NB - 1; b >= 0; --b)  // (B first: its rows are the ones that come from far away)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          __builtin_amdgcn_global_load_lds((b < NA ? (const char*)p.A : (const char*)p.B) + base + (voff[2 * b + t] + (t ? add1 : add0)),
+                                           (lds_ptr)(dst + b * 128 + t * 64), 16, 0, 0);
+    };
+    if (16 * seg + 16 > p.Kd) {
+      auto add = [&](int pc) { return (uint32_t)min(64 * seg, 4 * (max(p.Kd, 4) - 4 * pc - 4)); };
+      load(0u, add(piece0), add(piece1));
+    } else {
+      load((uint32_t)seg * 64u, 0u, 0u);
+    }
+    return;
+  }
   const char* abase = (const char*)p.A + (uint32_t)seg * 64u;
-  const char* bbase = (const char*)p.B + (CONV ? 0u : (uint32_t)seg * 64u);
   const bool tail = 8 * seg + 8 > p.Kw;  // the row ends inside this segment
   uint32_t boff[2] = {0u, 0u};
-  if (CONV) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      // piece c of the im2col row: run c / run_pieces (a kernel row), piece c % run_pieces of it; a
-      // piece beyond the row's last is not fetched (the reader zeroes it): its lane repeats the
-      // segment's first piece, which always exists
-      uint32_t c = 4u * (uint32_t)seg + (uint32_t)(t ? piece1 : piece0);
-      if (c >= p.npieces) c = 4u * (uint32_t)seg;
-      const uint32_t run = fast_div(c, p.div_run);
-      boff[t] = run * p.row_bytes + (c - run * p.run_pieces) * 16u;
-    }
+  for (int t = 0; t < 2; ++t) {
+    // piece c of the im2col row: run c / run_pieces (a kernel row), piece c % run_pieces of it; a
+    // piece beyond the row's last is not fetched (the reader zeroes it): its lane repeats the
+    // segment's first piece, which always exists
+    uint32_t c = 4u * (uint32_t)seg + (uint32_t)(t ? piece1 : piece0);
+    if (c >= p.npieces) c = 4u * (uint32_t)seg;
+    const uint32_t run = fast_div(c, p.div_run);
+    boff[t] = run * p.row_bytes + (c - run * p.run_pieces) * 16u;
   }
 #pragma unroll
-  for (int b = NB - 1; b >= 0; --b)  // (B first: its rows are the ones that come from far away)
+  for (int b = NB - 1; b >= 0; --b)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int pc = t ? piece1 : piece0;
       uint32_t off = voff[2 * b + t];
-      if (CONV && b >= NA) off += boff[t];
-      // (plain rows) a piece that starts beyond the row's last word: repeat the segment's first
+      if (b >= NA) off += boff[t];
+      // (filters) a piece that starts beyond the row's last word: repeat the segment's first
       else if (tail && 8 * seg + 2 * pc >= p.Kw) off -= 16u * pc;
-      __builtin_amdgcn_global_load_lds((b < NA ? abase : bbase) + off, (lds_ptr)(dst + b * 128 + t * 64), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((b < NA ? abase : (const char*)p.B) + off, (lds_ptr)(dst + b * 128 + t * 64), 16, 0, 0);
     }
 }
 
-// The same segment through registers, for rows that start 8-byte or 4-byte aligned only (an odd number
-// of words or dwords per row) and for images whose 16-byte pieces are not contiguous (an odd number of channel words):
-// the load unit writes LDS from 16-byte aligned addresses, an ordinary 16-byte load needs 4.  The words
-// go to the same places of the staging area when the wave gets to the segment.
-
-template <int NA, int NB, bool CONV, bool DWORDS>
+// The same segment of a convolution through registers, for images whose 16-byte pieces are not contiguous (an odd number of channel
+// words).  The words go to the same places of the staging area when the wave gets to the segment.
+template <int NA, int NB>
 __device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB][2], const uint32_t (&voff)[NB][2],
                                               int piece0, int piece1, int seg) {
-  const bool tail = DWORDS ? 16 * seg + 16 > p.Kd : 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
+  const bool tail = 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
 #pragma unroll
   for (int b = NB - 1; b >= 0; --b)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int pc = t ? piece1 : piece0;
       const char* base = b < NA ? (const char*)p.A : (const char*)p.B;
-      if (!(CONV && b >= NA) && !tail) {
+      if (b < NA && !tail) {
         const v4u_any v = *(const v4u_any*)(base + (uint32_t)seg * 64u + voff[b][t]);
         nx[b][t] = make_uint4(v[0], v[1], v[2], v[3]);
-      } else if constexpr (DWORDS) {  // dword by dword; those past the row are zero
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = 16 * seg + 4 * pc + e;
-          w[e] = *(const uint32_t*)(base + (voff[b][t] - 16u * pc + (uint32_t)min(k, p.Kd - 1) * 4u));
-          if (k >= p.Kd) w[e] = 0u;
-        }
-        nx[b][t] = make_uint4(w[0], w[1], w[2], w[3]);
       } else {  // word by word; words past the row repeat its last (the reader zeroes them)
         uint64_t w[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const uint32_t k = (uint32_t)min(8 * seg + 2 * pc + e, p.Kw - 1);
           uint32_t off;
-          if (CONV && b >= NA) {
+          if (b >= NA) {
             const uint32_t run = fast_div(k, p.div_run);
             off = voff[b][t] + run * p.row_bytes + (k - run * p.run_pieces) * 8u;
           } else {
@@ -303,10 +310,10 @@ constexpr int slot_size(int pl, bool split, bool half) { return std::max((TM * p
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
 // HALF: the partial tiles of a split cross LDS as pairs of 16-bit whole numbers (full sums up to 65535,
 // which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
-// segments travel through registers (see fetch_segment; 2: rows that start on any dword).
+// its segments travel through registers (see fetch_segment).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
-template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
 __global__ void __launch_bounds__(512)
 gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #ifdef BMX_FP4_STAMPS
@@ -421,7 +428,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 
   uint4 nx[NB][2];  // REG: the next segment's words
   if (seg_lo < seg_hi) {
-    if constexpr (REG) fetch_segment<NA, NB, CONV, REG == 2>(p, nx, voff, piece[0], piece[1], seg_lo);
+    if constexpr (REG) fetch_segment<NA, NB>(p, nx, voff, piece[0], piece[1], seg_lo);
     else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
   }
   if constexpr (CONV && OUT == kOutBits) {
@@ -462,7 +469,22 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int g = 0; g < 2; ++g) w[b][g] = stage[b * 128 + rd[g]];
-    if (8 * seg + 8 > p.Kw) {  // last segment of a row that ends inside it: words past the row are zero
+    if (!CONV && 16 * seg + 16 > p.Kd) {  // last segment of a row that ends inside it (see issue_segment): what stands in front of a
+                                           // part piece's dwords, and all past the row, is zero
+      const bool back = p.Kd >= 4;         // (in a row of less than a piece, what stands behind them)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int left = p.Kd - (16 * seg + 4 * (2 * g + h));  // dwords of this lane's piece
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          if (left < (back ? 4 : 1)) w[b][g].x = 0;
+          if (left < (back ? 3 : 2)) w[b][g].y = 0;
+          if (left < (back ? 2 : 3)) w[b][g].z = 0;
+          if (left < (back ? 1 : 4)) w[b][g].w = 0;
+        }
+      }
+    }
+    if (CONV && 8 * seg + 8 > p.Kw) {  // words past the row are zero
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         const int left = p.Kw - (8 * seg + 2 * (2 * g + h));  // valid words of this lane's piece
@@ -488,7 +510,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     if (seg == seg_lo) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); FP4_STAMP(2); }
 #endif
     if (seg + 1 < seg_hi) {
-      if constexpr (REG) fetch_segment<NA, NB, CONV, REG == 2>(p, nx, voff, piece[0], piece[1], seg + 1);
+      if constexpr (REG) fetch_segment<NA, NB>(p, nx, voff, piece[0], piece[1], seg + 1);
       else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1);
     }
 #pragma unroll
@@ -870,7 +892,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 int gemm_fp4_half = 0;  // 2 = keep fp32 partials (tests of both forms)
 namespace {
 
-template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, int REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   const int waves = SPLIT ? S : tiles_per_wg;
   const size_t lds = (size_t)waves * slot_size(PL, SPLIT, HALF) * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
@@ -910,7 +932,7 @@ void set_tile_order(Fp4Params& p, int S) {
 // A full sum is at most (bits of K) x (2^planes - 1), a full count K: whether 16 bits hold them
 bool fits_16_bits(int64_t K, int planes) { return K * ((1 << planes) - 1) <= 65535; }
 
-template <int PL, bool XNOR, int OUT, bool CONV = false, int REG = 0>
+template <int PL, bool XNOR, int OUT, bool CONV = false, bool REG = false>
 hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   if (S <= 1) return launch_tile<PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
   return fits_16_bits(p.Kreal, PL) && gemm_fp4_half != 2 ? launch_tile<PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s)
@@ -925,28 +947,28 @@ int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests
 // of few words since (the mean of the time over the best; graph times):
 //   - eight where each has a share of two groups, up to a tile a CU (256): 61 words on (8 / 4 waves, 64 to 256 tiles: 62
 //     words 0.96 to 0.97, 64 0.96, 66 0.97 to 1.01, 70 0.94, 74 0.97 to 1.02, 80 0.94 to 0.98; a whole layer of 256 tiles and 64
-//     words 7.25 / 7.57 us; rows through registers 1.00 / 1.14).  Of fewer groups six or seven waves would be left of them, which four
-//     beat (rows through registers, 50 to 60 words 1.07 / 1.00, bit planes 1.03 / 1.00).  The patches of a convolution, whose latency
+//     words 7.25 / 7.57 us).  Of fewer groups six or seven waves would be left of them, which four
+//     beat (bit planes 1.03 / 1.00).  The patches of a convolution, whose latency
 //     more waves hide, always eight (1.03 / 1.08 for four, 1.9 for one).
 //   - four where each has two groups, 29 words on, up to three tiles a CU (257 to 512 tiles 1.25 / 1.00 / 1.44 for 8 / 4 / 1; 513 to
 //     768 1.4 / 1.00 / 1.15; of 29 to 33 words 1.00 / 1.20, 4 / 1), and with more than one, but few, for some SIMDs (1025 to 1280: 1.45 /
-//     1.00 / 1.19; rows through registers of less than 34 words 1.02 / 1.00, 4 / 1, beyond 768: one).  Between them a SIMD has at most one
+//     1.00 / 1.19).  Between them a SIMD has at most one
 //     undivided tile: one wave (1.5 / 1.03 / 1.00; four over one of 75 to 144 words 1.04 over 37 int32 products, 1.05 over 166 of
 //     fp32).  Four and eight keep the SIMDs of a CU level where it has several tiles (390 x 3329 x 5632, 371 tiles, takes 10.4 us over four
 //     waves, 15.1 over five, 12.2 over three).
 //     Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09), and from 2049 to 2350 (- / 1.01 / 1.10; between, - /
 //     1.09 / 1.04).
-//   - three of 21 to 28 words (six or seven groups), up to two tiles a CU (3 / 2 / 1 waves, to 256 tiles 1.00 / 1.14 / 1.17, to 512 rows
-//     through registers 1.00 / 1.16 / 1.15, bit planes 1.00 / 1.08 / 1.11, direct rows 1.03 / 1.20 / 1.01; beyond, all 1.2 / 1.2 / 1.00).  Five
+//   - three of 21 to 28 words (six or seven groups), up to two tiles a CU (3 / 2 / 1 waves, to 256 tiles 1.00 / 1.14 / 1.17, to 512
+//     bit planes 1.00 / 1.08 / 1.11, others 1.03 / 1.20 / 1.01; beyond, all 1.2 / 1.2 / 1.00).  Five
 //     groups, 20 words, are not worth dividing (2 / 1 1.03 / 1.01 to 256 tiles, 1.24 / 1.00 to 512).
-enum class Rows { direct, registers, planes, patches };
+enum class Rows { direct, planes, patches };
 static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
   const bool patches = rows == Rows::patches;
   if (kwords < 21 && !patches) return 1;
   if (tiles <= 256 && (kwords >= 61 || patches)) return 8;
   if (kwords < 29 && !patches) return tiles <= 512 ? 3 : 1;
   if (tiles <= 512) return 4;
-  if (kwords < 34 && (patches || (rows == Rows::registers && tiles > 768))) return 1;
+  if (kwords < 34 && patches) return 1;
   if (kwords >= 75 && patches) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
   if (tiles <= 768 || (tiles > 1024 && tiles <= 1280)) return 4;
   return 1;
@@ -971,12 +993,9 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
                      hipError_t* err) {
   if (gemm_engine == 1 || gemm_engine == 2 || gemm_engine == 4) return false;
   if (planes < 1 || planes > 2) return false;
-  // rows that do not start 16-byte aligned travel through registers (xnor products only: a k-bit
-  // product's operands are the library's own rows)
-  const bool reg = (lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15) || (dwords & 1);
-  // (rows of 32-bit words where that shows: their own form, int32 results only)
-  const bool odd_dwords = (lda_bytes & 7) || (ldb_bytes & 7) || ((uintptr_t)A & 7) || ((uintptr_t)B & 7) || (dwords & 1);
-  if (reg && (rowsum || (odd_dwords && (!C_i32 || planes != 1)))) return false;
+  // rows are fetched 16 bytes at a time, the last 16 whole, and may start on any dword; shorter ones only where they are 16 bytes apart
+  const bool apart = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15);
+  if (dwords < 4 && !apart) return false;
   if ((int64_t)K * ((1 << planes) - 1) >= ((int64_t)1 << 24)) return false;
   if (!fp4_addresses(M, N, planes, lda_bytes, ldb_bytes, ldc, C_bits != nullptr)) return false;
   const int tiles_m = (int)ceil_div(M, 64), tiles_n = (int)ceil_div(N, 64);
@@ -1011,7 +1030,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.run_pieces = p.row_bytes = p.npieces = 1;
   p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
-  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? Rows::planes : reg ? Rows::registers : Rows::direct);
+  int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? Rows::planes : Rows::direct);
   S = S > 8 ? 8 : S;
   if (S > ngroups / 2) S = ngroups / 2;
   if (S < 1) S = 1;
@@ -1022,12 +1041,7 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (reg) {
-    if (odd_dwords) *err = launch_split<1, true, kOutI32, false, 2>(p, S, tiles_per_wg, blocks, s);
-    else if (C_bits) *err = launch_split<1, true, kOutBits, false, 1>(p, S, tiles_per_wg, blocks, s);
-    else if (C_i32) *err = launch_split<1, true, kOutI32, false, 1>(p, S, tiles_per_wg, blocks, s);
-    else *err = launch_split<1, true, kOutF32, false, 1>(p, S, tiles_per_wg, blocks, s);
-  } else if (planes == 1 && rowsum == nullptr) {
+  if (planes == 1 && rowsum == nullptr) {
     if (C_bits) *err = launch_split<1, true, kOutBits>(p, S, tiles_per_wg, blocks, s);
     else if (C_i32) *err = launch_split<1, true, kOutI32>(p, S, tiles_per_wg, blocks, s);
     else *err = launch_split<1, true, kOutF32>(p, S, tiles_per_wg, blocks, s);
@@ -1118,10 +1132,10 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (out_bits) *err = reg ? launch_split<1, true, kOutBits, true, 1>(p, S, tiles_per_wg, blocks, s)
+  if (out_bits) *err = reg ? launch_split<1, true, kOutBits, true, true>(p, S, tiles_per_wg, blocks, s)
                            : launch_split<1, true, kOutBits, true>(p, S, tiles_per_wg, blocks, s);
-  else if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, 1>(p, S, tiles_per_wg, blocks, s);
-  else if (reg) *err = launch_split<1, true, kOutF32, true, 1>(p, S, tiles_per_wg, blocks, s);
+  else if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, true>(p, S, tiles_per_wg, blocks, s);
+  else if (reg) *err = launch_split<1, true, kOutF32, true, true>(p, S, tiles_per_wg, blocks, s);
   else if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
   else *err = launch_split<1, true, kOutF32, true>(p, S, tiles_per_wg, blocks, s);
   return true;

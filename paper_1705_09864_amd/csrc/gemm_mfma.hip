@@ -572,12 +572,8 @@ bool launch_xnor_gemm_dwords(const uint32_t* A, int64_t lda_dw, const uint32_t* 
   return launch_gemm_small(A, lda_dw * 4, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, nullptr, nullptr, ldc, false, s,
                            err) ||
          launch_gemm_block(A, lda_dw * 4, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, ldc, false, s, err) ||
-         // (its loads pass registers here, which costs a large product more than widening the operands where K is not divided
-         // over a CU's waves: 3000 x 3000 x 2500 26.9 us a call as it is, 24.9 with the two passes; 2000 x 2000 x 1500 11.0 / 13.3.
-         // To 512 tiles K is: 64 x 32000 x 7003 16.8 / 32.1, 2504 x 672 x 7963 14.7 / 20.3, 900 x 1500 x 29979 31.7 / 40.5.)
-         (((double)M * N * K < 1.2e10 || ceil_div(M, 64) * ceil_div(N, 64) <= 512) &&
-          launch_gemm_fp4(A, lda_dw * 4, 1, nullptr, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, nullptr, nullptr, ldc,
-                          false, s, err));
+         launch_gemm_fp4(A, lda_dw * 4, 1, nullptr, B, ldb_dw * 4, M, N, K, dwords, nullptr, C, nullptr, nullptr, nullptr, ldc,
+                         false, s, err);
 }
 
 bool launch_xnor_gemm_mfma(const uint64_t* A, int64_t lda_w, const uint64_t* B, int64_t ldb_w, int M,

@@ -185,23 +185,23 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const int steps = (dwords + 7) / 8;
   // Against the kernels of 64 x 64 tiles and more, from 2500 products of 64 to 1300 such tiles and 1500 to 16000 tile steps of 32 x 32 x 256
   // (their time over this kernel's, in a graph).  Up to 28 words, where gemm_fp4_kernel does not divide K over four waves, up to 12288
-  // steps (8000 to 9000 1.10, 10000 to 13000 1.01 to 1.04, rows that pass through registers there 1.07 to 1.2).  Beyond, rows that travel to LDS
-  // there: below 128 of its tiles up to 8192 (7000 to 8000 1.09, then 0.92), to 255 up to 7000 (5000 to 7000 1.0 to 1.05, then 0.95 to
-  // 0.8), to 511 up to 8192 (0.99, then 0.88).  Rows that pass through registers: to 191 up to 9500 (9000 1.04; beyond 1.01), to 255 up
-  // to 8192 (7000 to 8000 1.0 to 1.1; beyond 0.98), to 511 up to 12288 (1.0 to 1.08).  From 512 tiles on 8192, where gemm_block.hip
-  // takes over rows that start on any dword (9000 to 12000 1.0 to 1.1); rows to LDS only where K is a single step (1.0; two and more
-  // 0.99 to 0.83), others, from 800 on, of one or two (1.02 to 1.2; three 0.97 to 1.03, more 0.92).
+  // steps (8000 to 9000 1.10, 10000 to 13000 1.01 to 1.04).  Beyond: below 128 of its tiles up to 8192 (7000 to 8000 1.09, then 0.92), to
+  // 255 up to 7000 (5000 to 7000 1.0 to 1.05, then 0.95 to 0.8), to 511 up to 8192 (0.99, then 0.88).
   // 12288 too where that kernel does not take the product; of a K of more than four steps for each of
   // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
+  // From 512 tiles of 64 x 64 on, where that kernel has work for most SIMDs (700 products of 200 to 1300 tiles, rows of any word): fp32
+  // results up to 699 tiles and three steps of K (1.04 to 1.07, then 0.94), of one step to 799 (1.03, then 0.95); int32 to 599 and two
+  // (1.03; three 0.99, beyond 0.95); packed bits all (1.2 to 1.6).
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
-  const bool direct = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15) && !(dwords & 1);
-  const bool pays = gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, C_bits != nullptr);
+  const bool apart = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15);  // (launch_gemm_fp4)
+  const bool pays = (dwords >= 4 || apart) && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, C_bits != nullptr);
   const int64_t most = steps > 64                                ? 2048
                        : !pays || (dwords <= 56 && tiles64 < 512) ? 12288
-                       : direct || tiles64 >= 512                 ? (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192)
-                                                                  : (tiles64 < 192 ? 9500 : tiles64 < 256 ? 8192 : 12288);
-  if (work > most || tiles > 4096) return false;
-  if (!C_bits && pays && (direct ? tiles64 >= 512 && steps > 1 : tiles64 >= 800 && steps > 2)) return false;
+                                                                  : (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192);
+  const int64_t below = C_bits ? 4097 : C_f32 ? (steps == 1 ? 800 : steps <= 3 ? 700 : 512) : (steps <= 2 ? 600 : 512);
+  // (packed bits of rows of less than 16 bytes have no other kernel of many tiles)
+  if ((work > most || tiles > 4096) && !(C_bits && dwords < 4 && !apart)) return false;
+  if (pays && tiles64 >= below) return false;
   int S = 1;
   while (S < 16 && 2 * S <= steps && 2 * S * tiles <= (work > 8192 ? 8192 : 4096)) S *= 2;
   SmallGemmParams p;

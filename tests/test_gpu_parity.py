@@ -1414,7 +1414,8 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
             Bd = np.full((N, ld), POISON, dtype=np.uint64); Bd[:, :w] = Bm
             a, b = dev(Ad.view(np.int64)), dev(Bd.view(np.int64))
             np.testing.assert_array_equal(B.xnor_gemm(a, b, K).cpu().numpy(), want)
-            assert "gemm_fp4_kernel<%s" % ("4,2,1,xnor,i32,block>" if form == 2 and ld % 2 == 0 else "2,2,1,xnor,i32,block") in B.last_kernel()
+            short = K <= 96 and ld % 2  # (rows of less than 16 bytes that the next begins in)
+            assert "gemm_fp4_kernel<%s" % ("4,2,1,xnor,i32,block>" if form == 2 and not short else "2,2,1,xnor,i32,block") in B.last_kernel()
             np.testing.assert_array_equal(2 * B.xnor_gemm(a, b, K, count=True).cpu().numpy() - K, want)
         dw = -(-K // 32)
         A32 = np.full(M * (dw + 1) + 1, 0xCDCDCDCD, dtype=np.uint32)
@@ -1423,7 +1424,7 @@ def test_gemm_fp4_block_form(form, M, N, K, pad):
         B32 = np.ascontiguousarray(Bm.view(np.uint32)[:, :dw])
         a32 = dev(A32.view(np.int32))[1:].view(M, dw + 1)
         np.testing.assert_array_equal(B.xnor_gemm_w32(a32, dev(B32.view(np.int32)), K).cpu().numpy(), want)
-        assert "gemm_fp4_kernel<2,2,1,xnor,i32,block of dwords>" in B.last_kernel()
+        assert "xnor,i32,block of dwords>" in B.last_kernel() if K <= 96 else "xnor,i32,block>" in B.last_kernel()
         x = rng.standard_normal((M, K)).astype(np.float32)
         wt = rng.uniform(-1, 1, (N, K)).astype(np.float32)
         alpha = rng.standard_normal(N).astype(np.float32)
@@ -1456,13 +1457,15 @@ def test_gemm_fp4_block_form_longest_k(form):
 
 
 @pytest.mark.parametrize("M,N,K,kind,block", [
-    # rows of an odd number of 32-bit words: from 513 tiles of 64 x 64 on
-    (1032, 1995, 3995, "w32", True), (2137, 971, 3163, "w32", True), (1142, 1962, 987, "w32", True),
+    # rows of an odd number of 32-bit words like others
+    (1032, 1995, 3995, "w32", False), (2137, 971, 3163, "w32", False), (1142, 1962, 987, "w32", False),
     (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False), (64, 32000, 7003, "w32", False), (900, 1500, 29979, "w32", False),
-    (129, 10300, 9003, "w32", False),
-    # fp32 results of up to 512 tiles of 128 x 128: from a K of 3500 on; past that whatever the K, and int32 results too
-    (2048, 2048, 3499, "f32", False), (2000, 2040, 3500, "f32", True), (1900, 2500, 1664, "f32", False),
-    (1900, 2500, 3584, "f32", True), (2041, 4090, 1664, "f32", False), (2690, 3130, 1664, "f32", True), (1900, 2500, 1664, "i32", True)])
+    (129, 10300, 9003, "w32", False), (2690, 3130, 2019, "w32", True),
+    # to 512 tiles of 128 x 128 never (384 from 240 dwords on); past that from 64 dwords on, where rows of results are whole lines from 38
+    (2048, 2048, 3499, "f32", False), (2000, 2040, 3500, "f32", False), (1900, 2500, 1664, "f32", False),
+    (1900, 2500, 3584, "f32", False), (2041, 4090, 1664, "f32", False), (2690, 3130, 1664, "f32", False), (1900, 2500, 1664, "i32", False),
+    (2041, 4090, 2048, "f32", False), (2053, 4090, 2048, "f32", True), (2053, 4090, 1984, "f32", False), (2053, 4064, 1280, "i32", True),
+    (2053, 4064, 1152, "i32", False), (2053, 3090, 7680, "i32", True), (2041, 3070, 7680, "i32", False), (2053, 3090, 7616, "i32", False)])
 def test_block_form_lines(M, N, K, kind, block):
     """Both sides of the lines between the kernel that stages rows once per workgroup and the 64 x 64 per wave kernel: the
     form that runs, and the same results from the other."""
@@ -1478,7 +1481,7 @@ def test_block_form_lines(M, N, K, kind, block):
         call = lambda: B.binary_fc_packed(A, K, W, alpha=alpha, mode=kind)  # noqa: E731
     got = call()
     assert ("block" in B.last_kernel()) == block, B.last_kernel()
-    assert kind != "w32" or block or ",reg>" in B.last_kernel(), B.last_kernel()  # (as they are, not widened)
+    assert "gemm_fp4_kernel" in B.last_kernel(), B.last_kernel()  # (as they are, not widened)
     with tuned(k19=1 if block else 3):
         want = call()
         assert ("block" in B.last_kernel()) != block, B.last_kernel()
@@ -1506,8 +1509,9 @@ def test_gemm_fp4_block_form_past_4_gib_of_results():
     A = torch.randint(-2 ** 62, 2 ** 62, (M, 12), device="cuda")[:, :11]
     Bm = torch.randint(-2 ** 62, 2 ** 62, (N, 12), device="cuda")[:, :11]
     for K in (704, 700):
-        got = B.xnor_gemm(A, Bm, K)
-        assert "block" in B.last_kernel()
+        with tuned(k19=3):
+            got = B.xnor_gemm(A, Bm, K)
+            assert "block" in B.last_kernel()
         with tuned(k7=1):
             want = B.xnor_gemm(A[-1000:], Bm, K)
         assert torch.equal(got[-1000:], want)
@@ -1612,11 +1616,11 @@ def test_gemm_fp4_largest_16_bit_sums(K, split):
 
 @pytest.mark.parametrize("tm,tn,words,split", [(16, 16, 18, 1), (16, 16, 20, 1), (16, 16, 21, 3), (16, 16, 28, 3), (16, 17, 20, 1), (16, 17, 23, 3),
                                                (16, 32, 28, 3), (16, 32, 27, 3), (19, 27, 27, 1), (16, 16, 29, 4), (16, 16, 60, 4), (16, 16, 59, 4),
-                                               (16, 16, 61, 8), (16, 32, 32, 4), (19, 27, 28, 1), (19, 27, 30, 4), (24, 32, 33, 4), (32, 33, 33, 1), (24, 32, 34, 4), (24, 33, 34, 1),
+                                               (16, 16, 61, 8), (16, 32, 32, 4), (19, 27, 28, 1), (19, 27, 30, 4), (24, 32, 33, 4), (32, 33, 33, 4), (24, 32, 34, 4), (24, 33, 34, 1),
                                                (24, 33, 76, 1), (32, 32, 98, 1), (32, 33, 34, 4), (32, 40, 34, 4), (32, 41, 34, 1)])
 def test_gemm_fp4_split_lines(tm, tn, words, split):
-    """Both sides of the lines between the waves that share a tile's K, by the tiles and words (an odd number of words: rows that pass
-    through registers); a last tile of one row and one column; the same results undivided."""
+    """Both sides of the lines between the waves that share a tile's K, by the tiles and words (an odd number of words: rows that start
+    on any word); a last tile of one row and one column; the same results undivided."""
     g = torch.Generator(device="cuda")
     g.manual_seed(tm * tn + words)
     A, W = (torch.randint(-2 ** 62, 2 ** 62, (64 * n - 63, words), device="cuda", generator=g) for n in (tm, tn))
@@ -1658,14 +1662,14 @@ def test_plane_gemm_split_lines(bits, words, split):
     np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(2 ** bits - 1))
 
 
-@pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, False), (1024, 4032, 2, True), (1024, 1024, 28, True),
+@pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, True), (1024, 4032, 2, False), (1024, 1024, 28, True),
                                              (1024, 960, 30, False), (1024, 1024, 32, True), (1024, 1024, 34, False), (512, 512, 126, True),
-                                             (512, 512, 130, False), (1024, 960, 32, False), (1024, 960, 31, True), (1024, 768, 46, False), (1024, 704, 47, True), (1024, 704, 53, False), (1024, 960, 39, False), (1024, 1024, 43, True),
+                                             (512, 512, 130, False), (1024, 960, 32, False), (1024, 960, 31, False), (1024, 768, 46, False), (1024, 704, 47, False), (1024, 704, 53, False), (1024, 960, 39, False), (1024, 1024, 43, False),
                                              (1024, 1024, 51, False), (1024, 1920, 24, True), (1024, 1920, 28, False),
-                                             (3200, 1024, 7, True), (3200, 1024, 9, False), (2560, 1024, 9, True)])
+                                             (3200, 1024, 7, False), (3200, 1024, 9, False), (2560, 1024, 9, False),
+                                             (2304, 1024, 8, True), (2304, 1024, 9, False), (2368, 1024, 8, True), (2432, 1024, 8, False)])
 def test_gemm_small_lines(M, N, words, small):
-    """Both sides of the lines between the kernel of 32 x 32 and those of larger tiles, for rows that these fetch 16 bytes at a time
-    (an even number of words) and for others; the same results from the popcount kernel."""
+    """Both sides of the lines between the kernel of 32 x 32 and those of larger tiles, rows of an even and of an odd number of words; the same results from the popcount kernel."""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + words)
     A, W = (torch.randint(-2 ** 62, 2 ** 62, (n, words), device="cuda", generator=g) for n in (M, N))
@@ -1734,7 +1738,7 @@ def test_conv_fp4_lds_staged_kernel(split):
 @pytest.mark.parametrize("M,N,K,off", [(512, 1024, 4096 - 64, 0), (700, 1900, 1, 0), (650, 2000, 129, 0), (520, 600, 64 * 49 - 3, 0),
                                        (1100, 1700, 64 * 7, 0), (640, 1300, 4096, 1), (333, 4001, 64 * 61, 1)])
 def test_gemm_fp4_rows_through_registers(M, N, K, off):
-    """Operand rows of an odd number of words, or an even number behind a base that is only 8-byte
+    """(Through registers they went once.)  Operand rows of an odd number of words, or an even number behind a base that is only 8-byte
     aligned, on the 64 x 64 per wave kernel: with and without a K split, K tails inside a segment,
     output rows that are whole 128-byte lines and that are not; int32, fp32 and packed bits."""
     rng = np.random.default_rng(M + N + K)
@@ -1750,12 +1754,43 @@ def test_gemm_fp4_rows_through_registers(M, N, K, off):
     ri, rf = oracle.binary_fc(a, w, alpha)
     with tuned(k7=5):
         np.testing.assert_array_equal(B.xnor_gemm(A, W, K).cpu().numpy(), ri)
-        assert "reg" in B.last_kernel()
+        assert "gemm_fp4_kernel" in B.last_kernel() or K <= 96  # (rows of less than 16 bytes stay with gemm_mfma.hip)
         np.testing.assert_array_equal(B.binary_fc_packed(A, K, W, alpha=dev(alpha)).cpu().numpy(), rf)
         bits = B.binary_fc_packed(A, K, W, alpha=dev(alpha), mode="bits", thr=dev(thr))
     ref = np.where(rf >= thr[None, :], np.float32(1), np.float32(-1))
     np.testing.assert_array_equal(bits.cpu().numpy(), B.binarize_pack(dev(ref), 1).cpu().numpy())
     np.testing.assert_array_equal(B.xnor_gemm(A, W, K, count=True).cpu().numpy(), (ri + K) // 2)
+
+
+@pytest.mark.parametrize("form", ["undivided", "divided", "block"])
+@pytest.mark.parametrize("dwords", list(range(4, 37)) + [95, 129, 160])
+def test_rows_on_any_dword_end_with_their_buffer(dwords, form):
+    """Rows of every length mod 16 dwords (a last segment of one to four pieces, the last one whole or of one to three dwords), as many
+    dwords apart and some more, from every dword of 16 bytes on, the last row's end the buffer's end: on the 64 x 64 per wave kernel, K
+    undivided and divided, and on the one that stages rows once per workgroup."""
+    K, M, N = 32 * dwords - dwords % 5, 70, 67
+    pins = {"undivided": dict(k7=5, k10=1), "divided": dict(k7=5, k10=4), "block": dict(k17=1, k19=2 + dwords % 2)}[form]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dwords)
+    mask = torch.full((dwords,), -1, dtype=torch.int32, device="cuda")
+    if K % 32:
+        mask[-1] = (1 << K % 32) - 1
+
+    def rows(n, apart, first):
+        flat = torch.randint(-2 ** 31, 2 ** 31, (first + (n - 1) * apart + dwords,), device="cuda", generator=g).to(torch.int32)
+        t = flat.as_strided((n, dwords), (apart, 1), first)
+        t &= mask
+        return t
+
+    def signs(t):
+        return ((t[:, :, None] >> torch.arange(32, device="cuda")) & 1).reshape(t.shape[0], -1)[:, :K].float() * 2 - 1
+
+    for first in range(4):
+        A, W = rows(M, dwords + dwords % 3, first), rows(N, dwords, 3 - first)
+        with tuned(**pins):
+            got = B.xnor_gemm_w32(A, W, K)
+            assert "gemm_fp4_kernel<" in B.last_kernel() and ("block" in B.last_kernel()) == (form == "block"), B.last_kernel()
+        assert torch.equal(got, (signs(A) @ signs(W).T).to(torch.int32))
 
 
 @pytest.mark.parametrize("word", [32, 64])
@@ -1785,7 +1820,7 @@ def test_gemm_small_and_rows_on_any_dword(M, N, K, off, word):
         assert ("gemm_small_kernel" in B.last_kernel()) != large
         with tuned(k19=1):  # (1100 x 2000 x 4000 is past the line from which the form of shared rows is ahead)
             np.testing.assert_array_equal(B.xnor_gemm_w32(A, W, K).cpu().numpy(), ri)
-            assert not large or words % 2 == 0 or "reg" in B.last_kernel()
+            assert not large or "gemm_fp4_kernel" in B.last_kernel()
         return
     np.testing.assert_array_equal(B.xnor_gemm(A, W, K).cpu().numpy(), ri)
     assert ("gemm_small_kernel" in B.last_kernel()) != large

@@ -191,14 +191,14 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
   // From 512 tiles of 64 x 64 on, where that kernel has work for most SIMDs (700 products of 200 to 1300 tiles, rows of any word): fp32
   // results up to 699 tiles and three steps of K (1.04 to 1.07, then 0.94), of one step to 799 (1.03, then 0.95); int32 to 599 and two
-  // (1.03; three 0.99, beyond 0.95); packed bits all (1.2 to 1.6).
+  // (1.03; three 0.99, beyond 0.95); packed bits not at all (0.91 at 512 to 0.72 at 1000), of one step only below 256 (1.02, 0.95).
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool apart = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15);  // (launch_gemm_fp4)
   const bool pays = (dwords >= 4 || apart) && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, C_bits != nullptr);
   const int64_t most = steps > 64                                ? 2048
                        : !pays || (dwords <= 56 && tiles64 < 512) ? 12288
                                                                   : (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192);
-  const int64_t below = C_bits ? 4097 : C_f32 ? (steps == 1 ? 800 : steps <= 3 ? 700 : 512) : (steps <= 2 ? 600 : 512);
+  const int64_t below = C_bits ? (steps == 1 ? 256 : 512) : C_f32 ? (steps == 1 ? 800 : steps <= 3 ? 700 : 512) : (steps <= 2 ? 600 : 512);
   // (packed bits of rows of less than 16 bytes have no other kernel of many tiles)
   if ((work > most || tiles > 4096) && !(C_bits && dwords < 4 && !apart)) return false;
   if (pays && tiles64 >= below) return false;

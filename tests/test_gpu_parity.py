@@ -1793,6 +1793,30 @@ def test_rows_on_any_dword_end_with_their_buffer(dwords, form):
         assert torch.equal(got, (signs(A) @ signs(W).T).to(torch.int32))
 
 
+@pytest.mark.parametrize("M,N,words", [(64, 64, 1), (63, 65, 2), (1, 4096, 3), (4096, 1, 5), (130, 191, 8), (129, 64, 33), (700, 1000, 11)])
+def test_gemm_fp4_bits_of_undivided_tiles(M, N, words):
+    """Packed decisions of a tile that one wave finishes, a word a row: tiles that end in every direction, columns past the last without
+    a bit, thresholds met exactly, infinities and NaN in scale and threshold; rows of the result further apart than their words."""
+    rng = np.random.default_rng(M + N + words)
+    K = 64 * words - (words > 1)
+    a, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    alpha = rng.choice([0.5, -0.25, 1.0, 0.0, np.inf, np.nan], N, p=[0.4, 0.2, 0.2, 0.1, 0.05, 0.05]).astype(np.float32)
+    thr = (rng.choice([0.5, -0.25, 1.0], N) * rng.integers(-6, 7, N)).astype(np.float32)
+    thr[::7], thr[3::7], thr[5::7] = 0.0, -np.inf, np.nan
+    dot = oracle.binary_fc(a, w, None)[0].astype(np.float32)
+    even = words + words % 2 if words < 2 else words  # (rows of one word 16 bytes apart)
+    A, W = (torch.nn.functional.pad(B.binarize_pack(dev(t), 1), (0, even - words)) for t in (a, w))
+    out = dev(np.full((M, -(-N // 64) + 1), -1, dtype=np.int64))
+    with tuned(k7=5, k10=1):
+        B.binary_fc_packed(A, K, W, alpha=dev(alpha), mode="bits", thr=dev(thr), out=out)
+        assert "gemm_fp4_kernel<2,2,1,xnor,bits>" in B.last_kernel() and "K split 1" in B.last_kernel(), B.last_kernel()
+    with np.errstate(invalid="ignore"):
+        want = np.where(alpha * dot >= thr, np.float32(1), np.float32(-1))
+    got = host_u64(out)
+    np.testing.assert_array_equal(got[:, :-1], oracle.binarize_pack(want, 1))
+    assert (got[:, -1] == np.uint64(0xFFFFFFFFFFFFFFFF)).all()
+
+
 @pytest.mark.parametrize("word", [32, 64])
 @pytest.mark.parametrize("M,N,K,off", [(1, 1, 1, 0), (33, 31, 33, 1), (5, 70, 65, 0), (40, 33, 97, 1), (32, 64, 128, 0), (31, 65, 256, 1),
                                        (70, 130, 257, 0), (64, 100, 1000, 1), (100, 90, 2017, 1), (3, 40, 4096, 0), (2, 33, 16385, 1),

@@ -613,7 +613,9 @@ static int quant_gemm(const float* a, int64_t lda, int bits_a, const float* w, i
   }
   hipStream_t s = (hipStream_t)stream;
   hipError_t direct = hipSuccess;
-  if (bmx::launch_quant_small(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, s, &direct))
+  const size_t tiles = bmx::quant_i8_workspace(M, N, K, bits_a, bits_w);  // (a call without a workspace yet comes back with all of it)
+  const bool pair = tiles && (!bmx::quant_few_bits(bits_a, bits_w) || !workspace || workspace_bytes >= tiles);
+  if (bmx::launch_quant_small(a, lda, bits_a, w, ldw, bits_w, M, N, K, out_i32_scaled, out_f32, ldo, pair, s, &direct))
     return hip_status(direct);
   if (!workspace) return BMX_ERR_WORKSPACE;
   // more bits than the FP4 form holds: bytes on the matrix cores

@@ -242,9 +242,10 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
                      int K, int32_t* S_out, float* out_f32, int64_t ldo, void* workspace, size_t workspace_bytes, hipStream_t s,
                      hipError_t* err);
 
-// The same in one launch without a workspace, for any pair of bit widths; false when too large for it.
+// The same in one launch without a workspace, for any pair of bit widths; false when too large for it.  pair: launch_quant_i8
+// would take the product (what it is weighed against; else the plane kernels are).
 bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
-                        int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err);
+                        int K, int32_t* S_out, float* out_f32, int64_t ldo, bool pair, hipStream_t s, hipError_t* err);
 
 // The same convolution on the GEMM kernel (filters = A rows streamed through SGPRs, im2col
 // rows gathered per chunk): for K that does not fit the stationary kernel or grids with too

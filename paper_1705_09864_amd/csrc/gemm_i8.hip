@@ -386,6 +386,99 @@ gemm_i8_kernel(const I8Params p) {
   finish_tile<TM, TN, SUMS, NIB, 8>(p, acc, sa, sb, red, lane, wave, tile_m, tile_n);
 }
 
+// The same product with 16 x 16 of C per workgroup, for results of few tiles.  There a CU waits for its one tile's operands, 64 bytes a
+// clock: a quarter of the tile has half of the bytes, and four times the CUs work on it.  The operands lie as above; a step of 64 k
+// (NIB: 128) is two of their tiles, whose four half tiles are the four quarters of the MFMA's K: a lane's 16 bytes are those of its
+// row, in runs of 256.  us a call in a graph, 32 x 32 / 16 x 16: 56 x 122 x 5294 of 3 x 8 bits 9.7 / 7.6, 297 x 64 x 4672 of 1 x 8 10.1 /
+// 8.6, 55 x 22 x 4359 of 3 x 2 6.8 / 5.8, 83 x 88 x 3058 of 1 x 2 6.4 / 5.4.
+template <bool SUMS, bool NIB>
+__global__ void __launch_bounds__(512)
+gemm_i8_16_kernel(const I8Params p) {
+  extern __shared__ int red[];
+  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.tiles_m), "s"(p.s_base), "s"(p.s_rem),
+               "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1), "s"(p.div_tiles_m.sh2), "s"(p.tiles), "s"(p.tiles_per_xcd));
+  static_assert(!(SUMS && NIB), "8 bits do not fit half a byte");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
+  if (lin >= p.tiles) return;  // (the whole workgroup)
+  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)lin, p.div_tiles_m)), tile_m = lin - tile_n * p.tiles_m;
+  const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0);
+  const int at = (lane >> 4) * 32 + (lane & 15);
+  const uint4* const arow = p.A + (int64_t)(tile_m >> 1) * p.nk * 64 + (tile_m & 1) * 16 + at;
+  const uint4* const brow = p.B + (int64_t)(tile_n >> 1) * p.nk * 64 + (tile_n & 1) * 16 + at;
+
+  v4i acc = {0, 0, 0, 0};
+  int sa = 0, sb = 0;
+  constexpr int kAhead = 4;
+  v4i a[2][kAhead], b[2][kAhead];
+  auto load = [&](int i, int k) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) {
+      const int kk = min(k + d, k_hi - 1) * 128;  // (a group's steps past the range repeat its last)
+      a[i][d] = *(const v4i*)(arow + kk);
+      b[i][d] = *(const v4i*)(brow + kk);
+    }
+  };
+  auto multiply = [&](int i, int k) {
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) {
+      if (k + d >= k_hi) break;  // wave-uniform
+      const v4i x = a[i][d], y = b[i][d];
+      if constexpr (NIB) {
+        constexpr int kLow = 0x0f0f0f0f, kHigh = (int)0xf0f0f0f0u, kHalf = 0x08080808;
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(x & kLow, ((y << 4) & kHigh) | kHalf, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8((x >> 4) & kLow, (y & kHigh) | kHalf, acc, 0, 0, 0);
+      } else {
+        if (SUMS) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            sa = __builtin_amdgcn_sdot4(x[e], 0x01010101, sa, false);
+            sb = __builtin_amdgcn_sdot4(y[e], 0x01010101, sb, false);
+          }
+        }
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, y, acc, 0, 0, 0);
+      }
+    }
+  };
+  if (k_lo < k_hi) {
+    load(0, k_lo);
+    for (int k = k_lo; k < k_hi; k += 2 * kAhead) {
+      if (k + kAhead < k_hi) load(1, k + kAhead);
+      multiply(0, k);
+      if (k + 2 * kAhead < k_hi) load(0, k + 2 * kAhead);
+      multiply(1, k + kAhead);
+    }
+  }
+  if (SUMS) {  // of row and column lane % 16
+    sa += __shfl_xor(sa, 16), sb += __shfl_xor(sb, 16);
+    sa += __shfl_xor(sa, 32), sb += __shfl_xor(sb, 32);
+  }
+  // the waves' sums meet: [wave][register][lane], and with SUMS [wave][row of a, of b] behind them; a thread a result
+  int* const sums = red + p.S * 256;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wave * 256 + 64 * e + lane] = acc[e];
+  if (SUMS && lane < 16) sums[wave * 32 + lane] = sa, sums[wave * 32 + 16 + lane] = sb;
+  __syncthreads();
+  for (int o = threadIdx.x; o < 256; o += 64 * p.S) {
+    const int row = 4 * ((o & 63) >> 4) + (o >> 6), col = o & 15;
+    int d = 0, ra = 0, cb = 0;
+#pragma unroll 4
+    for (int s = 0; s < p.S; ++s) {
+      d += red[s * 256 + o];
+      if (SUMS) ra += sums[s * 32 + row], cb += sums[s * 32 + 16 + col];
+    }
+    if (NIB) d >>= 3;
+    if (SUMS)
+      d = (int)((uint32_t)p.scale * ((uint32_t)d + (uint32_t)p.ca * (uint32_t)cb) + (uint32_t)p.rs * ((uint32_t)ra + (uint32_t)p.ca * (uint32_t)p.Kreal));
+    const int m = tile_m * 16 + row, n = tile_n * 16 + col;
+    if (m >= p.M || n >= p.N) continue;
+    const int64_t idx = (int64_t)m * p.ldc + n;
+    if (p.C_i32) p.C_i32[idx] = d;
+    if (p.C_f32) p.C_f32[idx] = quotient((float)d, p.denom, p.inv);
+  }
+}
+
 // ---- the whole product in one launch, for problems small enough that a second launch costs more
 // than quantising a row once per tile of results.  Up to 16 waves split the K of a T x T tile.  Of a step of KS = 1024 / T k a
 // wave fetches T rows of both operands, KS / 4 lanes to a row's 4 KS bytes (16 bytes straight into the
@@ -544,6 +637,13 @@ hipError_t launch_i8(const I8Params& p, hipStream_t s) {
   return launch_error();
 }
 
+template <bool SUMS, bool NIB>
+hipError_t launch_i8_16(const I8Params& p, hipStream_t s) {
+  note_kernel("gemm_i8_kernel<16 x 16%s> grid %d x %d, K split %d", SUMS ? ",sums" : NIB ? ",halves" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
+  launch_kernel(gemm_i8_16_kernel<SUMS, NIB>, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), (size_t)p.S * (1024 + (SUMS ? 128 : 0)), s, p);
+  return launch_error();
+}
+
 int64_t tile_bytes(int64_t rows, int64_t K) { return ceil_div(rows, 32) * 32 * ceil_div(K, 256) * 256; }
 
 }  // namespace
@@ -608,7 +708,7 @@ static void set_split(I8Params& p) {
 
 // The one-launch form, for any pair of bit widths; false when the problem is too large for it.
 bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w, int64_t ldw, int bits_w, int M, int N,
-                        int K, int32_t* S_out, float* out_f32, int64_t ldo, hipStream_t s, hipError_t* err) {
+                        int K, int32_t* S_out, float* out_f32, int64_t ldo, bool pair, hipStream_t s, hipError_t* err) {
   if (gemm_engine != 0) return false;
   const bool sums = bits_a == 8 || bits_w == 8;
   const int64_t t32 = ceil_div(M, 32) * ceil_div(N, 32), t16 = ceil_div(M, 16) * ceil_div(N, 16);
@@ -616,27 +716,33 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   // 32 x 32 over that as 16 x 16, up to 256 tiles of 16 x 16 1.24 to 1.37; 257 to 512 1.08 to 1.26 up to a K of 512, 0.90 beyond; 513
   // to 2048 1.08 to 1.17 up to 128, 0.8 beyond).
   const bool small = t16 <= 256 || (t16 <= 512 && K <= 512) || (t16 <= 2048 && K <= 128);
-  // Steps of K per CU up to which one launch is ahead of the better pair of launches (which the host makes in 7.8 us at the
-  // least): 16 x 16, 24 to 32 of them 1.42 times, 32 to 40 1.22, 40 to 48 1.06, 48 to 64 0.98; 32 x 32, a tile a CU or less, 20 to 28
-  // 1.11 in a graph and 1.36 as calls, 28 to 36 1.00 and 1.15 (8 bits
-  // at 256 tiles 0.9: 486 x 512 x 990 of 3 x 8 8.8 / 7.1), 36 to 40 0.91 and 1.02; more tiles, 16 to 24 1.02 and 1.12, 24 to 32 0.87 and 0.98.
-  // Over the same products the choice is 0.8 % behind the better.  us a call, before two values shared a byte and tiles were
-  // of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2 x 4 5.8 / 3.6,
-  // 202 x 192 x 437 5.0 / 3.4.
-  // (Where two values share a byte the pair is the faster one: with more than 128 tiles of 16 x 16 36 to 44 steps 0.92, 119 x 448 x 2684 of
-  // 1 x 1 bits 9.2 / 7.5.)
+  // Where 16 x 16 of the result per workgroup are one a CU and the pair of launches can be had: fitted to 900 products of 18 to 77 steps of
+  // 64 k, in us: a wave's steps and what the workgroups read (a row once per tile) on one side, the operands' way in once on the
+  // other.  By them the choice is 0.6 % behind the better form for two values a byte, 1.1 % else, as calls (the host makes two launches in
+  // 6.5 us at the least) and captured; by lines on the steps alone, set when the pair multiplied in tiles of 32 x 32, it was 1.2 to 2.2 %
+  // (by those / now, a call: 119 x 448 x 2240 of 2 x 1 bits 7.8 / 7.3 us, 43 x 1200 x 1900 of 4 x 4 7.9 / 7.1, 110 x 384 x 2690 of 8 x 8 9.6 /
+  // 7.3).
   const bool halves = bits_a <= 4 && bits_w <= 4;
   const int64_t steps = small ? ceil_div(K, 64) : ceil_div(K, 32) * ceil_div(t32, 256);
-  if (steps > (small ? (halves && t16 > 128 ? 36 : 44) : t32 > 256 ? 24 : sums ? 28 : 32)) return false;
-  // In a graph the host's part is not paid on replay, and the lines stand lower: where the GPU's part of both forms is level over 900
-  // products of 14 to 64 steps, rows of whole lines or not (a tile reads its own rows, each for itself).  There the choice by them is
-  // 1.5 % behind the better form, by the lines for calls 4.1 % (287 x 256 x 789 of 2 x 1 bits: one launch 6.9 us, two 5.5).
-  // (Up to four steps of K over many tiles stay: two launches 1.03 to 1.05, 1125 x 1216 x 128 of 8 x 1 bits 7.8 / 8.8.)
-  const bool ragged = (lda | ldw) % 32 != 0;
-  const int64_t graph_steps = !small      ? (t32 > 256 ? (K <= 128 ? 24 : 18) : t32 > 128 ? (ragged ? 18 : 22) : (ragged ? 22 : 28))
-                              : halves    ? std::max<int64_t>(24, 46 - t16 / (ragged ? 5 : 8))
-                                          : (ragged && t16 > 64 ? 38 : 44);
-  if (steps > graph_steps && capturing(s)) return false;
+  if (t16 <= 256 && pair) {
+    const double read = 128e-6 * (double)t16 * K, input = 4e-6 * ((double)M + N) * K;  // MB
+    const double one = halves ? 2.18 + 0.082 * steps + 0.044 * read : 2.50 + 0.083 * steps + 0.049 * read;
+    const double two = halves ? 4.86 + 0.184 * input : 5.25 + 0.315 * input;
+    if (one > two && (one > 6.5 || capturing(s))) return false;
+  } else {
+    // Steps of K per CU up to which one launch is ahead of the better pair of launches: 16 x 16 44; 32 x 32, a tile a CU or less, 20 to 28
+    // 1.11 in a graph and 1.36 as calls, 28 to 36 1.00 and 1.15 (8 bits at 256 tiles 0.9: 486 x 512 x 990 of 3 x 8 8.8 / 7.1), 36 to 40
+    // 0.91 and 1.02; more tiles, 16 to 24 1.02 and 1.12, 24 to 32 0.87 and 0.98.  us a call, before two values shared a byte and
+    // tiles were of 32 x 32 alone / now: 36 x 346 x 1062 of 1 x 1 bits 5.9 / 3.8, 213 x 256 x 818 of 8 x 1 8.0 / 4.1, 58 x 320 x 870 of 2
+    // x 4 5.8 / 3.6, 202 x 192 x 437 5.0 / 3.4.
+    if (steps > (small ? 44 : t32 > 256 ? 24 : sums ? 28 : 32)) return false;
+    // In a graph the host's part is not paid on replay, and the lines stand lower: where the GPU's part of both forms is level, rows of
+    // whole lines or not (a tile reads its own rows, each for itself; 287 x 256 x 789 of 2 x 1 bits: one launch 6.9 us, two 5.5).
+    // (Up to four steps of K over many tiles stay: two launches 1.03 to 1.05, 1125 x 1216 x 128 of 8 x 1 bits 7.8 / 8.8.)
+    const bool ragged = (lda | ldw) % 32 != 0;
+    const int64_t graph_steps = small ? 44 : t32 > 256 ? (K <= 128 ? 24 : 18) : t32 > 128 ? (ragged ? 18 : 22) : (ragged ? 22 : 28);
+    if (steps > graph_steps && capturing(s)) return false;
+  }
   if (K < 4 || (int64_t)M * lda * 4 >= ((int64_t)1 << 32) || (int64_t)N * ldw * 4 >= ((int64_t)1 << 32)) return false;
   const int T = small ? 16 : 32, nk = (int)ceil_div(K, 1024 / T);
   QuantSmallParams p;
@@ -716,6 +822,23 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   // x 1438 x 681 14.2 and 11.4; 1650 x 1566 x 103 16.8 and 12.2; 1098 x 1728 x 265 12.1 and 11.3.  Over 150
   // products 8.7 % and 1.8 % behind the best of all splits and forms.
   // (With two values a byte the same lines and splits are 0.5 % behind the best of all over 414 products.)
+  const bool sums = bits_a == 8 || bits_w == 8;
+  // 16 x 16 of C per workgroup up to one and a half of them a CU (250 products, the time of the calls over that with 32 x 32 and 32 x 64:
+  // up to 64 tiles 0.78 to 0.82, 65 to 128 0.81 to 0.85, 129 to 256 0.88, 257 to 384 0.98 of two values a byte and 0.96 of one,
+  // 385 to 512 0.99 and 1.01, beyond 1.04 to 1.16; sixteen waves of K are level with eight, four behind them to 256 tiles).
+  const int64_t t16 = ceil_div(M, 16) * ceil_div(N, 16);
+  if (t16 <= 384) {
+    p.tiles_m = (int)ceil_div(M, 16);
+    p.tiles = (int)t16;
+    p.tiles_per_xcd = (int)ceil_div(t16, 8);
+    const int steps = p.nk / 2;
+    p.S = std::min(8, steps);
+    p.s_base = steps / p.S;
+    p.s_rem = steps % p.S;
+    p.div_tiles_m = make_fast_div((uint32_t)p.tiles_m);
+    *err = halves ? launch_i8_16<false, true>(p, s) : sums ? launch_i8_16<true, false>(p, s) : launch_i8_16<false, false>(p, s);
+    return true;
+  }
   const int64_t t12 = ceil_div(M, 32) * ceil_div(N, 64), t22 = ceil_div(M, 64) * ceil_div(N, 64);
   const int TM = K >= 5000 && t22 >= 128 ? 2 : 1, TN = TM == 2 || (K > 1100 && t12 >= 128) ? 2 : 1;
   p.tiles_m = (int)ceil_div(M, 32 * TM);
@@ -725,7 +848,6 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   p.S = room >= 8 ? 8 : room >= 4 ? 4 : room >= 2 ? 2 : 1;
   while (p.S > 1 && p.S > 2 * q.kblocks) p.S /= 2;  // (each with 128 k at least)
   set_split(p);
-  const bool sums = bits_a == 8 || bits_w == 8;
   auto form = [&](auto tm, auto tn) {
     constexpr int M_ = decltype(tm)::value, N_ = decltype(tn)::value;
     return halves ? launch_i8<M_, N_, false, true>(p, s) : sums ? launch_i8<M_, N_, true, false>(p, s) : launch_i8<M_, N_, false, false>(p, s);

@@ -684,7 +684,7 @@ def test_quant_gemm_one_launch(M, N, K, ba, bw):
     assert_f32_close(of.cpu().numpy(), r32)
 
 
-@pytest.mark.parametrize("M,N,K", [(513, 580, 769), (545, 513, 1023), (33, 1100, 2817), (520, 300, 1025), (40, 3000, 1300), (70, 36, 4200), (16, 33, 3071), (200, 2100, 897)])
+@pytest.mark.parametrize("M,N,K", [(513, 580, 769), (545, 513, 1023), (33, 1100, 2817), (520, 300, 1025), (40, 3000, 1300), (70, 36, 4200), (16, 33, 3583), (200, 2100, 897)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (2, 1), (4, 1), (3, 2), (1, 3), (4, 4)])
 def test_quant_halves(M, N, K, ba, bw):
     """Two values a byte: K that ends in either half of a block of 256 and on its edge, rows that do not fill a block of 32, one
@@ -705,6 +705,24 @@ def test_quant_halves(M, N, K, ba, bw):
     np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
 
 
+@pytest.mark.parametrize("M,N,K,form", [(16, 16, 1, "16 x 16"), (33, 47, 255, "16 x 16"), (31, 17, 257, "16 x 16"), (90, 70, 769, "16 x 16"),
+                                        (16, 6144, 2049, "16 x 16"), (256, 384, 513, "16 x 16"), (17, 3073, 300, "1,1"), (176, 560, 600, "1,1")])
+@pytest.mark.parametrize("ba,bw", [(1, 1), (4, 3), (2, 5), (7, 2), (8, 4), (3, 8), (8, 8)])
+def test_quant_bytes_16_by_16(M, N, K, form, ba, bw):
+    """Bytes of few tiles: 16 x 16 of the result a workgroup and the line to larger ones (384 and 385 of them); one step for a wave, one
+    for some, several, a last one of padding; either half of the operands' blocks of 32 rows, part of one; operand rows apart."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a = rng.uniform(-0.1, 1.1, (M, K + 1)).astype(np.float32)
+    w = rng.uniform(-1.1, 1.1, (N, K + 3)).astype(np.float32)
+    rS, _, r32 = oracle.quant_gemm(a[:, :K].copy(), w[:, 3:].copy(), ba, bw)
+    with tuned(k7=3 if ba > 2 or bw > 1 else 0):  # (the pair of launches; of few bits the engine pins the planes)
+        S, of = B.quant_gemm(dev(a)[:, :K], dev(w)[:, 3:], ba, bits_w=bw)
+        if ba > 2 or bw > 1:
+            assert "gemm_i8_kernel<%s" % form in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
+
+
 @pytest.mark.parametrize("M,N,K,T", [(16, 16, 4, 16), (1, 1, 63, 16), (17, 31, 64, 16), (15, 33, 65, 16), (256, 256, 129, 16), (256, 257, 512, 16),
                                      (256, 257, 513, 32), (512, 1024, 128, 16), (512, 1025, 128, 32), (30, 50, 2816, 16), (300, 240, 700, 32), (300, 240, 896, 32), (730, 1439, 31, 32)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (8, 1), (2, 2), (4, 7), (8, 3), (1, 8), (8, 8)])
@@ -721,9 +739,11 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
 
 
 @pytest.mark.parametrize("M,N,K,ba,bw,call,graph", [
-    (119, 448, 2304, 1, 1, True, False), (119, 448, 2305, 1, 1, False, False), (119, 448, 2816, 8, 1, True, True), (119, 448, 2815, 8, 1, True, False),
-    (119, 448, 2432, 8, 1, True, True), (30, 40, 2816, 4, 4, True, True), (30, 40, 2815, 4, 8, True, True), (90, 60, 2688, 2, 2, True, True),
-    (90, 60, 2689, 2, 2, True, False), (241, 256, 1536, 2, 1, True, True), (241, 256, 1537, 2, 1, True, False), (287, 256, 704, 2, 1, True, True),
+    (119, 448, 1231, 1, 1, True, True), (119, 448, 1232, 1, 1, True, False), (119, 448, 1669, 1, 1, True, False), (119, 448, 1670, 1, 1, False, False),
+    (119, 448, 1344, 8, 1, True, True), (119, 448, 1345, 8, 1, True, False), (119, 448, 1472, 8, 1, True, False), (119, 448, 1473, 8, 1, False, False),
+    (30, 40, 2112, 4, 4, True, True), (30, 40, 2113, 4, 4, True, False), (30, 40, 3264, 4, 4, True, False), (30, 40, 3265, 4, 4, False, False),
+    (90, 60, 2048, 2, 2, True, True), (90, 60, 2049, 2, 2, True, False), (241, 256, 1118, 2, 1, True, True), (241, 256, 1119, 2, 1, True, False),
+    (1835, 24, 2158, 2, 8, True, True), (15, 17, 2816, 4, 4, True, True), (15, 17, 2817, 4, 4, False, False), (287, 256, 704, 2, 1, True, True),
     (287, 256, 705, 2, 1, True, False), (287, 256, 896, 2, 1, True, True), (287, 256, 928, 2, 1, True, False), (500, 512, 704, 8, 2, True, True),
     (500, 512, 736, 8, 2, True, False), (500, 512, 576, 8, 2, True, True), (500, 512, 575, 8, 2, True, True), (500, 512, 577, 8, 2, True, False),
     (600, 512, 288, 3, 3, True, True), (600, 512, 289, 3, 3, True, False), (1125, 1216, 128, 8, 1, True, True), (1125, 1216, 129, 8, 1, False, False)])

@@ -703,7 +703,7 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
       // (Rows that are parts of lines, from several workgroups a CU at once: stored as fast as a wave can, the parts get in each
       // other's way, and the bounds' instructions are the better pace: 4000 x 4001 x 128 13.7 / 14.7 us, 3520 x 6492 x 92 17.5 / 18.7;
       // with at most one a CU 896 x 3384 x 5120 13.9 / 13.3, 640 x 3367 x 2532 9.15 / 8.6.)
-      if (m0 + 32 * TM > M || n0 + 32 * TN > N || (!nt && gridDim.x > 256)) store_tile(std::false_type{}, std::true_type{});
+      if (m0 + 32 * TM > M || n0 + 32 * TN > N || (!nt && (int)gridDim.x * tiles_per_wg > 1024)) store_tile(std::false_type{}, std::true_type{});
       else if (nt) store_tile(std::true_type{}, std::false_type{});
       else store_tile(std::false_type{}, std::false_type{});
     }
@@ -1046,7 +1046,11 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   set_tile_order(p, S);
   p.g_base = ngroups / S;
   p.g_rem = ngroups - p.g_base * S;
-  const int tiles_per_wg = 4;
+  // Undivided, a workgroup is a wave where K is short: nothing is shared, and a wave starts when there is room for it and not for four
+  // (400 products, time over that with four: up to 7 words 0.96 to 1700 tiles and 0.98 beyond, 8 to 20 words 0.98; from 21 on 0.98 to 1.03,
+  // and over long K, where four keep the SIMDs of a CU level, 1.06 with 1700 to 2048 tiles; planes 1.05 with 300 to 1024).
+  // us in a graph: 2000 x 2048 x 320 as packed bits 5.4 / 5.1, 1462 x 1920 x 128 5.7 / 5.3.
+  const int tiles_per_wg = rowsum == nullptr && Kwords < 21 ? 1 : 4;
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;

@@ -189,16 +189,22 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // 255 up to 7000 (5000 to 7000 1.0 to 1.05, then 0.95 to 0.8), to 511 up to 8192 (0.99, then 0.88).
   // 12288 too where that kernel does not take the product; of a K of more than four steps for each of
   // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
-  // From 512 tiles of 64 x 64 on, where that kernel has work for most SIMDs (700 products of 200 to 1300 tiles, rows of any word): fp32
-  // results up to 699 tiles and three steps of K (1.04 to 1.07, then 0.94), of one step to 799 (1.03, then 0.95); int32 to 599 and two
-  // (1.03; three 0.99, beyond 0.95); packed bits not at all (0.91 at 512 to 0.72 at 1000), of one step only below 256 (1.02, 0.95).
+  // From some hundred tiles of 64 x 64 on, where that kernel has work for most SIMDs (1200 products of 200 to 1100 tiles and two words of K on,
+  // in a graph and as calls; the loss against the better kernel by these lines, and by one for all at 512): packed bits from 352 (0.1 to
+  // 0.2 %, 1.0), of one step of K from 256 (0.5, 8.4); int32 from 320 where all tiles are whole and stored without bounds (0.2 to 0.9, 0.8 to
+  // 2.6), of one step then from 256 (0.2, 5.7), from 448 where some are not (0.1 to 0.5, of one step of whole lines 1.5; 0.1 to 0.8 and 2.5);
+  // fp32 from 512 (0.3 to 1.1).  From 21 words on, where that kernel divides K over three waves or four, from 512 (652 x 2512 x 1472
+  // as bits 6.9 / 6.4).
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool apart = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15);  // (launch_gemm_fp4)
   const bool pays = (dwords >= 4 || apart) && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, C_bits != nullptr);
   const int64_t most = steps > 64                                ? 2048
                        : !pays || (dwords <= 56 && tiles64 < 512) ? 12288
                                                                   : (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192);
-  const int64_t below = C_bits ? (steps == 1 ? 256 : 512) : C_f32 ? (steps == 1 ? 800 : steps <= 3 ? 700 : 512) : (steps <= 2 ? 600 : 512);
+  const bool whole = M % 64 == 0 && N % 64 == 0;
+  const int64_t below = dwords > 40 || C_f32 ? 512
+                      : C_bits               ? (steps == 1 ? 256 : 352)
+                                             : (!whole ? 448 : steps == 1 ? 256 : 320);
   // (packed bits of rows of less than 16 bytes have no other kernel of many tiles)
   if ((work > most || tiles > 4096) && !(C_bits && dwords < 4 && !apart)) return false;
   if (pays && tiles64 >= below) return false;

@@ -185,7 +185,7 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
                        int out_pad, hipStream_t s, hipError_t* err);
 // Estimated time of a convolution of 8 words and more by launch_conv_block or launch_conv_fp4 in us;
 // form: launch_conv_block's choice, 0 for launch_conv_fp4.
-double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form);
+double conv_long_us(int64_t P, int O, int kwords, bool odd, int* form);
 extern int gemm_block, conv_block;
 // (out_bits, thr, out_pad as for launch_conv_mfma_ws)
 bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const uint64_t* Wp, int O, int KH, int KW,

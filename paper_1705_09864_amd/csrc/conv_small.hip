@@ -230,7 +230,7 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
     int form;
     if (work > 72000) return false;
     if (((uintptr_t)Wp & 15) == 0 && !conv_block && !gemm_fp4_split && !gemm_fp4_half && !gemm_fp4_band) {
-      if (K < 8 ? tiles >= 7000 : work > 12000 && 3.4 + 2.5e-4 * work > conv_long_us(P, O, K, (Cw & 1) || ((uintptr_t)Xp & 15), &form)) return false;
+      if (K < 8 ? tiles >= 7000 : work > 12000 && 3.4 + 2.5e-4 * work > conv_long_us(P, O, K, (KW * Cw) & 1, &form)) return false;
     }
   } else if (K == 1 || K == 2 || K == 4 || work > (tiles64 >= 64 && tiles > 3 * tiles64 && ((uintptr_t)Wp & 15) == 0 ? 12288 : 16384) || tiles > 4096) {
     return false;

@@ -22,8 +22,8 @@
 //   - Two waves share every block of rows; each counts the bits of half its blocks.
 //   - Rows may start on any dword, which is all that loads of 16 bytes need (dword by dword, four times the loads, 768 x 6619 x
 //     2240 took 15.4 us, now 12.3; 4224 x 4736 x 1600 23.1 / 22.4; 7934 x 1472 x 3008 19.7 / 18.3).
-//   - The convolution form gathers the im2col rows of 128 (256) pixels from the packed image, 16 bytes or a dword at a
-//     time, once for 128 (64) filters; where the patches start stands in LDS.  Its results are fp32, int32 or
+//   - The convolution form gathers the im2col rows of 128 (256) pixels from the packed image, 16 bytes at a
+//     time (a dword in segments that hold a piece of two runs of an odd number of words), once for 128 (64) filters; where the patches start stands in LDS.  Its results are fp32, int32 or
 //     the next convolution's packed image, halo included.
 //   (Three and four stages in flight changed nothing, at 8192^3 or with one workgroup per CU: it is issue and, with
 //   one wave on a SIMD, the chain of its own instructions that bounds the loop, not the memory behind it.)
@@ -72,7 +72,7 @@ struct BlockParams {
   // the next convolution's image of oHp x oWp x oCw words with a halo of opad.
   int HoWo, Wo, Ho, Hp, Wpp, Cw, stride, Nimg;
   uint32_t run, row_bytes;
-  FastDiv div_howo, div_wo, div_run;
+  FastDiv div_howo, div_wo, div_run, div_two_runs;
   const float* thr;
   int opad, oHp, oWp, oCw;
 };
@@ -104,8 +104,8 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
 
 // WM x 4 / WM waves of TM x TN blocks of 32 x 32 each.  A stage holds blocks of 32 rows x 64 bytes, A's, then B's, in the
 // layout of gemm_fp4.hip: piece c of row r of a block at 16-byte place 64 (r / 16) + 4 (r % 16) + (c xor ((r / 2) & 3)).
-// LW: bytes a lane fetches per load: 16, and 4 where rows are less than that and not that far apart, or (convolution form) the image
-// has an odd number of channel words.
+// LW: bytes a lane fetches per load: 16, and 4 where rows are less than that and not that far apart, or (convolution form) for the
+// patches in segments that hold a piece of two runs of an odd number of words.
 template <int WM, int TM, int TN, int OUT, int LW, bool CONV>
 __global__ void __launch_bounds__(256, TM * TN >= 8 ? 2 : 3)
 gemm_fp4_kernel(const BlockParams p) {
@@ -194,8 +194,8 @@ gemm_fp4_kernel(const BlockParams p) {
     }
     __syncthreads();
   }
-  uint32_t vp[CONV && LW == 16 ? HB : 1];
-  if constexpr (CONV && LW == 16) {
+  uint32_t vp[CONV ? HB : 1];
+  if constexpr (CONV) {
 #pragma unroll
     for (int k = 0; k < HB; ++k) vp[k] = patch[16 * (wave * HB + k) + (lane >> 2)];
   }
@@ -203,6 +203,13 @@ gemm_fp4_kernel(const BlockParams p) {
   auto in_patch = [&](uint32_t d) {
     const uint32_t w = d >> 1, run = fast_div(w, p.div_run);
     return run * p.row_bytes + (w - run * p.run) * 8u + (d & 1u) * 4u;
+  };
+  // whether a piece of segment seg of a patch holds words of two runs, or the patch's last word alone: an odd multiple of an odd run
+  // lies among its words
+  auto runs_meet = [&](int seg) {
+    const uint32_t end = 8u * (uint32_t)seg + 7u;
+    if (!(p.run & 1u) || end < p.run) return false;
+    return p.run * (2u * fast_div(end - p.run, p.div_two_runs) + 1u) >= 8u * (uint32_t)seg;
   };
   // Requests segment seg of the wave's half blocks into stage buf.
   auto issue = [&](int seg, int buf) {
@@ -216,7 +223,7 @@ gemm_fp4_kernel(const BlockParams p) {
     if constexpr (!CONV) {
 #pragma unroll
       for (int k = 0; k < HB; ++k) load_rows(tob + 1024u * k, p.B + at_seg, vb[k], LW, p.ldb, p.N, last);
-    } else if constexpr (LW == 16) {
+    } else if (LW == 16 || !runs_meet(seg)) {
       const uint32_t d = 16u * (uint32_t)seg + 4u * piece16;
       const uint32_t at = in_patch(d < (uint32_t)p.Kd ? d : 16u * (uint32_t)seg);
 #pragma unroll
@@ -332,8 +339,9 @@ gemm_fp4_kernel(const BlockParams p) {
       write_halo((uint64_t*)p.C, p.Nimg, p.Ho, p.Wo, p.opad, p.M, p.oCw, cw, tile_n * 256 + threadIdx.x, p.tiles_n * 256);
   }
   if (p.nseg > 1) {
-    constexpr int kLoads = HA * (LWA == 16 ? 1 : 4) + HB * (LW == 16 ? 1 : 4);  // a wave's loads per segment
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kLoads) : "memory");
+    constexpr int kLoads = HA * (LWA == 16 ? 1 : 4) + HB * (LW == 16 ? 1 : 4);  // a wave's loads of segment 1
+    if (CONV && LW == 4 && !runs_meet(1)) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(HA + HB) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kLoads) : "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     if (tail) {
@@ -503,7 +511,7 @@ hipError_t go(BlockParams& p, hipStream_t s) {
   p.tiles_per_xcd = (int)ceil_div((int64_t)p.tiles_m * p.tiles_n, 8);
   const unsigned blocks = 8u * (unsigned)p.tiles_per_xcd;
   note_kernel("block::gemm_fp4_kernel<%d,%d,1,xnor,%s,%sblock%s%s> grid %u x 256, K split 1, fp4", TM, TN,
-              OUT == kI32 ? "i32" : OUT == kBits ? "bits" : "f32", CONV ? "conv," : "", LW == 4 ? " of dwords" : "",
+              OUT == kI32 ? "i32" : OUT == kBits ? "bits" : "f32", CONV ? "conv," : "", LW != 4 ? "" : CONV ? " of odd runs" : " of dwords",
               WM == 1 ? " one high" : "", blocks);
   launch_kernel((gemm_fp4_kernel<WM, TM, TN, OUT, LW, CONV>), dim3(blocks), dim3(256), lds, s, p);
   return launch_error();
@@ -568,7 +576,7 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   p.nt = lines;
   p.HoWo = p.Wo = p.Ho = p.Hp = p.Wpp = p.Cw = p.stride = p.Nimg = 1;
   p.run = p.row_bytes = 1;
-  p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
+  p.div_howo = p.div_wo = p.div_run = p.div_two_runs = make_fast_div(1);
   p.thr = nullptr;
   p.opad = p.oHp = p.oWp = p.oCw = 0;
   const bool large = !short_rows && (gemm_block ? gemm_block == 2 : tiles >= 4096 && K >= 4096 && p.nt);
@@ -583,17 +591,18 @@ int conv_block = 0;  // 1 = never, 2 = 128 filters x 128 pixels and 3 = 64 x 256
 
 // Fitted to 361 convolutions of 8 to 392 words measured on each (us, fp32 results and packed bits; the choice by it is 0.16 %
 // off the best, 10 % at most; 0.66 % and 21 % while the terms were those of the kernels before their last change: 68175 pixels, 128 filters, 72
-// words 26.6 us in gemm_fp4.hip, 22.0 here).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU, more where words go
-// through registers (an odd number of channel words).  Here by workgroups per CU; one alone on a CU takes more than half as
-// long for a segment as two together.
-double conv_long_us(int64_t P, int O, int kwords, bool any_dword, int* form) {
+// words 26.6 us in gemm_fp4.hip, 22.0 here).  gemm_fp4.hip divides K of a 64 x 64 tile over a CU's waves: by its tiles per CU.
+// Here by workgroups per CU; one alone on a CU takes more than half as long for a segment as two together.  With runs of an odd
+// number of words, where the segments that two of them meet in take longer: of 400 such convolutions of 45 to 343 words the choice is
+// 0.08 % off the best, 6 % at most.
+double conv_long_us(int64_t P, int O, int kwords, bool odd, int* form) {
   const double K = kwords;
   const double n = (double)ceil_div(ceil_div(P, 64) * ceil_div(O, 64), 256);
   const double high = (double)ceil_div(ceil_div(P, 128) * ceil_div(O, 128), 256), mh = std::max(1.3, high);
   const double wide = (double)ceil_div(ceil_div(P, 256) * ceil_div(O, 64), 256), mw = std::max(1.3, wide);
-  const double there = any_dword ? 3.4 + n * (1.2 + 0.0243 * K) : 3.6 + n * (0.87 + 0.0195 * K);
-  const double us2 = any_dword ? 6.2 + 0.36 * high + 0.088 * mh * K : 5.25 + 0.99 * high + 0.0718 * mh * K;
-  const double us3 = any_dword ? 6.2 + 0.112 * mw * K : 4.5 + 1.14 * wide + 0.0783 * mw * K;
+  const double there = odd ? 3.65 + n * (0.78 + 0.0216 * K) : 3.6 + n * (0.87 + 0.0195 * K);
+  const double us2 = odd ? 5.65 + 1.08 * high + 0.0759 * mh * K : 5.25 + 0.99 * high + 0.0718 * mh * K;
+  const double us3 = odd ? 6.1 + 1.0 * wide + 0.0821 * mw * K : 4.5 + 1.14 * wide + 0.0783 * mw * K;
   *form = std::min(us2, us3) >= there ? 0 : us2 <= us3 ? 2 : 3;
   return std::min(there, std::min(us2, us3));
 }
@@ -613,10 +622,10 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= lim || ((int64_t)O + 256) * ld_words * 8 >= lim || P >= lim / 4) return false;
   if (((int64_t)Nimg * O + 256) * Ho * Wo * 4 >= lim) return false;
   if (out_bits && (int64_t)Nimg * (Ho + 2 * out_pad) * (Wo + 2 * out_pad) * words_for(O) >= lim / 4) return false;
-  const bool any_dword = (Cw & 1) || ((uintptr_t)Xp & 15);
+  const bool odd = (KW * Cw) & 1;
   int form = conv_block;
   if (form == 0) {
-    conv_long_us(P, O, kwords, any_dword, &form);
+    conv_long_us(P, O, kwords, odd, &form);
     // Short K stays with conv_mfma.hip, but for many filters over many pixels: there a pixel's words are expanded once per
     // 32 filters, here once per 128 or 64.  Of 182 of 36, 49 and 50 words, from 90000 steps of 32 x 32 x 256 on (us there /
     // here): as packed bits 27776 pixels, 448 filters, 50 words 31.8 / 20.6, 27664, 384, 36 20.1 / 15.8, 46371, 192, 49 24.1 / 20.5;
@@ -666,6 +675,7 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.div_howo = make_fast_div((uint32_t)p.HoWo);
   p.div_wo = make_fast_div((uint32_t)Wo);
   p.div_run = make_fast_div(p.run);
+  p.div_two_runs = make_fast_div(2 * p.run);
   p.opad = out_pad;
   p.oHp = Ho + 2 * out_pad;
   p.oWp = Wo + 2 * out_pad;
@@ -677,7 +687,7 @@ bool launch_conv_block(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
     return out_bits ? go<WM, 2, 2, kBits, LW, true>(p, s) : out_i32 ? go<WM, 2, 2, kI32, LW, true>(p, s) : go<WM, 2, 2, kF32, LW, true>(p, s);
   };
   auto high = [&](auto lw) { return one_high ? kind(std::integral_constant<int, 1>{}, lw) : kind(std::integral_constant<int, 2>{}, lw); };
-  *err = any_dword ? high(std::integral_constant<int, 4>{}) : high(std::integral_constant<int, 16>{});
+  *err = odd ? high(std::integral_constant<int, 4>{}) : high(std::integral_constant<int, 16>{});
   return true;
 }
 

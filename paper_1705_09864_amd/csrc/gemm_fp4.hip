@@ -46,7 +46,10 @@
 //     to back (workgroup b runs on XCD b % 8): every XCD gets a contiguous run of tiles, walked
 //     in bands of 8 or 16 rows of tiles.
 //   - The convolution form gathers the B operand (im2col rows) from the halo-padded packed
-//     image, 16 bytes per lane, through the same loads.
+//     image, 16 bytes per lane, through the same loads.  Where runs have an odd number of words only the segments that two of them
+//     meet in pass registers (all did once; us in a graph, before and now: 21600 pixels, 128 filters, 45 words, 678 tiles 12.9 -> 10.2;
+//     24 x 192 x 47 x 49 -> 64, 5 x 5, 17.6 -> 14.7; 22 x 192 x 42 x 42 -> 64, 7 x 7, as packed bits 20.1 -> 16.7; of 400 drawn ones
+//     1.07 in the mean, 1.2 to 1.3 between 513 and 768 tiles.  Those segments dword by dword straight to LDS: 1.05).
 #include <algorithm>
 #include <type_traits>
 
@@ -92,13 +95,12 @@ struct Fp4Params {
   // Convolution form (Sec. 3.1: M = filters, N = batch * output pixels, K = kh * kw * C): A is the
   // packed filter matrix, B the halo-padded packed image.  Column n is output pixel n (flat over
   // the images); its K words are KH runs of KW * Cw consecutive words, one run per kernel row
-  // (the taps of a kernel row are neighbouring pixels, channel words innermost), so with an even
-  // Cw every 16-byte piece of the im2col row is 16 consecutive bytes of the image.  alpha is per
+  // (the taps of a kernel row are neighbouring pixels, channel words innermost), so a 16-byte piece
+  // of the im2col row is 16 consecutive bytes of the image, but for those that two runs of an odd number of words meet in.  alpha is per
   // row m here, and the result goes to NCHW: element (image * M + m) * HoWo + pixel.
   int HoWo, Wo, Hp, Wpp, Cw, stride;
-  uint32_t run_pieces, row_bytes, npieces;  // pieces per run; bytes from run to run; pieces per pixel
-                                            // (through registers: words per run, per pixel)
-  FastDiv div_howo, div_wo, div_run;
+  uint32_t run, row_bytes;  // words per run; bytes from run to run
+  FastDiv div_howo, div_wo, div_run, div_two_runs;
   // packed bits of the convolution form: the next convolution's image (C_bits, 64-bit words), its size, words per pixel, halo;
   // thr is per row m
   int Nimg, Ho, opad, oHp, oWp, oCw;
@@ -149,13 +151,23 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
   return acc;
 }
 
+// Whether a piece of segment `seg` of an im2col row holds words of two runs, or the row's last word alone: an odd multiple of an odd
+// run lies among its words.
+__device__ __forceinline__ bool runs_meet(const Fp4Params& p, int seg) {
+  const uint32_t end = 8u * (uint32_t)seg + 7u;
+  if (!(p.run & 1u) || end < p.run) return false;
+  return p.run * (2u * fast_div(end - p.run, p.div_two_runs) + 1u) >= 8u * (uint32_t)seg;
+}
+
 // Request segment `seg` (64 bytes of every row of the wave's NB staged blocks) into the staging
 // area at dst: per block two loads of 16 rows, lane i of a load writing LDS bytes [16 i, 16 i + 16)
 // of its destination.  voff: a lane's byte offset of its piece in segment 0 of its row (CONV: for
-// the B blocks, of its pixel's patch; the piece's place inside the patch is found here).
-template <int NA, int NB, bool CONV>
+// the B blocks, of its pixel's patch; the piece's place inside the patch is found here).  ODD: runs may be of an odd number of words;
+// the segments that two of them meet in, one or two of 8 with 3 x 3 filters over 7 words, pass registers (nx, B's blocks) a word at a
+// time, and the caller writes them to the same places when it gets to them.
+template <int NA, int NB, bool CONV, bool ODD>
 __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, const uint32_t* voff /* [NB][2] */,
-                                              int piece0, int piece1, int seg) {
+                                              int piece0, int piece1, int seg, uint4* nx /* [NB - NA][2] */) {
   if constexpr (!CONV) {
     // A piece that the row ends in, and those behind it, are the row's last 16 bytes: nothing behind a row is read, which may be where
     // the buffer ends (rows of less are 16 bytes apart).  Up to 12 bytes in front of the segment, so the segment's place is in the
@@ -178,16 +190,16 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
   }
   const char* abase = (const char*)p.A + (uint32_t)seg * 64u;
   const bool tail = 8 * seg + 8 > p.Kw;  // the row ends inside this segment
+  const bool by_words = ODD && runs_meet(p, seg);
   uint32_t boff[2] = {0u, 0u};
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    // piece c of the im2col row: run c / run_pieces (a kernel row), piece c % run_pieces of it; a
-    // piece beyond the row's last is not fetched (the reader zeroes it): its lane repeats the
-    // segment's first piece, which always exists
-    uint32_t c = 4u * (uint32_t)seg + (uint32_t)(t ? piece1 : piece0);
-    if (c >= p.npieces) c = 4u * (uint32_t)seg;
-    const uint32_t run = fast_div(c, p.div_run);
-    boff[t] = run * p.row_bytes + (c - run * p.run_pieces) * 16u;
+    // piece c of the im2col row, from word 2 c on: run 2 c / run (a kernel row).  A piece beyond the row's last is not fetched (the
+    // reader zeroes it): its lane repeats the segment's first piece, which always exists
+    uint32_t w = 8u * (uint32_t)seg + 2u * (uint32_t)(t ? piece1 : piece0);
+    if (w >= (uint32_t)p.Kw) w = 8u * (uint32_t)seg;
+    const uint32_t run = fast_div(w, p.div_run);
+    boff[t] = run * p.row_bytes + (w - run * p.run) * 8u;
   }
 #pragma unroll
   for (int b = NB - 1; b >= 0; --b)
@@ -198,42 +210,28 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
       if (b >= NA) off += boff[t];
       // (filters) a piece that starts beyond the row's last word: repeat the segment's first
       else if (tail && 8 * seg + 2 * pc >= p.Kw) off -= 16u * pc;
-      __builtin_amdgcn_global_load_lds((b < NA ? abase : (const char*)p.B) + off, (lds_ptr)(dst + b * 128 + t * 64), 16, 0, 0);
+      if (b < NA || !by_words)
+        __builtin_amdgcn_global_load_lds((b < NA ? abase : (const char*)p.B) + off, (lds_ptr)(dst + b * 128 + t * 64), 16, 0, 0);
     }
-}
-
-// The same segment of a convolution through registers, for images whose 16-byte pieces are not contiguous (an odd number of channel
-// words).  The words go to the same places of the staging area when the wave gets to the segment.
-template <int NA, int NB>
-__device__ __forceinline__ void fetch_segment(const Fp4Params& p, uint4 (&nx)[NB][2], const uint32_t (&voff)[NB][2],
-                                              int piece0, int piece1, int seg) {
-  const bool tail = 8 * seg + 8 > p.Kw;  // (wave-uniform) the row ends inside this segment
+  if (by_words) {
+    // (words past the row repeat its last, the reader zeroes them)
+    uint32_t woff[2][2];
 #pragma unroll
-  for (int b = NB - 1; b >= 0; --b)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int pc = t ? piece1 : piece0;
-      const char* base = b < NA ? (const char*)p.A : (const char*)p.B;
-      if (b < NA && !tail) {
-        const v4u_any v = *(const v4u_any*)(base + (uint32_t)seg * 64u + voff[b][t]);
-        nx[b][t] = make_uint4(v[0], v[1], v[2], v[3]);
-      } else {  // word by word; words past the row repeat its last (the reader zeroes them)
-        uint64_t w[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const uint32_t k = (uint32_t)min(8 * seg + 2 * pc + e, p.Kw - 1);
-          uint32_t off;
-          if (b >= NA) {
-            const uint32_t run = fast_div(k, p.div_run);
-            off = voff[b][t] + run * p.row_bytes + (k - run * p.run_pieces) * 8u;
-          } else {
-            off = voff[b][t] - 16u * pc + k * 8u;
-          }
-          w[e] = *(const uint64_t*)(base + off);
-        }
-        nx[b][t] = make_uint4((uint32_t)w[0], (uint32_t)(w[0] >> 32), (uint32_t)w[1], (uint32_t)(w[1] >> 32));
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t w = (uint32_t)min(8 * seg + 2 * (t ? piece1 : piece0) + e, p.Kw - 1), run = fast_div(w, p.div_run);
+        woff[t][e] = run * p.row_bytes + (w - run * p.run) * 8u;
       }
-    }
+#pragma unroll
+    for (int b = NB - 1; b >= NA; --b)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint2 lo = *(const uint2*)((const char*)p.B + (voff[2 * b + t] + woff[t][0]));
+        const uint2 hi = *(const uint2*)((const char*)p.B + (voff[2 * b + t] + woff[t][1]));
+        nx[2 * (b - NA) + t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+  }
 }
 
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -312,11 +310,11 @@ constexpr int slot_size(int pl, bool split, bool half) { return std::max((TM * p
 // PL bit planes per A row; XNOR: the xnor form (row popcounts from the words themselves), else the plane form (row sums given); OUT: what the
 // xnor form stores; SPLIT: K split over the S waves of the workgroup (else a tile per wave);
 // HALF: the partial tiles of a split cross LDS as pairs of 16-bit whole numbers (full sums up to 65535,
-// which the launcher checks); CONV: the convolution form (see Fp4Params); REG:
-// its segments travel through registers (see fetch_segment).
+// which the launcher checks); CONV: the convolution form (see Fp4Params); ODD:
+// its runs have an odd number of words (see issue_segment; "reg" in the kernel's name).
 // One instantiation per combination keeps each kernel's code short: the instruction cache
 // starts cold at every launch, and a launch lasts a few microseconds.
-template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool ODD>
 __global__ void __launch_bounds__(512)
 gemm_fp4_kernel(const Fp4Params p, const int S_arg
 #ifdef BMX_FP4_STAMPS
@@ -429,11 +427,8 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   const float alpha_lane = (CONV && p.alpha) ? p.alpha[min(m0 + lane, p.M - 1)] : 1.0f;
   const float thr_lane = (CONV && OUT == kOutBits && p.thr) ? p.thr[min(m0 + lane, p.M - 1)] : 0.0f;
 
-  uint4 nx[NB][2];  // REG: the next segment's words
-  if (seg_lo < seg_hi) {
-    if constexpr (REG) fetch_segment<NA, NB>(p, nx, voff, piece[0], piece[1], seg_lo);
-    else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo);
-  }
+  uint4 nx[2 * TN];  // ODD
+  if (seg_lo < seg_hi) issue_segment<NA, NB, CONV, ODD>(p, stage, &voff[0][0], piece[0], piece[1], seg_lo, nx);
   if constexpr (CONV && OUT == kOutBits) {
     // word tile_m of the output image's halo, spread over the tiles of this row of tiles
     if (p.opad > 0) {
@@ -461,11 +456,9 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
   for (int seg = seg_lo; seg < seg_hi; ++seg) {
     // the segment's words into registers (the compiler waits for the loads in flight: it tracks
     // LDS writes of the load unit)
-    if constexpr (REG) {
+    if (ODD && runs_meet(p, seg)) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) stage[b * 128 + t * 64 + lane] = nx[b][t];
+      for (int k = 0; k < 2 * TN; ++k) stage[NA * 128 + k * 64 + lane] = nx[k];
     }
     uint4 w[NB][2];
 #pragma unroll
@@ -507,15 +500,11 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
     // because the compiler waits for every pending load of the load unit before an LDS read it
     // knows of, both measured no faster with operands that really come from HBM: 9.5 and 9.9
     // against 9.5 us on the first fully connected layer.)
-    // (Through registers a segment is written by the wave itself, behind its reads.)
-    if (!REG) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #ifdef BMX_FP4_STAMPS
     if (seg == seg_lo) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); FP4_STAMP(2); }
 #endif
-    if (seg + 1 < seg_hi) {
-      if constexpr (REG) fetch_segment<NA, NB>(p, nx, voff, piece[0], piece[1], seg + 1);
-      else issue_segment<NA, NB, CONV>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1);
-    }
+    if (seg + 1 < seg_hi) issue_segment<NA, NB, CONV, ODD>(p, stage, &voff[0][0], piece[0], piece[1], seg + 1, nx);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int kg = 2 * seg + g;
@@ -901,16 +890,16 @@ gemm_fp4_kernel(const Fp4Params p, const int S_arg
 int gemm_fp4_half = 0;  // 2 = keep fp32 partials (tests of both forms)
 namespace {
 
-template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool REG>
+template <int PL, bool XNOR, int OUT, bool SPLIT, bool HALF, bool CONV, bool ODD>
 hipError_t launch_tile(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
   const int waves = SPLIT ? S : tiles_per_wg;
   const size_t lds = (size_t)waves * slot_size(PL, SPLIT, HALF) * 16 + (SPLIT && CONV && OUT == kOutBits ? 512 : 0);
-  auto kern = gemm_fp4_kernel<PL, XNOR, OUT, SPLIT, HALF, CONV, REG>;
+  auto kern = gemm_fp4_kernel<PL, XNOR, OUT, SPLIT, HALF, CONV, ODD>;
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
   note_kernel("gemm_fp4_kernel<%d,%d,%d,%s,%s%s> grid %lld x %d, K split %d%s, fp4", TM, TN, PL, XNOR ? "xnor" : "planes",
-              !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? (REG ? ",conv,reg" : ",conv") : (REG ? ",reg" : ""),
+              !XNOR ? "S" : (OUT == kOutF32 ? "f32" : (OUT == kOutI32 ? "i32" : "bits")), CONV ? (ODD ? ",conv,reg" : ",conv") : "",
               (long long)blocks, 64 * waves, SPLIT ? S : 1, SPLIT && HALF ? " (16-bit partials)" : "");
 #ifdef BMX_FP4_STAMPS
   launch_kernel(kern, dim3((unsigned)blocks), dim3(64 * waves), lds, s, p, S, fp4_stamps);
@@ -941,11 +930,11 @@ void set_tile_order(Fp4Params& p, int S) {
 // A full sum is at most (bits of K) x (2^planes - 1), a full count K: whether 16 bits hold them
 bool fits_16_bits(int64_t K, int planes) { return K * ((1 << planes) - 1) <= 65535; }
 
-template <int PL, bool XNOR, int OUT, bool CONV = false, bool REG = false>
+template <int PL, bool XNOR, int OUT, bool CONV = false, bool ODD = false>
 hipError_t launch_split(const Fp4Params& p, int S, int tiles_per_wg, int64_t blocks, hipStream_t s) {
-  if (S <= 1) return launch_tile<PL, XNOR, OUT, false, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
-  return fits_16_bits(p.Kreal, PL) && gemm_fp4_half != 2 ? launch_tile<PL, XNOR, OUT, true, true, CONV, REG>(p, S, tiles_per_wg, blocks, s)
-                                                        : launch_tile<PL, XNOR, OUT, true, false, CONV, REG>(p, S, tiles_per_wg, blocks, s);
+  if (S <= 1) return launch_tile<PL, XNOR, OUT, false, false, CONV, ODD>(p, S, tiles_per_wg, blocks, s);
+  return fits_16_bits(p.Kreal, PL) && gemm_fp4_half != 2 ? launch_tile<PL, XNOR, OUT, true, true, CONV, ODD>(p, S, tiles_per_wg, blocks, s)
+                                                        : launch_tile<PL, XNOR, OUT, true, false, CONV, ODD>(p, S, tiles_per_wg, blocks, s);
 }
 
 }  // namespace
@@ -965,8 +954,9 @@ int gemm_fp4_split = 0;  // 0 = automatic; settable for sweeps and for the tests
 //     undivided tile: one wave (1.5 / 1.03 / 1.00; four over one of 75 to 144 words 1.04 over 37 int32 products, 1.05 over 166 of
 //     fp32).  Four and eight keep the SIMDs of a CU level where it has several tiles (390 x 3329 x 5632, 371 tiles, takes 10.4 us over four
 //     waves, 15.1 over five, 12.2 over three).
-//     Convolutions of 75 words on go on with four to 1700 tiles (1.28 / 1.01 / 1.09), and from 2049 to 2350 (- / 1.01 / 1.10; between, - /
-//     1.09 / 1.04).
+//     Convolutions go on with four to 1700 tiles (45 to 72 words, time over one wave's of 200: 769 to 1024 0.88 to 0.95, 1281 to 1500 0.87 to
+//     0.92, 1501 to 1700 0.97 to 1.0; of 75 words on 1.28 / 1.01 / 1.09 for 8 / 4 / 1), and from 2049 to 2350 (0.93 to 0.96; - / 1.01 / 1.10;
+//     between, 1.08 to 1.14; - / 1.09 / 1.04).
 //   - three of 21 to 28 words (six or seven groups), up to two tiles a CU (3 / 2 / 1 waves, to 256 tiles 1.00 / 1.14 / 1.17, to 512
 //     bit planes 1.00 / 1.08 / 1.11, others 1.03 / 1.20 / 1.01; beyond, all 1.2 / 1.2 / 1.00).  Five
 //     groups, 20 words, are not worth dividing (2 / 1 1.03 / 1.01 to 256 tiles, 1.24 / 1.00 to 512).
@@ -978,7 +968,7 @@ static int choose_k_split(int64_t tiles, int kwords, Rows rows) {
   if (kwords < 29 && !patches) return tiles <= 512 ? 3 : 1;
   if (tiles <= 512) return 4;
   if (kwords < 34 && patches) return 1;
-  if (kwords >= 75 && patches) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
+  if (patches) return tiles <= 1700 || (tiles > 2048 && tiles <= 2350) ? 4 : 1;
   if (tiles <= 768 || (tiles > 1024 && tiles <= 1280)) return 4;
   return 1;
 }
@@ -1036,8 +1026,8 @@ bool launch_gemm_fp4(const void* A, int64_t lda_bytes, int planes, const int32_t
   p.nt = ldc % 32 == 0 && (((uintptr_t)C_i32 | (uintptr_t)C_f32) & 127) == 0;
   p.HoWo = p.Wo = p.Hp = p.Wpp = p.Cw = p.stride = 1;
   p.Nimg = p.Ho = p.opad = p.oHp = p.oWp = p.oCw = 0;
-  p.run_pieces = p.row_bytes = p.npieces = 1;
-  p.div_howo = p.div_wo = p.div_run = make_fast_div(1);
+  p.run = p.row_bytes = 1;
+  p.div_howo = p.div_wo = p.div_run = p.div_two_runs = make_fast_div(1);
   // (every wave of a split keeps at least one 64-byte segment)
   int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, Kwords, rowsum ? Rows::planes : Rows::direct);
   S = S > 8 ? 8 : S;
@@ -1080,7 +1070,7 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t P = (int64_t)Nimg * Ho * Wo;
   const int Hp = H + 2 * pad, Wpp = W + 2 * pad;
   if ((ld_words & 1) || ((uintptr_t)Wp & 15)) return false;
-  const bool reg = (Cw & 1) || ((uintptr_t)Xp & 15);  // a piece is not 16 contiguous, aligned bytes: word by word
+  const bool odd = (KW * Cw) & 1;
   if ((int64_t)kwords * 64 >= ((int64_t)1 << 24)) return false;
   if ((int64_t)Nimg * Hp * Wpp * Cw * 8 >= ((int64_t)1 << 32) || (int64_t)O * ld_words * 8 >= ((int64_t)1 << 32))
     return false;
@@ -1127,12 +1117,12 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   p.Wpp = Wpp;
   p.Cw = Cw;
   p.stride = stride;
-  p.run_pieces = (uint32_t)(reg ? KW * Cw : KW * Cw / 2);
+  p.run = (uint32_t)(KW * Cw);
   p.row_bytes = (uint32_t)((int64_t)Wpp * Cw * 8);
-  p.npieces = (uint32_t)(reg ? kwords : kwords / 2);
   p.div_howo = make_fast_div((uint32_t)(Ho * Wo));
   p.div_wo = make_fast_div((uint32_t)Wo);
-  p.div_run = make_fast_div(p.run_pieces);
+  p.div_run = make_fast_div(p.run);
+  p.div_two_runs = make_fast_div(2 * p.run);
   // (a wave may carry a single group of 256 bits)
   int S = gemm_fp4_split > 0 ? gemm_fp4_split : choose_k_split(tiles, kwords, Rows::patches);
   S = S > 8 ? 8 : S;
@@ -1145,10 +1135,10 @@ bool launch_conv_fp4(const uint64_t* Xp, int Nimg, int C, int H, int W, const ui
   const int64_t wgs = S > 1 ? tiles : ceil_div(tiles, tiles_per_wg);
   p.tiles_per_xcd = (int)ceil_div(wgs, 8);
   const int64_t blocks = 8 * (int64_t)p.tiles_per_xcd;
-  if (out_bits) *err = reg ? launch_split<1, true, kOutBits, true, true>(p, S, tiles_per_wg, blocks, s)
+  if (out_bits) *err = odd ? launch_split<1, true, kOutBits, true, true>(p, S, tiles_per_wg, blocks, s)
                            : launch_split<1, true, kOutBits, true>(p, S, tiles_per_wg, blocks, s);
-  else if (reg && out_i32) *err = launch_split<1, true, kOutI32, true, true>(p, S, tiles_per_wg, blocks, s);
-  else if (reg) *err = launch_split<1, true, kOutF32, true, true>(p, S, tiles_per_wg, blocks, s);
+  else if (odd && out_i32) *err = launch_split<1, true, kOutI32, true, true>(p, S, tiles_per_wg, blocks, s);
+  else if (odd) *err = launch_split<1, true, kOutF32, true, true>(p, S, tiles_per_wg, blocks, s);
   else if (out_i32) *err = launch_split<1, true, kOutI32, true>(p, S, tiles_per_wg, blocks, s);
   else *err = launch_split<1, true, kOutF32, true>(p, S, tiles_per_wg, blocks, s);
   return true;

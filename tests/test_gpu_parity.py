@@ -1891,6 +1891,39 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("N,C,H,W,O,k,s,p,shift", [
+    (3, 190, 13, 12, 70, 3, 1, 1, 0),   # runs of 9 words: two meet in one segment, and a last word alone
+    (3, 60, 12, 13, 40, 3, 2, 1, 0),    # runs of 3, shorter than half a segment
+    (2, 60, 15, 14, 65, 7, 1, 0, 0),    # runs of 7: in every segment
+    (2, 320, 9, 11, 129, 1, 2, 0, 0),   # one run, in one segment
+    (4, 300, 11, 9, 64, 5, 1, 2, 0),    # 5 runs of 25
+    (2, 420, 10, 10, 66, 7, 1, 3, 0),   # 7 runs of 49
+    (3, 250, 12, 11, 67, 3, 1, 1, 1),   # an even number of channel words in an image that starts on an odd word
+    (3, 190, 12, 11, 67, 3, 1, 1, 1),   # an odd one
+])
+def test_conv_odd_runs(N, C, H, W, O, k, s, p, shift):
+    """The 64 x 64 per wave convolution and the one that stages a row once per workgroup, where 16-byte pieces of a patch cross
+    from one kernel row to the next, or the image is 8-byte aligned only: every way of dividing K, every kind of result."""
+    rng = np.random.default_rng(N + C + H + O + k)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, k, k)).astype(np.float32)
+    alpha, thr = rng.standard_normal(O).astype(np.float32), rng.standard_normal(O).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, s, p, alpha)
+    ref_bits = B.pack_nchw(dev(np.where(rf >= thr[None, :, None, None], np.float32(1), np.float32(-1))), 1)
+    Wp, packed = B.pack_conv_weights(dev(w)), B.pack_nchw(dev(x), p)
+    # (the image ends where its memory does)
+    flat = torch.empty(packed.numel() + shift, dtype=packed.dtype, device="cuda")
+    xp = flat[shift:].view(packed.shape).copy_(packed)
+    for pin in ({"k10": 1}, {"k10": 4}, {"k10": 8}, {"k20": 2}, {"k20": 3}):
+        with tuned(k18=1, **(pin if "k20" in pin else {"k5": 6, **pin})):
+            got = B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, integer_out=True)
+            assert "gemm_fp4_kernel" in B.last_kernel()
+            np.testing.assert_array_equal(got.cpu().numpy(), ri)
+            got = B.binary_conv2d_packed(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha))
+            np.testing.assert_array_equal(got.cpu().numpy(), rf)
+            got = B.binary_conv2d_bits(xp, C, Wp, O, k, k, s, p, alpha=dev(alpha), thr=dev(thr), out_pad=1)
+            np.testing.assert_array_equal(got.cpu().numpy(), ref_bits.cpu().numpy())
+
+
 @pytest.mark.parametrize("form", [1, 2, 3])
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,opad", [
     (1, 1, 1, 1, 1, 1, 1, 0, 0),        # one word, one pixel

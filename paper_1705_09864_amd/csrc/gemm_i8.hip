@@ -172,7 +172,7 @@ struct I8Params {
   const uint4 *A, *B;  // tiles of the activations and of the weights
   int M, N, nk;        // nk: k steps, of 32 or (two values a byte) 64
   int mblocks, nblocks;
-  int tiles_m, tiles, tiles_per_xcd;
+  int tiles_m, tiles_n, tiles_per_xcd;
   int S;
   int ca, scale, rs, Kreal;
   float denom, inv;  // inv = 1 / denom
@@ -180,8 +180,20 @@ struct I8Params {
   float* C_f32;
   int64_t ldc;
   int s_base, s_rem;  // k steps per wave: s_base, the first s_rem waves one more
-  FastDiv div_tiles_m;
+  // tile order, see tile_of: 2^lg_bands bands of `band` rows of tiles
+  int lg_bands, band;
+  FastDiv div_band;
 };
+
+// Workgroup b sits on XCD b % 8.  Band i has the rows of tiles i, i + bands, i + 2 bands and so on, and each of its XCDs a run of
+// its tiles, down the rows first: what an XCD's L2 fetches of the operands is a band's rows and its run's columns.
+__device__ __forceinline__ bool tile_of(const I8Params& p, int* tile_m, int* tile_n) {
+  const int xcd = (int)(blockIdx.x & 7), lg = p.lg_bands;
+  const int at = (xcd >> lg) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
+  *tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)at, p.div_band));
+  *tile_m = (xcd & ((1 << lg) - 1)) + ((at - *tile_n * p.band) << lg);
+  return *tile_m < p.tiles_m && *tile_n < p.tiles_n;
+}
 
 // Where both operands have at most four bits (NIB), a step is of 64 k: a byte of its tile holds a level of the activations, or
 // s of the weight 2 s + 1, for k and for k + 128 of a block of 256.  A weight is multiplied as the byte 16 s + 8, one instruction
@@ -299,15 +311,13 @@ __global__ void __launch_bounds__(512)
 gemm_i8_kernel(const I8Params p) {
   extern __shared__ int red[];
   // (all arguments named at the top: fetched in one batch, one trip to memory instead of one per group)
-  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.mblocks), "s"(p.nblocks), "s"(p.tiles_m),
-               "s"(p.tiles), "s"(p.tiles_per_xcd), "s"(p.s_base), "s"(p.s_rem), "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1),
-               "s"(p.div_tiles_m.sh2));
+  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.mblocks), "s"(p.nblocks),
+               "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.tiles_per_xcd), "s"(p.s_base), "s"(p.s_rem), "s"(p.lg_bands), "s"(p.band),
+               "s"(p.div_band.mul), "s"(p.div_band.sh1), "s"(p.div_band.sh2));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // workgroup b sits on XCD b % 8: every XCD gets a contiguous run of tiles, rows of C fastest
-  const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (lin >= p.tiles) return;  // (the whole workgroup)
-  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)lin, p.div_tiles_m)), tile_m = lin - tile_n * p.tiles_m;
+  int tile_m, tile_n;
+  if (!tile_of(p, &tile_m, &tile_n)) return;  // (the whole workgroup)
   const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0);
 
   const uint4 *arow[TM], *brow[TN];  // (blocks past the matrix repeat its last one)
@@ -395,14 +405,14 @@ template <bool SUMS, bool NIB>
 __global__ void __launch_bounds__(512)
 gemm_i8_16_kernel(const I8Params p) {
   extern __shared__ int red[];
-  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.tiles_m), "s"(p.s_base), "s"(p.s_rem),
-               "s"(p.div_tiles_m.mul), "s"(p.div_tiles_m.sh1), "s"(p.div_tiles_m.sh2), "s"(p.tiles), "s"(p.tiles_per_xcd));
+  asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.M), "s"(p.N), "s"(p.nk), "s"(p.S), "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.tiles_per_xcd), "s"(p.s_base), "s"(p.s_rem),
+               "s"(p.lg_bands), "s"(p.band),
+               "s"(p.div_band.mul), "s"(p.div_band.sh1), "s"(p.div_band.sh2));
   static_assert(!(SUMS && NIB), "8 bits do not fit half a byte");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lin = (int)(blockIdx.x & 7) * p.tiles_per_xcd + (int)(blockIdx.x >> 3);
-  if (lin >= p.tiles) return;  // (the whole workgroup)
-  const int tile_n = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)lin, p.div_tiles_m)), tile_m = lin - tile_n * p.tiles_m;
+  int tile_m, tile_n;
+  if (!tile_of(p, &tile_m, &tile_n)) return;  // (the whole workgroup)
   const int k_lo = wave * p.s_base + min(wave, p.s_rem), k_hi = k_lo + p.s_base + (wave < p.s_rem ? 1 : 0);
   const int at = (lane >> 4) * 32 + (lane & 15);
   const uint4* const arow = p.A + (int64_t)(tile_m >> 1) * p.nk * 64 + (tile_m & 1) * 16 + at;
@@ -703,7 +713,32 @@ void fill_product(I8Params& p, int bits_a, int bits_w, int M, int N, int K, int3
 static void set_split(I8Params& p) {
   p.s_base = p.nk / p.S;
   p.s_rem = p.nk % p.S;
-  p.div_tiles_m = make_fast_div((uint32_t)p.tiles_m);
+}
+
+// One, two, four or eight bands, whichever has an XCD fetch the fewest rows of the operands where that is a fifth less than with one, and
+// 192 KB (1256 x 1024 x 366 of 2 x 2 bits, 147 KB less, 7.65 / 8.1 us).
+// (A band that is a row short leaves its XCDs idle for it: not where a CU then has a tile more than it would, which may be one more
+// than it holds at once: 1750 x 1472 x 552 of 2 x 8 bits 15.2 / 16.3 us.)
+// us a call in a graph, one band / as here: 753 x 128 x 4045 of 2 x 8 bits 15.2 / 9.5, 1129 x 64 x 4864 of 3 x 8 15.9 / 11.5, 1141 x 45 x 5376
+// of 2 x 4 11.1 / 8.6, 1833 x 343 x 2176 of 3 x 4 13.1 / 11.5; of some 130 drawn products with more than one 1.08 in the mean, 1.14 where an XCD
+// fetches 800 KB less.
+static void set_tile_order(I8Params& p, int tile_rows, int tile_cols) {
+  p.lg_bands = 0;
+  p.band = p.tiles_m;
+  const int most = (int)ceil_div(p.tiles_m * p.tiles_n, 8);
+  p.tiles_per_xcd = most;
+  const float one = (float)(p.tiles_m * tile_rows) + 0.125f * (float)(p.tiles_n * tile_cols);
+  float least = std::min(0.8f * one, one - 196608.0f / (32.0f * (float)p.nk));  // (a step is 32 bytes of a row)
+  for (int lg = 1; lg <= 3 && p.tiles_m >> lg; ++lg) {
+    const int band = (p.tiles_m + (1 << lg) - 1) >> lg, per = (band * p.tiles_n + (8 >> lg) - 1) >> (3 - lg);
+    const float fetched = (float)(band * tile_rows) + 0.125f * (float)((p.tiles_n * tile_cols) << lg);
+    if (fetched >= least || (per + 31) / 32 > (most + 31) / 32) continue;
+    least = fetched;
+    p.lg_bands = lg;
+    p.band = band;
+    p.tiles_per_xcd = per;
+  }
+  p.div_band = make_fast_div((uint32_t)p.band);
 }
 
 // The one-launch form, for any pair of bit widths; false when the problem is too large for it.
@@ -829,22 +864,21 @@ bool launch_quant_i8(const float* a, int64_t lda, int bits_a, const float* w, in
   const int64_t t16 = ceil_div(M, 16) * ceil_div(N, 16);
   if (t16 <= 384) {
     p.tiles_m = (int)ceil_div(M, 16);
-    p.tiles = (int)t16;
-    p.tiles_per_xcd = (int)ceil_div(t16, 8);
+    p.tiles_n = (int)ceil_div(N, 16);
+    set_tile_order(p, 16, 16);
     const int steps = p.nk / 2;
     p.S = std::min(8, steps);
     p.s_base = steps / p.S;
     p.s_rem = steps % p.S;
-    p.div_tiles_m = make_fast_div((uint32_t)p.tiles_m);
     *err = halves ? launch_i8_16<false, true>(p, s) : sums ? launch_i8_16<true, false>(p, s) : launch_i8_16<false, false>(p, s);
     return true;
   }
   const int64_t t12 = ceil_div(M, 32) * ceil_div(N, 64), t22 = ceil_div(M, 64) * ceil_div(N, 64);
   const int TM = K >= 5000 && t22 >= 128 ? 2 : 1, TN = TM == 2 || (K > 1100 && t12 >= 128) ? 2 : 1;
   p.tiles_m = (int)ceil_div(M, 32 * TM);
-  p.tiles = (int)(p.tiles_m * ceil_div(N, 32 * TN));
-  p.tiles_per_xcd = (int)ceil_div(p.tiles, 8);
-  const int64_t room = (TM * TN == 4 ? 8 : TM * TN == 2 ? 12 : 24) / ceil_div(p.tiles, 256);  // waves a workgroup
+  p.tiles_n = (int)ceil_div(N, 32 * TN);
+  set_tile_order(p, 32 * TM, 32 * TN);
+  const int64_t room = (TM * TN == 4 ? 8 : TM * TN == 2 ? 12 : 24) / ceil_div((int64_t)p.tiles_m * p.tiles_n, 256);  // waves a workgroup
   p.S = room >= 8 ? 8 : room >= 4 ? 4 : room >= 2 ? 2 : 1;
   while (p.S > 1 && p.S > 2 * q.kblocks) p.S /= 2;  // (each with 128 k at least)
   set_split(p);

@@ -723,6 +723,21 @@ def test_quant_bytes_16_by_16(M, N, K, form, ba, bw):
     np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
 
 
+@pytest.mark.parametrize("M,N,K,form", [(300, 40, 2200, "16 x 16"), (250, 70, 2500, "16 x 16"), (136, 40, 5300, "16 x 16"), (700, 150, 1000, "1,1"),
+                                        (610, 330, 1100, "1,1"), (440, 640, 2800, "1,2"), (1500, 140, 1300, "1,2")])
+@pytest.mark.parametrize("ba,bw", [(4, 3), (8, 2)])
+def test_quant_bytes_bands(M, N, K, form, ba, bw):
+    """The order of the tiles of a product of bytes in two, four and eight bands, rows that do not come out even among them."""
+    rng = np.random.default_rng(M + N + K + 10 * ba + bw)
+    a, w = rng.uniform(-0.1, 1.1, (M, K)).astype(np.float32), rng.uniform(-1.1, 1.1, (N, K)).astype(np.float32)
+    rS, _, r32 = oracle.quant_gemm(a, w, ba, bw)
+    with tuned(k7=3):  # (the pair of launches)
+        S, of = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw)
+        assert "gemm_i8_kernel<%s" % form in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(S.cpu().numpy(), rS)
+    np.testing.assert_array_equal(of.cpu().numpy(), r32)
+
+
 @pytest.mark.parametrize("M,N,K,T", [(16, 16, 4, 16), (1, 1, 63, 16), (17, 31, 64, 16), (15, 33, 65, 16), (256, 256, 129, 16), (256, 257, 512, 16),
                                      (256, 257, 513, 32), (512, 1024, 128, 16), (512, 1025, 128, 32), (30, 50, 2816, 16), (300, 240, 700, 32), (300, 240, 896, 32), (730, 1439, 31, 32)])
 @pytest.mark.parametrize("ba,bw", [(1, 1), (8, 1), (2, 2), (4, 7), (8, 3), (1, 8), (8, 8)])

@@ -36,6 +36,7 @@ struct SmallConvParams {
   int O, P, K, Kreal;  // filters, output pixels, words and bits of a patch
   int s_base, s_rem;   // steps of four words per wave: s_base, the first s_rem waves one more
   int run;             // words of a patch per kernel row
+  int blocks, per_xcd;  // blocks of 32 pixels, and how many of them in a row every XCD takes, or 0: all in the grid's order
   uint32_t row_bytes;  // from kernel row to kernel row in the image
   int HoWo, Wo, Hp, Wpp, Cw, stride;
   FastDiv div_howo, div_wo, div_run;
@@ -61,10 +62,12 @@ conv_small_kernel(const SmallConvParams p) {
   __shared__ uint32_t masks[S > 1 && OUT == kBits ? S : 1][32];
   asm volatile("" ::"s"(p.X), "s"(p.W), "s"(p.ldw), "s"(p.O), "s"(p.P), "s"(p.K), "s"(p.s_base), "s"(p.s_rem), "s"(p.run),
                "s"(p.row_bytes), "s"(p.HoWo), "s"(p.Wo), "s"(p.Hp), "s"(p.Wpp), "s"(p.Cw), "s"(p.stride), "s"(p.div_howo.mul),
-               "s"(p.div_howo.sh1), "s"(p.div_howo.sh2), "s"(p.div_wo.mul), "s"(p.div_wo.sh1), "s"(p.div_wo.sh2));
+               "s"(p.div_howo.sh1), "s"(p.div_howo.sh2), "s"(p.div_wo.mul), "s"(p.div_wo.sh1), "s"(p.div_wo.sh2), "s"(p.per_xcd));
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
   const int wave = S > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-  const int m0 = blockIdx.y * 32, q = blockIdx.x * 32 + r;
+  const int block = p.per_xcd ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  if (block * 32 >= p.P) return;  // (the whole workgroup)
+  const int m0 = blockIdx.y * 32, q = block * 32 + r;
   const int s0 = wave * p.s_base + min(wave, p.s_rem), s1 = s0 + p.s_base + (wave < p.s_rem ? 1 : 0);
   // (filters and pixels past the last repeat it; their results are not stored)
   const int qc = min(q, p.P - 1);
@@ -103,8 +106,8 @@ conv_small_kernel(const SmallConvParams p) {
 
   if (OUT == kBits && p.opad > 0 && (m0 & 63) == 0) {
     // word m0 / 64 of the output image's halo, spread over the workgroups of this filter tile
-    write_halo((uint64_t*)p.out, p.Nimg, p.Ho, p.Wo, p.opad, p.O, p.oCw, m0 >> 6, blockIdx.x * (64 * S) + threadIdx.x,
-               gridDim.x * (64 * S));
+    write_halo((uint64_t*)p.out, p.Nimg, p.Ho, p.Wo, p.opad, p.O, p.oCw, m0 >> 6, block * (64 * S) + threadIdx.x,
+               p.blocks * (64 * S));
   }
 
   v16f acc;
@@ -267,7 +270,14 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.oHp = Ho + 2 * out_pad;
   p.oWp = Wo + 2 * out_pad;
   p.oCw = (int)oCw;
-  const dim3 grid((unsigned)tiles_p, (unsigned)tiles_o);
+  p.blocks = (int)tiles_p;
+  // Workgroup b sits on XCD b % 8: with a run of pixels and all filters to itself an XCD fetches few rows of the image, and one that
+  // several blocks' patches share once (300 drawn convolutions and chains 1.03 in the mean; us in a graph, in the grid's order / so: 174 x 131 x
+  // 13 x 12 -> 81, 1 x 1, 9.0 / 7.75, 47 x 243 x 26 x 28 -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3).  Not
+  // where the runs do not come out even and a CU would have a workgroup more (51 x 53 pixels, 3 tiles of filters, 7 x 7, 7.1 / 9.2).
+  p.per_xcd = (int)ceil_div(tiles_p, 8);
+  if (ceil_div(p.per_xcd * tiles_o, 32) > ceil_div(tiles, 256)) p.per_xcd = 0;
+  const dim3 grid((unsigned)(p.per_xcd ? 8 * p.per_xcd : tiles_p), (unsigned)tiles_o);
   note_kernel("conv_small_kernel<%s> grid %u x %u x %d", out_bits ? "bits" : out_i32 ? "i32" : "f32", grid.x, grid.y, 64 * S);
   if (out_bits) launch_kind<kBits>(p, S, grid, s);
   else if (out_i32) launch_kind<kI32>(p, S, grid, s);

@@ -1906,6 +1906,27 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("N,C,H,W,O", [(1, 300, 3, 9, 40), (1, 300, 14, 16, 33), (1, 300, 15, 15, 70), (1, 300, 15, 17, 260), (1, 300, 16, 16, 130),
+                                       (7, 300, 14, 14, 300), (3, 300, 27, 29, 100)])
+def test_conv_small_runs_of_pixels(N, C, H, W, O):
+    """The small convolution's pixels in runs per XCD or in the grid's order: one block and less than eight, whole eighths, one block
+    more, where a CU would have a workgroup more; the halo written by runs that do not come out even."""
+    rng = np.random.default_rng(N + H + W + O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, 3, 3)).astype(np.float32)
+    alpha, thr = rng.standard_normal(O).astype(np.float32), rng.standard_normal(O).astype(np.float32)
+    ri, rf = oracle.binary_conv2d(x, w, 1, 1, alpha)
+    Wp, xp = B.pack_conv_weights(dev(w)), B.pack_nchw(dev(x), 1)
+    got = B.binary_conv2d_packed(xp, C, Wp, O, 3, 3, 1, 1, integer_out=True)
+    assert "conv_small_kernel" in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(got.cpu().numpy(), ri)
+    np.testing.assert_array_equal(B.binary_conv2d_packed(xp, C, Wp, O, 3, 3, 1, 1, alpha=dev(alpha)).cpu().numpy(), rf)
+    ref = B.pack_nchw(dev(np.where(rf >= thr[None, :, None, None], np.float32(1), np.float32(-1))), 1)
+    out = torch.full(ref.shape, -1, dtype=ref.dtype, device="cuda")
+    got = B.binary_conv2d_bits(xp, C, Wp, O, 3, 3, 1, 1, alpha=dev(alpha), thr=dev(thr), out_pad=1, out=out)
+    assert "conv_small_kernel" in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(got.cpu().numpy(), ref.cpu().numpy())
+
+
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,shift", [
     (3, 190, 13, 12, 70, 3, 1, 1, 0),   # runs of 9 words: two meet in one segment, and a last word alone
     (3, 60, 12, 13, 40, 3, 2, 1, 0),    # runs of 3, shorter than half a segment

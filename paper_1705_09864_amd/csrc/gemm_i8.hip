@@ -753,17 +753,19 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   const bool small = t16 <= 256 || (t16 <= 512 && K <= 512) || (t16 <= 2048 && K <= 128);
   // Where 16 x 16 of the result per workgroup are one a CU and the pair of launches can be had: fitted to 900 products of 18 to 77 steps of
   // 64 k, in us: a wave's steps and what the workgroups read (a row once per tile) on one side, the operands' way in once on the
-  // other.  By them the choice is 0.6 % behind the better form for two values a byte, 1.1 % else, as calls (the host makes two launches in
-  // 6.5 us at the least) and captured; by lines on the steps alone, set when the pair multiplied in tiles of 32 x 32, it was 1.2 to 2.2 %
+  // other.  By them the choice is 0.6 % behind the better form for two values a byte, 1.1 % else, as calls and captured; by lines on the steps alone, set when the pair multiplied in tiles of 32 x 32, it was 1.2 to 2.2 %
   // (by those / now, a call: 119 x 448 x 2240 of 2 x 1 bits 7.8 / 7.3 us, 43 x 1200 x 1900 of 4 x 4 7.9 / 7.1, 110 x 384 x 2690 of 8 x 8 9.6 /
   // 7.3).
+  // As calls the host makes two launches in 6.5 to 7.2 us, and one launch reads operands that are still in the L2s in less than
+  // estimated: up to 44 steps the pair has to be worth it (of 20 products between, 6.5 us and more estimated for one launch, on three sets of inputs in turn: 1.06 in
+  // the mean and 0.94 to 1.24 up to 7 us, 1.15 above; on one set 407 x 125 x 1792 of 8 x 1 bits 7.0 / 5.1).
   const bool halves = bits_a <= 4 && bits_w <= 4;
   const int64_t steps = small ? ceil_div(K, 64) : ceil_div(K, 32) * ceil_div(t32, 256);
   if (t16 <= 256 && pair) {
     const double read = 128e-6 * (double)t16 * K, input = 4e-6 * ((double)M + N) * K;  // MB
     const double one = halves ? 2.18 + 0.082 * steps + 0.044 * read : 2.50 + 0.083 * steps + 0.049 * read;
     const double two = halves ? 4.86 + 0.184 * input : 5.25 + 0.315 * input;
-    if (one > two && (one > 6.5 || capturing(s))) return false;
+    if (one > two && (one > (steps > 44 ? 6.5 : 7.5) || capturing(s))) return false;
   } else {
     // Steps of K per CU up to which one launch is ahead of the better pair of launches: 16 x 16 44; 32 x 32, a tile a CU or less, 20 to 28
     // 1.11 in a graph and 1.36 as calls, 28 to 36 1.00 and 1.15 (8 bits at 256 tiles 0.9: 486 x 512 x 990 of 3 x 8 8.8 / 7.1), 36 to 40

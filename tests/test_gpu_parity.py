@@ -754,8 +754,8 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
 
 
 @pytest.mark.parametrize("M,N,K,ba,bw,call,graph", [
-    (119, 448, 1231, 1, 1, True, True), (119, 448, 1232, 1, 1, True, False), (119, 448, 1669, 1, 1, True, False), (119, 448, 1670, 1, 1, False, False),
-    (119, 448, 1344, 8, 1, True, True), (119, 448, 1345, 8, 1, True, False), (119, 448, 1472, 8, 1, True, False), (119, 448, 1473, 8, 1, False, False),
+    (119, 448, 1231, 1, 1, True, True), (119, 448, 1232, 1, 1, True, False), (119, 448, 2072, 1, 1, True, False), (119, 448, 2073, 1, 1, False, False),
+    (119, 448, 1344, 8, 1, True, True), (119, 448, 1345, 8, 1, True, False), (119, 448, 1845, 8, 1, True, False), (119, 448, 1846, 8, 1, False, False),
     (30, 40, 2112, 4, 4, True, True), (30, 40, 2113, 4, 4, True, False), (30, 40, 3264, 4, 4, True, False), (30, 40, 3265, 4, 4, False, False),
     (90, 60, 2048, 2, 2, True, True), (90, 60, 2049, 2, 2, True, False), (241, 256, 1118, 2, 1, True, True), (241, 256, 1119, 2, 1, True, False),
     (1835, 24, 2158, 2, 8, True, True), (15, 17, 2816, 4, 4, True, True), (15, 17, 2817, 4, 4, False, False), (287, 256, 704, 2, 1, True, True),
@@ -1904,6 +1904,20 @@ def test_conv_fp4_odd_channel_words(N, C, H, W, O, k, s, p):
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, integer_out=True).cpu().numpy(), ri)
         assert "conv,reg" in B.last_kernel()
         np.testing.assert_array_equal(B.binary_conv2d(dev(x), Wp, O, k, k, s, p, alpha=dev(alpha)).cpu().numpy(), rf)
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 1001, 70), (257, 1001, 200), (320, 831, 64), (1000, 500, 65), (40, 8300, 130), (9000, 33, 64)])
+def test_gemm_small_parts_of_lines(M, N, K):
+    """The small product where tiles side by side share lines of the result: 256 tiles and more, eighths that do not come out even."""
+    rng = np.random.default_rng(M + N + K)
+    a, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    alpha = rng.standard_normal(N).astype(np.float32)
+    ri, rf = oracle.binary_fc(a, w, alpha)
+    A, W = B.binarize_pack(dev(a), 1), B.binarize_pack(dev(w), 1)
+    got = B.xnor_gemm(A, W, K)
+    assert "gemm_small_kernel" in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(got.cpu().numpy(), ri)
+    np.testing.assert_array_equal(B.binary_fc_packed(A, K, W, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
 @pytest.mark.parametrize("N,C,H,W,O", [(1, 300, 3, 9, 40), (1, 300, 14, 16, 33), (1, 300, 15, 15, 70), (1, 300, 15, 17, 260), (1, 300, 16, 16, 130),

@@ -83,7 +83,9 @@ def check_codegen():
     the convolution kernel with its filters in LDS reads each MFMA's filter operand with one
     ds_read_b128 (split into dword pairs, the rows meet four ways on the banks), holds one set of
     result stores for blocks inside the result and one for its edge, and spills no scalar registers
-    (its instructions come from a cold cache at every launch)."""
+    (its instructions come from a cold cache at every launch); and the 64 x 64 per wave product kernel
+    requests a segment at two places, ahead of its loop and in it, the last like any other (with a place of its own for a row's
+    last segment a launch waited up to 0.9 us for those instructions)."""
     import re
     isa_check = _isa_check()
     for src in SOURCES:
@@ -96,6 +98,9 @@ def check_codegen():
             allowed = 16 if "gemm_mfma_kernelILi2ELi2E" in name else 0
             if spills > allowed:
                 raise RuntimeError("%s: kernel %s spills %d vector registers" % (src, name, spills))
+            m = re.search(r"\d+gemm_fp4_kernelILi(\d+)ELb\dELi\dELb\dELb\dELb0ELb0E", name)
+            if m and src == "gemm_fp4.hip" and ops["global_load_lds_dwordx4"] != 2 * 4 * (int(m.group(1)) + 1):
+                raise RuntimeError("%s: kernel %s holds %d loads to LDS, expected two sets of them" % (src, name, ops["global_load_lds_dwordx4"]))
             m = re.search(r"conv_mfma_ws_kernelILi(\d+)ELi(\d+)E", name)
             if m and ops["ds_read_b128"] < int(m.group(1)) * int(m.group(2)):
                 raise RuntimeError("%s: kernel %s reads its filter operands with %d ds_read_b128, "

@@ -188,7 +188,7 @@ def kernel_stats(path):
         t = ln.strip()
         if name and t and not t.startswith((";", ".", "_Z")) and ":" not in t.split()[0]:
             body[name][t.split()[0]] += 1
-        if t.startswith("s_endpgm"):
+        if t.startswith(".Lfunc_end"):  # (an early exit's s_endpgm may stand in the middle)
             name = None
         m = re.match(r"^\s+\.name:\s+(\S+)", ln)
         if m:

@@ -67,13 +67,20 @@ def test_compiled_kernels_have_no_inflight_hazard():
 @pytest.mark.skipif(shutil.which(hip_build.HIPCC) is None and not os.path.exists(hip_build.HIPCC),
                     reason="hipcc not available")
 def test_compiled_kernels_keep_registers_and_wide_lds_reads():
-    """No vector-register spills, no scratch memory, and in the short-K convolution kernel one 16-byte LDS read
+    """No vector-register spills, no scratch memory, in the short-K convolution kernel one 16-byte LDS read
     per MFMA filter operand, one set of result stores for blocks inside the result and one for its edge, and no
-    scalar-register spills (see build.check_codegen)."""
+    scalar-register spills, and in the 64 x 64 per wave product kernel two sets of loads (see build.check_codegen)."""
     hip_build.check_scalar_loads()   # makes sure the device listings exist
     hip_build.check_codegen()
     stats = isa_check.kernel_stats(hip_build.device_asm("conv_mfma.hip"))
     assert any("conv_mfma_ws_kernelILi9ELi1E" in k for k in stats)
+
+
+def test_kernel_stats_count_behind_an_early_exit(tmp_path):
+    f = tmp_path / "k.s"
+    f.write_text("_Z4kernv:\n\ts_cbranch_scc1 .LBB0_2\n\ts_endpgm\n.LBB0_2:\n\tv_mov_b32_e32 v0, 0\n\ts_endpgm\n.Lfunc_end0:\n"
+                 "\tv_mov_b32_e32 v0, 0\n    .name:           _Z4kernv\n    .vgpr_spill_count: 0\n")
+    assert isa_check.kernel_stats(str(f))["_Z4kernv"] == (0, {"s_cbranch_scc1": 1, "s_endpgm": 2, "v_mov_b32_e32": 1})
 
 
 # a compare writes a mask and an asm statement reads it at the join behind a branch around the

@@ -536,11 +536,15 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   if (gemm_block == 0 && (gemm_engine || gemm_fp4_split || gemm_fp4_half || gemm_fp4_band)) return false;
   // rows of less than 16 bytes that the next begins in: dword by dword
   const bool short_rows = dwords < 4 && ((lda_bytes & 15) || (ldb_bytes & 15) || ((uintptr_t)A & 15) || ((uintptr_t)B & 15));
-  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128);
+  const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128), tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool lines = ldc % 32 == 0 && (((uintptr_t)C_i32 | (uintptr_t)C_f32) & 127) == 0;
-  // Against gemm_fp4.hip, from 1243 products of 150 to 4000 tiles and 4 to 160 words, rows on any word (the time there over the time
-  // here, in a graph; the choice by this rule is 0.45 % off the best): to 512 tiles, two a CU, K is divided over a CU's waves there
-  // (150 to 255 tiles 0.87, 256 to 383 0.90, 384 to 511 0.95 of 8 to 19 words, 0.97 of 20 to 59, 0.99 of 60 to 119, 1.02 beyond).
+  // Against gemm_fp4.hip by its tiles of 64 x 64, from 1400 products of 700 to 2700 of them and 8 to 128 words, rows on any word (the
+  // time there over the time here, in a graph; the choice by this rule is 0.37 % off the best, where it was 0.90 % with all of up to 512
+  // tiles of 128 x 128 left there: 4480 x 1792 x 5343 20.9 there, 19.6 here):
+  //   - to 1280 K is divided over a CU's waves there (0.75 to 0.87), or a SIMD has one undivided tile (769 to 1024 0.91).
+  //   - to 2048, undivided and up to two a SIMD, here from 70 words on, with fp32 results, scaled behind there as the waves finish one
+  //     by one, from 50 (int32 of 20 to 39 words 0.97, 40 to 59 0.98, 60 to 89 1.02, 90 on 1.05; fp32 0.99, 1.01, 1.03, 1.06; the lines
+  //     where two in a hundred lose more than 2 %), but not past 512 tiles of 128 x 128, two workgroups a CU (513 to 540 0.88).
   // Beyond, the products have to outweigh the results' way out, which takes longer where rows of C are parts of lines and
   // a tile of 64 x 64 is a better piece of it (whole lines: 8 to 19 words 0.98, 20 to 39 1.01, 40 on 1.04 to 1.12; parts: 0.87, 0.97,
   // 1.04 to 1.12).  Results that kernel's 32-bit indices do not reach are this one's (2048 x 2560 x 4096, rows 1048576
@@ -554,10 +558,11 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // 78 / 85, 6144 x 6144 x 4096 60.5 / 62.4, 7168 x 7168 x 4096 83.5 / 84.3 (in bursts 77 / 86); 8192 x 8192 x 1024 50 / 54.
   if (gemm_block == 0) {
     if (short_rows) {  // (the results are the time; up to here gemm_small.hip takes them)
-      if (ceil_div(M, 64) * ceil_div(N, 64) <= 512) return false;
+      if (tiles64 <= 512) return false;
     } else if (tiles < 256 || dwords < 22) {
       return false;
-    } else if ((tiles <= (dwords >= 240 ? 384 : 512) || dwords < (lines ? 38 : 64)) && gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) {
+    } else if ((tiles64 <= 1280 || (tiles64 <= 2048 ? tiles > 512 || dwords < (C_f32 ? 100 : 140) : dwords < (lines ? 38 : 64))) &&
+               gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) {
       return false;
     }
   }

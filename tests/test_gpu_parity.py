@@ -1496,11 +1496,15 @@ def test_gemm_fp4_block_form_longest_k(form):
     (1032, 1995, 3995, "w32", False), (2137, 971, 3163, "w32", False), (1142, 1962, 987, "w32", False),
     (1535, 1317, 3163, "w32", False), (2041, 1020, 3995, "w32", False), (64, 32000, 7003, "w32", False), (900, 1500, 29979, "w32", False),
     (129, 10300, 9003, "w32", False), (2690, 3130, 2019, "w32", True),
-    # to 512 tiles of 128 x 128 never (384 from 240 dwords on); past that from 64 dwords on, where rows of results are whole lines from 38
+    # to 1280 tiles of 64 x 64 never; to 2048 from 140 dwords on, fp32 from 100, up to 512 tiles of 128 x 128; past that from 64 dwords
+    # on, where rows of results are whole lines from 38
     (2048, 2048, 3499, "f32", False), (2000, 2040, 3500, "f32", False), (1900, 2500, 1664, "f32", False),
     (1900, 2500, 3584, "f32", False), (2041, 4090, 1664, "f32", False), (2690, 3130, 1664, "f32", False), (1900, 2500, 1664, "i32", False),
     (2041, 4090, 2048, "f32", False), (2053, 4090, 2048, "f32", True), (2053, 4090, 1984, "f32", False), (2053, 4064, 1280, "i32", True),
-    (2053, 4064, 1152, "i32", False), (2053, 3090, 7680, "i32", True), (2041, 3070, 7680, "i32", False), (2053, 3090, 7616, "i32", False)])
+    (2053, 4064, 1152, "i32", False), (2053, 3090, 7680, "i32", True), (2041, 3070, 7680, "i32", True), (2053, 3090, 7616, "i32", True),
+    (4480, 1792, 5343, "i32", True), (2041, 3070, 4480, "i32", True), (2041, 3070, 4416, "i32", False), (2041, 3070, 3200, "f32", True),
+    (2041, 3070, 3136, "f32", False), (2041, 2560, 7680, "f32", False), (2041, 2590, 7680, "f32", True), (1472, 5568, 7680, "i32", False),
+    (2041, 3070, 4447, "w32", False), (2041, 3070, 4449, "w32", True)])
 def test_block_form_lines(M, N, K, kind, block):
     """Both sides of the lines between the kernel that stages rows once per workgroup and the 64 x 64 per wave kernel: the
     form that runs, and the same results from the other."""

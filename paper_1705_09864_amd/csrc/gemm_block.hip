@@ -547,8 +547,10 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   //     where two in a hundred lose more than 2 %), but not past 512 tiles of 128 x 128, two workgroups a CU (513 to 540 0.88).
   // Beyond, the products have to outweigh the results' way out, which takes longer where rows of C are parts of lines and
   // a tile of 64 x 64 is a better piece of it (whole lines: 8 to 19 words 0.98, 20 to 39 1.01, 40 on 1.04 to 1.12; parts: 0.87, 0.97,
-  // 1.04 to 1.12).  Results that kernel's 32-bit indices do not reach are this one's (2048 x 2560 x 4096, rows 1048576
-  // apart, 15.1 here, 28.5 in gemm_mfma.hip, which would get them).
+  // 1.04 to 1.12).  What that kernel does not take (rows of less than 16 bytes, whose results are the time, and results that its
+  // 32-bit indices do not reach) is this one's whatever K, where gemm_small.hip does not take it and from 512 of those tiles on: gemm_mfma.hip,
+  // which would get it, takes 28.5 us for 2048 x 2560 x 4096, rows 1048576 apart, 15.1 here; x 256 15.3 / 6.9; of 21 dwords, widened first,
+  // 28.7 / 7.6; 1800 x 1300 x 960 9.3 / 7.5, x 16384 34.7 / 28.8; 100 tiles, 640 x 640 x 640 5.4 / 5.2, but x 8192 9.1 / 15.0.
   // The larger of the two shapes (us as 128 x 128 / as 256 x 128, each held for 50 ms): its waves read LDS and expand less for a
   // product, which shows once the chip's power has settled, where the results leave in whole lines and fill many rounds:
   // 8192 x 8192 x 8192 186 / 177, x 4096 106 / 102; 8192 x 12288 x 8192 277 / 263, 16384 x 8192 x 8192 370 / 352, 10240 x 10240 x
@@ -557,12 +559,9 @@ bool launch_gemm_block(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // x 15000 x 9000 261 / 262.  Below 4096 tiles it depends on the last round: 8192 x 6144 x 8192 143 / 132, but 5120 x 5120 x 8192
   // 78 / 85, 6144 x 6144 x 4096 60.5 / 62.4, 7168 x 7168 x 4096 83.5 / 84.3 (in bursts 77 / 86); 8192 x 8192 x 1024 50 / 54.
   if (gemm_block == 0) {
-    if (short_rows) {  // (the results are the time; up to here gemm_small.hip takes them)
-      if (tiles64 <= 512) return false;
-    } else if (tiles < 256 || dwords < 22) {
-      return false;
-    } else if ((tiles64 <= 1280 || (tiles64 <= 2048 ? tiles > 512 || dwords < (C_f32 ? 100 : 140) : dwords < (lines ? 38 : 64))) &&
-               gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) {
+    if (short_rows || !gemm_fp4_pays(M, N, lda_bytes, ldb_bytes, ldc, false)) {  // (gemm_fp4.hip does not take it)
+      if (tiles64 < 512) return false;
+    } else if (dwords < 22 || tiles64 <= 1280 || (tiles64 <= 2048 ? tiles > 512 || dwords < (C_f32 ? 100 : 140) : dwords < (lines ? 38 : 64))) {
       return false;
     }
   }

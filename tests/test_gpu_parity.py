@@ -1673,7 +1673,9 @@ def test_gemm_fp4_split_lines(tm, tn, words, split):
 
 
 @pytest.mark.parametrize("M,N,words,ldc,kernel", [(2048, 2560, 64, 1 << 20, "block"), (2048, 2560, 64, 1 << 19, "gemm_fp4_kernel<2,2,1,xnor,i32> "),
-                                                  (32, 32768, 6, 3 << 23, "gemm_small")])
+                                                  (32, 32768, 6, 3 << 23, "gemm_small"), (2048, 2560, 10, 1 << 20, "block"),
+                                                  (2048, 2560, 9, 1 << 20, "block"), (1472, 1472, 5, 3 << 19, "block"), (2048, 2560, 1, 1 << 20, "block"),
+                                                  (1408, 1472, 5, 3 << 19, "gemm_mfma")])
 def test_rows_of_c_far_apart(M, N, words, ldc, kernel):
     """Results in a matrix whose rows are further apart than gemm_fp4.hip's 32-bit indices reach: the kernels that would leave it
     such a product take it themselves, as they did."""
@@ -1684,7 +1686,14 @@ def test_rows_of_c_far_apart(M, N, words, ldc, kernel):
     B.xnor_gemm(A, W, 64 * words, out=room[:, :N])
     assert kernel in B.last_kernel(), B.last_kernel()
     with tuned(k7=1):
-        assert torch.equal(room[:, :N], B.xnor_gemm(A, W, 64 * words))
+        want = B.xnor_gemm(A, W, 64 * words)
+    assert torch.equal(room[:, :N], want)
+    if kernel == "block":  # rows on any dword are not widened first
+        a32, w32 = (t.view(torch.int32)[:, :2 * words - 1].contiguous() for t in (A, W))
+        B.xnor_gemm_w32(a32, w32, 64 * words - 32, out=room[:, :N])
+        assert kernel in B.last_kernel(), B.last_kernel()
+        with tuned(k7=1):
+            assert torch.equal(room[:, :N], B.xnor_gemm_w32(a32, w32, 64 * words - 32))
 
 
 @pytest.mark.parametrize("words,split", [(20, 1), (22, 3), (28, 3), (29, 4), (60, 4), (61, 8)])

@@ -208,7 +208,9 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const int64_t below = dwords > 40 || C_f32 ? 512
                       : C_bits               ? (steps == 1 ? 256 : 352)
                                              : (!whole ? 448 : steps == 1 ? 256 : 320);
-  // (packed bits of rows of less than 16 bytes have no other kernel of many tiles)
+  // (Packed bits of rows of less than 16 bytes that the next begins in, whatever the size: gemm_fp4.hip does not take them, and gemm_mfma.hip, which
+  // would, is behind.  us in a graph there / here: 3000 x 2001 x 64 14.4 / 8.3, 4096 x 4096 26.1 / 17.1, 60000 x 300 33.3 / 18.6, 8192 x 8192
+  // 88.9 / 52.7; dword by dword through registers gemm_fp4_kernel once took 9.6, 17.3, 22.4 and 61.2.)
   if ((work > most || tiles > 4096) && !(C_bits && dwords < 4 && !apart)) return false;
   if (pays && tiles64 >= below) return false;
   int S = 1;

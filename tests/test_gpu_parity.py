@@ -1933,6 +1933,22 @@ def test_gemm_small_parts_of_lines(M, N, K):
     np.testing.assert_array_equal(B.binary_fc_packed(A, K, W, alpha=dev(alpha)).cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("M,N,K", [(3000, 2001, 64), (3001, 1990, 61), (60000, 70, 33), (70, 60000, 64), (9000, 33, 1)])
+def test_bits_of_one_word_rows_of_many_tiles(M, N, K):
+    """Packed decisions of rows of one word, a word apart, past the small kernel's lines for other rows: it takes them whatever the size."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    x, w = (torch.randint(0, 2, (n, K), device="cuda", generator=g).float() * 2 - 1 for n in (M, N))
+    thr = torch.randint(-K, K + 1, (N,), device="cuda", generator=g).float()
+    alpha = torch.rand(N, device="cuda", generator=g) - 0.25
+    A, W = B.binarize_pack(x, 1), B.binarize_pack(w, 1)
+    out = torch.full((M, -(-N // 64) + 1), -1, dtype=torch.int64, device="cuda")
+    B.binary_fc_packed(A, K, W, alpha=alpha, mode="bits", thr=thr, out=out)
+    assert "gemm_small_kernel<bits>" in B.last_kernel(), B.last_kernel()
+    want = B.binarize_pack((alpha * (x @ w.T) >= thr).float() * 2 - 1, 1)  # (whole numbers, exact in fp32)
+    assert torch.equal(out[:, :-1], want) and bool((out[:, -1] == -1).all())
+
+
 @pytest.mark.parametrize("N,C,H,W,O", [(1, 300, 3, 9, 40), (1, 300, 14, 16, 33), (1, 300, 15, 15, 70), (1, 300, 15, 17, 260), (1, 300, 16, 16, 130),
                                        (7, 300, 14, 14, 300), (3, 300, 27, 29, 100)])
 def test_conv_small_runs_of_pixels(N, C, H, W, O):

@@ -751,21 +751,23 @@ bool launch_quant_small(const float* a, int64_t lda, int bits_a, const float* w,
   // 32 x 32 over that as 16 x 16, up to 256 tiles of 16 x 16 1.24 to 1.37; 257 to 512 1.08 to 1.26 up to a K of 512, 0.90 beyond; 513
   // to 2048 1.08 to 1.17 up to 128, 0.8 beyond).
   const bool small = t16 <= 256 || (t16 <= 512 && K <= 512) || (t16 <= 2048 && K <= 128);
-  // Where 16 x 16 of the result per workgroup are one a CU and the pair of launches can be had: fitted to 900 products of 18 to 77 steps of
-  // 64 k, in us: a wave's steps and what the workgroups read (a row once per tile) on one side, the operands' way in once on the
-  // other.  By them the choice is 0.6 % behind the better form for two values a byte, 1.1 % else, as calls and captured; by lines on the steps alone, set when the pair multiplied in tiles of 32 x 32, it was 1.2 to 2.2 %
-  // (by those / now, a call: 119 x 448 x 2240 of 2 x 1 bits 7.8 / 7.3 us, 43 x 1200 x 1900 of 4 x 4 7.9 / 7.1, 110 x 384 x 2690 of 8 x 8 9.6 /
-  // 7.3).
-  // As calls the host makes two launches in 6.5 to 7.2 us, and one launch reads operands that are still in the L2s in less than
-  // estimated: up to 44 steps the pair has to be worth it (of 20 products between, 6.5 us and more estimated for one launch, on three sets of inputs in turn: 1.06 in
-  // the mean and 0.94 to 1.24 up to 7 us, 1.15 above; on one set 407 x 125 x 1792 of 8 x 1 bits 7.0 / 5.1).
+  // Where 16 x 16 of the result per workgroup are one a CU and the pair of launches can be had: fitted to 900 products of 10 to 128 steps of
+  // 64 k, in us in a graph, in the mean of one set of inputs and three in turn (operands that the L2s still hold, and others): a wave's
+  // steps and what the workgroups read (a row once per tile) on one side, the operands' way in once and a wave's steps on the other.  By
+  // them the choice is 0.2 (two values a byte) and 0.4 % behind the better form.  As calls the pair takes 6.1 to 7.2 us whatever its
+  // size, process by process, which is what the host needs to make its launches: it has to be worth 6.65 and 6.8 (0.2 and 0.25 % behind with
+  // three sets, 0.6 and 0.5 with one; 6.4 0.3 to 1.0, 7.2 0.4).  What decides most of what is left is where the operands are, which nobody
+  // knows here (a call, one launch / two, three sets and one: 139 x 256 x 2432 of 8 x 1 bits 7.9 / 6.5 and 5.8 / 6.5, two; 407 x 125 x 1792 6.2 /
+  // 6.4 and 4.9 / 6.4, one).
+  // Of more steps, where the fit ends, two launches (16 x 1408 x 10000 of 8 x 1 20.7 / 18.4; of 150 products of 128 to 512 steps one launch was
+  // ahead of two once, by 5 %).
   const bool halves = bits_a <= 4 && bits_w <= 4;
   const int64_t steps = small ? ceil_div(K, 64) : ceil_div(K, 32) * ceil_div(t32, 256);
   if (t16 <= 256 && pair) {
     const double read = 128e-6 * (double)t16 * K, input = 4e-6 * ((double)M + N) * K;  // MB
-    const double one = halves ? 2.18 + 0.082 * steps + 0.044 * read : 2.50 + 0.083 * steps + 0.049 * read;
-    const double two = halves ? 4.86 + 0.184 * input : 5.25 + 0.315 * input;
-    if (one > two && (one > (steps > 44 ? 6.5 : 7.5) || capturing(s))) return false;
+    const double one = halves ? 2.46 + 0.0756 * steps + 0.0375 * read : 2.67 + 0.0808 * steps + 0.0366 * read;
+    const double two = halves ? 4.71 + 0.012 * steps + 0.145 * input : 4.81 + 0.0228 * steps + 0.196 * input;
+    if (steps > 128 || (one > two && (one > (halves ? 6.65 : 6.8) || capturing(s)))) return false;
   } else {
     // Steps of K per CU up to which one launch is ahead of the better pair of launches: 16 x 16 44; 32 x 32, a tile a CU or less, 20 to 28
     // 1.11 in a graph and 1.36 as calls, 28 to 36 1.00 and 1.15 (8 bits at 256 tiles 0.9: 486 x 512 x 990 of 3 x 8 8.8 / 7.1), 36 to 40

@@ -754,17 +754,26 @@ def test_quant_one_launch_tiles(M, N, K, T, ba, bw):
 
 
 @pytest.mark.parametrize("M,N,K,ba,bw,call,graph", [
-    (119, 448, 1231, 1, 1, True, True), (119, 448, 1232, 1, 1, True, False), (119, 448, 2072, 1, 1, True, False), (119, 448, 2073, 1, 1, False, False),
-    (119, 448, 1344, 8, 1, True, True), (119, 448, 1345, 8, 1, True, False), (119, 448, 1845, 8, 1, True, False), (119, 448, 1846, 8, 1, False, False),
-    (30, 40, 2112, 4, 4, True, True), (30, 40, 2113, 4, 4, True, False), (30, 40, 3264, 4, 4, True, False), (30, 40, 3265, 4, 4, False, False),
-    (90, 60, 2048, 2, 2, True, True), (90, 60, 2049, 2, 2, True, False), (241, 256, 1118, 2, 1, True, True), (241, 256, 1119, 2, 1, True, False),
-    (1835, 24, 2158, 2, 8, True, True), (15, 17, 2816, 4, 4, True, True), (15, 17, 2817, 4, 4, False, False), (287, 256, 704, 2, 1, True, True),
+    (119, 448, 1231, 1, 1, True, True), (119, 448, 1280, 1, 1, True, True), (119, 448, 1281, 1, 1, True, False), (119, 448, 1856, 1, 1, True, False),
+    (119, 448, 1857, 1, 1, False, False), (119, 448, 2072, 1, 1, False, False), (119, 448, 2304, 1, 1, False, False), (119, 448, 2305, 1, 1, False, False),
+    (119, 448, 1344, 8, 1, True, True), (119, 448, 1345, 8, 1, True, True), (119, 448, 1408, 8, 1, True, True), (119, 448, 1409, 8, 1, True, False),
+    (119, 448, 1779, 8, 1, True, False), (119, 448, 1780, 8, 1, False, False), (119, 448, 1846, 8, 1, False, False), (119, 448, 2432, 8, 1, False, False),
+    (119, 448, 2815, 8, 1, False, False), (119, 448, 2816, 8, 1, False, False),
+    (30, 40, 2112, 4, 4, True, True), (30, 40, 2240, 4, 4, True, True), (30, 40, 2241, 4, 4, True, False), (30, 40, 2816, 4, 4, True, False),
+    (30, 40, 3264, 4, 4, True, False), (30, 40, 3456, 4, 4, True, False), (30, 40, 3457, 4, 4, False, False), (30, 40, 2815, 4, 8, True, False),
+    (90, 60, 2048, 2, 2, True, True), (90, 60, 2176, 2, 2, True, True), (90, 60, 2177, 2, 2, True, False), (90, 60, 2688, 2, 2, True, False),
+    (90, 60, 2689, 2, 2, True, False), (90, 60, 3200, 2, 2, True, False), (90, 60, 3201, 2, 2, False, False),
+    (241, 256, 1118, 2, 1, True, True), (241, 256, 1119, 2, 1, True, True), (241, 256, 1152, 2, 1, True, True), (241, 256, 1153, 2, 1, True, False),
+    (241, 256, 1536, 2, 1, True, False), (241, 256, 1537, 2, 1, True, False), (241, 256, 1728, 2, 1, True, False), (241, 256, 1729, 2, 1, False, False),
+    (1835, 24, 2158, 2, 8, True, True), (139, 256, 2432, 8, 1, False, False), (27, 21, 3264, 1, 2, True, False), (407, 125, 1792, 8, 1, True, False),
+    (40, 64, 3072, 8, 8, True, False), (40, 64, 3073, 8, 8, False, False), (16, 2048, 8192, 8, 8, True, True), (16, 2048, 8193, 8, 8, False, False),
+    (15, 17, 2816, 4, 4, True, True), (15, 17, 2817, 4, 4, False, False), (287, 256, 704, 2, 1, True, True),
     (287, 256, 705, 2, 1, True, False), (287, 256, 896, 2, 1, True, True), (287, 256, 928, 2, 1, True, False), (500, 512, 704, 8, 2, True, True),
     (500, 512, 736, 8, 2, True, False), (500, 512, 576, 8, 2, True, True), (500, 512, 575, 8, 2, True, True), (500, 512, 577, 8, 2, True, False),
     (600, 512, 288, 3, 3, True, True), (600, 512, 289, 3, 3, True, False), (1125, 1216, 128, 8, 1, True, True), (1125, 1216, 129, 8, 1, False, False)])
 def test_quant_one_launch_or_two(M, N, K, ba, bw, call, graph):
-    """The lines between one launch and two, for calls and for calls that are being captured; replays between calls give what the
-    calls give."""
+    """The lines between one launch and two, for calls and for calls that are being captured, K up to where the choice ends; replays
+    between calls give what the calls give."""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + K)
     a = torch.rand((M, K), device="cuda", generator=g)

@@ -272,8 +272,10 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.oCw = (int)oCw;
   p.blocks = (int)tiles_p;
   // Workgroup b sits on XCD b % 8: with a run of pixels and all filters to itself an XCD fetches few rows of the image, and one that
-  // several blocks' patches share once (300 drawn convolutions and chains 1.03 in the mean; us in a graph, in the grid's order / so: 174 x 131 x
-  // 13 x 12 -> 81, 1 x 1, 9.0 / 7.75, 47 x 243 x 26 x 28 -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3).  Not
+  // several blocks' patches share once (us in a graph, in the grid's order / so: 174 x 131 x 13 x 12 -> 81, 1 x 1, 9.0 / 7.75, 47 x 243 x 26 x 28
+  // -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3).  520 drawn ones against the grid's order built alone: 1.02 in the
+  // mean from 64 blocks of pixels on, 1.00 to 1.01 from 32, below that 0.999 (of two and three blocks, which leave XCDs without any, 0.994; 3 x
+  // 238 x 10 x 10 -> 64, 7 x 7, ten of them, 7.66 / 7.86), where the grid's order chosen here is 0.994: the choice costs what it gives.  Not
   // where the runs do not come out even and a CU would have a workgroup more (51 x 53 pixels, 3 tiles of filters, 7 x 7, 7.1 / 9.2).
   p.per_xcd = (int)ceil_div(tiles_p, 8);
   if (ceil_div(p.per_xcd * tiles_o, 32) > ceil_div(tiles, 256)) p.per_xcd = 0;

@@ -15,6 +15,8 @@
 // Measured, us per launch in a graph, against the general kernels: 46 x 430 x 875 2.8 / 4.7, 250 x 250 x 250
 // 3.1 / 4.8, 703 x 143 x 384 3.1 / 5.5, 18 x 128 x 2624 2.9 / 4.4, 1000 x 300 x 2000 3.8 / 6.1, 64 x 4289 x 3633
 // 4.2 / 7.1, 32 x 4096 x 9216 5.0 / 6.7, 365 x 4117 x 516 5.6 / 8.0.
+#include <type_traits>
+
 #include "bmx_internal.h"
 
 namespace bmx {
@@ -33,14 +35,14 @@ struct SmallGemmParams {
   const char* B;
   uint32_t lda, ldb;  // bytes
   int M, N, Kd, Kreal;  // Kd dwords of data per row, zero bits behind the K-th
-  int tiles_n, per_xcd;         // tiles in a row that every XCD takes, or 0: all in the grid's order
-  int s_base, s_rem;            // steps of eight dwords per wave: s_base, the first s_rem waves one more
+  int tiles_n, s_base, s_rem;  // steps of eight dwords per wave: s_base, the first s_rem waves one more
   FastDiv div_tiles_n;
   const float* alpha;  // per column, or null
   const float* thr;    // packed bits: per column threshold, or null (0)
   void* C;             // fp32, int32, or packed bits in dwords
   int ldc;             // elements per row (packed bits: dwords)
   int as_count;
+  int per_xcd;         // tiles in a row that every XCD takes (RUNS)
 };
 
 __device__ __forceinline__ v8i plane(const v4u& w, int n) {
@@ -52,18 +54,21 @@ __device__ __forceinline__ v8i plane(const v4u& w, int n) {
   return e;
 }
 
-template <int OUT, int S>
+// RUNS: a run of tiles per XCD, else in the grid's order.  (A kernel of its own: as a choice in one kernel the others, whose first addresses
+// wait for it, lost 0.8 % in the mean and 2.7 % at 3 us.)
+template <int OUT, int S, bool RUNS>
 __global__ void __launch_bounds__(64 * S)
 gemm_small_kernel(const SmallGemmParams p) {
   __shared__ float sums[S > 1 ? S : 1][17][64];  // a wave's sixteen sums per lane and its popcounts
   asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.M), "s"(p.N), "s"(p.Kd), "s"(p.tiles_n), "s"(p.s_base),
-               "s"(p.s_rem), "s"(p.div_tiles_n.mul), "s"(p.div_tiles_n.sh1), "s"(p.div_tiles_n.sh2), "s"(p.per_xcd), "s"(p.alpha), "s"(p.thr));
+               "s"(p.s_rem), "s"(p.div_tiles_n.mul), "s"(p.div_tiles_n.sh1), "s"(p.div_tiles_n.sh2), "s"(p.alpha), "s"(p.thr));
+  if (RUNS) asm volatile("" ::"s"(p.per_xcd));
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
   const int wave = S > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-  const int tile = p.per_xcd ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int tile = RUNS ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   const int tile_m = (int)__builtin_amdgcn_readfirstlane(fast_div((uint32_t)tile, p.div_tiles_n));
   const int m0 = tile_m * 32, n0 = (tile - tile_m * p.tiles_n) * 32;
-  if (m0 >= p.M) return;  // (the whole workgroup)
+  if (RUNS && m0 >= p.M) return;  // (the whole workgroup)
   const int col = n0 + r, ncol = min(col, p.N - 1);
   // (rows past a matrix repeat its last; their results are not stored)
   const uint32_t arow = (uint32_t)min(m0 + r, p.M - 1) * p.lda, brow = (uint32_t)ncol * p.ldb;
@@ -165,8 +170,15 @@ gemm_small_kernel(const SmallGemmParams p) {
 
 template <int OUT>
 void launch_kind(const SmallGemmParams& p, int S, int64_t blocks, hipStream_t s) {
-  auto kern = S == 1 ? gemm_small_kernel<OUT, 1> : S == 2 ? gemm_small_kernel<OUT, 2> : S == 4 ? gemm_small_kernel<OUT, 4>
-            : S == 8 ? gemm_small_kernel<OUT, 8> : gemm_small_kernel<OUT, 16>;
+  auto of = [&](auto runs) {
+    constexpr bool R = decltype(runs)::value;
+    return S == 1 ? gemm_small_kernel<OUT, 1, R> : S == 2 ? gemm_small_kernel<OUT, 2, R> : S == 4 ? gemm_small_kernel<OUT, 4, R>
+         : S == 8 ? gemm_small_kernel<OUT, 8, R> : gemm_small_kernel<OUT, 16, R>;
+  };
+  auto kern = of(std::false_type{});
+  if constexpr (OUT != kBits) {
+    if (p.per_xcd) kern = of(std::true_type{});
+  }
   launch_kernel(kern, dim3((unsigned)blocks), dim3(64 * S), 0, s, p);
 }
 

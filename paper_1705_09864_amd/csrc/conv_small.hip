@@ -15,6 +15,8 @@
 // 36 -> 64 7x7 3.8 / 5.7, 20 x 258 x 9 x 11 -> 82 3x3 3.7 / 6.3 and as packed bits 4.1 / 11.3, 3 x 384 x 27 x 26 -> 64
 // 7x7 6.7 / 9.0 and 7.2 / 14.2.
 
+#include <type_traits>
+
 #include "bmx_internal.h"
 #include "halo.h"
 
@@ -36,7 +38,6 @@ struct SmallConvParams {
   int O, P, K, Kreal;  // filters, output pixels, words and bits of a patch
   int s_base, s_rem;   // steps of four words per wave: s_base, the first s_rem waves one more
   int run;             // words of a patch per kernel row
-  int blocks, per_xcd;  // blocks of 32 pixels, and how many of them in a row every XCD takes, or 0: all in the grid's order
   uint32_t row_bytes;  // from kernel row to kernel row in the image
   int HoWo, Wo, Hp, Wpp, Cw, stride;
   FastDiv div_howo, div_wo, div_run;
@@ -44,6 +45,7 @@ struct SmallConvParams {
   const float* thr;    // packed bits: per filter threshold, or null (0)
   void* out;           // fp32 or int32 NCHW, or the next convolution's packed image in dwords
   int Nimg, Ho, oHp, oWp, oCw, opad;  // packed image: its size, words per pixel, halo
+  int blocks, per_xcd;  // blocks of 32 pixels, and how many of them in a row every XCD takes (RUNS)
 };
 
 __device__ __forceinline__ v8i plane(const v4u& w, int n) {
@@ -55,18 +57,21 @@ __device__ __forceinline__ v8i plane(const v4u& w, int n) {
   return e;
 }
 
-template <int OUT, int S>
+// RUNS: a run of blocks of pixels per XCD, else in the grid's order.  (A kernel of its own: as a choice in one kernel the others, whose first
+// addresses wait for it, lost 0.6 % in the mean.)
+template <int OUT, int S, bool RUNS>
 __global__ void __launch_bounds__(64 * S)
 conv_small_kernel(const SmallConvParams p) {
   __shared__ float sums[S > 1 ? S : 1][17][64];  // a wave's sixteen sums per lane and its popcounts
   __shared__ uint32_t masks[S > 1 && OUT == kBits ? S : 1][32];
   asm volatile("" ::"s"(p.X), "s"(p.W), "s"(p.ldw), "s"(p.O), "s"(p.P), "s"(p.K), "s"(p.s_base), "s"(p.s_rem), "s"(p.run),
                "s"(p.row_bytes), "s"(p.HoWo), "s"(p.Wo), "s"(p.Hp), "s"(p.Wpp), "s"(p.Cw), "s"(p.stride), "s"(p.div_howo.mul),
-               "s"(p.div_howo.sh1), "s"(p.div_howo.sh2), "s"(p.div_wo.mul), "s"(p.div_wo.sh1), "s"(p.div_wo.sh2), "s"(p.per_xcd));
+               "s"(p.div_howo.sh1), "s"(p.div_howo.sh2), "s"(p.div_wo.mul), "s"(p.div_wo.sh1), "s"(p.div_wo.sh2));
+  if (RUNS) asm volatile("" ::"s"(p.per_xcd));
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
   const int wave = S > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
-  const int block = p.per_xcd ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-  if (block * 32 >= p.P) return;  // (the whole workgroup)
+  const int block = RUNS ? (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  if (RUNS && block * 32 >= p.P) return;  // (the whole workgroup)
   const int m0 = blockIdx.y * 32, q = block * 32 + r;
   const int s0 = wave * p.s_base + min(wave, p.s_rem), s1 = s0 + p.s_base + (wave < p.s_rem ? 1 : 0);
   // (filters and pixels past the last repeat it; their results are not stored)
@@ -193,8 +198,12 @@ conv_small_kernel(const SmallConvParams p) {
 
 template <int OUT>
 void launch_kind(const SmallConvParams& p, int S, dim3 grid, hipStream_t s) {
-  auto kern = S == 1 ? conv_small_kernel<OUT, 1> : S == 2 ? conv_small_kernel<OUT, 2> : S == 4 ? conv_small_kernel<OUT, 4>
-            : S == 8 ? conv_small_kernel<OUT, 8> : conv_small_kernel<OUT, 16>;
+  auto of = [&](auto runs) {
+    constexpr bool R = decltype(runs)::value;
+    return S == 1 ? conv_small_kernel<OUT, 1, R> : S == 2 ? conv_small_kernel<OUT, 2, R> : S == 4 ? conv_small_kernel<OUT, 4, R>
+         : S == 8 ? conv_small_kernel<OUT, 8, R> : conv_small_kernel<OUT, 16, R>;
+  };
+  auto kern = p.per_xcd ? of(std::true_type{}) : of(std::false_type{});
   launch_kernel(kern, grid, dim3(64 * S), 0, s, p);
 }
 
@@ -273,12 +282,12 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.blocks = (int)tiles_p;
   // Workgroup b sits on XCD b % 8: with a run of pixels and all filters to itself an XCD fetches few rows of the image, and one that
   // several blocks' patches share once (us in a graph, in the grid's order / so: 174 x 131 x 13 x 12 -> 81, 1 x 1, 9.0 / 7.75, 47 x 243 x 26 x 28
-  // -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3).  520 drawn ones against the grid's order built alone: 1.02 in the
-  // mean from 64 blocks of pixels on, 1.00 to 1.01 from 32, below that 0.999 (of two and three blocks, which leave XCDs without any, 0.994; 3 x
-  // 238 x 10 x 10 -> 64, 7 x 7, ten of them, 7.66 / 7.86), where the grid's order chosen here is 0.994: the choice costs what it gives.  Not
-  // where the runs do not come out even and a CU would have a workgroup more (51 x 53 pixels, 3 tiles of filters, 7 x 7, 7.1 / 9.2).
+  // -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3; 211 drawn ones of 32 blocks of pixels and more 1.014 in the mean).
+  // Not of few blocks, which leave XCDs without any (170 drawn ones of up to 80 0.999, some of two to twenty 0.98: 3 x 238 x 10 x 10 -> 64, 7 x 7,
+  // 7.66 / 7.86); and not where the runs do not come out even and a CU would have a workgroup more (51 x 53 pixels, 3 tiles of filters, 7 x 7,
+  // 7.1 / 9.2).
   p.per_xcd = (int)ceil_div(tiles_p, 8);
-  if (ceil_div(p.per_xcd * tiles_o, 32) > ceil_div(tiles, 256)) p.per_xcd = 0;
+  if (tiles_p < 48 || ceil_div(p.per_xcd * tiles_o, 32) > ceil_div(tiles, 256)) p.per_xcd = 0;
   const dim3 grid((unsigned)(p.per_xcd ? 8 * p.per_xcd : tiles_p), (unsigned)tiles_o);
   note_kernel("conv_small_kernel<%s> grid %u x %u x %d", out_bits ? "bits" : out_i32 ? "i32" : "f32", grid.x, grid.y, 64 * S);
   if (out_bits) launch_kind<kBits>(p, S, grid, s);

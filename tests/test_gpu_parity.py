@@ -1961,8 +1961,8 @@ def test_bits_of_one_word_rows_of_many_tiles(M, N, K):
 @pytest.mark.parametrize("N,C,H,W,O", [(1, 300, 3, 9, 40), (1, 300, 14, 16, 33), (1, 300, 15, 15, 70), (1, 300, 15, 17, 260), (1, 300, 16, 16, 130),
                                        (7, 300, 14, 14, 300), (3, 300, 27, 29, 100)])
 def test_conv_small_runs_of_pixels(N, C, H, W, O):
-    """The small convolution's pixels in runs per XCD or in the grid's order: one block and less than eight, whole eighths, one block
-    more, where a CU would have a workgroup more; the halo written by runs that do not come out even."""
+    """The small convolution: one block of pixels and less than eight, whole eighths, one block more; the halo written by blocks in the
+    grid's order, and by runs per XCD that do not come out even (74 blocks)."""
     rng = np.random.default_rng(N + H + W + O)
     x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, 3, 3)).astype(np.float32)
     alpha, thr = rng.standard_normal(O).astype(np.float32), rng.standard_normal(O).astype(np.float32)
@@ -1977,6 +1977,18 @@ def test_conv_small_runs_of_pixels(N, C, H, W, O):
     got = B.binary_conv2d_bits(xp, C, Wp, O, 3, 3, 1, 1, alpha=dev(alpha), thr=dev(thr), out_pad=1, out=out)
     assert "conv_small_kernel" in B.last_kernel(), B.last_kernel()
     np.testing.assert_array_equal(got.cpu().numpy(), ref.cpu().numpy())
+
+
+@pytest.mark.parametrize("N,C,H,W,O,grid", [(3, 130, 10, 10, 64, 10), (1, 130, 47, 32, 33, 47), (1, 130, 48, 32, 33, 48), (1, 130, 683, 3, 70, 72),
+                                            (1, 130, 683, 3, 480, 65), (8, 130, 23, 21, 100, 128)])
+def test_conv_small_order(N, C, H, W, O, grid):
+    """Pixels in runs per XCD, eight of one length, from 48 blocks on, and in the grid's order below and where a CU would have more."""
+    rng = np.random.default_rng(N + H + W + O)
+    x, w = rng.standard_normal((N, C, H, W)).astype(np.float32), rng.standard_normal((O, C, 1, 1)).astype(np.float32)
+    ri, _ = oracle.binary_conv2d(x, w, 1, 0)
+    got = B.binary_conv2d_packed(B.pack_nchw(dev(x), 0), C, B.pack_conv_weights(dev(w)), O, 1, 1, 1, 0, integer_out=True)
+    assert "conv_small_kernel<i32> grid %d x" % grid in B.last_kernel(), B.last_kernel()
+    np.testing.assert_array_equal(got.cpu().numpy(), ri)
 
 
 @pytest.mark.parametrize("N,C,H,W,O,k,s,p,shift", [

@@ -1719,12 +1719,14 @@ def test_plane_gemm_split_lines(bits, words, split):
     np.testing.assert_array_equal(f.cpu().numpy(), rS.astype(np.float32) / np.float32(2 ** bits - 1))
 
 
-@pytest.mark.parametrize("M,N,words,small", [(1024, 1216, 6, True), (1024, 1280, 6, False), (1024, 4032, 2, False), (1024, 1024, 28, True),
+@pytest.mark.parametrize("M,N,words,small", [(1024, 1216, 6, True), (1024, 1280, 6, True), (1024, 4032, 2, False), (1024, 1024, 28, True),
                                              (1024, 960, 30, False), (1024, 1024, 32, True), (1024, 1024, 34, False), (512, 512, 126, True),
                                              (512, 512, 130, False), (1024, 960, 32, False), (1024, 960, 31, False), (1024, 768, 46, False), (1024, 704, 47, False), (1024, 704, 53, False), (1024, 960, 39, False), (1024, 1024, 43, False),
-                                             (1024, 1024, 51, False), (1024, 1920, 24, True), (1024, 1728, 30, False), (1024, 1280, 20, False), (1024, 1216, 20, True),
-                                             (3200, 1024, 7, False), (3200, 1024, 9, False), (2560, 1024, 9, False), (1024, 1700, 8, True), (1024, 1760, 8, False),
-                                             (1024, 960, 4, True), (1024, 1024, 4, False), (1000, 1024, 4, True), (1000, 1728, 3, True), (1000, 1792, 3, False)])
+                                             (1024, 1024, 51, False), (1024, 1920, 24, True), (1024, 1728, 30, False), (1024, 1280, 20, True), (1024, 1216, 20, True),
+                                             (3200, 1024, 7, False), (3200, 1024, 9, False), (2560, 1024, 9, False), (1024, 1700, 8, True), (1024, 1760, 8, True),
+                                             (1024, 960, 4, True), (1024, 1024, 4, True), (1000, 1024, 4, True), (1000, 1728, 3, True), (1000, 1792, 3, True),
+                                             (1024, 1536, 6, True), (1024, 1600, 6, False), (1024, 1536, 3, True), (1024, 1600, 3, False), (1000, 2368, 7, True), (1000, 2432, 7, False),
+                                             (1000, 3136, 3, True), (1000, 3200, 3, False)])
 def test_gemm_small_lines(M, N, words, small):
     """Both sides of the lines between the kernel of 32 x 32 and those of larger tiles, rows of an even and of an odd number of words; the same results from the popcount kernel."""
     g = torch.Generator(device="cuda")
@@ -1734,6 +1736,20 @@ def test_gemm_small_lines(M, N, words, small):
     assert ("gemm_small" in B.last_kernel()) == small, B.last_kernel()
     with tuned(k7=1):
         assert torch.equal(got, B.xnor_gemm(A, W, 64 * words))
+
+
+@pytest.mark.parametrize("M,N,words,small", [(1024, 1984, 6, True), (1024, 2048, 6, False), (1000, 2752, 7, True), (1000, 2816, 7, False),
+                                             (1000, 3136, 3, True), (1000, 3200, 3, False)])
+def test_gemm_small_lines_of_fp32(M, N, words, small):
+    """The same for fp32 results, scaled by a power of two per column."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + words)
+    A, W = (torch.randint(-2 ** 62, 2 ** 62, (n, words), device="cuda", generator=g) for n in (M, N))
+    alpha = 2.0 ** torch.randint(-3, 4, (N,), device="cuda", generator=g).float()
+    got = B.binary_fc_packed(A, 64 * words, W, alpha=alpha)
+    assert ("gemm_small" in B.last_kernel()) == small, B.last_kernel()
+    with tuned(k7=1):
+        assert torch.equal(got, B.xnor_gemm(A, W, 64 * words).float() * alpha)
 
 
 @pytest.mark.parametrize("O", [5, 33, 63, 64, 70])

@@ -41,6 +41,7 @@
 
 #include "bmx_internal.h"
 #include "halo.h"
+#include "row_pieces.h"
 
 namespace bmx {
 
@@ -143,14 +144,12 @@ gemm_fp4_kernel(const BlockParams p) {
   const int piece16 = (lane & 3) ^ ((lane >> 3) & 3);
   const int dw4[2] = {4 * (((lane & 15) >> 2) ^ (lane >> 5)) + (lane & 3), 4 * (((lane & 15) >> 2) ^ (2 + (lane >> 5))) + (lane & 3)};
   const int last0 = 16 * (p.nseg - 1) - (p.Kd - 1);
-  // (Rows of a product: a piece that the row ends in, and those behind it, are the row's last 16 bytes: nothing behind a row is read,
-  // which may be where the buffer ends.  That is up to 12 bytes in front of the segment: A and B are 16 bytes lower than the operands and
-  // all offsets 16 more, so that none is negative.  Rows of less than 16 bytes are whole pieces, which their stride holds, and filters
-  // of a convolution have them too.)
+  // (Rows of a product: A and B are 16 bytes lower than the operands and all offsets 16 more, so that none is negative.  Filters of a
+  // convolution are whole pieces.)
   constexpr uint32_t kLower = lowered(CONV, LW);
   const bool part_pieces = !CONV && LW == 16 && p.Kd >= 4;
   const uint32_t sub16 = CONV ? (last0 + 4 * piece16 > 0 ? 16u * piece16 : 0u)
-                              : 4u * (uint32_t)max(last0 + 4 * piece16 + (p.Kd < 4 ? p.Kd - 1 : 3), 0);
+                              : piece_back(p.nseg - 1, piece16, p.Kd);
   const uint32_t sub4[2] = {last0 + dw4[0] > 0 ? 4u * (last0 + dw4[0]) : 0u, last0 + dw4[1] > 0 ? 4u * (last0 + dw4[1]) : 0u};
   // offset of the lane's first load of each half block in segment 0 (LW 4: of its first two loads; the other two are eight rows on)
   uint32_t va[HA][2], vb[CONV ? 1 : HB][2];
@@ -208,13 +207,7 @@ gemm_fp4_kernel(const BlockParams p) {
     const uint32_t w = d >> 1, run = fast_div(w, p.div_run);
     return run * p.row_bytes + (w - run * p.run) * 8u + (d & 1u) * 4u;
   };
-  // whether a piece of segment seg of a patch holds words of two runs, or the patch's last word alone: an odd multiple of an odd run
-  // lies among its words
-  auto runs_meet = [&](int seg) {
-    const uint32_t end = 8u * (uint32_t)seg + 7u;
-    if (!(p.run & 1u) || end < p.run) return false;
-    return p.run * (2u * fast_div(end - p.run, p.div_two_runs) + 1u) >= 8u * (uint32_t)seg;
-  };
+  auto meet = [&](int seg) { return runs_meet(p.run, [&](uint32_t x) { return fast_div(x, p.div_two_runs); }, seg); };
   // Requests segment seg of the wave's half blocks into stage buf.
   auto issue = [&](int seg, int buf) {
     const bool last = tail && seg + 1 == p.nseg;
@@ -226,7 +219,7 @@ gemm_fp4_kernel(const BlockParams p) {
     if constexpr (!CONV) {
 #pragma unroll
       for (int k = 0; k < HB; ++k) load_rows(tob + 1024u * k, p.B + (uint32_t)seg * 64u, vb[k], LW, p.ldb, p.N, last);
-    } else if (LW == 16 || !runs_meet(seg)) {
+    } else if (LW == 16 || !meet(seg)) {
       const uint32_t d = 16u * (uint32_t)seg + 4u * piece16;
       const uint32_t at = in_patch(d < (uint32_t)p.Kd ? d : 16u * (uint32_t)seg);
 #pragma unroll
@@ -345,7 +338,7 @@ gemm_fp4_kernel(const BlockParams p) {
   }
   if (p.nseg > 1) {
     constexpr int kLoads = HA * (LWA == 16 ? 1 : 4) + HB * (LW == 16 ? 1 : 4);  // a wave's loads of segment 1
-    if (CONV && LW == 4 && !runs_meet(1)) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(HA + HB) : "memory");
+    if (CONV && LW == 4 && !meet(1)) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(HA + HB) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kLoads) : "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");

@@ -55,6 +55,7 @@
 
 #include "bmx_internal.h"
 #include "halo.h"
+#include "row_pieces.h"
 
 namespace bmx {
 
@@ -151,12 +152,8 @@ __device__ __forceinline__ int add_popcount4(int acc, const uint4& w) {
   return acc;
 }
 
-// Whether a piece of segment `seg` of an im2col row holds words of two runs, or the row's last word alone: an odd multiple of an odd
-// run lies among its words.
 __device__ __forceinline__ bool runs_meet(const Fp4Params& p, int seg) {
-  const uint32_t end = 8u * (uint32_t)seg + 7u;
-  if (!(p.run & 1u) || end < p.run) return false;
-  return p.run * (2u * fast_div(end - p.run, p.div_two_runs) + 1u) >= 8u * (uint32_t)seg;
+  return bmx::runs_meet(p.run, [&](uint32_t x) { return fast_div(x, p.div_two_runs); }, seg);
 }
 
 // Request segment `seg` (64 bytes of every row of the wave's NB staged blocks) into the staging
@@ -169,15 +166,12 @@ template <int NA, int NB, bool CONV, bool ODD>
 __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, const uint32_t* voff /* [NB][2] */,
                                               int piece0, int piece1, int seg, uint4* nx /* [NB - NA][2] */) {
   if constexpr (!CONV) {
-    // A piece that the row ends in, and those behind it, are the row's last 16 bytes: nothing behind a row is read, which may be where
-    // the buffer ends (rows of less are 16 bytes apart).  That is up to 12 bytes in front of the segment: A and B are 16 bytes lower than
-    // the operands and voff 16 more, so that no offset is below zero, which would be one of 4 GB.  (One set of loads for all segments:
-    // with one of its own for the last, whose instructions nothing had fetched yet, 2752 x 1984 x 1408 took 9.0 us and not 8.1.)
+    // (A and B are 16 bytes lower than the operands and voff 16 more, so that no offset is below zero, which would be one of 4 GB.
+    // One set of loads for all segments: with one of its own for a row's last, whose instructions nothing had fetched yet, 2752 x 1984 x
+    // 1408 took 9.0 us and not 8.1.)
     const char* const abase = (const char*)p.A + (uint32_t)seg * 64u;
     const char* const bbase = (const char*)p.B + (uint32_t)seg * 64u;
-    uint32_t back[2];  // (0 for whole pieces)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) back[t] = 4u * (uint32_t)max(16 * seg + 4 * (t ? piece1 : piece0) + 4 - max(p.Kd, 4), 0);
+    const uint32_t back[2] = {piece_back(seg, piece0, p.Kd), piece_back(seg, piece1, p.Kd)};
 #pragma unroll
     for (int b = NB - 1; b >= 0; --b)  // (B first: its rows are the ones that come from far away)
 #pragma unroll

@@ -85,7 +85,8 @@ def check_codegen():
     result stores for blocks inside the result and one for its edge, and spills no scalar registers
     (its instructions come from a cold cache at every launch); and the 64 x 64 per wave product kernel
     requests a segment at two places, ahead of its loop and in it, the last like any other (with a place of its own for a row's
-    last segment a launch waited up to 0.9 us for those instructions)."""
+    last segment a launch waited up to 0.9 us for those instructions), and undivided puts its packed words together with one
+    v_writelane_b32 a half word (which the source reaches by the name of the compiler's intrinsic) and one store; no kernel calls a function."""
     import re
     isa_check = _isa_check()
     for src in SOURCES:
@@ -101,6 +102,11 @@ def check_codegen():
             m = re.search(r"\d+gemm_fp4_kernelILi(\d+)ELb\dELi\dELb\dELb\dELb0ELb0E", name)
             if m and src == "gemm_fp4.hip" and ops["global_load_lds_dwordx4"] != 2 * 4 * (int(m.group(1)) + 1):
                 raise RuntimeError("%s: kernel %s holds %d loads to LDS, expected two sets of them" % (src, name, ops["global_load_lds_dwordx4"]))
+            if m and src == "gemm_fp4.hip" and "ILi1ELb1ELi2ELb0E" in name and (ops["v_writelane_b32"], ops["global_store_dwordx2"]) != (128, 1):
+                raise RuntimeError("%s: kernel %s makes its packed words with %d v_writelane_b32 and %d stores, expected 128 and one" %
+                                   (src, name, ops["v_writelane_b32"], ops["global_store_dwordx2"]))
+            if any(op.startswith("s_swappc") for op in ops):
+                raise RuntimeError("%s: kernel %s calls a function" % (src, name))
             m = re.search(r"conv_mfma_ws_kernelILi(\d+)ELi(\d+)E", name)
             if m and ops["ds_read_b128"] < int(m.group(1)) * int(m.group(2)):
                 raise RuntimeError("%s: kernel %s reads its filter operands with %d ds_read_b128, "

@@ -69,7 +69,8 @@ def test_compiled_kernels_have_no_inflight_hazard():
 def test_compiled_kernels_keep_registers_and_wide_lds_reads():
     """No vector-register spills, no scratch memory, in the short-K convolution kernel one 16-byte LDS read
     per MFMA filter operand, one set of result stores for blocks inside the result and one for its edge, and no
-    scalar-register spills, and in the 64 x 64 per wave product kernel two sets of loads (see build.check_codegen)."""
+    scalar-register spills, in the 64 x 64 per wave product kernel two sets of loads and packed words made by
+    v_writelane_b32, and no calls (see build.check_codegen)."""
     hip_build.check_scalar_loads()   # makes sure the device listings exist
     hip_build.check_codegen()
     stats = isa_check.kernel_stats(hip_build.device_asm("conv_mfma.hip"))

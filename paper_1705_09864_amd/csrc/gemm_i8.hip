@@ -642,14 +642,16 @@ hipError_t launch_i8(const I8Params& p, hipStream_t s) {
   static std::atomic<bool> asked[64];
   const hipError_t e = allow_lds((const void*)kern, lds, asked);
   if (e != hipSuccess) return e;
-  note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d", TM, TN, SUMS ? ",sums" : NIB ? ",halves" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
+  note_kernel("gemm_i8_kernel<%d,%d%s> grid %d x %d, K split %d, bands %d", TM, TN, SUMS ? ",sums" : NIB ? ",halves" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S,
+              1 << p.lg_bands);
   launch_kernel(kern, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), lds, s, p);
   return launch_error();
 }
 
 template <bool SUMS, bool NIB>
 hipError_t launch_i8_16(const I8Params& p, hipStream_t s) {
-  note_kernel("gemm_i8_kernel<16 x 16%s> grid %d x %d, K split %d", SUMS ? ",sums" : NIB ? ",halves" : "", 8 * p.tiles_per_xcd, 64 * p.S, p.S);
+  note_kernel("gemm_i8_kernel<16 x 16%s> (gemm_i8_16_kernel) grid %d x %d, K split %d, bands %d", SUMS ? ",sums" : NIB ? ",halves" : "",
+              8 * p.tiles_per_xcd, 64 * p.S, p.S, 1 << p.lg_bands);
   launch_kernel(gemm_i8_16_kernel<SUMS, NIB>, dim3((unsigned)(8 * p.tiles_per_xcd)), dim3(64 * p.S), (size_t)p.S * (1024 + (SUMS ? 128 : 0)), s, p);
   return launch_error();
 }

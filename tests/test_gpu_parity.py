@@ -723,17 +723,18 @@ def test_quant_bytes_16_by_16(M, N, K, form, ba, bw):
     np.testing.assert_array_equal(of.cpu().numpy(), r32)  # (the division, to the last bit)
 
 
-@pytest.mark.parametrize("M,N,K,form", [(300, 40, 2200, "16 x 16"), (250, 70, 2500, "16 x 16"), (136, 40, 5300, "16 x 16"), (700, 150, 1000, "1,1"),
-                                        (610, 330, 1100, "1,1"), (440, 640, 2800, "1,2"), (1500, 140, 1300, "1,2")])
+@pytest.mark.parametrize("M,N,K,form,bands", [(300, 40, 2200, "16 x 16", 8), (250, 70, 2500, "16 x 16", 4), (136, 40, 5300, "16 x 16", 4), (700, 150, 1000, "1,1", 8),
+                                              (610, 330, 1100, "1,1", 4), (440, 640, 2800, "1,2", 2), (1500, 140, 1300, "1,2", 8),
+                                              (256, 384, 513, "16 x 16", 1), (176, 560, 600, "1,1", 1), (700, 700, 5200, "1,2", 2)])
 @pytest.mark.parametrize("ba,bw", [(4, 3), (8, 2)])
-def test_quant_bytes_bands(M, N, K, form, ba, bw):
-    """The order of the tiles of a product of bytes in two, four and eight bands, rows that do not come out even among them."""
+def test_quant_bytes_bands(M, N, K, form, bands, ba, bw):
+    """The order of the tiles of a product of bytes in one band, two, four and eight, rows that do not come out even among them."""
     rng = np.random.default_rng(M + N + K + 10 * ba + bw)
     a, w = rng.uniform(-0.1, 1.1, (M, K)).astype(np.float32), rng.uniform(-1.1, 1.1, (N, K)).astype(np.float32)
     rS, _, r32 = oracle.quant_gemm(a, w, ba, bw)
     with tuned(k7=3):  # (the pair of launches)
         S, of = B.quant_gemm(dev(a), dev(w), ba, bits_w=bw)
-        assert "gemm_i8_kernel<%s" % form in B.last_kernel(), B.last_kernel()
+        assert "gemm_i8_kernel<%s" % form in B.last_kernel() and B.last_kernel().endswith("bands %d" % bands), B.last_kernel()
     np.testing.assert_array_equal(S.cpu().numpy(), rS)
     np.testing.assert_array_equal(of.cpu().numpy(), r32)
 

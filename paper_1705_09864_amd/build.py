@@ -84,8 +84,8 @@ def check_codegen():
     ds_read_b128 (split into dword pairs, the rows meet four ways on the banks), holds one set of
     result stores for blocks inside the result and one for its edge, and spills no scalar registers
     (its instructions come from a cold cache at every launch); and the 64 x 64 per wave product kernel
-    requests a segment at two places, ahead of its loop and in it, the last like any other (with a place of its own for a row's
-    last segment a launch waited up to 0.9 us for those instructions), and undivided puts its packed words together with one
+    requests a segment at two places, ahead of its loop and in it, the last like any other (a place of its own for a row's
+    last segment cost a launch up to 0.9 us), and undivided puts its packed words together with one
     v_writelane_b32 a half word (which the source reaches by the name of the compiler's intrinsic) and one store; no kernel calls a function."""
     import re
     isa_check = _isa_check()

@@ -281,8 +281,8 @@ bool launch_conv_small(const uint64_t* Xp, int Nimg, int C, int H, int W, const 
   p.oCw = (int)oCw;
   p.blocks = (int)tiles_p;
   // Workgroup b sits on XCD b % 8: with a run of pixels and all filters to itself an XCD fetches few rows of the image, and one that
-  // several blocks' patches share once (us in a graph, in the grid's order / so: 174 x 131 x 13 x 12 -> 81, 1 x 1, 9.0 / 7.75, 47 x 243 x 26 x 28
-  // -> 64, 3 x 3 / 2, 10.8 / 9.6, 159 x 64 x 19 x 19 -> 64, 7 x 7 / 2, 7.9 / 7.3; 211 drawn ones of 32 blocks of pixels and more 1.014 in the mean).
+  // several blocks' patches share once (us in a graph, in the grid's order / so: 47 x 243 x 26 x 28 -> 64, 3 x 3 / 2, 4.65 / 4.46, 100 x 320 x
+  // 14 x 14 -> 64, 1 x 1, 4.75 / 4.38; 211 drawn ones of 32 blocks of pixels and more 1.014 in the mean).
   // Not of few blocks, which leave XCDs without any (170 drawn ones of up to 80 0.999, some of two to twenty 0.98: 3 x 238 x 10 x 10 -> 64, 7 x 7,
   // 7.66 / 7.86); and not where the runs do not come out even and a CU would have a workgroup more (51 x 53 pixels, 3 tiles of filters, 7 x 7,
   // 7.1 / 9.2).

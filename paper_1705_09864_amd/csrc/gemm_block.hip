@@ -20,8 +20,8 @@
 //   - The operands of the next plane of bits are made between the products of this one (sched_barrier: left to
 //     itself the compiler makes them all at once, and then multiplies with the vector ALU idle).
 //   - Two waves share every block of rows; each counts the bits of half its blocks.
-//   - Rows may start on any dword, which is all that loads of 16 bytes need (dword by dword, four times the loads, 768 x 6619 x
-//     2240 took 15.4 us, now 12.3; 4224 x 4736 x 1600 23.1 / 22.4; 7934 x 1472 x 3008 19.7 / 18.3).
+//   - Rows may start on any dword, which is all that loads of 16 bytes need (dword by dword, four times the loads, 4224 x
+//     4736 x 1600 took 23.8 us, now 22.8).
 //   - The convolution form gathers the im2col rows of 128 (256) pixels from the packed image, 16 bytes at a
 //     time (a dword in segments that hold a piece of two runs of an odd number of words), once for 128 (64) filters; where the patches start stands in LDS.  Its results are fp32, int32 or
 //     the next convolution's packed image, halo included.

@@ -27,7 +27,8 @@
 //     Which 16-byte piece a lane fetches is permuted (piece = slot xor ((row >> 1) & 3)), so
 //     that the MFMA-layout reads, lane (r, h) <- piece 2 g + h of row r, fall on all banks.  Rows may start on any
 //     dword: these loads need no more (rows of an odd number of words went through registers once: 2947 x 6975 x 2624
-//     as packed bits 48.5 -> 39.2 us, 3318 x 778 x 3264, fp32, 12.3 -> 9.2, 2212 x 2496 x 1472 of 32-bit words 9.9 -> 8.7).
+//     as packed bits 48.5 -> 39.2 us, with a word a lane at its end 31.0; 3318 x 778 x 3264, fp32, 12.1 -> 9.2, 2212 x 2496 x 1472 of 32-bit words
+//     9.8 -> 8.9).
 //   - A wave owns its staging area and its range of K: no barrier in the main loop.  The words
 //     of a 64-byte segment are read into registers, the next segment's loads are issued into
 //     the same area once those reads have completed, and the 32 MFMAs of the segment run with
@@ -167,8 +168,7 @@ __device__ __forceinline__ void issue_segment(const Fp4Params& p, uint4* dst, co
                                               int piece0, int piece1, int seg, uint4* nx /* [NB - NA][2] */) {
   if constexpr (!CONV) {
     // (A and B are 16 bytes lower than the operands and voff 16 more, so that no offset is below zero, which would be one of 4 GB.
-    // One set of loads for all segments: with one of its own for a row's last, whose instructions nothing had fetched yet, 2752 x 1984 x
-    // 1408 took 9.0 us and not 8.1.)
+    // One set of loads for all segments: with one of its own for a row's last 2752 x 1984 x 1408 took 9.0 us and not 8.1.)
     const char* const abase = (const char*)p.A + (uint32_t)seg * 64u;
     const char* const bbase = (const char*)p.B + (uint32_t)seg * 64u;
     const uint32_t back[2] = {piece_back(seg, piece0, p.Kd), piece_back(seg, piece1, p.Kd)};

@@ -721,9 +721,9 @@ static void set_split(I8Params& p) {
 // 192 KB (1256 x 1024 x 366 of 2 x 2 bits, 147 KB less, 7.65 / 8.1 us).
 // (A band that is a row short leaves its XCDs idle for it: not where a CU then has a tile more than it would, which may be one more
 // than it holds at once: 1750 x 1472 x 552 of 2 x 8 bits 15.2 / 16.3 us.)
-// us a call in a graph, one band / as here: 753 x 128 x 4045 of 2 x 8 bits 15.2 / 9.5, 1129 x 64 x 4864 of 3 x 8 15.9 / 11.5, 1141 x 45 x 5376
-// of 2 x 4 11.1 / 8.6, 1833 x 343 x 2176 of 3 x 4 13.1 / 11.5; of some 130 drawn products with more than one 1.08 in the mean, 1.14 where an XCD
-// fetches 800 KB less.
+// us a call in a graph, three sets of inputs in turn, one band / as here: 1472 x 64 x 1361 of 8 x 2 bits 9.7 / 7.6, 1045 x 61 x 3520 of 8 x 1 13.8 /
+// 10.95, 922 x 53 x 5376 of 3 x 1 11.9 / 10.1, 1575 x 82 x 2944 of 3 x 8 14.6 / 12.45; of 160 drawn products with more than one 1.07 in the mean
+// (two bands 1.02, four 1.03, eight 1.12).
 static void set_tile_order(I8Params& p, int tile_rows, int tile_cols) {
   p.lg_bands = 0;
   p.band = p.tiles_m;

@@ -206,11 +206,13 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   // sixteen waves only few (200 x 300 x 30000 12.1 / 10.4); and 4096 tiles, where the results outweigh the rest.
   // From some hundred tiles of 64 x 64 on, where that kernel has work for most SIMDs (this one's time over its, 2100 products of 64 to 1100
   // tiles and 2 to 20 words, in a graph and as calls): packed bits from 352 (300 to 351 1.00, 0.98; 352 to 399 1.02, 1.00), of one step of K
-  // from 256 (200 to 255 1.09, 0.97; 256 to 319 1.11, 1.01); results of which all tiles are whole, stored without bounds, int32 from 400
-  // (350 to 399 1.02, 0.97; 400 to 447 1.02, 1.01), fp32 from 512 (0.97, 0.96; 512 to 599 1.04, 1.03); of which some are not, from 600, fp32 from 700,
-  // and of one step of K from 800 (int32 of 448 to 511 0.91, 0.90, 512 to 599 0.98, 0.96; 600 to 699 of one step 0.98, 0.95, of more 1.02,
-  // 1.03; fp32 0.90 to 0.96 there).  The choice is 0.5 % behind the better kernel, packed bits 0.8 % in a graph and 0.2 as calls; 1.7 and 2.2 %
-  // while int32 had 256 to 448, drawn before tiles side by side shared an XCD.  From 21 words on, where that kernel
+  // from 256 (200 to 255 1.09, 0.97; 256 to 319 1.11, 1.01); int32 and fp32 results by which tiles there are whole, stored without bounds.
+  // All: int32 from 400 (350 to 399 1.02, 0.97; 400 to 447 1.02, 1.01), fp32 and one step of K from 512 (fp32 448 to 511 0.97, 0.97; 512 to
+  // 599 1.06, 1.07; int32 of one step 400 to 447 0.93, 0.90, 512 to 599 1.04, 1.00).  All but the last rows': from 512 (int32 448 to 511
+  // 0.98, 0.97, 512 to 599 1.06, 1.06; fp32 0.93, 0.93, then 1.03, 1.03), of one step from 800 (int32 700 to 799 0.97, 0.96, 800 to 1023 1.04,
+  // 1.02).  Columns that end inside a tile: from 700 (int32 600 to 699 0.98, 0.97, 700 to 799 1.00, 1.00; fp32 0.95, 0.95, then 0.99, 0.99), of
+  // one step none (800 to 1023 0.93, 0.91).  The choice is 0.5 % behind the better kernel (0.9 % without the case of whole columns), packed bits
+  // 0.8 % in a graph and 0.2 as calls; 1.7 and 2.2 % while int32 had 256 to 448, drawn before tiles side by side shared an XCD.  From 21 words on, where that kernel
   // divides K over three waves or four, from 512 (652 x 2512 x 1472 as bits 6.9 / 6.4).
   const int64_t work = tiles * steps, tiles64 = ceil_div(M, 64) * ceil_div(N, 64);
   const bool apart = !((lda_bytes | ldb_bytes) & 15) && !(((uintptr_t)A | (uintptr_t)B) & 15);  // (launch_gemm_fp4)
@@ -218,11 +220,12 @@ bool launch_gemm_small(const void* A, int64_t lda_bytes, const void* B, int64_t 
   const int64_t most = steps > 64                                ? 2048
                        : !pays || (dwords <= 56 && tiles64 < 512) ? 12288
                                                                   : (tiles64 >= 128 && tiles64 < 256 ? 7000 : 8192);
-  const bool whole = M % 64 == 0 && N % 64 == 0;
+  const bool cols = N % 64 == 0, whole = cols && M % 64 == 0;
   const int64_t below = dwords > 40 ? 512
                       : C_bits      ? (steps == 1 ? 256 : 352)
-                      : whole       ? (C_f32 ? 512 : 400)
-                                    : (steps == 1 ? 800 : C_f32 ? 700 : 600);
+                      : whole       ? (C_f32 || steps == 1 ? 512 : 400)
+                      : cols        ? (steps == 1 ? 800 : 512)
+                                    : (steps == 1 ? lim : 700);
   // (Packed bits of rows of less than 16 bytes that the next begins in, whatever the size: gemm_fp4.hip does not take them, and gemm_mfma.hip, which
   // would, is behind.  us in a graph there / here: 3000 x 2001 x 64 14.4 / 8.3, 4096 x 4096 26.1 / 17.1, 60000 x 300 33.3 / 18.6, 8192 x 8192
   // 88.9 / 52.7; dword by dword through registers gemm_fp4_kernel once took 9.6, 17.3, 22.4 and 61.2.)
